@@ -47,6 +47,33 @@ __device__ __forceinline__ float block_sum(float x, float* red) {
   return s;
 }
 
+// Results that workgroups of one launch hand to the last of them.  publish() / collect() are agent-scope accesses, coherent
+// between the XCDs' caches one by one, so that no workgroup has to write back or invalidate its L2 (a device-wide fence in every
+// workgroup cost ~3 us of a 5 us kernel).
+__device__ __forceinline__ void publish(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double collect(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// Whether this workgroup is the last of `total` to get here, for every thread of it; the last one may collect() what the
+// others published before they came.  `ticket` starts at zero and is left at zero.
+__device__ __forceinline__ bool last_block(uint32_t* ticket, int total, int* s_last) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's published values have reached memory
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const bool last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)total - 1u;
+    if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_last = last ? 1 : 0;
+  }
+  __syncthreads();
+  return *s_last != 0;
+}
+
+// b^t for an integer t >= 0 by squaring: forty dependent multiplications at most, where pow() costs a microsecond or two
+__device__ __forceinline__ double ipow(double b, int64_t t) {
+  double r = 1.0;
+  for (; t > 0; t >>= 1, b *= b)
+    if (t & 1) r *= b;
+  return r;
+}
+
 // A non-GEMM parameter as the current pass sees it: theta[k] + s * v[k], with s = +-eps read from the device
 // (s_ptr == nullptr: the unperturbed parameter).
 struct ParamView {

@@ -105,15 +105,7 @@ __global__ __launch_bounds__(EW_THREADS) void k_adam(float* __restrict__ g, floa
   }
 }
 
-__global__ void k_step_scalars(int64_t* counters, int advance, float lr, float beta1, float beta2, float* step) {
-  const int64_t t = counters[0] + advance;
-  if (advance != 0) counters[0] = t;
-  if (t < 1) return;
-  const double c1 = 1.0 / (1.0 - pow((double)beta1, (double)t));
-  const double c2 = 1.0 / sqrt(1.0 - pow((double)beta2, (double)t));
-  step[0] = (float)((double)lr * c1); step[1] = (float)c2;
-  step[2] = (float)((double)lr * c1 * c2); step[3] = (float)c2;
-}
+__global__ void k_step_scalars(StepScalars s) { step_scalars(s); }
 
 // SGD: theta' = theta - lr b, b = mu b_prev + (g + wd theta) (heavy-ball momentum; b lives in `buf`, untouched when
 // mu = 0).  Also refreshes the bf16 working copy and its residual half over the first n16 elements.
@@ -147,11 +139,36 @@ __device__ __forceinline__ float adapt_one(float g, float m, float v, float gm, 
   return D * gm;
 }
 
+template <int N>
+__device__ __forceinline__ double block_tree_sum(double x, double* red) {   // N threads; the sum is for thread 0
+  red[threadIdx.x] = x;
+  __syncthreads();
+  for (int o = N / 2; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    __syncthreads();
+  }
+  return red[0];
+}
+// eps = alpha / ||v|| from the sum of squares: scalars[0] = eps, scalars[1] = ||v||.  A zero or non-finite norm gives
+// eps = 0 and raises status[0] = 1 (status is cleared to 0 otherwise), which turns the rest of the meta step into a no-op.
+__device__ __forceinline__ void finish_eps(double sum_sq, float alpha, float* __restrict__ scalars, int64_t* __restrict__ status) {
+  if (threadIdx.x != 0) return;
+  const double nrm = sqrt(sum_sq);
+  const bool ok = (nrm > 0.0) && (nrm < 1e300) && (nrm == nrm);
+  const float eps = ok ? (float)((double)alpha / nrm) : 0.f;
+  const bool ok2 = ok && eps > 0.f && eps < 3.0e38f;
+  scalars[0] = ok2 ? eps : 0.f;
+  scalars[1] = (float)nrm;
+  status[0] = ok2 ? 0 : 1;
+}
+
 __global__ __launch_bounds__(EW_THREADS) void k_adapt_norm(const float* __restrict__ g, const float* __restrict__ m,
                                                            const float* __restrict__ v, const float* __restrict__ gmeta,
                                                            float* __restrict__ vdir, double* __restrict__ partial,
-                                                           int64_t n, AdaptArgs a) {
+                                                           int64_t n, AdaptArgs a, EpsFinish fin) {
   __shared__ float red[16];
+  __shared__ double dred[EW_THREADS];
+  __shared__ int s_last;
   if (a.dev != nullptr) { a.lr_c1_c2 = a.dev[2]; a.c2 = a.dev[3]; }
   const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
   float acc = 0.f;
@@ -190,12 +207,14 @@ __global__ __launch_bounds__(EW_THREADS) void k_adapt_norm(const float* __restri
     acc = fmaf(o, o, acc);
   }
   const float s = block_sum(acc, red);
-  if (threadIdx.x == 0) partial[blockIdx.x] = (double)s;
+  if (threadIdx.x == 0) publish(partial + blockIdx.x, (double)s);
+  if (fin.ticket == nullptr || !last_block(fin.ticket, gridDim.x, &s_last)) return;
+  double d = 0.0;
+  for (int i = threadIdx.x; i < (int)gridDim.x; i += EW_THREADS) d += collect(partial + i);
+  finish_eps(block_tree_sum<EW_THREADS>(d, dred), fin.alpha, fin.scalars, fin.status);
 }
 
-// Second stage: fixed-order sum of the per-block partials in double, eps = alpha / ||v||.
-// scalars[0] = eps, scalars[1] = ||v||.  A zero or non-finite norm gives eps = 0 and raises status[0] = 1
-// (status is cleared to 0 otherwise), which turns the rest of the meta step into a no-op.
+// The second stage as a launch of its own: fixed-order sum of the per-block partials in double, then eps.
 __global__ __launch_bounds__(1024) void k_eps_from_partials(const double* __restrict__ partial, int nparts, float alpha,
                                                             float* __restrict__ scalars, int64_t* __restrict__ status) {
   __shared__ double red[1024];
@@ -205,21 +224,7 @@ __global__ __launch_bounds__(1024) void k_eps_from_partials(const double* __rest
     s0 += partial[i]; s1 += partial[i + 1024]; s2 += partial[i + 2048]; s3 += partial[i + 3072];
   }
   for (; i < nparts; i += 1024) s0 += partial[i];
-  red[threadIdx.x] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double nrm = sqrt(red[0]);
-    const bool ok = (nrm > 0.0) && (nrm < 1e300) && (nrm == nrm);
-    const float eps = ok ? (float)((double)alpha / nrm) : 0.f;
-    const bool ok2 = ok && eps > 0.f && eps < 3.0e38f;
-    scalars[0] = ok2 ? eps : 0.f;
-    scalars[1] = (float)nrm;
-    status[0] = ok2 ? 0 : 1;
-  }
+  finish_eps(block_tree_sum<1024>((s0 + s1) + (s2 + s3), red), alpha, scalars, status);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -390,12 +395,23 @@ __global__ __launch_bounds__(EW_THREADS) void k_fill_f32(float* __restrict__ p, 
 }
 
 __global__ __launch_bounds__(EW_THREADS) void k_copy_f32(float* __restrict__ dst, const float* __restrict__ src, int64_t n) {
-  const int64_t nv = n / EW_VEC;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride)
-    reinterpret_cast<float4*>(dst)[i] = reinterpret_cast<const float4*>(src)[i];
+  const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
+  for (int64_t base = (int64_t)blockIdx.x * EW_TRIP + threadIdx.x; base < nv; base += trip) {
+    f4 X[EW_U];
+#pragma unroll
+    for (int u = 0; u < EW_U; ++u)
+      if (base + u * EW_THREADS < nv) X[u] = ld_nt(src, base + u * EW_THREADS);
+#pragma unroll
+    for (int u = 0; u < EW_U; ++u)
+      if (base + u * EW_THREADS < nv) st_nt(dst, base + u * EW_THREADS, X[u]);
+  }
   const int64_t k = nv * EW_VEC + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k < n) dst[k] = src[k];
+}
+// the same for a pointer that is not 16-byte aligned
+__global__ __launch_bounds__(EW_THREADS) void k_copy_words(float* __restrict__ dst, const float* __restrict__ src, int64_t n) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) dst[k] = src[k];
 }
 
 __global__ __launch_bounds__(EW_THREADS) void k_to_bf16(bf16_t* __restrict__ dst, const float* __restrict__ src, int64_t n) {
@@ -419,9 +435,7 @@ void launch_adam(hipStream_t st, float* g, float* m, float* v, float* theta, bf1
   ProfScope ps(st, F_ADAM, 28.0 * n + (theta16 ? 2.0 * n16 : 0.0) + (a.lo ? 2.0 * n16 : 0.0));
   launch_kernel(ps, k_adam, ew_grid(n), EW_THREADS, 0, st, g, m, v, theta, theta16, n, n16, a);
 }
-void launch_step_scalars(hipStream_t st, int64_t* counters, int advance, float lr, float beta1, float beta2, float* step) {
-  k_step_scalars<<<1, 1, 0, st>>>(counters, advance, lr, beta1, beta2, step);
-}
+void launch_step_scalars(hipStream_t st, const StepScalars& s) { k_step_scalars<<<1, 1, 0, st>>>(s); }
 void launch_sgd(hipStream_t st, float* g, float* buf, float* theta, bf16_t* theta16, bf16_t* lo, int64_t n, int64_t n16,
                 float lr, float wd, float mu) {
   if (n <= 0) return;
@@ -431,16 +445,19 @@ void launch_adapt_norm(hipStream_t st, const float* g, const float* m, const flo
                        double* partial, int64_t n, const AdaptArgs& a, float alpha, float* scalars, int64_t* status) {
   const int grid = ew_grid(n);
   ProfScope ps(st, F_ADAPT_NORM, (a.mode == 0 ? 20.0 : 8.0) * n);
-  launch_kernel(ps, k_adapt_norm, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a);
+  launch_kernel(ps, k_adapt_norm, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a, EpsFinish{});
   k_eps_from_partials<<<1, 1024, 0, st>>>(partial, grid, alpha, scalars, status);
 }
 int launch_adapt_slice(hipStream_t st, const float* g, const float* m, const float* v, const float* gmeta, float* vdir,
-                       double* partial, int64_t n, const AdaptArgs& a, int max_blocks) {
+                       double* partial, int64_t n, const AdaptArgs& a, int max_blocks, const EpsFinish& fin, bool* finished) {
   if (n <= 0) return 0;
   int grid = ew_grid(n);
   if (grid > max_blocks) grid = max_blocks;
+  // every block takes a ticket: worth a launch saved while there are few of them
+  const bool here = fin.ticket != nullptr && grid <= 512;
+  if (finished != nullptr) *finished = here;
   ProfScope ps(st, F_ADAPT_NORM, (a.mode == 0 ? 20.0 : 8.0) * n);
-  launch_kernel(ps, k_adapt_norm, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a);
+  launch_kernel(ps, k_adapt_norm, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a, here ? fin : EpsFinish{});
   return grid;
 }
 void launch_eps_from_partials(hipStream_t st, const double* partial, int count, float alpha, float* scalars, int64_t* status) {
@@ -482,7 +499,8 @@ void launch_fill_f32(hipStream_t st, float* p, float val, int64_t n) {
 }
 void launch_copy_f32(hipStream_t st, float* dst, const float* src, int64_t n) {
   if (n <= 0) return;
-  k_copy_f32<<<ew_grid(n), EW_THREADS, 0, st>>>(dst, src, n);
+  if ((((uintptr_t)dst | (uintptr_t)src) & 15) == 0) k_copy_f32<<<ew_grid(n), EW_THREADS, 0, st>>>(dst, src, n);
+  else k_copy_words<<<ew_grid(n), EW_THREADS, 0, st>>>(dst, src, n);
 }
 void launch_to_bf16(hipStream_t st, bf16_t* dst, const float* src, int64_t n) {
   if (n <= 0) return;

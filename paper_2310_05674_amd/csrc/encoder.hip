@@ -90,8 +90,8 @@ class EncoderModel : public Model {
   }
 
   // nw = 1: one pass with weights w[0].  nw = 2: the theta + eps v and theta - eps v passes of Eq. 5 on the same
-  // batch, stacked along the row dimension (forward only, keep must be false); logits [nw B x C].
-  void run_forward(hipStream_t st, const PassWeights* w, int nw, const sama_batch& b, bool keep, float* logits) {
+  // batch, stacked along the row dimension (forward only, keep must be false).
+  HeadView run_forward(hipStream_t st, const PassWeights* w, int nw, const sama_batch& b, bool keep) {
     const int B = b.n, M = B * S_, R = nw * M;
     ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};
     LnFwdArgs e{};
@@ -126,16 +126,19 @@ class EncoderModel : public Model {
       n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = R; n2.d = d_;
       launch_ln_fwd(st, n2);
     }
-    pv.flip_row = nw == 2 ? B : 0;                  // the head's rows are samples
-    launch_head_fwd(st, res_[0], S_, d_, nw * B, C_, pv, wc_, bc_, logits);   // res_[0] = fp32 output of the last LayerNorm
+    HeadView h{};                                   // position 0 of the fp32 output of the last LayerNorm
+    h.x = res_[0]; h.stride = (int64_t)S_ * d_; h.pass_stride = (int64_t)M * d_; h.k = d_;
+    h.pv = ParamView{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, 0};
+    h.w_off = wc_; h.b_off = bc_;
+    return h;
   }
 
-  void forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep, float* logits) override {
-    run_forward(st, &w, 1, b, keep, logits);
+  HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep) override {
+    return run_forward(st, &w, 1, b, keep);
   }
-  void forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b, float* logits) override {
+  HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b) override {
     const PassWeights w[2] = {wp, wm};
-    run_forward(st, w, 2, b, false, logits);
+    return run_forward(st, w, 2, b, false);
   }
 
   void mlm_forward(hipStream_t st, const PassWeights* w, int nw, int pass_rows, bool kept, const MlmBatch& mb,

@@ -1,6 +1,6 @@
 // Non-GEMM pieces of the post-LN encoder base learner (Sec. 4.1 uses BERT / RoBERTa-shaped models):
 // embedding gather + LayerNorm, LayerNorm forward / backward, fused attention forward / backward on the matrix
-// cores, classifier head, column sums, embedding gradients.  All reductions run in a fixed order.
+// cores, classifier head backward, column sums, embedding gradients.  All reductions run in a fixed order.
 #include "common.h"
 #include "kernels.h"
 
@@ -515,19 +515,6 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
 }
 
 // =========================================================================================== classifier head
-__global__ __launch_bounds__(256) void k_head_fwd(const float* __restrict__ x, int S, int d, int B, int C, ParamView pv,
-                                                  int64_t wc_off, int64_t bc_off, float* __restrict__ logits) {
-  const int lane = threadIdx.x & 63, idx = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (idx >= B * C) return;
-  const int b = idx / C, c = idx - b * C;
-  const float sc = pv.scale_row(b);
-  const float* xr = x + (int64_t)b * S * d;
-  float acc = 0.f;
-  for (int k = lane; k < d; k += 64) acc = fmaf(xr[k], pv.at(wc_off + (int64_t)c * d + k, sc), acc);
-  acc = wave_sum(acc);
-  if (lane == 0) logits[idx] = acc + pv.at(bc_off + c, sc);
-}
-
 __global__ __launch_bounds__(256) void k_head_bwd_w(const float* __restrict__ x, int S, int d, int B, int C,
                                                     const float* __restrict__ dlogits, float* __restrict__ gWc, float* __restrict__ gbc) {
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -702,11 +689,6 @@ void launch_attention_bwd(hipStream_t st, const bf16_t* qkv, const bf16_t* out, 
       break;
     default: break;
   }
-}
-void launch_head_fwd(hipStream_t st, const float* x, int S, int d, int B, int C, ParamView pv, int64_t wc_off, int64_t bc_off,
-                     float* logits) {
-  ProfScope ps(st, F_OTHER, 0.0);
-  launch_kernel(ps, k_head_fwd, (B * C + 3) / 4, 256, 0, st, x, S, d, B, C, pv, wc_off, bc_off, logits);
 }
 void launch_head_bwd(hipStream_t st, const float* x, int S, int d, int B, int C, const float* theta, int64_t wc_off,
                      int64_t bc_off, const float* dlogits, float* grad, float* dx) {

@@ -85,8 +85,19 @@ struct AdaptArgs {
 };
 // The step-dependent scalars of Adam and of its adaptation, kept on the device so that a captured sequence of launches
 // stays valid from replay to replay: t = (counters[0] += advance); step[0..3] = {lr / (1 - beta1^t),
-// 1 / sqrt(1 - beta2^t), lr c1 c2, c2} in double arithmetic (left alone while t < 1).
-void launch_step_scalars(hipStream_t, int64_t* counters, int advance, float lr, float beta1, float beta2, float* step);
+// 1 / sqrt(1 - beta2^t), lr c1 c2, c2} in double arithmetic (left alone while t < 1).  A base step advances them in its
+// per-sample stage; launch_step_scalars is the form on its own.
+struct StepScalars { int64_t* counters; int advance; float lr, beta1, beta2; float* step; };
+__device__ __forceinline__ void step_scalars(const StepScalars& s) {
+  const int64_t t = s.counters[0] + s.advance;
+  if (s.advance != 0) s.counters[0] = t;
+  if (t < 1) return;
+  const double c1 = 1.0 / (1.0 - ipow((double)s.beta1, t));
+  const double c2 = 1.0 / sqrt(1.0 - ipow((double)s.beta2, t));
+  s.step[0] = (float)((double)s.lr * c1); s.step[1] = (float)c2;
+  s.step[2] = (float)((double)s.lr * c1 * c2); s.step[3] = (float)c2;
+}
+void launch_step_scalars(hipStream_t, const StepScalars&);
 // With a non-zero weight decay the L2 term is added to g in place (g then is the gradient the solver was given).
 void launch_adam(hipStream_t, float* g, float* m, float* v, float* theta, bf16_t* theta16, int64_t n, int64_t n16,
                  const AdamArgs&);
@@ -99,8 +110,12 @@ void launch_adapt_norm(hipStream_t, const float* g, const float* m, const float*
                        int64_t* status);
 // The same in pieces: v = D . gmeta over one range, its per-block sums of squares into partial[0 .. returned count)
 // (at most max_blocks), and, once every range is done, eps and the status word from all the partials in index order.
+// A range that is the only one may be given `fin` (a ticket as in last_block): if it is small enough its last block also
+// does the second step, which *finished tells.
+struct EpsFinish { float alpha; float* scalars; int64_t* status; uint32_t* ticket; };
 int launch_adapt_slice(hipStream_t, const float* g, const float* m, const float* v, const float* gmeta, float* vdir,
-                       double* partial, int64_t n, const AdaptArgs&, int max_blocks);
+                       double* partial, int64_t n, const AdaptArgs&, int max_blocks, const EpsFinish& fin = EpsFinish{},
+                       bool* finished = nullptr);
 void launch_eps_from_partials(hipStream_t, const double* partial, int count, float alpha, float* scalars, int64_t* status);
 void launch_perturb_lo(hipStream_t, const float* theta, const float* vdir, const float* eps_ptr, bf16_t* lo_p,
                        bf16_t* lo_m, int64_t n16);
@@ -124,29 +139,11 @@ void launch_fill_i64x4(hipStream_t, int64_t* p, int64_t a, int64_t b, int64_t c,
 
 // ------------------------------------------------------------------ per-sample stage (sample_stage.hip)
 enum { STAGE_BASE = 0, STAGE_META = 1, STAGE_GLAM = 2, STAGE_EVAL = 3 };   // EVAL: BASE's losses and weights only
-struct SampleStageArgs {
-  const float* logits;  // [B x C], row stride ld
-  int ld, C, B, H, mode;
-  const int32_t* y;
-  const uint8_t* mask;  // may be null
-  const float* lambda;  // [3H+1] weighting net, then the corrector [Hc*2C + Hc + C*Hc + C] when Hc > 0
-  int Hc; float kappa;  // label corrector (BASE and GLAM): Hc = 0 turns it off
-  double* corr_scratch; // [B x 2C] device scratch of the corrector's backward (GLAM with Hc > 0)
-  float* losses;        // [B] out (may be null in EVAL)
-  float* weights;       // [B] out, w(l_i; lambda), or null
-  float* dlogits;       // [B x C] out, row stride C (BASE, META)
-  float* loss_scalar;   // out: sum_i coef_i l_i
-  float* loss_user;     // optional second destination
-  double* glam;         // [n_lambda] out (GLAM), same layout as lambda
-  // Sequence mode (pos_loss != null; BASE or GLAM): sample i is sequence i of B, its loss the mean of pos_loss[j] over
-  // the positions with pos_row[j] / S == i (0 without any); logits, y, dlogits are unused.  BASE writes
-  // pos_coef[j] = mask_i w_i / (B_eff count_i) and ADDS sum_i coef_i l_i to *loss_scalar (and *loss_user).
-  const float* pos_loss; const int32_t* pos_row; int n_pos, S;
-  float* pos_coef;
-};
-void launch_sample_stage(hipStream_t, const SampleStageArgs&);
+constexpr int STAGE_MAX_BLOCKS = 64;
+int stage_blocks(int B);   // most workgroups a stage over B samples uses per pass (the number of its partials)
+// h from the two lambda-gradients (Eq. 5) and, with do_update, Adam on lambda
 struct MetaUpdateArgs {
-  const double* glam_p; const double* glam_m;
+  double* glam_p; double* glam_m;   // [nl] out: the two lambda-gradients
   const float* scalars;   // [0] = eps
   int64_t* counters;      // [1] = meta step count, [2] = status
   float* hypergrad;       // [nl] out
@@ -157,7 +154,39 @@ struct MetaUpdateArgs {
   int nl, do_update;
   float lr, beta1, beta2, eps;
 };
-void launch_meta_update(hipStream_t, const MetaUpdateArgs&);
+// The classifier: logits[i][c] = x[i * stride + :] . W[c] + b[c], W and b inside theta, contraction over k features.  The
+// second pass of Eq. 5 reads its features pass_stride behind and sees the opposite perturbation.
+struct HeadView {
+  const float* x; int64_t stride, pass_stride;
+  int k;
+  ParamView pv; int64_t w_off, b_off;
+};
+struct SampleStageArgs {
+  HeadView head;
+  int C, B, H, mode;
+  float* logits;        // [B x C] out, or null
+  const int32_t* y;
+  const uint8_t* mask;  // may be null
+  const float* lambda;  // [3H+1] weighting net, then the corrector [Hc*2C + Hc + C*Hc + C] when Hc > 0
+  int Hc; float kappa;  // label corrector (BASE and GLAM): Hc = 0 turns it off
+  float* losses;        // [B] out (may be null in EVAL)
+  float* weights;       // [B] out, w(l_i; lambda), or null
+  float* dlogits;       // [B x C] out, row stride C (BASE, META)
+  float* loss_scalar;   // out: sum_i coef_i l_i
+  float* loss_user;     // optional second destination
+  // GLAM: both passes of Eq. 5 in one launch, then the combine and the update of `mu` (which may write `lambda`)
+  MetaUpdateArgs mu;
+  double* part;         // partials: 2 * stage_blocks(B) * n_lambda (GLAM), stage_blocks(B) (BASE, META)
+  uint32_t* ticket;     // zero; zero again after the launch
+  StepScalars step;     // counters != null: also advances the base solver's step-dependent scalars
+  // Sequence mode (pos_loss != null; BASE or GLAM): sample i is sequence i of B, its loss the mean of pos_loss[j] over
+  // the positions with pos_row[j] / S == i (0 without any); head, y, dlogits are unused.  The - pass of GLAM reads pos_loss
+  // pos_pass_stride behind the + pass.  BASE writes
+  // pos_coef[j] = mask_i w_i / (B_eff count_i) and ADDS sum_i coef_i l_i to *loss_scalar (and *loss_user).
+  const float* pos_loss; const int32_t* pos_row; int n_pos, S; int64_t pos_pass_stride;
+  float* pos_coef;
+};
+void launch_sample_stage(hipStream_t, const SampleStageArgs&);
 
 // ------------------------------------------------------------------ fp32 GEMM (gemm_f32.hip)
 // C[M x N] = sum_k A(i,k) B(k,j), A(i,k) = A[i*sa_i + k*sa_k], B(k,j) = Bh[k*sb_k + j*sb_j] (+ bscale * Bv[same]),
@@ -171,10 +200,11 @@ struct GemmF32Args {
   const float* bias; const float* bias_v;  // null = no bias; perturbed with the same bscale
   const float* gate;                       // null = none
   int relu;
+  float* rowsum;                           // null, or [M] out: rowsum[i] = sum_k A(i,k) (the bias gradient beside a weight gradient)
 };
-void launch_gemm_f32(hipStream_t, const GemmF32Args&);
-// out[j] = sum_i X[i*ld + j], fixed order.
-void launch_colsum_f32(hipStream_t, const float* X, int64_t ld, int M, int N, float* out);
+constexpr int GEMM_F32_MAX_JOBS = 2;
+// one or two independent problems in one launch
+void launch_gemm_f32_batch(hipStream_t, const GemmF32Args* p, int count);
 
 // ------------------------------------------------------------------ bf16 MFMA GEMM (gemm_bf16.hip)
 enum { GEMM_ACT_NONE = 0, GEMM_ACT_GELU_FWD = 1, GEMM_ACT_GELU_BWD = 2 };
@@ -245,9 +275,6 @@ void launch_attention_fwd(hipStream_t, const bf16_t* qkv, bf16_t* out, float* ls
                           const int32_t* lens, int lens_period);
 void launch_attention_bwd(hipStream_t, const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, const float* lse,
                           bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, int lens_period);
-// classifier on the position-0 hidden state: logits[b][c] = x[b*S] . Wc[c] + bc[c]
-void launch_head_fwd(hipStream_t, const float* x, int S, int d, int B, int C, ParamView pv, int64_t wc_off, int64_t bc_off,
-                     float* logits);
 // dWc, dbc into grad; dx[b*S][:] = dlogits[b] . Wc written into the zero-filled dx [B*S x d]
 void launch_head_bwd(hipStream_t, const float* x, int S, int d, int B, int C, const float* theta, int64_t wc_off,
                      int64_t bc_off, const float* dlogits, float* grad, float* dx);

@@ -7,6 +7,7 @@
 #include <vector>
 #include "../../include/sama.h"
 #include "common.h"
+#include "kernels.h"
 
 namespace sama {
 
@@ -72,14 +73,10 @@ class Model {
   void set_grad_sink(GradSink* s) { sink_ = s; }   // for the next backward() / backward_mlm(); null = none
   // carve activation buffers for batches up to max_b
   virtual void plan(BumpAlloc& ws, int max_b) = 0;
-  // logits[B x C] (fp32, row stride C) for batch `b`; keep = retain what backward needs
-  virtual void forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep, float* logits) = 0;
-  // The theta + eps v and theta - eps v passes of Eq. 5 on the same batch, forward only: logits [2B x C], the + pass
-  // first.  Models that gain from it run the two passes stacked in the same launches.
-  virtual void forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b, float* logits) {
-    forward(st, wp, b, false, logits);
-    forward(st, wm, b, false, logits + (size_t)b.n * n_classes());
-  }
+  // everything up to the classifier for batch `b`; keep = retain what backward needs.  The result says where the features are.
+  virtual HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep) = 0;
+  // The theta + eps v and theta - eps v passes of Eq. 5 on the same batch, forward only, stacked in the same launches.
+  virtual HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b) = 0;
   // grad[n] = d/dtheta sum_i sum_c dlogits[i][c] z_ic, at the unperturbed theta of the last keep=true forward
   virtual void backward(hipStream_t st, const PassWeights& w, const sama_batch& b, const float* dlogits, float* grad) = 0;
   virtual int n_classes() const = 0;

@@ -68,11 +68,12 @@ struct sama_ctx {
   float *theta, *m, *v, *g, *gmeta, *vdir;
   bf16_t *theta16, *lo_0, *lo_p, *lo_m;   // bf16 working copy; residual half of the current theta; halves of theta +- eps v
   float *lambda, *meta_m, *meta_v, *hyper, *glam_p32, *glam_m32;
-  double *glam_p, *glam_m, *partial, *corr_scratch;
+  double *glam_p, *glam_m, *partial, *stage_part;   // stage_part: per-workgroup partials of the per-sample stage
+  uint32_t* ticket;   // {per-sample stage, adaptation}: workgroups that have finished (zero between launches)
   float* scalars;     // {eps, ||v||, L_base, L_meta}
   float* step;        // step-dependent optimizer scalars (launch_step_scalars)
   int64_t* counters;  // {t (mirror), meta_t, status, 0}
-  float *logits, *dlogits, *losses;
+  float *dlogits, *losses;
   // auxiliary task: concatenated [ft | pt] batch, per-position losses (two stacked passes) and coefficients
   int32_t *ids_cat, *y_cat, *len_cat; uint8_t* mask_cat; float *loss_pos, *coef_pos;
   int64_t t;  // base step count (host)
@@ -143,13 +144,13 @@ static size_t carve(sama_ctx* c, void* base) {
   c->partial = ws.take<double>(EW_MAX_BLOCKS);
   c->scalars = ws.take<float>(4);
   c->step = ws.take<float>(8);
+  c->ticket = ws.take<uint32_t>(2);
   c->counters = ws.take<int64_t>(4);
   const int mb = max_rows(c->cfg);
   const int C = c->cfg.dims[c->cfg.n_dims - 1];
-  c->logits = ws.take<float>((size_t)2 * mb * C);   // room for the stacked + and - passes
   c->dlogits = ws.take<float>((size_t)mb * C);
   c->losses = ws.take<float>(mb);
-  c->corr_scratch = c->cfg.corr_hidden > 0 ? ws.take<double>((size_t)c->cfg.max_batch * 2 * C) : nullptr;
+  c->stage_part = ws.take<double>((size_t)2 * stage_blocks(mb) * nl);
   if (c->cfg.aux_mlm) {
     const size_t P = (size_t)(c->cfg.max_aux_masked + 63) / 64 * 64;
     c->ids_cat = ws.take<int32_t>((size_t)mb * c->cfg.dims[4]); c->y_cat = ws.take<int32_t>(mb); c->len_cat = ws.take<int32_t>(mb); c->mask_cat = ws.take<uint8_t>(mb);
@@ -236,7 +237,7 @@ static void base_update_rest(sama_ctx* c, UpdateSink& sink) {
     pos = r.first + r.second;
   }
   if (pos < c->n) base_update_range(c, st, sink.t, pos, c->n - pos);
-  c->t = sink.t;   // the device's counter was advanced by launch_step_scalars at the start of the step
+  c->t = sink.t;   // the device's counter was advanced by the step's per-sample stage
   c->lr_step = c->cfg.base_lr;
 }
 
@@ -321,6 +322,7 @@ sama_status sama_init(const sama_config* cfg, void* workspace, size_t workspace_
   launch_fill_f32(st, c->hyper, 0.f, c->nl); launch_fill_f32(st, c->glam_p32, 0.f, c->nl); launch_fill_f32(st, c->glam_m32, 0.f, c->nl);
   launch_fill_f32(st, c->scalars, 0.f, 4);
   launch_fill_f32(st, c->step, 0.f, 8);
+  launch_fill_f32(st, (float*)c->ticket, 0.f, 2);
   launch_fill_i64x4(st, c->counters, 0, 0, 0, 0, 15);
   if (c->bf16) { launch_to_bf16(st, c->theta16, c->theta, c->n_gemm); launch_residual_lo(st, c->theta, c->lo_0, c->n_gemm); }
   sama_status s = check_hip(nullptr, "sama_init");
@@ -341,19 +343,33 @@ static PassWeights pass_weights(sama_ctx* c, float sign, const bf16_t* lo) {
 // the base step's (and the forward-only evaluation's) view
 static PassWeights base_weights(sama_ctx* c) { return pass_weights(c, 0.f, (c->bf16 && !c->cfg.fast_base_pass) ? c->lo_0 : nullptr); }
 
+static SampleStageArgs stage_args(sama_ctx* c, int mode, int B) {
+  SampleStageArgs sa{};
+  sa.mode = mode; sa.B = B; sa.H = c->cfg.wnet_hidden; sa.lambda = c->lambda;
+  sa.part = c->stage_part; sa.ticket = c->ticket;
+  return sa;
+}
+// a stage over the classifier's logits of batch b
+static SampleStageArgs class_stage_args(sama_ctx* c, int mode, const sama_batch* b, const HeadView& head) {
+  SampleStageArgs sa = stage_args(c, mode, b->n);
+  sa.head = head; sa.C = c->model->n_classes(); sa.y = b->y; sa.mask = b->sample_mask;
+  sa.Hc = c->cfg.corr_hidden; sa.kappa = c->cfg.corr_kappa; sa.losses = c->losses; sa.dlogits = c->dlogits;
+  return sa;
+}
+static StepScalars next_step(sama_ctx* c) {
+  return StepScalars{c->counters, 1, c->cfg.base_lr, c->cfg.beta1, c->cfg.beta2, c->step};
+}
+
 sama_status sama_base_step(sama_ctx* c, const sama_batch* train, float* loss_out) {
   if (!c) return SAMA_EINVAL;
   sama_status s = check_batch(c, train, c->cfg.max_batch, "train");
   if (s != SAMA_OK) return s;
   hipStream_t st = c->stream;
   (void)hipGetLastError();
-  launch_step_scalars(st, c->counters, 1, c->cfg.base_lr, c->cfg.beta1, c->cfg.beta2, c->step);
   const PassWeights w = base_weights(c);
-  c->model->forward(st, w, *train, true, c->logits);
-  SampleStageArgs sa{};
-  sa.logits = c->logits; sa.ld = c->model->n_classes(); sa.C = sa.ld; sa.B = train->n; sa.H = c->cfg.wnet_hidden;
-  sa.mode = STAGE_BASE; sa.Hc = c->cfg.corr_hidden; sa.kappa = c->cfg.corr_kappa; sa.y = train->y; sa.mask = train->sample_mask; sa.lambda = c->lambda;
-  sa.losses = c->losses; sa.dlogits = c->dlogits; sa.loss_scalar = c->scalars + 2; sa.loss_user = loss_out;
+  const HeadView head = c->model->forward(st, w, *train, true);
+  SampleStageArgs sa = class_stage_args(c, STAGE_BASE, train, head);
+  sa.loss_scalar = c->scalars + 2; sa.loss_user = loss_out; sa.step = next_step(c);
   launch_sample_stage(st, sa);
   UpdateSink sink(c, c->t + 1);
   c->model->set_grad_sink(&sink);
@@ -371,15 +387,9 @@ sama_status sama_eval(sama_ctx* c, const sama_batch* batch, float* logits_out, f
   hipStream_t st = c->stream;
   (void)hipGetLastError();
   const PassWeights w = base_weights(c);
-  float* logits = logits_out != nullptr ? logits_out : c->logits;
-  c->model->forward(st, w, *batch, false, logits);
-  if (losses_out != nullptr || weights_out != nullptr) {
-    SampleStageArgs sa{};
-    sa.logits = logits; sa.ld = c->model->n_classes(); sa.C = sa.ld; sa.B = batch->n; sa.H = c->cfg.wnet_hidden;
-    sa.mode = STAGE_EVAL; sa.Hc = c->cfg.corr_hidden; sa.kappa = c->cfg.corr_kappa; sa.y = batch->y; sa.mask = nullptr;
-    sa.lambda = c->lambda; sa.losses = losses_out; sa.weights = weights_out;
-    launch_sample_stage(st, sa);
-  }
+  SampleStageArgs sa = class_stage_args(c, STAGE_EVAL, batch, c->model->forward(st, w, *batch, false));
+  sa.logits = logits_out; sa.mask = nullptr; sa.losses = losses_out; sa.weights = weights_out;
+  launch_sample_stage(st, sa);
   return check_hip(c, "sama_eval");
 }
 
@@ -389,13 +399,9 @@ sama_status sama_eval(sama_ctx* c, const sama_batch* batch, float* logits_out, f
 static bool meta_direction(sama_ctx* c, const sama_batch* meta, bool update) {
   hipStream_t st = c->stream;
   const sama_config& f = c->cfg;
-  const int C = c->model->n_classes();
   // hi + lo of the master weights: the gradient is taken at theta, not bf16(theta)
   const PassWeights w0 = pass_weights(c, 0.f, (c->bf16 && !f.fast_meta_pass) ? c->lo_0 : nullptr);
-  c->model->forward(st, w0, *meta, true, c->logits);
-  SampleStageArgs sa{};
-  sa.logits = c->logits; sa.ld = C; sa.C = C; sa.B = meta->n; sa.H = f.wnet_hidden; sa.mode = STAGE_META;
-  sa.y = meta->y; sa.mask = meta->sample_mask; sa.lambda = c->lambda; sa.losses = c->losses; sa.dlogits = c->dlogits;
+  SampleStageArgs sa = class_stage_args(c, STAGE_META, meta, c->model->forward(st, w0, *meta, true));
   sa.loss_scalar = c->scalars + 3;
   launch_sample_stage(st, sa);
   AdaptArgs ad{};
@@ -414,15 +420,21 @@ static bool meta_direction(sama_ctx* c, const sama_batch* meta, bool update) {
   c->model->backward(st, w0, *meta, c->dlogits, c->gmeta);
   c->model->set_grad_sink(nullptr);
   std::sort(sink.done.begin(), sink.done.end());
+  bool finished = false;   // eps by the last workgroup of the one launch there is
   {
     std::vector<std::pair<int64_t, int64_t>> gaps;
     int64_t pos = 0;
     for (auto& r : sink.done) { if (r.first > pos) gaps.push_back({pos, r.first - pos}); pos = r.first + r.second; }
     if (pos < c->n) gaps.push_back({pos, c->n - pos});
     const int per_gap = gaps.empty() ? 0 : (EW_MAX_BLOCKS - sink.used) / (int)gaps.size();
-    for (auto& r : gaps) sink.slice(st, r.first, r.second, per_gap);
+    if (sink.used == 0 && gaps.size() == 1) {
+      const EpsFinish fin{f.alpha, c->scalars, c->counters + 2, c->ticket + 1};
+      sink.used = launch_adapt_slice(st, c->g, c->m, c->v, c->gmeta, c->vdir, c->partial, c->n, ad, per_gap, fin, &finished);
+    } else {
+      for (auto& r : gaps) sink.slice(st, r.first, r.second, per_gap);
+    }
   }
-  launch_eps_from_partials(st, c->partial, sink.used, f.alpha, c->scalars, c->counters + 2);
+  if (!finished) launch_eps_from_partials(st, c->partial, sink.used, f.alpha, c->scalars, c->counters + 2);
   // A step that is applied nudges the GEMM block of theta in the same pass that writes the low halves; the non-GEMM
   // tail is nudged after the two passes, which read it as theta +- eps v.
   const bool fused_nudge = update && c->bf16 && c->n_gemm % 4 == 0;
@@ -432,9 +444,8 @@ static bool meta_direction(sama_ctx* c, const sama_batch* meta, bool update) {
   return fused_nudge;
 }
 
-// Second half: h from the two lambda-gradients (Eq. 5), Adam on lambda and the nudge of theta when `update`.
-static void meta_finish(sama_ctx* c, float* hyper_out, float* eps_out, bool update, bool fused_nudge) {
-  hipStream_t st = c->stream;
+// What the stage of the two passes does with their lambda-gradients: h (Eq. 5), and Adam on lambda when `update`.
+static MetaUpdateArgs meta_update_args(sama_ctx* c, float* hyper_out, float* eps_out, bool update) {
   const sama_config& f = c->cfg;
   MetaUpdateArgs mu{};
   mu.glam_p = c->glam_p; mu.glam_m = c->glam_m; mu.scalars = c->scalars; mu.counters = c->counters;
@@ -442,13 +453,17 @@ static void meta_finish(sama_ctx* c, float* hyper_out, float* eps_out, bool upda
   mu.glam_p_f32 = c->glam_p32; mu.glam_m_f32 = c->glam_m32;
   mu.lambda = c->lambda; mu.meta_m = c->meta_m; mu.meta_v = c->meta_v; mu.nl = c->nl; mu.do_update = update ? 1 : 0;
   mu.lr = f.meta_lr; mu.beta1 = f.meta_beta1; mu.beta2 = f.meta_beta2; mu.eps = f.meta_eps;
-  launch_meta_update(st, mu);
+  return mu;
+}
+// The nudge of theta at the end of an applied step.
+static void meta_nudge(sama_ctx* c, bool fused_nudge) {
+  hipStream_t st = c->stream;
   // a hypergradient that is not finite skips the step (status word): the tail is then left alone and the GEMM block's
   // early nudge is taken back
-  if (update && fused_nudge) {
+  if (fused_nudge) {
     launch_unnudge(st, c->theta, c->vdir, c->scalars, c->counters + 2, c->theta16, c->lo_0, c->n_gemm);
     launch_nudge(st, c->theta + c->n_gemm, c->vdir + c->n_gemm, c->scalars, c->counters + 2, nullptr, nullptr, c->n - c->n_gemm, 0);
-  } else if (update) {
+  } else {
     launch_nudge(st, c->theta, c->vdir, c->scalars, c->counters + 2, c->theta16, c->lo_0, c->n, c->n_gemm);
   }
 }
@@ -463,20 +478,13 @@ static sama_status meta_common(sama_ctx* c, const sama_batch* train, const sama_
   if (c->t < 1) return fail(c, SAMA_ESTATE, "meta gradient requested before any sama_base_step");
   hipStream_t st = c->stream;
   (void)hipGetLastError();
-  const sama_config& f = c->cfg;
-  const int C = c->model->n_classes();
   const bool fused_nudge = meta_direction(c, meta, update);
   // passes 2 and 3: dL_base/dlambda at theta +- eps v; forward only, then the weight net's backward
-  c->model->forward_pair(st, pass_weights(c, 1.f, c->lo_p), pass_weights(c, -1.f, fused_nudge ? c->lo_0 : c->lo_m), *train, c->logits);
-  for (int pass = 0; pass < 2; ++pass) {
-    SampleStageArgs sg{};
-    sg.logits = c->logits + (size_t)pass * train->n * C; sg.ld = C; sg.C = C; sg.B = train->n; sg.H = f.wnet_hidden; sg.mode = STAGE_GLAM;
-    sg.Hc = f.corr_hidden; sg.kappa = f.corr_kappa; sg.corr_scratch = c->corr_scratch;
-    sg.y = train->y; sg.mask = train->sample_mask; sg.lambda = c->lambda; sg.losses = c->losses;
-    sg.glam = pass == 0 ? c->glam_p : c->glam_m;
-    launch_sample_stage(st, sg);
-  }
-  meta_finish(c, hyper_out, eps_out, update, fused_nudge);
+  const HeadView head = c->model->forward_pair(st, pass_weights(c, 1.f, c->lo_p), pass_weights(c, -1.f, fused_nudge ? c->lo_0 : c->lo_m), *train);
+  SampleStageArgs sg = class_stage_args(c, STAGE_GLAM, train, head);
+  sg.mu = meta_update_args(c, hyper_out, eps_out, update);
+  launch_sample_stage(st, sg);
+  if (update) meta_nudge(c, fused_nudge);
   return check_hip(c, update ? "sama_meta_step" : "sama_meta_grad");
 }
 
@@ -490,14 +498,12 @@ static sama_status check_aux(sama_ctx* c, const sama_aux_batch* pt) {
   return SAMA_OK;
 }
 
-// the sequence-mode stage on the masked-token losses of one pass
-static void aux_stage(sama_ctx* c, const sama_aux_batch* pt, int mode, const float* loss_pos, float* losses, double* glam,
-                      float* loss_user) {
-  SampleStageArgs sa{};
-  sa.B = pt->n_seq; sa.H = c->cfg.wnet_hidden; sa.mode = mode; sa.lambda = c->lambda; sa.losses = losses;
-  sa.pos_loss = loss_pos; sa.pos_row = pt->mask_row; sa.n_pos = pt->n_mask; sa.S = c->cfg.dims[4];
-  sa.pos_coef = c->coef_pos; sa.loss_scalar = c->scalars + 2; sa.loss_user = loss_user; sa.glam = glam;
-  launch_sample_stage(c->stream, sa);
+// a stage over the masked-token losses
+static SampleStageArgs aux_stage_args(sama_ctx* c, const sama_aux_batch* pt, int mode, float* losses) {
+  SampleStageArgs sa = stage_args(c, mode, pt->n_seq);
+  sa.losses = losses;
+  sa.pos_loss = c->loss_pos; sa.pos_row = pt->mask_row; sa.n_pos = pt->n_mask; sa.S = c->cfg.dims[4];
+  return sa;
 }
 
 sama_status sama_aux_base_step(sama_ctx* c, const sama_batch* ft, const sama_aux_batch* pt, float* loss_out) {
@@ -508,24 +514,23 @@ sama_status sama_aux_base_step(sama_ctx* c, const sama_batch* ft, const sama_aux
   if (s != SAMA_OK) return s;
   hipStream_t st = c->stream;
   (void)hipGetLastError();
-  const int S = c->cfg.dims[4], C = c->model->n_classes(), n_ft = ft->n, n_pt = pt->n_seq;
-  launch_step_scalars(st, c->counters, 1, c->cfg.base_lr, c->cfg.beta1, c->cfg.beta2, c->step);
+  const int S = c->cfg.dims[4], n_ft = ft->n, n_pt = pt->n_seq;
   const bool padded = ft->seq_len != nullptr || pt->seq_len != nullptr;
   launch_aux_cat(st, (const int32_t*)ft->x, ft->y, ft->sample_mask, n_ft, pt->ids, n_pt, S, c->ids_cat, c->y_cat, c->mask_cat,
                  ft->seq_len, pt->seq_len, padded ? c->len_cat : nullptr);
   const sama_batch cat{c->ids_cat, c->y_cat, c->mask_cat, n_ft + n_pt, padded ? c->len_cat : nullptr};
   const PassWeights w = base_weights(c);
-  c->model->forward(st, w, cat, true, c->logits);
+  const HeadView head = c->model->forward(st, w, cat, true);
   // finetuning term: mean cross-entropy over the ft rows (the auxiliary rows are masked out of the classifier loss)
-  SampleStageArgs sa{};
-  sa.logits = c->logits; sa.ld = C; sa.C = C; sa.B = cat.n; sa.H = c->cfg.wnet_hidden; sa.mode = STAGE_META;
-  sa.y = cat.y; sa.mask = cat.sample_mask; sa.lambda = c->lambda; sa.losses = c->losses; sa.dlogits = c->dlogits;
-  sa.loss_scalar = c->scalars + 2; sa.loss_user = loss_out;
+  SampleStageArgs sa = class_stage_args(c, STAGE_META, &cat, head);
+  sa.loss_scalar = c->scalars + 2; sa.loss_user = loss_out; sa.step = next_step(c);
   launch_sample_stage(st, sa);
   // weighted pretraining term
   const MlmBatch mb{pt->mask_row, pt->mask_tgt, pt->n_mask, n_ft * S, n_pt * S};
   c->model->mlm_forward(st, &w, 1, cat.n * S, true, mb, c->loss_pos);
-  aux_stage(c, pt, STAGE_BASE, c->loss_pos, c->losses + n_ft, nullptr, loss_out);
+  SampleStageArgs sp = aux_stage_args(c, pt, STAGE_BASE, c->losses + n_ft);
+  sp.pos_coef = c->coef_pos; sp.loss_scalar = c->scalars + 2; sp.loss_user = loss_out;
+  launch_sample_stage(st, sp);
   UpdateSink sink(c, c->t + 1);
   c->model->set_grad_sink(&sink);
   c->model->backward_mlm(st, w, cat, c->dlogits, c->g, mb, c->coef_pos);
@@ -543,13 +548,11 @@ sama_status sama_aux_eval(sama_ctx* c, const sama_aux_batch* pt, float* losses_o
   const int S = c->cfg.dims[4];
   const sama_batch ptb{pt->ids, nullptr, nullptr, pt->n_seq, pt->seq_len};
   const PassWeights w = base_weights(c);
-  c->model->forward(st, w, ptb, true, c->logits);        // the head reads the kept last hidden state
+  c->model->forward(st, w, ptb, true);        // the head reads the kept last hidden state
   const MlmBatch mb{pt->mask_row, pt->mask_tgt, pt->n_mask, 0, pt->n_seq * S};
   c->model->mlm_forward(st, &w, 1, pt->n_seq * S, true, mb, c->loss_pos);
-  SampleStageArgs sa{};
-  sa.B = pt->n_seq; sa.H = c->cfg.wnet_hidden; sa.mode = STAGE_EVAL; sa.lambda = c->lambda;
-  sa.losses = losses_out; sa.weights = weights_out;
-  sa.pos_loss = c->loss_pos; sa.pos_row = pt->mask_row; sa.n_pos = pt->n_mask; sa.S = S;
+  SampleStageArgs sa = aux_stage_args(c, pt, STAGE_EVAL, losses_out);
+  sa.weights = weights_out;
   launch_sample_stage(st, sa);
   return check_hip(c, "sama_aux_eval");
 }
@@ -569,13 +572,14 @@ static sama_status aux_meta_common(sama_ctx* c, const sama_aux_batch* pt, const 
   // passes 2 and 3 on the auxiliary sequences alone: the finetuning term of L_base does not depend on lambda
   const sama_batch ptb{pt->ids, nullptr, nullptr, pt->n_seq, pt->seq_len};
   const PassWeights w[2] = {pass_weights(c, 1.f, c->lo_p), pass_weights(c, -1.f, fused_nudge ? c->lo_0 : c->lo_m)};
-  c->model->forward_pair(st, w[0], w[1], ptb, c->logits);
+  c->model->forward_pair(st, w[0], w[1], ptb);
   const MlmBatch mb{pt->mask_row, pt->mask_tgt, pt->n_mask, 0, pt->n_seq * S};
   c->model->mlm_forward(st, w, 2, pt->n_seq * S, false, mb, c->loss_pos);
-  const int P = c->model->mlm_stride();
-  for (int pass = 0; pass < 2; ++pass)
-    aux_stage(c, pt, STAGE_GLAM, c->loss_pos + (size_t)pass * P, c->losses, pass == 0 ? c->glam_p : c->glam_m, nullptr);
-  meta_finish(c, hyper_out, eps_out, update, fused_nudge);
+  SampleStageArgs sg = aux_stage_args(c, pt, STAGE_GLAM, c->losses);
+  sg.pos_pass_stride = c->model->mlm_stride();
+  sg.mu = meta_update_args(c, hyper_out, eps_out, update);
+  launch_sample_stage(st, sg);
+  if (update) meta_nudge(c, fused_nudge);
   return check_hip(c, update ? "sama_aux_meta_step" : "sama_aux_meta_grad");
 }
 
@@ -625,9 +629,8 @@ sama_status sama_get_state(sama_ctx* c, int32_t which, void* dst) {
   if (!dst) return fail(c, SAMA_EINVAL, "null dst");
   void* p; size_t bytes; bool wr;
   if (!state_ptr(c, which, &p, &bytes, &wr)) return fail(c, SAMA_EINVAL, "unknown state selector");
-  if (hipMemcpyAsync(dst, p, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
-    return fail(c, SAMA_EHIP, "sama_get_state: copy failed");
-  return SAMA_OK;
+  launch_copy_f32(c->stream, (float*)dst, (const float*)p, (int64_t)(bytes / 4));
+  return check_hip(c, "sama_get_state");
 }
 
 sama_status sama_set_state(sama_ctx* c, int32_t which, const void* src) {
@@ -650,7 +653,9 @@ sama_status sama_set_state(sama_ctx* c, int32_t which, const void* src) {
     if (host[0] < 0 || host[1] < 0) return fail(c, SAMA_EINVAL, "negative counters");
     c->t = host[0];
     c->lr_step = c->cfg.base_lr;   // a state put in from outside is taken to have been reached at the rate in force
-    launch_step_scalars(c->stream, c->counters, 0, c->cfg.base_lr, c->cfg.beta1, c->cfg.beta2, c->step);
+    StepScalars now = next_step(c);
+    now.advance = 0;
+    launch_step_scalars(c->stream, now);
   }
   return check_hip(c, "sama_set_state");
 }

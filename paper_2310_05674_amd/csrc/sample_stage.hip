@@ -1,4 +1,5 @@
-// Per-sample stage between the model's logits and its backward pass (Sec. 4.1):
+// Classifier head and per-sample stage between the model's last hidden state and its backward pass (Sec. 4.1):
+//   z_i = W x_i + b
 //   l_i = logsumexp(z_i) - z_i[y_i];  w_i = sigmoid(W2 . relu(W1 l_i + b1) + b2);  B_eff = sum mask
 //   BASE: coef_i = mask_i w_i / B_eff   META: coef_i = mask_i / B_eff   -> dz_i = coef_i (softmax(z_i) - e_{y_i})
 //   GLAM: dL_base/dlambda = (1/B_eff) sum_i mask_i l_i dw(l_i; lambda)/dlambda   (weight-net backward only)
@@ -7,152 +8,363 @@
 //   BASE: dz_i = coef_i (softmax(z_i) - c_i)
 //   GLAM: additionally d/dlambda_c = sum_i coef_i sum_k (-log p_ik) dc_ik/dlambda_c  (corrector backward; its inputs are constants)
 // and the finite-difference combine + Adam step on lambda (Eq. 5, Table 4).
-// Batches are at most a few hundred samples: one workgroup, samples staged in LDS, every sum in a fixed order,
-// arithmetic in double so that the +-eps difference of Eq. 5 is not lost to rounding.
+//
+// Everything here is small and latency-bound, a launch of its own costing as much as most of these steps.  The logits of a
+// workgroup's 32 samples come from the fp32 matrix cores, the eight waves splitting the contraction.  Sixteen lanes share a sample (classes, weight-net and corrector hidden
+// units are split between them and joined by shuffles), a workgroup holds 32 samples at a time, and a batch is spread over
+// up to STAGE_MAX_BLOCKS workgroups.  What a mode sums over the batch (the loss, the lambda-gradient) leaves each
+// workgroup as a partial; the workgroup that finishes last adds the partials in workgroup order, so results do not depend on
+// timing.  The + and the - pass of Eq. 5 are one launch (grid.y), and the last workgroup of that launch also combines them
+// and updates lambda.  Arithmetic is in double so that the +-eps difference of Eq. 5 is not lost to rounding.
+//
+// Measured against one workgroup per pass with a lane per sample and launches of their own for the head, the two passes, the
+// update of lambda and the step scalars (kernel durations in a trace): label correction with 203 samples, Hc = 64, 10 classes
+// 347 -> 21 us (base step) and 2 x 347 + 9 -> 43 us (both passes and the update); scoring 2048 samples 44 + 7 -> 8.5 us;
+// reweighting with 128 samples, H = 100: 13 + 8 -> 10 us and 2 x (13 + 8) + 5 -> 15 us.
 #include "common.h"
 #include "kernels.h"
+#include "mfma_f32.h"
 
 namespace sama {
 namespace {
 
-__device__ __forceinline__ double block_sum_d(double x, double* red) {
-  __syncthreads();
-  red[threadIdx.x] = x;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+constexpr int ST_THREADS = 512, ST_LANES = 16, ST_SAMPLES = ST_THREADS / ST_LANES;   // samples per trip
+constexpr int ST_MAX_RUN = (MAX_BATCH + STAGE_MAX_BLOCKS - 1) / STAGE_MAX_BLOCKS < ST_SAMPLES ? ST_SAMPLES : (MAX_BATCH + STAGE_MAX_BLOCKS - 1) / STAGE_MAX_BLOCKS;
+constexpr int MAX_CORR = MAX_CORR_HIDDEN * 2 * MAX_CORR_CLASSES + MAX_CORR_HIDDEN + MAX_CORR_CLASSES * MAX_CORR_HIDDEN + MAX_CORR_CLASSES;
+constexpr int CQ = 4;                        // classes per lane: up to 64 over sixteen lanes
+static_assert(ST_MAX_RUN == ST_SAMPLES && ST_SAMPLES == 32 && ST_THREADS == 64 * FWAVES, "one trip of 2 x 16 samples per workgroup");
+
+// s_z[i][c] = logits of samples i_begin + i (two 16-row MFMA tiles), c < C: wave w takes every FWAVES-th chunk of the
+// contraction, requests four chunks at a time, and the partial tiles are added in wave order.  red: FWAVES x 32 x 17.
+__device__ void head_logits(const HeadView& h, int pass, int i_begin, int n_own, int C, float* __restrict__ red, double* __restrict__ s_z) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
+  const float* x = h.x + pass * h.pass_stride + i_begin * h.stride;
+  const float* W = h.pv.theta + h.w_off;
+  const float* Wv = h.pv.vdir + h.w_off;
+  const float s = pass == 0 ? h.pv.scale() : -h.pv.scale();
+  const bool x_vec = (h.stride & 3) == 0 && ((uintptr_t)x & 15) == 0;
+  const bool w_vec = (h.k & 3) == 0 && (((uintptr_t)W | (s != 0.f ? (uintptr_t)Wv : 0)) & 15) == 0;
+  constexpr int DEPTH = 4;
+  for (int c0 = 0; c0 < C; c0 += 16) {
+    float4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    for (int kb = wave * FCH; kb < h.k; kb += DEPTH * FWAVES * FCH) {
+      float4v av[DEPTH][2], bv[DEPTH], pv[DEPTH];
+#pragma unroll
+      for (int u = 0; u < DEPTH; ++u) {
+        const int k = kb + u * FWAVES * FCH + 4 * q;      // a chunk beyond the end reads as zeros
+        av[u][0] = load_k4(x, h.stride, 1, r, n_own, k, h.k, x_vec);
+        av[u][1] = load_k4(x, h.stride, 1, 16 + r, n_own, k, h.k, x_vec);
+        bv[u] = load_k4(W, h.k, 1, c0 + r, C, k, h.k, w_vec);
+        if (s != 0.f) pv[u] = load_k4(Wv, h.k, 1, c0 + r, C, k, h.k, w_vec);
+      }
+#pragma unroll
+      for (int u = 0; u < DEPTH; ++u) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float b = s != 0.f ? fmaf(s, pv[u][c], bv[u][c]) : bv[u][c];
+          acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][0][c], b, acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][1][c], b, acc[1], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[(wave * 32 + 16 * t + 4 * q + e) * 17 + r] = acc[t][e];
+    __syncthreads();
+    {
+      const int i = threadIdx.x >> 4, c = threadIdx.x & 15;   // 512 threads: one of the 32 x 16 outputs each
+      if (c0 + c < C) {
+        double z = (double)h.pv.at(h.b_off + c0 + c, s);
+#pragma unroll
+        for (int w = 0; w < FWAVES; ++w) z += (double)red[(w * 32 + i) * 17 + c];
+        s_z[i * 64 + c0 + c] = z;
+      }
+    }
     __syncthreads();
   }
-  const double r = red[0];
-  __syncthreads();
-  return r;
 }
 
-__global__ __launch_bounds__(256) void k_sample_stage(SampleStageArgs a) {
-  __shared__ double s_l[MAX_BATCH];    // l_i
-  __shared__ double s_dz[MAX_BATCH];   // per-sample dL/dz of the weight net (GLAM) or coef (BASE/META)
-  __shared__ float s_lam[3 * MAX_WNET_HIDDEN + 1];
-  __shared__ double red[256];
-  __shared__ float s_lc[MAX_CORR_HIDDEN * 2 * MAX_CORR_CLASSES + MAX_CORR_HIDDEN + MAX_CORR_CLASSES * MAX_CORR_HIDDEN + MAX_CORR_CLASSES];
-  const int tid = threadIdx.x, H = a.H, B = a.B, C = a.C;
-  const bool seq_mode = a.pos_loss != nullptr;          // per-sequence losses from masked-token positions
-  const int Hc = (a.mode == STAGE_META || seq_mode) ? 0 : a.Hc;      // the clean batch keeps its hard labels
-  for (int i = tid; i < 3 * H + 1; i += 256) s_lam[i] = a.lambda[i];
-  const int nlc = Hc > 0 ? Hc * 2 * C + Hc + C * Hc + C : 0;
-  for (int i = tid; i < nlc; i += 256) s_lc[i] = a.lambda[3 * H + 1 + i];
+// every lane of a group of sixteen gets the sum / maximum over the group
+__device__ __forceinline__ double sum16(double x) {
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+__device__ __forceinline__ double max16(double x) {
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
+  return x;
+}
+// sum over the workgroup in a fixed order, for every thread; `red` holds ST_THREADS / 64 values
+__device__ __forceinline__ double block_sum_d(double x, double* red) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
   __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < ST_THREADS / 64; ++k) s += red[k];
+  return s;
+}
+
+// h = -(glam+ - glam-) / (2 eps); then (optionally) Adam on lambda.  A raised status word (counters[2]) or a
+// hypergradient with a non-finite component zeroes h and skips the update; the latter raises the status word itself.
+// glam+ / glam- are the sums of the workgroups' partials in order.
+__device__ void meta_update(const MetaUpdateArgs& a, const double* part, int nblk) {
+  const float eps = a.scalars[0];
+  bool skip = (a.counters[2] != 0) || !(eps > 0.f);
+  int bad = 0;
+  for (int i = threadIdx.x; i < a.nl; i += ST_THREADS) {
+    double gp = 0.0, gm = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < nblk; ++k) {
+      gp += collect(part + (int64_t)k * a.nl + i);
+      gm += collect(part + (int64_t)(nblk + k) * a.nl + i);
+    }
+    a.glam_p[i] = gp; a.glam_m[i] = gm;
+    if (!skip) {
+      const double h = -(gp - gm) / (2.0 * (double)eps);
+      if (!(fabs(h) <= 3.0e38)) bad = 1;   // NaN, infinite, or beyond what the fp32 outputs hold
+    }
+  }
+  const int64_t t = a.counters[1] + 1;
+  if (__syncthreads_or(bad)) {   // every thread has read counters[2] above
+    skip = true;
+    if (threadIdx.x == 0) a.counters[2] = 1;
+  }
+  const double c1 = 1.0 / (1.0 - ipow((double)a.beta1, t));
+  const double c2 = 1.0 / sqrt(1.0 - ipow((double)a.beta2, t));
+  for (int i = threadIdx.x; i < a.nl; i += ST_THREADS) {
+    const double gp = a.glam_p[i], gm = a.glam_m[i];   // written by this thread above
+    const double h = skip ? 0.0 : -(gp - gm) / (2.0 * (double)eps);
+    a.hypergrad[i] = (float)h;
+    if (a.hypergrad_user) a.hypergrad_user[i] = (float)h;
+    a.glam_p_f32[i] = (float)gp;
+    a.glam_m_f32[i] = (float)gm;
+    if (a.do_update && !skip) {
+      const double m = (double)a.beta1 * a.meta_m[i] + (1.0 - (double)a.beta1) * h;
+      const double v = (double)a.beta2 * a.meta_v[i] + (1.0 - (double)a.beta2) * h * h;
+      a.meta_m[i] = (float)m;
+      a.meta_v[i] = (float)v;
+      a.lambda[i] = (float)((double)a.lambda[i] - (double)a.lr * c1 * m / (c2 * sqrt(v) + (double)a.eps));
+    }
+  }
+  if (threadIdx.x == 0) {
+    if (a.eps_user) *a.eps_user = skip ? 0.f : eps;
+    if (a.do_update && !skip) a.counters[1] = t;
+  }
+}
+
+// CORR: label correction compiled in (its arrays make up most of the LDS)
+template <bool CORR>
+__global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, int run, int nblk) {
+  __shared__ double s_l[ST_MAX_RUN];    // l_i of this workgroup's samples
+  __shared__ double s_dz[ST_MAX_RUN];   // per-sample dL/dz of the weight net (GLAM)
+  __shared__ float s_cnt[ST_MAX_RUN];   // sequence mode: positions per sequence
+  __shared__ float s_lam[3 * MAX_WNET_HIDDEN + 1];
+  __shared__ double red[ST_THREADS / 64];
+  __shared__ int s_last;
+  __shared__ float s_hred[FWAVES * 32 * 17];
+  __shared__ double s_z[ST_SAMPLES * 64];
+  __shared__ float s_lc[CORR ? MAX_CORR : 1];
+  __shared__ double s_a[CORR ? ST_SAMPLES * MAX_CORR_HIDDEN : 1], s_t[CORR ? ST_SAMPLES * MAX_CORR_HIDDEN : 1];   // relu(a_ij), dL/da_ij
+  __shared__ double s_p[CORR ? ST_SAMPLES * MAX_CORR_CLASSES : 1], s_ds[CORR ? ST_SAMPLES * MAX_CORR_CLASSES : 1];
+  __shared__ int s_y[CORR ? ST_SAMPLES : 1];
+  const int tid = threadIdx.x, lane = tid & (ST_LANES - 1), grp = tid / ST_LANES, H = a.H, B = a.B, C = a.C;
+  if ((int)blockIdx.x == nblk) {   // the step-dependent scalars of the base solver (the update runs much later)
+    if (tid == 0) step_scalars(a.step);
+    return;
+  }
+  const int pass = blockIdx.y, i_begin = blockIdx.x * run, i_end = min(B, i_begin + run), n_own = i_end - i_begin;
+  const bool seq_mode = a.pos_loss != nullptr;          // per-sequence losses from masked-token positions
+  const int Hc = CORR ? a.Hc : 0;
+  const float* pos_loss = a.pos_loss + pass * a.pos_pass_stride;
+  float* losses = pass == (int)gridDim.y - 1 ? a.losses : nullptr;   // of the most recent pass
+
+  for (int i = tid; i < 3 * H + 1; i += ST_THREADS) s_lam[i] = a.lambda[i];
+  const int nlc = Hc > 0 ? Hc * 2 * C + Hc + C * Hc + C : 0;
+  if (CORR)
+    for (int i = tid; i < nlc; i += ST_THREADS) s_lc[i] = a.lambda[3 * H + 1 + i];
+  double beff = (double)B;
+  if (a.mask != nullptr) {
+    double cnt = 0.0;
+    for (int i = tid; i < B; i += ST_THREADS) cnt += a.mask[i] != 0 ? 1.0 : 0.0;
+    beff = block_sum_d(cnt, red);
+  }
+  const double inv_beff = beff > 0.0 ? 1.0 / beff : 0.0;
+  __syncthreads();
+  if (!seq_mode) head_logits(a.head, pass, i_begin, n_own, C, s_hred, s_z);
   const float* W1 = s_lam; const float* b1 = s_lam + H; const float* W2 = s_lam + 2 * H;
   const double b2 = (double)s_lam[3 * H];
   const float* W1c = s_lc; const float* b1c = s_lc + Hc * 2 * C; const float* W2c = b1c + Hc; const float* b2c = W2c + C * Hc;
 
-  double cnt = 0.0;
-  for (int i = tid; i < B; i += 256) cnt += (a.mask == nullptr || a.mask[i] != 0) ? 1.0 : 0.0;
-  const double beff = block_sum_d(cnt, red);
-  const double inv_beff = beff > 0.0 ? 1.0 / beff : 0.0;
-
-  double lsum = 0.0;
-  float* s_cnt = s_lc;                                  // sequence mode: positions per sequence (the corrector is off)
-  // wave w takes sequences w, w + 4, ...: its lanes stride over the positions (coalesced), keep the matching losses,
-  // and a shuffle tree adds the 64 partial sums in a fixed order
-  for (int i = tid >> 6; seq_mode && i < B; i += 4) {
-    double acc = 0.0, n_i = 0.0;
-    for (int j = tid & 63; j < a.n_pos; j += 64) {
-      int r = a.pos_row[j];
-      r = r < 0 ? 0 : (r >= B * a.S ? B * a.S - 1 : r);
-      if (r / a.S == i) { acc += (double)a.pos_loss[j]; n_i += 1.0; }
-    }
-    for (int o = 32; o > 0; o >>= 1) { acc += __shfl_xor(acc, o, 64); n_i += __shfl_xor(n_i, o, 64); }
-    if ((tid & 63) == 0) { s_l[i] = n_i > 0.0 ? acc / n_i : 0.0; s_cnt[i] = (float)n_i; }
-  }
-  if (seq_mode) __syncthreads();
-  for (int i = tid; seq_mode && i < B; i += 256) {
-    const double l = s_l[i];
-    const double mk = (a.mask == nullptr || a.mask[i] != 0) ? 1.0 : 0.0;
-    if (a.losses != nullptr) a.losses[i] = (float)l;
-    double zz = b2;
-    for (int h = 0; h < H; ++h) zz += (double)W2[h] * fmax((double)W1[h] * l + (double)b1[h], 0.0);
-    const double w = 1.0 / (1.0 + exp(-zz));
-    if (a.weights != nullptr) a.weights[i] = (float)w;
-    if (a.mode == STAGE_EVAL) continue;
-    if (a.mode == STAGE_GLAM) {
-      s_dz[i] = w * (1.0 - w) * l * mk * inv_beff;
-    } else {
-      s_dz[i] = mk * w * inv_beff;
-      lsum += s_dz[i] * l;
-    }
-  }
-  if (seq_mode && a.mode != STAGE_GLAM && a.mode != STAGE_EVAL) {   // uniform over the block
-    __syncthreads();
-    for (int j = tid; j < a.n_pos; j += 256) {
-      int r = a.pos_row[j];
-      r = r < 0 ? 0 : (r >= B * a.S ? B * a.S - 1 : r);
-      const int i = r / a.S;
-      a.pos_coef[j] = (float)(s_dz[i] / (double)s_cnt[i]);     // s_cnt[i] >= 1: position j itself belongs to i
-    }
-  }
-  for (int i = tid; !seq_mode && i < B; i += 256) {
-    const float* z = a.logits + (int64_t)i * a.ld;
-    double zmax = (double)z[0];
-    for (int c = 1; c < C; ++c) zmax = fmax(zmax, (double)z[c]);
-    double se = 0.0;
-    for (int c = 0; c < C; ++c) se += exp((double)z[c] - zmax);
-    const double lse = log(se) + zmax;
-    const int yi = min(max(a.y[i], 0), C - 1);   // labels outside [0, C) are clamped
-    const double mk = (a.mask == nullptr || a.mask[i] != 0) ? 1.0 : 0.0;
-    double l;
-    double cs[MAX_CORR_CLASSES];                       // corrected soft label (Hc > 0)
-    if (Hc > 0) {
-      double sc[MAX_CORR_CLASSES], pk[MAX_CORR_CLASSES];
-      for (int k = 0; k < C; ++k) { sc[k] = (double)b2c[k] + (k == yi ? (double)a.kappa : 0.0); pk[k] = exp((double)z[k] - lse); }
-      for (int j = 0; j < Hc; ++j) {
-        double aj = (double)b1c[j] + (double)W1c[j * 2 * C + yi];
-        for (int k = 0; k < C; ++k) aj += (double)W1c[j * 2 * C + C + k] * pk[k];
-        if (aj > 0.0)
-          for (int k = 0; k < C; ++k) sc[k] += (double)W2c[k * Hc + j] * aj;
+  if (seq_mode) {
+    // wave w takes sequences w, w + waves, ...: its lanes stride over the positions (coalesced), keep the matching losses,
+    // and a shuffle tree adds the 64 partial sums in a fixed order
+    for (int i = tid >> 6; i < n_own; i += ST_THREADS / 64) {
+      double acc = 0.0, n_i = 0.0;
+      for (int j = tid & 63; j < a.n_pos; j += 64) {
+        int r = a.pos_row[j];
+        r = r < 0 ? 0 : (r >= B * a.S ? B * a.S - 1 : r);
+        if (r / a.S == i_begin + i) { acc += (double)pos_loss[j]; n_i += 1.0; }
       }
-      double smax = sc[0];
-      for (int k = 1; k < C; ++k) smax = fmax(smax, sc[k]);
-      double ssum = 0.0;
-      for (int k = 0; k < C; ++k) { cs[k] = exp(sc[k] - smax); ssum += cs[k]; }
-      l = 0.0;
-      for (int k = 0; k < C; ++k) { cs[k] /= ssum; l -= cs[k] * ((double)z[k] - lse); }
-    } else {
-      l = lse - (double)z[yi];
+      for (int o = 32; o > 0; o >>= 1) { acc += __shfl_xor(acc, o, 64); n_i += __shfl_xor(n_i, o, 64); }
+      if ((tid & 63) == 0) { s_l[i] = n_i > 0.0 ? acc / n_i : 0.0; s_cnt[i] = (float)n_i; }
     }
-    if (a.losses != nullptr) a.losses[i] = (float)l;
-    s_l[i] = l;
+    __syncthreads();
+  }
+  double lsum = 0.0;
+  constexpr int PAIRS = CORR ? (MAX_CORR_HIDDEN * MAX_CORR_CLASSES + ST_THREADS - 1) / ST_THREADS : 1;
+  double gW2[PAIRS], gWp[PAIRS], gWy[PAIRS], gb1[PAIRS], gb2[PAIRS];   // corrector backward: thread owns (hidden unit, class) pairs
+#pragma unroll
+  for (int u = 0; u < PAIRS; ++u) gW2[u] = gWp[u] = gWy[u] = gb1[u] = gb2[u] = 0.0;
+
+  for (int i0 = i_begin; i0 < i_end; i0 += ST_SAMPLES) {   // every thread takes part in every trip (barriers with CORR)
+    const int i = i0 + grp;
+    const bool live = i < i_end;
+    const int ic = live ? i : i_end - 1;
+    const double mk = (live && (a.mask == nullptr || a.mask[ic] != 0)) ? 1.0 : 0.0;
+    double l, lse = 0.0, zc[CQ] = {0.0, 0.0, 0.0, 0.0};
+    int yi = 0;
+    double cs = 0.0;                                      // corrected soft label of class `lane` (Hc > 0)
+    if (seq_mode) {
+      l = s_l[ic - i_begin];
+    } else {
+      const double* z = s_z + (ic - i_begin) * 64;
+      yi = min(max(a.y[ic], 0), C - 1);   // labels outside [0, C) are clamped
+#pragma unroll
+      for (int q = 0; q < CQ; ++q) zc[q] = lane + ST_LANES * q < C ? z[lane + ST_LANES * q] : -1.0e300;
+      const double zy = z[yi];
+      if (a.logits != nullptr && live) {
+#pragma unroll
+        for (int q = 0; q < CQ; ++q)
+          if (lane + ST_LANES * q < C) a.logits[(int64_t)i * C + lane + ST_LANES * q] = (float)z[lane + ST_LANES * q];
+      }
+      const double zmax = max16(fmax(fmax(zc[0], zc[1]), fmax(zc[2], zc[3])));
+      double se = 0.0;
+#pragma unroll
+      for (int q = 0; q < CQ; ++q)
+        if (lane + ST_LANES * q < C) se += exp(zc[q] - zmax);
+      lse = log(sum16(se)) + zmax;
+      if (CORR) {
+        const bool own = lane < C;                        // C <= 16: lane k holds class k
+        const double lp = zc[0] - lse, p = own ? exp(lp) : 0.0;
+        s_p[grp * MAX_CORR_CLASSES + lane] = p;
+        if (lane == 0) s_y[grp] = yi;
+        __syncthreads();
+        double sc[MAX_CORR_CLASSES];
+#pragma unroll
+        for (int k = 0; k < MAX_CORR_CLASSES; ++k) sc[k] = 0.0;
+        for (int j = lane; j < Hc; j += ST_LANES) {
+          double aj = (double)b1c[j] + (double)W1c[j * 2 * C + yi];
+          for (int k = 0; k < C; ++k) aj += (double)W1c[j * 2 * C + C + k] * s_p[grp * MAX_CORR_CLASSES + k];
+          aj = aj > 0.0 ? aj : 0.0;
+          s_a[grp * MAX_CORR_HIDDEN + j] = aj;
+#pragma unroll
+          for (int k = 0; k < MAX_CORR_CLASSES; ++k)
+            if (k < C) sc[k] += (double)W2c[k * Hc + j] * aj;
+        }
+        double s_own = 0.0;
+#pragma unroll
+        for (int k = 0; k < MAX_CORR_CLASSES; ++k) {
+          if (k < C) {   // the same for every lane
+            const double tot = sum16(sc[k]);
+            if (k == lane) s_own = tot + (double)b2c[k] + (k == yi ? (double)a.kappa : 0.0);
+          }
+        }
+        const double smax = max16(own ? s_own : -1.0e300);
+        cs = own ? exp(s_own - smax) : 0.0;
+        cs /= sum16(cs);
+        l = -sum16(own ? cs * lp : 0.0);
+      } else {
+        l = lse - zy;
+      }
+    }
+    if (losses != nullptr && live && lane == 0) losses[i] = (float)l;
     double w = 1.0;
     if (a.mode != STAGE_META) {
-      double zz = b2;
-      for (int h = 0; h < H; ++h) zz += (double)W2[h] * fmax((double)W1[h] * l + (double)b1[h], 0.0);
-      w = 1.0 / (1.0 + exp(-zz));
+      double zz = 0.0;
+      for (int h = lane; h < H; h += ST_LANES) zz += (double)W2[h] * fmax((double)W1[h] * l + (double)b1[h], 0.0);
+      w = 1.0 / (1.0 + exp(-(sum16(zz) + b2)));
     }
-    if (a.weights != nullptr) a.weights[i] = (float)w;
-    if (a.mode == STAGE_EVAL) continue;
+    if (a.weights != nullptr && live && lane == 0) a.weights[i] = (float)w;
+    if (a.mode == STAGE_EVAL) {
+      if (CORR) __syncthreads();                          // s_p is rewritten by the next trip
+      continue;
+    }
+    const double coef = mk * w * inv_beff;
     if (a.mode == STAGE_GLAM) {
-      s_dz[i] = w * (1.0 - w) * l * mk * inv_beff;
-      if (Hc > 0) {
-        // ds_ik = c_ik (dc_ik - sum_k' c_ik' dc_ik'), dc_ik = -coef_i log p_ik; kept with p_i for the second phase
-        const double coef = mk * w * inv_beff;
-        double dot = 0.0;
-        for (int k = 0; k < C; ++k) dot += cs[k] * (-coef * ((double)z[k] - lse));
-        for (int k = 0; k < C; ++k) {
-          a.corr_scratch[(int64_t)i * 2 * C + k] = cs[k] * (-coef * ((double)z[k] - lse) - dot);
-          a.corr_scratch[(int64_t)i * 2 * C + C + k] = exp((double)z[k] - lse);
+      if (live && lane == 0) { s_l[i - i_begin] = l; s_dz[i - i_begin] = w * (1.0 - w) * l * mk * inv_beff; }
+      if (CORR) {
+        // ds_ik = c_ik (dc_ik - sum_k' c_ik' dc_ik'), dc_ik = -coef_i log p_ik;  t_ij = [a_ij > 0] sum_k W2c[k][j] ds_ik
+        const double dc = lane < C ? -coef * (zc[0] - lse) : 0.0;
+        const double dot = sum16(cs * dc), ds = cs * (dc - dot);
+        s_ds[grp * MAX_CORR_CLASSES + lane] = ds;
+        __syncthreads();
+        for (int j = lane; j < Hc; j += ST_LANES) {
+          double t = 0.0;
+          for (int k = 0; k < C; ++k) t += (double)W2c[k * Hc + j] * s_ds[grp * MAX_CORR_CLASSES + k];
+          s_t[grp * MAX_CORR_HIDDEN + j] = s_a[grp * MAX_CORR_HIDDEN + j] > 0.0 ? t : 0.0;
         }
+        __syncthreads();
+        const int ns = min(ST_SAMPLES, i_end - i0);
+#pragma unroll
+        for (int u = 0; u < PAIRS; ++u) {
+          const int pr = tid + u * ST_THREADS, j = pr % Hc, k = pr / Hc;
+          if (k >= C) continue;
+          for (int s = 0; s < ns; ++s) {
+            const double aj = s_a[s * MAX_CORR_HIDDEN + j], t = s_t[s * MAX_CORR_HIDDEN + j], d = s_ds[s * MAX_CORR_CLASSES + k];
+            gW2[u] += d * aj;
+            gWp[u] += t * s_p[s * MAX_CORR_CLASSES + k];
+            gWy[u] += s_y[s] == k ? t : 0.0;
+            gb1[u] += t;      // kept by the pairs with k == 0
+            gb2[u] += d;      // kept by the pairs with j == 0
+          }
+        }
+        __syncthreads();
+      }
+    } else if (seq_mode) {
+      if (lane == 0) {
+        if (live) s_dz[i - i_begin] = coef;
+        lsum += coef * l;
       }
     } else {
-      const double coef = mk * w * inv_beff;
-      lsum += coef * l;
-      for (int c = 0; c < C; ++c) {
-        const double p = exp((double)z[c] - lse);
-        const double target = Hc > 0 ? cs[c] : (c == yi ? 1.0 : 0.0);
-        a.dlogits[(int64_t)i * C + c] = (float)(coef * (p - target));
+      if (lane == 0) lsum += coef * l;
+#pragma unroll
+      for (int q = 0; q < CQ; ++q) {
+        const int c = lane + ST_LANES * q;
+        if (live && c < C) {
+          const double target = CORR ? cs : (c == yi ? 1.0 : 0.0);
+          a.dlogits[(int64_t)i * C + c] = (float)(coef * (exp(zc[q] - lse) - target));
+        }
       }
+      if (CORR) __syncthreads();
     }
   }
+  if (a.mode == STAGE_EVAL) return;
+
+  const int total = nblk * gridDim.y;      // workgroups whose partials make the result
   if (a.mode != STAGE_GLAM) {
-    const double L = block_sum_d(lsum, red);
+    if (seq_mode) {
+      __syncthreads();
+      for (int j = tid; j < a.n_pos; j += ST_THREADS) {
+        int r = a.pos_row[j];
+        r = r < 0 ? 0 : (r >= B * a.S ? B * a.S - 1 : r);
+        const int i = r / a.S;
+        if (i >= i_begin && i < i_end) a.pos_coef[j] = (float)(s_dz[i - i_begin] / (double)s_cnt[i - i_begin]);   // s_cnt >= 1: position j itself
+      }
+    }
+    double L = block_sum_d(lsum, red);
+    if (total > 1) {
+      if (tid == 0) publish(a.part + blockIdx.x, L);
+      if (!last_block(a.ticket, total, &s_last)) return;
+      if (tid == 0) {
+        L = 0.0;
+        for (int k = 0; k < nblk; ++k) L += collect(a.part + k);
+      }
+    }
     if (tid == 0) {
       if (a.loss_scalar) *a.loss_scalar = seq_mode ? *a.loss_scalar + (float)L : (float)L;
       if (a.loss_user) *a.loss_user = seq_mode ? *a.loss_user + (float)L : (float)L;
@@ -160,19 +372,20 @@ __global__ __launch_bounds__(256) void k_sample_stage(SampleStageArgs a) {
     return;
   }
   __syncthreads();
-  // weight-net backward: hidden unit h is shared by nch consecutive lanes of a wave (the largest power of two <= 256 / H,
-  // at most 64), each walking a contiguous run of the samples in order; every lane then adds the nch partial sums of its
-  // unit in chunk order through shuffles (fixed order, no atomics)
+  double* glam = a.part + (int64_t)(pass * nblk + blockIdx.x) * a.mu.nl;
+  // weight-net backward: hidden unit h is shared by nch consecutive lanes of a wave (the largest power of two <=
+  // ST_THREADS / H, at most 64), each walking a contiguous run of the samples in order; every lane then adds the nch partial
+  // sums of its unit in chunk order through shuffles (fixed order, no atomics)
   {
     int nch = 1;
-    while (2 * nch * H <= 256 && nch < 64) nch *= 2;
-    const int run = (B + nch - 1) / nch;
-    const int h = tid / nch, c = tid % nch;              // 256 / nch >= H units in one trip
+    while (2 * nch * H <= ST_THREADS && nch < 64) nch *= 2;
+    const int per = (n_own + nch - 1) / nch;
+    const int h = tid / nch, c = tid % nch;              // ST_THREADS / nch >= H units in one trip
     double part[3] = {0.0, 0.0, 0.0};                    // dW1, db1, dW2
     if (h < H) {
       const double w1 = W1[h], bb = b1[h], w2 = W2[h];
-      const int i1 = (c + 1) * run < B ? (c + 1) * run : B;
-      for (int i = c * run; i < i1; ++i) {
+      const int i1 = (c + 1) * per < n_own ? (c + 1) * per : n_own;
+      for (int i = c * per; i < i1; ++i) {
         const double l = s_l[i], dz = s_dz[i];
         const double pre = w1 * l + bb;
         if (pre > 0.0) {
@@ -188,94 +401,41 @@ __global__ __launch_bounds__(256) void k_sample_stage(SampleStageArgs a) {
     for (int k = 0; k < nch; ++k)
 #pragma unroll
       for (int q = 0; q < 3; ++q) tot[q] += __shfl(part[q], base + k, 64);
-    if (h < H && c == 0) { a.glam[h] = tot[0]; a.glam[H + h] = tot[1]; a.glam[2 * H + h] = tot[2]; }
+    if (h < H && c == 0) { publish(glam + h, tot[0]); publish(glam + H + h, tot[1]); publish(glam + 2 * H + h, tot[2]); }
   }
   double dsum = 0.0;
-  for (int i = tid; i < B; i += 256) dsum += s_dz[i];
+  for (int i = tid; i < n_own; i += ST_THREADS) dsum += s_dz[i];
   const double db2 = block_sum_d(dsum, red);
-  if (tid == 0) a.glam[3 * H] = db2;
-  if (Hc == 0) return;
-  // corrector backward: thread j owns hidden unit j (row j of W1c, b1c[j], column j of W2c) and walks the samples in
-  // order; threads Hc .. Hc + C - 1 own b2c.  The per-sample ds_i and p_i come back from the scratch written above
-  // (same block: the barrier inside block_sum_d orders the writes before these reads).
-  double* gc = a.glam + 3 * H + 1;
-  for (int j = tid; j < Hc + C; j += 256) {
-    if (j >= Hc) {
-      const int k = j - Hc;
-      double acc = 0.0;
-      for (int i = 0; i < B; ++i) acc += a.corr_scratch[(int64_t)i * 2 * C + k];
-      gc[Hc * 2 * C + Hc + C * Hc + k] = acc;
-      continue;
-    }
-    double dW1[2 * MAX_CORR_CLASSES], dW2[MAX_CORR_CLASSES];
-    for (int q = 0; q < 2 * C; ++q) dW1[q] = 0.0;
-    for (int k = 0; k < C; ++k) dW2[k] = 0.0;
-    double db1 = 0.0;
-    for (int i = 0; i < B; ++i) {
-      const double* ds = a.corr_scratch + (int64_t)i * 2 * C;
-      const double* p = ds + C;
-      const int yi = min(max(a.y[i], 0), C - 1);   // labels outside [0, C) are clamped
-      double aj = (double)b1c[j] + (double)W1c[j * 2 * C + yi];
-      for (int k = 0; k < C; ++k) aj += (double)W1c[j * 2 * C + C + k] * p[k];
-      if (aj > 0.0) {
-        double t = 0.0;
-        for (int k = 0; k < C; ++k) { dW2[k] += ds[k] * aj; t += (double)W2c[k * Hc + j] * ds[k]; }
-        db1 += t;
-        dW1[yi] += t;
-        for (int k = 0; k < C; ++k) dW1[C + k] += t * p[k];
-      }
-    }
-    for (int q = 0; q < 2 * C; ++q) gc[j * 2 * C + q] = dW1[q];
-    gc[Hc * 2 * C + j] = db1;
-    for (int k = 0; k < C; ++k) gc[Hc * 2 * C + Hc + k * Hc + j] = dW2[k];
-  }
-}
-
-// h = -(glam+ - glam-) / (2 eps); then (optionally) Adam on lambda.  A raised status word (counters[2]) or a
-// hypergradient with a non-finite component zeroes h and skips the update; the latter raises the status word itself.
-__global__ __launch_bounds__(256) void k_meta_update(MetaUpdateArgs a) {
-  const float eps = a.scalars[0];
-  bool skip = (a.counters[2] != 0) || !(eps > 0.f);
-  int bad = 0;
-  if (!skip)
-    for (int i = threadIdx.x; i < a.nl; i += 256) {
-      const double h = -(a.glam_p[i] - a.glam_m[i]) / (2.0 * (double)eps);
-      if (!(fabs(h) <= 3.0e38)) bad = 1;   // NaN, infinite, or beyond what the fp32 outputs hold
-    }
-  if (__syncthreads_or(bad)) {   // every thread has read counters[2] above
-    skip = true;
-    if (threadIdx.x == 0) a.counters[2] = 1;
-  }
-  const int64_t t = a.counters[1] + 1;
-  const double c1 = 1.0 / (1.0 - pow((double)a.beta1, (double)t));
-  const double c2 = 1.0 / sqrt(1.0 - pow((double)a.beta2, (double)t));
-  for (int i = threadIdx.x; i < a.nl; i += 256) {
-    const double gp = a.glam_p[i], gm = a.glam_m[i];
-    const double h = skip ? 0.0 : -(gp - gm) / (2.0 * (double)eps);
-    a.hypergrad[i] = (float)h;
-    if (a.hypergrad_user) a.hypergrad_user[i] = (float)h;
-    a.glam_p_f32[i] = (float)gp;
-    a.glam_m_f32[i] = (float)gm;
-    if (a.do_update && !skip) {
-      const double m = (double)a.beta1 * a.meta_m[i] + (1.0 - (double)a.beta1) * h;
-      const double v = (double)a.beta2 * a.meta_v[i] + (1.0 - (double)a.beta2) * h * h;
-      a.meta_m[i] = (float)m;
-      a.meta_v[i] = (float)v;
-      a.lambda[i] = (float)((double)a.lambda[i] - (double)a.lr * c1 * m / (c2 * sqrt(v) + (double)a.eps));
+  if (tid == 0) publish(glam + 3 * H, db2);
+  if (CORR) {
+    double* gc = glam + 3 * H + 1;
+#pragma unroll
+    for (int u = 0; u < PAIRS; ++u) {
+      const int pr = tid + u * ST_THREADS, j = pr % Hc, k = pr / Hc;
+      if (k >= C) continue;
+      publish(gc + j * 2 * C + k, gWy[u]);
+      publish(gc + j * 2 * C + C + k, gWp[u]);
+      publish(gc + Hc * 2 * C + Hc + k * Hc + j, gW2[u]);
+      if (k == 0) publish(gc + Hc * 2 * C + j, gb1[u]);
+      if (j == 0) publish(gc + Hc * 2 * C + Hc + C * Hc + k, gb2[u]);
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    if (a.eps_user) *a.eps_user = skip ? 0.f : eps;
-    if (a.do_update && !skip) a.counters[1] = t;
-  }
+  if (!last_block(a.ticket, total, &s_last)) return;
+  meta_update(a.mu, a.part, nblk);
 }
 }  // namespace
 
+int stage_blocks(int B) {
+  const int n = (B + ST_SAMPLES - 1) / ST_SAMPLES;
+  return n < STAGE_MAX_BLOCKS ? n : STAGE_MAX_BLOCKS;
+}
 void launch_sample_stage(hipStream_t st, const SampleStageArgs& a) {
   ProfScope ps(st, F_SAMPLE_STAGE, 0.0);
-  launch_kernel(ps, k_sample_stage, 1, 256, 0, st, a);
+  const bool corr = a.Hc > 0 && a.mode != STAGE_META && a.pos_loss == nullptr;   // the clean batch keeps its hard labels
+  const int run = (a.B + stage_blocks(a.B) - 1) / stage_blocks(a.B), nblk = (a.B + run - 1) / run;
+  const dim3 grid(nblk + (a.step.counters != nullptr ? 1 : 0), a.mode == STAGE_GLAM ? 2 : 1);   // a base step's scalars: one workgroup more
+  if (corr) launch_kernel(ps, k_sample_stage<true>, grid, ST_THREADS, 0, st, a, run, nblk);
+  else launch_kernel(ps, k_sample_stage<false>, grid, ST_THREADS, 0, st, a, run, nblk);
 }
-void launch_meta_update(hipStream_t st, const MetaUpdateArgs& a) { k_meta_update<<<1, 256, 0, st>>>(a); }
 
 }  // namespace sama
