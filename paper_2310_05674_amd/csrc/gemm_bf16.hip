@@ -336,15 +336,13 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
     }
     if (res32 != nullptr) { c[0] += rr32.x; c[1] += rr32.y; c[2] += rr32.z; c[3] += rr32.w; }
     if (act == GEMM_ACT_GELU_FWD) {
-      if (C16_pre != nullptr) {   // kept for a backward pass, which sees it rounded: the activation is taken from that
-        uint2 pk;
-        pk.x = pack_bf16x2(c[0], c[1]);
-        pk.y = pack_bf16x2(c[2], c[3]);
-        *reinterpret_cast<uint2*>(C16_pre + o) = pk;
-        c[0] = bf16_to_f32((bf16_t)pk.x); c[1] = bf16_to_f32((bf16_t)(pk.x >> 16));
-        c[2] = bf16_to_f32((bf16_t)pk.y); c[3] = bf16_to_f32((bf16_t)(pk.y >> 16));
-      }
-      c[0] = gelu_f(c[0]); c[1] = gelu_f(c[1]); c[2] = gelu_f(c[2]); c[3] = gelu_f(c[3]);
+      uint2 pk;
+      pk.x = pack_bf16x2(c[0], c[1]);
+      pk.y = pack_bf16x2(c[2], c[3]);
+      if (C16_pre != nullptr) *reinterpret_cast<uint2*>(C16_pre + o) = pk;   // forward-only passes do not keep it
+      // the backward pass sees the rounded pre-activation, so the activation is taken from it too
+      c[0] = gelu_f(bf16_to_f32((bf16_t)pk.x)); c[1] = gelu_f(bf16_to_f32((bf16_t)(pk.x >> 16)));
+      c[2] = gelu_f(bf16_to_f32((bf16_t)pk.y)); c[3] = gelu_f(bf16_to_f32((bf16_t)(pk.y >> 16)));
     } else if (act == GEMM_ACT_GELU_BWD) {
       c[0] *= dgelu_f(bf16_to_f32((bf16_t)axv.x)); c[1] *= dgelu_f(bf16_to_f32((bf16_t)(axv.x >> 16)));
       c[2] *= dgelu_f(bf16_to_f32((bf16_t)axv.y)); c[3] *= dgelu_f(bf16_to_f32((bf16_t)(axv.y >> 16)));
