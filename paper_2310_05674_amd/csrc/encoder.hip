@@ -129,7 +129,7 @@ class EncoderModel : public Model {
     HeadView h{};                                   // position 0 of the fp32 output of the last LayerNorm
     h.x = res_[0]; h.stride = (int64_t)S_ * d_; h.pass_stride = (int64_t)M * d_; h.k = d_;
     h.pv = ParamView{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, 0};
-    h.w_off = wc_; h.b_off = bc_;
+    h.w_off = wc_; h.b_off = bc_; h.dots = true;
     return h;
   }
 

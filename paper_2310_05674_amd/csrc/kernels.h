@@ -160,6 +160,7 @@ struct HeadView {
   const float* x; int64_t stride, pass_stride;
   int k;
   ParamView pv; int64_t w_off, b_off;
+  bool dots;   // few rows of many features: each logit a dot product of one wave; otherwise fp32 matrix-core tiles
 };
 struct SampleStageArgs {
   HeadView head;

@@ -85,6 +85,33 @@ __device__ void head_logits(const HeadView& h, int pass, int i_begin, int n_own,
   }
 }
 
+// The same with a wave per sample: 64 strided partial sums in fp32, joined by a shuffle tree.  The losses of the two passes of
+// Eq. 5 differ in their last digits only, and a deep model's gradients follow those of its logits, so what the
+// encoder's logits are rounded to is kept independent of how a workgroup's tiles split the features.
+__device__ void head_dots(const HeadView& h, int pass, int i_begin, int n_own, int C, double* __restrict__ s_z) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float s = pass == 0 ? h.pv.scale() : -h.pv.scale();
+  constexpr int CU = 4;   // classes at a time
+  for (int i = wave; i < n_own; i += FWAVES) {
+    const float* x = h.x + pass * h.pass_stride + (int64_t)(i_begin + i) * h.stride;
+    for (int c0 = 0; c0 < C; c0 += CU) {
+      float acc[CU] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+      for (int k = lane; k < h.k; k += 64) {
+        const float xk = x[k];
+#pragma unroll
+        for (int u = 0; u < CU; ++u) acc[u] = fmaf(xk, h.pv.at(h.w_off + (int64_t)min(c0 + u, C - 1) * h.k + k, s), acc[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < CU; ++u) {
+        const float z = wave_sum(acc[u]);
+        if (lane == 0 && c0 + u < C) s_z[i * 64 + c0 + u] = (double)(z + h.pv.at(h.b_off + c0 + u, s));
+      }
+    }
+  }
+  __syncthreads();
+}
+
 // every lane of a group of sixteen gets the sum / maximum over the group
 __device__ __forceinline__ double sum16(double x) {
 #pragma unroll
@@ -195,7 +222,10 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
   }
   const double inv_beff = beff > 0.0 ? 1.0 / beff : 0.0;
   __syncthreads();
-  if (!seq_mode) head_logits(a.head, pass, i_begin, n_own, C, s_hred, s_z);
+  if (!seq_mode) {
+    if (a.head.dots) head_dots(a.head, pass, i_begin, n_own, C, s_z);
+    else head_logits(a.head, pass, i_begin, n_own, C, s_hred, s_z);
+  }
   const float* W1 = s_lam; const float* b1 = s_lam + H; const float* W2 = s_lam + 2 * H;
   const double b2 = (double)s_lam[3 * H];
   const float* W1c = s_lc; const float* b1c = s_lc + Hc * 2 * C; const float* W2c = b1c + Hc; const float* b2c = W2c + C * Hc;
