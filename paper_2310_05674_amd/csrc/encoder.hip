@@ -1,6 +1,7 @@
 // Post-LN transformer encoder classifier in bf16 with fp32 accumulation: the explicit forward / backward kernel
 // sequence (no autograd).  x0 = LN(tok[ids] + pos); per layer x <- LN1(x + Attn(x)), x <- LN2(x + FFN(x));
 // logits = x_L[:, 0] Wc^T + bc.  Residual sums and every LayerNorm input stay fp32; GEMM operands are bf16.
+#include <algorithm>
 #include "kernels.h"
 #include "model.h"
 
@@ -25,14 +26,15 @@ class EncoderModel : public Model {
     }
     tok_ = find("tok_emb"); pos_ = find("pos_emb"); eg_ = find("emb_ln_g"); eb_ = find("emb_ln_b"); wc_ = find("Wc"); bc_ = find("bc");
     wm_ = find("Wmlm"); bm_ = find("bmlm");
-    P_ = wm_ >= 0 ? (c.max_aux_masked + 63) / 64 * 64 : 0;
+    Pmax_ = wm_ >= 0 ? (c.max_aux_masked + 63) / 64 * 64 : 0;
   }
   int n_classes() const override { return C_; }
   bool has_mlm() const override { return wm_ >= 0; }
   int mlm_stride() const override { return P_; }
 
   void plan(BumpAlloc& ws, int max_b) override {
-    const size_t M = (size_t)max_b * S_;
+    const size_t sel = std::max(((size_t)max_b * SELECT_SEQ_ROWS + 63) / 64 * 64, (size_t)Pmax_);   // most selected rows
+    const size_t M = (size_t)max_b * S_;                                                            // >= sel
     X_.resize(L_ + 1); qkv_.resize(L_); lse_.resize(L_); ao_.resize(L_); pre1_.resize(L_); mean1_.resize(L_); rstd1_.resize(L_);
     x1_.resize(L_); fpre_.resize(L_); fact_.resize(L_); pre2_.resize(L_); mean2_.resize(L_); rstd2_.resize(L_);
     // Forward-only passes run in activation slot 0 and ping-pong between X_[0] / X_[1]; the + and the - pass of
@@ -49,6 +51,7 @@ class EncoderModel : public Model {
     dX_[0] = ws.take<float>(M * d_); dX_[1] = ws.take<float>(M * d_);
     res_[0] = ws.take<float>(2 * M * d_); res_[1] = ws.take<float>(2 * M * d_);
     ds32_ = ws.take<float>(M * d_); do_ = ws.take<bf16_t>(M * d_);
+    ao_sel_ = ws.take<bf16_t>(2 * sel * d_); res_sel_ = ws.take<float>(2 * sel * d_); do_sel_ = ws.take<bf16_t>(sel * d_);
     // What a layer's weight-gradient launches read exists twice (layer parity): they run on a second stream while the
     // next layer's backward chain already writes the other set.
     for (int p = 0; p < 2; ++p) {
@@ -61,10 +64,11 @@ class EncoderModel : public Model {
       lnpart_[p][0] = ws.take<float>(nblk * 3 * d_); lnpart_[p][1] = ws.take<float>(nblk * 3 * d_);
       cspart_[p][0] = ws.take<float>(nrb * wide); cspart_[p][1] = ws.take<float>(nrb * wide);
     }
-    if (has_mlm()) {   // masked-token head: P_ positions (a multiple of 64, zero rows beyond the batch's), two stacked passes
-      hm_ = ws.take<bf16_t>((size_t)2 * P_ * d_); hm_lo_ = ws.take<bf16_t>((size_t)2 * P_ * d_); zt_ = ws.take<float>((size_t)2 * P_ * V_); lse_pos_ = ws.take<float>((size_t)2 * P_);
-      dzt_ = ws.take<bf16_t>((size_t)P_ * V_); dhm_ = ws.take<float>((size_t)GEMM_MAX_BATCH * P_ * d_);
-      cs_mlm_ = ws.take<float>((size_t)((P_ + COLSUM_ROWS - 1) / COLSUM_ROWS) * V_);
+    if (has_mlm()) {   // masked-token head: up to Pmax_ positions, two stacked passes
+      const size_t P = Pmax_;
+      hm_ = ws.take<bf16_t>(2 * P * d_); hm_lo_ = ws.take<bf16_t>(2 * P * d_); zt_ = ws.take<float>(2 * P * V_); lse_pos_ = ws.take<float>(2 * P);
+      dzt_ = ws.take<bf16_t>(P * V_); dhm_ = ws.take<float>((size_t)GEMM_MAX_BATCH * P * d_);
+      cs_mlm_ = ws.take<float>((P + COLSUM_ROWS - 1) / COLSUM_ROWS * V_);
     }
   }
 
@@ -89,15 +93,34 @@ class EncoderModel : public Model {
     launch_gemm_bf16_batch(st, g, nw);
   }
 
+  // What follows the last attention is row by row, and of its result only position 0 of each sequence (the classifier) or
+  // the masked positions are read, so the last layer's output projection, LayerNorms and FFN, 9/12 of its matrix work, run on
+  // those rows alone, side by side; the other rows have no influence on a result and their gradients are zero.  A pass that
+  // keeps what the backward of both heads needs (n = 0) stays on all rows: the masked ones lie in nearly every group of 16 rows.
+  RowSelect select(const sama_batch& b, bool keep, const MlmBatch* mb) const {
+    RowSelect s{};
+    s.S = S_;
+    if (mb != nullptr) {
+      if (keep) return s;
+      s.n_mask = mb->n_mask; s.mask_rows = mb->rows; s.mask_base = mb->row_base; s.mask_total = mb->rows_in_batch;
+      s.n = (mb->n_mask + 63) / 64 * 64;
+    } else {
+      s.n_cls = b.n;
+      s.n = (b.n * SELECT_SEQ_ROWS + 63) / 64 * 64;
+    }
+    return s;
+  }
+
   // nw = 1: one pass with weights w[0].  nw = 2: the theta + eps v and theta - eps v passes of Eq. 5 on the same
   // batch, stacked along the row dimension (forward only, keep must be false).
-  HeadView run_forward(hipStream_t st, const PassWeights* w, int nw, const sama_batch& b, bool keep) {
-    const int B = b.n, M = B * S_, R = nw * M;
-    ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};
+  HeadView run_forward(hipStream_t st, const PassWeights* w, int nw, const sama_batch& b, bool keep, const MlmBatch* mb) {
+    const int B = b.n, M = B * S_;
+    const RowSelect sel = select(b, keep, mb);
+    ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};   // flips behind the first pass's rows
     LnFwdArgs e{};
     e.x = nullptr; e.ids = (const int32_t*)b.x; e.ids_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep ? pre0_ : nullptr;
     e.pv = pv; e.g_off = eg_; e.b_off = eb_; e.y = X_[0]; e.y32 = res_[0]; e.mean = keep ? mean0_ : nullptr; e.rstd = keep ? rstd0_ : nullptr;
-    e.M = R; e.d = d_;
+    e.M = nw * M; e.d = d_;
     launch_ln_fwd(st, e);
     for (int l = 0; l < L_; ++l) {
       const int s = keep ? l : 0;                       // activation slot: forward-only passes reuse slot 0
@@ -108,46 +131,52 @@ class EncoderModel : public Model {
       g.C16 = qkv_[s];
       fwd_linear(st, w, nw, xin, d_, o.Wqkv, 3 * d_, o.bqkv, M, g);
       launch_attention_fwd(st, qkv_[s], ao_[s], keep ? lse_[s] : nullptr, nw * B, S_, heads_, d_, b.seq_len, B);
+      const bool last = l == L_ - 1 && sel.n > 0;
+      const int rows = last ? sel.n : M;            // of one pass, from here on
+      if (last) {
+        launch_select_rows(st, sel, nw, M, d_, ao_[s], res_[0], ao_sel_, res_sel_);
+        if (nw == 2) pv.flip_row = rows;
+      }
       g = GemmBf16Args{};
-      g.res32 = res_[0]; g.C32 = pre1_[s];          // the residual stream stays fp32
-      fwd_linear(st, w, nw, ao_[s], d_, o.Wo, d_, o.bo, M, g);
+      g.res32 = last ? res_sel_ : res_[0]; g.C32 = pre1_[s];          // the residual stream stays fp32
+      fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g);
       LnFwdArgs n1{};
       n1.x = pre1_[s]; n1.pv = pv; n1.g_off = o.ln1g; n1.b_off = o.ln1b; n1.y = x1_[s]; n1.y32 = res_[1];
-      n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = R; n1.d = d_;
+      n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = nw * rows; n1.d = d_;
       launch_ln_fwd(st, n1);
       g = GemmBf16Args{};
       g.act = GEMM_ACT_GELU_FWD; g.C16_pre = keep ? fpre_[s] : nullptr; g.C16 = fact_[s];   // only a backward pass reads the pre-activation
-      fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, M, g);
+      fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g);
       g = GemmBf16Args{};
       g.res32 = res_[1]; g.C32 = pre2_[s];
-      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, M, g);
+      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g);
       LnFwdArgs n2{};
       n2.x = pre2_[s]; n2.pv = pv; n2.g_off = o.ln2g; n2.b_off = o.ln2b; n2.y = xout; n2.y32 = res_[0];
-      n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = R; n2.d = d_;
+      n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = nw * rows; n2.d = d_;
       launch_ln_fwd(st, n2);
     }
     HeadView h{};                                   // position 0 of the fp32 output of the last LayerNorm
-    h.x = res_[0]; h.stride = (int64_t)S_ * d_; h.pass_stride = (int64_t)M * d_; h.k = d_;
+    h.x = res_[0]; h.stride = (int64_t)(sel.n > 0 ? SELECT_SEQ_ROWS : S_) * d_; h.pass_stride = (int64_t)(sel.n > 0 ? sel.n : M) * d_; h.k = d_;
     h.pv = ParamView{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, 0};
     h.w_off = wc_; h.b_off = bc_; h.dots = true;
     return h;
   }
 
-  HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep) override {
-    return run_forward(st, &w, 1, b, keep);
+  HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep, const MlmBatch* mb) override {
+    return run_forward(st, &w, 1, b, keep, mb);
   }
-  HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b) override {
+  HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b, const MlmBatch* mb) override {
     const PassWeights w[2] = {wp, wm};
-    return run_forward(st, w, 2, b, false);
+    return run_forward(st, w, 2, b, false, mb);
   }
 
-  void mlm_forward(hipStream_t st, const PassWeights* w, int nw, int pass_rows, bool kept, const MlmBatch& mb,
-                   float* loss_pos) override {
+  void mlm_forward(hipStream_t st, const PassWeights* w, int nw, bool kept, const MlmBatch& mb, float* loss_pos) override {
+    P_ = (mb.n_mask + 63) / 64 * 64;
     // A kept pass (base step) contracts the bf16 hidden states like every other layer.  The +- passes of Eq. 5 feed
     // a loss whose difference is the signal: their hidden states enter as the two-term split of the fp32 LayerNorm
     // output, x_hi (W_hi + W_lo) + x_lo W_hi, so that the rounding of x to bf16 does not bury that difference.
-    if (kept) launch_gather_rows(st, X_[L_], pass_rows, mb.row_base, mb.rows_in_batch, mb.rows, mb.n_mask, P_, d_, nw, hm_);
-    else launch_gather_rows_split(st, res_[0], pass_rows, mb.row_base, mb.rows_in_batch, mb.rows, mb.n_mask, P_, d_, nw, hm_, hm_lo_);
+    if (kept) launch_select_rows(st, masked(mb), 1, 0, d_, X_[L_], nullptr, hm_, nullptr);
+    else launch_split_rows(st, res_[0], (int64_t)P_ * d_, mb.n_mask, P_, d_, nw, hm_, hm_lo_);   // such a pass ends on the masked rows
     GemmBf16Args g{};
     g.C32 = zt_;
     fwd_linear(st, w, nw, hm_, d_, wm_, V_, bm_, P_, g);
@@ -164,6 +193,8 @@ class EncoderModel : public Model {
     }
     launch_mlm_ce(st, zt_, V_, P_, mb.tgt, mb.n_mask, nw, loss_pos, lse_pos_);
   }
+
+  RowSelect masked(const MlmBatch& mb) const { return select(sama_batch{}, false, &mb); }
 
   // dW[N x K] = dY^T . X into `out`
   GemmBf16Args wgrad(const bf16_t* dY, int N, const bf16_t* X, int K, int M, float* out) const {
@@ -214,11 +245,11 @@ class EncoderModel : public Model {
   void run_backward(hipStream_t st, const PassWeights& w, const sama_batch& b, const float* dlogits, float* grad,
                     const MlmBatch* mb, const float* coef_pos) {
     const int B = b.n, M = B * S_;
-    const int nblk = (M + LN_BWD_ROWS - 1) / LN_BWD_ROWS;
+    const RowSelect sel = select(b, true, mb);
     float* dx = dX_[0];
     float* dx_next = dX_[1];
-    launch_fill_f32(st, dx, 0.f, (int64_t)M * d_);
-    launch_head_bwd(st, res_[0], S_, d_, B, C_, w.theta, wc_, bc_, dlogits, grad, dx);
+    launch_fill_f32(st, dx, 0.f, (int64_t)(sel.n > 0 ? sel.n : M) * d_);
+    launch_head_bwd(st, res_[0], sel.n > 0 ? SELECT_SEQ_ROWS : S_, d_, B, C_, w.theta, wc_, bc_, dlogits, grad, dx);
     if (mb) mlm_backward(st, w, *mb, coef_pos, grad, dx);
     else if (has_mlm()) {   // a loss without masked-token terms leaves the head's gradient at zero
       launch_fill_f32(st, grad + wm_, 0.f, (int64_t)V_ * d_);
@@ -238,30 +269,37 @@ class EncoderModel : public Model {
       if (two && side_busy_[p]) { (void)hipStreamWaitEvent(st, ev_side_[p], 0); side_busy_[p] = false; }
       bf16_t* const ds2 = ds16_[p][0]; bf16_t* const ds1 = ds16_[p][1]; bf16_t* const dpre = dpre_[p]; bf16_t* const dqkv = dqkv_[p];
       GemmBf16Args wg[4];
+      const bool last = l == L_ - 1 && sel.n > 0;  // the gradient arrives, and stays down to the output projection, on the selected rows
+      const int rows = last ? sel.n : M;
       // LN2
-      LnBwdArgs n2{dx, pre2_[l], mean2_[l], rstd2_[l], w.theta + o.ln2g, ds32_, ds2, lnpart_[p][0], M, d_};
+      LnBwdArgs n2{dx, pre2_[l], mean2_[l], rstd2_[l], w.theta + o.ln2g, ds32_, ds2, lnpart_[p][0], rows, d_};
       launch_ln_bwd(st, n2);
       // FFN
-      wg[0] = wgrad(ds2, d_, fact_[l], ffn_, M, grad + o.W2);
-      GemmBf16Args g = dgrad(w, ds2, d_, o.W2, ffn_, M);
+      wg[0] = wgrad(ds2, d_, fact_[l], ffn_, rows, grad + o.W2);
+      GemmBf16Args g = dgrad(w, ds2, d_, o.W2, ffn_, rows);
       g.act = GEMM_ACT_GELU_BWD; g.aux16 = fpre_[l]; g.C16 = dpre;
       launch_gemm_bf16(st, g);
-      wg[1] = wgrad(dpre, ffn_, x1_[l], d_, M, grad + o.W1);
-      g = dgrad(w, dpre, ffn_, o.W1, d_, M);
+      wg[1] = wgrad(dpre, ffn_, x1_[l], d_, rows, grad + o.W1);
+      g = dgrad(w, dpre, ffn_, o.W1, d_, rows);
       g.res32 = ds32_; g.C32 = dx_next;                       // + the residual branch
       launch_gemm_bf16(st, g);
       // LN1
-      LnBwdArgs n1{dx_next, pre1_[l], mean1_[l], rstd1_[l], w.theta + o.ln1g, ds32_, ds1, lnpart_[p][1], M, d_};
+      LnBwdArgs n1{dx_next, pre1_[l], mean1_[l], rstd1_[l], w.theta + o.ln1g, ds32_, ds1, lnpart_[p][1], rows, d_};
       launch_ln_bwd(st, n1);
       // attention
-      wg[2] = wgrad(ds1, d_, ao_[l], d_, M, grad + o.Wo);
-      g = dgrad(w, ds1, d_, o.Wo, d_, M);
-      g.C16 = do_;
+      wg[2] = wgrad(ds1, d_, last ? ao_sel_ : ao_[l], d_, rows, grad + o.Wo);
+      g = dgrad(w, ds1, d_, o.Wo, d_, rows);
+      g.C16 = last ? do_sel_ : do_;
       launch_gemm_bf16(st, g);
+      const float* dres = ds32_;                              // the residual branch around the attention
+      if (last) {
+        launch_spread_rows(st, sel, M, d_, do_sel_, ds32_, do_, dx_next);
+        dres = dx_next;
+      }
       launch_attention_bwd(st, qkv_[l], ao_[l], do_, lse_[l], dqkv, B, S_, heads_, d_, b.seq_len, B);
       wg[3] = wgrad(dqkv, 3 * d_, X_[l], d_, M, grad + o.Wqkv);
       g = dgrad(w, dqkv, 3 * d_, o.Wqkv, d_, M);
-      g.res32 = ds32_; g.C32 = dx;                            // gradient w.r.t. the layer input
+      g.res32 = dres; g.C32 = dx;                             // gradient w.r.t. the layer input
       if (two) {   // everything the side launches read is written by now (the last dgrad only reads dqkv)
         (void)hipEventRecord(ev_chain_[p], st);
         (void)hipStreamWaitEvent(side_, ev_chain_[p], 0);
@@ -270,14 +308,15 @@ class EncoderModel : public Model {
       const bool sink_now = two && g_side_sink && sink_ != nullptr;
       if (sink_now) (void)hipEventRecord(ev_last_[p], st);   // behind the layer's last read of its own weights
       launch_gemm_bf16_batch(ss, wg, 4);
-      const ColsumJob cj[2] = {{dpre, M, ffn_, cspart_[p][0]}, {dqkv, M, 3 * d_, cspart_[p][1]}};
+      const ColsumJob cj[2] = {{dpre, rows, ffn_, cspart_[p][0]}, {dqkv, M, 3 * d_, cspart_[p][1]}};
       launch_colsum_partial_multi(ss, cj, 2);
-      const int nrb = (M + COLSUM_ROWS - 1) / COLSUM_ROWS;
+      const int nblk = M / LN_BWD_ROWS, nrb = M / COLSUM_ROWS;   // S is a multiple of 64
+      const int ls = last ? S_ / LN_BWD_ROWS : 0, lk = SELECT_SEQ_ROWS / LN_BWD_ROWS, cs = last ? S_ / COLSUM_ROWS : 0, ck = SELECT_SEQ_ROWS / COLSUM_ROWS;
       const ReduceRowsJob rj[4] = {
-          {lnpart_[p][0], nblk, 3 * d_, d_, d_, {grad + o.ln2g, grad + o.ln2b, grad + o.b2}},
-          {lnpart_[p][1], nblk, 3 * d_, d_, d_, {grad + o.ln1g, grad + o.ln1b, grad + o.bo}},
-          {cspart_[p][0], nrb, ffn_, 0, ffn_, {grad + o.b1, nullptr, nullptr}},
-          {cspart_[p][1], nrb, 3 * d_, 0, 3 * d_, {grad + o.bqkv, nullptr, nullptr}}};
+          {lnpart_[p][0], nblk, 3 * d_, d_, d_, {grad + o.ln2g, grad + o.ln2b, grad + o.b2}, ls, lk},
+          {lnpart_[p][1], nblk, 3 * d_, d_, d_, {grad + o.ln1g, grad + o.ln1b, grad + o.bo}, ls, lk},
+          {cspart_[p][0], nrb, ffn_, 0, ffn_, {grad + o.b1, nullptr, nullptr}, cs, ck},
+          {cspart_[p][1], nrb, 3 * d_, 0, 3 * d_, {grad + o.bqkv, nullptr, nullptr}, 0, 0}};
       launch_reduce_rows_multi(ss, rj, 4);
       if (two) { (void)hipEventRecord(ev_side_[p], side_); side_busy_[p] = true; }
       if (sink_now) {   // this layer's gradients are final (matrices and vectors are one range each); a consumer may
@@ -292,7 +331,7 @@ class EncoderModel : public Model {
       if (two && side_busy_[p]) { (void)hipStreamWaitEvent(st, ev_side_[p], 0); side_busy_[p] = false; }
     LnBwdArgs n0{dx, pre0_, mean0_, rstd0_, w.theta + eg_, ds32_, nullptr, lnpart_[0][0], M, d_};
     launch_ln_bwd(st, n0);
-    launch_reduce_rows(st, lnpart_[0][0], nblk, 3 * d_, d_, d_, grad + eg_, grad + eb_, nullptr);
+    launch_reduce_rows(st, lnpart_[0][0], M / LN_BWD_ROWS, 3 * d_, d_, d_, grad + eg_, grad + eb_, nullptr);
     launch_fill_f32(st, grad + tok_, 0.f, (int64_t)V_ * d_);
     launch_embedding_bwd(st, ds32_, (const int32_t*)b.x, B, S_, d_, V_, grad + tok_, grad + pos_);
   }
@@ -325,7 +364,7 @@ class EncoderModel : public Model {
   int L_, d_, heads_, ffn_, S_, V_, C_;
   std::vector<LayerOff> off_;
   int64_t tok_, pos_, eg_, eb_, wc_, bc_, wm_, bm_;
-  int P_ = 0;   // masked-token head: padded maximum number of positions
+  int Pmax_ = 0, P_ = 0;   // masked-token head: most positions, and those of the last pass (multiples of 64)
   bf16_t* hm_ = nullptr; bf16_t* hm_lo_ = nullptr; float* zt_ = nullptr; float* lse_pos_ = nullptr; bf16_t* dzt_ = nullptr; float* dhm_ = nullptr;
   float* cs_mlm_ = nullptr;
   std::vector<bf16_t*> X_, qkv_, ao_, x1_, fpre_, fact_;
@@ -334,6 +373,7 @@ class EncoderModel : public Model {
   float* dX_[2] = {nullptr, nullptr};
   float* res_[2] = {nullptr, nullptr};   // fp32 LayerNorm outputs: the residual stream of the current forward pass
   float* ds32_ = nullptr; bf16_t* do_ = nullptr;
+  bf16_t *ao_sel_ = nullptr, *do_sel_ = nullptr; float* res_sel_ = nullptr;   // compact rows of the last layer
   bf16_t* ds16_[2][2] = {}; bf16_t* dpre_[2] = {}; bf16_t* dqkv_[2] = {};   // [layer parity]
   float* lnpart_[2][2] = {}; float* cspart_[2][2] = {};
   hipStream_t side_ = nullptr; hipEvent_t ev_chain_[2] = {}, ev_side_[2] = {}, ev_last_[2] = {};

@@ -191,7 +191,15 @@ __global__ __launch_bounds__(256) void k_reduce_rows(ReduceRowsMulti m) {
   if (c < a.N) {
     const float* p = a.partial + (int64_t)v * a.vstride + c;
 #pragma unroll 4
-    for (int r = rg; r < a.nrows; r += 8) acc += p[(int64_t)r * a.stride];
+    for (int r = rg; r < a.nrows; r += 8) {
+      int at = r;
+      if (a.seq_blocks > 0) {
+        const int s = r / a.seq_blocks, o = r - s * a.seq_blocks;
+        if (o >= a.kept_blocks) continue;
+        at = s * a.kept_blocks + o;
+      }
+      acc += p[(int64_t)at * a.stride];
+    }
   }
   s_part[rg][cl] = acc;
   __syncthreads();
@@ -540,6 +548,35 @@ __global__ __launch_bounds__(256) void k_head_bwd_x(int S, int d, int B, int C, 
   dx[(int64_t)b * S * d + k] = s;
 }
 
+// =========================================================================================== rows that are read
+// token row of compact row i (i < s.n), or -1 where there is none
+__device__ __forceinline__ int selected_row(const RowSelect& s, int i) {
+  if (s.n_mask > 0) return i < s.n_mask ? s.mask_base + min(max(s.mask_rows[i], 0), s.mask_total - 1) : -1;
+  const int b = i / SELECT_SEQ_ROWS;
+  return b < s.n_cls ? b * s.S + i % SELECT_SEQ_ROWS : -1;
+}
+__global__ __launch_bounds__(256) void k_select_rows(RowSelect s, int pass_rows, int d, const bf16_t* __restrict__ a16,
+                                                     const float* __restrict__ x32, bf16_t* __restrict__ a16_out, float* __restrict__ x32_out) {
+  const int r = selected_row(s, blockIdx.x), nq = d >> 2;
+  const int64_t from = (int64_t)blockIdx.y * pass_rows + max(r, 0), to = (int64_t)blockIdx.y * s.n + blockIdx.x;
+  for (int q = threadIdx.x; q < nq; q += 256) {
+    reinterpret_cast<uint2*>(a16_out + to * d)[q] = r >= 0 ? reinterpret_cast<const uint2*>(a16 + from * d)[q] : make_uint2(0u, 0u);
+    if (x32 != nullptr)
+      reinterpret_cast<float4*>(x32_out + to * d)[q] = r >= 0 ? reinterpret_cast<const float4*>(x32 + from * d)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+}
+__global__ __launch_bounds__(256) void k_spread_rows(RowSelect s, int d, const bf16_t* __restrict__ a16, const float* __restrict__ x32,
+                                                     bf16_t* __restrict__ a16_out, float* __restrict__ x32_out) {
+  const int64_t to = blockIdx.x;
+  const int b = blockIdx.x / s.S, p = blockIdx.x % s.S, nq = d >> 2;
+  const bool kept = p < SELECT_SEQ_ROWS;
+  const int64_t from = kept ? b * SELECT_SEQ_ROWS + p : 0;
+  for (int q = threadIdx.x; q < nq; q += 256) {
+    reinterpret_cast<uint2*>(a16_out + to * d)[q] = kept ? reinterpret_cast<const uint2*>(a16 + from * d)[q] : make_uint2(0u, 0u);
+    reinterpret_cast<float4*>(x32_out + to * d)[q] = kept ? reinterpret_cast<const float4*>(x32 + from * d)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+}
+
 // =========================================================================================== embedding gradients
 __global__ __launch_bounds__(256) void k_pos_grad(const float* __restrict__ demb, int B, int S, int d, float* __restrict__ g_pos) {
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -695,6 +732,15 @@ void launch_head_bwd(hipStream_t st, const float* x, int S, int d, int B, int C,
   ProfScope ps(st, F_OTHER, 0.0);
   launch_kernel(ps, k_head_bwd_w, (C * d + 255) / 256, 256, 0, st, x, S, d, B, C, dlogits, grad + wc_off, grad + bc_off);
   launch_kernel(ps, k_head_bwd_x, (B * d + 255) / 256, 256, 0, st, S, d, B, C, theta + wc_off, dlogits, dx);
+}
+void launch_select_rows(hipStream_t st, const RowSelect& s, int nw, int pass_rows, int d, const bf16_t* a16, const float* x32,
+                        bf16_t* a16_out, float* x32_out) {
+  ProfScope ps(st, F_OTHER, 12.0 * nw * s.n * d);
+  launch_kernel(ps, k_select_rows, dim3(s.n, nw), 256, 0, st, s, pass_rows, d, a16, x32, a16_out, x32_out);
+}
+void launch_spread_rows(hipStream_t st, const RowSelect& s, int M, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out, float* x32_out) {
+  ProfScope ps(st, F_OTHER, 6.0 * (M + s.n) * d);
+  launch_kernel(ps, k_spread_rows, M, 256, 0, st, s, d, a16, x32, a16_out, x32_out);
 }
 void launch_embedding_bwd(hipStream_t st, const float* demb, const int32_t* ids, int B, int S, int d, int V, float* g_tok, float* g_pos) {
   ProfScope ps(st, F_OTHER, 4.0 * B * S * d);

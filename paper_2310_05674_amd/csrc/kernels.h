@@ -261,7 +261,12 @@ void launch_reduce_rows(hipStream_t, const float* partial, int nrows, int64_t st
 // the same for up to REDUCE_MAX_JOBS independent reductions in one launch (a job with fewer than three outputs
 // leaves the trailing out[] null)
 constexpr int REDUCE_MAX_JOBS = 4;
-struct ReduceRowsJob { const float* partial; int nrows; int64_t stride, vstride; int N; float* out[3]; };
+// A matrix of selected rows (SELECT_SEQ_ROWS of every row_step token rows) is reduced in the order of its token rows: `nrows`
+// counts them all, in blocks of row_step / blocks_per_seq, and those of the rows left out are skipped.
+struct ReduceRowsJob {
+  const float* partial; int nrows; int64_t stride, vstride; int N; float* out[3];
+  int seq_blocks, kept_blocks;              // 0, or: of each seq_blocks blocks the first kept_blocks are there
+};
 void launch_reduce_rows_multi(hipStream_t, const ReduceRowsJob* jobs, int count);
 // first stage of the column sums of up to two bf16 matrices [M x N] (ld = N): partial [ceil(M / COLSUM_ROWS)][N]
 struct ColsumJob { const bf16_t* X; int M, N; float* partial; };
@@ -276,7 +281,23 @@ void launch_attention_fwd(hipStream_t, const bf16_t* qkv, bf16_t* out, float* ls
                           const int32_t* lens, int lens_period);
 void launch_attention_bwd(hipStream_t, const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, const float* lse,
                           bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, int lens_period);
-// dWc, dbc into grad; dx[b*S][:] = dlogits[b] . Wc written into the zero-filled dx [B*S x d]
+// The token rows whose last hidden state is read, side by side in a compact matrix of n rows (a multiple of 64; rows without a
+// token are zero).  Either the first SELECT_SEQ_ROWS positions of each of n_cls sequences -- the classifier reads the first of
+// them, and sums over token rows keep the composition of the groups of 16 that the matrix cores add at a time --, or
+// (n_mask > 0) the masked positions.
+constexpr int SELECT_SEQ_ROWS = 16;
+struct RowSelect {
+  int n, S, n_cls;
+  int n_mask;
+  const int32_t* mask_rows;                 // [n_mask] token row among the mask_total rows from mask_base on, clamped into range
+  int mask_base, mask_total;
+};
+// compact row i of pass k <- row of token i (passes pass_rows apart in the sources, n in the results); x32 / x32_out may be null
+void launch_select_rows(hipStream_t, const RowSelect&, int nw, int pass_rows, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out,
+                        float* x32_out);
+// The adjoint for a selection by sequence: each of the M token rows = its compact row, or zero
+void launch_spread_rows(hipStream_t, const RowSelect&, int M, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out, float* x32_out);
+// dWc, dbc into grad; dx[b*S][:] = dlogits[b] . Wc written into the zero-filled dx; S = rows of x and dx per sequence
 void launch_head_bwd(hipStream_t, const float* x, int S, int d, int B, int C, const float* theta, int64_t wc_off,
                      int64_t bc_off, const float* dlogits, float* grad, float* dx);
 // embedding gradients from demb [B*S x d]: pos_emb rows summed over the batch; tok_emb rows summed over the
@@ -290,13 +311,9 @@ void launch_embedding_bwd(hipStream_t, const float* demb, const int32_t* ids, in
 void launch_aux_cat(hipStream_t, const int32_t* ids_ft, const int32_t* y_ft, const uint8_t* mask_ft, int n_ft,
                     const int32_t* ids_pt, int n_pt, int S, int32_t* ids_out, int32_t* y_out, uint8_t* mask_out,
                     const int32_t* len_ft, const int32_t* len_pt, int32_t* len_out);
-// out[(k P + j)][:] = X[k pass_rows + row_base + rows[j]][:], j < n_mask, k < nw; rows n_mask..P-1 zero; rows[] is
-// clamped to [0, rows_in_batch)
-void launch_gather_rows(hipStream_t, const bf16_t* X, int pass_rows, int row_base, int rows_in_batch, const int32_t* rows,
-                        int n_mask, int P, int d, int nw, bf16_t* out);
-// the same from an fp32 source, as the two-term split hi = bf16(x), lo = bf16(x - hi)
-void launch_gather_rows_split(hipStream_t, const float* X, int pass_rows, int row_base, int rows_in_batch, const int32_t* rows,
-                              int n_mask, int P, int d, int nw, bf16_t* hi, bf16_t* lo);
+// row j of pass k of X (passes pass_stride apart) as the two-term split hi = bf16(x), lo = bf16(x - hi) in row k P + j;
+// rows n_mask..P-1 of a pass are zero
+void launch_split_rows(hipStream_t, const float* X, int64_t pass_stride, int n_mask, int P, int d, int nw, bf16_t* hi, bf16_t* lo);
 // loss_pos[k P + j] = logsumexp(Z[k P + j][:V]) - Z[k P + j][tgt[j]], lse_pos likewise (V % 4 == 0)
 void launch_mlm_ce(hipStream_t, const float* Z, int V, int P, const int32_t* tgt, int n_mask, int nw, float* loss_pos,
                    float* lse_pos);

@@ -1,6 +1,6 @@
 // Masked-token head of the auxiliary task (Sec. 4.3): token logits z_j = x_L[row_j] Wmlm^T + bmlm over the whole
 // vocabulary at each masked position j, loss_j = logsumexp(z_j) - z_j[tgt_j].  The logit GEMMs run in gemm_bf16.hip;
-// here are the HBM-bound kernels around them: gathering the masked rows, the softmax / cross-entropy pass over the
+// here are the HBM-bound kernels around them: the split of the masked rows, the softmax / cross-entropy pass over the
 // [positions x V] logits and its backward, and the scatter of the hidden-state gradient back to the token rows.
 // Position and target indices arrive from the caller's device buffers and are clamped into range before use.
 #include "kernels.h"
@@ -24,29 +24,14 @@ __global__ __launch_bounds__(256) void k_aux_cat(const int32_t* ids_ft, const in
   }
 }
 
-// out[(k P + j)][:] = X[k pass_rows + row_base + rows[j]][:] for j < n_mask, zero rows up to P (d % 8 == 0)
-__global__ __launch_bounds__(128) void k_gather_rows(const bf16_t* X, int pass_rows, int row_base, int rows_in_batch,
-                                                     const int32_t* rows, int n_mask, int P, int d, bf16_t* out) {
-  const int j = blockIdx.x, k = blockIdx.y;
-  uint4* o = reinterpret_cast<uint4*>(out + ((int64_t)k * P + j) * d);
-  if (j < n_mask) {
-    const int r = clampi(rows[j], 0, rows_in_batch - 1);
-    const uint4* s = reinterpret_cast<const uint4*>(X + ((int64_t)k * pass_rows + row_base + r) * d);
-    for (int c = threadIdx.x; c < d / 8; c += 128) o[c] = s[c];
-  } else {
-    for (int c = threadIdx.x; c < d / 8; c += 128) o[c] = make_uint4(0u, 0u, 0u, 0u);
-  }
-}
-
-// The same rows from an fp32 source as a two-term split: hi = bf16(x), lo = bf16(x - hi)  (d % 4 == 0)
-__global__ __launch_bounds__(128) void k_gather_rows_split(const float* X, int pass_rows, int row_base, int rows_in_batch,
-                                                           const int32_t* rows, int n_mask, int P, int d, bf16_t* hi, bf16_t* lo) {
+// Row j of pass k of an fp32 source as a two-term split: hi = bf16(x), lo = bf16(x - hi) for j < n_mask, zero rows up to P
+// (d % 4 == 0)
+__global__ __launch_bounds__(128) void k_split_rows(const float* X, int64_t pass_stride, int n_mask, int P, int d, bf16_t* hi, bf16_t* lo) {
   const int j = blockIdx.x, k = blockIdx.y;
   uint2* oh = reinterpret_cast<uint2*>(hi + ((int64_t)k * P + j) * d);
   uint2* ol = reinterpret_cast<uint2*>(lo + ((int64_t)k * P + j) * d);
   if (j < n_mask) {
-    const int r = clampi(rows[j], 0, rows_in_batch - 1);
-    const float4* s = reinterpret_cast<const float4*>(X + ((int64_t)k * pass_rows + row_base + r) * d);
+    const float4* s = reinterpret_cast<const float4*>(X + k * pass_stride + (int64_t)j * d);
     for (int c = threadIdx.x; c < d / 4; c += 128) {
       const float4 x = s[c];
       const uint2 h = make_uint2(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w));
@@ -159,15 +144,9 @@ void launch_aux_cat(hipStream_t st, const int32_t* ids_ft, const int32_t* y_ft, 
   launch_kernel(ps, k_aux_cat, ((n_ft + n_pt) * S + 255) / 256, 256, 0, st, ids_ft, y_ft, mask_ft, n_ft, ids_pt, n_pt, S, ids_out, y_out, mask_out,
                                                              len_ft, len_pt, len_out);
 }
-void launch_gather_rows(hipStream_t st, const bf16_t* X, int pass_rows, int row_base, int rows_in_batch, const int32_t* rows,
-                        int n_mask, int P, int d, int nw, bf16_t* out) {
-  ProfScope ps(st, F_OTHER, 4.0 * nw * P * d);
-  launch_kernel(ps, k_gather_rows, dim3(P, nw), 128, 0, st, X, pass_rows, row_base, rows_in_batch, rows, n_mask, P, d, out);
-}
-void launch_gather_rows_split(hipStream_t st, const float* X, int pass_rows, int row_base, int rows_in_batch, const int32_t* rows,
-                              int n_mask, int P, int d, int nw, bf16_t* hi, bf16_t* lo) {
+void launch_split_rows(hipStream_t st, const float* X, int64_t pass_stride, int n_mask, int P, int d, int nw, bf16_t* hi, bf16_t* lo) {
   ProfScope ps(st, F_OTHER, 8.0 * nw * P * d);
-  launch_kernel(ps, k_gather_rows_split, dim3(P, nw), 128, 0, st, X, pass_rows, row_base, rows_in_batch, rows, n_mask, P, d, hi, lo);
+  launch_kernel(ps, k_split_rows, dim3(P, nw), 128, 0, st, X, pass_stride, n_mask, P, d, hi, lo);
 }
 void launch_mlm_ce(hipStream_t st, const float* Z, int V, int P, const int32_t* tgt, int n_mask, int nw, float* loss_pos,
                    float* lse_pos) {

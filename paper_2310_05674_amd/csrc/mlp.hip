@@ -48,10 +48,10 @@ class MlpModel : public Model {
     h.w_off = woff_[L_ - 1]; h.b_off = boff_[L_ - 1];
     return h;
   }
-  HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool /*keep*/) override {
+  HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool /*keep*/, const MlmBatch*) override {
     return run_forward(st, &w, 1, b);
   }
-  HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b) override {
+  HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b, const MlmBatch*) override {
     const PassWeights w[2] = {wp, wm};
     return run_forward(st, w, 2, b);
   }

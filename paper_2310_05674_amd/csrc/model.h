@@ -73,20 +73,22 @@ class Model {
   void set_grad_sink(GradSink* s) { sink_ = s; }   // for the next backward() / backward_mlm(); null = none
   // carve activation buffers for batches up to max_b
   virtual void plan(BumpAlloc& ws, int max_b) = 0;
-  // everything up to the classifier for batch `b`; keep = retain what backward needs.  The result says where the features are.
-  virtual HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep) = 0;
+  // everything up to the classifier for batch `b`; keep = retain what backward needs.  The result says where the features
+  // are.  `mb` (models with a masked-token head): the positions that head will read after this pass; a batch without
+  // labels (b.y null) is read by that head only.
+  virtual HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep, const MlmBatch* mb = nullptr) = 0;
   // The theta + eps v and theta - eps v passes of Eq. 5 on the same batch, forward only, stacked in the same launches.
-  virtual HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b) = 0;
+  virtual HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b,
+                                const MlmBatch* mb = nullptr) = 0;
   // grad[n] = d/dtheta sum_i sum_c dlogits[i][c] z_ic, at the unperturbed theta of the last keep=true forward
   virtual void backward(hipStream_t st, const PassWeights& w, const sama_batch& b, const float* dlogits, float* grad) = 0;
   virtual int n_classes() const = 0;
   // ---- masked-token head (models built with one)
   virtual bool has_mlm() const { return false; }
-  virtual int mlm_stride() const { return 0; }   // positions per pass in loss_pos (the padded maximum)
+  virtual int mlm_stride() const { return 0; }   // positions per pass in loss_pos, as the last mlm_forward() wrote it
   // loss_pos[k * mlm_stride() + j] = masked-token loss of position j under pass k (k < nw) of the last forward
-  // (kept = true, nw = 1) or forward_pair (kept = false, nw = 2); pass_rows = token rows of one pass.
-  virtual void mlm_forward(hipStream_t, const PassWeights*, int /*nw*/, int /*pass_rows*/, bool /*kept*/, const MlmBatch&,
-                           float* /*loss_pos*/) {}
+  // (kept = true, nw = 1) or forward_pair (kept = false, nw = 2), which was given the same `mb`
+  virtual void mlm_forward(hipStream_t, const PassWeights*, int /*nw*/, bool /*kept*/, const MlmBatch&, float* /*loss_pos*/) {}
   // backward() with the head's loss added: grad = d/dtheta [sum dlogits . z + sum_j coef_pos[j] loss_pos_j], after a
   // kept forward and mlm_forward on the same batch
   virtual void backward_mlm(hipStream_t, const PassWeights&, const sama_batch&, const float* /*dlogits*/, float* /*grad*/,

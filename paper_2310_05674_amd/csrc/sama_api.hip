@@ -520,14 +520,14 @@ sama_status sama_aux_base_step(sama_ctx* c, const sama_batch* ft, const sama_aux
                  ft->seq_len, pt->seq_len, padded ? c->len_cat : nullptr);
   const sama_batch cat{c->ids_cat, c->y_cat, c->mask_cat, n_ft + n_pt, padded ? c->len_cat : nullptr};
   const PassWeights w = base_weights(c);
-  const HeadView head = c->model->forward(st, w, cat, true);
+  const MlmBatch mb{pt->mask_row, pt->mask_tgt, pt->n_mask, n_ft * S, n_pt * S};
+  const HeadView head = c->model->forward(st, w, cat, true, &mb);
   // finetuning term: mean cross-entropy over the ft rows (the auxiliary rows are masked out of the classifier loss)
   SampleStageArgs sa = class_stage_args(c, STAGE_META, &cat, head);
   sa.loss_scalar = c->scalars + 2; sa.loss_user = loss_out; sa.step = next_step(c);
   launch_sample_stage(st, sa);
   // weighted pretraining term
-  const MlmBatch mb{pt->mask_row, pt->mask_tgt, pt->n_mask, n_ft * S, n_pt * S};
-  c->model->mlm_forward(st, &w, 1, cat.n * S, true, mb, c->loss_pos);
+  c->model->mlm_forward(st, &w, 1, true, mb, c->loss_pos);
   SampleStageArgs sp = aux_stage_args(c, pt, STAGE_BASE, c->losses + n_ft);
   sp.pos_coef = c->coef_pos; sp.loss_scalar = c->scalars + 2; sp.loss_user = loss_out;
   launch_sample_stage(st, sp);
@@ -548,9 +548,9 @@ sama_status sama_aux_eval(sama_ctx* c, const sama_aux_batch* pt, float* losses_o
   const int S = c->cfg.dims[4];
   const sama_batch ptb{pt->ids, nullptr, nullptr, pt->n_seq, pt->seq_len};
   const PassWeights w = base_weights(c);
-  c->model->forward(st, w, ptb, true);        // the head reads the kept last hidden state
   const MlmBatch mb{pt->mask_row, pt->mask_tgt, pt->n_mask, 0, pt->n_seq * S};
-  c->model->mlm_forward(st, &w, 1, pt->n_seq * S, true, mb, c->loss_pos);
+  c->model->forward(st, w, ptb, true, &mb);   // the head reads the kept last hidden state
+  c->model->mlm_forward(st, &w, 1, true, mb, c->loss_pos);
   SampleStageArgs sa = aux_stage_args(c, pt, STAGE_EVAL, losses_out);
   sa.weights = weights_out;
   launch_sample_stage(st, sa);
@@ -572,9 +572,9 @@ static sama_status aux_meta_common(sama_ctx* c, const sama_aux_batch* pt, const 
   // passes 2 and 3 on the auxiliary sequences alone: the finetuning term of L_base does not depend on lambda
   const sama_batch ptb{pt->ids, nullptr, nullptr, pt->n_seq, pt->seq_len};
   const PassWeights w[2] = {pass_weights(c, 1.f, c->lo_p), pass_weights(c, -1.f, fused_nudge ? c->lo_0 : c->lo_m)};
-  c->model->forward_pair(st, w[0], w[1], ptb);
   const MlmBatch mb{pt->mask_row, pt->mask_tgt, pt->n_mask, 0, pt->n_seq * S};
-  c->model->mlm_forward(st, w, 2, pt->n_seq * S, false, mb, c->loss_pos);
+  c->model->forward_pair(st, w[0], w[1], ptb, &mb);
+  c->model->mlm_forward(st, w, 2, false, mb, c->loss_pos);
   SampleStageArgs sg = aux_stage_args(c, pt, STAGE_GLAM, c->losses);
   sg.pos_pass_stride = c->model->mlm_stride();
   sg.mu = meta_update_args(c, hyper_out, eps_out, update);
