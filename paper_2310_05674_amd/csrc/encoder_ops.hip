@@ -190,15 +190,14 @@ __global__ __launch_bounds__(256) void k_reduce_rows(ReduceRowsMulti m) {
   float acc = 0.f;
   if (c < a.N) {
     const float* p = a.partial + (int64_t)v * a.vstride + c;
+    if (a.seq_blocks == 0) {
 #pragma unroll 4
-    for (int r = rg; r < a.nrows; r += 8) {
-      int at = r;
-      if (a.seq_blocks > 0) {
+      for (int r = rg; r < a.nrows; r += 8) acc += p[(int64_t)r * a.stride];
+    } else {
+      for (int r = rg; r < a.nrows; r += 8) {
         const int s = r / a.seq_blocks, o = r - s * a.seq_blocks;
-        if (o >= a.kept_blocks) continue;
-        at = s * a.kept_blocks + o;
+        if (o < a.kept_blocks) acc += p[(int64_t)(s * a.kept_blocks + o) * a.stride];
       }
-      acc += p[(int64_t)at * a.stride];
     }
   }
   s_part[rg][cl] = acc;

@@ -4,6 +4,10 @@
 //
 //   operand slabs go global -> LDS directly (global_load_lds_dwordx4, 1 KB per wave instruction) into dense,
 //   XOR-swizzled stages, NSTAGE - 1 slabs in flight, one barrier per slab; no staging registers
+//   most tiles have waves that do nothing but issue those loads: a wave that issues a slab's loads itself waits for the
+//   address units to take them, a third of the slab's matrix time, before it multiplies.  Against the same tile without them:
+//   256 x 128 hi + lo 6%, 128 x 128 10%, 128 x 96 11%, 128 x 64 4% faster, 128 x 128 single-term TN 16% (geometric means
+//   over 65 and 51 problems); four such waves are 4% faster than two, eight the same as four
 //   an operand whose contraction index is contiguous in memory is staged [row][k] and fetched with 16-byte reads;
 //   one whose contraction index is the strided one (dgrad's W, both operands of wgrad) is staged as it lies in
 //   memory, [k][row], and fetched with the transposing LDS read (ds_read_b64_tr_b16)
@@ -37,21 +41,24 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void gvoid;
 constexpr int LDS_MAX = 160 * 1024;
 
-template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NSTAGE_, bool DUAL_>
+// PW: waves that only load (0: the multiplying waves load for themselves).  SB: see the kernel.
+template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NSTAGE_, bool DUAL_, int PW_ = 0, bool SB_ = false>
 struct Tile {
+  static constexpr int PW = PW_;
+  static constexpr bool SB = SB_;
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_, NSTAGE = NSTAGE_;
   static constexpr bool DUAL = DUAL_;
-  static constexpr int WAVES = WGM * WGN, THREADS = WAVES * 64;
+  static constexpr int WAVES = WGM * WGN, LW = PW > 0 ? PW : WAVES, THREADS = (WAVES + PW) * 64;   // multiplying, loading
   static constexpr int WM = BM / WGM, WN = BN / WGN, XT = WM / 32, YT = WN / 32;
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + (DUAL ? 2 : 1) * B_BYTES;
-  static constexpr int NLA = A_BYTES / 1024 / WAVES, NLB = B_BYTES / 1024 / WAVES;   // wave-level 1 KB loads per slab
+  static constexpr int NLA = A_BYTES / 1024 / LW, NLB = B_BYTES / 1024 / LW;   // 1 KB loads of a loading wave per slab
   static constexpr int NL = NLA + (DUAL ? 2 : 1) * NLB;
   static_assert(LDS_MAX >= NSTAGE * STAGE_BYTES, "stages exceed the 160 KB of LDS");
   static constexpr int LDS_MAIN = NSTAGE * STAGE_BYTES;
   static constexpr int EPI_LD = WN + 8;   // 4 rows apart = 32 banks apart: the two lane halves of a staging write do not collide
   static constexpr int LDS_EPI = WAVES * 32 * EPI_LD * 4;
   static constexpr int LDS_BYTES = LDS_MAIN > LDS_EPI ? LDS_MAIN : LDS_EPI;
-  static_assert(A_BYTES % (1024 * WAVES) == 0 && B_BYTES % (1024 * WAVES) == 0, "slab must split into whole wave loads");
+  static_assert(A_BYTES % (1024 * LW) == 0 && B_BYTES % (1024 * LW) == 0, "slab must split into whole wave loads");
   static_assert(NL * (NSTAGE - 2) <= 63, "vmcnt range");
 };
 
@@ -79,9 +86,17 @@ __device__ __forceinline__ float dgelu_f(float x) {
 //   KC (contraction contiguous, storage [rows][k]): stage [R][BK]; the 16-byte chunk index within a row is XORed
 //     with (row / RP) % NCH so that 16 consecutive rows at one logical chunk fill all 64 banks.
 //   KS (contraction strided, storage [k][rows]): stage [BK][R]; the 64-byte chunk index within a k-row is XORed with
-//     (k-row / RP) % W (RP = k-rows per 256 bytes, W = min(chunks per k-row, 4)) so that the four k-rows one
-//     transposing read touches fill all 64 banks.
+//     chunk_swizzle(k-row) so that the four k-rows one transposing read touches fill all 64 banks.
 // Rows past `nrows` are clamped (their products land in outputs the epilogue never stores).
+// A k-row of R values is R / 32 chunks; four consecutive k-rows have to put one chunk each into the four quarters of the
+// banks.  Rows a multiple of four chunks long all start at the same bank, rows of two chunks pairwise, rows of six at
+// alternating halves; rows of one or three chunks are spread already.
+template <int R>
+__device__ __forceinline__ int chunk_swizzle(int kr) {
+  constexpr int NC = R / 32;
+  static_assert(NC % 4 == 0 || NC == 1 || NC == 2 || NC == 3 || NC == 6, "tile width");
+  return NC % 4 == 0 ? (kr & 3) : (NC == 2 || NC == 6) ? ((kr >> 1) & 1) : 0;
+}
 template <bool KC, int R, int BK>
 __device__ __forceinline__ uint32_t piece_offset(int ldsoff, int row0, int nrows, int64_t ld) {
   if (KC) {
@@ -90,9 +105,9 @@ __device__ __forceinline__ uint32_t piece_offset(int ldsoff, int row0, int nrows
     const int c = p ^ ((r / RP) % NCH);
     return (uint32_t)(((int64_t)min(row0 + r, nrows - 1) * ld + c * 8) * 2);
   } else {
-    constexpr int RBS = R * 2, RP = RBS >= 256 ? 1 : 256 / RBS, W = RBS / 64 < 4 ? RBS / 64 : 4;
+    constexpr int RBS = R * 2;
     const int kr = ldsoff / RBS, q16 = (ldsoff % RBS) / 16;
-    const int ql = (((q16 >> 2) ^ ((kr / RP) % W)) << 2) | (q16 & 3);
+    const int ql = (((q16 >> 2) ^ chunk_swizzle<R>(kr)) << 2) | (q16 & 3);
     return (uint32_t)(((int64_t)kr * ld + min(row0 + ql * 8, nrows - 8)) * 2);
   }
 }
@@ -107,11 +122,11 @@ __device__ __forceinline__ int fetch_lane_offset(int lane, int ks_or_tile) {
     const int s = (rl / RP) % NCH;
     return rl * RB + (((2 * ks_or_tile + hi) ^ s) * 16);                  // per ks
   } else {
-    constexpr int RBS = R * 2, RP = RBS >= 256 ? 1 : 256 / RBS, W = RBS / 64 < 4 ? RBS / 64 : 4;
+    constexpr int RBS = R * 2;
     const int g = lane >> 4, j = lane & 15;
     const int cc = ks_or_tile;                                            // 64-byte chunk of the tile = tile_row0 / 32
-    const int kr = 8 * (g >> 1) + (j >> 2);                               // (kr / RP) % W is the same for kr + 4 and kr + 16
-    return kr * RBS + ((cc ^ ((kr / RP) % W)) * 64) + (16 * (g & 1) + 4 * (j & 3)) * 2;   // per tile
+    const int kr = 8 * (g >> 1) + (j >> 2);                               // the swizzle is the same for kr + 4 and kr + 16
+    return kr * RBS + ((cc ^ chunk_swizzle<R>(kr)) * 64) + (16 * (g & 1) + 4 * (j & 3)) * 2;   // per tile
   }
 }
 
@@ -125,6 +140,9 @@ template <typename T, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int ntiles, int tiles_per_xcd) {
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, XT = T::XT, YT = T::YT, NSTAGE = T::NSTAGE, WAVES = T::WAVES;
   constexpr bool DUAL = T::DUAL;
+  // Whether the operands of a k-step are fetched right before it (fewer registers, the order left to the compiler) instead of
+  // during the step before.  With the transposing reads of a strided operand the three-stage tiles are 7-9% faster that way.
+  constexpr bool SB = T::SB || (!B_KC && T::PW > 0 && NSTAGE == 3);
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -163,40 +181,42 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   const char* const pB2 = reinterpret_cast<const char*>(a.B2);
   const int iters = (!DUAL && pB2 != nullptr) ? 2 * nk : nk;   // non-DUAL tiles contract with hi, then with lo
 
+  const int lw = T::PW > 0 ? wave - WAVES : wave;            // number among the loading waves
+  const bool loader = T::PW == 0 || wave >= WAVES;
   // per-lane global offsets of this wave's loads
   uint32_t offA[T::NLA], offB[T::NLB];
 #pragma unroll
-  for (int q = 0; q < T::NLA; ++q) offA[q] = piece_offset<A_KC, BM, BK>((q * WAVES + wave) * 1024 + lane * 16, i0, a.M, a.lda);
+  for (int q = 0; q < T::NLA; ++q) offA[q] = piece_offset<A_KC, BM, BK>((q * T::LW + lw) * 1024 + lane * 16, i0, a.M, a.lda);
 #pragma unroll
-  for (int q = 0; q < T::NLB; ++q) offB[q] = piece_offset<B_KC, BN, BK>((q * WAVES + wave) * 1024 + lane * 16, j0, a.N, a.ldb);
+  for (int q = 0; q < T::NLB; ++q) offB[q] = piece_offset<B_KC, BN, BK>((q * T::LW + lw) * 1024 + lane * 16, j0, a.N, a.ldb);
   const int64_t stepA = A_KC ? (int64_t)BK * 2 : (int64_t)BK * a.lda * 2;   // bytes per slab
   const int64_t stepB = B_KC ? (int64_t)BK * 2 : (int64_t)BK * a.ldb * 2;
 
   // Direct global -> LDS loads: lane l of a wave-level load lands at (m0) + 16 l.  Written as inline assembly so
   // that the only waits on them are the explicit vmcnt waits below.
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)smem_raw;
-  // All NL wave-level loads of a slab are issued together right after the barrier that frees their stage (spreading
-  // them over the k-steps of the slab computed meanwhile measured 3-8% slower: it shortens the prefetch distance).
+  // All NL loads of a slab are issued together right after the barrier that frees their stage (in waves that also
+  // multiply, spreading them over the k-steps measured 3-8% slower: it shortens the prefetch distance).
   constexpr int KS = BK / 16;
   auto issue = [&](int sl) {
-    if (sl >= iters) return;
+    if (sl >= iters || !loader) return;
     const int stage = sl % NSTAGE;
     const int kq = sl >= nk ? sl - nk : sl;
     const char* ap = pA + kq * stepA;
     const char* bp = (sl >= nk ? pB2 : pB) + kq * stepB;
     const char* b2p = pB2 + kq * stepB;
-    const uint32_t sa = lds0 + stage * T::STAGE_BYTES + wave * 1024;
+    const uint32_t sa = lds0 + stage * T::STAGE_BYTES + lw * 1024;
     const uint32_t sb = sa + T::A_BYTES;
 #pragma unroll
     for (int t = 0; t < T::NL; ++t) {
       if (t < T::NLA) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sa + t * WAVES * 1024), "v"(offA[t]), "s"(ap) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sa + t * T::LW * 1024), "v"(offA[t]), "s"(ap) : "memory", "m0");
       } else if (t < T::NLA + T::NLB) {
         const int q = t - T::NLA;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sb + q * WAVES * 1024), "v"(offB[q]), "s"(bp) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sb + q * T::LW * 1024), "v"(offB[q]), "s"(bp) : "memory", "m0");
       } else {
         const int q = t - T::NLA - T::NLB;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sb + T::B_BYTES + q * WAVES * 1024), "v"(offB[q]), "s"(b2p) : "memory", "m0");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sb + T::B_BYTES + q * T::LW * 1024), "v"(offB[q]), "s"(b2p) : "memory", "m0");
       }
     }
   };
@@ -243,10 +263,11 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
 
   static_assert(KS % 2 == 0, "operand double buffer parity");
   bf16x8 av[2][XT], bv[2][YT], bw[2][DUAL ? YT : 1];
-  // make slab `sl` visible: own loads landed, then everyone's; afterwards the stage of slab sl - 1 is free
+  // make slab `sl` visible: a loading wave's own loads landed, then everyone's; afterwards the stage of slab sl - 1 is free
   auto arrive = [&](int sl) {
     const int younger = iters - 1 - sl;
-    if (younger >= NSTAGE - 2) {
+    if (!loader) {
+    } else if (younger >= NSTAGE - 2) {
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(T::NL * (NSTAGE - 2)) : "memory");
     } else if (NSTAGE >= 4 && younger == NSTAGE - 3) {
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(T::NL * (NSTAGE >= 4 ? NSTAGE - 3 : 0)) : "memory");
@@ -270,10 +291,14 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
       for (int y = 0; y < YT; ++y) bw[buf][y] = fetchB(sb + T::B_BYTES, y, ks);
     }
   };
+  if (T::PW > 0 && loader) {   // the barriers of the others, and the loads
+    for (int i = 0; i < iters; ++i) arrive(i);
+    __syncthreads();
+    return;
+  }
   arrive(0);
-  fetch(0, 0, 0);
   auto mfma_step = [&](int cur) {
-    __builtin_amdgcn_sched_barrier(0);
+    if (!SB) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int x = 0; x < XT; ++x)
 #pragma unroll
@@ -284,26 +309,38 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
 #pragma unroll
         for (int y = 0; y < YT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[cur][x], bw[cur][y], acc[x][y], 0, 0, 0);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if (!SB) __builtin_amdgcn_sched_barrier(0);
   };
-  for (int i = 0; i + 1 < iters; ++i) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int cur = ks & 1;
-      if (ks + 1 < KS) {
-        fetch(i, ks + 1, cur ^ 1);
-      } else {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of slab i are complete
-        arrive(i + 1);
-        fetch(i + 1, 0, cur ^ 1);
+  if (SB) {
+    for (int i = 0; i < iters; ++i) {
+      if (i > 0) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of slab i - 1 are complete
+        arrive(i);
       }
-      mfma_step(cur);
-    }
-  }
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {   // last slab
-    if (ks + 1 < KS) fetch(iters - 1, ks + 1, (ks & 1) ^ 1);
-    mfma_step(ks & 1);
+      for (int ks = 0; ks < KS; ++ks) { fetch(i, ks, 0); mfma_step(0); }
+    }
+  } else {
+    fetch(0, 0, 0);
+    for (int i = 0; i + 1 < iters; ++i) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int cur = ks & 1;
+        if (ks + 1 < KS) {
+          fetch(i, ks + 1, cur ^ 1);
+        } else {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of slab i are complete
+          arrive(i + 1);
+          fetch(i + 1, 0, cur ^ 1);
+        }
+        mfma_step(cur);
+      }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {   // last slab
+      if (ks + 1 < KS) fetch(iters - 1, ks + 1, (ks & 1) ^ 1);
+      mfma_step(ks & 1);
+    }
   }
   __syncthreads();
 
@@ -312,7 +349,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   float* epi = reinterpret_cast<float*>(smem_raw) + wave * 32 * EPI_LD;
   const int cg = lane % LPR, rq = lane / LPR;
   const int gj = j0 + wc + 4 * cg;
-  const bool col_ok = gj < a.N;
+  const bool col_ok = gj < a.N && (LPR * RPP == 64 || lane < LPR * RPP);   // 96-wide wave tiles: 24 lanes a row, two rows
   float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
   if (col_ok && a.bias != nullptr) {
     bias = *reinterpret_cast<const float4*>(a.bias + gj);
@@ -438,68 +475,89 @@ void launch_tile(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count
   launch_kernel(ps, k_gemm_bf16<T, A_KC, B_KC>, 8 * per_xcd, T::THREADS, T::LDS_BYTES, st, b, nt, per_xcd);
 }
 
-// Tile configurations <BM, BN, BK, waves in M, waves in N, stages, DUAL>
-typedef Tile<256, 256, 64, 2, 4, 2, false> TL;    // 8 waves of 128 x 64, 2 stages of 64 KB
-typedef Tile<256, 128, 64, 4, 2, 3, false> TM;    // 8 waves of 64 x 64, 3 stages of 48 KB
-typedef Tile<128, 128, 64, 2, 2, 2, false> TS;    // 4 waves of 64 x 64, 2 stages of 32 KB: two blocks per CU
-typedef Tile<128, 64, 64, 2, 2, 3, false> TX;     // 4 waves of 64 x 32, 3 stages of 24 KB: two blocks per CU
-typedef Tile<128, 64, 64, 2, 2, 4, false> TX4;    // 4 stages: one block per CU, deeper prefetch
-typedef Tile<128, 64, 64, 4, 2, 4, false> TX8;    // 8 waves of 32 x 32: the small tile when one block per CU is all there is
-typedef Tile<128, 128, 64, 4, 2, 3, false> TS8;   // 8 waves of 32 x 64
-typedef Tile<256, 256, 32, 2, 4, 3, true> DL;     // DUAL: 3 stages of 48 KB
-typedef Tile<256, 128, 64, 4, 2, 2, true> DM;     // 2 stages of 64 KB
-typedef Tile<128, 128, 64, 2, 2, 3, true> DS;     // 3 stages of 48 KB
-typedef Tile<128, 64, 64, 2, 2, 2, true> DX;      // 2 stages of 32 KB: two blocks per CU
-typedef Tile<128, 64, 64, 2, 2, 4, true> DX4;     // 4 stages of 32 KB
+// Tiles <BM, BN, BK, multiplying waves in M, in N, stages, hi + lo, loading waves, operands fetched one step at a time>
+typedef Tile<256, 256, 64, 2, 4, 2, false> S1;
+typedef Tile<256, 192, 64, 4, 2, 2, false, 4, true> S2;
+typedef Tile<256, 128, 64, 4, 2, 3, false, 4, true> S3;
+typedef Tile<128, 128, 64, 4, 2, 4, false, 4> S4;
+typedef Tile<128, 64, 64, 4, 2, 4, false, 4> S5;
+typedef Tile<64, 64, 64, 2, 2, 4, false> S6;         // two workgroups per CU
+typedef Tile<128, 128, 64, 4, 2, 2, false> S7;       // two workgroups per CU
+typedef Tile<256, 192, 64, 4, 2, 2, true, 4, true> D1;
+typedef Tile<256, 128, 64, 4, 2, 2, true, 4> D2;
+typedef Tile<128, 128, 64, 4, 2, 3, true, 4> D3;
+typedef Tile<128, 96, 64, 4, 1, 3, true, 4> D4;
+typedef Tile<128, 64, 64, 4, 2, 4, true, 4> D5;
+typedef Tile<64, 64, 64, 2, 2, 4, true, 2> D6;
+typedef Tile<64, 64, 64, 2, 2, 3, true, 2> D7;       // two workgroups per CU
+typedef Tile<64, 32, 64, 2, 1, 4, true, 1> D8;       // two workgroups per CU
+
+// What a launch costs with a tile, in us: launch + per round (epilogue + 64-deep slabs x time of a slab).  A round is up to
+// `per_cu` tiles on each of the 256 CUs; a slab takes `few` with a handful of tiles on the chip, `one` with one on every CU
+// and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.  The numbers
+// are least-squares fits over 924 problems (widths 192 to 1024, FFN 2 to 4 times that, 64 to 8192 rows; NT, NN, pairs of NT,
+// and a layer's four TN problems in a launch), weights cold.  Picking by them takes 2.4% (hi + lo) and 1.6% (single-term)
+// longer in total than the fastest tile of each problem.
+struct TileCost { int id, bm, bn, per_cu; double launch, few, one, two, all, epilogue; };
+constexpr TileCost SINGLE[] = {
+    {1, 256, 256, 1, 5.86, 1.357, 1.841, 0, 0, 3.21}, {2, 256, 192, 1, 7.02, 1.127, 1.366, 0, 0, 2.00},
+    {3, 256, 128, 1, 0.22, 0.672, 0.926, 0, 0, 7.37}, {4, 128, 128, 1, 0.32, 0.456, 0.556, 0, 0, 5.32},
+    {5, 128, 64, 1, 3.20, 0.338, 0.396, 0, 0, 2.37},  {6, 64, 64, 2, 4.56, 0.204, 0.279, 0.396, 0.475, 1.18},
+    {7, 128, 128, 2, 0.00, 0.746, 0.899, 1.033, 1.153, 4.79}};
+constexpr TileCost HILO[] = {
+    {11, 256, 192, 1, 1.77, 1.374, 2.418, 0, 0, 7.85}, {12, 256, 128, 1, 0.69, 0.998, 1.646, 0, 0, 6.22},
+    {13, 128, 128, 1, 1.37, 0.567, 0.934, 0, 0, 4.05}, {14, 128, 96, 1, 1.97, 0.557, 0.775, 0, 0, 3.88},
+    {15, 128, 64, 1, 2.34, 0.325, 0.535, 0, 0, 2.59},  {16, 64, 64, 1, 3.34, 0.232, 0.349, 0, 0, 1.57},
+    {17, 64, 64, 2, 3.98, 0.248, 0.351, 0.465, 0.650, 0.99}, {18, 64, 32, 2, 4.06, 0.180, 0.278, 0.308, 0.450, 1.00}};
 
 int g_force_shape = 0, g_group = 8;
 
-// Which block tile: estimated cycles per 64-deep k-slab on the busiest CU.  A CU ingests ~25 B/clk from L2 (measured),
-// i.e. 5.12 clk per 128-byte operand row, and sustains ~70% of its 4096 flop/clk MFMA rate; rounds = how many tiles
-// the busiest of the 256 CUs works through.  The two smaller tiles exist in a form of which two blocks fit a CU side
-// by side (measured: two co-resident blocks take 1.3 times one) and, for single-term problems, in an 8-wave form that
-// is the fastest when one block per CU is all the problem gives.  Near-ties go to the larger tile.
-int pick_tile(const GemmBf16Args* p, int count, bool dual) {
-  static const int dims[4][2] = {{256, 256}, {256, 128}, {128, 128}, {128, 64}};
-  const double nb = dual ? 2.0 : 1.0;
+template <int N>
+int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count) {
   int best = 0;
-  int64_t best_tiles = 0;
   double best_cost = 0.0;
-  for (int c = 0; c < 4; ++c) {
-    const int bm = dims[c][0], bn = dims[c][1];
+  for (const TileCost& c : costs) {
     int64_t tiles = 0;
-    for (int k = 0; k < count; ++k) tiles += (int64_t)((p[k].M + bm - 1) / bm) * ((p[k].N + bn - 1) / bn);
-    const bool pairs = c == 3 || (c == 2 && !dual);   // a form with two blocks per CU exists
-    const double rounds = (pairs && tiles > 256) ? 1.3 * (double)((tiles + 511) / 512) : (double)((tiles + 255) / 256);
-    const double ingest = 5.12 * (bm + nb * bn), mfma = bm * bn * nb / 22.0;
-    const double cost = rounds * (ingest > mfma ? ingest : mfma) * (1.0 + 0.05 * c);
-    if (c == 0 || cost < best_cost) { best = c; best_cost = cost; best_tiles = tiles; }
+    double slabs = 0.0;                                    // of all tiles
+    for (int k = 0; k < count; ++k) {
+      const int64_t t = (int64_t)((p[k].M + c.bm - 1) / c.bm) * ((p[k].N + c.bn - 1) / c.bn);
+      tiles += t;
+      slabs += (double)t * (p[k].K / 64);
+    }
+    slabs /= (double)tiles;
+    const int64_t cap = 256 * c.per_cu, rest = tiles % cap;
+    double cost = c.launch + (double)(tiles / cap) * (slabs * (c.per_cu > 1 ? c.all : c.one) + c.epilogue);
+    if (rest > 0) {
+      const double slab = rest <= 256 ? c.few + (c.one - c.few) * (double)rest / 256.0 : c.two + (c.all - c.two) * (double)(rest - 256) / (double)(cap - 256);
+      cost += slabs * slab + c.epilogue;
+    }
+    if (best == 0 || cost < best_cost) { best = c.id; best_cost = cost; }
   }
-  if (dual) return best == 3 ? (best_tiles <= 256 ? 15 : 14) : 11 + best;
-  if (best == 2) return best_tiles <= 256 ? 7 : 3;
-  if (best == 3) return best_tiles <= 256 ? 6 : 4;
-  return 1 + best;
+  return best;
 }
 
 template <bool A_KC, bool B_KC>
 void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count) {
   const bool dual = p[0].B2 != nullptr;
   int shape = g_force_shape;
-  if (shape >= 11 && !dual) shape = 0;   // DUAL tiles read B2
-  if (shape == 0) shape = pick_tile(p, count, dual);
+  if (shape >= 11 && !dual) shape = 0;   // hi + lo tiles read B2
+  if (shape == 0) shape = dual ? pick_tile(HILO, p, count) : pick_tile(SINGLE, p, count);
   switch (shape) {
-    case 1: launch_tile<TL, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 2: launch_tile<TM, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 4: launch_tile<TX, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 5: launch_tile<TX4, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 6: launch_tile<TX8, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 7: launch_tile<TS8, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 11: launch_tile<DL, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 12: launch_tile<DM, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 13: launch_tile<DS, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 14: launch_tile<DX, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 15: launch_tile<DX4, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    default: launch_tile<TS, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 1: launch_tile<S1, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 2: launch_tile<S2, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 3: launch_tile<S3, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 4: launch_tile<S4, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 5: launch_tile<S5, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 6: launch_tile<S6, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 11: launch_tile<D1, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 12: launch_tile<D2, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 13: launch_tile<D3, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 14: launch_tile<D4, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 15: launch_tile<D5, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 16: launch_tile<D6, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 17: launch_tile<D7, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 18: launch_tile<D8, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    default: launch_tile<S7, A_KC, B_KC>(ps, st, p, count, g_group); break;
   }
 }
 }  // namespace

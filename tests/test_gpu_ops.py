@@ -166,6 +166,34 @@ def test_gemm_bf16(M, N, K, a_trans, b_trans, split):
     assert np.array_equal(o32b.cpu().numpy(), outs[-1])                    # bit-stable from run to run
 
 
+@pytest.mark.parametrize("M,N,K,a_trans,b_trans,split", [
+    (8, 8, 64, False, True, True), (72, 40, 128, False, False, True), (64, 104, 64, False, True, True), (200, 96, 192, False, False, True),
+    (312, 200, 256, False, True, True), (8, 8, 64, True, False, False), (72, 104, 128, True, False, False), (264, 200, 320, True, False, False)])
+def test_gemm_bf16_tile_edges(M, N, K, a_trans, b_trans, split):
+    """Every tile of the class at sizes around the tiles' edges, with one to five slabs (fewer than a tile has stages, and
+    more): the bits of the tile the heuristic picks, and numpy float64."""
+    import ctypes
+    from paper_2310_05674_amd import binding as B
+    r = CounterRNG(900 + M + N + K)
+    A = round_to_bf16(r.normal(1, M * K)).reshape((K, M) if a_trans else (M, K))
+    Bm = round_to_bf16(r.normal(2, N * K)).reshape((N, K) if b_trans else (K, N))
+    B2 = round_to_bf16(0.004 * r.normal(3, N * K)).reshape(Bm.shape) if split else None
+    Bf = Bm + (B2 if split else 0.0)
+    want = (A.T if a_trans else A) @ (Bf.T if b_trans else Bf)
+    tA, tB = _dev(A, torch.bfloat16), _dev(Bm, torch.bfloat16)
+    tB2 = _dev(B2, torch.bfloat16) if split else None
+    L = B.load_library()
+    first = None
+    for shape in (0,) + (tuple(range(11, 19)) if split else tuple(range(1, 8))):
+        L.sama_dev_gemm_shape(ctypes.c_int32(shape))
+        o32 = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+        B.op_gemm_bf16(tA, tB, a_trans=a_trans, b_trans=b_trans, B2=tB2, out32=o32)
+        got = o32.cpu().numpy()
+        first = got if first is None else first
+        assert rel_l2(got, want) < 1e-5 and np.array_equal(got, first), shape
+    L.sama_dev_gemm_shape(ctypes.c_int32(0))
+
+
 def test_gemm_rejects_unsupported_shapes():
     from paper_2310_05674_amd import binding as B
     A = torch.zeros((64, 96), dtype=torch.bfloat16, device=DEV); Bm = torch.zeros((64, 96), dtype=torch.bfloat16, device=DEV)
