@@ -47,6 +47,8 @@ class EncoderModel : public Model {
       x1_[l] = ws.take<bf16_t>(R * d_); fpre_[l] = ws.take<bf16_t>(R * ffn_); fact_[l] = ws.take<bf16_t>(R * ffn_);
       pre2_[l] = ws.take<float>(R * d_); mean2_[l] = ws.take<float>(M); rstd2_[l] = ws.take<float>(M);
     }
+    plan_.start = ws.take<int32_t>(MAX_SEQ + 1); plan_.rows = ws.take<int32_t>(1); plan_.ids = ws.take<int32_t>(M); plan_.src = ws.take<int32_t>(M);
+    plan_.group = ws.take<int32_t>(M / ROW_GROUP);
     pre0_ = ws.take<float>(M * d_); mean0_ = ws.take<float>(M); rstd0_ = ws.take<float>(M);
     dX_[0] = ws.take<float>(M * d_); dX_[1] = ws.take<float>(M * d_);
     res_[0] = ws.take<float>(2 * M * d_); res_[1] = ws.take<float>(2 * M * d_);
@@ -75,14 +77,14 @@ class EncoderModel : public Model {
   // One linear layer of `nw` stacked passes (pass k owns rows [k M, (k + 1) M) of every activation): the same
   // epilogue `e` (its pointers are those of pass 0) for each pass, with that pass's weights.
   void fwd_linear(hipStream_t st, const PassWeights* w, int nw, const bf16_t* A, int K, int64_t woff, int N, int64_t boff, int M,
-                  const GemmBf16Args& e) const {
+                  const GemmBf16Args& e, const int32_t* rows = nullptr) const {
     GemmBf16Args g[2];
     for (int k = 0; k < nw; ++k) {
       g[k] = e;
       const int64_t ro = (int64_t)k * M * N;
       g[k].A = A + (int64_t)k * M * K; g[k].lda = K; g[k].a_trans = 0;
       g[k].B = w[k].hi + woff; g[k].B2 = w[k].lo ? w[k].lo + woff : nullptr; g[k].ldb = K; g[k].b_trans = 1;
-      g[k].M = M; g[k].N = N; g[k].K = K; g[k].ldc = N;
+      g[k].M = M; g[k].N = N; g[k].K = K; g[k].ldc = N; g[k].rows = rows;
       g[k].bias = w[k].theta + boff;
       if (w[k].sign != 0.f) { g[k].bias_v = w[k].vdir + boff; g[k].beps = w[k].eps_ptr; g[k].bsign = w[k].sign; }
       if (e.res32) g[k].res32 = e.res32 + ro;
@@ -99,7 +101,7 @@ class EncoderModel : public Model {
   // keeps what the backward of both heads needs (n = 0) stays on all rows: the masked ones lie in nearly every group of 16 rows.
   RowSelect select(const sama_batch& b, bool keep, const MlmBatch* mb) const {
     RowSelect s{};
-    s.S = S_;
+    s.S = S_; s.start = b.seq_len != nullptr ? plan_.start : nullptr;
     if (mb != nullptr) {
       if (keep) return s;
       s.n_mask = mb->n_mask; s.mask_rows = mb->rows; s.mask_base = mb->row_base; s.mask_total = mb->rows_in_batch;
@@ -116,9 +118,11 @@ class EncoderModel : public Model {
   HeadView run_forward(hipStream_t st, const PassWeights* w, int nw, const sama_batch& b, bool keep, const MlmBatch* mb) {
     const int B = b.n, M = B * S_;
     const RowSelect sel = select(b, keep, mb);
+    const RowPlan rp = b.seq_len != nullptr ? plan_ : RowPlan{};   // a padded batch: only the rows that matter
+    if (b.seq_len != nullptr) launch_row_plan(st, (const int32_t*)b.x, b.seq_len, B, S_, mb ? masked(b, *mb) : RowSelect{}, rp);
     ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};   // flips behind the first pass's rows
     LnFwdArgs e{};
-    e.x = nullptr; e.ids = (const int32_t*)b.x; e.ids_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep ? pre0_ : nullptr;
+    e.x = nullptr; e.ids = rp.ids ? rp.ids : (const int32_t*)b.x; e.src = rp.src; e.rows = rp.rows; e.pass_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep ? pre0_ : nullptr;
     e.pv = pv; e.g_off = eg_; e.b_off = eb_; e.y = X_[0]; e.y32 = res_[0]; e.mean = keep ? mean0_ : nullptr; e.rstd = keep ? rstd0_ : nullptr;
     e.M = nw * M; e.d = d_;
     launch_ln_fwd(st, e);
@@ -129,40 +133,43 @@ class EncoderModel : public Model {
       const LayerOff& o = off_[l];
       GemmBf16Args g{};
       g.C16 = qkv_[s];
-      fwd_linear(st, w, nw, xin, d_, o.Wqkv, 3 * d_, o.bqkv, M, g);
-      launch_attention_fwd(st, qkv_[s], ao_[s], keep ? lse_[s] : nullptr, nw * B, S_, heads_, d_, b.seq_len, B);
+      fwd_linear(st, w, nw, xin, d_, o.Wqkv, 3 * d_, o.bqkv, M, g, rp.rows);
+      launch_attention_fwd(st, qkv_[s], ao_[s], keep ? lse_[s] : nullptr, nw, B, S_, heads_, d_, b.seq_len, rp);
       const bool last = l == L_ - 1 && sel.n > 0;
       const int rows = last ? sel.n : M;            // of one pass, from here on
+      const int32_t* const in_use = last ? nullptr : rp.rows;
       if (last) {
         launch_select_rows(st, sel, nw, M, d_, ao_[s], res_[0], ao_sel_, res_sel_);
         if (nw == 2) pv.flip_row = rows;
       }
       g = GemmBf16Args{};
       g.res32 = last ? res_sel_ : res_[0]; g.C32 = pre1_[s];          // the residual stream stays fp32
-      fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g);
+      fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g, in_use);
       LnFwdArgs n1{};
       n1.x = pre1_[s]; n1.pv = pv; n1.g_off = o.ln1g; n1.b_off = o.ln1b; n1.y = x1_[s]; n1.y32 = res_[1];
-      n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = nw * rows; n1.d = d_;
+      n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
       launch_ln_fwd(st, n1);
       g = GemmBf16Args{};
       g.act = GEMM_ACT_GELU_FWD; g.C16_pre = keep ? fpre_[s] : nullptr; g.C16 = fact_[s];   // only a backward pass reads the pre-activation
-      fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g);
+      fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g, in_use);
       g = GemmBf16Args{};
       g.res32 = res_[1]; g.C32 = pre2_[s];
-      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g);
+      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g, in_use);
       LnFwdArgs n2{};
       n2.x = pre2_[s]; n2.pv = pv; n2.g_off = o.ln2g; n2.b_off = o.ln2b; n2.y = xout; n2.y32 = res_[0];
-      n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = nw * rows; n2.d = d_;
+      n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = nw * rows; n2.d = d_; n2.pass_rows = rows; n2.rows = in_use;
       launch_ln_fwd(st, n2);
     }
     HeadView h{};                                   // position 0 of the fp32 output of the last LayerNorm
     h.x = res_[0]; h.stride = (int64_t)(sel.n > 0 ? SELECT_SEQ_ROWS : S_) * d_; h.pass_stride = (int64_t)(sel.n > 0 ? sel.n : M) * d_; h.k = d_;
     h.pv = ParamView{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, 0};
     h.w_off = wc_; h.b_off = bc_; h.dots = true;
+    h.start = sel.n > 0 ? nullptr : rp.start;
     return h;
   }
 
   HeadView forward(hipStream_t st, const PassWeights& w, const sama_batch& b, bool keep, const MlmBatch* mb) override {
+    if (mb) mask_sel_ = masked(b, *mb);
     return run_forward(st, &w, 1, b, keep, mb);
   }
   HeadView forward_pair(hipStream_t st, const PassWeights& wp, const PassWeights& wm, const sama_batch& b, const MlmBatch* mb) override {
@@ -170,12 +177,13 @@ class EncoderModel : public Model {
     return run_forward(st, w, 2, b, false, mb);
   }
 
+  // (called with the batch of the last forward() or forward_pair())
   void mlm_forward(hipStream_t st, const PassWeights* w, int nw, bool kept, const MlmBatch& mb, float* loss_pos) override {
     P_ = (mb.n_mask + 63) / 64 * 64;
     // A kept pass (base step) contracts the bf16 hidden states like every other layer.  The +- passes of Eq. 5 feed
     // a loss whose difference is the signal: their hidden states enter as the two-term split of the fp32 LayerNorm
     // output, x_hi (W_hi + W_lo) + x_lo W_hi, so that the rounding of x to bf16 does not bury that difference.
-    if (kept) launch_select_rows(st, masked(mb), 1, 0, d_, X_[L_], nullptr, hm_, nullptr);
+    if (kept) launch_select_rows(st, mask_sel_, 1, 0, d_, X_[L_], nullptr, hm_, nullptr);
     else launch_split_rows(st, res_[0], (int64_t)P_ * d_, mb.n_mask, P_, d_, nw, hm_, hm_lo_);   // such a pass ends on the masked rows
     GemmBf16Args g{};
     g.C32 = zt_;
@@ -194,22 +202,22 @@ class EncoderModel : public Model {
     launch_mlm_ce(st, zt_, V_, P_, mb.tgt, mb.n_mask, nw, loss_pos, lse_pos_);
   }
 
-  RowSelect masked(const MlmBatch& mb) const { return select(sama_batch{}, false, &mb); }
+  RowSelect masked(const sama_batch& b, const MlmBatch& mb) const { return select(b, false, &mb); }
 
   // dW[N x K] = dY^T . X into `out`
-  GemmBf16Args wgrad(const bf16_t* dY, int N, const bf16_t* X, int K, int M, float* out) const {
+  GemmBf16Args wgrad(const bf16_t* dY, int N, const bf16_t* X, int K, int M, float* out, const int32_t* rows = nullptr) const {
     GemmBf16Args g{};
     g.A = dY; g.lda = N; g.a_trans = 1;
     g.B = X; g.ldb = K; g.b_trans = 0;
-    g.M = N; g.N = K; g.K = M; g.ldc = K; g.C32 = out;
+    g.M = N; g.N = K; g.K = M; g.ldc = K; g.C32 = out; g.rows = rows;
     return g;
   }
   // dX[M x K] = dY[M x N] . W[N x K]
-  GemmBf16Args dgrad(const PassWeights& w, const bf16_t* dY, int N, int64_t woff, int K, int M) const {
+  GemmBf16Args dgrad(const PassWeights& w, const bf16_t* dY, int N, int64_t woff, int K, int M, const int32_t* rows) const {
     GemmBf16Args g{};
     g.A = dY; g.lda = N; g.a_trans = 0;
     g.B = w.hi + woff; g.B2 = w.lo ? w.lo + woff : nullptr; g.ldb = K; g.b_trans = 0;
-    g.M = M; g.N = K; g.K = N; g.ldc = K;
+    g.M = M; g.N = K; g.K = N; g.ldc = K; g.rows = rows;
     return g;
   }
 
@@ -237,7 +245,7 @@ class EncoderModel : public Model {
       g[k].C32 = dhm_ + (int64_t)k * P_ * d_;
     }
     launch_gemm_bf16_batch(st, g, np);
-    launch_scatter_add_rows(st, dhm_, np, (int64_t)P_ * d_, mb.row_base, mb.rows_in_batch, mb.rows, mb.n_mask, d_, dx);
+    launch_scatter_add_rows(st, dhm_, np, (int64_t)P_ * d_, mask_sel_, d_, dx);
     launch_gemm_bf16(st, wgrad(dzt_, V_, hm_, d_, P_, grad + wm_));
     launch_colsum_bf16(st, dzt_, P_, V_, cs_mlm_, grad + bm_);
   }
@@ -246,10 +254,11 @@ class EncoderModel : public Model {
                     const MlmBatch* mb, const float* coef_pos) {
     const int B = b.n, M = B * S_;
     const RowSelect sel = select(b, true, mb);
+    const RowPlan rp = b.seq_len != nullptr ? plan_ : RowPlan{};   // of the kept forward pass
     float* dx = dX_[0];
     float* dx_next = dX_[1];
     launch_fill_f32(st, dx, 0.f, (int64_t)(sel.n > 0 ? sel.n : M) * d_);
-    launch_head_bwd(st, res_[0], sel.n > 0 ? SELECT_SEQ_ROWS : S_, d_, B, C_, w.theta, wc_, bc_, dlogits, grad, dx);
+    launch_head_bwd(st, res_[0], sel.n > 0 ? SELECT_SEQ_ROWS : S_, sel.n > 0 ? nullptr : rp.start, d_, B, C_, w.theta, wc_, bc_, dlogits, grad, dx);
     if (mb) mlm_backward(st, w, *mb, coef_pos, grad, dx);
     else if (has_mlm()) {   // a loss without masked-token terms leaves the head's gradient at zero
       launch_fill_f32(st, grad + wm_, 0.f, (int64_t)V_ * d_);
@@ -271,34 +280,35 @@ class EncoderModel : public Model {
       GemmBf16Args wg[4];
       const bool last = l == L_ - 1 && sel.n > 0;  // the gradient arrives, and stays down to the output projection, on the selected rows
       const int rows = last ? sel.n : M;
+      const int32_t* const in_use = last ? nullptr : rp.rows;
       // LN2
-      LnBwdArgs n2{dx, pre2_[l], mean2_[l], rstd2_[l], w.theta + o.ln2g, ds32_, ds2, lnpart_[p][0], rows, d_};
+      LnBwdArgs n2{dx, pre2_[l], mean2_[l], rstd2_[l], w.theta + o.ln2g, ds32_, ds2, lnpart_[p][0], rows, d_, in_use};
       launch_ln_bwd(st, n2);
       // FFN
-      wg[0] = wgrad(ds2, d_, fact_[l], ffn_, rows, grad + o.W2);
-      GemmBf16Args g = dgrad(w, ds2, d_, o.W2, ffn_, rows);
+      wg[0] = wgrad(ds2, d_, fact_[l], ffn_, rows, grad + o.W2, in_use);
+      GemmBf16Args g = dgrad(w, ds2, d_, o.W2, ffn_, rows, in_use);
       g.act = GEMM_ACT_GELU_BWD; g.aux16 = fpre_[l]; g.C16 = dpre;
       launch_gemm_bf16(st, g);
-      wg[1] = wgrad(dpre, ffn_, x1_[l], d_, rows, grad + o.W1);
-      g = dgrad(w, dpre, ffn_, o.W1, d_, rows);
+      wg[1] = wgrad(dpre, ffn_, x1_[l], d_, rows, grad + o.W1, in_use);
+      g = dgrad(w, dpre, ffn_, o.W1, d_, rows, in_use);
       g.res32 = ds32_; g.C32 = dx_next;                       // + the residual branch
       launch_gemm_bf16(st, g);
       // LN1
-      LnBwdArgs n1{dx_next, pre1_[l], mean1_[l], rstd1_[l], w.theta + o.ln1g, ds32_, ds1, lnpart_[p][1], rows, d_};
+      LnBwdArgs n1{dx_next, pre1_[l], mean1_[l], rstd1_[l], w.theta + o.ln1g, ds32_, ds1, lnpart_[p][1], rows, d_, in_use};
       launch_ln_bwd(st, n1);
       // attention
-      wg[2] = wgrad(ds1, d_, last ? ao_sel_ : ao_[l], d_, rows, grad + o.Wo);
-      g = dgrad(w, ds1, d_, o.Wo, d_, rows);
+      wg[2] = wgrad(ds1, d_, last ? ao_sel_ : ao_[l], d_, rows, grad + o.Wo, in_use);
+      g = dgrad(w, ds1, d_, o.Wo, d_, rows, in_use);
       g.C16 = last ? do_sel_ : do_;
       launch_gemm_bf16(st, g);
       const float* dres = ds32_;                              // the residual branch around the attention
       if (last) {
-        launch_spread_rows(st, sel, M, d_, do_sel_, ds32_, do_, dx_next);
+        launch_spread_rows(st, sel, rp, M, d_, do_sel_, ds32_, do_, dx_next);
         dres = dx_next;
       }
-      launch_attention_bwd(st, qkv_[l], ao_[l], do_, lse_[l], dqkv, B, S_, heads_, d_, b.seq_len, B);
-      wg[3] = wgrad(dqkv, 3 * d_, X_[l], d_, M, grad + o.Wqkv);
-      g = dgrad(w, dqkv, 3 * d_, o.Wqkv, d_, M);
+      launch_attention_bwd(st, qkv_[l], ao_[l], do_, lse_[l], dqkv, B, S_, heads_, d_, b.seq_len, rp);
+      wg[3] = wgrad(dqkv, 3 * d_, X_[l], d_, M, grad + o.Wqkv, rp.rows);
+      g = dgrad(w, dqkv, 3 * d_, o.Wqkv, d_, M, rp.rows);
       g.res32 = dres; g.C32 = dx;                             // gradient w.r.t. the layer input
       if (two) {   // everything the side launches read is written by now (the last dgrad only reads dqkv)
         (void)hipEventRecord(ev_chain_[p], st);
@@ -308,15 +318,17 @@ class EncoderModel : public Model {
       const bool sink_now = two && g_side_sink && sink_ != nullptr;
       if (sink_now) (void)hipEventRecord(ev_last_[p], st);   // behind the layer's last read of its own weights
       launch_gemm_bf16_batch(ss, wg, 4);
-      const ColsumJob cj[2] = {{dpre, rows, ffn_, cspart_[p][0]}, {dqkv, M, 3 * d_, cspart_[p][1]}};
+      const ColsumJob cj[2] = {{dpre, rows, ffn_, cspart_[p][0], in_use}, {dqkv, M, 3 * d_, cspart_[p][1], rp.rows}};
       launch_colsum_partial_multi(ss, cj, 2);
       const int nblk = M / LN_BWD_ROWS, nrb = M / COLSUM_ROWS;   // S is a multiple of 64
       const int ls = last ? S_ / LN_BWD_ROWS : 0, lk = SELECT_SEQ_ROWS / LN_BWD_ROWS, cs = last ? S_ / COLSUM_ROWS : 0, ck = SELECT_SEQ_ROWS / COLSUM_ROWS;
+      const int32_t* const gr = last ? nullptr : rp.group;
+      constexpr int lg = ROW_GROUP / LN_BWD_ROWS, cg = ROW_GROUP / COLSUM_ROWS;
       const ReduceRowsJob rj[4] = {
-          {lnpart_[p][0], nblk, 3 * d_, d_, d_, {grad + o.ln2g, grad + o.ln2b, grad + o.b2}, ls, lk},
-          {lnpart_[p][1], nblk, 3 * d_, d_, d_, {grad + o.ln1g, grad + o.ln1b, grad + o.bo}, ls, lk},
-          {cspart_[p][0], nrb, ffn_, 0, ffn_, {grad + o.b1, nullptr, nullptr}, cs, ck},
-          {cspart_[p][1], nrb, 3 * d_, 0, 3 * d_, {grad + o.bqkv, nullptr, nullptr}, 0, 0}};
+          {lnpart_[p][0], nblk, 3 * d_, d_, d_, {grad + o.ln2g, grad + o.ln2b, grad + o.b2}, ls, lk, gr, lg},
+          {lnpart_[p][1], nblk, 3 * d_, d_, d_, {grad + o.ln1g, grad + o.ln1b, grad + o.bo}, ls, lk, gr, lg},
+          {cspart_[p][0], nrb, ffn_, 0, ffn_, {grad + o.b1, nullptr, nullptr}, cs, ck, gr, cg},
+          {cspart_[p][1], nrb, 3 * d_, 0, 3 * d_, {grad + o.bqkv, nullptr, nullptr}, 0, 0, rp.group, cg}};
       launch_reduce_rows_multi(ss, rj, 4);
       if (two) { (void)hipEventRecord(ev_side_[p], side_); side_busy_[p] = true; }
       if (sink_now) {   // this layer's gradients are final (matrices and vectors are one range each); a consumer may
@@ -329,11 +341,12 @@ class EncoderModel : public Model {
     if (sink_used) { (void)hipEventRecord(ev_side_[0], side_); side_busy_[0] = true; }   // join behind the consumer's work too
     for (int p = 0; p < 2; ++p)
       if (two && side_busy_[p]) { (void)hipStreamWaitEvent(st, ev_side_[p], 0); side_busy_[p] = false; }
-    LnBwdArgs n0{dx, pre0_, mean0_, rstd0_, w.theta + eg_, ds32_, nullptr, lnpart_[0][0], M, d_};
+    LnBwdArgs n0{dx, pre0_, mean0_, rstd0_, w.theta + eg_, ds32_, nullptr, lnpart_[0][0], M, d_, rp.rows};
     launch_ln_bwd(st, n0);
-    launch_reduce_rows(st, lnpart_[0][0], M / LN_BWD_ROWS, 3 * d_, d_, d_, grad + eg_, grad + eb_, nullptr);
+    const ReduceRowsJob r0{lnpart_[0][0], M / LN_BWD_ROWS, 3 * d_, d_, d_, {grad + eg_, grad + eb_, nullptr}, 0, 0, rp.group, ROW_GROUP / LN_BWD_ROWS};
+    launch_reduce_rows_multi(st, &r0, 1);
     launch_fill_f32(st, grad + tok_, 0.f, (int64_t)V_ * d_);
-    launch_embedding_bwd(st, ds32_, (const int32_t*)b.x, B, S_, d_, V_, grad + tok_, grad + pos_);
+    launch_embedding_bwd(st, ds32_, (const int32_t*)b.x, B, S_, d_, V_, grad + tok_, grad + pos_, rp);
   }
 
   // second stream (default priority, created at the first backward pass) and the events that order it
@@ -369,6 +382,8 @@ class EncoderModel : public Model {
   float* cs_mlm_ = nullptr;
   std::vector<bf16_t*> X_, qkv_, ao_, x1_, fpre_, fact_;
   std::vector<float*> lse_, pre1_, mean1_, rstd1_, pre2_, mean2_, rstd2_;
+  RowPlan plan_{};            // of the last padded batch
+  RowSelect mask_sel_{};      // masked positions of the last batch with any
   float *pre0_ = nullptr, *mean0_ = nullptr, *rstd0_ = nullptr;
   float* dX_[2] = {nullptr, nullptr};
   float* res_[2] = {nullptr, nullptr};   // fp32 LayerNorm outputs: the residual stream of the current forward pass

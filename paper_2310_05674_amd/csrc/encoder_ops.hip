@@ -13,15 +13,58 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr float LN_EPS = 1e-5f;
 
+// =========================================================================================== rows of a padded batch
+// Every block works out where all the sequences go (at most 128 of them); thread i then places token row i of the padded
+// batch, and marks row i of the plan where no sequence has it.
+__global__ __launch_bounds__(256) void k_row_plan(const int32_t* __restrict__ ids, const int32_t* __restrict__ lens, int B, int S, RowSelect sel,
+                                                  RowPlan out) {
+  __shared__ int s_kept[MAX_SEQ], s_start[MAX_SEQ + 1];
+  for (int b = threadIdx.x; b < B; b += 256) s_kept[b] = min(max(lens[b], 1), S);
+  __syncthreads();
+  for (int j = threadIdx.x; j < sel.n_mask; j += 256) {
+    const int r = sel.mask_base + min(max(sel.mask_rows[j], 0), sel.mask_total - 1);
+    atomicMax(&s_kept[r / S], r % S + 1);
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {   // prefix sums: two sequences per lane, then across the wave
+    const int b = 2 * threadIdx.x;
+    const int k0 = b < B ? (s_kept[b] + ROW_GROUP - 1) / ROW_GROUP * ROW_GROUP : 0, k1 = b + 1 < B ? (s_kept[b + 1] + ROW_GROUP - 1) / ROW_GROUP * ROW_GROUP : 0;
+    int sum = k0 + k1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(sum, o, 64);
+      if ((int)threadIdx.x >= o) sum += t;
+    }
+    if (b < B) { s_start[b] = sum - k0 - k1; s_start[b + 1] = sum - k1; }
+    if (b + 1 < B) s_start[b + 2] = sum;
+  }
+  __syncthreads();
+  const int total = s_start[B], i = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.x == 0) {
+    for (int b = threadIdx.x; b <= B; b += 256) out.start[b] = s_start[b];
+    if (threadIdx.x == 0) *out.rows = (total + 63) / 64 * 64;
+  }
+  if (i >= B * S) return;
+  const int b = i / S, pos = i - b * S, kept = s_start[b + 1] - s_start[b];
+  if (pos < kept) {
+    out.src[s_start[b] + pos] = i;
+    out.ids[s_start[b] + pos] = ids[i];
+  }
+  if (pos % ROW_GROUP == 0) out.group[i / ROW_GROUP] = pos < kept ? (s_start[b] + pos) / ROW_GROUP : -1;
+  if (i >= total) { out.src[i] = -1; out.ids[i] = 0; }
+}
+
 // =========================================================================================== LayerNorm forward
 // One wave per row; the row lives in registers, NV 16-byte pieces per lane (d <= 256 NV).  Statistics in fp32 with a centred
 // second pass.
 template <int NV>
 __global__ __launch_bounds__(256) void k_ln_fwd(LnFwdArgs a) {
   const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= a.M) return;
+  const int r = a.pass_rows > 0 ? row % a.pass_rows : row;   // within its pass
+  if (row >= a.M || (a.rows != nullptr && r >= *a.rows)) return;
   const int nq = a.d >> 2;  // float4 chunks per row
   const float sc = a.pv.scale_row(row);
+  const int pos = a.x != nullptr ? 0 : (a.src != nullptr ? max(a.src[r], 0) : r) % a.S;
   float4 xr[NV];
   float sum = 0.f;
 #pragma unroll
@@ -32,8 +75,8 @@ __global__ __launch_bounds__(256) void k_ln_fwd(LnFwdArgs a) {
       if (a.x != nullptr) {
         xr[j] = reinterpret_cast<const float4*>(a.x + (int64_t)row * a.d)[q];
       } else {
-        const int id = min(max(a.ids[a.ids_rows > 0 ? row % a.ids_rows : row], 0), a.V - 1);   // ids outside [0, V) are clamped
-        const int64_t to = a.tok_off + (int64_t)id * a.d + 4 * q, po = a.pos_off + (int64_t)(row % a.S) * a.d + 4 * q;
+        const int id = min(max(a.ids[r], 0), a.V - 1);   // ids outside [0, V) are clamped
+        const int64_t to = a.tok_off + (int64_t)id * a.d + 4 * q, po = a.pos_off + (int64_t)pos * a.d + 4 * q;
         float4 t = *reinterpret_cast<const float4*>(a.pv.theta + to), p = *reinterpret_cast<const float4*>(a.pv.theta + po);
         if (sc != 0.f) {
           const float4 tv = *reinterpret_cast<const float4*>(a.pv.vdir + to), pvv = *reinterpret_cast<const float4*>(a.pv.vdir + po);
@@ -88,6 +131,8 @@ __global__ __launch_bounds__(256) void k_ln_fwd(LnFwdArgs a) {
 template <int NV>
 __global__ __launch_bounds__(256) void k_ln_bwd(LnBwdArgs a) {
   __shared__ float s_acc[4][3][256 * NV];
+  const int M = a.rows != nullptr ? __builtin_amdgcn_readfirstlane(*a.rows) : a.M;
+  if ((int)blockIdx.x * LN_BWD_ROWS >= M) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nq = a.d >> 2;
   float4 dg[NV], db[NV], dc[NV], gam[NV];
@@ -104,12 +149,12 @@ __global__ __launch_bounds__(256) void k_ln_bwd(LnBwdArgs a) {
   for (int rr = 0; rr < RW; ++rr) {
     const int row = r0 + rr;
     mus[rr] = rstds[rr] = 0.f;
-    if (row < a.M) { mus[rr] = a.mean[row]; rstds[rr] = a.rstd[row]; }
+    if (row < M) { mus[rr] = a.mean[row]; rstds[rr] = a.rstd[row]; }
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       const int q = lane + 64 * j;
       xin[rr][j] = dyin[rr][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (row < a.M && q < nq) {
+      if (row < M && q < nq) {
         xin[rr][j] = reinterpret_cast<const float4*>(a.x + (int64_t)row * a.d)[q];
         dyin[rr][j] = reinterpret_cast<const float4*>(a.dy + (int64_t)row * a.d)[q];
       }
@@ -118,7 +163,7 @@ __global__ __launch_bounds__(256) void k_ln_bwd(LnBwdArgs a) {
 #pragma unroll
   for (int rr = 0; rr < RW; ++rr) {
     const int row = r0 + rr;
-    if (row >= a.M) break;
+    if (row >= M) break;
     const float mu = mus[rr], rstd = rstds[rr];
     float4 xh[NV], dyg[NV];
     float s1 = 0.f, s2 = 0.f;
@@ -180,6 +225,7 @@ __global__ __launch_bounds__(256) void k_ln_bwd(LnBwdArgs a) {
 struct ReduceRowsMulti { ReduceRowsJob j[REDUCE_MAX_JOBS]; int first_block[REDUCE_MAX_JOBS + 1]; int count; };
 __global__ __launch_bounds__(256) void k_reduce_rows(ReduceRowsMulti m) {
   __shared__ float s_part[8][33];
+  __shared__ int s_group[MAX_TOKENS / ROW_GROUP];
   int job = 0;
 #pragma unroll
   for (int k = 1; k < REDUCE_MAX_JOBS; ++k)
@@ -188,16 +234,27 @@ __global__ __launch_bounds__(256) void k_reduce_rows(ReduceRowsMulti m) {
   const int local = blockIdx.x - m.first_block[job], nbx = (a.N + 31) / 32;
   const int cl = threadIdx.x & 31, rg = threadIdx.x >> 5, c = (local % nbx) * 32 + cl, v = local / nbx;
   float acc = 0.f;
+  if (a.group != nullptr) {
+    for (int g = threadIdx.x; g * a.group_blocks < a.nrows; g += 256) s_group[g] = a.group[g];
+    __syncthreads();
+  }
   if (c < a.N) {
     const float* p = a.partial + (int64_t)v * a.vstride + c;
-    if (a.seq_blocks == 0) {
+    if (a.group != nullptr) {
 #pragma unroll 4
-      for (int r = rg; r < a.nrows; r += 8) acc += p[(int64_t)r * a.stride];
-    } else {
+      for (int r = rg; r < a.nrows; r += 8) {
+        const int g = s_group[r / a.group_blocks];
+        const float v = p[(int64_t)(max(g, 0) * a.group_blocks + r % a.group_blocks) * a.stride];
+        acc += g >= 0 ? v : 0.f;
+      }
+    } else if (a.seq_blocks > 0) {
       for (int r = rg; r < a.nrows; r += 8) {
         const int s = r / a.seq_blocks, o = r - s * a.seq_blocks;
         if (o < a.kept_blocks) acc += p[(int64_t)(s * a.kept_blocks + o) * a.stride];
       }
+    } else {
+#pragma unroll 4
+      for (int r = rg; r < a.nrows; r += 8) acc += p[(int64_t)r * a.stride];
     }
   }
   s_part[rg][cl] = acc;
@@ -218,18 +275,17 @@ __global__ __launch_bounds__(256) void k_colsum_partial_bf16(ColsumMulti m) {
   const ColsumJob& a = m.j[job];
   const int local = blockIdx.x - m.first_block[job], nbx = (a.N + 2047) / 2048;
   const int c = ((local % nbx) * 256 + threadIdx.x) * 8, rb = local / nbx;
-  if (c >= a.N) return;
-  const int r0 = rb * COLSUM_ROWS;
+  const int r0 = rb * COLSUM_ROWS, M = __builtin_amdgcn_readfirstlane(a.rows != nullptr ? *a.rows : a.M);
+  if (c >= a.N || r0 >= M) return;
   float s[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) s[e] = 0.f;
   uint4 v[COLSUM_ROWS];
 #pragma unroll
   for (int r = 0; r < COLSUM_ROWS; ++r)
-    v[r] = (r0 + r < a.M) ? *reinterpret_cast<const uint4*>(a.X + (int64_t)(r0 + r) * a.N + c) : make_uint4(0u, 0u, 0u, 0u);
+    v[r] = (r0 + r < M) ? *reinterpret_cast<const uint4*>(a.X + (int64_t)(r0 + r) * a.N + c) : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
   for (int r = 0; r < COLSUM_ROWS; ++r) {
-    if (r0 + r >= a.M) break;
     const uint32_t w[4] = {v[r].x, v[r].y, v[r].z, v[r].w};
 #pragma unroll
     for (int e = 0; e < 8; ++e) s[e] += bf16_to_f32((bf16_t)(w[e >> 1] >> ((e & 1) * 16)));
@@ -255,13 +311,14 @@ __device__ __forceinline__ s16x4 pack4(float a, float b, float c, float d) {
 // operand: for the 32x32x8 MFMA, lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] through ds_read_b64_tr_b16.
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 constexpr int SLD = AD + 32;
+// Rows from `kept` on are zeros: what lies behind a sequence's rows may be anything.
 template <int THREADS, int ROWS>
-__device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ src, int64_t ld, bf16_t* __restrict__ S) {
+__device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ src, int64_t ld, int kept, bf16_t* __restrict__ S) {
 #pragma unroll
   for (int c0 = 0; c0 < ROWS * 8; c0 += THREADS) {
     const int c = c0 + threadIdx.x, row = c >> 3, ec = c & 7;
     if (ROWS * 8 % THREADS == 0 || c < ROWS * 8)
-      *reinterpret_cast<uint4*>(S + row * SLD + ec * 8) = *reinterpret_cast<const uint4*>(src + (int64_t)row * ld + ec * 8);
+      *reinterpret_cast<uint4*>(S + row * SLD + ec * 8) = row < kept ? *reinterpret_cast<const uint4*>(src + (int64_t)row * ld + ec * 8) : make_uint4(0u, 0u, 0u, 0u);
   }
 }
 __device__ __forceinline__ s16x4 ld_transposed(const bf16_t* __restrict__ S, int e32, int k0, int lane) {
@@ -285,28 +342,37 @@ __device__ __forceinline__ f32x16 rows_dot_rows(const bf16_t* __restrict__ R, co
   return acc;
 }
 
-// lens (or null): real tokens of sequence b % lens_period, clamped into [1, S]; keys at positions beyond get no weight.
-__device__ __forceinline__ int seq_len_of(const int32_t* __restrict__ lens, int lens_period, int b, int S) {
-  if (lens == nullptr) return S;
-  const int n = lens[b % lens_period];
-  return n < 1 ? 1 : (n > S ? S : n);
+// The rows of sequence b, of which `kept` are there, and its real tokens (keys at positions beyond get no weight).
+struct SeqRows { int row0, kept, len; };
+template <bool PADDED>
+__device__ __forceinline__ SeqRows seq_rows(const int32_t* __restrict__ lens, const RowPlan& plan, int pass, int b, int B, int S) {
+  if (!PADDED) return SeqRows{(pass * B + b) * S, S, S};
+  const int n = lens[b], r0 = plan.start[b];
+  return SeqRows{pass * B * S + r0, plan.start[b + 1] - r0, n < 1 ? 1 : (n > S ? S : n)};
+}
+// zeros into the rows of the plan that belong to no sequence, 64 columns at `out` of row 0 of the pass
+template <int THREADS>
+__device__ __forceinline__ void zero_tail(const RowPlan& plan, int B, bf16_t* __restrict__ out, int64_t ld) {
+  const int r0 = plan.start[B], n = *plan.rows - r0;
+  for (int c = threadIdx.x; c < n * 8; c += THREADS) *reinterpret_cast<uint4*>(out + (int64_t)(r0 + (c >> 3)) * ld + (c & 7) * 8) = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // Forward.  Four waves; wave w owns the query tiles w, w + 4, ... (32 queries each).  S^T[key][q] tiles leave each lane
 // with one query column, so the softmax over keys is an in-lane reduction plus one cross-half shuffle, and the
 // probability tile is already in the B-operand layout of the 32x32x8 MFMA for O^T[e][q] = sum_key V^T[e][key] P^T[key][q].
 template <int NT>
-__device__ __forceinline__ void attn_scores(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, int64_t ld, int qt, int len,
+__device__ __forceinline__ void attn_scores(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, int64_t ld, int qt, int len, int nk,
                                             int lane, f32x16 (&s)[NT], float& inv, float* __restrict__ lse_row) {
 #pragma unroll
-  for (int kt = 0; kt < NT; ++kt) s[kt] = rows_dot_rows(K, Q, ld, 32 * kt, 32 * qt, lane);
+  for (int kt = 0; kt < NT; ++kt)
+    if (kt < nk) s[kt] = rows_dot_rows(K, Q, ld, 32 * kt, 32 * qt, lane);   // nk: tiles with a real key
   float mx = -3.0e38f;
 #pragma unroll
   for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int key = 32 * kt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      s[kt][r] = key < len ? s[kt][r] * 0.125f : -3.0e38f;   // exp(-3e38 - mx) = 0: key 0 is always real
+      s[kt][r] = (kt < nk && key < len) ? s[kt][r] * 0.125f : -3.0e38f;   // exp(-3e38 - mx) = 0: key 0 is always real
       mx = fmaxf(mx, s[kt][r]);
     }
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
@@ -322,49 +388,55 @@ __device__ __forceinline__ void attn_scores(const bf16_t* __restrict__ Q, const 
 
 template <int NT, bool PADDED>   // PADDED = false: no lengths given, the comparisons against len fold away
 __global__ __launch_bounds__(256) void k_attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
-                                                  int heads, int d, const int32_t* __restrict__ lens, int lens_period) {
+                                                  int heads, int d, const int32_t* __restrict__ lens, RowPlan plan, int B) {
   constexpr int S = 32 * NT;
   __shared__ __attribute__((aligned(16))) bf16_t Vs[S * SLD];
-  const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int h = blockIdx.x, b = blockIdx.y, pass = b / B, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ld = 3 * (int64_t)d;
-  const bf16_t* Q = qkv + (int64_t)b * S * ld + h * AD;
+  const SeqRows sr = seq_rows<PADDED>(lens, plan, pass, b - pass * B, B, S);
+  const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
   const bf16_t* K = Q + d;
   const bf16_t* V = Q + 2 * d;
-  const int len = PADDED ? seq_len_of(lens, lens_period, b, S) : S;
+  const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
+  if (PADDED && b == pass * B) zero_tail<256>(plan, B, out + (int64_t)pass * B * S * d + h * AD, d);
   float* lse_row = lse != nullptr ? lse + ((int64_t)b * heads + h) * S : nullptr;
-  stage_rows<256, S>(V, ld, Vs);
+  stage_rows<256, S>(V, ld, kept, Vs);
   f32x16 s[NT];
   float inv = 0.f;
   int qt = wave;
-  if (qt < NT) attn_scores<NT>(Q, K, ld, qt, len, lane, s, inv, lse_row);   // overlaps the staging of V
+  if (qt < nq) attn_scores<NT>(Q, K, ld, qt, len, nk, lane, s, inv, lse_row);   // overlaps the staging of V
   __syncthreads();                                                          // reached once by every wave
-  while (qt < NT) {
+  while (qt < nq) {
     f32x16 o[2];
 #pragma unroll
     for (int et = 0; et < 2; ++et) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[et][r] = 0.f;
 #pragma unroll
-      for (int kt = 0; kt < NT; ++kt)
+      for (int kt = 0; kt < NT; ++kt) {
+        if (kt >= nk) break;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           const s16x4 pb = pack4(s[kt][4 * c] * inv, s[kt][4 * c + 1] * inv, s[kt][4 * c + 2] * inv, s[kt][4 * c + 3] * inv);
           const s16x4 va = ld_transposed(Vs, 32 * et, 32 * kt + 8 * c, lane);
           o[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(va, pb, o[et], 0, 0, 0);
         }
+      }
     }
-    bf16_t* orow = out + ((int64_t)b * S + 32 * qt + (lane & 31)) * d + h * AD;
+    bf16_t* orow = out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD;
+    const bool there = !PADDED || 32 * qt + (lane & 31) < kept;
 #pragma unroll
     for (int et = 0; et < 2; ++et)
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
+        if (!there) break;
         uint2 pk;
         pk.x = pack_bf16x2(o[et][4 * c], o[et][4 * c + 1]);
         pk.y = pack_bf16x2(o[et][4 * c + 2], o[et][4 * c + 3]);
         *reinterpret_cast<uint2*>(orow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
       }
     qt += 4;
-    if (qt < NT) attn_scores<NT>(Q, K, ld, qt, len, lane, s, inv, lse_row);
+    if (qt < nq) attn_scores<NT>(Q, K, ld, qt, len, nk, lane, s, inv, lse_row);
   }
 }
 
@@ -379,7 +451,7 @@ template <int NT, bool PADDED>
 __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
                                                   const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                   bf16_t* __restrict__ dqkv, int heads, int d, const int32_t* __restrict__ lens,
-                                                  int lens_period) {
+                                                  RowPlan plan, int B) {
   constexpr int S = 32 * NT, TILE_UNROLL = NT <= 4 ? NT : 1;
   __shared__ __attribute__((aligned(16))) bf16_t Ks[S * SLD];
   __shared__ __attribute__((aligned(16))) bf16_t Qs[S * SLD];
@@ -387,16 +459,19 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
   __shared__ float s_D[S], s_lse[S];
   const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
   const bool phase_a = threadIdx.x < 256;
-  const int len = PADDED ? seq_len_of(lens, lens_period, b, S) : S;
   const int64_t ld = 3 * (int64_t)d;
-  const bf16_t* Q = qkv + (int64_t)b * S * ld + h * AD;
+  const SeqRows sr = seq_rows<PADDED>(lens, plan, 0, b, B, S);
+  const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
+  const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
   const bf16_t* K = Q + d;
   const bf16_t* V = Q + 2 * d;
-  const bf16_t* O = out + (int64_t)b * S * d + h * AD;
-  const bf16_t* dO = dout + (int64_t)b * S * d + h * AD;
-  stage_rows<512, S>(K, ld, Ks);
-  stage_rows<512, S>(Q, ld, Qs);
-  stage_rows<512, S>(dO, d, dOs);
+  const bf16_t* O = out + (int64_t)sr.row0 * d + h * AD;
+  const bf16_t* dO = dout + (int64_t)sr.row0 * d + h * AD;
+  if (PADDED && b == 0)
+    for (int k = 0; k < 3; ++k) zero_tail<512>(plan, B, dqkv + k * d + h * AD, ld);
+  stage_rows<512, S>(K, ld, kept, Ks);
+  stage_rows<512, S>(Q, ld, kept, Qs);
+  stage_rows<512, S>(dO, d, kept, dOs);
   if (phase_a) {
     // two threads per query; 2 S and 256 are multiples of the wave size, so a wave is in or out of a trip as a whole
     for (int t = threadIdx.x; t < 2 * S; t += 256) {
@@ -404,6 +479,7 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
       float acc = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
+        if (PADDED && q >= kept) break;
         const uint4 o4 = *reinterpret_cast<const uint4*>(O + (int64_t)q * d + half * 32 + 8 * i);
         const uint4 d4 = *reinterpret_cast<const uint4*>(dO + (int64_t)q * d + half * 32 + 8 * i);
         const uint32_t ow[4] = {o4.x, o4.y, o4.z, o4.w}, dw[4] = {d4.x, d4.y, d4.z, d4.w};
@@ -412,14 +488,14 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
           acc = fmaf(bf16_to_f32((bf16_t)(ow[e >> 1] >> ((e & 1) * 16))), bf16_to_f32((bf16_t)(dw[e >> 1] >> ((e & 1) * 16))), acc);
       }
       acc += __shfl_xor(acc, 1, 64);
-      if (half == 0) { s_D[q] = acc; s_lse[q] = lse[((int64_t)b * heads + h) * S + q]; }
+      if (half == 0) { s_D[q] = acc; s_lse[q] = (!PADDED || q < kept) ? lse[((int64_t)b * heads + h) * S + q] : 0.f; }
     }
   }
   __syncthreads();
 
   // ---- phase A: dQ
   if (phase_a) {
-    for (int qt = wave; qt < NT; qt += 4) {
+    for (int qt = wave; qt < nq; qt += 4) {
       const int q = 32 * qt + (lane & 31);
       const float lq = s_lse[q], Dq = s_D[q];
       f32x16 dq[2];
@@ -429,6 +505,7 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
         for (int r = 0; r < 16; ++r) dq[et][r] = 0.f;
 #pragma unroll TILE_UNROLL   // the long sequences keep one tile's operands in flight: unrolled they spill
       for (int kt = 0; kt < NT; ++kt) {
+        if (kt >= nk) break;
         f32x16 st = rows_dot_rows(K, Q, ld, 32 * kt, 32 * qt, lane);     // S^T[key][q]
         const bf16_t* vp = V + (int64_t)(32 * kt + (lane & 31)) * ld + 8 * (lane >> 5);
         const bf16_t* dop = dO + (int64_t)(32 * qt + (lane & 31)) * d + 8 * (lane >> 5);
@@ -452,11 +529,12 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
           }
         }
       }
-      bf16_t* dqrow = dqkv + ((int64_t)b * S + q) * ld + h * AD;
+      bf16_t* dqrow = dqkv + ((int64_t)sr.row0 + q) * ld + h * AD;
 #pragma unroll
       for (int et = 0; et < 2; ++et)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
+          if (PADDED && q >= kept) break;
           uint2 pk;
           pk.x = pack_bf16x2(dq[et][4 * c], dq[et][4 * c + 1]);
           pk.y = pack_bf16x2(dq[et][4 * c + 2], dq[et][4 * c + 3]);
@@ -467,7 +545,7 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
 
   // ---- phase B: dK, dV
   if (!phase_a) {
-    for (int kt = wave; kt < NT; kt += 4) {
+    for (int kt = wave; kt < nq; kt += 4) {
       const bool real_key = (32 * kt + (lane & 31)) < len;              // this lane's key
       f32x16 dk[2], dv[2];
 #pragma unroll
@@ -476,6 +554,7 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
         for (int r = 0; r < 16; ++r) { dk[et][r] = 0.f; dv[et][r] = 0.f; }
 #pragma unroll TILE_UNROLL
       for (int qt = 0; qt < NT; ++qt) {
+        if (qt >= nq || kt >= nk) break;                                // no such queries, or keys without weight
         f32x16 st = rows_dot_rows(Q, K, ld, 32 * qt, 32 * kt, lane);     // S[q][key]
         const bf16_t* dop = dO + (int64_t)(32 * qt + (lane & 31)) * d + 8 * (lane >> 5);
         const bf16_t* vp = V + (int64_t)(32 * kt + (lane & 31)) * ld + 8 * (lane >> 5);
@@ -488,9 +567,10 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          const float p = real_key ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
+          const bool on = real_key && (!PADDED || q < kept);
+          const float p = on ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
           st[r] = p;
-          ds[r] = p * (dp[r] - s_D[q]) * 0.125f;
+          ds[r] = on ? p * (dp[r] - s_D[q]) * 0.125f : 0.f;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -503,12 +583,14 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
           }
         }
       }
-      bf16_t* krow = dqkv + ((int64_t)b * S + 32 * kt + (lane & 31)) * ld + d + h * AD;
+      bf16_t* krow = dqkv + ((int64_t)sr.row0 + 32 * kt + (lane & 31)) * ld + d + h * AD;
+      const bool there = !PADDED || 32 * kt + (lane & 31) < kept;
       bf16_t* vrow = krow + d;
 #pragma unroll
       for (int et = 0; et < 2; ++et)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
+          if (!there) break;
           uint2 pk;
           pk.x = pack_bf16x2(dk[et][4 * c], dk[et][4 * c + 1]);
           pk.y = pack_bf16x2(dk[et][4 * c + 2], dk[et][4 * c + 3]);
@@ -522,13 +604,13 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
 }
 
 // =========================================================================================== classifier head
-__global__ __launch_bounds__(256) void k_head_bwd_w(const float* __restrict__ x, int S, int d, int B, int C,
+__global__ __launch_bounds__(256) void k_head_bwd_w(const float* __restrict__ x, int S, const int32_t* __restrict__ start, int d, int B, int C,
                                                     const float* __restrict__ dlogits, float* __restrict__ gWc, float* __restrict__ gbc) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < C * d) {
     const int c = i / d, k = i - c * d;
     float s = 0.f;
-    for (int b = 0; b < B; ++b) s = fmaf(dlogits[b * C + c], x[(int64_t)b * S * d + k], s);
+    for (int b = 0; b < B; ++b) s = fmaf(dlogits[b * C + c], x[(int64_t)(start != nullptr ? start[b] : b * S) * d + k], s);
     gWc[i] = s;
   }
   if (i < C) {
@@ -537,23 +619,17 @@ __global__ __launch_bounds__(256) void k_head_bwd_w(const float* __restrict__ x,
     gbc[i] = s;
   }
 }
-__global__ __launch_bounds__(256) void k_head_bwd_x(int S, int d, int B, int C, const float* __restrict__ Wc,
+__global__ __launch_bounds__(256) void k_head_bwd_x(int S, const int32_t* __restrict__ start, int d, int B, int C, const float* __restrict__ Wc,
                                                     const float* __restrict__ dlogits, float* __restrict__ dx) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= B * d) return;
   const int b = i / d, k = i - b * d;
   float s = 0.f;
   for (int c = 0; c < C; ++c) s = fmaf(dlogits[b * C + c], Wc[(int64_t)c * d + k], s);
-  dx[(int64_t)b * S * d + k] = s;
+  dx[(int64_t)(start != nullptr ? start[b] : b * S) * d + k] = s;
 }
 
 // =========================================================================================== rows that are read
-// token row of compact row i (i < s.n), or -1 where there is none
-__device__ __forceinline__ int selected_row(const RowSelect& s, int i) {
-  if (s.n_mask > 0) return i < s.n_mask ? s.mask_base + min(max(s.mask_rows[i], 0), s.mask_total - 1) : -1;
-  const int b = i / SELECT_SEQ_ROWS;
-  return b < s.n_cls ? b * s.S + i % SELECT_SEQ_ROWS : -1;
-}
 __global__ __launch_bounds__(256) void k_select_rows(RowSelect s, int pass_rows, int d, const bf16_t* __restrict__ a16,
                                                      const float* __restrict__ x32, bf16_t* __restrict__ a16_out, float* __restrict__ x32_out) {
   const int r = selected_row(s, blockIdx.x), nq = d >> 2;
@@ -564,11 +640,13 @@ __global__ __launch_bounds__(256) void k_select_rows(RowSelect s, int pass_rows,
       reinterpret_cast<float4*>(x32_out + to * d)[q] = r >= 0 ? reinterpret_cast<const float4*>(x32 + from * d)[q] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 }
-__global__ __launch_bounds__(256) void k_spread_rows(RowSelect s, int d, const bf16_t* __restrict__ a16, const float* __restrict__ x32,
+__global__ __launch_bounds__(256) void k_spread_rows(RowSelect s, RowPlan plan, int d, const bf16_t* __restrict__ a16, const float* __restrict__ x32,
                                                      bf16_t* __restrict__ a16_out, float* __restrict__ x32_out) {
   const int64_t to = blockIdx.x;
-  const int b = blockIdx.x / s.S, p = blockIdx.x % s.S, nq = d >> 2;
-  const bool kept = p < SELECT_SEQ_ROWS;
+  if (plan.rows != nullptr && (int)blockIdx.x >= *plan.rows) return;
+  const int o = plan.src != nullptr ? plan.src[blockIdx.x] : (int)blockIdx.x;
+  const int b = o / s.S, p = o % s.S, nq = d >> 2;
+  const bool kept = o >= 0 && p < SELECT_SEQ_ROWS;
   const int64_t from = kept ? b * SELECT_SEQ_ROWS + p : 0;
   for (int q = threadIdx.x; q < nq; q += 256) {
     reinterpret_cast<uint2*>(a16_out + to * d)[q] = kept ? reinterpret_cast<const uint2*>(a16 + from * d)[q] : make_uint2(0u, 0u);
@@ -577,20 +655,28 @@ __global__ __launch_bounds__(256) void k_spread_rows(RowSelect s, int d, const b
 }
 
 // =========================================================================================== embedding gradients
-__global__ __launch_bounds__(256) void k_pos_grad(const float* __restrict__ demb, int B, int S, int d, float* __restrict__ g_pos) {
+__global__ __launch_bounds__(256) void k_pos_grad(const float* __restrict__ demb, int B, int S, int d, RowPlan plan, float* __restrict__ g_pos) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= S * d) return;
   float s = 0.f;
-  for (int b = 0; b < B; ++b) s += demb[(int64_t)b * S * d + i];
+  if (plan.start == nullptr) {
+    for (int b = 0; b < B; ++b) s += demb[(int64_t)b * S * d + i];
+  } else {
+    const int pos = i / d;
+    for (int b = 0; b < B; ++b)
+      if (pos < plan.start[b + 1] - plan.start[b]) s += demb[(int64_t)plan.start[b] * d + i];
+  }
   g_pos[i] = s;
 }
 
 // One block per position m.  The block lists, in ascending order, every position holding the same token id;
 // only the block of the first occurrence goes on, and writes the ordered sum of those rows.
-__global__ __launch_bounds__(256) void k_tok_grad(const float* __restrict__ demb, const int32_t* __restrict__ ids, int M, int d,
-                                                  int V, float* __restrict__ g_tok) {
+__global__ __launch_bounds__(256) void k_tok_grad(const float* __restrict__ demb, const int32_t* __restrict__ ids, int all_rows,
+                                                  const int32_t* __restrict__ rows, int d, int V, float* __restrict__ g_tok) {
   __shared__ int s_list[MAX_TOKENS];
   __shared__ int s_cnt, s_wave[4];
+  const int M = rows != nullptr ? *rows : all_rows;
+  if ((int)blockIdx.x >= M) return;
   const int m = blockIdx.x, id = min(max(ids[m], 0), V - 1), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;   // clamped as in the forward pass
   if (threadIdx.x == 0) s_cnt = 0;
   __syncthreads();
@@ -684,67 +770,70 @@ void launch_colsum_bf16(hipStream_t st, const bf16_t* X, int M, int N, float* pa
 }
 // (S = 32 would fit the kernels, but the weight-gradient GEMMs contract over batch * S token rows in slabs of 64)
 bool attention_supports(int S) { return S == 64 || S == 128 || S == 256; }
-void launch_attention_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* out, float* lse, int B, int S, int heads, int d,
-                          const int32_t* lens, int lens_period) {
-  ProfScope ps(st, F_ATTN_FWD, 4.0 * B * heads * (double)S * S * 64.0);
-  const dim3 grid(heads, B);
-  const int lp = lens_period > 0 ? lens_period : 1;
+void launch_attention_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* out, float* lse, int nw, int B, int S, int heads, int d,
+                          const int32_t* lens, const RowPlan& plan) {
+  ProfScope ps(st, F_ATTN_FWD, 4.0 * nw * B * heads * (double)S * S * 64.0);
+  const dim3 grid(heads, nw * B);
   switch (S) {
     case 64:
-      if (lens) launch_kernel(ps, k_attn_fwd<2, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, lp);
-      else launch_kernel(ps, k_attn_fwd<2, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, lp);
+      if (lens) launch_kernel(ps, k_attn_fwd<2, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_fwd<2, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
       break;
     case 128:
-      if (lens) launch_kernel(ps, k_attn_fwd<4, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, lp);
-      else launch_kernel(ps, k_attn_fwd<4, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, lp);
+      if (lens) launch_kernel(ps, k_attn_fwd<4, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_fwd<4, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
       break;
     case 256:
-      if (lens) launch_kernel(ps, k_attn_fwd<8, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, lp);
-      else launch_kernel(ps, k_attn_fwd<8, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, lp);
+      if (lens) launch_kernel(ps, k_attn_fwd<8, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_fwd<8, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
       break;
     default: break;   // make_encoder admits no other length
   }
 }
 void launch_attention_bwd(hipStream_t st, const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, const float* lse,
-                          bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, int lens_period) {
+                          bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, const RowPlan& plan) {
   ProfScope ps(st, F_ATTN_BWD, 10.0 * B * heads * (double)S * S * 64.0);
   const dim3 grid(heads, B);
-  const int lp = lens_period > 0 ? lens_period : 1;
   switch (S) {
     case 64:
-      if (lens) launch_kernel(ps, k_attn_bwd<2, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, lp);
-      else launch_kernel(ps, k_attn_bwd<2, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, lp);
+      if (lens) launch_kernel(ps, k_attn_bwd<2, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_bwd<2, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
       break;
     case 128:
-      if (lens) launch_kernel(ps, k_attn_bwd<4, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, lp);
-      else launch_kernel(ps, k_attn_bwd<4, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, lp);
+      if (lens) launch_kernel(ps, k_attn_bwd<4, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_bwd<4, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
       break;
     case 256:
-      if (lens) launch_kernel(ps, k_attn_bwd<8, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, lp);
-      else launch_kernel(ps, k_attn_bwd<8, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, lp);
+      if (lens) launch_kernel(ps, k_attn_bwd<8, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_bwd<8, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
       break;
     default: break;
   }
 }
-void launch_head_bwd(hipStream_t st, const float* x, int S, int d, int B, int C, const float* theta, int64_t wc_off,
+void launch_head_bwd(hipStream_t st, const float* x, int S, const int32_t* start, int d, int B, int C, const float* theta, int64_t wc_off,
                      int64_t bc_off, const float* dlogits, float* grad, float* dx) {
   ProfScope ps(st, F_OTHER, 0.0);
-  launch_kernel(ps, k_head_bwd_w, (C * d + 255) / 256, 256, 0, st, x, S, d, B, C, dlogits, grad + wc_off, grad + bc_off);
-  launch_kernel(ps, k_head_bwd_x, (B * d + 255) / 256, 256, 0, st, S, d, B, C, theta + wc_off, dlogits, dx);
+  launch_kernel(ps, k_head_bwd_w, (C * d + 255) / 256, 256, 0, st, x, S, start, d, B, C, dlogits, grad + wc_off, grad + bc_off);
+  launch_kernel(ps, k_head_bwd_x, (B * d + 255) / 256, 256, 0, st, S, start, d, B, C, theta + wc_off, dlogits, dx);
+}
+void launch_row_plan(hipStream_t st, const int32_t* ids, const int32_t* lens, int B, int S, const RowSelect& sel, const RowPlan& out) {
+  ProfScope ps(st, F_OTHER, 16.0 * B * S);
+  launch_kernel(ps, k_row_plan, (B * S + 255) / 256, 256, 0, st, ids, lens, B, S, sel, out);
 }
 void launch_select_rows(hipStream_t st, const RowSelect& s, int nw, int pass_rows, int d, const bf16_t* a16, const float* x32,
                         bf16_t* a16_out, float* x32_out) {
   ProfScope ps(st, F_OTHER, 12.0 * nw * s.n * d);
   launch_kernel(ps, k_select_rows, dim3(s.n, nw), 256, 0, st, s, pass_rows, d, a16, x32, a16_out, x32_out);
 }
-void launch_spread_rows(hipStream_t st, const RowSelect& s, int M, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out, float* x32_out) {
+void launch_spread_rows(hipStream_t st, const RowSelect& s, const RowPlan& plan, int M, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out, float* x32_out) {
   ProfScope ps(st, F_OTHER, 6.0 * (M + s.n) * d);
-  launch_kernel(ps, k_spread_rows, M, 256, 0, st, s, d, a16, x32, a16_out, x32_out);
+  launch_kernel(ps, k_spread_rows, M, 256, 0, st, s, plan, d, a16, x32, a16_out, x32_out);
 }
-void launch_embedding_bwd(hipStream_t st, const float* demb, const int32_t* ids, int B, int S, int d, int V, float* g_tok, float* g_pos) {
+void launch_embedding_bwd(hipStream_t st, const float* demb, const int32_t* ids, int B, int S, int d, int V, float* g_tok, float* g_pos,
+                          const RowPlan& plan) {
   ProfScope ps(st, F_OTHER, 4.0 * B * S * d);
-  launch_kernel(ps, k_pos_grad, (S * d + 255) / 256, 256, 0, st, demb, B, S, d, g_pos);
-  launch_kernel(ps, k_tok_grad, B * S, 256, 0, st, demb, ids, B * S, d, V, g_tok);
+  launch_kernel(ps, k_pos_grad, (S * d + 255) / 256, 256, 0, st, demb, B, S, d, plan, g_pos);
+  launch_kernel(ps, k_tok_grad, B * S, 256, 0, st, demb, plan.ids != nullptr ? plan.ids : ids, B * S, plan.start != nullptr ? plan.start + B : nullptr, d, V, g_tok);
 }
 
 }  // namespace sama

@@ -150,16 +150,37 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs; each XCD gets a contiguous run of tile ids, and
   // tile ids walk down `group` tile rows before moving one tile column to the right, so that the tiles in flight on
   // one XCD form a compact patch (few distinct A and B panels in its L2).
-  int pid = (blockIdx.x & 7) * tiles_per_xcd + (blockIdx.x >> 3);
-  if (pid >= ntiles) return;
-  int prob = 0;
+  // Where the rows in use are known on the device only, the launch has the tiles of all rows, and the order is made here over
+  // those in use (the problems of a batch then have the same rows).
+  const int32_t* const in_use = batch.p[0].rows;
+  const int rows = in_use != nullptr ? __builtin_amdgcn_readfirstlane(*in_use) : 0;
+  const bool fewer_tiles = A_KC && in_use != nullptr;
+  int pid, prob = 0;
+  if (fewer_tiles) {
+    const int gy = (rows + BM - 1) / BM;
+    int n = 0;
+    for (int k = 0; k < batch.count; ++k) n += gy * ((batch.p[k].N + BN - 1) / BN);
+    const int per_xcd = (n + 7) / 8;
+    pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || pid >= n) return;
+    for (int k = 0; k + 1 < batch.count; ++k) {
+      const int t = gy * ((batch.p[k].N + BN - 1) / BN);
+      if (pid < t) break;
+      pid -= t;
+      prob = k + 1;
+    }
+  } else {
+    pid = (blockIdx.x & 7) * tiles_per_xcd + (blockIdx.x >> 3);
+    if (pid >= ntiles) return;
 #pragma unroll
-  for (int k = 1; k < GEMM_MAX_BATCH; ++k)
-    if (k < batch.count && pid >= batch.first_tile[k]) prob = k;
-  pid -= batch.first_tile[prob];
+    for (int k = 1; k < GEMM_MAX_BATCH; ++k)
+      if (k < batch.count && pid >= batch.first_tile[k]) prob = k;
+    pid -= batch.first_tile[prob];
+  }
   const GemmBf16Args& a = batch.p[prob];
   const int group = batch.group;
-  const int gx = (a.N + BN - 1) / BN, gy = (a.M + BM - 1) / BM;
+  const int Mrows = fewer_tiles ? rows : a.M;
+  const int gx = (a.N + BN - 1) / BN, gy = (Mrows + BM - 1) / BM;
   const int width = group * gx, grp = pid / width, first = grp * group;
   const int gsz = min(gy - first, group);
   const int ti = first + (pid % width) % gsz, tj = (pid % width) / gsz;
@@ -173,7 +194,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
 
-  const int nk = a.K / BK;
+  const int nk = (!A_KC && a.rows != nullptr ? __builtin_amdgcn_readfirstlane(*a.rows) : a.K) / BK;
   // The operand pointers live in registers for the whole k loop (read through `a` they would be re-fetched from the
   // kernel-argument segment after every inline-assembly load, a scalar-memory round trip per slab).
   const char* const pA = reinterpret_cast<const char*>(a.A);
@@ -186,7 +207,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   // per-lane global offsets of this wave's loads
   uint32_t offA[T::NLA], offB[T::NLB];
 #pragma unroll
-  for (int q = 0; q < T::NLA; ++q) offA[q] = piece_offset<A_KC, BM, BK>((q * T::LW + lw) * 1024 + lane * 16, i0, a.M, a.lda);
+  for (int q = 0; q < T::NLA; ++q) offA[q] = piece_offset<A_KC, BM, BK>((q * T::LW + lw) * 1024 + lane * 16, i0, Mrows, a.lda);
 #pragma unroll
   for (int q = 0; q < T::NLB; ++q) offB[q] = piece_offset<B_KC, BN, BK>((q * T::LW + lw) * 1024 + lane * 16, j0, a.N, a.ldb);
   const int64_t stepA = A_KC ? (int64_t)BK * 2 : (int64_t)BK * a.lda * 2;   // bytes per slab
@@ -361,7 +382,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   }
   const bf16_t* const res16 = a.res16; const float* const res32 = a.res32; const bf16_t* const aux16 = a.aux16;
   bf16_t* const C16_pre = a.C16_pre; bf16_t* const C16 = a.C16; float* const C32 = a.C32;
-  const int act = a.act, Mrows = a.M;
+  const int act = a.act;
   const int64_t ldc = a.ldc;
   constexpr int NIT = 32 / RPP;
   // one output vector: bias, residual, activation, stores
@@ -520,9 +541,11 @@ int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count) {
     int64_t tiles = 0;
     double slabs = 0.0;                                    // of all tiles
     for (int k = 0; k < count; ++k) {
-      const int64_t t = (int64_t)((p[k].M + c.bm - 1) / c.bm) * ((p[k].N + c.bn - 1) / c.bn);
+      // of a padded batch two thirds of the rows are expected to be in use
+      const int M = p[k].rows != nullptr && !p[k].a_trans ? (p[k].M * 2 + 2) / 3 : p[k].M, K = p[k].rows != nullptr && p[k].a_trans ? (p[k].K * 2 + 2) / 3 : p[k].K;
+      const int64_t t = (int64_t)((M + c.bm - 1) / c.bm) * ((p[k].N + c.bn - 1) / c.bn);
       tiles += t;
-      slabs += (double)t * (p[k].K / 64);
+      slabs += (double)t * K / 64.0;
     }
     slabs /= (double)tiles;
     const int64_t cap = 256 * c.per_cu, rest = tiles % cap;

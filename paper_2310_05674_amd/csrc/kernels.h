@@ -160,6 +160,7 @@ struct HeadView {
   const float* x; int64_t stride, pass_stride;
   int k;
   ParamView pv; int64_t w_off, b_off;
+  const int32_t* start;   // null, or row (of k values) of each sample instead of i * stride / k
   bool dots;   // few rows of many features: each logit a dot product of one wave; otherwise fp32 matrix-core tiles
 };
 struct SampleStageArgs {
@@ -222,6 +223,7 @@ struct GemmBf16Args {
   const bf16_t* res16; const float* res32;
   int act; const bf16_t* aux16; bf16_t* C16_pre;
   float* C32; bf16_t* C16;
+  const int32_t* rows;   // null, or (device) the token rows in use: a multiple of 64 that replaces M (a_trans = 0) or K (a_trans = 1)
 };
 const char* check_gemm_bf16(const GemmBf16Args&);  // null if the shapes / alignments are supported
 void launch_gemm_bf16(hipStream_t, const GemmBf16Args&);
@@ -238,11 +240,29 @@ void gemm_bf16_force_shape(int shape);  // tuning hook: 0 = heuristic, else 100 
 constexpr int LN_MAX_D = 2048;       // LayerNorm kernels keep a row in registers (4 or 8 16-byte pieces per lane)
 constexpr int LN_BWD_ROWS = 8;       // rows per block in the LayerNorm backward (size of its partial sums)
 constexpr int COLSUM_ROWS = 16;      // rows per block in the column-sum kernel
+// Where the token rows of a padded batch lie.  Of each sequence only the positions that can influence a result are there, its
+// real tokens (and masked positions), rounded up to 16 so that the groups of 16 rows the matrix cores add at a time are those of
+// the padded batch and every sum over rows keeps its order; the sequences follow one another.  All null: nothing is left out,
+// position p of sequence b is row b S + p.
+constexpr int ROW_GROUP = 16;
+constexpr int MAX_SEQ = MAX_TOKENS / 64;
+struct RowPlan {
+  int32_t* start;   // [B + 1] row of each sequence's position 0; start[B] = rows of all sequences
+  int32_t* rows;    // [1] start[B] rounded up to a multiple of 64
+  int32_t* ids;     // [M] token of each row (0 behind start[B])
+  int32_t* src;     // [M] b S + p of each row (-1 behind start[B])
+  int32_t* group;   // [M / 16] where each group of 16 rows of the padded batch went, in groups, or -1
+};
+struct RowSelect;
+// lens [B]: real tokens; sel.n_mask > 0: masked positions to keep as well
+void launch_row_plan(hipStream_t, const int32_t* ids, const int32_t* lens, int B, int S, const RowSelect& sel, const RowPlan& out);
 struct LnFwdArgs {
   const float* x;          // [M x d] input, or null: embedding mode (x = tok_emb[id] + pos_emb[m % S])
   const int32_t* ids; int S; int64_t tok_off, pos_off; float* x_out;  // embedding mode; x_out [M x d] may be null
   int V;                   // embedding mode: vocabulary size, ids are clamped into [0, V)
-  int ids_rows;            // embedding mode: row r reads ids[r % ids_rows] (0 = M; stacked passes share one id array)
+  int pass_rows;           // rows of one of the stacked passes (0: not stacked); they share the ids
+  const int32_t* rows;     // null, or rows in use of each pass (RowPlan); embedding mode then takes src's positions
+  const int32_t* src;
   ParamView pv; int64_t g_off, b_off;                                 // gamma / beta inside theta
   bf16_t* y; float* y32; float* mean; float* rstd;                    // y32 (fp32 copy for the residual path), mean, rstd may be null
   int M, d;
@@ -253,6 +273,7 @@ struct LnBwdArgs {
   float* dx32; bf16_t* dx16;
   float* partial;          // [ceil(M / LN_BWD_ROWS)][3][d]: dgamma, dbeta, column sums of dx
   int M, d;
+  const int32_t* rows;     // null, or rows in use
 };
 void launch_ln_bwd(hipStream_t, const LnBwdArgs&);
 // out_v[c] = sum_r partial[r*stride + v*vstride + c] for the non-null outputs v = 0, 1, 2, in a fixed order
@@ -266,21 +287,23 @@ constexpr int REDUCE_MAX_JOBS = 4;
 struct ReduceRowsJob {
   const float* partial; int nrows; int64_t stride, vstride; int N; float* out[3];
   int seq_blocks, kept_blocks;              // 0, or: of each seq_blocks blocks the first kept_blocks are there
+  const int32_t* group; int group_blocks;   // null, or RowPlan's, and blocks per group
 };
 void launch_reduce_rows_multi(hipStream_t, const ReduceRowsJob* jobs, int count);
 // first stage of the column sums of up to two bf16 matrices [M x N] (ld = N): partial [ceil(M / COLSUM_ROWS)][N]
-struct ColsumJob { const bf16_t* X; int M, N; float* partial; };
+struct ColsumJob { const bf16_t* X; int M, N; float* partial; const int32_t* rows; };   // rows: null, or rows in use
 void launch_colsum_partial_multi(hipStream_t, const ColsumJob* jobs, int count);
 // column sums of a bf16 matrix [M x N] (ld = N) through partial [ceil(M / COLSUM_ROWS)][N]
 void launch_colsum_bf16(hipStream_t, const bf16_t* X, int M, int N, float* partial, float* out);
 // softmax(q k^T / 8) v for S in {64, 128, 256} (attention_supports), head width 64; qkv [B*S x 3d] bf16; out [B*S x d]
-// bf16; lse [B][heads][S].  lens (device, or null = all S): sequence b has lens[b % lens_period] real tokens (clamped into
-// [1, S]); keys beyond get no weight.
+// bf16; lse [nw B][heads][S]; nw stacked passes of B sequences.  lens (device, or null = all S): sequence b has lens[b] real
+// tokens (clamped into [1, S]); keys beyond get no weight; its rows lie where the plan says.  Rows of the plan that belong to
+// no sequence get zeros.
 bool attention_supports(int S);
-void launch_attention_fwd(hipStream_t, const bf16_t* qkv, bf16_t* out, float* lse, int B, int S, int heads, int d,
-                          const int32_t* lens, int lens_period);
+void launch_attention_fwd(hipStream_t, const bf16_t* qkv, bf16_t* out, float* lse, int nw, int B, int S, int heads, int d,
+                          const int32_t* lens, const RowPlan& plan);
 void launch_attention_bwd(hipStream_t, const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, const float* lse,
-                          bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, int lens_period);
+                          bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, const RowPlan& plan);
 // The token rows whose last hidden state is read, side by side in a compact matrix of n rows (a multiple of 64; rows without a
 // token are zero).  Either the first SELECT_SEQ_ROWS positions of each of n_cls sequences -- the classifier reads the first of
 // them, and sums over token rows keep the composition of the groups of 16 that the matrix cores add at a time --, or
@@ -291,19 +314,33 @@ struct RowSelect {
   int n_mask;
   const int32_t* mask_rows;                 // [n_mask] token row among the mask_total rows from mask_base on, clamped into range
   int mask_base, mask_total;
+  const int32_t* start;                     // RowPlan's (null: nothing left out)
 };
+// token row of compact row i (i < s.n), or -1 where there is none
+__device__ __forceinline__ int selected_row(const RowSelect& s, int i) {
+  if (s.n_mask > 0) {
+    if (i >= s.n_mask) return -1;
+    const int r = s.mask_base + min(max(s.mask_rows[i], 0), s.mask_total - 1);
+    return s.start != nullptr ? s.start[r / s.S] + r % s.S : r;
+  }
+  const int b = i / SELECT_SEQ_ROWS;
+  if (b >= s.n_cls) return -1;
+  return (s.start != nullptr ? s.start[b] : b * s.S) + i % SELECT_SEQ_ROWS;
+}
 // compact row i of pass k <- row of token i (passes pass_rows apart in the sources, n in the results); x32 / x32_out may be null
 void launch_select_rows(hipStream_t, const RowSelect&, int nw, int pass_rows, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out,
                         float* x32_out);
 // The adjoint for a selection by sequence: each of the M token rows = its compact row, or zero
-void launch_spread_rows(hipStream_t, const RowSelect&, int M, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out, float* x32_out);
-// dWc, dbc into grad; dx[b*S][:] = dlogits[b] . Wc written into the zero-filled dx; S = rows of x and dx per sequence
-void launch_head_bwd(hipStream_t, const float* x, int S, int d, int B, int C, const float* theta, int64_t wc_off,
+void launch_spread_rows(hipStream_t, const RowSelect&, const RowPlan&, int M, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out, float* x32_out);
+// dWc, dbc into grad; dx[r][:] = dlogits[b] . Wc written into the zero-filled dx, with r = b S, or start[b] when start is given
+void launch_head_bwd(hipStream_t, const float* x, int S, const int32_t* start, int d, int B, int C, const float* theta, int64_t wc_off,
                      int64_t bc_off, const float* dlogits, float* grad, float* dx);
 // embedding gradients from demb [B*S x d]: pos_emb rows summed over the batch; tok_emb rows summed over the
 // occurrences of each id in ascending position order (the tok_emb part of grad must be zero on entry)
 // (ids outside [0, V) are clamped into it, here and in the forward pass)
-void launch_embedding_bwd(hipStream_t, const float* demb, const int32_t* ids, int B, int S, int d, int V, float* g_tok, float* g_pos);
+// with a plan: demb by its rows, ids the plan's
+void launch_embedding_bwd(hipStream_t, const float* demb, const int32_t* ids, int B, int S, int d, int V, float* g_tok, float* g_pos,
+                          const RowPlan& plan);
 
 
 // ------------------------------------------------------------------ masked-token head (mlm_head.hip)
@@ -320,8 +357,7 @@ void launch_mlm_ce(hipStream_t, const float* Z, int V, int P, const int32_t* tgt
 // dZ [P x V] bf16 = coef_pos[j] (softmax(Z[j]) - onehot(tgt[j])), zero rows from n_mask on
 void launch_mlm_dz(hipStream_t, const float* Z, int V, const int32_t* tgt, const float* coef_pos, const float* lse_pos,
                    int n_mask, int P, bf16_t* dZ);
-// dx[row_base + rows[j]][:] += sum_{k < nparts} part[k * part_stride + j * d + :]; the rows must be distinct
-void launch_scatter_add_rows(hipStream_t, const float* part, int nparts, int64_t part_stride, int row_base, int rows_in_batch,
-                             const int32_t* rows, int n_mask, int d, float* dx);
+// dx[selected_row(sel, j)][:] += sum_{k < nparts} part[k * part_stride + j * d + :] for the masked positions j; they are distinct
+void launch_scatter_add_rows(hipStream_t, const float* part, int nparts, int64_t part_stride, const RowSelect& sel, int d, float* dx);
 
 }  // namespace sama

@@ -122,12 +122,11 @@ __global__ __launch_bounds__(CE_THREADS) void k_mlm_dz(const float* Z, int V, co
   }
 }
 
-// dx[row_base + rows[j]][:] += sum_k part[k][j][:]  (positions are distinct: one workgroup owns one row of dx)
-__global__ __launch_bounds__(256) void k_scatter_add_rows(const float* part, int nparts, int64_t part_stride, int row_base,
-                                                          int rows_in_batch, const int32_t* rows, int d, float* dx) {
+// dx[row of position j][:] += sum_k part[k][j][:]  (positions are distinct: one workgroup owns one row of dx)
+__global__ __launch_bounds__(256) void k_scatter_add_rows(const float* part, int nparts, int64_t part_stride, RowSelect sel, int d,
+                                                          float* dx) {
   const int j = blockIdx.x;
-  const int r = clampi(rows[j], 0, rows_in_batch - 1);
-  float* o = dx + (int64_t)(row_base + r) * d;
+  float* o = dx + (int64_t)selected_row(sel, j) * d;
   for (int c = threadIdx.x; c < d; c += 256) {
     float acc = 0.f;
     for (int k = 0; k < nparts; ++k) acc += part[k * part_stride + (int64_t)j * d + c];
@@ -158,10 +157,10 @@ void launch_mlm_dz(hipStream_t st, const float* Z, int V, const int32_t* tgt, co
   ProfScope ps(st, F_MLM_SOFTMAX, 6.0 * n_mask * (double)V + 2.0 * (P - n_mask) * (double)V);
   launch_kernel(ps, k_mlm_dz, P, CE_THREADS, 0, st, Z, V, tgt, coef_pos, lse_pos, n_mask, dZ);
 }
-void launch_scatter_add_rows(hipStream_t st, const float* part, int nparts, int64_t part_stride, int row_base, int rows_in_batch,
-                             const int32_t* rows, int n_mask, int d, float* dx) {
-  ProfScope ps(st, F_OTHER, 4.0 * (nparts + 2) * n_mask * d);
-  launch_kernel(ps, k_scatter_add_rows, n_mask, 256, 0, st, part, nparts, part_stride, row_base, rows_in_batch, rows, d, dx);
+void launch_scatter_add_rows(hipStream_t st, const float* part, int nparts, int64_t part_stride, const RowSelect& sel, int d,
+                             float* dx) {
+  ProfScope ps(st, F_OTHER, 4.0 * (nparts + 2) * sel.n_mask * d);
+  launch_kernel(ps, k_scatter_add_rows, sel.n_mask, 256, 0, st, part, nparts, part_stride, sel, d, dx);
 }
 
 }  // namespace sama

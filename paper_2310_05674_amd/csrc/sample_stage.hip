@@ -88,25 +88,43 @@ __device__ void head_logits(const HeadView& h, int pass, int i_begin, int n_own,
 // The same with a wave per sample: 64 strided partial sums in fp32, joined by a shuffle tree.  The losses of the two passes of
 // Eq. 5 differ in their last digits only, and a deep model's gradients follow those of its logits, so what the
 // encoder's logits are rounded to is kept independent of how a workgroup's tiles split the features.
+// Up to four samples of a wave and four classes share each element of W that is read.
+template <bool PERTURBED>
 __device__ void head_dots(const HeadView& h, int pass, int i_begin, int n_own, int C, double* __restrict__ s_z) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float s = pass == 0 ? h.pv.scale() : -h.pv.scale();
-  constexpr int CU = 4;   // classes at a time
-  for (int i = wave; i < n_own; i += FWAVES) {
-    const float* x = h.x + pass * h.pass_stride + (int64_t)(i_begin + i) * h.stride;
+  constexpr int CU = 4, SU = ST_SAMPLES / FWAVES;   // sample wave + FWAVES u of the workgroup's is this wave's u-th
+  const float* x[SU];
+#pragma unroll
+  for (int u = 0; u < SU; ++u) {
+    const int i = i_begin + min(wave + FWAVES * u, n_own - 1);
+    x[u] = h.x + pass * h.pass_stride + (h.start != nullptr ? (int64_t)h.start[i] * h.k : (int64_t)i * h.stride);
+  }
+  if (wave < n_own) {
     for (int c0 = 0; c0 < C; c0 += CU) {
-      float acc[CU] = {0.f, 0.f, 0.f, 0.f};
+      float acc[SU][CU] = {};
 #pragma unroll 4
       for (int k = lane; k < h.k; k += 64) {
-        const float xk = x[k];
+        float w[CU], xk[SU];
 #pragma unroll
-        for (int u = 0; u < CU; ++u) acc[u] = fmaf(xk, h.pv.at(h.w_off + (int64_t)min(c0 + u, C - 1) * h.k + k, s), acc[u]);
+        for (int c = 0; c < CU; ++c) {
+          const int64_t o = h.w_off + (int64_t)min(c0 + c, C - 1) * h.k + k;
+          w[c] = PERTURBED ? fmaf(s, h.pv.vdir[o], h.pv.theta[o]) : h.pv.theta[o];
+        }
+#pragma unroll
+        for (int u = 0; u < SU; ++u) xk[u] = x[u][k];
+#pragma unroll
+        for (int u = 0; u < SU; ++u)
+#pragma unroll
+          for (int c = 0; c < CU; ++c) acc[u][c] = fmaf(xk[u], w[c], acc[u][c]);
       }
 #pragma unroll
-      for (int u = 0; u < CU; ++u) {
-        const float z = wave_sum(acc[u]);
-        if (lane == 0 && c0 + u < C) s_z[i * 64 + c0 + u] = (double)(z + h.pv.at(h.b_off + c0 + u, s));
-      }
+      for (int u = 0; u < SU; ++u)
+#pragma unroll
+        for (int c = 0; c < CU; ++c) {
+          const float z = wave_sum(acc[u][c]);
+          if (lane == 0 && c0 + c < C && wave + FWAVES * u < n_own) s_z[(wave + FWAVES * u) * 64 + c0 + c] = (double)(z + h.pv.at(h.b_off + c0 + c, s));
+        }
     }
   }
   __syncthreads();
@@ -223,7 +241,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
   const double inv_beff = beff > 0.0 ? 1.0 / beff : 0.0;
   __syncthreads();
   if (!seq_mode) {
-    if (a.head.dots) head_dots(a.head, pass, i_begin, n_own, C, s_z);
+    if (a.head.dots && a.head.pv.scale() != 0.f) head_dots<true>(a.head, pass, i_begin, n_own, C, s_z);
+    else if (a.head.dots) head_dots<false>(a.head, pass, i_begin, n_own, C, s_z);
     else head_logits(a.head, pass, i_begin, n_own, C, s_hred, s_z);
   }
   const float* W1 = s_lam; const float* b1 = s_lam + H; const float* W2 = s_lam + 2 * H;
