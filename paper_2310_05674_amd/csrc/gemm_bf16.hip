@@ -25,8 +25,9 @@
 // Several independent problems of one storage class can share a launch (the + and - pass of Eq. 5, the four weight
 // gradients of a layer): more tiles per launch for the small per-layer shapes.
 //
-// Fused epilogues: + bias (fp32, optionally perturbed), + residual (bf16 or fp32), GELU forward (writes both the
+// Fused epilogues: + bias (fp32, optionally perturbed), + residual (fp32), GELU forward (writes both the
 // pre-activation and the activation), GELU backward (multiplies by gelu'(pre)), fp32 and/or bf16 stores.
+#include <type_traits>
 #include "common.h"
 #include "kernels.h"
 
@@ -62,9 +63,16 @@ struct Tile {
   static_assert(NL * (NSTAGE - 2) <= 63, "vmcnt range");
 };
 
+// The correctly rounded 1 / y of a y in [1, 2^100]: the hardware's approximation and one Newton step (checked against
+// __frcp_rn for every float of that range), a third of the instructions of the general division.
+__device__ __forceinline__ float recip_rn(float y) {
+  const float r = __builtin_amdgcn_rcpf(y);
+  return fmaf(fmaf(-y, r, 1.f), r, r);
+}
+// For |z| so large that y would leave the range, exp(-z^2) is 0 and so is whatever it is multiplied by.
 __device__ __forceinline__ void erf_and_gauss(float z, float& erfz, float& ez2) {
   const float az = fabsf(z);
-  const float t = __frcp_rn(fmaf(0.3275911f, az, 1.f));
+  const float t = recip_rn(fminf(fmaf(0.3275911f, az, 1.f), 0x1p100f));
   ez2 = __expf(-az * az);
   const float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f), 0.254829592f);
   const float e = 1.f - poly * ez2;
@@ -380,100 +388,102 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
       bias.x = fmaf(s, bv.x, bias.x); bias.y = fmaf(s, bv.y, bias.y); bias.z = fmaf(s, bv.z, bias.z); bias.w = fmaf(s, bv.w, bias.w);
     }
   }
-  const bf16_t* const res16 = a.res16; const float* const res32 = a.res32; const bf16_t* const aux16 = a.aux16;
+  const float* const res32 = a.res32; const bf16_t* const aux16 = a.aux16;
   bf16_t* const C16_pre = a.C16_pre; bf16_t* const C16 = a.C16; float* const C32 = a.C32;
   const int act = a.act;
-  const int64_t ldc = a.ldc;
+  const int64_t ldc = a.ldc, base = (int64_t)(i0 + wr) * ldc + j0 + wc;   // of the wave's tile
+  const uint32_t lane_off = (uint32_t)(rq * ldc) + 4u * cg;               // a step is a uniform distance plus this (rq < 8)
   constexpr int NIT = 32 / RPP;
-  // one output vector: bias, residual, activation, stores
-  auto finish = [&](const float4& v, int64_t o, const float4& rr32, const uint2& rr16, const uint2& axv) {
-    float c[4] = {v.x + bias.x, v.y + bias.y, v.z + bias.z, v.w + bias.w};
-    if (res16 != nullptr) {
-      c[0] += bf16_to_f32((bf16_t)rr16.x); c[1] += bf16_to_f32((bf16_t)(rr16.x >> 16));
-      c[2] += bf16_to_f32((bf16_t)rr16.y); c[3] += bf16_to_f32((bf16_t)(rr16.y >> 16));
-    }
-    if (res32 != nullptr) { c[0] += rr32.x; c[1] += rr32.y; c[2] += rr32.z; c[3] += rr32.w; }
-    if (act == GEMM_ACT_GELU_FWD) {
-      uint2 pk;
-      pk.x = pack_bf16x2(c[0], c[1]);
-      pk.y = pack_bf16x2(c[2], c[3]);
-      if (C16_pre != nullptr) *reinterpret_cast<uint2*>(C16_pre + o) = pk;   // forward-only passes do not keep it
-      // the backward pass sees the rounded pre-activation, so the activation is taken from it too
-      c[0] = gelu_f(bf16_to_f32((bf16_t)pk.x)); c[1] = gelu_f(bf16_to_f32((bf16_t)(pk.x >> 16)));
-      c[2] = gelu_f(bf16_to_f32((bf16_t)pk.y)); c[3] = gelu_f(bf16_to_f32((bf16_t)(pk.y >> 16)));
-    } else if (act == GEMM_ACT_GELU_BWD) {
-      c[0] *= dgelu_f(bf16_to_f32((bf16_t)axv.x)); c[1] *= dgelu_f(bf16_to_f32((bf16_t)(axv.x >> 16)));
-      c[2] *= dgelu_f(bf16_to_f32((bf16_t)axv.y)); c[3] *= dgelu_f(bf16_to_f32((bf16_t)(axv.y >> 16)));
-    }
-    if (C32 != nullptr) *reinterpret_cast<float4*>(C32 + o) = make_float4(c[0], c[1], c[2], c[3]);
-    if (C16 != nullptr) {
-      uint2 pk;
-      pk.x = pack_bf16x2(c[0], c[1]);
-      pk.y = pack_bf16x2(c[2], c[3]);
-      *reinterpret_cast<uint2*>(C16 + o) = pk;
-    }
-  };
-  const bool side = res32 != nullptr || res16 != nullptr || act == GEMM_ACT_GELU_BWD;
-  constexpr bool PREFETCH = NIT <= 8;   // wider wave tiles have no registers to spare for the side inputs of a whole slice
+  // A slice of 32 rows goes through LDS at a time and is finished four steps (of RPP rows) at a time, each operation for the
+  // four together; the side inputs (an fp32 residual or a saved pre-activation, an epilogue has one of them at most) of the next
+  // four steps are requested before the current ones are finished, across the slices.
+  constexpr int CH = 4, PER = NIT / CH, NCH = XT * PER;
+  static_assert(NIT % CH == 0, "steps of a slice");
+  const bool side = res32 != nullptr || act == GEMM_ACT_GELU_BWD;
+  auto epilogue = [&](auto all_rows) {   // all_rows: every row of the tile exists
+    auto exists = [&](int row) { return decltype(all_rows)::value || i0 + wr + row < Mrows; };   // row: within the wave's tile
+    auto step = [&](int q, int u) { return base + (int64_t)((q / PER) * 32 + RPP * ((q % PER) * CH + u)) * ldc; };
+    auto row_of = [&](int q, int u) { return rq + RPP * ((q % PER) * CH + u); };   // within the slice
+    auto load_side = [&](int q, uint4 (&sv)[CH]) {
 #pragma unroll
-  for (int x = 0; x < XT; ++x) {
-    // Side inputs of this 32-row slice (residual, saved pre-activation) are requested before the accumulators go
-    // through LDS, so that their latency hides behind the staging.  Launches without side inputs skip this path.
-    float4 r32[PREFETCH ? NIT : 1];
-    uint2 r16[PREFETCH ? NIT : 1], ax[PREFETCH ? NIT : 1];
-    if (PREFETCH && side && col_ok) {
-#pragma unroll
-      for (int itr = 0; itr < (PREFETCH ? NIT : 1); ++itr) {
-        const int gi = i0 + wr + x * 32 + rq + RPP * itr;
-        r32[itr] = make_float4(0.f, 0.f, 0.f, 0.f); r16[itr] = make_uint2(0u, 0u); ax[itr] = make_uint2(0u, 0u);
-        if (gi < Mrows) {
-          const int64_t o = (int64_t)gi * ldc + gj;
-          if (res32 != nullptr) r32[itr] = *reinterpret_cast<const float4*>(res32 + o);
-          if (res16 != nullptr) r16[itr] = *reinterpret_cast<const uint2*>(res16 + o);
-          if (act == GEMM_ACT_GELU_BWD) ax[itr] = *reinterpret_cast<const uint2*>(aux16 + o);
+      for (int u = 0; u < CH; ++u) {
+        if (!exists((q / PER) * 32 + row_of(q, u))) continue;
+        if (res32 != nullptr) {
+          sv[u] = *reinterpret_cast<const uint4*>(res32 + step(q, u) + lane_off);
+        } else {
+          const uint2 t = *reinterpret_cast<const uint2*>(aux16 + step(q, u) + lane_off);
+          sv[u].x = t.x; sv[u].y = t.y;
         }
       }
+    };
+    constexpr bool AHEAD = XT * YT <= 4;   // more accumulators leave no registers for two sets of side inputs
+    uint4 sv[AHEAD ? 2 : 1][CH] = {};
+    if (AHEAD && side && col_ok) load_side(0, sv[0]);
+#pragma unroll
+    for (int q = 0; q < NCH; ++q) {
+      const int x = q / PER;
+      if (!AHEAD && side && col_ok) load_side(q, sv[0]);
+      if (q % PER == 0) {
+        // the staging region is private to the wave: LDS operations of one wave complete in order, no block barrier
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+#pragma unroll
+        for (int y = 0; y < YT; ++y)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            epi[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * EPI_LD + y * 32 + (lane & 31)] = acc[x][y][r];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      }
+      if (!col_ok) continue;
+      if (AHEAD && side && q + 1 < NCH) load_side(q + 1, sv[AHEAD ? (q + 1) & 1 : 0]);
+      float c[CH][4];
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const float4 v = *reinterpret_cast<const float4*>(epi + row_of(q, u) * EPI_LD + 4 * cg);
+        c[u][0] = v.x + bias.x; c[u][1] = v.y + bias.y; c[u][2] = v.z + bias.z; c[u][3] = v.w + bias.w;
+      }
+      if (res32 != nullptr) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+          const uint4 r = sv[AHEAD ? q & 1 : 0][u];
+          c[u][0] += __uint_as_float(r.x); c[u][1] += __uint_as_float(r.y); c[u][2] += __uint_as_float(r.z); c[u][3] += __uint_as_float(r.w);
+        }
+      }
+      if (act == GEMM_ACT_GELU_FWD) {
+        // the backward pass sees the rounded pre-activation, so the activation is taken from it too
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+          const uint2 pk = make_uint2(pack_bf16x2(c[u][0], c[u][1]), pack_bf16x2(c[u][2], c[u][3]));
+          if (C16_pre != nullptr && exists(x * 32 + row_of(q, u))) *reinterpret_cast<uint2*>(C16_pre + step(q, u) + lane_off) = pk;   // forward-only passes do not keep it
+          c[u][0] = bf16_to_f32((bf16_t)pk.x); c[u][1] = bf16_to_f32((bf16_t)(pk.x >> 16));
+          c[u][2] = bf16_to_f32((bf16_t)pk.y); c[u][3] = bf16_to_f32((bf16_t)(pk.y >> 16));
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) c[u][e] = gelu_f(c[u][e]);
+      } else if (act == GEMM_ACT_GELU_BWD) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+          const uint4 r = sv[AHEAD ? q & 1 : 0][u];
+          c[u][0] *= dgelu_f(bf16_to_f32((bf16_t)r.x)); c[u][1] *= dgelu_f(bf16_to_f32((bf16_t)(r.x >> 16)));
+          c[u][2] *= dgelu_f(bf16_to_f32((bf16_t)r.y)); c[u][3] *= dgelu_f(bf16_to_f32((bf16_t)(r.y >> 16)));
+        }
+      }
+      if (C32 != nullptr) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          if (exists(x * 32 + row_of(q, u))) *reinterpret_cast<float4*>(C32 + step(q, u) + lane_off) = make_float4(c[u][0], c[u][1], c[u][2], c[u][3]);
+      }
+      if (C16 != nullptr) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          if (exists(x * 32 + row_of(q, u))) *reinterpret_cast<uint2*>(C16 + step(q, u) + lane_off) = make_uint2(pack_bf16x2(c[u][0], c[u][1]), pack_bf16x2(c[u][2], c[u][3]));
+      }
     }
-    // the staging region is private to the wave: LDS operations of one wave complete in order, no block barrier
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-#pragma unroll
-    for (int y = 0; y < YT; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        epi[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * EPI_LD + y * 32 + (lane & 31)] = acc[x][y][r];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (!col_ok) continue;
-    if (side && PREFETCH) {
-#pragma unroll
-      for (int itr = 0; itr < (PREFETCH ? NIT : 1); ++itr) {
-        const int row = rq + RPP * itr, gi = i0 + wr + x * 32 + row;
-        if (gi >= Mrows) break;
-        finish(*reinterpret_cast<const float4*>(epi + row * EPI_LD + 4 * cg), (int64_t)gi * ldc + gj, r32[itr], r16[itr], ax[itr]);
-      }
-    } else if (side) {
-#pragma unroll 4
-      for (int itr = 0; itr < NIT; ++itr) {
-        const int row = rq + RPP * itr, gi = i0 + wr + x * 32 + row;
-        if (gi >= Mrows) break;
-        const int64_t o = (int64_t)gi * ldc + gj;
-        float4 q32 = make_float4(0.f, 0.f, 0.f, 0.f);
-        uint2 q16 = make_uint2(0u, 0u), qa = make_uint2(0u, 0u);
-        if (res32 != nullptr) q32 = *reinterpret_cast<const float4*>(res32 + o);
-        if (res16 != nullptr) q16 = *reinterpret_cast<const uint2*>(res16 + o);
-        if (act == GEMM_ACT_GELU_BWD) qa = *reinterpret_cast<const uint2*>(aux16 + o);
-        finish(*reinterpret_cast<const float4*>(epi + row * EPI_LD + 4 * cg), o, q32, q16, qa);
-      }
-    } else {
-      const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
-      const uint2 z2 = make_uint2(0u, 0u);
-#pragma unroll 4
-      for (int itr = 0; itr < NIT; ++itr) {
-        const int row = rq + RPP * itr, gi = i0 + wr + x * 32 + row;
-        if (gi >= Mrows) break;
-        finish(*reinterpret_cast<const float4*>(epi + row * EPI_LD + 4 * cg), (int64_t)gi * ldc + gj, z4, z2, z2);
-      }
-    }
-  }
+  };
+  if (i0 + wr >= Mrows) return;
+  if (i0 + BM <= Mrows) epilogue(std::true_type{});
+  else epilogue(std::false_type{});
 }
 
 template <typename T, bool A_KC, bool B_KC>
@@ -592,7 +602,8 @@ const char* check_gemm_bf16(const GemmBf16Args& a) {
   if (a.lda % 8 != 0 || a.ldb % 8 != 0 || a.ldc % 4 != 0) return "leading dimensions must be multiples of 8 (A, B) and 4 (C)";
   if (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.B2 | (uintptr_t)a.bias | (uintptr_t)a.bias_v | (uintptr_t)a.C32 |
        (uintptr_t)a.res32) & 15) return "operands, bias, fp32 residual and fp32 output must be 16-byte aligned";
-  if (((uintptr_t)a.C16 | (uintptr_t)a.C16_pre | (uintptr_t)a.aux16 | (uintptr_t)a.res16) & 7) return "bf16 epilogue tensors must be 8-byte aligned";
+  if (((uintptr_t)a.C16 | (uintptr_t)a.C16_pre | (uintptr_t)a.aux16) & 7) return "bf16 epilogue tensors must be 8-byte aligned";
+  if (a.res32 != nullptr && a.act == GEMM_ACT_GELU_BWD) return "a residual and the GELU backward exclude each other";
   if (a.lda < (a.a_trans ? a.M : a.K) || a.ldb < (a.b_trans ? a.K : a.N) || a.ldc < a.N) return "leading dimension too small";
   const int64_t abytes = (int64_t)(a.a_trans ? a.K : a.M) * a.lda * 2, bbytes = (int64_t)(a.b_trans ? a.N : a.K) * a.ldb * 2;
   if (abytes >= ((int64_t)1 << 31) || bbytes >= ((int64_t)1 << 31)) return "operands must be smaller than 2 GiB";

@@ -212,7 +212,7 @@ void launch_gemm_f32_batch(hipStream_t, const GemmF32Args* p, int count);
 enum { GEMM_ACT_NONE = 0, GEMM_ACT_GELU_FWD = 1, GEMM_ACT_GELU_BWD = 2 };
 // C[M x N] = A . (B + B2).  a_trans = 0: A stored [M][K]; 1: stored [K][M].  b_trans = 1: B stored [N][K]
 // (a weight matrix [out x in] used forward); 0: stored [K][N].  B2 (same storage as B) may be null.
-// Epilogue, in this order: + bias[j] (+ bsign * *beps * bias_v[j]); + res16 / res32 [i*ldc + j];
+// Epilogue, in this order: + bias[j] (+ bsign * *beps * bias_v[j]); + res32 [i*ldc + j] (not with GELU_BWD);
 // GELU_FWD: C16_pre = bf16(c) (stored when C16_pre is given), c = gelu(that);  GELU_BWD: c *= gelu'(aux16[i*ldc + j]);  stores to C32 and/or C16.
 struct GemmBf16Args {
   const bf16_t* A; int64_t lda; int a_trans;
@@ -220,7 +220,7 @@ struct GemmBf16Args {
   int M, N, K;
   int64_t ldc;
   const float* bias; const float* bias_v; const float* beps; float bsign;
-  const bf16_t* res16; const float* res32;
+  const float* res32;
   int act; const bf16_t* aux16; bf16_t* C16_pre;
   float* C32; bf16_t* C16;
   const int32_t* rows;   // null, or (device) the token rows in use: a multiple of 64 that replaces M (a_trans = 0) or K (a_trans = 1)
