@@ -299,18 +299,21 @@ __global__ __launch_bounds__(256) void k_colsum_partial_bf16(ColsumMulti m) {
 // Sequence length S = 32 NT (NT = 2, 4 or 8 tiles of 32 positions), head width 64.
 constexpr int AD = 64;  // head width
 
-__device__ __forceinline__ bf16x8 ld_bf16x8(const bf16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
 __device__ __forceinline__ s16x4 pack4(float a, float b, float c, float d) {
   s16x4 r;
   r[0] = (short)f32_to_bf16(a); r[1] = (short)f32_to_bf16(b); r[2] = (short)f32_to_bf16(c); r[3] = (short)f32_to_bf16(d);
   return r;
 }
 
-// A [ROWS x 64] bf16 tile (row stride ld) staged in LDS as it lies in memory, S[row][e] with row stride SLD (192 bytes:
-// the four rows one transposing read touches fall into four different 64-byte bank windows), and its transposed MFMA
-// operand: for the 32x32x8 MFMA, lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] through ds_read_b64_tr_b16.
+// A [ROWS x 64] bf16 matrix of a head (row stride ld in memory) is staged in LDS in dense rows of 128 bytes, the 16-byte chunk
+// index of row r XORed with chunk_swz(r).  It is read in two ways, both without bank conflicts:
+//   rows_operand: lane l takes 8 consecutive values of row base + l % 32 (sixteen rows at one chunk: sixteen 16-byte slots)
+//   ld_transposed: for the 32x32x8 MFMA, lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] through ds_read_b64_tr_b16 (the
+//     four rows one read touches lie in four different 64-byte windows)
+// Every operand of the attention kernels comes from there: fetched from global memory between the dependent products of a tile, as
+// they were, each costs the latency of the L2 or beyond (S = 128, 384 heads: forward 12.4 us, backward 37.6 us).
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-constexpr int SLD = AD + 32;
+__device__ __forceinline__ int chunk_swz(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
 // Rows from `kept` on are zeros: what lies behind a sequence's rows may be anything.
 template <int THREADS, int ROWS>
 __device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ src, int64_t ld, int kept, bf16_t* __restrict__ S) {
@@ -318,27 +321,30 @@ __device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ src, int64
   for (int c0 = 0; c0 < ROWS * 8; c0 += THREADS) {
     const int c = c0 + threadIdx.x, row = c >> 3, ec = c & 7;
     if (ROWS * 8 % THREADS == 0 || c < ROWS * 8)
-      *reinterpret_cast<uint4*>(S + row * SLD + ec * 8) = row < kept ? *reinterpret_cast<const uint4*>(src + (int64_t)row * ld + ec * 8) : make_uint4(0u, 0u, 0u, 0u);
+      *reinterpret_cast<uint4*>(S + row * AD + (ec ^ chunk_swz(row)) * 8) = row < kept ? *reinterpret_cast<const uint4*>(src + (int64_t)row * ld + ec * 8) : make_uint4(0u, 0u, 0u, 0u);
   }
 }
+struct RowsOperand { bf16x8 k[4]; };   // the four k-steps (of 16 features) of 32 rows
+__device__ __forceinline__ RowsOperand rows_operand(const bf16_t* __restrict__ S, int base, int lane) {
+  RowsOperand o;
+  const int row = base + (lane & 31), s = chunk_swz(row);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) o.k[ks] = *reinterpret_cast<const bf16x8*>(S + row * AD + ((2 * ks + (lane >> 5)) ^ s) * 8);
+  return o;
+}
 __device__ __forceinline__ s16x4 ld_transposed(const bf16_t* __restrict__ S, int e32, int k0, int lane) {
-  const int g = lane >> 4, j = lane & 15;
-  const bf16_t* p = S + (k0 + 4 * (g >> 1) + (j >> 2)) * SLD + e32 + 16 * (g & 1) + 4 * (j & 3);
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+  const int g = lane >> 4, j = lane & 15, row = k0 + 4 * (g >> 1) + (j >> 2), e = e32 + 16 * (g & 1) + 4 * (j & 3);
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(S + row * AD + ((e >> 3) ^ chunk_swz(row)) * 8 + (e & 7)));
 }
 
-// X^T-style product tile: acc[32 x 32] (+)= sum_e R[rbase + l%32][e] * Cc[cbase + l%32][e], both operands read
-// from global rows of 64 contiguous bf16 (row stride ld).  Result lane layout: column = cbase + l%32,
+// X^T-style product tile: acc[32 x 32] = sum_e R[row][e] * C[column][e].  Result lane layout: column = cbase + l%32,
 // rows rbase + 8(r/4) + 4(l/32) + r%4.
-__device__ __forceinline__ f32x16 rows_dot_rows(const bf16_t* __restrict__ R, const bf16_t* __restrict__ Cc, int64_t ld,
-                                                int rbase, int cbase, int lane) {
+__device__ __forceinline__ f32x16 rows_dot_rows(const RowsOperand& R, const RowsOperand& C) {
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  const bf16_t* rp = R + (int64_t)(rbase + (lane & 31)) * ld + 8 * (lane >> 5);
-  const bf16_t* cp = Cc + (int64_t)(cbase + (lane & 31)) * ld + 8 * (lane >> 5);
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_bf16x8(rp + 16 * ks), ld_bf16x8(cp + 16 * ks), acc, 0, 0, 0);
+  for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(R.k[ks], C.k[ks], acc, 0, 0, 0);
   return acc;
 }
 
@@ -361,11 +367,11 @@ __device__ __forceinline__ void zero_tail(const RowPlan& plan, int B, bf16_t* __
 // with one query column, so the softmax over keys is an in-lane reduction plus one cross-half shuffle, and the
 // probability tile is already in the B-operand layout of the 32x32x8 MFMA for O^T[e][q] = sum_key V^T[e][key] P^T[key][q].
 template <int NT>
-__device__ __forceinline__ void attn_scores(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, int64_t ld, int qt, int len, int nk,
+__device__ __forceinline__ void attn_scores(const RowsOperand& q, const bf16_t* __restrict__ Ks, int qt, int len, int nk,
                                             int lane, f32x16 (&s)[NT], float& inv, float* __restrict__ lse_row) {
 #pragma unroll
   for (int kt = 0; kt < NT; ++kt)
-    if (kt < nk) s[kt] = rows_dot_rows(K, Q, ld, 32 * kt, 32 * qt, lane);   // nk: tiles with a real key
+    if (kt < nk) s[kt] = rows_dot_rows(rows_operand(Ks, 32 * kt, lane), q);   // nk: tiles with a real key
   float mx = -3.0e38f;
 #pragma unroll
   for (int kt = 0; kt < NT; ++kt)
@@ -390,22 +396,31 @@ template <int NT, bool PADDED>   // PADDED = false: no lengths given, the compar
 __global__ __launch_bounds__(256) void k_attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
                                                   int heads, int d, const int32_t* __restrict__ lens, RowPlan plan, int B) {
   constexpr int S = 32 * NT;
-  __shared__ __attribute__((aligned(16))) bf16_t Vs[S * SLD];
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[S * AD];
+  __shared__ __attribute__((aligned(16))) bf16_t Vs[S * AD];
   const int h = blockIdx.x, b = blockIdx.y, pass = b / B, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ld = 3 * (int64_t)d;
   const SeqRows sr = seq_rows<PADDED>(lens, plan, pass, b - pass * B, B, S);
   const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
-  const bf16_t* K = Q + d;
-  const bf16_t* V = Q + 2 * d;
   const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
   if (PADDED && b == pass * B) zero_tail<256>(plan, B, out + (int64_t)pass * B * S * d + h * AD, d);
   float* lse_row = lse != nullptr ? lse + ((int64_t)b * heads + h) * S : nullptr;
-  stage_rows<256, S>(V, ld, kept, Vs);
+  // the queries of a tile are used by one wave only: from global memory, and those of a wave's first tile beside the staging
+  auto queries = [&](int qt) {
+    RowsOperand q;
+    const bf16_t* p = Q + (int64_t)(32 * qt + (lane & 31)) * ld + 8 * (lane >> 5);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) q.k[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
+    return q;
+  };
   f32x16 s[NT];
   float inv = 0.f;
   int qt = wave;
-  if (qt < nq) attn_scores<NT>(Q, K, ld, qt, len, nk, lane, s, inv, lse_row);   // overlaps the staging of V
-  __syncthreads();                                                          // reached once by every wave
+  RowsOperand q = queries(qt < nq ? qt : 0);
+  stage_rows<256, S>(Q + d, ld, kept, Ks);
+  stage_rows<256, S>(Q + 2 * d, ld, kept, Vs);
+  __syncthreads();
+  if (qt < nq) attn_scores<NT>(q, Ks, qt, len, nk, lane, s, inv, lse_row);
   while (qt < nq) {
     f32x16 o[2];
 #pragma unroll
@@ -436,50 +451,66 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const bf16_t* __restrict__ qkv
         *reinterpret_cast<uint2*>(orow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
       }
     qt += 4;
-    if (qt < nq) attn_scores<NT>(Q, K, ld, qt, len, nk, lane, s, inv, lse_row);
+    if (qt < nq) {
+      q = queries(qt);
+      attn_scores<NT>(q, Ks, qt, len, nk, lane, s, inv, lse_row);
+    }
   }
 }
 
-// Backward.  Probabilities are recomputed from q, k and the saved log-sum-exp.
-// Phase A (a wave owns 32 queries at a time): dS^T[key][q] -> dQ^T[e][q] = sum_key K^T[e][key] dS^T[key][q].
-// Phase B (a wave owns 32 keys at a time):    P[q][key], dS[q][key] -> dV^T[e][key] = sum_q dO^T[e][q] P[q][key],
-//                                                                      dK^T[e][key] = sum_q Q^T[e][q] dS[q][key].
+// Backward.  Probabilities are recomputed from q, k and the saved log-sum-exp; a wave owns 32 queries or keys at a time.
+//   dQ: dS^T[key][q] -> dQ^T[e][q] = sum_key K^T[e][key] dS^T[key][q]
+//   dK: dS[q][key]   -> dK^T[e][key] = sum_q Q^T[e][q] dS[q][key]
+//   dV: P[q][key]    -> dV^T[e][key] = sum_q dO^T[e][q] P[q][key]
 // dS = P (dP - D) / 8 with D[q] = sum_e dO[q][e] O[q][e].
-// The two phases only read what is staged and are independent: waves 0-3 run phase A while waves 4-7 run phase B, each
-// over the tiles w, w + 4, ... of its phase.
+// Each of the three is a workgroup of its own (blockIdx.z): it stages the two matrices it walks over, and its waves hold the
+// rows of their own tile and 32 accumulators.  The scores are formed three times instead of twice, but three to four
+// workgroups share a CU where one of the three together, with 64 KB and 167 registers, had it alone: 384 heads of 128
+// positions were one and a half rounds of 16 us.
+template <int NT> struct AttnBwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES, PER_SIMD = NT < 8 ? 3 : 4; };
 template <int NT, bool PADDED>
-__global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
-                                                  const bf16_t* __restrict__ dout, const float* __restrict__ lse,
-                                                  bf16_t* __restrict__ dqkv, int heads, int d, const int32_t* __restrict__ lens,
-                                                  RowPlan plan, int B) {
-  constexpr int S = 32 * NT, TILE_UNROLL = NT <= 4 ? NT : 1;
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[S * SLD];
-  __shared__ __attribute__((aligned(16))) bf16_t Qs[S * SLD];
-  __shared__ __attribute__((aligned(16))) bf16_t dOs[S * SLD];
+__global__ __launch_bounds__(AttnBwd<NT>::THREADS, AttnBwd<NT>::PER_SIMD) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
+                                                                      const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                                      bf16_t* __restrict__ dqkv, int heads, int d, const int32_t* __restrict__ lens,
+                                                                      RowPlan plan, int B) {
+  constexpr int S = 32 * NT, WAVES = AttnBwd<NT>::WAVES, THREADS = AttnBwd<NT>::THREADS;
+  enum { DK = 0, DQ = 1, DV = 2 };
+  __shared__ __attribute__((aligned(16))) bf16_t s_r[S * AD];   // dQ: K, dK and dV: Q
+  __shared__ __attribute__((aligned(16))) bf16_t s_t[S * AD];   // dQ: V, dK and dV: dO
   __shared__ float s_D[S], s_lse[S];
-  const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) & 3;
-  const bool phase_a = threadIdx.x < 256;
+  const int h = blockIdx.x, b = blockIdx.y, part = blockIdx.z, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ld = 3 * (int64_t)d;
   const SeqRows sr = seq_rows<PADDED>(lens, plan, 0, b, B, S);
   const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
   const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
-  const bf16_t* K = Q + d;
-  const bf16_t* V = Q + 2 * d;
   const bf16_t* O = out + (int64_t)sr.row0 * d + h * AD;
   const bf16_t* dO = dout + (int64_t)sr.row0 * d + h * AD;
-  if (PADDED && b == 0)
-    for (int k = 0; k < 3; ++k) zero_tail<512>(plan, B, dqkv + k * d + h * AD, ld);
-  stage_rows<512, S>(K, ld, kept, Ks);
-  stage_rows<512, S>(Q, ld, kept, Qs);
-  stage_rows<512, S>(dO, d, kept, dOs);
-  if (phase_a) {
-    // two threads per query; 2 S and 256 are multiples of the wave size, so a wave is in or out of a trip as a whole
-    for (int t = threadIdx.x; t < 2 * S; t += 256) {
-      const int q = t >> 1, half = t & 1;
-      float acc = 0.f;
+  const int to = part == DQ ? 0 : (part == DK ? d : 2 * d);      // where the result goes among the columns of dqkv
+  if (PADDED && b == 0) zero_tail<THREADS>(plan, B, dqkv + to + h * AD, ld);
+  // rows 32 tile + lane % 32 of a matrix, as rows_operand() would give them
+  auto own_rows = [&](const bf16_t* X, int64_t stride, int tile) {
+    RowsOperand o;
+    const bf16_t* p = X + (int64_t)(32 * tile + (lane & 31)) * stride + 8 * (lane >> 5);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) o.k[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
+    return o;
+  };
+  if (part == DQ) {
+    stage_rows<THREADS, S>(Q + d, ld, kept, s_r);
+    stage_rows<THREADS, S>(Q + 2 * d, ld, kept, s_t);
+  } else {
+    stage_rows<THREADS, S>(Q, ld, kept, s_r);
+    stage_rows<THREADS, S>(dO, d, kept, s_t);
+  }
+  // two threads per query; 2 S is a multiple of the number of threads
+  for (int t = threadIdx.x; t < 2 * S; t += THREADS) {
+    const int q = t >> 1, half = t & 1;
+    const bool there = !PADDED || q < kept;
+    float acc = 0.f;
+    if (part != DV) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if (PADDED && q >= kept) break;
+        if (!there) break;
         const uint4 o4 = *reinterpret_cast<const uint4*>(O + (int64_t)q * d + half * 32 + 8 * i);
         const uint4 d4 = *reinterpret_cast<const uint4*>(dO + (int64_t)q * d + half * 32 + 8 * i);
         const uint32_t ow[4] = {o4.x, o4.y, o4.z, o4.w}, dw[4] = {d4.x, d4.y, d4.z, d4.w};
@@ -488,118 +519,84 @@ __global__ __launch_bounds__(512) void k_attn_bwd(const bf16_t* __restrict__ qkv
           acc = fmaf(bf16_to_f32((bf16_t)(ow[e >> 1] >> ((e & 1) * 16))), bf16_to_f32((bf16_t)(dw[e >> 1] >> ((e & 1) * 16))), acc);
       }
       acc += __shfl_xor(acc, 1, 64);
-      if (half == 0) { s_D[q] = acc; s_lse[q] = (!PADDED || q < kept) ? lse[((int64_t)b * heads + h) * S + q] : 0.f; }
     }
+    if (half == 0) { s_D[q] = acc; s_lse[q] = there ? lse[((int64_t)b * heads + h) * S + q] : 0.f; }
   }
   __syncthreads();
 
-  // ---- phase A: dQ
-  if (phase_a) {
-    for (int qt = wave; qt < nq; qt += 4) {
-      const int q = 32 * qt + (lane & 31);
-      const float lq = s_lse[q], Dq = s_D[q];
-      f32x16 dq[2];
+  for (int own = wave; own < nq; own += WAVES) {                   // tile of queries (dQ) or keys
+    f32x16 g[2];
 #pragma unroll
-      for (int et = 0; et < 2; ++et)
+    for (int et = 0; et < 2; ++et)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) dq[et][r] = 0.f;
-#pragma unroll TILE_UNROLL   // the long sequences keep one tile's operands in flight: unrolled they spill
-      for (int kt = 0; kt < NT; ++kt) {
-        if (kt >= nk) break;
-        f32x16 st = rows_dot_rows(K, Q, ld, 32 * kt, 32 * qt, lane);     // S^T[key][q]
-        const bf16_t* vp = V + (int64_t)(32 * kt + (lane & 31)) * ld + 8 * (lane >> 5);
-        const bf16_t* dop = dO + (int64_t)(32 * qt + (lane & 31)) * d + 8 * (lane >> 5);
-        f32x16 dp;
+      for (int r = 0; r < 16; ++r) g[et][r] = 0.f;
+    const int col = 32 * own + (lane & 31);                        // this lane's query or key
+    // g^T[e][own] += sum over the 32 rows of `tile` of T^T[e][row] w[row][own]
+    auto accumulate = [&](const bf16_t* T, int tile, const f32x16& w) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) dp[r] = 0.f;
+      for (int c = 0; c < 4; ++c) {
+        const s16x4 wb = pack4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_bf16x8(vp + 16 * ks), ld_bf16x8(dop + 16 * ks), dp, 0, 0, 0);
+        for (int et = 0; et < 2; ++et)
+          g[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(T, 32 * et, 32 * tile + 8 * c, lane), wb, g[et], 0, 0, 0);
+      }
+    };
+    if (part == DQ) {
+      const float lq = s_lse[col], Dq = s_D[col];
+      const RowsOperand qop = own_rows(Q, ld, own), dop = own_rows(dO, d, own);
+#pragma unroll 1
+      for (int kt = 0; kt < nk; ++kt) {
+        f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * kt, lane), qop);          // S^T[key][q]
+        const f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * kt, lane), dop);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = 32 * kt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           st[r] = key < len ? __expf(st[r] * 0.125f - lq) * (dp[r] - Dq) * 0.125f : 0.f;   // dS^T; a padded key has P = 0
         }
+        accumulate(s_r, kt, st);
+      }
+    } else if (own < nk) {                                         // otherwise keys without weight
+      const bool real_key = col < len;
+      const RowsOperand kop = own_rows(Q + d, ld, own);
+      if (part == DK) {
+        const RowsOperand vop = own_rows(Q + 2 * d, ld, own);
+#pragma unroll 1
+        for (int qt = 0; qt < nq; ++qt) {
+          f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);        // S[q][key]
+          const f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * qt, lane), vop);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const s16x4 dsb = pack4(st[4 * c], st[4 * c + 1], st[4 * c + 2], st[4 * c + 3]);
-#pragma unroll
-          for (int et = 0; et < 2; ++et) {
-            const s16x4 ka = ld_transposed(Ks, 32 * et, 32 * kt + 8 * c, lane);
-            dq[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ka, dsb, dq[et], 0, 0, 0);
+          for (int r = 0; r < 16; ++r) {
+            const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            const bool on = real_key && (!PADDED || q < kept);
+            const float p = on ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
+            st[r] = on ? p * (dp[r] - s_D[q]) * 0.125f : 0.f;
           }
+          accumulate(s_r, qt, st);
+        }
+      } else {
+#pragma unroll 1
+        for (int qt = 0; qt < nq; ++qt) {
+          f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            st[r] = (real_key && (!PADDED || q < kept)) ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
+          }
+          accumulate(s_t, qt, st);
         }
       }
-      bf16_t* dqrow = dqkv + ((int64_t)sr.row0 + q) * ld + h * AD;
-#pragma unroll
-      for (int et = 0; et < 2; ++et)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (PADDED && q >= kept) break;
-          uint2 pk;
-          pk.x = pack_bf16x2(dq[et][4 * c], dq[et][4 * c + 1]);
-          pk.y = pack_bf16x2(dq[et][4 * c + 2], dq[et][4 * c + 3]);
-          *reinterpret_cast<uint2*>(dqrow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
-        }
     }
-  }
-
-  // ---- phase B: dK, dV
-  if (!phase_a) {
-    for (int kt = wave; kt < nq; kt += 4) {
-      const bool real_key = (32 * kt + (lane & 31)) < len;              // this lane's key
-      f32x16 dk[2], dv[2];
+    if (PADDED && col >= kept) continue;
+    bf16_t* row = dqkv + ((int64_t)sr.row0 + col) * ld + to + h * AD;
 #pragma unroll
-      for (int et = 0; et < 2; ++et)
+    for (int et = 0; et < 2; ++et)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { dk[et][r] = 0.f; dv[et][r] = 0.f; }
-#pragma unroll TILE_UNROLL
-      for (int qt = 0; qt < NT; ++qt) {
-        if (qt >= nq || kt >= nk) break;                                // no such queries, or keys without weight
-        f32x16 st = rows_dot_rows(Q, K, ld, 32 * qt, 32 * kt, lane);     // S[q][key]
-        const bf16_t* dop = dO + (int64_t)(32 * qt + (lane & 31)) * d + 8 * (lane >> 5);
-        const bf16_t* vp = V + (int64_t)(32 * kt + (lane & 31)) * ld + 8 * (lane >> 5);
-        f32x16 dp;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dp[r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_bf16x8(dop + 16 * ks), ld_bf16x8(vp + 16 * ks), dp, 0, 0, 0);
-        f32x16 ds;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          const bool on = real_key && (!PADDED || q < kept);
-          const float p = on ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
-          st[r] = p;
-          ds[r] = on ? p * (dp[r] - s_D[q]) * 0.125f : 0.f;
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const s16x4 pb = pack4(st[4 * c], st[4 * c + 1], st[4 * c + 2], st[4 * c + 3]);
-          const s16x4 dsb = pack4(ds[4 * c], ds[4 * c + 1], ds[4 * c + 2], ds[4 * c + 3]);
-#pragma unroll
-          for (int et = 0; et < 2; ++et) {
-            dv[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(dOs, 32 * et, 32 * qt + 8 * c, lane), pb, dv[et], 0, 0, 0);
-            dk[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(Qs, 32 * et, 32 * qt + 8 * c, lane), dsb, dk[et], 0, 0, 0);
-          }
-        }
+      for (int c = 0; c < 4; ++c) {
+        uint2 pk;
+        pk.x = pack_bf16x2(g[et][4 * c], g[et][4 * c + 1]);
+        pk.y = pack_bf16x2(g[et][4 * c + 2], g[et][4 * c + 3]);
+        *reinterpret_cast<uint2*>(row + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
       }
-      bf16_t* krow = dqkv + ((int64_t)sr.row0 + 32 * kt + (lane & 31)) * ld + d + h * AD;
-      const bool there = !PADDED || 32 * kt + (lane & 31) < kept;
-      bf16_t* vrow = krow + d;
-#pragma unroll
-      for (int et = 0; et < 2; ++et)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (!there) break;
-          uint2 pk;
-          pk.x = pack_bf16x2(dk[et][4 * c], dk[et][4 * c + 1]);
-          pk.y = pack_bf16x2(dk[et][4 * c + 2], dk[et][4 * c + 3]);
-          *reinterpret_cast<uint2*>(krow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
-          pk.x = pack_bf16x2(dv[et][4 * c], dv[et][4 * c + 1]);
-          pk.y = pack_bf16x2(dv[et][4 * c + 2], dv[et][4 * c + 3]);
-          *reinterpret_cast<uint2*>(vrow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
-        }
-    }
   }
 }
 
@@ -793,19 +790,19 @@ void launch_attention_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* out, float*
 void launch_attention_bwd(hipStream_t st, const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, const float* lse,
                           bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, const RowPlan& plan) {
   ProfScope ps(st, F_ATTN_BWD, 10.0 * B * heads * (double)S * S * 64.0);
-  const dim3 grid(heads, B);
+  const dim3 grid(heads, B, 3);
   switch (S) {
     case 64:
-      if (lens) launch_kernel(ps, k_attn_bwd<2, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_bwd<2, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      if (lens) launch_kernel(ps, k_attn_bwd<2, true>, grid, AttnBwd<2>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_bwd<2, false>, grid, AttnBwd<2>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
       break;
     case 128:
-      if (lens) launch_kernel(ps, k_attn_bwd<4, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_bwd<4, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      if (lens) launch_kernel(ps, k_attn_bwd<4, true>, grid, AttnBwd<4>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_bwd<4, false>, grid, AttnBwd<4>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
       break;
     case 256:
-      if (lens) launch_kernel(ps, k_attn_bwd<8, true>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_bwd<8, false>, grid, 512, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      if (lens) launch_kernel(ps, k_attn_bwd<8, true>, grid, AttnBwd<8>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_bwd<8, false>, grid, AttnBwd<8>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
       break;
     default: break;
   }
