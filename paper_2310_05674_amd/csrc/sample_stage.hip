@@ -103,7 +103,7 @@ __device__ void head_dots(const HeadView& h, int pass, int i_begin, int n_own, i
   if (wave < n_own) {
     for (int c0 = 0; c0 < C; c0 += CU) {
       float acc[SU][CU] = {};
-#pragma unroll 4
+#pragma unroll 8
       for (int k = lane; k < h.k; k += 64) {
         float w[CU], xk[SU];
 #pragma unroll
