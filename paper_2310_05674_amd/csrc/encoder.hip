@@ -260,8 +260,7 @@ class EncoderModel : public Model {
     const RowPlan rp = b.seq_len != nullptr ? plan_ : RowPlan{};   // of the kept forward pass
     float* dx = dX_[0];
     float* dx_next = dX_[1];
-    launch_fill_f32(st, dx, 0.f, (int64_t)(sel.n > 0 ? sel.n : M) * d_);
-    launch_head_bwd(st, res_[0], sel.n > 0 ? SELECT_SEQ_ROWS : S_, sel.n > 0 ? nullptr : rp.start, d_, B, C_, w.theta, wc_, bc_, dlogits, grad, dx);
+    launch_head_bwd(st, res_[0], sel.n > 0 ? SELECT_SEQ_ROWS : S_, sel.n > 0 ? nullptr : rp.start, d_, B, C_, w.theta, wc_, bc_, dlogits, grad, dx, sel.n > 0 ? sel.n : M);
     if (mb) mlm_backward(st, w, *mb, coef_pos, grad, dx);
     else if (has_mlm()) {   // a loss without masked-token terms leaves the head's gradient at zero
       launch_fill_f32(st, grad + wm_, 0.f, (int64_t)V_ * d_);

@@ -336,9 +336,9 @@ void launch_select_rows(hipStream_t, const RowSelect&, int nw, int pass_rows, in
                         float* x32_out);
 // The adjoint for a selection by sequence: each of the M token rows = its compact row, or zero
 void launch_spread_rows(hipStream_t, const RowSelect&, const RowPlan&, int M, int d, const bf16_t* a16, const float* x32, bf16_t* a16_out, float* x32_out);
-// dWc, dbc into grad; dx[r][:] = dlogits[b] . Wc written into the zero-filled dx, with r = b S, or start[b] when start is given
+// dWc, dbc into grad; dx[r][:] = dlogits[b] . Wc for r = b S, or r = start[b] when start is given, zeros in the others of its `rows`
 void launch_head_bwd(hipStream_t, const float* x, int S, const int32_t* start, int d, int B, int C, const float* theta, int64_t wc_off,
-                     int64_t bc_off, const float* dlogits, float* grad, float* dx);
+                     int64_t bc_off, const float* dlogits, float* grad, float* dx, int rows);
 // embedding gradients from demb [B*S x d]: pos_emb rows summed over the batch; tok_emb rows summed over the
 // occurrences of each id in ascending position order (the tok_emb part of grad must be zero on entry)
 // (ids outside [0, V) are clamped into it, here and in the forward pass)
