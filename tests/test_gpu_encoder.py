@@ -670,3 +670,52 @@ def test_wide_encoder(d, heads, ffn):
     assert e["glam_p"] < GBAR and e["glam_m"] < GBAR and e["eps"] < EBAR
     assert e["h"] < hbar
     gpu.close()
+
+
+@pytest.mark.parametrize("d,B,lens,repeat", [
+    (192, 1, [1], False), (192, 1, [16], False), (192, 2, [17, 128], False), (192, 5, [1, 15, 16, 113, 128], True),
+    (192, 5, [1, 1, 1, 1, 1], True), (320, 9, None, True), (320, 6, None, False)])
+def test_padded_rows_and_embedding_gradients_at_their_edges(d, B, lens, repeat):
+    """Base step against the oracle where the packing of padded rows can go wrong (lengths beside the 16-row groups, one token in
+    all) and where the embedding gradients can (one token id at every position, 1152 rows of one sum; batches that are no multiple
+    of the four sequences whose rows fill a tile of the last layer)."""
+    S = 128
+    wl = make_workload(3, n_train=4 * B, n_meta=4, dims=(2, d, d // 64, 320, S, 600, 3), batch=B, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    (x, y), _ = _batches(wl, 0)
+    if repeat:
+        x = np.full_like(x, 7)
+    xo = x if lens is None else with_lengths(x, np.array(lens, dtype=np.int32))
+    push_state(orc, gpu)
+    lo = orc.base_step(xo, y)
+    gpu.base_step(dev_batch(gpu, x, y, lens=None if lens is None else np.array(lens, dtype=np.int32)))
+    g = pull(gpu, "G")
+    print(f"d={d} B={B} lens={lens}: rel-L2 g {rel_l2(g, orc.g):.3e}")
+    assert rel_l2(g, orc.g) < KTOL
+    for name in ("tok_emb", "pos_emb", "Wc", "bc"):
+        off, shape = orc.model.slices[name]
+        sl = slice(off, off + int(np.prod(shape)))
+        assert rel_l2(g[sl], orc.g[sl]) < TOL, name
+    assert abs(float(pull(gpu, "SCALARS")[2]) - lo) < 2e-2 * abs(lo)
+    gpu.close()
+
+
+@pytest.mark.parametrize("d,ffn,S,B,padded", [
+    (128, 256, 64, 1, False), (192, 448, 64, 2, True), (192, 448, 128, 1, False), (320, 1088, 128, 1, True), (192, 384, 128, 8, False),
+    (192, 448, 128, 9, True)])
+def test_eval_of_few_rows(d, ffn, S, B, padded):
+    """sama_eval where its products have at most 128 rows (one text, two short ones, the last layer's rows of eight) and just
+    beyond, against the oracle: contractions that do not divide among the waves of a workgroup, widths beside its columns."""
+    import torch
+    wl = make_workload(3, n_train=4 * B, n_meta=4, dims=(2, d, d // 64, ffn, S, 600, 3), batch=B, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.05), init_lambda(wl), base_lr=1e-3)
+    (x, y), _ = _batches(wl, 0)
+    push_state(orc, gpu)
+    orc.t = 1
+    lens = np.minimum(S, 1 + 37 * np.arange(1, B + 1)).astype(np.int32)
+    out = [torch.zeros(s, device=gpu.dev) for s in ((B, 3), (B,), (B,))]
+    gpu.eval(dev_batch(gpu, x, y, lens=lens if padded else None), *out)
+    for name, got, want in zip(("logits", "losses", "weights"), out, orc.evaluate(with_lengths(x, lens) if padded else x, y)):
+        print(f"{name} {rel_l2(got.cpu().numpy(), want):.2e}")
+        assert rel_l2(got.cpu().numpy(), want) < KTOL
+    gpu.close()
