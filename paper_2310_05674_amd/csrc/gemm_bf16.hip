@@ -498,23 +498,24 @@ typedef Tile<64, 64, 64, 2, 2, 4, true, 2> D6;
 typedef Tile<64, 64, 64, 2, 2, 3, true, 2> D7;       // two workgroups per CU
 typedef Tile<64, 32, 64, 2, 1, 4, true, 1> D8;       // two workgroups per CU
 
-// What a launch costs with a tile, in us: launch + per round (epilogue + 64-deep slabs x time of a slab).  A round is up to
-// `per_cu` tiles on each of the 256 CUs; a slab takes `few` with a handful of tiles on the chip, `one` with one on every CU
-// and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.  The numbers
-// are least-squares fits over 924 problems (widths 192 to 1024, FFN 2 to 4 times that, 64 to 8192 rows; NT, NN, pairs of NT,
-// and a layer's four TN problems in a launch), weights cold.  Picking by them takes 2.4% (hi + lo) and 1.6% (single-term)
-// longer in total than the fastest tile of each problem.
-struct TileCost { int id, bm, bn, per_cu; double launch, few, one, two, all, epilogue; };
+// What a launch costs with a tile, in us, beyond what it costs with any: per round, epilogue + 64-deep slabs x time of a slab.
+// A round is up to `per_cu` tiles on each of the 256 CUs; a slab takes `few` with a handful of tiles on the chip, `one` with one
+// on every CU and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.
+// The numbers are robust least-squares fits of the logarithms over 2561 timed problems (widths 192 to 2048, FFN 2 and 4 times that,
+// 64 to 8192 rows: NT, NN, pairs of NT, a layer's four TN problems in a launch; the vocabulary head's products over 8192 to
+// 50304 tokens; weights cold): profiles/gemm_tile_costs.md.  Picking by them takes 0.6% (hi + lo) and 0.7% (single-term) longer
+// in total than the fastest tile of each problem, the same on problems left out of the fit; the head's products 1.5 to 3%.
+struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; };
 constexpr TileCost SINGLE[] = {
-    {1, 256, 256, 1, 5.86, 1.357, 1.841, 0, 0, 3.21}, {2, 256, 192, 1, 7.02, 1.127, 1.366, 0, 0, 2.00},
-    {3, 256, 128, 1, 0.22, 0.672, 0.926, 0, 0, 7.37}, {4, 128, 128, 1, 0.32, 0.456, 0.556, 0, 0, 5.32},
-    {5, 128, 64, 1, 3.20, 0.338, 0.396, 0, 0, 2.37},  {6, 64, 64, 2, 4.56, 0.204, 0.279, 0.396, 0.475, 1.18},
-    {7, 128, 128, 2, 0.00, 0.746, 0.899, 1.033, 1.153, 4.79}};
+    {1, 256, 256, 1, 1.282, 1.816, 0, 0, 8.26}, {2, 256, 192, 1, 1.060, 1.218, 0, 0, 8.62},
+    {3, 256, 128, 1, 0.561, 0.923, 0, 0, 6.42}, {4, 128, 128, 1, 0.419, 0.620, 0, 0, 3.28},
+    {5, 128, 64, 1, 0.333, 0.416, 0, 0, 2.07},  {6, 64, 64, 2, 0.259, 0.281, 0.470, 0.486, 1.36},
+    {7, 128, 128, 2, 0.714, 0.836, 0.836, 1.184, 3.72}};
 constexpr TileCost HILO[] = {
-    {11, 256, 192, 1, 1.77, 1.374, 2.418, 0, 0, 7.85}, {12, 256, 128, 1, 0.69, 0.998, 1.646, 0, 0, 6.22},
-    {13, 128, 128, 1, 1.37, 0.567, 0.934, 0, 0, 4.05}, {14, 128, 96, 1, 1.97, 0.557, 0.775, 0, 0, 3.88},
-    {15, 128, 64, 1, 2.34, 0.325, 0.535, 0, 0, 2.59},  {16, 64, 64, 1, 3.34, 0.232, 0.349, 0, 0, 1.57},
-    {17, 64, 64, 2, 3.98, 0.248, 0.351, 0.465, 0.650, 0.99}, {18, 64, 32, 2, 4.06, 0.180, 0.278, 0.308, 0.450, 1.00}};
+    {11, 256, 192, 1, 1.425, 2.186, 0, 0, 12.13}, {12, 256, 128, 1, 1.072, 1.533, 0, 0, 7.70},
+    {13, 128, 128, 1, 0.679, 0.933, 0, 0, 4.45},  {14, 128, 96, 1, 0.669, 0.783, 0, 0, 4.50},
+    {15, 128, 64, 1, 0.482, 0.605, 0, 0, 2.45},   {16, 64, 64, 1, 0.433, 0.433, 0, 0, 1.67},
+    {17, 64, 64, 2, 0.442, 0.470, 0.722, 0.722, 1.61}, {18, 64, 32, 2, 0.321, 0.340, 0.528, 0.528, 1.43}};
 
 int g_force_shape = 0, g_group = 8;
 
@@ -534,7 +535,7 @@ int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count) {
     }
     slabs /= (double)tiles;
     const int64_t cap = 256 * c.per_cu, rest = tiles % cap;
-    double cost = c.launch + (double)(tiles / cap) * (slabs * (c.per_cu > 1 ? c.all : c.one) + c.epilogue);
+    double cost = (double)(tiles / cap) * (slabs * (c.per_cu > 1 ? c.all : c.one) + c.epilogue);
     if (rest > 0) {
       const double slab = rest <= 256 ? c.few + (c.one - c.few) * (double)rest / 256.0 : c.two + (c.all - c.two) * (double)(rest - 256) / (double)(cap - 256);
       cost += slabs * slab + c.epilogue;
