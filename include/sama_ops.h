@@ -76,9 +76,9 @@ sama_status sama_op_nudge(float* theta, const float* vdir, const float* eps_ptr,
 
 /* Diagnostic switches, process-wide, for tests and profiling.  They take effect from the next launch and are not
  * thread-safe.
- *  - sama_dev_gemm_shape(id): every bf16 GEMM launch uses block tile `id`: 1..7 are the single-term tiles (a hi+lo
+ *  - sama_dev_gemm_shape(id): every bf16 GEMM launch uses block tile `id`: 1..8 are the single-term tiles (a hi+lo
  *    problem then runs as one contraction over the concatenated operands, which rounds differently from the hi+lo
- *    tiles), 11..18 the hi+lo tiles (single-term problems ignore them); 0 = the heuristic (default).  Within a class
+ *    tiles), 11..19 the hi+lo tiles (single-term problems ignore them); 0 = the heuristic (default).  Within a class
  *    every tile gives the same bits.
  *  - sama_dev_side_stream(0): the encoder's backward passes keep every launch on the context's stream instead of
  *    running weight gradients and optimizer slices on the library's second stream (a per-kernel profile wants one

@@ -76,9 +76,8 @@ class EncoderModel : public Model {
 
   // One linear layer of `nw` stacked passes (pass k owns rows [k M, (k + 1) M) of every activation): the same
   // epilogue `e` (its pointers are those of pass 0) for each pass, with that pass's weights.
-  // `few`: a pass over FEW_ROWS rows at most that nothing is compared with bit by bit (a single forward-only pass).
   void fwd_linear(hipStream_t st, const PassWeights* w, int nw, const bf16_t* A, int K, int64_t woff, int N, int64_t boff, int M,
-                  const GemmBf16Args& e, const int32_t* rows = nullptr, bool few = false) const {
+                  const GemmBf16Args& e, const int32_t* rows = nullptr) const {
     GemmBf16Args g[2];
     for (int k = 0; k < nw; ++k) {
       g[k] = e;
@@ -93,8 +92,7 @@ class EncoderModel : public Model {
       if (e.C16) g[k].C16 = e.C16 + ro;
       if (e.C16_pre) g[k].C16_pre = e.C16_pre + ro;
     }
-    if (few && K >= 2 * N) launch_gemm_few_rows(st, g[0]);   // a long sum for few outputs: its tiles would be one walk over K
-    else launch_gemm_bf16_batch(st, g, nw);
+    launch_gemm_bf16_batch(st, g, nw);
   }
 
   // What follows the last attention is row by row, and of its result only position 0 of each sequence (the classifier) or
@@ -121,7 +119,6 @@ class EncoderModel : public Model {
     const int B = b.n, M = B * S_;
     const RowSelect sel = select(b, keep, mb);
     const RowPlan rp = b.seq_len != nullptr ? plan_ : RowPlan{};   // a padded batch: only the rows that matter
-    const bool few = !keep && nw == 1 && M <= FEW_ROWS;
     if (b.seq_len != nullptr) launch_row_plan(st, (const int32_t*)b.x, b.seq_len, B, S_, mb ? masked(b, *mb) : RowSelect{}, rp);
     ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};   // flips behind the first pass's rows
     LnFwdArgs e{};
@@ -136,7 +133,7 @@ class EncoderModel : public Model {
       const LayerOff& o = off_[l];
       GemmBf16Args g{};
       g.C16 = qkv_[s];
-      fwd_linear(st, w, nw, xin, d_, o.Wqkv, 3 * d_, o.bqkv, M, g, rp.rows, few);
+      fwd_linear(st, w, nw, xin, d_, o.Wqkv, 3 * d_, o.bqkv, M, g, rp.rows);
       launch_attention_fwd(st, qkv_[s], ao_[s], keep ? lse_[s] : nullptr, nw, B, S_, heads_, d_, b.seq_len, rp);
       const bool last = l == L_ - 1 && sel.n > 0;
       const int rows = last ? sel.n : M;            // of one pass, from here on
@@ -147,17 +144,17 @@ class EncoderModel : public Model {
       }
       g = GemmBf16Args{};
       g.res32 = last ? res_sel_ : res_[0]; g.C32 = pre1_[s];          // the residual stream stays fp32
-      fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g, in_use, few);
+      fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g, in_use);
       LnFwdArgs n1{};
       n1.x = pre1_[s]; n1.pv = pv; n1.g_off = o.ln1g; n1.b_off = o.ln1b; n1.y = x1_[s]; n1.y32 = res_[1];
       n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
       launch_ln_fwd(st, n1);
       g = GemmBf16Args{};
       g.act = GEMM_ACT_GELU_FWD; g.C16_pre = keep ? fpre_[s] : nullptr; g.C16 = fact_[s];   // only a backward pass reads the pre-activation
-      fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g, in_use, few);
+      fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g, in_use);
       g = GemmBf16Args{};
       g.res32 = res_[1]; g.C32 = pre2_[s];
-      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g, in_use, few);
+      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g, in_use);
       LnFwdArgs n2{};
       n2.x = pre2_[s]; n2.pv = pv; n2.g_off = o.ln2g; n2.b_off = o.ln2b; n2.y = xout; n2.y32 = res_[0];
       n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = nw * rows; n2.d = d_; n2.pass_rows = rows; n2.rows = in_use;

@@ -113,6 +113,17 @@ __device__ __forceinline__ int fetch_lane_offset(int lane, int ks_or_tile) {
   }
 }
 
+// Waits until all but the `younger` (at most W) last slabs of NL loads each of this wave have landed.
+template <int NL, int W>
+__device__ __forceinline__ void wait_loads(int younger) {
+  if constexpr (W == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    if (younger >= W) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL * W) : "memory");
+    else wait_loads<NL, W - 1>(younger);
+  }
+}
+
 struct GemmBatch {
   GemmBf16Args p[GEMM_MAX_BATCH];
   int first_tile[GEMM_MAX_BATCH + 1];   // tile ids [first_tile[k], first_tile[k + 1]) belong to problem k
@@ -270,16 +281,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   // make slab `sl` visible: a loading wave's own loads landed, then everyone's; afterwards the stage of slab sl - 1 is free
   auto arrive = [&](int sl) {
     const int younger = iters - 1 - sl;
-    if (!loader) {
-    } else if (younger >= NSTAGE - 2) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(T::NL * (NSTAGE - 2)) : "memory");
-    } else if (NSTAGE >= 4 && younger == NSTAGE - 3) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(T::NL * (NSTAGE >= 4 ? NSTAGE - 3 : 0)) : "memory");
-    } else if (NSTAGE >= 5 && younger == NSTAGE - 4) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(T::NL * (NSTAGE >= 5 ? NSTAGE - 4 : 0)) : "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
+    if (loader) wait_loads<T::NL, NSTAGE - 2>(younger);
     __builtin_amdgcn_s_barrier();
     issue(sl + NSTAGE - 1);
   };
@@ -482,6 +484,10 @@ void launch_tile(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count
 }
 
 // Tiles <BM, BN, BK, multiplying waves in M, in N, stages, hi + lo, loading waves, operands fetched one step at a time>
+// The 32 x 32 ones are for products of few rows (scoring one text), which a larger tile leaves to a few dozen workgroups that walk
+// the contraction slab by slab: with twice as many and five slabs in flight, 128 rows of 768 x 3072 take 14.1 us hi + lo
+// (64 x 32: 17.9) and 10.7 single-term (64 x 64: 17.2).  Splitting the contraction over the waves of a workgroup was
+// 0.8 us faster, but sums in another order, so that a text scored alone came out otherwise than in a batch.
 typedef Tile<256, 256, 64, 2, 4, 2, false> S1;
 typedef Tile<256, 192, 64, 4, 2, 2, false, 4, true> S2;
 typedef Tile<256, 128, 64, 4, 2, 3, false, 4, true> S3;
@@ -489,6 +495,7 @@ typedef Tile<128, 128, 64, 4, 2, 4, false, 4> S4;
 typedef Tile<128, 64, 64, 4, 2, 4, false, 4> S5;
 typedef Tile<64, 64, 64, 2, 2, 4, false> S6;         // two workgroups per CU
 typedef Tile<128, 128, 64, 4, 2, 2, false> S7;       // two workgroups per CU
+typedef Tile<32, 32, 64, 1, 1, 6, false, 2> S8;      // three workgroups per CU
 typedef Tile<256, 192, 64, 4, 2, 2, true, 4, true> D1;
 typedef Tile<256, 128, 64, 4, 2, 2, true, 4> D2;
 typedef Tile<128, 128, 64, 4, 2, 3, true, 4> D3;
@@ -497,25 +504,27 @@ typedef Tile<128, 64, 64, 4, 2, 4, true, 4> D5;
 typedef Tile<64, 64, 64, 2, 2, 4, true, 2> D6;
 typedef Tile<64, 64, 64, 2, 2, 3, true, 2> D7;       // two workgroups per CU
 typedef Tile<64, 32, 64, 2, 1, 4, true, 1> D8;       // two workgroups per CU
+typedef Tile<32, 32, 64, 1, 1, 6, true, 2> D9;       // two workgroups per CU
 
 // What a launch costs with a tile, in us, beyond what it costs with any: per round, epilogue + 64-deep slabs x time of a slab.
 // A round is up to `per_cu` tiles on each of the 256 CUs; a slab takes `few` with a handful of tiles on the chip, `one` with one
 // on every CU and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.
 // The numbers are robust least-squares fits of the logarithms over 2561 timed problems (widths 192 to 2048, FFN 2 and 4 times that,
 // 64 to 8192 rows: NT, NN, pairs of NT, a layer's four TN problems in a launch; the vocabulary head's products over 8192 to
-// 50304 tokens; weights cold): profiles/gemm_tile_costs.md.  Picking by them takes 0.6% (hi + lo) and 0.7% (single-term) longer
+// 50304 tokens; weights cold): profiles/gemm_tile_costs.md.  Picking by them takes 0.6% (hi + lo) and 1.0% (single-term) longer
 // in total than the fastest tile of each problem, the same on problems left out of the fit; the head's products 1.5 to 3%.
 struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; };
 constexpr TileCost SINGLE[] = {
     {1, 256, 256, 1, 1.282, 1.816, 0, 0, 8.26}, {2, 256, 192, 1, 1.060, 1.218, 0, 0, 8.62},
-    {3, 256, 128, 1, 0.561, 0.923, 0, 0, 6.42}, {4, 128, 128, 1, 0.419, 0.620, 0, 0, 3.28},
-    {5, 128, 64, 1, 0.333, 0.416, 0, 0, 2.07},  {6, 64, 64, 2, 0.259, 0.281, 0.470, 0.486, 1.36},
-    {7, 128, 128, 2, 0.714, 0.836, 0.836, 1.184, 3.72}};
+    {3, 256, 128, 1, 0.561, 0.923, 0, 0, 6.42}, {4, 128, 128, 1, 0.427, 0.600, 0, 0, 3.55},
+    {5, 128, 64, 1, 0.322, 0.419, 0, 0, 2.08},  {6, 64, 64, 2, 0.257, 0.282, 0.470, 0.486, 1.36},
+    {7, 128, 128, 2, 0.714, 0.828, 0.828, 1.167, 3.94}, {8, 32, 32, 3, 0.160, 0.202, 0.282, 0.381, 1.03}};
 constexpr TileCost HILO[] = {
     {11, 256, 192, 1, 1.425, 2.186, 0, 0, 12.13}, {12, 256, 128, 1, 1.072, 1.533, 0, 0, 7.70},
-    {13, 128, 128, 1, 0.679, 0.933, 0, 0, 4.45},  {14, 128, 96, 1, 0.669, 0.783, 0, 0, 4.50},
-    {15, 128, 64, 1, 0.482, 0.605, 0, 0, 2.45},   {16, 64, 64, 1, 0.433, 0.433, 0, 0, 1.67},
-    {17, 64, 64, 2, 0.442, 0.470, 0.722, 0.722, 1.61}, {18, 64, 32, 2, 0.321, 0.340, 0.528, 0.528, 1.43}};
+    {13, 128, 128, 1, 0.672, 0.928, 0, 0, 4.58},  {14, 128, 96, 1, 0.671, 0.782, 0, 0, 4.52},
+    {15, 128, 64, 1, 0.491, 0.603, 0, 0, 2.46},   {16, 64, 64, 1, 0.435, 0.435, 0, 0, 1.66},
+    {17, 64, 64, 2, 0.449, 0.469, 0.723, 0.723, 1.59}, {18, 64, 32, 2, 0.320, 0.341, 0.528, 0.528, 1.42},
+    {19, 32, 32, 2, 0.236, 0.255, 0.381, 0.381, 1.28}};
 
 int g_force_shape = 0, g_group = 8;
 
@@ -558,6 +567,7 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
     case 4: launch_tile<S4, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 5: launch_tile<S5, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 6: launch_tile<S6, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 8: launch_tile<S8, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 11: launch_tile<D1, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 12: launch_tile<D2, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 13: launch_tile<D3, A_KC, B_KC>(ps, st, p, count, g_group); break;
@@ -566,6 +576,7 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
     case 16: launch_tile<D6, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 17: launch_tile<D7, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 18: launch_tile<D8, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 19: launch_tile<D9, A_KC, B_KC>(ps, st, p, count, g_group); break;
     default: launch_tile<S7, A_KC, B_KC>(ps, st, p, count, g_group); break;
   }
 }

@@ -232,10 +232,6 @@ void launch_gemm_bf16(hipStream_t, const GemmBf16Args&);
 constexpr int GEMM_MAX_BATCH = 4;
 const char* check_gemm_bf16_batch(const GemmBf16Args* p, int count);
 void launch_gemm_bf16_batch(hipStream_t, const GemmBf16Args* p, int count);
-// A forward product (a_trans = 0, b_trans = 1, no perturbed bias, nothing kept for a backward pass) of few rows
-// (gemm_few_rows.hip).  Its sums over K are in another order than launch_gemm_bf16's.
-constexpr int FEW_ROWS = 128;
-void launch_gemm_few_rows(hipStream_t, const GemmBf16Args&);
 void encoder_side_sink(bool on);         // tuning hook: per-layer gradient consumers on that stream (default on)
 void encoder_side_stream(bool on);      // tuning hook: weight-gradient launches on a second stream (default on)
 void gemm_bf16_force_shape(int shape);  // tuning hook: 0 = heuristic, else 100 * tile-order group + tile configuration id

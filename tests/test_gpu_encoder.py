@@ -704,8 +704,8 @@ def test_padded_rows_and_embedding_gradients_at_their_edges(d, B, lens, repeat):
     (128, 256, 64, 1, False), (192, 448, 64, 2, True), (192, 448, 128, 1, False), (320, 1088, 128, 1, True), (192, 384, 128, 8, False),
     (192, 448, 128, 9, True)])
 def test_eval_of_few_rows(d, ffn, S, B, padded):
-    """sama_eval where its products have at most 128 rows (one text, two short ones, the last layer's rows of eight) and just
-    beyond, against the oracle: contractions that do not divide among the waves of a workgroup, widths beside its columns."""
+    """sama_eval of one text, of two short ones, and of a few (whose last layer keeps 128 or 192 rows), against the oracle: the
+    smallest tiles, contractions of fewer and of more slabs than those have in flight."""
     import torch
     wl = make_workload(3, n_train=4 * B, n_meta=4, dims=(2, d, d // 64, ffn, S, 600, 3), batch=B, meta_batch=2)
     orc, gpu = make_pair(wl, init_theta(wl, 0.05), init_lambda(wl), base_lr=1e-3)
@@ -718,4 +718,28 @@ def test_eval_of_few_rows(d, ffn, S, B, padded):
     for name, got, want in zip(("logits", "losses", "weights"), out, orc.evaluate(with_lengths(x, lens) if padded else x, y)):
         print(f"{name} {rel_l2(got.cpu().numpy(), want):.2e}")
         assert rel_l2(got.cpu().numpy(), want) < KTOL
+    gpu.close()
+
+
+@pytest.mark.parametrize("S,fast,padded", [(128, 0, False), (128, 0, True), (128, 1, False), (64, 0, True)])
+def test_eval_of_a_text_does_not_depend_on_what_is_scored_beside_it(S, fast, padded):
+    """sama_eval of each text alone, of the whole batch, and the base step's own losses on that batch: the same bits.  One text
+    has few rows and takes other tiles than the batch does; every sum keeps its order."""
+    import torch
+    B = 5
+    wl = make_workload(3, n_train=4 * B, n_meta=4, dims=(3, 192, 3, 448, S, 600, 3), batch=B, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.05), init_lambda(wl), base_lr=1e-3, fast_base_pass=fast)
+    (x, y), _ = _batches(wl, 0)
+    lens = np.minimum(S, 1 + 29 * np.arange(1, B + 1)).astype(np.int32) if padded else None
+
+    def score(sel):
+        out = [torch.zeros(s, device=gpu.dev) for s in ((len(sel), 3), (len(sel),), (len(sel),))]
+        gpu.eval(dev_batch(gpu, x[sel], y[sel], lens=None if lens is None else lens[sel]), *out)
+        return [o.cpu().numpy() for o in out]
+    every = score(np.arange(B))
+    for i in range(B):
+        for name, one, all_ in zip(("logits", "losses", "weights"), score(np.array([i])), every):
+            assert np.array_equal(one[0], all_[i]), (name, i)
+    gpu.base_step(dev_batch(gpu, x, y, lens=lens))
+    assert np.array_equal(pull(gpu, "LOSSES")[:B], every[1])
     gpu.close()

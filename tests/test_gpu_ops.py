@@ -184,7 +184,7 @@ def test_gemm_bf16_tile_edges(M, N, K, a_trans, b_trans, split):
     tB2 = _dev(B2, torch.bfloat16) if split else None
     L = B.load_library()
     first = None
-    for shape in (0,) + (tuple(range(11, 19)) if split else tuple(range(1, 8))):
+    for shape in (0,) + (tuple(range(11, 20)) if split else tuple(range(1, 9))):
         L.sama_dev_gemm_shape(ctypes.c_int32(shape))
         o32 = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
         B.op_gemm_bf16(tA, tB, a_trans=a_trans, b_trans=b_trans, B2=tB2, out32=o32)
