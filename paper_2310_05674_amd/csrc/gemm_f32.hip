@@ -158,10 +158,14 @@ void launch_gemm_f32_batch(hipStream_t st, const GemmF32Args* a, int count) {
     flops += 2.0 * a[k].M * a[k].N * a[k].K;
   }
   ProfScope ps(st, F_GEMM_F32, flops);
-  // The smallest tile gives the shortest chain and the most workgroups; it reads every operand row once per 16 columns, so
-  // once there are more small tiles than the chip holds at a time the larger one takes over.
-  if (tiles(a, count, 16, 16) <= 512) launch_tile_f32<1, 1, 8>(ps, st, a, count);
-  else if (tiles(a, count, 32, 32) <= 512) launch_tile_f32<2, 2, 4>(ps, st, a, count);
+  // The smallest tile gives the shortest chain and the most workgroups; it reads every operand row once per 16 columns, and as
+  // soon as some CU has two of its workgroups to run the next larger tile is the faster one.  us, 16 x 16 / 32 x 32: 256 tiles
+  // (512 x 128 x 784) 5.8 / 9.3, 384 (512 x 192 x 784) 9.7 / 9.4, 384 (512 x 192 x 256) 6.7 / 5.5; 32 x 32 / 64 x 32: 256 tiles
+  // (1024 x 256 x 784) 9.6 / 15.3, 320 (1024 x 320 x 784) 16.8 / 15.3.  Over 408 products and pairs (32 to 2048 rows, widths to
+  // 320, K to 1024) these lines take 1.2% longer than the fastest tile of each, lines at 512 3.6% (geometric means).
+  constexpr int CUS = 256;
+  if (tiles(a, count, 16, 16) <= CUS) launch_tile_f32<1, 1, 8>(ps, st, a, count);
+  else if (tiles(a, count, 32, 32) <= CUS) launch_tile_f32<2, 2, 4>(ps, st, a, count);
   else launch_tile_f32<4, 2, 2>(ps, st, a, count);
 }
 

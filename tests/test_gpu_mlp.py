@@ -274,6 +274,30 @@ def test_ragged_shapes():
     gpu.close()
 
 
+@pytest.mark.parametrize("B", [37, 203, 700, 2003])
+def test_every_fp32_tile(B):
+    """A base step at batches whose products take each of the three output tiles, none of which divides the widths or the batch;
+    and the first 37 samples scored alone: every tile sums in the same order, so they keep their bits."""
+    import torch
+    from datagen.workloads import Workload
+    dims = (301, 173, 10)
+    r = CounterRNG(77)
+    wl = Workload(cfg=0, kind="mlp", dims=dims, bf16=False, H=9, batch=B, meta_batch=B, base_lr=1e-2, meta_lr=1e-3, alpha=0.5,
+                  noise=0.0, n_train=B, n_meta=B, steps=1)
+    x = r.normal(1, B * 301).reshape(B, 301).astype(np.float32); y = r.integers(2, B, 10).astype(np.int32)
+    th0 = (0.06 * r.normal(5, 301 * 173 + 173 * 10 + 173 + 10)).astype(np.float32).astype(np.float64)
+    lam0 = r.normal(6, 28).astype(np.float32).astype(np.float64)
+    orc, gpu = make_pair(wl, th0, lam0)
+    out = [[torch.zeros(n, 10, device=gpu.dev), torch.zeros(n, device=gpu.dev), torch.zeros(n, device=gpu.dev)] for n in (B, 37)]
+    gpu.eval(dev_batch(gpu, x, y), *out[0])
+    gpu.eval(dev_batch(gpu, x[:37], y[:37]), *out[1])
+    for all_, few in zip(*out):
+        assert torch.equal(all_[:37], few)
+    orc.base_step(x, y); gpu.base_step(dev_batch(gpu, x, y))
+    assert rel_l2(pull(gpu, "G"), orc.g) < TOL and rel_l2(pull(gpu, "THETA"), orc.theta) < TOL
+    gpu.close()
+
+
 def test_batch_size_limits():
     """One sample, the largest batch the library takes (2048), and the sizes it must refuse."""
     import torch
