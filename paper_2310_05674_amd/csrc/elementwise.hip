@@ -453,8 +453,10 @@ int launch_adapt_slice(hipStream_t st, const float* g, const float* m, const flo
   if (n <= 0) return 0;
   int grid = ew_grid(n);
   if (grid > max_blocks) grid = max_blocks;
-  // every block takes a ticket: worth a launch saved while there are few of them
-  const bool here = fin.ticket != nullptr && grid <= 512;
+  // Every block takes a ticket, one after the other; the second step in a launch of its own costs as much as a hundred of them.
+  // us, one launch / two: 64 blocks 5.9 / 6.3, 104 blocks 6.25 / 6.30, 112 blocks 6.38 / 6.32, 256 blocks 8.4 / 6.8, 512 blocks 12 / 9.6.
+  constexpr int FINISH_BLOCKS = 104;
+  const bool here = fin.ticket != nullptr && grid <= FINISH_BLOCKS;
   if (finished != nullptr) *finished = here;
   ProfScope ps(st, F_ADAPT_NORM, (a.mode == 0 ? 20.0 : 8.0) * n);
   launch_kernel(ps, k_adapt_norm, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a, here ? fin : EpsFinish{});
