@@ -65,8 +65,8 @@ def main():
                     help="auxiliary-task reweighting (Sec. 4.3) instead of the headline workload: the 12-layer encoder with a "
                          "50304-token masked-token head, 16 finetuning + 16 auxiliary sequences per base step")
     ap.add_argument("--length-mix", action="store_true",
-                    help="encoder workloads: padded batches with a seeded length mix (key-padding mask); padded tokens are "
-                         "still computed, so the rate is that of full sequences")
+                    help="encoder workloads: padded batches with a seeded length mix (key-padding mask); of each sequence "
+                         "only its real tokens, rounded up to 16, are computed")
     ap.add_argument("--graph", action="store_true",
                     help="capture each iteration (unroll base steps + meta step) into a HIP graph once per synthetic batch and time "
                          "replays instead of eager calls")

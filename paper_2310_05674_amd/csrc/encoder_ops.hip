@@ -310,8 +310,10 @@ __device__ __forceinline__ s16x4 pack4(float a, float b, float c, float d) {
 //   rows_operand: lane l takes 8 consecutive values of row base + l % 32 (sixteen rows at one chunk: sixteen 16-byte slots)
 //   ld_transposed: for the 32x32x8 MFMA, lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] through ds_read_b64_tr_b16 (the
 //     four rows one read touches lie in four different 64-byte windows)
-// Every operand of the attention kernels comes from there: fetched from global memory between the dependent products of a tile, as
-// they were, each costs the latency of the L2 or beyond (S = 128, 384 heads: forward 12.4 us, backward 37.6 us).
+// The matrices that a tile's products walk over come from there: fetched from global memory between those dependent products,
+// each operand costs the latency of the L2 or beyond (S = 128, 384 heads: backward 37.6 us that way, 23.6 from LDS).  What a wave
+// holds for a whole tile -- the queries of the forward pass, the own rows of the backward pass -- is read by one wave only, once
+// a tile, and comes from global memory.
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 __device__ __forceinline__ int chunk_swz(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
 // Rows from `kept` on are zeros: what lies behind a sequence's rows may be anything.
@@ -464,9 +466,10 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const bf16_t* __restrict__ qkv
 //   dV: P[q][key]    -> dV^T[e][key] = sum_q dO^T[e][q] P[q][key]
 // dS = P (dP - D) / 8 with D[q] = sum_e dO[q][e] O[q][e].
 // Each of the three is a workgroup of its own (blockIdx.z): it stages the two matrices it walks over, and its waves hold the
-// rows of their own tile and 32 accumulators.  The scores are formed three times instead of twice, but three to four
-// workgroups share a CU where one of the three together, with 64 KB and 167 registers, had it alone: 384 heads of 128
-// positions were one and a half rounds of 16 us.
+// rows of their own tile and 32 accumulators.  The scores are formed three times instead of twice, but three workgroups share a CU
+// (S = 64 and 128, by their 137 to 146 registers; two of eight waves at S = 256, by 67.6 KB of LDS) where one that formed all three,
+// with 64 KB and 167 registers, had it alone: 384 heads of 128 positions were one and a half rounds of 16 us.  At S = 256 the 128
+// registers of eight waves to a workgroup leave 8 or 9 values in scratch; 384 heads 96 -> 59 us all the same.
 template <int NT> struct AttnBwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES, PER_SIMD = NT < 8 ? 3 : 4; };
 template <int NT, bool PADDED>
 __global__ __launch_bounds__(AttnBwd<NT>::THREADS, AttnBwd<NT>::PER_SIMD) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
