@@ -270,6 +270,9 @@ def main():
                                  "unit": "TFLOP/s", "peak": PEAK_BF16_TFLOPS if wl.bf16 else PEAK_FP32_MATRIX_TFLOPS},
             "kernels": kernels,
         }
+        if args.length_mix:
+            out["roofline"]["padding"] = ("work is counted over all positions of the padded batches, of which only the real ones are computed: the "
+                                          "rates of the GEMM, attention and row-wise families are above what the kernels reach")
     if unroll10 is not None:
         out["unroll10"] = unroll10
 
