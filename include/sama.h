@@ -221,7 +221,9 @@ sama_status sama_aux_meta_step(sama_ctx* ctx, const sama_aux_batch* pt, const sa
  * weights_out [n] = w(l_i; lambda) -- the per-sample importance the meta learner has learned (what the reweighting and
  * pruning applications of Sec. 4 read off it).  DEVICE pointers, each may be NULL.  n up to max(max_batch,
  * max_meta_batch); sample_mask is ignored, seq_len honoured.  bf16 models evaluate with the weights the base
- * step's forward uses (fast_base_pass).  Changes no state (LOSSES and SCALARS keep what the last step left). */
+ * step's forward uses (fast_base_pass).  What a sample gets does not depend, to the bit, on the others of its batch, and its
+ * loss is the one a base step at the same theta and lambda leaves in LOSSES.  Changes no state (LOSSES and SCALARS
+ * keep what the last step left). */
 sama_status sama_eval(sama_ctx* ctx, const sama_batch* batch, float* logits_out /*DEVICE*/, float* losses_out /*DEVICE*/,
                       float* weights_out /*DEVICE*/);
 

@@ -82,9 +82,9 @@ sama_status sama_op_nudge(float* theta, const float* vdir, const float* eps_ptr,
  *    every tile gives the same bits.
  *  - sama_dev_side_stream(0): the encoder's backward passes keep every launch on the context's stream instead of
  *    running weight gradients and optimizer slices on the library's second stream (a per-kernel profile wants one
- *    stream); 1 = default.  Changes no result bit.
+ *    stream); 1 = default.  A base step keeps its bits; a meta step adds the partial sums of ||v||^2 in another order.
  *  - sama_dev_side_sink(0): the optimizer and adaptation slices wait for the end of the backward pass instead of
- *    following each layer's gradients; 1 = default.  Changes no result bit. */
+ *    following each layer's gradients; 1 = default.  The same holds for its bits. */
 void sama_dev_gemm_shape(int32_t id);
 void sama_dev_side_stream(int32_t on);
 void sama_dev_side_sink(int32_t on);
