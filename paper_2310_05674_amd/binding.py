@@ -104,6 +104,8 @@ def load_library():
     L.sama_op_gemm_bf16.argtypes = [vp, i64, i32, vp, vp, i64, i32, i32, i32, i32, vp, vp, vp, i64, vp]
     L.sama_op_gemm_bf16_batch.restype = C.c_int
     L.sama_op_gemm_bf16_batch.argtypes = [i32, vp, vp, vp, vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32), i32, i32, vp]
+    L.sama_op_gelu_table_bytes.restype = C.c_size_t; L.sama_op_gelu_table_bytes.argtypes = []
+    L.sama_op_gemm_bf16_gelu.restype = C.c_int; L.sama_op_gemm_bf16_gelu.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp]
     L.sama_set_lr.restype = C.c_int; L.sama_set_lr.argtypes = [vp, f32, f32]
     L.sama_eval.restype = C.c_int; L.sama_eval.argtypes = [vp, vp, vp, vp, vp]
     L.sama_aux_eval.restype = C.c_int; L.sama_aux_eval.argtypes = [vp, vp, vp, vp]
@@ -331,6 +333,18 @@ def op_gemm_bf16_batch(As, Bs, outs, *, a_trans=False, b_trans=True, B2s=None):
                                    vp(*[o.data_ptr() for o in outs]), ia(*Ms), ia(*Ns), ia(*Ks), int(a_trans), int(b_trans), _stream())
     if rc != 0:
         raise SamaError(rc, "sama_op_gemm_bf16_batch rejected the arguments")
+
+
+def op_gemm_bf16_gelu(A, B, B2, out32, *, b_trans=True, aux16=None, pre16=None):
+    """The encoder's GELU epilogues through sama_op_gemm_bf16_gelu: forward without aux16, backward with it (dense 2-D bf16
+    operands, fp32 output)."""
+    import torch
+    L = load_library()
+    M, K = A.shape
+    table = torch.empty(L.sama_op_gelu_table_bytes(), dtype=torch.uint8, device=A.device)
+    rc = L.sama_op_gemm_bf16_gelu(_p(A), _p(B), _p(B2), int(b_trans), M, out32.shape[1], K, _p(aux16), _p(pre16), _p(out32), _p(table), _stream())
+    if rc != 0:
+        raise SamaError(rc, "sama_op_gemm_bf16_gelu rejected the arguments")
 
 
 def op_adam(g, m, v, theta, theta16, n16, t, lr, beta1, beta2, eps, wd=0.0):

@@ -47,6 +47,7 @@ class EncoderModel : public Model {
       x1_[l] = ws.take<bf16_t>(R * d_); fpre_[l] = ws.take<bf16_t>(R * ffn_); fact_[l] = ws.take<bf16_t>(R * ffn_);
       pre2_[l] = ws.take<float>(R * d_); mean2_[l] = ws.take<float>(M); rstd2_[l] = ws.take<float>(M);
     }
+    gelu_tab_ = (float*)ws.take<char>(gelu_table_bytes());
     plan_.start = ws.take<int32_t>(MAX_SEQ + 1); plan_.rows = ws.take<int32_t>(1); plan_.ids = ws.take<int32_t>(M); plan_.src = ws.take<int32_t>(M);
     plan_.group = ws.take<int32_t>(M / ROW_GROUP);
     pre0_ = ws.take<float>(M * d_); mean0_ = ws.take<float>(M); rstd0_ = ws.take<float>(M);
@@ -73,6 +74,8 @@ class EncoderModel : public Model {
       cs_mlm_ = ws.take<float>((P + COLSUM_ROWS - 1) / COLSUM_ROWS * V_);
     }
   }
+
+  void prepare(hipStream_t st) override { launch_gelu_tables(st, gelu_tab_); }
 
   // One linear layer of `nw` stacked passes (pass k owns rows [k M, (k + 1) M) of every activation): the same
   // epilogue `e` (its pointers are those of pass 0) for each pass, with that pass's weights.
@@ -150,7 +153,7 @@ class EncoderModel : public Model {
       n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
       launch_ln_fwd(st, n1);
       g = GemmBf16Args{};
-      g.act = GEMM_ACT_GELU_FWD; g.C16_pre = keep ? fpre_[s] : nullptr; g.C16 = fact_[s];   // only a backward pass reads the pre-activation
+      g.act = GEMM_ACT_GELU_FWD; g.gelu_tab = gelu_tab_; g.C16_pre = keep ? fpre_[s] : nullptr; g.C16 = fact_[s];   // only a backward pass reads the pre-activation
       fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g, in_use);
       g = GemmBf16Args{};
       g.res32 = res_[1]; g.C32 = pre2_[s];
@@ -286,7 +289,7 @@ class EncoderModel : public Model {
       // FFN
       wg[0] = wgrad(ds2, d_, fact_[l], ffn_, rows, grad + o.W2, in_use);
       GemmBf16Args g = dgrad(w, ds2, d_, o.W2, ffn_, rows, in_use);
-      g.act = GEMM_ACT_GELU_BWD; g.aux16 = fpre_[l]; g.C16 = dpre;
+      g.act = GEMM_ACT_GELU_BWD; g.gelu_tab = gelu_tab_; g.aux16 = fpre_[l]; g.C16 = dpre;
       launch_gemm_bf16(st, g);
       wg[1] = wgrad(dpre, ffn_, x1_[l], d_, rows, grad + o.W1, in_use);
       g = dgrad(w, dpre, ffn_, o.W1, d_, rows, in_use);
@@ -381,6 +384,7 @@ class EncoderModel : public Model {
   float* cs_mlm_ = nullptr;
   std::vector<bf16_t*> X_, qkv_, ao_, x1_, fpre_, fact_;
   std::vector<float*> lse_, pre1_, mean1_, rstd1_, pre2_, mean2_, rstd2_;
+  float* gelu_tab_ = nullptr;
   RowPlan plan_{};            // of the last padded batch
   RowSelect mask_sel_{};      // masked positions of the last batch with any
   float *pre0_ = nullptr, *mean0_ = nullptr, *rstd0_ = nullptr;

@@ -26,7 +26,8 @@
 // gradients of a layer): more tiles per launch for the small per-layer shapes.
 //
 // Fused epilogues: + bias (fp32, optionally perturbed), + residual (fp32), GELU forward (writes both the
-// pre-activation and the activation), GELU backward (multiplies by gelu'(pre)), fp32 and/or bf16 stores.
+// pre-activation and the activation), GELU backward (multiplies by gelu'(pre)), fp32 and/or bf16 stores.  The large hi + lo
+// tiles look the GELU factors up in a table that their loading waves bring into LDS during the last slab.
 #include <type_traits>
 #include "common.h"
 #include "gelu.h"
@@ -60,6 +61,14 @@ struct Tile {
   static constexpr int EPI_LD = WN + 8;   // 4 rows apart = 32 banks apart: the two lane halves of a staging write do not collide
   static constexpr int LDS_EPI = WAVES * 32 * EPI_LD * 4;
   static constexpr int LDS_BYTES = LDS_MAIN > LDS_EPI ? LDS_MAIN : LDS_EPI;
+  // Whether the GELU epilogues look their values up (gelu.h).  The table comes into a stage that the last slab does not use, while
+  // that slab is multiplied, and stays clear of the epilogue's staging.  Computed, a value is 26 quarter-rate vector instructions,
+  // 6 us of the epilogue of 256 tiles of 256 x 128 in which the matrix cores stand still; looked up it is seven and an LDS read.
+  // us computed / looked up, forward: 2048 x 4096 x 1024 (256 x 128 tiles) 39.9 / 35.9, 4096 x 3072 x 768 (256 x 192) 48.2 / 42.3;
+  // backward 41.1 / 38.7, 51.6 / 47.0; with 128 x 128 tiles, 1024 x 3072 x 768, 19.8 / 18.5.  Smaller tiles compute: the table
+  // would be more to load than a slab of them.
+  static constexpr bool TAB = DUAL && PW > 0 && BM * BN >= 128 * 128;
+  static_assert(!TAB || (NSTAGE >= 2 && STAGE_BYTES >= GELU_TAB_BYTES && LDS_MAIN - GELU_TAB_BYTES >= LDS_EPI), "room for the table");
   static_assert(A_BYTES % (1024 * LW) == 0 && B_BYTES % (1024 * LW) == 0, "slab must split into whole wave loads");
   static_assert(NL * (NSTAGE - 2) <= 63, "vmcnt range");
 };
@@ -196,6 +205,10 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   const char* const pB2 = reinterpret_cast<const char*>(a.B2);
   const int iters = (!DUAL && pB2 != nullptr) ? 2 * nk : nk;   // non-DUAL tiles contract with hi, then with lo
 
+  // the GELU table's place: at the top, or at the bottom (and the staging of the epilogue above it) if the last slab is at the top
+  const bool look_up = T::TAB && a.act != GEMM_ACT_NONE;
+  const bool tab_low = (iters - 1) % NSTAGE == NSTAGE - 1;
+  const int tab_at = tab_low ? 0 : T::LDS_MAIN - GELU_TAB_BYTES;
   const int lw = T::PW > 0 ? wave - WAVES : wave;            // number among the loading waves
   const bool loader = T::PW == 0 || wave >= WAVES;
   // per-lane global offsets of this wave's loads
@@ -299,6 +312,18 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   };
   if (T::PW > 0 && loader) {   // the barriers of the others, and the loads
     for (int i = 0; i < iters; ++i) arrive(i);
+    if constexpr (T::TAB) {
+      if (look_up) {   // all slabs but the last have been read
+        const char* const tab = reinterpret_cast<const char*>(a.gelu_tab) + (a.act == GEMM_ACT_GELU_BWD ? GELU_TAB_BYTES : 0);
+#pragma unroll
+        for (int q = 0; q < (GELU_TAB_BYTES / 1024 + T::LW - 1) / T::LW; ++q) {
+          const int piece = q * T::LW + lw;
+          if (piece < GELU_TAB_BYTES / 1024)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + tab_at + piece * 1024), "v"(lane * 16), "s"(tab + piece * 1024) : "memory", "m0");
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+    }
     __syncthreads();
     return;
   }
@@ -352,7 +377,8 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
 
   // ---- epilogue: accumulators -> LDS (per wave, 32 x WN fp32 at a time) -> row-contiguous global accesses
   constexpr int EPI_LD = T::EPI_LD, LPR = T::WN / 4, RPP = 64 / LPR;   // lanes per row, rows per pass
-  float* epi = reinterpret_cast<float*>(smem_raw) + wave * 32 * EPI_LD;
+  float* epi = reinterpret_cast<float*>(smem_raw + (look_up && tab_low ? GELU_TAB_BYTES : 0)) + wave * 32 * EPI_LD;
+  const unsigned char* const tab = smem_raw + tab_at;
   const int cg = lane % LPR, rq = lane / LPR;
   const int gj = j0 + wc + 4 * cg;
   const bool col_ok = gj < a.N && (LPR * RPP == 64 || lane < LPR * RPP);   // 96-wide wave tiles: 24 lanes a row, two rows
@@ -377,6 +403,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   constexpr int CH = 4, PER = NIT / CH, NCH = XT * PER;
   static_assert(NIT % CH == 0, "steps of a slice");
   const bool side = res32 != nullptr || act == GEMM_ACT_GELU_BWD;
+  auto entry = [&](uint32_t offset) { return *reinterpret_cast<const float*>(tab + offset); };   // of the GELU table
   auto epilogue = [&](auto all_rows) {   // all_rows: every row of the tile exists
     auto exists = [&](int row) { return decltype(all_rows)::value || i0 + wr + row < Mrows; };   // row: within the wave's tile
     auto step = [&](int q, int u) { return base + (int64_t)((q / PER) * 32 + RPP * ((q % PER) * CH + u)) * ldc; };
@@ -433,17 +460,30 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
           if (C16_pre != nullptr && exists(x * 32 + row_of(q, u))) *reinterpret_cast<uint2*>(C16_pre + step(q, u) + lane_off) = pk;   // forward-only passes do not keep it
           c[u][0] = bf16_to_f32((bf16_t)pk.x); c[u][1] = bf16_to_f32((bf16_t)(pk.x >> 16));
           c[u][2] = bf16_to_f32((bf16_t)pk.y); c[u][3] = bf16_to_f32((bf16_t)(pk.y >> 16));
+          if constexpr (T::TAB) {
+            const uint32_t o0 = gelu_tab_offsets(pk.x), o1 = gelu_tab_offsets(pk.y);
+            c[u][0] *= entry(o0 & 0xffffu); c[u][1] *= entry(o0 >> 16); c[u][2] *= entry(o1 & 0xffffu); c[u][3] *= entry(o1 >> 16);
+          }
         }
+        if constexpr (!T::TAB) {
 #pragma unroll
-        for (int u = 0; u < CH; ++u)
+          for (int u = 0; u < CH; ++u)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) c[u][e] = gelu_f(c[u][e]);
+            for (int e = 0; e < 4; ++e) c[u][e] = gelu_f(c[u][e]);
+        }
       } else if (act == GEMM_ACT_GELU_BWD) {
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
           const uint4 r = sv[AHEAD ? q & 1 : 0][u];
-          c[u][0] *= dgelu_f(bf16_to_f32((bf16_t)r.x)); c[u][1] *= dgelu_f(bf16_to_f32((bf16_t)(r.x >> 16)));
-          c[u][2] *= dgelu_f(bf16_to_f32((bf16_t)r.y)); c[u][3] *= dgelu_f(bf16_to_f32((bf16_t)(r.y >> 16)));
+          const float x[4] = {bf16_to_f32((bf16_t)r.x), bf16_to_f32((bf16_t)(r.x >> 16)), bf16_to_f32((bf16_t)r.y), bf16_to_f32((bf16_t)(r.y >> 16))};
+          if constexpr (T::TAB) {   // + 0 x: of an infinity or a NaN the derivative is NaN
+            const uint32_t o0 = gelu_tab_offsets(r.x), o1 = gelu_tab_offsets(r.y);
+            c[u][0] *= fmaf(x[0], 0.f, entry(o0 & 0xffffu)); c[u][1] *= fmaf(x[1], 0.f, entry(o0 >> 16));
+            c[u][2] *= fmaf(x[2], 0.f, entry(o1 & 0xffffu)); c[u][3] *= fmaf(x[3], 0.f, entry(o1 >> 16));
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c[u][e] *= dgelu_f(x[e]);
+          }
         }
       }
       if (C32 != nullptr) {
@@ -594,6 +634,19 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
 }
 }  // namespace
 
+__global__ __launch_bounds__(256) void k_gelu_tables(float* __restrict__ tab) {
+  const int i = blockIdx.x * 256 + threadIdx.x, sign = blockIdx.y;
+  if (i >= GELU_TAB_ENTRIES) return;
+  const float x = bf16_to_f32((bf16_t)((GELU_TAB_FIRST + i) | sign << 15));
+  tab[(sign << 12) + i] = gelu_cdf_f(x);
+  tab[GELU_TAB_BYTES / 4 + (sign << 12) + i] = dgelu_f(x);
+}
+size_t gelu_table_bytes() { return 2 * GELU_TAB_BYTES; }
+void launch_gelu_tables(hipStream_t st, float* tab) {
+  ProfScope ps(st, F_OTHER, 0.0);
+  launch_kernel(ps, k_gelu_tables, dim3((GELU_TAB_ENTRIES + 255) / 256, 2), 256, 0, st, tab);
+}
+
 const char* check_gemm_bf16(const GemmBf16Args& a) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return "empty GEMM";
   if (a.K % 64 != 0) return "K must be a multiple of 64";
@@ -602,6 +655,7 @@ const char* check_gemm_bf16(const GemmBf16Args& a) {
   if (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.B2 | (uintptr_t)a.bias | (uintptr_t)a.bias_v | (uintptr_t)a.C32 |
        (uintptr_t)a.res32) & 15) return "operands, bias, fp32 residual and fp32 output must be 16-byte aligned";
   if (((uintptr_t)a.C16 | (uintptr_t)a.C16_pre | (uintptr_t)a.aux16) & 7) return "bf16 epilogue tensors must be 8-byte aligned";
+  if (a.act != GEMM_ACT_NONE && (a.gelu_tab == nullptr || ((uintptr_t)a.gelu_tab & 15) != 0)) return "the GELU epilogues need their 16-byte aligned table";
   if (a.res32 != nullptr && a.act == GEMM_ACT_GELU_BWD) return "a residual and the GELU backward exclude each other";
   if (a.lda < (a.a_trans ? a.M : a.K) || a.ldb < (a.b_trans ? a.K : a.N) || a.ldc < a.N) return "leading dimension too small";
   const int64_t abytes = (int64_t)(a.a_trans ? a.K : a.M) * a.lda * 2, bbytes = (int64_t)(a.b_trans ? a.N : a.K) * a.ldb * 2;

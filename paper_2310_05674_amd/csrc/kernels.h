@@ -222,9 +222,13 @@ struct GemmBf16Args {
   const float* bias; const float* bias_v; const float* beps; float bsign;
   const float* res32;
   int act; const bf16_t* aux16; bf16_t* C16_pre;
+  const float* gelu_tab;   // the GELU epilogues: what launch_gelu_tables() wrote
   float* C32; bf16_t* C16;
   const int32_t* rows;   // null, or (device) the token rows in use: a multiple of 64 that replaces M (a_trans = 0) or K (a_trans = 1)
 };
+// The factors of gelu and gelu' for every bf16 value (gelu.h), gelu_table_bytes() bytes, 16-byte aligned.
+size_t gelu_table_bytes();
+void launch_gelu_tables(hipStream_t, float* tab);
 const char* check_gemm_bf16(const GemmBf16Args&);  // null if the shapes / alignments are supported
 void launch_gemm_bf16(hipStream_t, const GemmBf16Args&);
 // Up to GEMM_MAX_BATCH independent problems in one launch; they must agree in a_trans, b_trans and in whether B2 is

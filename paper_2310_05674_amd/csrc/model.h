@@ -73,6 +73,8 @@ class Model {
   void set_grad_sink(GradSink* s) { sink_ = s; }   // for the next backward() / backward_mlm(); null = none
   // carve activation buffers for batches up to max_b
   virtual void plan(BumpAlloc& ws, int max_b) = 0;
+  // fills what the workspace holds for the life of the context, once
+  virtual void prepare(hipStream_t) {}
   // everything up to the classifier for batch `b`; keep = retain what backward needs.  The result says where the features
   // are.  `mb` (models with a masked-token head): the positions that head will read after this pass; a batch without
   // labels (b.y null) is read by that head only.

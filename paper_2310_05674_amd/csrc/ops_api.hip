@@ -74,6 +74,23 @@ sama_status sama_op_gemm_bf16_batch(int32_t count, const void* const* A, const v
   return hipGetLastError() == hipSuccess ? SAMA_OK : SAMA_EHIP;
 }
 
+size_t sama_op_gelu_table_bytes(void) { return gelu_table_bytes(); }
+sama_status sama_op_gemm_bf16_gelu(const void* A, const void* B, const void* B2, int32_t b_trans, int32_t M, int32_t N, int32_t K,
+                                   const void* aux16, void* pre16, float* C32, void* table, void* hip_stream) {
+  if (!A || !B || !B2 || !C32 || !table || ((uintptr_t)table & 15) != 0) return SAMA_EINVAL;
+  GemmBf16Args g{};
+  g.A = (const bf16_t*)A; g.lda = K;
+  g.B = (const bf16_t*)B; g.B2 = (const bf16_t*)B2; g.b_trans = b_trans ? 1 : 0; g.ldb = b_trans ? K : N;
+  g.M = M; g.N = N; g.K = K; g.ldc = N; g.C32 = C32; g.gelu_tab = (const float*)table;
+  g.act = aux16 ? GEMM_ACT_GELU_BWD : GEMM_ACT_GELU_FWD;
+  g.aux16 = (const bf16_t*)aux16; g.C16_pre = aux16 ? nullptr : (bf16_t*)pre16;
+  if (check_gemm_bf16(g) != nullptr) return SAMA_EINVAL;
+  (void)hipGetLastError();
+  launch_gelu_tables((hipStream_t)hip_stream, (float*)table);
+  launch_gemm_bf16((hipStream_t)hip_stream, g);
+  return hipGetLastError() == hipSuccess ? SAMA_OK : SAMA_EHIP;
+}
+
 sama_status sama_op_adam(float* g, float* m, float* v, float* theta, void* theta16, int64_t n, int64_t n16, int64_t t,
                          float lr, float beta1, float beta2, float eps, float weight_decay, void* hip_stream) {
   if (!g || !m || !v || !theta || n < 0 || n16 < 0 || n16 > n || t < 1) return SAMA_EINVAL;

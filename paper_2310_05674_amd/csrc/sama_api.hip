@@ -325,6 +325,7 @@ sama_status sama_init(const sama_config* cfg, void* workspace, size_t workspace_
   launch_fill_f32(st, (float*)c->ticket, 0.f, 2);
   launch_fill_i64x4(st, c->counters, 0, 0, 0, 0, 15);
   if (c->bf16) { launch_to_bf16(st, c->theta16, c->theta, c->n_gemm); launch_residual_lo(st, c->theta, c->lo_0, c->n_gemm); }
+  c->model->prepare(st);
   sama_status s = check_hip(nullptr, "sama_init");
   if (s != SAMA_OK) return s;
   *out = c.release();

@@ -194,6 +194,60 @@ def test_gemm_bf16_tile_edges(M, N, K, a_trans, b_trans, split):
     L.sama_dev_gemm_shape(ctypes.c_int32(0))
 
 
+@pytest.mark.parametrize("K", [64, 128, 192])
+def test_gelu_of_every_bf16_value(K):
+    """The tiles that look the GELU factors up (11, 12, 13) against those that compute them (14, 15, 16), bit for bit, on every bf16
+    value, infinities and NaNs among them, and on ragged tiles; one to three slabs put the table at each of its places.  Bar
+    against float64: erf to 1.5e-7, times |x|, and a few fp32 roundings of the result."""
+    import ctypes
+    from scipy.special import erf
+    from paper_2310_05674_amd import binding as B
+    L = B.load_library()
+    bits = torch.arange(65536, dtype=torch.int32, device=DEV).to(torch.int16).reshape(256, 256)
+    x = bits.view(torch.bfloat16)
+    xf = x.double().cpu().numpy()
+    ok = np.isfinite(xf) & (np.abs(xf) < 1e30)
+    with np.errstate(all="ignore"):
+        cdf = 0.5 * (1 + erf(xf / np.sqrt(2)))
+        dg = cdf + xf * np.exp(-0.5 * xf * xf) / np.sqrt(2 * np.pi)
+    e0 = torch.zeros((256, K), dtype=torch.bfloat16, device=DEV); e0[:, K - 1] = 1.0
+    # row i, column j of A . B^T is the value of bits 256 i + j: a power of two times 1 or 2 with a fraction
+    i, j = torch.arange(256, device=DEV), torch.arange(256, device=DEV)
+    pa, pb = torch.zeros_like(e0), torch.zeros_like(e0)
+    pa[:, 0] = ((1 - 2 * (i >> 7)) * torch.exp2((2 * (i & 127) - 127).double())).to(torch.bfloat16)
+    pb[:, 0] = ((1 + (j & 127) / 128.0) * (1 + (j >> 7))).to(torch.bfloat16)
+    pa[3, 0], pa[5, 0] = float("nan"), float("inf")
+    zero = torch.zeros_like(e0)
+    got = {}
+    try:
+        for tile in (11, 12, 13, 14, 15, 16):
+            L.sama_dev_gemm_shape(ctypes.c_int32(tile))
+            for b_trans in (True, False):   # backward: 1 * gelu'(x)
+                o = torch.empty((256, 256), device=DEV)
+                w = e0 if b_trans else e0.t().contiguous()
+                B.op_gemm_bf16_gelu(e0, w, torch.zeros_like(w), o, b_trans=b_trans, aux16=x.contiguous())
+                got[tile, "b", b_trans] = o
+            o, pre = torch.empty((256, 256), device=DEV), torch.empty((256, 256), dtype=torch.bfloat16, device=DEV)
+            B.op_gemm_bf16_gelu(pa, pb, zero, o, pre16=pre)
+            got[tile, "f", True], got[tile, "pre", True] = o, pre.float()
+            o = torch.empty((200, 136), device=DEV)
+            B.op_gemm_bf16_gelu(pa[:200].contiguous(), pb[:136].contiguous(), zero[:136].contiguous(), o)
+            got[tile, "ragged", True] = o
+    finally:
+        L.sama_dev_gemm_shape(ctypes.c_int32(0))
+    for (tile, what, bt), o in got.items():
+        r = got[16, what, bt]
+        assert torch.equal(o.isnan(), r.isnan()) and torch.equal(o.nan_to_num(7.0), r.nan_to_num(7.0)), (tile, what, bt)
+    b = got[16, "b", True].cpu().numpy()
+    assert np.all(np.abs(b - dg)[ok] <= 1e-6) and np.all(np.isnan(b[~np.isfinite(xf)]))
+    f, pre = got[16, "f", True].double().cpu().numpy(), got[16, "pre", True].double().cpu().numpy()
+    fin = np.isfinite(pre)
+    assert fin[8:120].all() and np.array_equal(pre[8:120], xf[8:120])   # (rows 3 and 5 hold NaN and infinities, the edges overflow or are subnormal)
+    want = pre[fin] * 0.5 * (1 + erf(pre[fin] / np.sqrt(2)))
+    assert np.all(np.abs(f[fin] - want) <= 3e-7 * np.abs(pre[fin]))
+    assert torch.equal(got[16, "ragged", True].nan_to_num(7.0), got[16, "f", True][:200, :136].nan_to_num(7.0))
+
+
 def test_gemm_rejects_unsupported_shapes():
     from paper_2310_05674_amd import binding as B
     A = torch.zeros((64, 96), dtype=torch.bfloat16, device=DEV); Bm = torch.zeros((64, 96), dtype=torch.bfloat16, device=DEV)
