@@ -23,16 +23,71 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
 // round-to-nearest-even; NaN stays NaN
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return (bf16_t)pack_bf16x2(f, 0.f); }
 
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+// Butterflies over a wave, or over each group of sixteen of its lanes, without LDS: lanes 32 and 16 apart by the permlane swaps,
+// lanes of a group by rotations.  A level joins the lanes 32, 16, 8, 4, 2, 1 apart; once the lanes 8 (4, 2) apart agree, a
+// rotation by 4 (2, 1) reaches the same value as the exchange with the lane that far apart would.  A shuffle goes through the LDS
+// unit, ~60 cycles a level; these are one or two vector instructions.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+template <int N>
+__device__ __forceinline__ uint32_t rot16(uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + N, 0xf, 0xf, false); }
+template <int N>
+__device__ __forceinline__ float rot16(float x) { return __uint_as_float(rot16<N>(__float_as_uint(x))); }
+template <int N>
+__device__ __forceinline__ double rot16(double x) {
+  const u32x2 v = __builtin_bit_cast(u32x2, x);
+  return __builtin_bit_cast(double, (u32x2){rot16<N>(v[0]), rot16<N>(v[1])});
+}
+// the two halves of every pair of lanes 32 (16) apart, for both of them
+__device__ __forceinline__ void halves32(uint32_t x, uint32_t& a, uint32_t& b) { const u32x2 r = __builtin_amdgcn_permlane32_swap(x, x, false, false); a = r[0]; b = r[1]; }
+__device__ __forceinline__ void halves16(uint32_t x, uint32_t& a, uint32_t& b) { const u32x2 r = __builtin_amdgcn_permlane16_swap(x, x, false, false); a = r[0]; b = r[1]; }
+template <typename F>
+__device__ __forceinline__ float join32(float x, F op) { uint32_t a, b; halves32(__float_as_uint(x), a, b); return op(__uint_as_float(a), __uint_as_float(b)); }
+template <typename F>
+__device__ __forceinline__ float join16(float x, F op) { uint32_t a, b; halves16(__float_as_uint(x), a, b); return op(__uint_as_float(a), __uint_as_float(b)); }
+template <typename F>
+__device__ __forceinline__ double join32(double x, F op) {
+  const u32x2 v = __builtin_bit_cast(u32x2, x);
+  u32x2 a, b; uint32_t p, q;
+  halves32(v[0], p, q); a[0] = p; b[0] = q;
+  halves32(v[1], p, q); a[1] = p; b[1] = q;
+  return op(__builtin_bit_cast(double, a), __builtin_bit_cast(double, b));
+}
+template <typename F>
+__device__ __forceinline__ double join16(double x, F op) {
+  const u32x2 v = __builtin_bit_cast(u32x2, x);
+  u32x2 a, b; uint32_t p, q;
+  halves16(v[0], p, q); a[0] = p; b[0] = q;
+  halves16(v[1], p, q); a[1] = p; b[1] = q;
+  return op(__builtin_bit_cast(double, a), __builtin_bit_cast(double, b));
+}
+// over the sixteen lanes of a group; every one of them gets the result
+template <typename T, typename F>
+__device__ __forceinline__ T join_group(T x, F op) {
+  x = op(x, rot16<8>(x)); x = op(x, rot16<4>(x)); x = op(x, rot16<2>(x));
+  return op(x, rot16<1>(x));
+}
+// The same from the other end, over runs of n lanes (a power of two, the same for the wave): neighbours, pairs, then mirror images,
+// which are as good as the exchange across the run once the halves agree within themselves.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const u32x2 v = __builtin_bit_cast(u32x2, x);
+  return __builtin_bit_cast(double, (u32x2){(uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[0], CTRL, 0xf, 0xf, false), (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[1], CTRL, 0xf, 0xf, false)});
+}
+__device__ __forceinline__ double run_sum(double x, int n) {
+  const auto add = [](double a, double b) { return a + b; };
+  if (n > 1) x += dpp<0xb1>(x);     // quad_perm 1 0 3 2
+  if (n > 2) x += dpp<0x4e>(x);     // quad_perm 2 3 0 1
+  if (n > 4) x += dpp<0x141>(x);    // row_half_mirror
+  if (n > 8) x += dpp<0x140>(x);    // row_mirror
+  if (n > 16) x = join16(x, add);
+  if (n > 32) x = join32(x, add);
   return x;
 }
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
+// over the wave
+template <typename T, typename F>
+__device__ __forceinline__ T join_wave(T x, F op) { return join_group(join16(join32(x, op), op), op); }
+__device__ __forceinline__ float wave_sum(float x) { return join_wave(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ double wave_sum(double x) { return join_wave(x, [](double a, double b) { return a + b; }); }
 
 // Sum over a block of up to 1024 threads in a fixed order: wave shuffles, then the wave leaders' values
 // added serially from LDS.  Every thread gets the result.  `red` holds >= 16 floats.

@@ -21,6 +21,8 @@
 // update of lambda and the step scalars (kernel durations in a trace): label correction with 203 samples, Hc = 64, 10 classes
 // 347 -> 21 us (base step) and 2 x 347 + 9 -> 43 us (both passes and the update); scoring 2048 samples 44 + 7 -> 8.5 us;
 // reweighting with 128 samples, H = 100: 13 + 8 -> 10 us and 2 x (13 + 8) + 5 -> 15 us.
+// Sums across lanes by vector instructions instead of shuffles through LDS, and the other workgroups' partials requested at once
+// instead of one or four at a time: a logistic-regression iteration (512 samples, H = 16; three stages) 62.2 -> 55.5 us.
 #include "common.h"
 #include "kernels.h"
 #include "mfma_f32.h"
@@ -131,20 +133,11 @@ __device__ void head_dots(const HeadView& h, int pass, int i_begin, int n_own, i
 }
 
 // every lane of a group of sixteen gets the sum / maximum over the group
-__device__ __forceinline__ double sum16(double x) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-__device__ __forceinline__ double max16(double x) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) x = fmax(x, __shfl_xor(x, o, 64));
-  return x;
-}
+__device__ __forceinline__ double sum16(double x) { return join_group(x, [](double a, double b) { return a + b; }); }
+__device__ __forceinline__ double max16(double x) { return join_group(x, [](double a, double b) { return fmax(a, b); }); }
 // sum over the workgroup in a fixed order, for every thread; `red` holds ST_THREADS / 64 values
 __device__ __forceinline__ double block_sum_d(double x, double* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  x = wave_sum(x);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
@@ -157,16 +150,22 @@ __device__ __forceinline__ double block_sum_d(double x, double* red) {
 // h = -(glam+ - glam-) / (2 eps); then (optionally) Adam on lambda.  A raised status word (counters[2]) or a
 // hypergradient with a non-finite component zeroes h and skips the update; the latter raises the status word itself.
 // glam+ / glam- are the sums of the workgroups' partials in order.
+constexpr int COLLECT = 16;
 __device__ void meta_update(const MetaUpdateArgs& a, const double* part, int nblk) {
   const float eps = a.scalars[0];
   bool skip = (a.counters[2] != 0) || !(eps > 0.f);
   int bad = 0;
   for (int i = threadIdx.x; i < a.nl; i += ST_THREADS) {
     double gp = 0.0, gm = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < nblk; ++k) {
-      gp += collect(part + (int64_t)k * a.nl + i);
-      gm += collect(part + (int64_t)(nblk + k) * a.nl + i);
+    for (int k0 = 0; k0 < nblk; k0 += COLLECT) {   // a load of each takes a microsecond: COLLECT workgroups' at once
+      double p[COLLECT], m[COLLECT];
+#pragma unroll
+      for (int u = 0; u < COLLECT; ++u) {
+        p[u] = k0 + u < nblk ? collect(part + (int64_t)(k0 + u) * a.nl + i) : 0.0;
+        m[u] = k0 + u < nblk ? collect(part + (int64_t)(nblk + k0 + u) * a.nl + i) : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < COLLECT; ++u) { gp += p[u]; gm += m[u]; }
     }
     a.glam_p[i] = gp; a.glam_m[i] = gm;
     if (!skip) {
@@ -259,7 +258,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
         r = r < 0 ? 0 : (r >= B * a.S ? B * a.S - 1 : r);
         if (r / a.S == i_begin + i) { acc += (double)pos_loss[j]; n_i += 1.0; }
       }
-      for (int o = 32; o > 0; o >>= 1) { acc += __shfl_xor(acc, o, 64); n_i += __shfl_xor(n_i, o, 64); }
+      acc = wave_sum(acc); n_i = wave_sum(n_i);
       if ((tid & 63) == 0) { s_l[i] = n_i > 0.0 ? acc / n_i : 0.0; s_cnt[i] = (float)n_i; }
     }
     __syncthreads();
@@ -409,10 +408,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
     if (total > 1) {
       if (tid == 0) publish(a.part + blockIdx.x, L);
       if (!last_block(a.ticket, total, &s_last)) return;
-      if (tid == 0) {
-        L = 0.0;
-        for (int k = 0; k < nblk; ++k) L += collect(a.part + k);
-      }
+      static_assert(STAGE_MAX_BLOCKS <= 64, "a partial per lane");
+      if (tid < 64) L = wave_sum(tid < nblk ? collect(a.part + tid) : 0.0);
     }
     if (tid == 0) {
       if (a.loss_scalar) *a.loss_scalar = seq_mode ? *a.loss_scalar + (float)L : (float)L;
@@ -423,8 +420,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
   __syncthreads();
   double* glam = a.part + (int64_t)(pass * nblk + blockIdx.x) * a.mu.nl;
   // weight-net backward: hidden unit h is shared by nch consecutive lanes of a wave (the largest power of two <=
-  // ST_THREADS / H, at most 64), each walking a contiguous run of the samples in order; every lane then adds the nch partial
-  // sums of its unit in chunk order through shuffles (fixed order, no atomics)
+  // ST_THREADS / H, at most 64), each walking a contiguous run of the samples in order; the nch partial sums of a unit
+  // are then added pairwise across the lanes (fixed order, no atomics)
   {
     int nch = 1;
     while (2 * nch * H <= ST_THREADS && nch < 64) nch *= 2;
@@ -445,12 +442,9 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
         }
       }
     }
-    const int base = (tid & 63) & ~(nch - 1);
-    double tot[3] = {0.0, 0.0, 0.0};
-    for (int k = 0; k < nch; ++k)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) tot[q] += __shfl(part[q], base + k, 64);
-    if (h < H && c == 0) { publish(glam + h, tot[0]); publish(glam + H + h, tot[1]); publish(glam + 2 * H + h, tot[2]); }
+    for (int q = 0; q < 3; ++q) part[q] = run_sum(part[q], nch);
+    if (h < H && c == 0) { publish(glam + h, part[0]); publish(glam + H + h, part[1]); publish(glam + 2 * H + h, part[2]); }
   }
   double dsum = 0.0;
   for (int i = tid; i < n_own; i += ST_THREADS) dsum += s_dz[i];

@@ -384,3 +384,55 @@ def test_reweighting_learns_to_down_weight_flipped_labels(cfg, steps):
     assert wc > 1.2 * wf and wc - wf > 10 * abs(wc0 - wf0)
     assert acc > acc0 + 0.25
     gpu.close()
+
+
+def _linear_workload(d, C, H, B, alpha):
+    from datagen.workloads import Workload
+    r = CounterRNG(1000 + d + B + H)
+    wl = Workload(cfg=0, kind="mlp", dims=(d, C), bf16=False, H=H, batch=B, meta_batch=B, base_lr=1e-2, meta_lr=1e-3, alpha=alpha,
+                  noise=0.0, n_train=B, n_meta=B, steps=1)
+    x = r.normal(1, B * d).reshape(B, d).astype(np.float32); y = r.integers(2, B, C).astype(np.int32)
+    th0 = (0.3 * r.normal(5, d * C + C)).astype(np.float32).astype(np.float64)
+    lam0 = r.normal(6, 3 * H + 1).astype(np.float32).astype(np.float64)
+    return wl, x, y, th0, lam0, r
+
+
+@pytest.mark.parametrize("B,H", [(33, 5), (512, 16), (1100, 100), (2048, 256)])
+def test_stage_sums_over_workgroups_and_hidden_units(B, H):
+    """The per-sample stage with 2, 16, 35 and 64 workgroups, and with 64, 32, 4 and 2 lanes to a hidden unit of the weight net:
+    loss, lambda-gradients of the two passes, h and the update of lambda."""
+    import torch
+    wl, x, y, th0, lam0, r = _linear_workload(32, 3, H, B, 0.5)
+    orc, gpu = make_pair(wl, th0, lam0)
+    xm, ym = r.normal(8, 20 * 32).reshape(20, 32).astype(np.float32), r.integers(9, 20, 3).astype(np.int32)
+    loss = torch.zeros(1, device=gpu.dev)
+    for _ in range(3):
+        want = orc.base_step(x, y); gpu.base_step(dev_batch(gpu, x, y), loss)
+    assert abs(loss.item() - want) < 1e-5 * abs(want)      # fp32 parameters and logits, double from there on
+    push_state(orc, gpu)
+    rr = orc.meta_step(x, y, xm, ym); gpu.meta_step(dev_batch(gpu, x, y), dev_batch(gpu, xm, ym))
+    # the logits are sums of 32 fp32 products and eps v comes from such a pass too; h divides the difference of the two by its size
+    bar = 5e-6
+    amplified = (np.linalg.norm(rr["glam_p"]) + np.linalg.norm(rr["glam_m"])) / np.linalg.norm(rr["glam_p"] - rr["glam_m"])
+    assert rel_l2(pull(gpu, "GLAM_PLUS"), rr["glam_p"]) < bar and rel_l2(pull(gpu, "GLAM_MINUS"), rr["glam_m"]) < bar
+    assert rel_l2(pull(gpu, "HYPERGRAD"), rr["h"]) < bar * amplified
+    assert rel_l2(pull(gpu, "LAMBDA"), orc.lam) < 1e-6
+    gpu.close()
+
+
+@pytest.mark.parametrize("d,C", [(24, 3), (682, 6), (1024, 12), (1025, 8)])
+def test_sgd_update_of_every_element(d, C):
+    """SGD with momentum and weight decay over 75 to 12300 parameters (whole and partial vectors, one to four workgroups): each
+    element against the update from the gradient the library kept, to the rounding of three fp32 operations."""
+    wl, x, y, th0, lam0, r = _linear_workload(d, C, 8, 16, 0.5)
+    orc, gpu = make_pair(wl, th0, lam0, base_opt="sgd", base_lr=0.05, momentum=0.9, weight_decay=0.25)
+    n = d * C + C
+    m0 = r.normal(11, n).astype(np.float32)
+    gpu.set_state("M", m0)
+    orc.base_step(x, y); gpu.base_step(dev_batch(gpu, x, y))
+    g, m, th = (pull(gpu, k).astype(np.float64) for k in ("G", "M", "THETA"))
+    assert rel_l2(g, orc.g) < TOL
+    ulp = 2.0 ** -23
+    assert np.all(np.abs(m - (0.9 * m0.astype(np.float64) + g)) <= 2 * ulp * (np.abs(m0) + np.abs(g)))
+    assert np.all(np.abs(th - (th0 - 0.05 * m)) <= 2 * ulp * (np.abs(th0) + 0.05 * np.abs(m)))
+    gpu.close()
