@@ -126,97 +126,80 @@ __global__ __launch_bounds__(256) void k_ln_fwd(LnFwdArgs a) {
 
 // =========================================================================================== LayerNorm backward
 // dx = rstd (dy g - mean(dy g) - xh mean(dy g xh)); per-block partial sums of dgamma = dy xh, dbeta = dy and of
-// dx itself (the bias gradient of the linear layer feeding this LayerNorm).  A block owns LN_BWD_ROWS rows,
-// each wave walks its rows in order, lanes keep per-column accumulators, the four waves are added in order.
+// dx itself (the bias gradient of the linear layer feeding this LayerNorm).  A block owns LN_BWD_ROWS rows, a wave one of them;
+// the three vectors' rows go through LDS one vector at a time and are added in row order.  Bound by memory where there is much of
+// it (8192 rows of 768: 16.3 us, 6.0 TB/s) and by the chain from the loads through two sums over the row where there is little: two
+// rows to a wave and sums by shuffles took 8.4 us for 2048 rows of 1024, now 6.9, and 5.6 for 512 of 768, now 4.6.
 template <int NV>
-__global__ __launch_bounds__(256) void k_ln_bwd(LnBwdArgs a) {
-  __shared__ float s_acc[4][3][256 * NV];
+__global__ __launch_bounds__(64 * LN_BWD_ROWS) void k_ln_bwd(LnBwdArgs a) {
+  __shared__ float4 s_rows[LN_BWD_ROWS][64 * NV];
   const int M = a.rows != nullptr ? __builtin_amdgcn_readfirstlane(*a.rows) : a.M;
   if ((int)blockIdx.x * LN_BWD_ROWS >= M) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * LN_BWD_ROWS + wave;
   const int nq = a.d >> 2;
-  float4 dg[NV], db[NV], dc[NV], gam[NV];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    dg[j] = db[j] = dc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    gam[j] = (lane + 64 * j < nq) ? reinterpret_cast<const float4*>(a.gamma)[lane + 64 * j] : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  const int r0 = blockIdx.x * LN_BWD_ROWS + wave * (LN_BWD_ROWS / 4);
-  constexpr int RW = LN_BWD_ROWS / 4;   // rows per wave: all of their loads are issued before the first row is reduced
-  float4 xin[RW][NV], dyin[RW][NV];
-  float mus[RW], rstds[RW];
-#pragma unroll
-  for (int rr = 0; rr < RW; ++rr) {
-    const int row = r0 + rr;
-    mus[rr] = rstds[rr] = 0.f;
-    if (row < M) { mus[rr] = a.mean[row]; rstds[rr] = a.rstd[row]; }
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int q = lane + 64 * j;
-      xin[rr][j] = dyin[rr][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (row < M && q < nq) {
-        xin[rr][j] = reinterpret_cast<const float4*>(a.x + (int64_t)row * a.d)[q];
-        dyin[rr][j] = reinterpret_cast<const float4*>(a.dy + (int64_t)row * a.d)[q];
-      }
-    }
-  }
-#pragma unroll
-  for (int rr = 0; rr < RW; ++rr) {
-    const int row = r0 + rr;
-    if (row >= M) break;
-    const float mu = mus[rr], rstd = rstds[rr];
-    float4 xh[NV], dyg[NV];
-    float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int q = lane + 64 * j;
-      xh[j] = dyg[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (q < nq) {
-        const float4 x = xin[rr][j];
-        const float4 dy = dyin[rr][j];
-        xh[j] = make_float4((x.x - mu) * rstd, (x.y - mu) * rstd, (x.z - mu) * rstd, (x.w - mu) * rstd);
-        dyg[j] = make_float4(dy.x * gam[j].x, dy.y * gam[j].y, dy.z * gam[j].z, dy.w * gam[j].w);
-        dg[j].x = fmaf(dy.x, xh[j].x, dg[j].x); dg[j].y = fmaf(dy.y, xh[j].y, dg[j].y);
-        dg[j].z = fmaf(dy.z, xh[j].z, dg[j].z); dg[j].w = fmaf(dy.w, xh[j].w, dg[j].w);
-        db[j].x += dy.x; db[j].y += dy.y; db[j].z += dy.z; db[j].w += dy.w;
-        s1 += (dyg[j].x + dyg[j].y) + (dyg[j].z + dyg[j].w);
-        s2 += (dyg[j].x * xh[j].x + dyg[j].y * xh[j].y) + (dyg[j].z * xh[j].z + dyg[j].w * xh[j].w);
-      }
-    }
-    const float m1 = wave_sum(s1) / (float)a.d, m2 = wave_sum(s2) / (float)a.d;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int q = lane + 64 * j;
-      if (q < nq) {
-        float4 dx;
-        dx.x = rstd * (dyg[j].x - m1 - xh[j].x * m2); dx.y = rstd * (dyg[j].y - m1 - xh[j].y * m2);
-        dx.z = rstd * (dyg[j].z - m1 - xh[j].z * m2); dx.w = rstd * (dyg[j].w - m1 - xh[j].w * m2);
-        dc[j].x += dx.x; dc[j].y += dx.y; dc[j].z += dx.z; dc[j].w += dx.w;
-        if (a.dx32 != nullptr) reinterpret_cast<float4*>(a.dx32 + (int64_t)row * a.d)[q] = dx;
-        if (a.dx16 != nullptr) {
-          uint2 pk;
-          pk.x = pack_bf16x2(dx.x, dx.y);
-          pk.y = pack_bf16x2(dx.z, dx.w);
-          *reinterpret_cast<uint2*>(a.dx16 + (int64_t)row * a.d + 4 * q) = pk;
-        }
-      }
-    }
-  }
+  const bool live = row < M;
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 xh[NV], dy[NV], gam[NV];
+  float mu = 0.f, rstd = 0.f;
+  if (live) { mu = a.mean[row]; rstd = a.rstd[row]; }
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int q = lane + 64 * j;
-    if (q < nq) {
-      reinterpret_cast<float4*>(s_acc[wave][0])[q] = dg[j];
-      reinterpret_cast<float4*>(s_acc[wave][1])[q] = db[j];
-      reinterpret_cast<float4*>(s_acc[wave][2])[q] = dc[j];
+    xh[j] = dy[j] = gam[j] = zero;
+    if (live && q < nq) {
+      xh[j] = reinterpret_cast<const float4*>(a.x + (int64_t)row * a.d)[q];
+      dy[j] = reinterpret_cast<const float4*>(a.dy + (int64_t)row * a.d)[q];
+      gam[j] = reinterpret_cast<const float4*>(a.gamma)[q];
     }
   }
-  __syncthreads();
-  float* out = a.partial + (int64_t)blockIdx.x * 3 * a.d;
-  for (int i = threadIdx.x; i < 3 * a.d; i += 256) {
-    const int v = i / a.d, c = i - v * a.d;
-    out[i] = ((s_acc[0][v][c] + s_acc[1][v][c]) + s_acc[2][v][c]) + s_acc[3][v][c];
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    if (lane + 64 * j >= nq) continue;
+    xh[j] = make_float4((xh[j].x - mu) * rstd, (xh[j].y - mu) * rstd, (xh[j].z - mu) * rstd, (xh[j].w - mu) * rstd);
+    gam[j] = make_float4(dy[j].x * gam[j].x, dy[j].y * gam[j].y, dy[j].z * gam[j].z, dy[j].w * gam[j].w);   // dy g from here on
+    s1 += (gam[j].x + gam[j].y) + (gam[j].z + gam[j].w);
+    s2 += (gam[j].x * xh[j].x + gam[j].y * xh[j].y) + (gam[j].z * xh[j].z + gam[j].w * xh[j].w);
   }
+  const float m1 = wave_sum(s1) / (float)a.d, m2 = wave_sum(s2) / (float)a.d;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int q = lane + 64 * j;
+    float4 dx;
+    dx.x = rstd * (gam[j].x - m1 - xh[j].x * m2); dx.y = rstd * (gam[j].y - m1 - xh[j].y * m2);
+    dx.z = rstd * (gam[j].z - m1 - xh[j].z * m2); dx.w = rstd * (gam[j].w - m1 - xh[j].w * m2);
+    if (live && q < nq) {
+      if (a.dx32 != nullptr) reinterpret_cast<float4*>(a.dx32 + (int64_t)row * a.d)[q] = dx;
+      if (a.dx16 != nullptr) {
+        uint2 pk;
+        pk.x = pack_bf16x2(dx.x, dx.y);
+        pk.y = pack_bf16x2(dx.z, dx.w);
+        *reinterpret_cast<uint2*>(a.dx16 + (int64_t)row * a.d + 4 * q) = pk;
+      }
+    }
+    gam[j] = dx;
+    xh[j] = make_float4(dy[j].x * xh[j].x, dy[j].y * xh[j].y, dy[j].z * xh[j].z, dy[j].w * xh[j].w);
+  }
+  float* const out = a.partial + (int64_t)blockIdx.x * 3 * a.d;
+  auto add_rows = [&](const float4 (&v)[NV], float* o) {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) s_rows[wave][lane + 64 * j] = v[j];
+    __syncthreads();
+    for (int q = threadIdx.x; q < nq; q += 64 * LN_BWD_ROWS) {
+      float4 t = s_rows[0][q];
+#pragma unroll
+      for (int r = 1; r < LN_BWD_ROWS; ++r) {
+        const float4 u = s_rows[r][q];
+        t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+      }
+      reinterpret_cast<float4*>(o)[q] = t;
+    }
+  };
+  add_rows(xh, out);
+  __syncthreads();
+  add_rows(dy, out + a.d);
+  __syncthreads();
+  add_rows(gam, out + 2 * a.d);
 }
 
 // out_v[c] = sum_r partial[r*stride + v*vstride + c] for up to three vectors v per job, several jobs per launch.
@@ -763,8 +746,8 @@ void launch_ln_fwd(hipStream_t st, const LnFwdArgs& a) {
 }
 void launch_ln_bwd(hipStream_t st, const LnBwdArgs& a) {
   ProfScope ps(st, F_LN_BWD, 14.0 * a.M * a.d);
-  if (a.d <= 1024) launch_kernel(ps, k_ln_bwd<4>, (a.M + LN_BWD_ROWS - 1) / LN_BWD_ROWS, 256, 0, st, a);
-  else launch_kernel(ps, k_ln_bwd<8>, (a.M + LN_BWD_ROWS - 1) / LN_BWD_ROWS, 256, 0, st, a);
+  if (a.d <= 1024) launch_kernel(ps, k_ln_bwd<4>, (a.M + LN_BWD_ROWS - 1) / LN_BWD_ROWS, 64 * LN_BWD_ROWS, 0, st, a);
+  else launch_kernel(ps, k_ln_bwd<8>, (a.M + LN_BWD_ROWS - 1) / LN_BWD_ROWS, 64 * LN_BWD_ROWS, 0, st, a);
 }
 void launch_reduce_rows_multi(hipStream_t st, const ReduceRowsJob* jobs, int count) {
   ReduceRowsMulti m{};
