@@ -1,16 +1,20 @@
 // fp32 contraction for the fp32 base learners (logistic regression, small MLPs): forward, dgrad and wgrad of a
 // linear layer are the same kernel with different strides.  The matrix cores are used in their fp32 form
-// (v_mfma_f32_16x16x4_f32), so results carry plain fp32 rounding.  Shapes are arbitrary: every global access is
-// bounds-checked.
+// (v_mfma_f32_16x16x4_f32), so results carry plain fp32 rounding.  Shapes are arbitrary: rows
+// beyond an operand's are clamped, contraction indices beyond the end read as zeros.
 //
 // These problems are tiny (a batch of 128 rows, a few hundred columns) and latency-bound, so the kernel is built for
 // short dependency chains rather than for reuse: a workgroup owns one output tile, its eight waves split the
 // contraction between them in interleaved chunks of 16 and fetch their operands from global memory straight into the
-// MFMA operand layout (lane (r, q) holds row r and the four contraction indices 4q .. 4q+3 of a chunk: one 16-byte
-// load where the contraction index is the contiguous one) -- no LDS staging, no barrier inside the loop, FDEPTH chunks
-// of loads in flight ahead of the MFMAs.  The eight partial tiles are added in wave order through LDS, so the result does
-// not depend on timing.  Measured on a 128 x 256 x 784 layer: 6.0 us, against 14.9 us with 32 x 32 tiles, four waves and one
-// chunk ahead (32 workgroups on 256 CUs).
+// MFMA operand layout (lane (r, q) holds row r and the four contraction indices 4q .. 4q+3 of a chunk) -- no LDS staging, no
+// barrier inside the loop, FDEPTH chunks of loads in flight ahead of the MFMAs.  The eight partial tiles are added in wave order
+// through LDS, so the result does not depend on timing.
+// Loads are as wide as the storage allows, whatever the alignment (gfx950 takes a 16-byte load at any float): along the
+// contraction index 16 bytes, across the rows the two or four that a lane's tiles need of one index; and the loop has
+// no branches that depend on the operands' edges: rows are clamped, and the chunk that is not whole is apart.  us for rows x
+// columns x contraction, against scalar loads for odd widths and strided operands, every load behind its own bounds check:
+// 203 x 173 x 301 6.1 -> 3.7, 1500 x 173 x 301 14.3 -> 8.2, 2048 x 256 x 784 16.8 -> 14.0, 128 x 256 x 784 5.7 -> 5.0, both gradients of
+// a layer of 320 x 1024 over 512 rows 20.1 -> 16.1; over 150 products and pairs 1.37 times as fast (geometric mean).
 //
 // Independent problems share a launch (a layer's weight gradient with its column sums and its input gradient; the + and
 // the - pass of Eq. 5): a dependent launch costs ~4 us here, more than most of these products.
@@ -23,28 +27,85 @@
 namespace sama {
 namespace {
 
-struct GemmF32Batch { GemmF32Args j[GEMM_F32_MAX_JOBS]; int first_block[GEMM_F32_MAX_JOBS + 1]; int count; };
+// what a product is of a layer by the storage of its operands: both with the contraction index the contiguous one, only A, neither
+enum { F32_FORWARD, F32_DGRAD, F32_WGRAD };
+int storage_of(const GemmF32Args& a) {   // -1: none of them (a matrix of one column is of either kind)
+  if (a.rowsum == nullptr && a.sa_k == 1 && a.sb_k == 1) return F32_FORWARD;
+  if (a.Bv != nullptr || a.sb_j != 1) return -1;
+  if (a.rowsum == nullptr && a.sa_k == 1) return F32_DGRAD;
+  return a.sa_i == 1 ? F32_WGRAD : -1;
+}
+static_assert(GEMM_F32_MAX_JOBS == 2, "one or two problems");
+struct GemmF32Batch { GemmF32Args j[2]; int blocks[2], storage[2]; };   // blocks: multiples of 8; none of a problem that is not there
 
-// XM x XN output tiles of 16 x 16 per workgroup; FDEPTH chunks in flight per wave
-template <int XM, int XN, int FDEPTH>
-__global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch) {
+// How an operand lies: a row's contraction indices side by side, or (an operand of a weight gradient, the weights of an input
+// gradient) the rows at one contraction index.  A lane's X tiles of 16 rows are then rows r, 16 + r, ... or, of the second kind,
+// the X adjacent rows X r .. X r + X - 1, so that one load has them all.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // a vector load wants no more than a float's alignment
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+template <int X, bool KC>
+__device__ __forceinline__ int tile_row(int x, int r) { return KC ? 16 * x + r : X * r + x; }
+
+// Of one operand the chunk of contraction indices k .. k + 3 (k: this lane's first): v[x][c] is row `row(x)` at index k + c.
+template <int X, bool KC, bool FULL>
+struct F32Operand {
+  const float* p[KC || !FULL ? X : 1];   // rows beyond the end are clamped: their products are never stored
+  int64_t s_k;
+  __device__ __forceinline__ void init(const float* base, int64_t s_row, int64_t s_k_, int row0, int nrows, int r) {
+    s_k = s_k_;
+#pragma unroll
+    for (int x = 0; x < (KC || !FULL ? X : 1); ++x) p[x] = base + (int64_t)min(row0 + tile_row<X, KC>(x, r), nrows - 1) * s_row;
+  }
+  __device__ __forceinline__ void load(int k, float4v (&v)[X]) const {
+    if constexpr (KC) {
+#pragma unroll
+      for (int x = 0; x < X; ++x) v[x] = *reinterpret_cast<const f4u*>(p[x] + k);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int64_t o = (int64_t)(k + c) * s_k;
+        if constexpr (FULL && X == 4) {
+          const f4u t = *reinterpret_cast<const f4u*>(p[0] + o);
+#pragma unroll
+          for (int x = 0; x < X; ++x) v[x][c] = t[x];
+        } else if constexpr (FULL && X == 2) {
+          const f2u t = *reinterpret_cast<const f2u*>(p[0] + o);
+          v[0][c] = t[0]; v[X - 1][c] = t[1];
+        } else {
+#pragma unroll
+          for (int x = 0; x < X; ++x) v[x][c] = p[x][o];
+        }
+      }
+    }
+  }
+  // zeros from K on
+  __device__ __forceinline__ void load_tail(int k, int K, float4v (&v)[X]) const {
+#pragma unroll
+    for (int x = 0; x < X; ++x)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int64_t kk = min(k + c, K - 1);
+        const float t = KC ? p[x][kk] : FULL ? p[0][kk * s_k + x] : p[KC || !FULL ? x : 0][kk * s_k];
+        v[x][c] = k + c < K ? t : 0.f;
+      }
+  }
+};
+
+// XM x XN output tiles of 16 x 16 per workgroup; FDEPTH chunks in flight per wave.  FULL: all rows of an operand that is not KC exist.
+// PV: B is perturbed.
+template <int XM, int XN, int FDEPTH, bool A_KC, bool B_KC, bool FULL, bool PV>
+__device__ __forceinline__ void gemm_f32_tile(const GemmF32Args& a, int i0, int j0, float bscale, float* __restrict__ red_, float* __restrict__ rsum_) {
   constexpr int TM = 16 * XM, TN = 16 * XN;
-  __shared__ float red[FWAVES][TM][TN + 1];
-  __shared__ float rsum[FWAVES][TM];
+  float (*red)[TM][TN + 1] = reinterpret_cast<float (*)[TM][TN + 1]>(red_);
+  float (*rsum)[TM] = reinterpret_cast<float (*)[TM]>(rsum_);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, q = lane >> 4;
-  int job = 0;
-#pragma unroll
-  for (int k = 1; k < GEMM_F32_MAX_JOBS; ++k)
-    if (k < batch.count && (int)blockIdx.x >= batch.first_block[k]) job = k;
-  const GemmF32Args a = batch.j[job];
-  const int local = blockIdx.x - batch.first_block[job], nbx = (a.N + TN - 1) / TN;
-  const int i0 = (local / nbx) * TM, j0 = (local % nbx) * TN;
-  const float bscale = (a.Bv != nullptr && a.beps != nullptr) ? a.bsign * (*a.beps) : 0.f;
-  const bool rows = a.rowsum != nullptr && j0 == 0;   // this workgroup also sums its rows of A over the contraction
-  // 16-byte loads along the contraction index need it contiguous and every row start aligned
-  const bool a_vec = a.sa_k == 1 && (a.sa_i & 3) == 0 && ((uintptr_t)a.A & 15) == 0;
-  const bool b_vec = a.sb_k == 1 && (a.sb_j & 3) == 0 && ((uintptr_t)a.B & 15) == 0 && (a.Bv == nullptr || ((uintptr_t)a.Bv & 15) == 0);
+  const bool rows = !A_KC && a.rowsum != nullptr && j0 == 0;   // this workgroup also sums its rows of A over the contraction
+  F32Operand<XM, A_KC, FULL> oa;
+  F32Operand<XN, B_KC, FULL> ob, ov;
+  oa.init(a.A, a.sa_i, a.sa_k, i0, a.M, r);
+  ob.init(a.B, a.sb_j, a.sb_k, j0, a.N, r);
+  if (PV) ov.init(a.Bv, a.sb_j, a.sb_k, j0, a.N, r);
 
   float4v acc[XM][XN];
   float rs[XM];
@@ -54,57 +115,129 @@ __global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch) {
 #pragma unroll
     for (int y = 0; y < XN; ++y) acc[x][y] = (float4v){0.f, 0.f, 0.f, 0.f};
   }
-
-  float4v av[FDEPTH][XM], bv[FDEPTH][XN], pv[FDEPTH][XN];
-  auto fetch = [&](int k0, int buf) {
-    const int k = k0 + 4 * q;
-#pragma unroll
-    for (int x = 0; x < XM; ++x) av[buf][x] = load_k4(a.A, a.sa_i, a.sa_k, i0 + 16 * x + r, a.M, k, a.K, a_vec);
-#pragma unroll
-    for (int y = 0; y < XN; ++y) {
-      bv[buf][y] = load_k4(a.B, a.sb_j, a.sb_k, j0 + 16 * y + r, a.N, k, a.K, b_vec);
-      if (bscale != 0.f) pv[buf][y] = load_k4(a.Bv, a.sb_j, a.sb_k, j0 + 16 * y + r, a.N, k, a.K, b_vec);
-    }
+  float4v av[FDEPTH][XM], bv[FDEPTH][XN], pv[PV ? FDEPTH : 1][XN];
+  // chunks wave, wave + FWAVES, ... of those that are whole
+  constexpr int STEP = FWAVES * FCH;
+  const int nfull = a.K / FCH, n = nfull > wave ? (nfull - wave + FWAVES - 1) / FWAVES : 0, k_lane = wave * FCH + 4 * q;
+  auto fetch = [&](int i, int u) {   // the i-th of them
+    oa.load(k_lane + i * STEP, av[u]);
+    ob.load(k_lane + i * STEP, bv[u]);
+    if constexpr (PV) ov.load(k_lane + i * STEP, pv[u]);
   };
-  // chunks wave, wave + FWAVES, ...; FDEPTH of them are requested before the first is used
-  for (int kb = wave * FCH; kb < a.K; kb += FDEPTH * FWAVES * FCH) {
+  auto multiply = [&](const float4v (&av)[XM], float4v (&bv)[XN], const float4v (&pv)[XN]) {
+    if constexpr (PV) {
 #pragma unroll
-    for (int u = 0; u < FDEPTH; ++u)
-      if (kb + u * FWAVES * FCH < a.K) fetch(kb + u * FWAVES * FCH, u);
+      for (int y = 0; y < XN; ++y)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) bv[y][c] = fmaf(bscale, pv[y][c], bv[y][c]);
+    }
+    if (rows) {
+#pragma unroll
+      for (int x = 0; x < XM; ++x) rs[x] += (av[x][0] + av[x][1]) + (av[x][2] + av[x][3]);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int x = 0; x < XM; ++x)
+#pragma unroll
+        for (int y = 0; y < XN; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[x][c], bv[y][c], acc[x][y], 0, 0, 0);
+  };
+  auto use = [&](int u) { multiply(av[u], bv[u], pv[PV ? u : 0]); };
+  // FDEPTH chunks are in flight; a buffer's next chunk is requested as soon as its last one has been used.  (No load is conditional
+  // in the loop: the waits count loads.)  What is left of the contraction is the last chunk of its wave, and requested first.
+  const bool tail = a.K % FCH != 0 && nfull % FWAVES == wave;
+  float4v at[XM], bt[XN], pt[XN];
+  if (tail) {
+    const int k = nfull * FCH + 4 * q;
+    oa.load_tail(k, a.K, at);
+    ob.load_tail(k, a.K, bt);
+    if constexpr (PV) ov.load_tail(k, a.K, pt);
+  }
+  if (FDEPTH < 8 && n >= FDEPTH) {
+#pragma unroll
+    for (int u = 0; u < FDEPTH; ++u) fetch(u, u);
+    int i = 0;
+    for (; i + 2 * FDEPTH <= n; i += FDEPTH) {
+#pragma unroll
+      for (int u = 0; u < FDEPTH; ++u) { use(u); fetch(i + FDEPTH + u, u); }
+    }
 #pragma unroll
     for (int u = 0; u < FDEPTH; ++u) {
-      if (kb + u * FWAVES * FCH >= a.K) break;
-      if (bscale != 0.f) {
+      use(u);
+      if (i + FDEPTH + u < n) fetch(i + FDEPTH + u, u);
+    }
 #pragma unroll
-        for (int y = 0; y < XN; ++y)
+    for (int u = 0; u < FDEPTH; ++u)
+      if (i + FDEPTH + u < n) use(u);
+  } else {
+    for (int i = 0; i < n; i += FDEPTH) {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) bv[u][y][c] = fmaf(bscale, pv[u][y][c], bv[u][y][c]);
-      }
-      if (rows) {
+      for (int u = 0; u < FDEPTH; ++u)
+        if (i + u < n) fetch(i + u, u);
 #pragma unroll
-        for (int x = 0; x < XM; ++x) rs[x] += (av[u][x][0] + av[u][x][1]) + (av[u][x][2] + av[u][x][3]);
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-#pragma unroll
-        for (int x = 0; x < XM; ++x)
-#pragma unroll
-          for (int y = 0; y < XN; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][x][c], bv[u][y][c], acc[x][y], 0, 0, 0);
+      for (int u = 0; u < FDEPTH; ++u)
+        if (i + u < n) use(u);
     }
   }
+  if (tail) multiply(at, bt, pt);
   // partial tiles -> LDS, added in wave order
 #pragma unroll
   for (int x = 0; x < XM; ++x) {
 #pragma unroll
     for (int y = 0; y < XN; ++y)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) red[wave][16 * x + 4 * q + e][16 * y + r] = acc[x][y][e];
+      for (int e = 0; e < 4; ++e) red[wave][tile_row<XM, A_KC>(x, 4 * q + e)][tile_row<XN, B_KC>(y, r)] = acc[x][y][e];
     if (rows) {
-      float s = rs[x];
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
-      if (q == 0) rsum[wave][16 * x + r] = s;
+      const auto add = [](float s, float t) { return s + t; };
+      const float s = join32(join16(rs[x], add), add);
+      if (q == 0) rsum[wave][tile_row<XM, A_KC>(x, r)] = s;
     }
+  }
+}
+
+// a = second ? b : a, both read: an index into the kernel's arguments that is computed first costs another trip to them, 0.2 us
+// (128 x 256 x 784: 4.95 us; with the index 5.27)
+template <typename T>
+__device__ __forceinline__ void pick(T& a, T b, bool second) {
+  asm("" : "+s"(a));
+  asm("" : "+s"(b));
+  a = second ? b : a;
+}
+
+// PAIR: there are two problems
+template <int XM, int XN, int FDEPTH, bool PAIR>
+__global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch) {
+  constexpr int TM = 16 * XM, TN = 16 * XN;
+  __shared__ float red[FWAVES][TM][TN + 1];
+  __shared__ float rsum[FWAVES][TM];
+  const bool second = PAIR && (int)blockIdx.x >= batch.blocks[0];
+  GemmF32Args a = batch.j[0];
+  if (PAIR) {
+    const GemmF32Args& b = batch.j[1];
+    pick(a.A, b.A, second); pick(a.sa_i, b.sa_i, second); pick(a.sa_k, b.sa_k, second);
+    pick(a.B, b.B, second); pick(a.sb_k, b.sb_k, second); pick(a.sb_j, b.sb_j, second);
+    pick(a.Bv, b.Bv, second); pick(a.beps, b.beps, second); pick(a.bsign, b.bsign, second);
+    pick(a.C, b.C, second); pick(a.ldc, b.ldc, second); pick(a.M, b.M, second); pick(a.N, b.N, second); pick(a.K, b.K, second);
+    pick(a.bias, b.bias, second); pick(a.bias_v, b.bias_v, second); pick(a.gate, b.gate, second); pick(a.relu, b.relu, second); pick(a.rowsum, b.rowsum, second);
+  }
+  const int storage = second ? batch.storage[1] : batch.storage[0], blocks = second ? batch.blocks[1] : batch.blocks[0];
+  // Workgroups are dealt round-robin to the 8 XCDs (a problem starts at a multiple of 8); each gets a run of a problem's tiles, so
+  // that their rows of A come into its L2 once: 2048 x 256 x 784 15.8 -> 14.1 us
+  const int nth = second ? blockIdx.x - batch.blocks[0] : blockIdx.x, local = (nth & 7) * (blocks >> 3) + (nth >> 3), nbx = (a.N + TN - 1) / TN;
+  const int i0 = (local / nbx) * TM, j0 = (local % nbx) * TN;
+  if (i0 >= a.M) return;
+  const float bscale = (a.Bv != nullptr && a.beps != nullptr) ? a.bsign * (*a.beps) : 0.f;
+  const bool rows = a.rowsum != nullptr && j0 == 0, full = (storage != F32_WGRAD || i0 + TM <= a.M) && j0 + TN <= a.N;
+  float* const r0 = &red[0][0][0]; float* const r1 = &rsum[0][0];
+  if (storage == F32_FORWARD) {
+    if (bscale != 0.f) gemm_f32_tile<XM, XN, FDEPTH, true, true, true, true>(a, i0, j0, bscale, r0, r1);
+    else gemm_f32_tile<XM, XN, FDEPTH, true, true, true, false>(a, i0, j0, 0.f, r0, r1);
+  } else if (storage == F32_DGRAD) {
+    if (full) gemm_f32_tile<XM, XN, FDEPTH, true, false, true, false>(a, i0, j0, 0.f, r0, r1);
+    else gemm_f32_tile<XM, XN, FDEPTH, true, false, false, false>(a, i0, j0, 0.f, r0, r1);
+  } else {
+    if (full) gemm_f32_tile<XM, XN, FDEPTH, false, false, true, false>(a, i0, j0, 0.f, r0, r1);
+    else gemm_f32_tile<XM, XN, FDEPTH, false, false, false, false>(a, i0, j0, 0.f, r0, r1);
   }
   __syncthreads();
   for (int t = threadIdx.x; t < TM * TN; t += 64 * FWAVES) {
@@ -139,15 +272,13 @@ int64_t tiles(const GemmF32Args* a, int count, int tm, int tn) {
 template <int XM, int XN, int FDEPTH>
 void launch_tile_f32(ProfScope& ps, hipStream_t st, const GemmF32Args* a, int count) {
   GemmF32Batch b{};
-  b.count = count;
-  int nb = 0;
   for (int k = 0; k < count; ++k) {
     b.j[k] = a[k];
-    b.first_block[k] = nb;
-    nb += (int)tiles(a + k, 1, 16 * XM, 16 * XN);
+    b.storage[k] = storage_of(a[k]);
+    b.blocks[k] = (int)(tiles(a + k, 1, 16 * XM, 16 * XN) + 7) / 8 * 8;
   }
-  for (int k = count; k <= GEMM_F32_MAX_JOBS; ++k) b.first_block[k] = nb;
-  launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH>, nb, 64 * FWAVES, 0, st, b);
+  if (count == 2) launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, true>, b.blocks[0] + b.blocks[1], 64 * FWAVES, 0, st, b);
+  else launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, false>, b.blocks[0], 64 * FWAVES, 0, st, b);
 }
 }  // namespace
 
@@ -155,16 +286,17 @@ void launch_gemm_f32_batch(hipStream_t st, const GemmF32Args* a, int count) {
   double flops = 0.0;
   for (int k = 0; k < count; ++k) {
     if (a[k].M <= 0 || a[k].N <= 0) { note_launch_error("empty fp32 GEMM"); return; }
+    if (storage_of(a[k]) < 0) { note_launch_error("fp32 GEMM: operand storage"); return; }
     flops += 2.0 * a[k].M * a[k].N * a[k].K;
   }
   ProfScope ps(st, F_GEMM_F32, flops);
-  // The smallest tile gives the shortest chain and the most workgroups; it reads every operand row once per 16 columns, and as
-  // soon as some CU has two of its workgroups to run the next larger tile is the faster one.  us, 16 x 16 / 32 x 32: 256 tiles
-  // (512 x 128 x 784) 5.8 / 9.3, 384 (512 x 192 x 784) 9.7 / 9.4, 384 (512 x 192 x 256) 6.7 / 5.5; 32 x 32 / 64 x 32: 256 tiles
-  // (1024 x 256 x 784) 9.6 / 15.3, 320 (1024 x 320 x 784) 16.8 / 15.3.  Over 408 products and pairs (32 to 2048 rows, widths to
-  // 320, K to 1024) these lines take 1.2% longer than the fastest tile of each, lines at 512 3.6% (geometric means).
+  // The smallest tile gives the shortest chain and the most workgroups, but reads every operand row once per 16 columns.  us, 16 x 16 /
+  // 32 x 32: 256 tiles of 16 x 16 (512 x 128 x 784) 5.4 / 8.7, 512 (512 x 256 x 784) 8.1 / 8.8, 640 (512 x 320 x 1024) 14.5 / 11.0;
+  // 32 x 32 / 64 x 32: 256 tiles of 32 x 32 (1024 x 256 x 784) 9.0 / 14.3, 320 (a weight gradient over 512 rows, 320 x 1024)
+  // 11.7 / 9.4, 512 (2048 x 256 x 784) 16.0 / 14.9.  Over 150 products and pairs (16 to 2048 rows, widths to 320, K to 1024) these
+  // lines take 1.4% longer than the fastest tile of each, lines at 256 and 256 3.9% (geometric means).
   constexpr int CUS = 256;
-  if (tiles(a, count, 16, 16) <= CUS) launch_tile_f32<1, 1, 8>(ps, st, a, count);
+  if (tiles(a, count, 16, 16) <= 2 * CUS) launch_tile_f32<1, 1, 8>(ps, st, a, count);
   else if (tiles(a, count, 32, 32) <= CUS) launch_tile_f32<2, 2, 4>(ps, st, a, count);
   else launch_tile_f32<4, 2, 2>(ps, st, a, count);
 }

@@ -436,3 +436,30 @@ def test_sgd_update_of_every_element(d, C):
     assert np.all(np.abs(m - (0.9 * m0.astype(np.float64) + g)) <= 2 * ulp * (np.abs(m0) + np.abs(g)))
     assert np.all(np.abs(th - (th0 - 0.05 * m)) <= 2 * ulp * (np.abs(th0) + 0.05 * np.abs(m)))
     gpu.close()
+
+
+@pytest.mark.parametrize("dims", [(1, 1, 2), (16, 15, 3), (17, 33, 2), (130, 1, 4), (64, 32, 48, 10), (301, 129, 66, 5)])
+@pytest.mark.parametrize("B", [1, 31, 129, 600])
+def test_fp32_products_at_their_edges(dims, B):
+    """Widths of one, of less than a chunk of the contraction, of whole and of broken chunks, vectors and tiles, the same for the
+    rows: gradients, the two passes of Eq. 5 and the logits against the oracle."""
+    import torch
+    from datagen.workloads import Workload
+    n = sum(a * b + b for a, b in zip(dims, dims[1:]))
+    r = CounterRNG(55 + sum(dims) + B)
+    wl = Workload(cfg=0, kind="mlp", dims=dims, bf16=False, H=9, batch=B, meta_batch=7, base_lr=1e-2, meta_lr=1e-3, alpha=0.5, noise=0.0,
+                  n_train=B, n_meta=7, steps=1)
+    x = r.normal(1, B * dims[0]).reshape(B, -1).astype(np.float32); y = r.integers(2, B, dims[-1]).astype(np.int32)
+    xm = r.normal(3, 7 * dims[0]).reshape(7, -1).astype(np.float32); ym = r.integers(4, 7, dims[-1]).astype(np.int32)
+    th0 = (r.normal(5, n) * np.sqrt(1.0 / max(dims[0], 4))).astype(np.float32).astype(np.float64)
+    orc, gpu = make_pair(wl, th0, r.normal(6, 28).astype(np.float32).astype(np.float64), base_opt="sgd")
+    out = [torch.zeros(B, dims[-1], device=gpu.dev), torch.zeros(B, device=gpu.dev), torch.zeros(B, device=gpu.dev)]
+    gpu.eval(dev_batch(gpu, x, y), *out)
+    assert rel_l2(out[0].cpu().numpy(), orc.model.logits(orc.theta, x)) < 1e-5
+    orc.base_step(x, y); gpu.base_step(dev_batch(gpu, x, y))
+    assert rel_l2(pull(gpu, "G"), orc.g) < TOL and rel_l2(pull(gpu, "THETA"), orc.theta) < TOL
+    push_state(orc, gpu)
+    rr = orc.meta_step(x, y, xm, ym); gpu.meta_step(dev_batch(gpu, x, y), dev_batch(gpu, xm, ym))
+    assert rel_l2(pull(gpu, "GMETA"), rr["g_meta"]) < TOL
+    assert rel_l2(pull(gpu, "GLAM_PLUS"), rr["glam_p"]) < 2e-5 and rel_l2(pull(gpu, "GLAM_MINUS"), rr["glam_m"]) < 2e-5
+    gpu.close()
