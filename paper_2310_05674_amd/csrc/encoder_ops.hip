@@ -126,30 +126,32 @@ __global__ __launch_bounds__(256) void k_ln_fwd(LnFwdArgs a) {
 
 // =========================================================================================== LayerNorm backward
 // dx = rstd (dy g - mean(dy g) - xh mean(dy g xh)); per-block partial sums of dgamma = dy xh, dbeta = dy and of
-// dx itself (the bias gradient of the linear layer feeding this LayerNorm).  A block owns LN_BWD_ROWS rows, a wave one of them;
-// the three vectors' rows go through LDS one vector at a time and are added in row order.  Bound by memory where there is much of
-// it (8192 rows of 768: 16.3 us, 6.0 TB/s) and by the chain from the loads through two sums over the row where there is little: two
-// rows to a wave and sums by shuffles took 8.4 us for 2048 rows of 1024, now 6.9, and 5.6 for 512 of 768, now 4.6.
+// dx itself (the bias gradient of the linear layer feeding this LayerNorm).  A block owns LN_BWD_ROWS rows, a wave one of them; what
+// the sums are made of goes through LDS, 1024 columns at a time, and is added in pairs of rows, the pairs in order.
+// Bound by memory where there is much of it (8192 rows of 768: 16.1 us, 6.1 TB/s) and by the chain from the loads through two sums
+// over the row where there is little: two rows to a wave and sums by shuffles took 8.4 us for 2048 rows of 1024, now 6.5, and 5.7
+// for 512 of 768, now 4.2.
 template <int NV>
 __global__ __launch_bounds__(64 * LN_BWD_ROWS) void k_ln_bwd(LnBwdArgs a) {
-  __shared__ float4 s_rows[LN_BWD_ROWS][64 * NV];
+  constexpr int G = 4;   // pieces of a lane in a turn
+  static_assert(NV % G == 0 && LN_BWD_ROWS == 8, "turns; four pairs of rows");
+  __shared__ float4 s_a[LN_BWD_ROWS][64 * G], s_b[LN_BWD_ROWS][64 * G];
   const int M = a.rows != nullptr ? __builtin_amdgcn_readfirstlane(*a.rows) : a.M;
   if ((int)blockIdx.x * LN_BWD_ROWS >= M) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * LN_BWD_ROWS + wave;
   const int nq = a.d >> 2;
   const bool live = row < M;
-  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 xh[NV], dy[NV], gam[NV];
+  float4 xh[NV], dy[NV], dx[NV];   // dx: gamma, then dy g, then dx
   float mu = 0.f, rstd = 0.f;
   if (live) { mu = a.mean[row]; rstd = a.rstd[row]; }
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int q = lane + 64 * j;
-    xh[j] = dy[j] = gam[j] = zero;
+    xh[j] = dy[j] = dx[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (live && q < nq) {
       xh[j] = reinterpret_cast<const float4*>(a.x + (int64_t)row * a.d)[q];
       dy[j] = reinterpret_cast<const float4*>(a.dy + (int64_t)row * a.d)[q];
-      gam[j] = reinterpret_cast<const float4*>(a.gamma)[q];
+      dx[j] = reinterpret_cast<const float4*>(a.gamma)[q];
     }
   }
   float s1 = 0.f, s2 = 0.f;
@@ -157,49 +159,66 @@ __global__ __launch_bounds__(64 * LN_BWD_ROWS) void k_ln_bwd(LnBwdArgs a) {
   for (int j = 0; j < NV; ++j) {
     if (lane + 64 * j >= nq) continue;
     xh[j] = make_float4((xh[j].x - mu) * rstd, (xh[j].y - mu) * rstd, (xh[j].z - mu) * rstd, (xh[j].w - mu) * rstd);
-    gam[j] = make_float4(dy[j].x * gam[j].x, dy[j].y * gam[j].y, dy[j].z * gam[j].z, dy[j].w * gam[j].w);   // dy g from here on
-    s1 += (gam[j].x + gam[j].y) + (gam[j].z + gam[j].w);
-    s2 += (gam[j].x * xh[j].x + gam[j].y * xh[j].y) + (gam[j].z * xh[j].z + gam[j].w * xh[j].w);
+    dx[j] = make_float4(dy[j].x * dx[j].x, dy[j].y * dx[j].y, dy[j].z * dx[j].z, dy[j].w * dx[j].w);
+    s1 += (dx[j].x + dx[j].y) + (dx[j].z + dx[j].w);
+    s2 += (dx[j].x * xh[j].x + dx[j].y * xh[j].y) + (dx[j].z * xh[j].z + dx[j].w * xh[j].w);
   }
   const float m1 = wave_sum(s1) / (float)a.d, m2 = wave_sum(s2) / (float)a.d;
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const int q = lane + 64 * j;
-    float4 dx;
-    dx.x = rstd * (gam[j].x - m1 - xh[j].x * m2); dx.y = rstd * (gam[j].y - m1 - xh[j].y * m2);
-    dx.z = rstd * (gam[j].z - m1 - xh[j].z * m2); dx.w = rstd * (gam[j].w - m1 - xh[j].w * m2);
+    dx[j].x = rstd * (dx[j].x - m1 - xh[j].x * m2); dx[j].y = rstd * (dx[j].y - m1 - xh[j].y * m2);
+    dx[j].z = rstd * (dx[j].z - m1 - xh[j].z * m2); dx[j].w = rstd * (dx[j].w - m1 - xh[j].w * m2);
     if (live && q < nq) {
-      if (a.dx32 != nullptr) reinterpret_cast<float4*>(a.dx32 + (int64_t)row * a.d)[q] = dx;
+      if (a.dx32 != nullptr) reinterpret_cast<float4*>(a.dx32 + (int64_t)row * a.d)[q] = dx[j];
       if (a.dx16 != nullptr) {
         uint2 pk;
-        pk.x = pack_bf16x2(dx.x, dx.y);
-        pk.y = pack_bf16x2(dx.z, dx.w);
+        pk.x = pack_bf16x2(dx[j].x, dx[j].y);
+        pk.y = pack_bf16x2(dx[j].z, dx[j].w);
         *reinterpret_cast<uint2*>(a.dx16 + (int64_t)row * a.d + 4 * q) = pk;
       }
     }
-    gam[j] = dx;
-    xh[j] = make_float4(dy[j].x * xh[j].x, dy[j].y * xh[j].y, dy[j].z * xh[j].z, dy[j].w * xh[j].w);
   }
-  float* const out = a.partial + (int64_t)blockIdx.x * 3 * a.d;
-  auto add_rows = [&](const float4 (&v)[NV], float* o) {
+  float4* const out = reinterpret_cast<float4*>(a.partial + (int64_t)blockIdx.x * 3 * a.d);
+  const int tid = threadIdx.x;
+  auto pairs_in_order = [](auto pair) {
+    float4 t = pair(0);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) s_rows[wave][lane + 64 * j] = v[j];
-    __syncthreads();
-    for (int q = threadIdx.x; q < nq; q += 64 * LN_BWD_ROWS) {
-      float4 t = s_rows[0][q];
-#pragma unroll
-      for (int r = 1; r < LN_BWD_ROWS; ++r) {
-        const float4 u = s_rows[r][q];
-        t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
-      }
-      reinterpret_cast<float4*>(o)[q] = t;
-    }
+    for (int r = 2; r < LN_BWD_ROWS; r += 2) { const float4 u = pair(r); t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w; }
+    return t;
   };
-  add_rows(xh, out);
-  __syncthreads();
-  add_rows(dy, out + a.d);
-  __syncthreads();
-  add_rows(gam, out + 2 * a.d);
+#pragma unroll
+  for (int j0 = 0; j0 < NV; j0 += G) {
+    if (64 * j0 >= nq) break;
+    if (j0 > 0) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < G; ++j) { s_a[wave][lane + 64 * j] = xh[j0 + j]; s_b[wave][lane + 64 * j] = dy[j0 + j]; }
+    __syncthreads();
+    // half of the threads dgamma, the other half dbeta
+    const int c = tid & (64 * G - 1), q = 64 * j0 + c;
+    static_assert(64 * LN_BWD_ROWS == 2 * 64 * G, "a thread per quad of columns and sum");
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (q < nq) {
+      if (tid < 64 * G) t = pairs_in_order([&](int r) {
+        const float4 x0 = s_a[r][c], d0 = s_b[r][c], x1 = s_a[r + 1][c], d1 = s_b[r + 1][c];
+        return make_float4(fmaf(d1.x, x1.x, d0.x * x0.x), fmaf(d1.y, x1.y, d0.y * x0.y), fmaf(d1.z, x1.z, d0.z * x0.z), fmaf(d1.w, x1.w, d0.w * x0.w));
+      });
+      else t = pairs_in_order([&](int r) {
+        const float4 d0 = s_b[r][c], d1 = s_b[r + 1][c];
+        return make_float4(d0.x + d1.x, d0.y + d1.y, d0.z + d1.z, d0.w + d1.w);
+      });
+      out[(tid < 64 * G ? 0 : nq) + q] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < G; ++j) s_a[wave][lane + 64 * j] = dx[j0 + j];
+    __syncthreads();
+    if (tid < 64 * G && q < nq)
+      out[2 * nq + q] = pairs_in_order([&](int r) {
+        const float4 d0 = s_a[r][c], d1 = s_a[r + 1][c];
+        return make_float4(d0.x + d1.x, d0.y + d1.y, d0.z + d1.z, d0.w + d1.w);
+      });
+  }
 }
 
 // out_v[c] = sum_r partial[r*stride + v*vstride + c] for up to three vectors v per job, several jobs per launch.
