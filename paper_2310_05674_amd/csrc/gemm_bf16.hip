@@ -139,6 +139,18 @@ struct GemmBatch {
   int count, group;
 };
 
+struct LoopArgs {
+  const bf16_t *A, *B, *B2;
+  int64_t lda, ldb;
+  int M, N, K, act;
+  const float* gelu_tab;
+  const int32_t* rows;
+  __device__ __forceinline__ void pin() {   // keeps the reads where they are
+    asm("" : "+s"(A), "+s"(B), "+s"(B2), "+s"(lda), "+s"(ldb), "+s"(M), "+s"(N), "+s"(K), "+s"(act), "+s"(gelu_tab), "+s"(rows));
+  }
+};
+__device__ __forceinline__ LoopArgs loop_args(const GemmBf16Args& a) { return LoopArgs{a.A, a.B, a.B2, a.lda, a.ldb, a.M, a.N, a.K, a.act, a.gelu_tab, a.rows}; }
+
 template <typename T, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int ntiles, int tiles_per_xcd) {
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, XT = T::XT, YT = T::YT, NSTAGE = T::NSTAGE, WAVES = T::WAVES;
@@ -175,15 +187,21 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   } else {
     pid = (blockIdx.x & 7) * tiles_per_xcd + (blockIdx.x >> 3);
     if (pid >= ntiles) return;
+    int before = 0;
 #pragma unroll
     for (int k = 1; k < GEMM_MAX_BATCH; ++k)
-      if (k < batch.count && pid >= batch.first_tile[k]) prob = k;
-    pid -= batch.first_tile[prob];
+      if (k < batch.count && pid >= batch.first_tile[k]) { prob = k; before = batch.first_tile[k]; }
+    pid -= before;
   }
-  const GemmBf16Args& a = batch.p[prob];
+  // What the loop needs of problem 0 is read with the kernel's first arguments: an index into them that is computed first costs another
+  // trip to memory, 0.2 us, and most launches have one problem.
+  const GemmBf16Args& a = batch.p[prob];   // for the epilogue
+  LoopArgs la = loop_args(batch.p[0]);
+  la.pin();
+  if (prob != 0) la = loop_args(a);
   const int group = batch.group;
-  const int Mrows = fewer_tiles ? rows : a.M;
-  const int gx = (a.N + BN - 1) / BN, gy = (Mrows + BM - 1) / BM;
+  const int Mrows = fewer_tiles ? rows : la.M;
+  const int gx = (la.N + BN - 1) / BN, gy = (Mrows + BM - 1) / BM;
   const int width = group * gx, grp = pid / width, first = grp * group;
   const int gsz = min(gy - first, group);
   const int ti = first + (pid % width) % gsz, tj = (pid % width) / gsz;
@@ -197,16 +215,16 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
 
-  const int nk = (!A_KC && a.rows != nullptr ? __builtin_amdgcn_readfirstlane(*a.rows) : a.K) / BK;
+  const int nk = (!A_KC && la.rows != nullptr ? __builtin_amdgcn_readfirstlane(*la.rows) : la.K) / BK;
   // The operand pointers live in registers for the whole k loop (read through `a` they would be re-fetched from the
   // kernel-argument segment after every inline-assembly load, a scalar-memory round trip per slab).
-  const char* const pA = reinterpret_cast<const char*>(a.A);
-  const char* const pB = reinterpret_cast<const char*>(a.B);
-  const char* const pB2 = reinterpret_cast<const char*>(a.B2);
+  const char* const pA = reinterpret_cast<const char*>(la.A);
+  const char* const pB = reinterpret_cast<const char*>(la.B);
+  const char* const pB2 = reinterpret_cast<const char*>(la.B2);
   const int iters = (!DUAL && pB2 != nullptr) ? 2 * nk : nk;   // non-DUAL tiles contract with hi, then with lo
 
   // the GELU table's place: at the top, or at the bottom (and the staging of the epilogue above it) if the last slab is at the top
-  const bool look_up = T::TAB && a.act != GEMM_ACT_NONE;
+  const bool look_up = T::TAB && la.act != GEMM_ACT_NONE;
   const bool tab_low = (iters - 1) % NSTAGE == NSTAGE - 1;
   const int tab_at = tab_low ? 0 : T::LDS_MAIN - GELU_TAB_BYTES;
   const int lw = T::PW > 0 ? wave - WAVES : wave;            // number among the loading waves
@@ -214,11 +232,11 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
   // per-lane global offsets of this wave's loads
   uint32_t offA[T::NLA], offB[T::NLB];
 #pragma unroll
-  for (int q = 0; q < T::NLA; ++q) offA[q] = piece_offset<A_KC, BM, BK>((q * T::LW + lw) * 1024 + lane * 16, i0, Mrows, a.lda);
+  for (int q = 0; q < T::NLA; ++q) offA[q] = piece_offset<A_KC, BM, BK>((q * T::LW + lw) * 1024 + lane * 16, i0, Mrows, la.lda);
 #pragma unroll
-  for (int q = 0; q < T::NLB; ++q) offB[q] = piece_offset<B_KC, BN, BK>((q * T::LW + lw) * 1024 + lane * 16, j0, a.N, a.ldb);
-  const int64_t stepA = A_KC ? (int64_t)BK * 2 : (int64_t)BK * a.lda * 2;   // bytes per slab
-  const int64_t stepB = B_KC ? (int64_t)BK * 2 : (int64_t)BK * a.ldb * 2;
+  for (int q = 0; q < T::NLB; ++q) offB[q] = piece_offset<B_KC, BN, BK>((q * T::LW + lw) * 1024 + lane * 16, j0, la.N, la.ldb);
+  const int64_t stepA = A_KC ? (int64_t)BK * 2 : (int64_t)BK * la.lda * 2;   // bytes per slab
+  const int64_t stepB = B_KC ? (int64_t)BK * 2 : (int64_t)BK * la.ldb * 2;
 
   // Direct global -> LDS loads: lane l of a wave-level load lands at (m0) + 16 l.  Written as inline assembly so
   // that the only waits on them are the explicit vmcnt waits below.
@@ -314,7 +332,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
     for (int i = 0; i < iters; ++i) arrive(i);
     if constexpr (T::TAB) {
       if (look_up) {   // all slabs but the last have been read
-        const char* const tab = reinterpret_cast<const char*>(a.gelu_tab) + (a.act == GEMM_ACT_GELU_BWD ? GELU_TAB_BYTES : 0);
+        const char* const tab = reinterpret_cast<const char*>(la.gelu_tab) + (la.act == GEMM_ACT_GELU_BWD ? GELU_TAB_BYTES : 0);
 #pragma unroll
         for (int q = 0; q < (GELU_TAB_BYTES / 1024 + T::LW - 1) / T::LW; ++q) {
           const int piece = q * T::LW + lw;
