@@ -367,9 +367,11 @@ __device__ __forceinline__ void zero_tail(const RowPlan& plan, int B, bf16_t* __
   for (int c = threadIdx.x; c < n * 8; c += THREADS) *reinterpret_cast<uint4*>(out + (int64_t)(r0 + (c >> 3)) * ld + (c & 7) * 8) = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// Forward.  Four waves; wave w owns the query tiles w, w + 4, ... (32 queries each).  S^T[key][q] tiles leave each lane
-// with one query column, so the softmax over keys is an in-lane reduction plus one cross-half shuffle, and the
+// Forward.  A wave owns a tile of 32 queries (S = 64: two of the four waves only stage).  S^T[key][q] tiles leave each lane
+// with one query column, so the softmax over keys is an in-lane reduction plus one exchange between the halves, and the
 // probability tile is already in the B-operand layout of the 32x32x8 MFMA for O^T[e][q] = sum_key V^T[e][key] P^T[key][q].
+// With a loop over the tiles of a wave, even one that never turns, the 16 NT comparisons of keys with the length are kept as lane
+// masks across it, hundreds of scalar registers of which most spill.
 template <int NT>
 __device__ __forceinline__ void attn_scores(const RowsOperand& q, const bf16_t* __restrict__ Ks, int qt, int len, int nk,
                                             int lane, f32x16 (&s)[NT], float& inv, float* __restrict__ lse_row) {
@@ -385,21 +387,23 @@ __device__ __forceinline__ void attn_scores(const RowsOperand& q, const bf16_t* 
       s[kt][r] = (kt < nk && key < len) ? s[kt][r] * 0.125f : -3.0e38f;   // exp(-3e38 - mx) = 0: key 0 is always real
       mx = fmaxf(mx, s[kt][r]);
     }
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = join32(mx, [](float a, float b) { return fmaxf(a, b); });
   float sum = 0.f;
 #pragma unroll
   for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { s[kt][r] = __expf(s[kt][r] - mx); sum += s[kt][r]; }
-  sum += __shfl_xor(sum, 32, 64);
+  sum = join32(sum, [](float a, float b) { return a + b; });
   inv = 1.f / sum;
   if (lane < 32 && lse_row != nullptr) lse_row[32 * qt + lane] = mx + __logf(sum);
 }
 
+template <int NT> struct AttnFwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES; };
 template <int NT, bool PADDED>   // PADDED = false: no lengths given, the comparisons against len fold away
-__global__ __launch_bounds__(256) void k_attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
+__global__ __launch_bounds__(AttnFwd<NT>::THREADS) void k_attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
                                                   int heads, int d, const int32_t* __restrict__ lens, RowPlan plan, int B) {
-  constexpr int S = 32 * NT;
+  constexpr int S = 32 * NT, THREADS = AttnFwd<NT>::THREADS;
+  static_assert(NT <= AttnFwd<NT>::WAVES, "a tile of queries per wave");
   __shared__ __attribute__((aligned(16))) bf16_t Ks[S * AD];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[S * AD];
   const int h = blockIdx.x, b = blockIdx.y, pass = b / B, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -407,59 +411,50 @@ __global__ __launch_bounds__(256) void k_attn_fwd(const bf16_t* __restrict__ qkv
   const SeqRows sr = seq_rows<PADDED>(lens, plan, pass, b - pass * B, B, S);
   const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
   const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
-  if (PADDED && b == pass * B) zero_tail<256>(plan, B, out + (int64_t)pass * B * S * d + h * AD, d);
+  if (PADDED && b == pass * B) zero_tail<THREADS>(plan, B, out + (int64_t)pass * B * S * d + h * AD, d);
   float* lse_row = lse != nullptr ? lse + ((int64_t)b * heads + h) * S : nullptr;
-  // the queries of a tile are used by one wave only: from global memory, and those of a wave's first tile beside the staging
-  auto queries = [&](int qt) {
-    RowsOperand q;
-    const bf16_t* p = Q + (int64_t)(32 * qt + (lane & 31)) * ld + 8 * (lane >> 5);
+  const int qt = wave;
+  // the queries of a tile are used by one wave only: from global memory, beside the staging
+  RowsOperand q;
+  {
+    const bf16_t* p = Q + (int64_t)(32 * (qt < nq ? qt : 0) + (lane & 31)) * ld + 8 * (lane >> 5);
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) q.k[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-    return q;
-  };
+  }
+  stage_rows<THREADS, S>(Q + d, ld, kept, Ks);
+  stage_rows<THREADS, S>(Q + 2 * d, ld, kept, Vs);
+  __syncthreads();
+  if (qt >= nq) return;
   f32x16 s[NT];
   float inv = 0.f;
-  int qt = wave;
-  RowsOperand q = queries(qt < nq ? qt : 0);
-  stage_rows<256, S>(Q + d, ld, kept, Ks);
-  stage_rows<256, S>(Q + 2 * d, ld, kept, Vs);
-  __syncthreads();
-  if (qt < nq) attn_scores<NT>(q, Ks, qt, len, nk, lane, s, inv, lse_row);
-  while (qt < nq) {
-    f32x16 o[2];
+  attn_scores<NT>(q, Ks, qt, len, nk, lane, s, inv, lse_row);
+  f32x16 o[2];
 #pragma unroll
-    for (int et = 0; et < 2; ++et) {
+  for (int et = 0; et < 2; ++et) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[et][r] = 0.f;
+    for (int r = 0; r < 16; ++r) o[et][r] = 0.f;
 #pragma unroll
-      for (int kt = 0; kt < NT; ++kt) {
-        if (kt >= nk) break;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const s16x4 pb = pack4(s[kt][4 * c] * inv, s[kt][4 * c + 1] * inv, s[kt][4 * c + 2] * inv, s[kt][4 * c + 3] * inv);
-          const s16x4 va = ld_transposed(Vs, 32 * et, 32 * kt + 8 * c, lane);
-          o[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(va, pb, o[et], 0, 0, 0);
-        }
-      }
-    }
-    bf16_t* orow = out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD;
-    const bool there = !PADDED || 32 * qt + (lane & 31) < kept;
-#pragma unroll
-    for (int et = 0; et < 2; ++et)
+    for (int kt = 0; kt < NT; ++kt) {
+      if (kt >= nk) break;
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        if (!there) break;
-        uint2 pk;
-        pk.x = pack_bf16x2(o[et][4 * c], o[et][4 * c + 1]);
-        pk.y = pack_bf16x2(o[et][4 * c + 2], o[et][4 * c + 3]);
-        *reinterpret_cast<uint2*>(orow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
+        const s16x4 pb = pack4(s[kt][4 * c] * inv, s[kt][4 * c + 1] * inv, s[kt][4 * c + 2] * inv, s[kt][4 * c + 3] * inv);
+        const s16x4 va = ld_transposed(Vs, 32 * et, 32 * kt + 8 * c, lane);
+        o[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(va, pb, o[et], 0, 0, 0);
       }
-    qt += 4;
-    if (qt < nq) {
-      q = queries(qt);
-      attn_scores<NT>(q, Ks, qt, len, nk, lane, s, inv, lse_row);
     }
   }
+  if (PADDED && 32 * qt + (lane & 31) >= kept) return;
+  bf16_t* orow = out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD;
+#pragma unroll
+  for (int et = 0; et < 2; ++et)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      uint2 pk;
+      pk.x = pack_bf16x2(o[et][4 * c], o[et][4 * c + 1]);
+      pk.y = pack_bf16x2(o[et][4 * c + 2], o[et][4 * c + 3]);
+      *reinterpret_cast<uint2*>(orow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
+    }
 }
 
 // Backward.  Probabilities are recomputed from q, k and the saved log-sum-exp; a wave owns 32 queries or keys at a time.
@@ -818,16 +813,16 @@ void launch_attention_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* out, float*
   const dim3 grid(heads, nw * B);
   switch (S) {
     case 64:
-      if (lens) launch_kernel(ps, k_attn_fwd<2, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_fwd<2, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      if (lens) launch_kernel(ps, k_attn_fwd<2, true>, grid, AttnFwd<2>::THREADS, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_fwd<2, false>, grid, AttnFwd<2>::THREADS, 0, st, qkv, out, lse, heads, d, lens, plan, B);
       break;
     case 128:
-      if (lens) launch_kernel(ps, k_attn_fwd<4, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_fwd<4, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      if (lens) launch_kernel(ps, k_attn_fwd<4, true>, grid, AttnFwd<4>::THREADS, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_fwd<4, false>, grid, AttnFwd<4>::THREADS, 0, st, qkv, out, lse, heads, d, lens, plan, B);
       break;
     case 256:
-      if (lens) launch_kernel(ps, k_attn_fwd<8, true>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_fwd<8, false>, grid, 256, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      if (lens) launch_kernel(ps, k_attn_fwd<8, true>, grid, AttnFwd<8>::THREADS, 0, st, qkv, out, lse, heads, d, lens, plan, B);
+      else launch_kernel(ps, k_attn_fwd<8, false>, grid, AttnFwd<8>::THREADS, 0, st, qkv, out, lse, heads, d, lens, plan, B);
       break;
     default: break;   // make_encoder admits no other length
   }
