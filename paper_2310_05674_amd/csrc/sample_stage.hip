@@ -17,12 +17,14 @@
 // timing.  The + and the - pass of Eq. 5 are one launch (grid.y), and the last workgroup of that launch also combines them
 // and updates lambda.  Arithmetic is in double so that the +-eps difference of Eq. 5 is not lost to rounding.
 //
-// Measured against one workgroup per pass with a lane per sample and launches of their own for the head, the two passes, the
-// update of lambda and the step scalars (kernel durations in a trace): label correction with 203 samples, Hc = 64, 10 classes
-// 347 -> 21 us (base step) and 2 x 347 + 9 -> 43 us (both passes and the update); scoring 2048 samples 44 + 7 -> 8.5 us;
-// reweighting with 128 samples, H = 100: 13 + 8 -> 10 us and 2 x (13 + 8) + 5 -> 15 us.
-// Sums across lanes by vector instructions instead of shuffles through LDS, and the other workgroups' partials requested at once
-// instead of one or four at a time: a logistic-regression iteration (512 samples, H = 16; three stages) 62.2 -> 55.5 us.
+// What it costs is one chain of steps, each executed once: 0.5 us for a trip to memory that nothing runs beside, 0.5 to 1.5 us for
+// an exponential or logarithm in double with its code coming in, 2 us for the hand-over to the last workgroup.  So loads are
+// wide and without branches, what later steps need is requested before the head's operands, the corrector is converted to double
+// once, a lane works on four hidden units at a time, and the last workgroup requests all partials and the state of lambda at once.
+// us per launch (start of a kernel to that of the next), first with a load or a shuffle through LDS wherever one was needed, then as
+// it is: logistic regression, 512 samples, base step 10.6 -> 6.9, both passes and the update 17.9 -> 10.5; 128 samples of 256
+// features, H = 100 10.0 -> 8.3 and 15.1 -> 13.5; label correction, 203 samples, Hc = 64 19.8 -> 12.5 and 44.5 -> 29.9; an encoder's
+// text alone 13.4 -> 7.0, 32 texts 17.6 -> 11.6 and 27.4 -> 18.5.
 #include "common.h"
 #include "kernels.h"
 #include "mfma_f32.h"
@@ -36,38 +38,59 @@ constexpr int MAX_CORR = MAX_CORR_HIDDEN * 2 * MAX_CORR_CLASSES + MAX_CORR_HIDDE
 constexpr int CQ = 4;                        // classes per lane: up to 64 over sixteen lanes
 static_assert(ST_MAX_RUN == ST_SAMPLES && ST_SAMPLES == 32 && ST_THREADS == 64 * FWAVES, "one trip of 2 x 16 samples per workgroup");
 
+constexpr int HEAD_LDS = 8192;   // floats of LDS for the head
+static_assert(FWAVES * 32 * 17 <= HEAD_LDS, "partial tiles");
 // s_z[i][c] = logits of samples i_begin + i (two 16-row MFMA tiles), c < C: wave w takes every FWAVES-th chunk of the
-// contraction, requests four chunks at a time, and the partial tiles are added in wave order.  red: FWAVES x 32 x 17.
-__device__ void head_logits(const HeadView& h, int pass, int i_begin, int n_own, int C, float* __restrict__ red, double* __restrict__ s_z) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
-  const float* x = h.x + pass * h.pass_stride + i_begin * h.stride;
-  const float* W = h.pv.theta + h.w_off;
-  const float* Wv = h.pv.vdir + h.w_off;
+// contraction, requests four chunks at a time, and the partial tiles are added in wave order.
+__device__ __forceinline__ void head_logits(const HeadView& h, int pass, int i_begin, int n_own, int C, float* __restrict__ red, double* __restrict__ s_z) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = lane & 15, q = lane >> 4;
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
   const float s = pass == 0 ? h.pv.scale() : -h.pv.scale();
-  const bool x_vec = (h.stride & 3) == 0 && ((uintptr_t)x & 15) == 0;
-  const bool w_vec = (h.k & 3) == 0 && (((uintptr_t)W | (s != 0.f ? (uintptr_t)Wv : 0)) & 15) == 0;
-  constexpr int DEPTH = 4;
+  // rows and classes beyond the end are clamped: their products are not read
+  const float* const x0 = h.x + pass * h.pass_stride + (int64_t)(i_begin + min(r, n_own - 1)) * h.stride;
+  const float* const x1 = h.x + pass * h.pass_stride + (int64_t)(i_begin + min(16 + r, n_own - 1)) * h.stride;
+  constexpr int DEPTH = 4, STEP = FWAVES * FCH;
+  const int nfull = h.k / FCH, n = nfull > wave ? (nfull - wave + FWAVES - 1) / FWAVES : 0;
+  const bool tail = h.k % FCH != 0 && nfull % FWAVES == wave;
   for (int c0 = 0; c0 < C; c0 += 16) {
+    const int own_c = c0 + (threadIdx.x & 15);
+    const float bias = h.pv.at(h.b_off + min(own_c, C - 1), s);
+    const int64_t wrow = h.w_off + (int64_t)min(c0 + r, C - 1) * h.k;
+    const float* const W = h.pv.theta + wrow;
+    const float* const Wv = h.pv.vdir + wrow;
     float4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    for (int kb = wave * FCH; kb < h.k; kb += DEPTH * FWAVES * FCH) {
-      float4v av[DEPTH][2], bv[DEPTH], pv[DEPTH];
+    auto multiply = [&](const float4v& a0, const float4v& a1, const float4v& bw, const float4v& bp) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float b = s != 0.f ? fmaf(s, bp[c], bw[c]) : bw[c];
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[c], b, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[c], b, acc[1], 0, 0, 0);
+      }
+    };
+    for (int i = 0; i < n; i += DEPTH) {
+      float4v a0[DEPTH], a1[DEPTH], bw[DEPTH], bp[DEPTH];
 #pragma unroll
       for (int u = 0; u < DEPTH; ++u) {
-        const int k = kb + u * FWAVES * FCH + 4 * q;      // a chunk beyond the end reads as zeros
-        av[u][0] = load_k4(x, h.stride, 1, r, n_own, k, h.k, x_vec);
-        av[u][1] = load_k4(x, h.stride, 1, 16 + r, n_own, k, h.k, x_vec);
-        bv[u] = load_k4(W, h.k, 1, c0 + r, C, k, h.k, w_vec);
-        if (s != 0.f) pv[u] = load_k4(Wv, h.k, 1, c0 + r, C, k, h.k, w_vec);
+        if (i + u >= n) break;
+        const int k = wave * FCH + (i + u) * STEP + 4 * q;
+        a0[u] = *reinterpret_cast<const f4u*>(x0 + k);
+        a1[u] = *reinterpret_cast<const f4u*>(x1 + k);
+        bw[u] = *reinterpret_cast<const f4u*>(W + k);
+        bp[u] = s != 0.f ? *reinterpret_cast<const f4u*>(Wv + k) : bw[u];
       }
 #pragma unroll
-      for (int u = 0; u < DEPTH; ++u) {
+      for (int u = 0; u < DEPTH; ++u)
+        if (i + u < n) multiply(a0[u], a1[u], bw[u], bp[u]);
+    }
+    if (tail) {
+      float4v t[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float b = s != 0.f ? fmaf(s, pv[u][c], bv[u][c]) : bv[u][c];
-          acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][0][c], b, acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][1][c], b, acc[1], 0, 0, 0);
-        }
+      for (int c = 0; c < 4; ++c) {
+        const int k = nfull * FCH + 4 * q + c, kk = min(k, h.k - 1);
+        t[0][c] = k < h.k ? x0[kk] : 0.f; t[1][c] = k < h.k ? x1[kk] : 0.f;
+        t[2][c] = k < h.k ? W[kk] : 0.f; t[3][c] = k < h.k && s != 0.f ? Wv[kk] : 0.f;
       }
+      multiply(t[0], t[1], t[2], t[3]);
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -76,60 +99,75 @@ __device__ void head_logits(const HeadView& h, int pass, int i_begin, int n_own,
     __syncthreads();
     {
       const int i = threadIdx.x >> 4, c = threadIdx.x & 15;   // 512 threads: one of the 32 x 16 outputs each
-      if (c0 + c < C) {
-        double z = (double)h.pv.at(h.b_off + c0 + c, s);
+      if (own_c < C) {
+        double z = (double)bias;
 #pragma unroll
         for (int w = 0; w < FWAVES; ++w) z += (double)red[(w * 32 + i) * 17 + c];
-        s_z[i * 64 + c0 + c] = z;
+        s_z[i * 64 + own_c] = z;
       }
     }
-    __syncthreads();
+    if (c0 + 16 < C) __syncthreads();
   }
 }
 
 // The same with a wave per sample: 64 strided partial sums in fp32, joined by a shuffle tree.  The losses of the two passes of
 // Eq. 5 differ in their last digits only, and a deep model's gradients follow those of its logits, so what the
 // encoder's logits are rounded to is kept independent of how a workgroup's tiles split the features.
-// Up to four samples of a wave and four classes share each element of W that is read.
-template <bool PERTURBED>
-__device__ void head_dots(const HeadView& h, int pass, int i_begin, int n_own, int C, double* __restrict__ s_z) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// W, as the pass sees it, comes through LDS, CU classes and 1024 features at a time, and a wave has that many features of its
+// samples in registers: one trip to memory.  What is beyond the features or classes is zero.
+template <int SU>
+__device__ __forceinline__ void head_dots(const HeadView& h, int pass, int i_begin, int n_own, int C, float* __restrict__ s_w, double* __restrict__ s_z) {
+  constexpr int CU = 8, KB = HEAD_LDS / CU, KT = KB / 64, WT = KB / ST_THREADS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float s = pass == 0 ? h.pv.scale() : -h.pv.scale();
-  constexpr int CU = 4, SU = ST_SAMPLES / FWAVES;   // sample wave + FWAVES u of the workgroup's is this wave's u-th
-  const float* x[SU];
+  const float* x[SU];   // sample wave + FWAVES u of the workgroup's is this wave's u-th
 #pragma unroll
   for (int u = 0; u < SU; ++u) {
     const int i = i_begin + min(wave + FWAVES * u, n_own - 1);
     x[u] = h.x + pass * h.pass_stride + (h.start != nullptr ? (int64_t)h.start[i] * h.k : (int64_t)i * h.stride);
   }
-  if (wave < n_own) {
-    for (int c0 = 0; c0 < C; c0 += CU) {
-      float acc[SU][CU] = {};
-#pragma unroll 8
-      for (int k = lane; k < h.k; k += 64) {
-        float w[CU], xk[SU];
+  for (int c0 = 0; c0 < C; c0 += CU) {
+    const float bias = h.pv.at(h.b_off + min(c0 + (lane & (CU - 1)), C - 1), s);   // of class c0 + lane
+    float acc[SU][CU] = {};
+    for (int k0 = 0; k0 < h.k; k0 += KB) {
+      const int nk = min(KB, h.k - k0);
+      float xk[SU][KT], w[CU][WT];
 #pragma unroll
-        for (int c = 0; c < CU; ++c) {
-          const int64_t o = h.w_off + (int64_t)min(c0 + c, C - 1) * h.k + k;
-          w[c] = PERTURBED ? fmaf(s, h.pv.vdir[o], h.pv.theta[o]) : h.pv.theta[o];
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int u = 0; u < SU; ++u) xk[u][t] = 64 * t + lane < nk ? x[u][k0 + 64 * t + lane] : 0.f;
+#pragma unroll
+      for (int c = 0; c < CU; ++c)
+#pragma unroll
+        for (int t = 0; t < WT; ++t) {
+          const int k = t * ST_THREADS + tid;
+          w[c][t] = c0 + c < C && k < nk ? h.pv.at(h.w_off + (int64_t)(c0 + c) * h.k + k0 + k, s) : 0.f;
         }
+      if (c0 + k0 > 0) __syncthreads();
 #pragma unroll
-        for (int u = 0; u < SU; ++u) xk[u] = x[u][k];
+      for (int c = 0; c < CU; ++c)
 #pragma unroll
-        for (int u = 0; u < SU; ++u)
+        for (int t = 0; t < WT; ++t) s_w[c * KB + t * ST_THREADS + tid] = w[c][t];
+      __syncthreads();
 #pragma unroll
-          for (int c = 0; c < CU; ++c) acc[u][c] = fmaf(xk[u], w[c], acc[u][c]);
-      }
-#pragma unroll
-      for (int u = 0; u < SU; ++u)
+      for (int t = 0; t < KT; ++t)
 #pragma unroll
         for (int c = 0; c < CU; ++c) {
-          const float z = wave_sum(acc[u][c]);
-          if (lane == 0 && c0 + c < C && wave + FWAVES * u < n_own) s_z[(wave + FWAVES * u) * 64 + c0 + c] = (double)(z + h.pv.at(h.b_off + c0 + c, s));
+          const float w = s_w[c * KB + 64 * t + lane];
+#pragma unroll
+          for (int u = 0; u < SU; ++u) acc[u][c] = fmaf(xk[u][t], w, acc[u][c]);
         }
     }
+#pragma unroll
+    for (int c = 0; c < CU; ++c) {
+      const float b = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(bias), c));
+#pragma unroll
+      for (int u = 0; u < SU; ++u) {
+        const float z = wave_sum(acc[u][c]);
+        if (lane == 0 && wave + FWAVES * u < n_own && c0 + c < C) s_z[(wave + FWAVES * u) * 64 + c0 + c] = (double)(z + b);
+      }
+    }
   }
-  __syncthreads();
 }
 
 // every lane of a group of sixteen gets the sum / maximum over the group
@@ -149,53 +187,94 @@ __device__ __forceinline__ double block_sum_d(double x, double* red) {
 
 // h = -(glam+ - glam-) / (2 eps); then (optionally) Adam on lambda.  A raised status word (counters[2]) or a
 // hypergradient with a non-finite component zeroes h and skips the update; the latter raises the status word itself.
-// glam+ / glam- are the sums of the workgroups' partials in order.
-constexpr int COLLECT = 16;
-__device__ void meta_update(const MetaUpdateArgs& a, const double* part, int nblk) {
+// glam+ / glam- are the sums of the workgroups' partials in order.  A load of one takes a microsecond: a thread requests those of
+// EL components and KC workgroups at once, and everything else it will need beside them.  One chunk of EL * ST_THREADS
+// components stays in registers from the sums to the update; where there are more, the sums are read back.
+template <int EL, int KC>
+__device__ __forceinline__ void meta_update(const MetaUpdateArgs& a, const double* part, int nblk) {
+  const int tid = threadIdx.x;
   const float eps = a.scalars[0];
+  const int64_t t = a.counters[1] + 1;
   bool skip = (a.counters[2] != 0) || !(eps > 0.f);
+  const bool one = a.nl <= EL * ST_THREADS;
   int bad = 0;
-  for (int i = threadIdx.x; i < a.nl; i += ST_THREADS) {
-    double gp = 0.0, gm = 0.0;
-    for (int k0 = 0; k0 < nblk; k0 += COLLECT) {   // a load of each takes a microsecond: COLLECT workgroups' at once
-      double p[COLLECT], m[COLLECT];
+  double gp[EL], gm[EL], c1 = 0.0, c2 = 0.0;
+  float m0[EL], v0[EL], l0[EL];
+  auto state = [&](int i0) {
 #pragma unroll
-      for (int u = 0; u < COLLECT; ++u) {
-        p[u] = k0 + u < nblk ? collect(part + (int64_t)(k0 + u) * a.nl + i) : 0.0;
-        m[u] = k0 + u < nblk ? collect(part + (int64_t)(nblk + k0 + u) * a.nl + i) : 0.0;
+    for (int e = 0; e < EL; ++e) {
+      const int i = i0 + e * ST_THREADS;
+      m0[e] = v0[e] = l0[e] = 0.f;
+      if (a.do_update && i < a.nl) { m0[e] = a.meta_m[i]; v0[e] = a.meta_v[i]; l0[e] = a.lambda[i]; }
+    }
+  };
+  for (int i0 = tid; i0 < a.nl; i0 += EL * ST_THREADS) {
+    if (one) state(i0);
+#pragma unroll
+    for (int e = 0; e < EL; ++e) gp[e] = gm[e] = 0.0;
+    for (int k0 = 0; k0 < nblk; k0 += KC) {
+      double p[KC][EL], m[KC][EL];
+#pragma unroll
+      for (int u = 0; u < KC; ++u)
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+          const bool there = k0 + u < nblk && i0 + e * ST_THREADS < a.nl;
+          const double* q = part + (int64_t)(k0 + u) * a.nl + i0 + e * ST_THREADS;
+          p[u][e] = there ? collect(q) : 0.0;
+          m[u][e] = there ? collect(q + (int64_t)nblk * a.nl) : 0.0;
+        }
+      if (k0 == 0 && i0 == tid) {   // beside the first loads
+        c1 = 1.0 / (1.0 - ipow((double)a.beta1, t));
+        c2 = 1.0 / sqrt(1.0 - ipow((double)a.beta2, t));
       }
 #pragma unroll
-      for (int u = 0; u < COLLECT; ++u) { gp += p[u]; gm += m[u]; }
+      for (int u = 0; u < KC; ++u)
+#pragma unroll
+        for (int e = 0; e < EL; ++e) { gp[e] += p[u][e]; gm[e] += m[u][e]; }
     }
-    a.glam_p[i] = gp; a.glam_m[i] = gm;
-    if (!skip) {
-      const double h = -(gp - gm) / (2.0 * (double)eps);
-      if (!(fabs(h) <= 3.0e38)) bad = 1;   // NaN, infinite, or beyond what the fp32 outputs hold
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+      const int i = i0 + e * ST_THREADS;
+      if (i >= a.nl) break;
+      a.glam_p[i] = gp[e]; a.glam_m[i] = gm[e];
+      if (!skip) {
+        const double h = -(gp[e] - gm[e]) / (2.0 * (double)eps);
+        if (!(fabs(h) <= 3.0e38)) bad = 1;   // NaN, infinite, or beyond what the fp32 outputs hold
+      }
     }
   }
-  const int64_t t = a.counters[1] + 1;
   if (__syncthreads_or(bad)) {   // every thread has read counters[2] above
     skip = true;
-    if (threadIdx.x == 0) a.counters[2] = 1;
+    if (tid == 0) a.counters[2] = 1;
   }
-  const double c1 = 1.0 / (1.0 - ipow((double)a.beta1, t));
-  const double c2 = 1.0 / sqrt(1.0 - ipow((double)a.beta2, t));
-  for (int i = threadIdx.x; i < a.nl; i += ST_THREADS) {
-    const double gp = a.glam_p[i], gm = a.glam_m[i];   // written by this thread above
-    const double h = skip ? 0.0 : -(gp - gm) / (2.0 * (double)eps);
-    a.hypergrad[i] = (float)h;
-    if (a.hypergrad_user) a.hypergrad_user[i] = (float)h;
-    a.glam_p_f32[i] = (float)gp;
-    a.glam_m_f32[i] = (float)gm;
-    if (a.do_update && !skip) {
-      const double m = (double)a.beta1 * a.meta_m[i] + (1.0 - (double)a.beta1) * h;
-      const double v = (double)a.beta2 * a.meta_v[i] + (1.0 - (double)a.beta2) * h * h;
-      a.meta_m[i] = (float)m;
-      a.meta_v[i] = (float)v;
-      a.lambda[i] = (float)((double)a.lambda[i] - (double)a.lr * c1 * m / (c2 * sqrt(v) + (double)a.eps));
+  for (int i0 = tid; i0 < a.nl; i0 += EL * ST_THREADS) {
+    if (!one) {
+      state(i0);
+#pragma unroll
+      for (int e = 0; e < EL; ++e) {   // written by this thread above
+        const int i = i0 + e * ST_THREADS;
+        gp[e] = i < a.nl ? a.glam_p[i] : 0.0; gm[e] = i < a.nl ? a.glam_m[i] : 0.0;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+      const int i = i0 + e * ST_THREADS;
+      if (i >= a.nl) break;
+      const double h = skip ? 0.0 : -(gp[e] - gm[e]) / (2.0 * (double)eps);
+      a.hypergrad[i] = (float)h;
+      if (a.hypergrad_user) a.hypergrad_user[i] = (float)h;
+      a.glam_p_f32[i] = (float)gp[e];
+      a.glam_m_f32[i] = (float)gm[e];
+      if (a.do_update && !skip) {
+        const double m = (double)a.beta1 * m0[e] + (1.0 - (double)a.beta1) * h;
+        const double v = (double)a.beta2 * v0[e] + (1.0 - (double)a.beta2) * h * h;
+        a.meta_m[i] = (float)m;
+        a.meta_v[i] = (float)v;
+        a.lambda[i] = (float)((double)l0[e] - (double)a.lr * c1 * m / (c2 * sqrt(v) + (double)a.eps));
+      }
     }
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     if (a.eps_user) *a.eps_user = skip ? 0.f : eps;
     if (a.do_update && !skip) a.counters[1] = t;
   }
@@ -210,10 +289,12 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
   __shared__ float s_lam[3 * MAX_WNET_HIDDEN + 1];
   __shared__ double red[ST_THREADS / 64];
   __shared__ int s_last;
-  __shared__ float s_hred[FWAVES * 32 * 17];
+  __shared__ double s_a[ST_SAMPLES * MAX_CORR_HIDDEN];   // relu(a_ij); before that, the head's
+  static_assert(sizeof(s_a) >= HEAD_LDS * sizeof(float), "the head's share");
+  float* const s_head = reinterpret_cast<float*>(s_a);
   __shared__ double s_z[ST_SAMPLES * 64];
-  __shared__ float s_lc[CORR ? MAX_CORR : 1];
-  __shared__ double s_a[CORR ? ST_SAMPLES * MAX_CORR_HIDDEN : 1], s_t[CORR ? ST_SAMPLES * MAX_CORR_HIDDEN : 1];   // relu(a_ij), dL/da_ij
+  __shared__ double s_lc[CORR ? MAX_CORR : 1];           // the corrector, converted once
+  __shared__ double s_t[CORR ? ST_SAMPLES * MAX_CORR_HIDDEN : 1];   // dL/da_ij
   __shared__ double s_p[CORR ? ST_SAMPLES * MAX_CORR_CLASSES : 1], s_ds[CORR ? ST_SAMPLES * MAX_CORR_CLASSES : 1];
   __shared__ int s_y[CORR ? ST_SAMPLES : 1];
   const int tid = threadIdx.x, lane = tid & (ST_LANES - 1), grp = tid / ST_LANES, H = a.H, B = a.B, C = a.C;
@@ -227,10 +308,25 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
   const float* pos_loss = a.pos_loss + pass * a.pos_pass_stride;
   float* losses = pass == (int)gridDim.y - 1 ? a.losses : nullptr;   // of the most recent pass
 
-  for (int i = tid; i < 3 * H + 1; i += ST_THREADS) s_lam[i] = a.lambda[i];
+  // What the samples' steps will need is requested before the head's operands, and put in place behind the head.
+  const bool weighs = a.mode != STAGE_META;             // the clean batch has unit weights
+  float lam[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) lam[u] = weighs && tid + u * ST_THREADS < 3 * H + 1 ? a.lambda[tid + u * ST_THREADS] : 0.f;
+  static_assert(3 * MAX_WNET_HIDDEN + 1 <= 2 * ST_THREADS, "two parameters a thread");
+  const int i_own = min(i_begin + grp, i_end - 1);      // one trip: ST_SAMPLES samples at most
+  const int y_own = seq_mode ? 0 : a.y[i_own];
+  const bool masked_out = a.mask != nullptr && a.mask[i_own] == 0;
   const int nlc = Hc > 0 ? Hc * 2 * C + Hc + C * Hc + C : 0;
   if (CORR)
-    for (int i = tid; i < nlc; i += ST_THREADS) s_lc[i] = a.lambda[3 * H + 1 + i];
+    for (int i = tid; i < nlc; i += 4 * ST_THREADS) {
+      float t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = i + u * ST_THREADS < nlc ? a.lambda[3 * H + 1 + i + u * ST_THREADS] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i + u * ST_THREADS < nlc) s_lc[i + u * ST_THREADS] = (double)t[u];
+    }
   double beff = (double)B;
   if (a.mask != nullptr) {
     double cnt = 0.0;
@@ -238,15 +334,18 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
     beff = block_sum_d(cnt, red);
   }
   const double inv_beff = beff > 0.0 ? 1.0 / beff : 0.0;
-  __syncthreads();
   if (!seq_mode) {
-    if (a.head.dots && a.head.pv.scale() != 0.f) head_dots<true>(a.head, pass, i_begin, n_own, C, s_z);
-    else if (a.head.dots) head_dots<false>(a.head, pass, i_begin, n_own, C, s_z);
-    else head_logits(a.head, pass, i_begin, n_own, C, s_hred, s_z);
+    if (!a.head.dots) head_logits(a.head, pass, i_begin, n_own, C, s_head, s_z);
+    else if (n_own <= FWAVES) head_dots<1>(a.head, pass, i_begin, n_own, C, s_head, s_z);
+    else head_dots<ST_SAMPLES / FWAVES>(a.head, pass, i_begin, n_own, C, s_head, s_z);
   }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (tid + u * ST_THREADS < 3 * H + 1) s_lam[tid + u * ST_THREADS] = lam[u];
+  __syncthreads();
   const float* W1 = s_lam; const float* b1 = s_lam + H; const float* W2 = s_lam + 2 * H;
   const double b2 = (double)s_lam[3 * H];
-  const float* W1c = s_lc; const float* b1c = s_lc + Hc * 2 * C; const float* W2c = b1c + Hc; const float* b2c = W2c + C * Hc;
+  const double* W1c = s_lc; const double* b1c = s_lc + Hc * 2 * C; const double* W2c = b1c + Hc; const double* b2c = W2c + C * Hc;
 
   if (seq_mode) {
     // wave w takes sequences w, w + waves, ...: its lanes stride over the positions (coalesced), keep the matching losses,
@@ -265,15 +364,17 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
   }
   double lsum = 0.0;
   constexpr int PAIRS = CORR ? (MAX_CORR_HIDDEN * MAX_CORR_CLASSES + ST_THREADS - 1) / ST_THREADS : 1;
-  double gW2[PAIRS], gWp[PAIRS], gWy[PAIRS], gb1[PAIRS], gb2[PAIRS];   // corrector backward: thread owns (hidden unit, class) pairs
+  double gW2[PAIRS], gWp[PAIRS], gWy[PAIRS], gb2[PAIRS], gb1 = 0.0;   // corrector backward: thread owns (hidden unit, class) pairs
+  const int pair_step = CORR ? min(ST_THREADS / Hc, C) : 1, pair_j = CORR ? tid % Hc : 0, pair_k = CORR ? tid / Hc : 0;
 #pragma unroll
-  for (int u = 0; u < PAIRS; ++u) gW2[u] = gWp[u] = gWy[u] = gb1[u] = gb2[u] = 0.0;
+  for (int u = 0; u < PAIRS; ++u) gW2[u] = gWp[u] = gWy[u] = gb2[u] = 0.0;
 
-  for (int i0 = i_begin; i0 < i_end; i0 += ST_SAMPLES) {   // every thread takes part in every trip (barriers with CORR)
-    const int i = i0 + grp;
+  static_assert(ST_MAX_RUN <= ST_SAMPLES, "one trip");
+  do {                                                    // every thread takes part (barriers with CORR)
+    const int i = i_begin + grp;
     const bool live = i < i_end;
-    const int ic = live ? i : i_end - 1;
-    const double mk = (live && (a.mask == nullptr || a.mask[ic] != 0)) ? 1.0 : 0.0;
+    const int ic = i_own;
+    const double mk = live && !masked_out ? 1.0 : 0.0;
     double l, lse = 0.0, zc[CQ] = {0.0, 0.0, 0.0, 0.0};
     int yi = 0;
     double cs = 0.0;                                      // corrected soft label of class `lane` (Hc > 0)
@@ -281,7 +382,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
       l = s_l[ic - i_begin];
     } else {
       const double* z = s_z + (ic - i_begin) * 64;
-      yi = min(max(a.y[ic], 0), C - 1);   // labels outside [0, C) are clamped
+      yi = min(max(y_own, 0), C - 1);   // labels outside [0, C) are clamped
 #pragma unroll
       for (int q = 0; q < CQ; ++q) zc[q] = lane + ST_LANES * q < C ? z[lane + ST_LANES * q] : -1.0e300;
       const double zy = z[yi];
@@ -302,24 +403,51 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
         s_p[grp * MAX_CORR_CLASSES + lane] = p;
         if (lane == 0) s_y[grp] = yi;
         __syncthreads();
+        // A lane takes four hidden units and four classes at a time, so that its LDS reads and chains of additions overlap; units and
+        // classes beyond the end add zeros.
         double sc[MAX_CORR_CLASSES];
 #pragma unroll
         for (int k = 0; k < MAX_CORR_CLASSES; ++k) sc[k] = 0.0;
-        for (int j = lane; j < Hc; j += ST_LANES) {
-          double aj = (double)b1c[j] + (double)W1c[j * 2 * C + yi];
-          for (int k = 0; k < C; ++k) aj += (double)W1c[j * 2 * C + C + k] * s_p[grp * MAX_CORR_CLASSES + k];
-          aj = aj > 0.0 ? aj : 0.0;
-          s_a[grp * MAX_CORR_HIDDEN + j] = aj;
+        for (int j0 = lane; j0 - lane < Hc; j0 += 4 * ST_LANES) {
+          int jj[4];
+          double aj[4];
 #pragma unroll
-          for (int k = 0; k < MAX_CORR_CLASSES; ++k)
-            if (k < C) sc[k] += (double)W2c[k * Hc + j] * aj;
+          for (int u = 0; u < 4; ++u) {
+            jj[u] = min(j0 + u * ST_LANES, Hc - 1);
+            aj[u] = b1c[jj[u]] + W1c[jj[u] * 2 * C + yi];
+          }
+          for (int k0 = 0; k0 < C; k0 += 4) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const int k = min(k0 + v, C - 1);
+              const double pk = k0 + v < C ? s_p[grp * MAX_CORR_CLASSES + k] : 0.0;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) aj[u] += (k0 + v < C ? W1c[jj[u] * 2 * C + C + k] : 0.0) * pk;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const bool there = j0 + u * ST_LANES < Hc;
+            aj[u] = there && aj[u] > 0.0 ? aj[u] : 0.0;
+            if (there) s_a[grp * MAX_CORR_HIDDEN + jj[u]] = aj[u];
+          }
+#pragma unroll
+          for (int k0 = 0; k0 < MAX_CORR_CLASSES; k0 += 4) {
+            if (k0 >= C) break;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+              for (int u = 0; u < 4; ++u) sc[k0 + v] += (j0 + u * ST_LANES < Hc ? W2c[min(k0 + v, C - 1) * Hc + jj[u]] : 0.0) * aj[u];
+          }
         }
         double s_own = 0.0;
 #pragma unroll
-        for (int k = 0; k < MAX_CORR_CLASSES; ++k) {
-          if (k < C) {   // the same for every lane
-            const double tot = sum16(sc[k]);
-            if (k == lane) s_own = tot + (double)b2c[k] + (k == yi ? (double)a.kappa : 0.0);
+        for (int k0 = 0; k0 < MAX_CORR_CLASSES; k0 += 4) {
+          if (k0 >= C) break;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const double tot = sum16(sc[k0 + v]);
+            if (k0 + v == lane && own) s_own = tot + b2c[lane] + (lane == yi ? (double)a.kappa : 0.0);
           }
         }
         const double smax = max16(own ? s_own : -1.0e300);
@@ -338,10 +466,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
       w = 1.0 / (1.0 + exp(-(sum16(zz) + b2)));
     }
     if (a.weights != nullptr && live && lane == 0) a.weights[i] = (float)w;
-    if (a.mode == STAGE_EVAL) {
-      if (CORR) __syncthreads();                          // s_p is rewritten by the next trip
-      continue;
-    }
+    if (a.mode == STAGE_EVAL) return;
     const double coef = mk * w * inv_beff;
     if (a.mode == STAGE_GLAM) {
       if (live && lane == 0) { s_l[i - i_begin] = l; s_dz[i - i_begin] = w * (1.0 - w) * l * mk * inv_beff; }
@@ -351,27 +476,45 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
         const double dot = sum16(cs * dc), ds = cs * (dc - dot);
         s_ds[grp * MAX_CORR_CLASSES + lane] = ds;
         __syncthreads();
-        for (int j = lane; j < Hc; j += ST_LANES) {
-          double t = 0.0;
-          for (int k = 0; k < C; ++k) t += (double)W2c[k * Hc + j] * s_ds[grp * MAX_CORR_CLASSES + k];
-          s_t[grp * MAX_CORR_HIDDEN + j] = s_a[grp * MAX_CORR_HIDDEN + j] > 0.0 ? t : 0.0;
+        for (int j0 = lane; j0 - lane < Hc; j0 += 4 * ST_LANES) {
+          int jj[4];
+          double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) jj[u] = min(j0 + u * ST_LANES, Hc - 1);
+          for (int k0 = 0; k0 < C; k0 += 4) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const int k = min(k0 + v, C - 1);
+              const double dk = k0 + v < C ? s_ds[grp * MAX_CORR_CLASSES + k] : 0.0;
+#pragma unroll
+              for (int u = 0; u < 4; ++u) t[u] += (k0 + v < C ? W2c[k * Hc + jj[u]] : 0.0) * dk;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (j0 + u * ST_LANES < Hc) s_t[grp * MAX_CORR_HIDDEN + jj[u]] = s_a[grp * MAX_CORR_HIDDEN + jj[u]] > 0.0 ? t[u] : 0.0;
         }
         __syncthreads();
-        const int ns = min(ST_SAMPLES, i_end - i0);
+        // thread: hidden unit pair_j, classes pair_k, pair_k + pair_step, ...; it shares what it reads of the unit between them
+        if (pair_k < pair_step) {
+          const int last = C - 1;
+#pragma unroll 4
+          for (int s = 0; s < n_own; ++s) {
+            const double aj = s_a[s * MAX_CORR_HIDDEN + pair_j], t = s_t[s * MAX_CORR_HIDDEN + pair_j];
+            const int ys = s_y[s];
 #pragma unroll
-        for (int u = 0; u < PAIRS; ++u) {
-          const int pr = tid + u * ST_THREADS, j = pr % Hc, k = pr / Hc;
-          if (k >= C) continue;
-          for (int s = 0; s < ns; ++s) {
-            const double aj = s_a[s * MAX_CORR_HIDDEN + j], t = s_t[s * MAX_CORR_HIDDEN + j], d = s_ds[s * MAX_CORR_CLASSES + k];
-            gW2[u] += d * aj;
-            gWp[u] += t * s_p[s * MAX_CORR_CLASSES + k];
-            gWy[u] += s_y[s] == k ? t : 0.0;
-            gb1[u] += t;      // kept by the pairs with k == 0
-            gb2[u] += d;      // kept by the pairs with j == 0
+            for (int u = 0; u < PAIRS; ++u) {
+              if (u * pair_step >= C) break;   // the same for every thread
+              const int k = min(pair_k + u * pair_step, last);
+              const double d = s_ds[s * MAX_CORR_CLASSES + k];
+              gW2[u] += d * aj;
+              gWp[u] += t * s_p[s * MAX_CORR_CLASSES + k];
+              gWy[u] += ys == k ? t : 0.0;
+              gb2[u] += d;      // kept for pair_j == 0
+            }
+            gb1 += t;           // kept for pair_k == 0
           }
         }
-        __syncthreads();
       }
     } else if (seq_mode) {
       if (lane == 0) {
@@ -388,10 +531,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
           a.dlogits[(int64_t)i * C + c] = (float)(coef * (exp(zc[q] - lse) - target));
         }
       }
-      if (CORR) __syncthreads();
     }
-  }
-  if (a.mode == STAGE_EVAL) return;
+  } while (false);
 
   const int total = nblk * gridDim.y;      // workgroups whose partials make the result
   if (a.mode != STAGE_GLAM) {
@@ -452,19 +593,23 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
   if (tid == 0) publish(glam + 3 * H, db2);
   if (CORR) {
     double* gc = glam + 3 * H + 1;
+    const int j = pair_j;
+    if (pair_k < pair_step) {
 #pragma unroll
-    for (int u = 0; u < PAIRS; ++u) {
-      const int pr = tid + u * ST_THREADS, j = pr % Hc, k = pr / Hc;
-      if (k >= C) continue;
-      publish(gc + j * 2 * C + k, gWy[u]);
-      publish(gc + j * 2 * C + C + k, gWp[u]);
-      publish(gc + Hc * 2 * C + Hc + k * Hc + j, gW2[u]);
-      if (k == 0) publish(gc + Hc * 2 * C + j, gb1[u]);
-      if (j == 0) publish(gc + Hc * 2 * C + Hc + C * Hc + k, gb2[u]);
+      for (int u = 0; u < PAIRS; ++u) {
+        const int k = pair_k + u * pair_step;
+        if (k >= C) break;
+        publish(gc + j * 2 * C + k, gWy[u]);
+        publish(gc + j * 2 * C + C + k, gWp[u]);
+        publish(gc + Hc * 2 * C + Hc + k * Hc + j, gW2[u]);
+        if (j == 0) publish(gc + Hc * 2 * C + Hc + C * Hc + k, gb2[u]);
+      }
+      if (pair_k == 0) publish(gc + Hc * 2 * C + j, gb1);
     }
   }
   if (!last_block(a.ticket, total, &s_last)) return;
-  meta_update(a.mu, a.part, nblk);
+  if (CORR) meta_update<5, 4>(a.mu, a.part, nblk);   // lambda is that of the corrector for the most part
+  else meta_update<1, 16>(a.mu, a.part, nblk);
 }
 }  // namespace
 

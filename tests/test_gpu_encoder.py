@@ -743,3 +743,21 @@ def test_eval_of_a_text_does_not_depend_on_what_is_scored_beside_it(S, fast, pad
     gpu.base_step(dev_batch(gpu, x, y, lens=lens))
     assert np.array_equal(pull(gpu, "LOSSES")[:B], every[1])
     gpu.close()
+
+
+@pytest.mark.parametrize("C,d", [(8, 192), (9, 192), (21, 1088)])
+def test_head_of_many_classes_and_features(C, d):
+    """The classifier with as many classes as are taken at a time, one more, and three times as many over more features than are:
+    a text alone (a wave) and among eleven others (two samples to a wave), bit for bit; the logits against the oracle."""
+    import torch
+    wl = make_workload(3, n_train=12, n_meta=2, dims=(1, d, d // 64, 128, 64, 300, C), batch=12, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.05), init_lambda(wl), base_lr=1e-3)
+    x, y = wl.x_train[:12], wl.y_train[:12]
+    push_state(orc, gpu)
+    out = [[torch.zeros(s, device=gpu.dev) for s in ((n, C), (n,), (n,))] for n in (12, 1)]
+    gpu.eval(dev_batch(gpu, x, y), *out[0])
+    gpu.eval(dev_batch(gpu, x[:1], y[:1]), *out[1])
+    for all_, one in zip(*out):
+        assert torch.equal(all_[:1], one)
+    assert rel_l2(out[0][0].cpu().numpy(), orc.evaluate(x, y)[0]) < KTOL
+    gpu.close()

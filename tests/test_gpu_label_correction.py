@@ -107,3 +107,32 @@ def test_label_correction_small_encoder_bf16():
         assert e["h_r"] < 2e-2 and e["h_c"] < 2e-2, e
         assert e["theta"] < 2e-2 and e["lam"] < 2e-2
     gpu.close()
+
+
+@pytest.mark.parametrize("C,Hc,B", [(2, 1, 33), (3, 7, 5), (5, 17, 31), (9, 64, 203), (16, 100, 40), (16, 128, 70)])
+def test_corrector_sizes(C, Hc, B):
+    """Numbers of classes and hidden units below, at and beyond what a lane and a thread of the stage take at a time (four of each
+    forwards; Hc threads to a class backwards): losses, gradient, both parts of the lambda-gradient and its update."""
+    from datagen import CounterRNG
+    from datagen.workloads import Workload
+    d, H, r = 16, 9, CounterRNG(300 + C + Hc + B)
+    wl = Workload(cfg=0, kind="mlp", dims=(d, C), bf16=False, H=H, batch=B, meta_batch=9, base_lr=1e-2, meta_lr=1e-3, alpha=0.5,
+                  noise=0.0, n_train=B, n_meta=9, steps=1)
+    x = r.normal(1, B * d).reshape(B, d).astype(np.float32); y = r.integers(2, B, C).astype(np.int32)
+    xm = r.normal(3, 9 * d).reshape(9, d).astype(np.float32); ym = r.integers(4, 9, C).astype(np.int32)
+    n_corr = Hc * 2 * C + Hc + C * Hc + C
+    th0 = (0.4 * r.normal(5, d * C + C)).astype(np.float32).astype(np.float64)
+    lam0 = np.concatenate([r.normal(6, 3 * H + 1), 0.5 * r.normal(7, n_corr)]).astype(np.float32).astype(np.float64)
+    orc, gpu = make_pair(wl, th0, lam0, base_opt="sgd", corr_hidden=Hc, corr_kappa=1.0)
+    l_want = orc.model.losses(orc.theta, x, orc.targets(orc.theta, x, y))
+    orc.base_step(x, y); gpu.base_step(dev_batch(gpu, x, y))
+    assert np.max(np.abs(pull(gpu, "LOSSES")[:B] - l_want)) < 1e-5 * max(1.0, np.max(l_want))
+    assert rel_l2(pull(gpu, "G"), orc.g) < 1e-4
+    push_state(orc, gpu)
+    rr = orc.meta_step(x, y, xm, ym); gpu.meta_step(dev_batch(gpu, x, y), dev_batch(gpu, xm, ym))
+    nr = 3 * H + 1
+    for name, want in (("GLAM_PLUS", rr["glam_p"]), ("GLAM_MINUS", rr["glam_m"])):
+        got = pull(gpu, name)
+        assert rel_l2(got[:nr], want[:nr]) < 1e-5 and rel_l2(got[nr:], want[nr:]) < 1e-5, name
+    assert rel_l2(pull(gpu, "LAMBDA"), orc.lam) < 1e-6
+    gpu.close()
