@@ -6,11 +6,17 @@
 #include "model.h"
 
 namespace sama {
-static bool g_side_stream = true, g_side_sink = true;
-void encoder_side_stream(bool on) { g_side_stream = on; }
+static int g_side_stream = -1;   // the rule below; 0 never, 1 always
+static bool g_side_sink = true;
+void encoder_side_stream(int mode) { g_side_stream = mode; }
 void encoder_side_sink(bool on) { g_side_sink = on; }
 namespace {
-inline bool side_enabled() { return g_side_stream; }
+// Whether a backward pass over `rows` token rows puts a layer's weight gradients and what follows them on the second stream.  What the
+// chain's kernels leave of the chip is worth it once they are long: the events between the streams cost two microseconds each.
+// ms per iteration of two base steps, 4 layers, one stream / two, by rows x parameters of a layer: 0.9e9 (512 x 384 wide) 1.84 / 2.04,
+// 3.2e9 (4096 x 256) 2.55 / 2.58, 3.6e9 (2048 x 384) 2.52 / 2.63, 3.6e9 (512 x 768) 3.17 / 3.16, 6.4e9 (2048 x 512) 3.23 / 3.20,
+// 7.2e9 (4096 x 384) 3.60 / 3.57, 12.9e9 (4096 x 512) 4.53 / 4.41, 29e9 (4096 x 768) 7.36 / 7.11.
+inline bool side_wanted(int64_t rows, int64_t layer_params) { return g_side_stream >= 0 ? g_side_stream != 0 : rows * layer_params >= 5000000000ll; }
 
 struct LayerOff { int64_t Wqkv, Wo, W1, W2, bqkv, bo, ln1g, ln1b, b1, b2, ln2g, ln2b; };
 
@@ -271,7 +277,7 @@ class EncoderModel : public Model {
     // depends on them, and the chain's launches (small dgrad tiles, LayerNorm, attention) leave room on the CUs.
     // Their inputs alternate between two buffer sets; the chain waits for the launches of two layers ago before it
     // overwrites a set, and the pass ends with both streams joined.
-    const bool two = side_enabled() && ensure_side();
+    const bool two = side_wanted(M, (int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_) && ensure_side();
     hipStream_t ss = two ? side_ : st;
     bool sink_used = false;
     for (int l = L_ - 1; l >= 0; --l) {
@@ -351,15 +357,17 @@ class EncoderModel : public Model {
     launch_embedding_bwd(st, ds32_, (const int32_t*)b.x, B, S_, d_, V_, grad + tok_, grad + pos_, rp);
   }
 
-  // second stream (default priority, created at the first backward pass) and the events that order it
+  // second stream (default priority, created at the first backward pass that wants it) and the events that order it.  Both streams
+  // are this GPU's and no host reads anything by these events, so they go without the system-scope fence, which writes the caches
+  // back in the middle of the chain: 4 x 256 iteration 1967 -> 1923 us, 24 x 1024 29.42 -> 29.31 ms.
   bool ensure_side() {
     if (side_ != nullptr) return true;
     if (side_failed_) return false;
     bool ok = hipStreamCreateWithFlags(&side_, hipStreamNonBlocking) == hipSuccess;
     for (int p = 0; p < 2 && ok; ++p)
-      ok = hipEventCreateWithFlags(&ev_chain_[p], hipEventDisableTiming) == hipSuccess &&
-           hipEventCreateWithFlags(&ev_side_[p], hipEventDisableTiming) == hipSuccess &&
-           hipEventCreateWithFlags(&ev_last_[p], hipEventDisableTiming) == hipSuccess;
+      ok = hipEventCreateWithFlags(&ev_chain_[p], hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess &&
+           hipEventCreateWithFlags(&ev_side_[p], hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess &&
+           hipEventCreateWithFlags(&ev_last_[p], hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess;
     if (!ok) { release_side(); side_failed_ = true; (void)hipGetLastError(); }
     return ok;
   }
