@@ -462,21 +462,28 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS) void k_attn_fwd(const bf16_t*
 //   dK: dS[q][key]   -> dK^T[e][key] = sum_q Q^T[e][q] dS[q][key]
 //   dV: P[q][key]    -> dV^T[e][key] = sum_q dO^T[e][q] P[q][key]
 // dS = P (dP - D) / 8 with D[q] = sum_e dO[q][e] O[q][e].
-// Each of the three is a workgroup of its own (blockIdx.z): it stages the two matrices it walks over, and its waves hold the
-// rows of their own tile and 32 accumulators.  The scores are formed three times instead of twice, but three workgroups share a CU
-// (S = 64 and 128, by their 137 to 146 registers; two of eight waves at S = 256, by 67.6 KB of LDS) where one that formed all three,
-// with 64 KB and 167 registers, had it alone: 384 heads of 128 positions were one and a half rounds of 16 us.  At S = 256 the 128
-// registers of eight waves to a workgroup leave 8 or 9 values in scratch; 384 heads 96 -> 59 us all the same.
-template <int NT> struct AttnBwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES, PER_SIMD = NT < 8 ? 3 : 4; };
-template <int NT, bool PADDED>
-__global__ __launch_bounds__(AttnBwd<NT>::THREADS, AttnBwd<NT>::PER_SIMD) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
+// A workgroup (blockIdx.z) forms one of the three, or (PARTS 2) dQ or the other two: it stages the two matrices it walks over, and
+// its waves hold the rows of their own tile and 32 or 64 accumulators.  Bound by the latency of a tile's chain (LDS, product,
+// exponentials, product) and by the requests for the rows it stages and holds.
+//   Three parts: the scores are formed three times instead of twice, but 3 to 4 workgroups share a CU (35 KB of LDS at S = 128, at most
+//   128 registers; 2 of eight waves at S = 256, with 68 KB) where one that formed all three, with 64 KB, had it alone.
+//   Two parts: a round of three workgroups to a CU instead of four, with a longer chain each (12 heads of S = 128: 9.8 us against
+//   6.8), so only once there are more heads than CUs: S = 128, 384 heads 18.6 us against 19.1 and, padded, 17.5 against 20.7;
+//   1024 heads 50.3 against 53.3, padded 36.7 against 39.1.  256 heads 13.7 against 12.2, 128 10.8 against 8.6.  At S = 64 the two are
+//   equal; at S = 256 the registers leave one workgroup to a CU (padded 52 against 47 us).
+// A wave has one tile and no loop around it: with one, the padded forms kept lane masks and eight-wave forms values across it in
+// scratch (384 heads, S = 128 padded 22.0 -> 20.7 us; S = 256 52 -> 48 us, padded 52 -> 47 us).
+// The own rows and D's are fetched behind the staged ones, whose lines they share: ahead of them, with 2 or 32 lines to an
+// instruction each, they held those up (384 heads 20.8 -> 24.4 us).
+template <int NT, bool PADDED, int PARTS>
+__global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
                                                                       const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                                       bf16_t* __restrict__ dqkv, int heads, int d, const int32_t* __restrict__ lens,
                                                                       RowPlan plan, int B) {
-  constexpr int S = 32 * NT, WAVES = AttnBwd<NT>::WAVES, THREADS = AttnBwd<NT>::THREADS;
-  enum { DK = 0, DQ = 1, DV = 2 };
-  __shared__ __attribute__((aligned(16))) bf16_t s_r[S * AD];   // dQ: K, dK and dV: Q
-  __shared__ __attribute__((aligned(16))) bf16_t s_t[S * AD];   // dQ: V, dK and dV: dO
+  constexpr int S = 32 * NT, THREADS = 64 * NT;
+  enum { DK = 0, DQ = 1, DV = 2 };   // of two parts the first is both dK and dV
+  __shared__ __attribute__((aligned(16))) bf16_t s_r[S * AD];   // dQ: K; dK and dV: Q
+  __shared__ __attribute__((aligned(16))) bf16_t s_t[S * AD];   // dQ: V; dK and dV: dO
   __shared__ float s_D[S], s_lse[S];
   const int h = blockIdx.x, b = blockIdx.y, part = blockIdx.z, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t ld = 3 * (int64_t)d;
@@ -485,8 +492,10 @@ __global__ __launch_bounds__(AttnBwd<NT>::THREADS, AttnBwd<NT>::PER_SIMD) void k
   const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
   const bf16_t* O = out + (int64_t)sr.row0 * d + h * AD;
   const bf16_t* dO = dout + (int64_t)sr.row0 * d + h * AD;
-  const int to = part == DQ ? 0 : (part == DK ? d : 2 * d);      // where the result goes among the columns of dqkv
-  if (PADDED && b == 0) zero_tail<THREADS>(plan, B, dqkv + to + h * AD, ld);
+  if (PADDED && b == 0) {
+    zero_tail<THREADS>(plan, B, dqkv + (part == DQ ? 0 : (part == DK ? d : 2 * d)) + h * AD, ld);
+    if (PARTS == 2 && part != DQ) zero_tail<THREADS>(plan, B, dqkv + 2 * d + h * AD, ld);
+  }
   // rows 32 tile + lane % 32 of a matrix, as rows_operand() would give them
   auto own_rows = [&](const bf16_t* X, int64_t stride, int tile) {
     RowsOperand o;
@@ -507,86 +516,92 @@ __global__ __launch_bounds__(AttnBwd<NT>::THREADS, AttnBwd<NT>::PER_SIMD) void k
     const int q = t >> 1, half = t & 1;
     const bool there = !PADDED || q < kept;
     float acc = 0.f;
-    if (part != DV) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (!there) break;
-        const uint4 o4 = *reinterpret_cast<const uint4*>(O + (int64_t)q * d + half * 32 + 8 * i);
-        const uint4 d4 = *reinterpret_cast<const uint4*>(dO + (int64_t)q * d + half * 32 + 8 * i);
-        const uint32_t ow[4] = {o4.x, o4.y, o4.z, o4.w}, dw[4] = {d4.x, d4.y, d4.z, d4.w};
+    for (int i = 0; i < 4; ++i) {
+      if (!there || (PARTS == 3 && part == DV)) break;
+      const uint4 o4 = *reinterpret_cast<const uint4*>(O + (int64_t)q * d + half * 32 + 8 * i);
+      const uint4 d4 = *reinterpret_cast<const uint4*>(dO + (int64_t)q * d + half * 32 + 8 * i);
+      const uint32_t ow[4] = {o4.x, o4.y, o4.z, o4.w}, dw[4] = {d4.x, d4.y, d4.z, d4.w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e)
-          acc = fmaf(bf16_to_f32((bf16_t)(ow[e >> 1] >> ((e & 1) * 16))), bf16_to_f32((bf16_t)(dw[e >> 1] >> ((e & 1) * 16))), acc);
-      }
-      acc += __shfl_xor(acc, 1, 64);
+      for (int e = 0; e < 8; ++e)
+        acc = fmaf(bf16_to_f32((bf16_t)(ow[e >> 1] >> ((e & 1) * 16))), bf16_to_f32((bf16_t)(dw[e >> 1] >> ((e & 1) * 16))), acc);
     }
+    acc += __shfl_xor(acc, 1, 64);
     if (half == 0) { s_D[q] = acc; s_lse[q] = there ? lse[((int64_t)b * heads + h) * S + q] : 0.f; }
   }
   __syncthreads();
 
-  for (int own = wave; own < nq; own += WAVES) {                   // tile of queries (dQ) or keys
-    f32x16 g[2];
+  if (wave >= nq) return;                                          // a wave owns a tile of queries (dQ) or keys
+  const int own = wave;
+  f32x16 g[2], gv[2];                                            // dQ, or dK and dV
+#pragma unroll
+  for (int et = 0; et < 2; ++et)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) g[et][r] = gv[et][r] = 0.f;
+  const int col = 32 * own + (lane & 31);                        // this lane's query or key
+  // g^T[e][own] += sum over the 32 rows of `tile` of T^T[e][row] w[row][own]
+  auto accumulate = [&](f32x16 (&g)[2], const bf16_t* T, int tile, const f32x16& w) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const s16x4 wb = pack4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]);
+#pragma unroll
+      for (int et = 0; et < 2; ++et)
+        g[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(T, 32 * et, 32 * tile + 8 * c, lane), wb, g[et], 0, 0, 0);
+    }
+  };
+  if (part == DQ) {
+    const float lq = s_lse[col], Dq = s_D[col];
+    const RowsOperand qop = own_rows(Q, ld, own), dop = own_rows(dO, d, own);
+#pragma unroll 1
+    for (int kt = 0; kt < nk; ++kt) {
+      f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * kt, lane), qop);          // S^T[key][q]
+      const f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * kt, lane), dop);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = 32 * kt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        st[r] = !PADDED || key < len ? __expf(st[r] * 0.125f - lq) * (dp[r] - Dq) * 0.125f : 0.f;   // dS^T; a padded key has P = 0
+      }
+      accumulate(g, s_r, kt, st);
+    }
+  } else if (PARTS == 3 && part == DV) {
+    if (own < nk) {
+      const RowsOperand kop = own_rows(Q + d, ld, own);
+#pragma unroll 1
+      for (int qt = 0; qt < nq; ++qt) {
+        f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+          st[r] = !PADDED || q < kept ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
+        }
+        accumulate(g, s_t, qt, st);
+      }
+    }
+  } else if (own < nk) {                                         // otherwise keys without weight
+    const RowsOperand kop = own_rows(Q + d, ld, own), vop = own_rows(Q + 2 * d, ld, own);
+#pragma unroll 1
+    for (int qt = 0; qt < nq; ++qt) {
+      f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);          // S[q][key]
+      f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * qt, lane), vop);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+        const bool on = !PADDED || q < kept;
+        st[r] = on ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;                    // P
+        dp[r] = on ? st[r] * (dp[r] - s_D[q]) * 0.125f : 0.f;                    // dS
+      }
+      if constexpr (PARTS == 2) accumulate(gv, s_t, qt, st);
+      accumulate(g, s_r, qt, dp);
+    }
+  }
+  if (PADDED && part != DQ && col >= len) {                      // a key without weight
 #pragma unroll
     for (int et = 0; et < 2; ++et)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) g[et][r] = 0.f;
-    const int col = 32 * own + (lane & 31);                        // this lane's query or key
-    // g^T[e][own] += sum over the 32 rows of `tile` of T^T[e][row] w[row][own]
-    auto accumulate = [&](const bf16_t* T, int tile, const f32x16& w) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const s16x4 wb = pack4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]);
-#pragma unroll
-        for (int et = 0; et < 2; ++et)
-          g[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(T, 32 * et, 32 * tile + 8 * c, lane), wb, g[et], 0, 0, 0);
-      }
-    };
-    if (part == DQ) {
-      const float lq = s_lse[col], Dq = s_D[col];
-      const RowsOperand qop = own_rows(Q, ld, own), dop = own_rows(dO, d, own);
-#pragma unroll 1
-      for (int kt = 0; kt < nk; ++kt) {
-        f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * kt, lane), qop);          // S^T[key][q]
-        const f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * kt, lane), dop);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = 32 * kt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          st[r] = key < len ? __expf(st[r] * 0.125f - lq) * (dp[r] - Dq) * 0.125f : 0.f;   // dS^T; a padded key has P = 0
-        }
-        accumulate(s_r, kt, st);
-      }
-    } else if (own < nk) {                                         // otherwise keys without weight
-      const bool real_key = col < len;
-      const RowsOperand kop = own_rows(Q + d, ld, own);
-      if (part == DK) {
-        const RowsOperand vop = own_rows(Q + 2 * d, ld, own);
-#pragma unroll 1
-        for (int qt = 0; qt < nq; ++qt) {
-          f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);        // S[q][key]
-          const f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * qt, lane), vop);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            const bool on = real_key && (!PADDED || q < kept);
-            const float p = on ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
-            st[r] = on ? p * (dp[r] - s_D[q]) * 0.125f : 0.f;
-          }
-          accumulate(s_r, qt, st);
-        }
-      } else {
-#pragma unroll 1
-        for (int qt = 0; qt < nq; ++qt) {
-          f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            st[r] = (real_key && (!PADDED || q < kept)) ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
-          }
-          accumulate(s_t, qt, st);
-        }
-      }
-    }
-    if (PADDED && col >= kept) continue;
+      for (int r = 0; r < 16; ++r) g[et][r] = gv[et][r] = 0.f;
+  }
+  if (PADDED && col >= kept) return;
+  auto store = [&](const f32x16 (&g)[2], int to) {   // to: where the result goes among the columns of dqkv
     bf16_t* row = dqkv + ((int64_t)sr.row0 + col) * ld + to + h * AD;
 #pragma unroll
     for (int et = 0; et < 2; ++et)
@@ -597,7 +612,9 @@ __global__ __launch_bounds__(AttnBwd<NT>::THREADS, AttnBwd<NT>::PER_SIMD) void k
         pk.y = pack_bf16x2(g[et][4 * c + 2], g[et][4 * c + 3]);
         *reinterpret_cast<uint2*>(row + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
       }
-  }
+  };
+  store(g, part == DQ ? 0 : (part == DK ? d : 2 * d));
+  if (PARTS == 2 && part != DQ) store(gv, 2 * d);
 }
 
 // =========================================================================================== classifier head
@@ -830,20 +847,17 @@ void launch_attention_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* out, float*
 void launch_attention_bwd(hipStream_t st, const bf16_t* qkv, const bf16_t* out, const bf16_t* dout, const float* lse,
                           bf16_t* dqkv, int B, int S, int heads, int d, const int32_t* lens, const RowPlan& plan) {
   ProfScope ps(st, F_ATTN_BWD, 10.0 * B * heads * (double)S * S * 64.0);
-  const dim3 grid(heads, B, 3);
+  auto launch = [&](auto tiles, auto parts) {
+    constexpr int NT = decltype(tiles)::value, PARTS = decltype(parts)::value;
+    auto kernel = lens ? k_attn_bwd<NT, true, PARTS> : k_attn_bwd<NT, false, PARTS>;
+    launch_kernel(ps, kernel, dim3(heads, B, PARTS), 64 * NT, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
+  };
+  const std::integral_constant<int, 2> two;
+  const std::integral_constant<int, 3> three;
   switch (S) {
-    case 64:
-      if (lens) launch_kernel(ps, k_attn_bwd<2, true>, grid, AttnBwd<2>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_bwd<2, false>, grid, AttnBwd<2>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      break;
-    case 128:
-      if (lens) launch_kernel(ps, k_attn_bwd<4, true>, grid, AttnBwd<4>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_bwd<4, false>, grid, AttnBwd<4>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      break;
-    case 256:
-      if (lens) launch_kernel(ps, k_attn_bwd<8, true>, grid, AttnBwd<8>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      else launch_kernel(ps, k_attn_bwd<8, false>, grid, AttnBwd<8>::THREADS, 0, st, qkv, out, dout, lse, dqkv, heads, d, lens, plan, B);
-      break;
+    case 64: launch(two, three); break;
+    case 128: (int64_t)heads * B > 256 ? launch(std::integral_constant<int, 4>(), two) : launch(std::integral_constant<int, 4>(), three); break;
+    case 256: launch(std::integral_constant<int, 8>(), three); break;
     default: break;
   }
 }

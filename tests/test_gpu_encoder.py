@@ -525,6 +525,24 @@ def test_other_sequence_lengths(S, padded, B):
     gpu.close()
 
 
+@pytest.mark.parametrize("B,padded", [(32, False), (32, True), (33, False), (33, True)])
+def test_attention_backward_on_both_sides_of_its_parts(B, padded):
+    """256 heads of 128 positions take the backward pass in three parts, 264 in two: a base step against the oracle."""
+    wl = make_workload(3, n_train=2 * B, n_meta=4, dims=(1, 512, 8, 512, 128, 600, 3), batch=B, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.05), init_lambda(wl), base_lr=1e-3)
+    (x, y), _ = _batches(wl, 0)
+    lens = seq_lengths(wl.seed + 7, B, 128)
+    lens[:4] = 1, 128, 32, 33
+    push_state(orc, gpu)
+    orc.base_step(with_lengths(x, lens) if padded else x, y)
+    gpu.base_step(dev_batch(gpu, x, y, lens=lens if padded else None))
+    g = pull(gpu, "G")
+    errs = _group_errors(orc, g, orc.g)
+    print(f"B={B} padded={padded}: rel-L2 g {rel_l2(g, orc.g):.3e}; worst group {max(errs, key=errs.get)} {max(errs.values()):.3e}")
+    assert rel_l2(g, orc.g) < KTOL and all(e < TOL for e in errs.values()), errs
+    gpu.close()
+
+
 def test_out_of_range_ids_and_labels_are_clamped():
     """Token ids outside [0, V) and labels outside [0, C) are clamped on the device by every kernel that indexes with
     them (embedding gather, token-gradient scatter, per-sample stage): a batch carrying such values gives the bits of
