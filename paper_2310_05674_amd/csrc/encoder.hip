@@ -12,11 +12,13 @@ void encoder_side_stream(int mode) { g_side_stream = mode; }
 void encoder_side_sink(bool on) { g_side_sink = on; }
 namespace {
 // Whether a backward pass over `rows` token rows puts a layer's weight gradients and what follows them on the second stream.  What the
-// chain's kernels leave of the chip is worth it once they are long: the events between the streams cost two microseconds each.
-// ms per iteration of two base steps, 4 layers, one stream / two, by rows x parameters of a layer: 0.9e9 (512 x 384 wide) 1.84 / 2.04,
-// 3.2e9 (4096 x 256) 2.55 / 2.58, 3.6e9 (2048 x 384) 2.52 / 2.63, 3.6e9 (512 x 768) 3.17 / 3.16, 6.4e9 (2048 x 512) 3.23 / 3.20,
-// 7.2e9 (4096 x 384) 3.60 / 3.57, 12.9e9 (4096 x 512) 4.53 / 4.41, 29e9 (4096 x 768) 7.36 / 7.11.
-inline bool side_wanted(int64_t rows, int64_t layer_params) { return g_side_stream >= 0 ? g_side_stream != 0 : rows * layer_params >= 5000000000ll; }
+// chain's kernels leave of the chip is worth it once they are long and many: the events between the streams cost the host, which
+// short kernels wait for, and the pass some ten microseconds at its end.
+// us per iteration of one base step, two streams / one, by rows x parameters of the layers: 0.9e9 (512 rows, 2 x 192) 617 / 587,
+// 4.8e9 (1024, 12 x 192) 3003 / 2923, 4.8e9 (512, 12 x 256) 3142 / 2961, 6.4e9 (2048, 4 x 256) 1320 / 1311, 7.2e9 (4096, 4 x 192)
+// 1488 / 1557, 10e9 (512, 12 x 384) 3668 / 3619, 13e9 (4096, 4 x 256) 1634 / 1705, 15e9 (1024, 4 x 576) 1792 / 1815, 19e9 (2048,
+// 12 x 256) 3794 / 3940, 46e9 (1024, 12 x 576) 5350 / 5546.
+inline bool side_wanted(int64_t rows, int64_t params) { return g_side_stream >= 0 ? g_side_stream != 0 : rows * params >= 7000000000ll; }
 
 struct LayerOff { int64_t Wqkv, Wo, W1, W2, bqkv, bo, ln1g, ln1b, b1, b2, ln2g, ln2b; };
 
@@ -277,7 +279,7 @@ class EncoderModel : public Model {
     // depends on them, and the chain's launches (small dgrad tiles, LayerNorm, attention) leave room on the CUs.
     // Their inputs alternate between two buffer sets; the chain waits for the launches of two layers ago before it
     // overwrites a set, and the pass ends with both streams joined.
-    const bool two = side_wanted(M, (int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_) && ensure_side();
+    const bool two = side_wanted(M, L_ * ((int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_)) && ensure_side();
     hipStream_t ss = two ? side_ : st;
     bool sink_used = false;
     for (int l = L_ - 1; l >= 0; --l) {
@@ -338,6 +340,7 @@ class EncoderModel : public Model {
           {cspart_[p][0], nrb, ffn_, 0, ffn_, {grad + o.b1, nullptr, nullptr}, cs, ck, gr, cg},
           {cspart_[p][1], nrb, 3 * d_, 0, 3 * d_, {grad + o.bqkv, nullptr, nullptr}, 0, 0, rp.group, cg}};
       launch_reduce_rows_multi(ss, rj, 4);
+      if (two && l == L_ - 1) launch_fill_f32(side_, grad + tok_, 0.f, (int64_t)V_ * d_);   // for the scatter at the end
       if (two) { (void)hipEventRecord(ev_side_[p], side_); side_busy_[p] = true; }
       if (sink_now) {   // this layer's gradients are final (matrices and vectors are one range each); a consumer may
         (void)hipStreamWaitEvent(side_, ev_last_[p], 0);   // overwrite the layer's weights once its last dgrad has read them
@@ -347,14 +350,18 @@ class EncoderModel : public Model {
       }
     }
     if (sink_used) { (void)hipEventRecord(ev_side_[0], side_); side_busy_[0] = true; }   // join behind the consumer's work too
-    for (int p = 0; p < 2; ++p)
-      if (two && side_busy_[p]) { (void)hipStreamWaitEvent(st, ev_side_[p], 0); side_busy_[p] = false; }
-    LnBwdArgs n0{dx, pre0_, mean0_, rstd0_, w.theta + eg_, ds32_, nullptr, lnpart_[0][0], M, d_, rp.rows};
+    // The embeddings need nothing of the last layer's side launches, which end beside them (4 x 256 iteration 1735 -> 1634 us, 12 x 768
+    // of 512 rows 6403 -> 6367): only what used lnpart_[1] is waited for first, and with one layer the cleared token rows.
+    auto join = [&](int p) { if (two && side_busy_[p]) { (void)hipStreamWaitEvent(st, ev_side_[p], 0); side_busy_[p] = false; } };
+    join(1);
+    if (L_ == 1) join(0);
+    LnBwdArgs n0{dx, pre0_, mean0_, rstd0_, w.theta + eg_, ds32_, nullptr, lnpart_[1][0], M, d_, rp.rows};
     launch_ln_bwd(st, n0);
-    const ReduceRowsJob r0{lnpart_[0][0], M / LN_BWD_ROWS, 3 * d_, d_, d_, {grad + eg_, grad + eb_, nullptr}, 0, 0, rp.group, ROW_GROUP / LN_BWD_ROWS};
+    const ReduceRowsJob r0{lnpart_[1][0], M / LN_BWD_ROWS, 3 * d_, d_, d_, {grad + eg_, grad + eb_, nullptr}, 0, 0, rp.group, ROW_GROUP / LN_BWD_ROWS};
     launch_reduce_rows_multi(st, &r0, 1);
-    launch_fill_f32(st, grad + tok_, 0.f, (int64_t)V_ * d_);
+    if (!two) launch_fill_f32(st, grad + tok_, 0.f, (int64_t)V_ * d_);
     launch_embedding_bwd(st, ds32_, (const int32_t*)b.x, B, S_, d_, V_, grad + tok_, grad + pos_, rp);
+    join(0);
   }
 
   // second stream (default priority, created at the first backward pass that wants it) and the events that order it.  Both streams
