@@ -124,18 +124,37 @@ class EncoderModel : public Model {
     return s;
   }
 
+  // The next weights for the LayerNorm of a pass over `rows` rows to fetch, where that pays: the products of few rows are bound by weights
+  // that come from memory, and a LayerNorm leaves most of its bandwidth unused.  With the rows of a long product there is
+  // time for both, and fetching ahead only delays the LayerNorm; and what the last-level cache (256 MB) holds from one pass to the
+  // next needs no fetching: when scoring, the two halves of the weights; in training, with the optimizer's state, 20 bytes each.
+  // Without / with it, 12 x 768: scoring 128 rows 676 / 644 us, 512 825 / 735, 2048 1378 / 1251, 4096 1900 / 1897; base step of 1024
+  // rows 2964 / 2820, 2048 3869 / 3670, 4096 5519 / 5547, 4096 padded 4832 / 4728.  24 x 1024: base step of 512 rows 6754 / 6519, 2048 10697 / 10676.
+  // The stacked passes count their rows together (24 x 1024 iteration of 1024 rows with / without them 19.56 / 19.28 ms, 12 x 768 of 1024 7.15 /
+  // 7.24).  Scoring with 12 x 576 (177 MB) 699 / 708, base step of 2048 rows of 8 x 384 (260 MB with the state) 1358 / 1317.
+  WeightsAhead weights_ahead(const PassWeights* w, int nw, bool scoring, int64_t off, int64_t n, int rows, const int32_t* in_use) const {
+    WeightsAhead a{};
+    a.max_rows = (2 << 20) / (nw * d_);
+    const int64_t params = L_ * ((int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_);
+    if (params * (scoring ? 4 : 20) < 256000000 || (in_use == nullptr && rows >= a.max_rows)) return a;
+    for (int k = 0; k < nw; ++k) { a.p[2 * k] = w[k].hi + off; a.p[2 * k + 1] = w[k].lo != nullptr ? w[k].lo + off : nullptr; }
+    a.n = n;
+    return a;
+  }
+
   // nw = 1: one pass with weights w[0].  nw = 2: the theta + eps v and theta - eps v passes of Eq. 5 on the same
   // batch, stacked along the row dimension (forward only, keep must be false).
   HeadView run_forward(hipStream_t st, const PassWeights* w, int nw, const sama_batch& b, bool keep, const MlmBatch* mb) {
     const int B = b.n, M = B * S_;
     const RowSelect sel = select(b, keep, mb);
     const RowPlan rp = b.seq_len != nullptr ? plan_ : RowPlan{};   // a padded batch: only the rows that matter
+    const bool scoring = nw == 1 && !keep;
     if (b.seq_len != nullptr) launch_row_plan(st, (const int32_t*)b.x, b.seq_len, B, S_, mb ? masked(b, *mb) : RowSelect{}, rp);
     ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};   // flips behind the first pass's rows
     LnFwdArgs e{};
     e.x = nullptr; e.ids = rp.ids ? rp.ids : (const int32_t*)b.x; e.src = rp.src; e.rows = rp.rows; e.pass_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep ? pre0_ : nullptr;
     e.pv = pv; e.g_off = eg_; e.b_off = eb_; e.y = X_[0]; e.y32 = res_[0]; e.mean = keep ? mean0_ : nullptr; e.rstd = keep ? rstd0_ : nullptr;
-    e.M = nw * M; e.d = d_;
+    e.M = nw * M; e.d = d_; e.ahead = weights_ahead(w, nw, scoring, off_[0].Wqkv, (int64_t)4 * d_ * d_, M, rp.rows);
     launch_ln_fwd(st, e);
     for (int l = 0; l < L_; ++l) {
       const int s = keep ? l : 0;                       // activation slot: forward-only passes reuse slot 0
@@ -159,6 +178,7 @@ class EncoderModel : public Model {
       LnFwdArgs n1{};
       n1.x = pre1_[s]; n1.pv = pv; n1.g_off = o.ln1g; n1.b_off = o.ln1b; n1.y = x1_[s]; n1.y32 = res_[1];
       n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
+      n1.ahead = weights_ahead(w, nw, scoring, o.W1, (int64_t)2 * ffn_ * d_, rows, in_use);
       launch_ln_fwd(st, n1);
       g = GemmBf16Args{};
       g.act = GEMM_ACT_GELU_FWD; g.gelu_tab = gelu_tab_; g.C16_pre = keep ? fpre_[s] : nullptr; g.C16 = fact_[s];   // only a backward pass reads the pre-activation
@@ -169,6 +189,7 @@ class EncoderModel : public Model {
       LnFwdArgs n2{};
       n2.x = pre2_[s]; n2.pv = pv; n2.g_off = o.ln2g; n2.b_off = o.ln2b; n2.y = xout; n2.y32 = res_[0];
       n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = nw * rows; n2.d = d_; n2.pass_rows = rows; n2.rows = in_use;
+      if (l + 1 < L_) n2.ahead = weights_ahead(w, nw, scoring, off_[l + 1].Wqkv, (int64_t)4 * d_ * d_, M, rp.rows);
       launch_ln_fwd(st, n2);
     }
     HeadView h{};                                   // position 0 of the fp32 output of the last LayerNorm
@@ -288,11 +309,12 @@ class EncoderModel : public Model {
       if (two && side_busy_[p]) { (void)hipStreamWaitEvent(st, ev_side_[p], 0); side_busy_[p] = false; }
       bf16_t* const ds2 = ds16_[p][0]; bf16_t* const ds1 = ds16_[p][1]; bf16_t* const dpre = dpre_[p]; bf16_t* const dqkv = dqkv_[p];
       GemmBf16Args wg[4];
+      auto ahead = [&](int64_t off, int64_t n) { return weights_ahead(&w, 1, false, off, n, M, rp.rows); };   // as below: W2, W1; Wo, Wqkv
       const bool last = l == L_ - 1 && sel.n > 0;  // the gradient arrives, and stays down to the output projection, on the selected rows
       const int rows = last ? sel.n : M;
       const int32_t* const in_use = last ? nullptr : rp.rows;
       // LN2
-      LnBwdArgs n2{dx, pre2_[l], mean2_[l], rstd2_[l], w.theta + o.ln2g, ds32_, ds2, lnpart_[p][0], rows, d_, in_use};
+      LnBwdArgs n2{dx, pre2_[l], mean2_[l], rstd2_[l], w.theta + o.ln2g, ds32_, ds2, lnpart_[p][0], rows, d_, in_use, ahead(o.W1, (int64_t)2 * ffn_ * d_)};
       launch_ln_bwd(st, n2);
       // FFN
       wg[0] = wgrad(ds2, d_, fact_[l], ffn_, rows, grad + o.W2, in_use);
@@ -304,7 +326,7 @@ class EncoderModel : public Model {
       g.res32 = ds32_; g.C32 = dx_next;                       // + the residual branch
       launch_gemm_bf16(st, g);
       // LN1
-      LnBwdArgs n1{dx_next, pre1_[l], mean1_[l], rstd1_[l], w.theta + o.ln1g, ds32_, ds1, lnpart_[p][1], rows, d_, in_use};
+      LnBwdArgs n1{dx_next, pre1_[l], mean1_[l], rstd1_[l], w.theta + o.ln1g, ds32_, ds1, lnpart_[p][1], rows, d_, in_use, ahead(o.Wqkv, (int64_t)4 * d_ * d_)};
       launch_ln_bwd(st, n1);
       // attention
       wg[2] = wgrad(ds1, d_, last ? ao_sel_ : ao_[l], d_, rows, grad + o.Wo, in_use);
@@ -355,7 +377,7 @@ class EncoderModel : public Model {
     auto join = [&](int p) { if (two && side_busy_[p]) { (void)hipStreamWaitEvent(st, ev_side_[p], 0); side_busy_[p] = false; } };
     join(1);
     if (L_ == 1) join(0);
-    LnBwdArgs n0{dx, pre0_, mean0_, rstd0_, w.theta + eg_, ds32_, nullptr, lnpart_[1][0], M, d_, rp.rows};
+    LnBwdArgs n0{dx, pre0_, mean0_, rstd0_, w.theta + eg_, ds32_, nullptr, lnpart_[1][0], M, d_, rp.rows, {}};
     launch_ln_bwd(st, n0);
     const ReduceRowsJob r0{lnpart_[1][0], M / LN_BWD_ROWS, 3 * d_, d_, d_, {grad + eg_, grad + eb_, nullptr}, 0, 0, rp.group, ROW_GROUP / LN_BWD_ROWS};
     launch_reduce_rows_multi(st, &r0, 1);

@@ -54,12 +54,28 @@ __global__ __launch_bounds__(256) void k_row_plan(const int32_t* __restrict__ id
   if (i >= total) { out.src[i] = -1; out.ids[i] = 0; }
 }
 
+// One load brings a line of 128 bytes into the caches; the value is not used.
+__device__ __forceinline__ void fetch_ahead(const WeightsAhead& w, const int32_t* __restrict__ rows, int block, int threads) {
+  if (rows != nullptr && *rows >= w.max_rows) return;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    if (w.p[k] == nullptr) continue;
+#pragma unroll 4
+    for (int64_t i = ((int64_t)block * threads + threadIdx.x) * 64; i < w.n; i += (int64_t)AHEAD_BLOCKS * threads * 64) {
+      const uint32_t v = *reinterpret_cast<const uint32_t*>(w.p[k] + i);
+      asm volatile("" ::"v"(v));
+    }
+  }
+}
+
 // =========================================================================================== LayerNorm forward
 // One wave per row; the row lives in registers, NV 16-byte pieces per lane (d <= 256 NV).  Statistics in fp32 with a centred
 // second pass.
 template <int NV>
 __global__ __launch_bounds__(256) void k_ln_fwd(LnFwdArgs a) {
-  const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int block = (int)blockIdx.x - (a.ahead.n > 0 ? AHEAD_BLOCKS : 0);
+  if (block < 0) return fetch_ahead(a.ahead, a.rows, blockIdx.x, 256);
+  const int lane = threadIdx.x & 63, row = block * 4 + (threadIdx.x >> 6);
   const int r = a.pass_rows > 0 ? row % a.pass_rows : row;   // within its pass
   if (row >= a.M || (a.rows != nullptr && r >= *a.rows)) return;
   const int nq = a.d >> 2;  // float4 chunks per row
@@ -136,9 +152,11 @@ __global__ __launch_bounds__(64 * LN_BWD_ROWS) void k_ln_bwd(LnBwdArgs a) {
   constexpr int G = 4;   // pieces of a lane in a turn
   static_assert(NV % G == 0 && LN_BWD_ROWS == 8, "turns; four pairs of rows");
   __shared__ float4 s_a[LN_BWD_ROWS][64 * G], s_b[LN_BWD_ROWS][64 * G];
+  const int block = (int)blockIdx.x - (a.ahead.n > 0 ? AHEAD_BLOCKS : 0);
+  if (block < 0) return fetch_ahead(a.ahead, a.rows, blockIdx.x, 64 * LN_BWD_ROWS);
   const int M = a.rows != nullptr ? __builtin_amdgcn_readfirstlane(*a.rows) : a.M;
-  if ((int)blockIdx.x * LN_BWD_ROWS >= M) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = blockIdx.x * LN_BWD_ROWS + wave;
+  if (block * LN_BWD_ROWS >= M) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = block * LN_BWD_ROWS + wave;
   const int nq = a.d >> 2;
   const bool live = row < M;
   float4 xh[NV], dy[NV], dx[NV];   // dx: gamma, then dy g, then dx
@@ -179,7 +197,7 @@ __global__ __launch_bounds__(64 * LN_BWD_ROWS) void k_ln_bwd(LnBwdArgs a) {
       }
     }
   }
-  float4* const out = reinterpret_cast<float4*>(a.partial + (int64_t)blockIdx.x * 3 * a.d);
+  float4* const out = reinterpret_cast<float4*>(a.partial + (int64_t)block * 3 * a.d);
   const int tid = threadIdx.x;
   auto pairs_in_order = [](auto pair) {
     float4 t = pair(0);
@@ -772,13 +790,15 @@ __global__ __launch_bounds__(256) void k_embedding_grad(const float* __restrict_
 
 void launch_ln_fwd(hipStream_t st, const LnFwdArgs& a) {
   ProfScope ps(st, F_LN_FWD, 6.0 * a.M * a.d);
-  if (a.d <= 1024) launch_kernel(ps, k_ln_fwd<4>, (a.M + 3) / 4, 256, 0, st, a);
-  else launch_kernel(ps, k_ln_fwd<8>, (a.M + 3) / 4, 256, 0, st, a);
+  const int blocks = (a.M + 3) / 4 + (a.ahead.n > 0 ? AHEAD_BLOCKS : 0);
+  if (a.d <= 1024) launch_kernel(ps, k_ln_fwd<4>, blocks, 256, 0, st, a);
+  else launch_kernel(ps, k_ln_fwd<8>, blocks, 256, 0, st, a);
 }
 void launch_ln_bwd(hipStream_t st, const LnBwdArgs& a) {
   ProfScope ps(st, F_LN_BWD, 14.0 * a.M * a.d);
-  if (a.d <= 1024) launch_kernel(ps, k_ln_bwd<4>, (a.M + LN_BWD_ROWS - 1) / LN_BWD_ROWS, 64 * LN_BWD_ROWS, 0, st, a);
-  else launch_kernel(ps, k_ln_bwd<8>, (a.M + LN_BWD_ROWS - 1) / LN_BWD_ROWS, 64 * LN_BWD_ROWS, 0, st, a);
+  const int blocks = (a.M + LN_BWD_ROWS - 1) / LN_BWD_ROWS + (a.ahead.n > 0 ? AHEAD_BLOCKS : 0);
+  if (a.d <= 1024) launch_kernel(ps, k_ln_bwd<4>, blocks, 64 * LN_BWD_ROWS, 0, st, a);
+  else launch_kernel(ps, k_ln_bwd<8>, blocks, 64 * LN_BWD_ROWS, 0, st, a);
 }
 void launch_reduce_rows_multi(hipStream_t st, const ReduceRowsJob* jobs, int count) {
   ReduceRowsMulti m{};

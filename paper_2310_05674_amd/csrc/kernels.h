@@ -260,6 +260,12 @@ struct RowPlan {
 struct RowSelect;
 // lens [B]: real tokens; sel.n_mask > 0: masked positions to keep as well
 void launch_row_plan(hipStream_t, const int32_t* ids, const int32_t* lens, int B, int S, const RowSelect& sel, const RowPlan& out);
+// Weights that the products behind a LayerNorm will read: workgroups of its launch beside those of the rows fetch them.
+struct WeightsAhead {
+  const bf16_t* p[4]; int64_t n;   // up to four arrays of n values each (a multiple of 64), or null; n = 0: none
+  int max_rows;                    // no longer worth it with this many rows in use
+};
+constexpr int AHEAD_BLOCKS = 256;
 struct LnFwdArgs {
   const float* x;          // [M x d] input, or null: embedding mode (x = tok_emb[id] + pos_emb[m % S])
   const int32_t* ids; int S; int64_t tok_off, pos_off; float* x_out;  // embedding mode; x_out [M x d] may be null
@@ -270,6 +276,7 @@ struct LnFwdArgs {
   ParamView pv; int64_t g_off, b_off;                                 // gamma / beta inside theta
   bf16_t* y; float* y32; float* mean; float* rstd;                    // y32 (fp32 copy for the residual path), mean, rstd may be null
   int M, d;
+  WeightsAhead ahead;
 };
 void launch_ln_fwd(hipStream_t, const LnFwdArgs&);
 struct LnBwdArgs {
@@ -278,6 +285,7 @@ struct LnBwdArgs {
   float* partial;          // [ceil(M / LN_BWD_ROWS)][3][d]: dgamma, dbeta, column sums of dx
   int M, d;
   const int32_t* rows;     // null, or rows in use
+  WeightsAhead ahead;
 };
 void launch_ln_bwd(hipStream_t, const LnBwdArgs&);
 // out_v[c] = sum_r partial[r*stride + v*vstride + c] for the non-null outputs v = 0, 1, 2, in a fixed order

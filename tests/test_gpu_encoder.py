@@ -763,6 +763,33 @@ def test_eval_of_a_text_does_not_depend_on_what_is_scored_beside_it(S, fast, pad
     gpu.close()
 
 
+@pytest.mark.parametrize("B,padded", [(2, False), (3, True)])
+def test_weights_fetched_ahead(B, padded):
+    """16 million weights of 8 layers, with their state more than the last-level cache holds, and few rows: the LayerNorms' launches
+    fetch the next weights beside their rows.  A base step and the passes of a meta step against the oracle."""
+    wl = make_workload(3, n_train=2 * B, n_meta=4, dims=(8, 448, 7, 1344, 64, 300, 3), batch=B, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    (x, y), (xm, ym) = _batches(wl, 0)
+    lens = np.array([1, 64, 33][:B], dtype=np.int32) if padded else None
+    xo = with_lengths(x, lens) if padded else x
+    for _ in range(3):   # after a single one every entry of Eq. 4's direction is the sign of its gradient, which rounding decides
+        orc.base_step(xo, y)
+    push_state(orc, gpu)
+    orc.base_step(xo, y)
+    gpu.base_step(dev_batch(gpu, x, y, lens=lens))
+    g = pull(gpu, "G")
+    errs = _group_errors(orc, g, orc.g)
+    print(f"B={B} padded={padded}: rel-L2 g {rel_l2(g, orc.g):.3e}; worst group {max(errs, key=errs.get)} {max(errs.values()):.3e}")
+    assert rel_l2(g, orc.g) < KTOL and all(e < TOL for e in errs.values()), errs
+    push_state(orc, gpu)
+    r = orc.meta_step(xo, y, xm, ym)
+    gpu.meta_step(dev_batch(gpu, x, y, lens=lens), dev_batch(gpu, xm, ym))
+    e = dict(gmeta=rel_l2(pull(gpu, "GMETA"), r["g_meta"]), glam_p=rel_l2(pull(gpu, "GLAM_PLUS"), r["glam_p"]))
+    print(" ".join(f"{k}={v:.2e}" for k, v in e.items()))
+    assert e["gmeta"] < KTOL and e["glam_p"] < KTOL
+    gpu.close()
+
+
 @pytest.mark.parametrize("C,d", [(8, 192), (9, 192), (21, 1088)])
 def test_head_of_many_classes_and_features(C, d):
     """The classifier with as many classes as are taken at a time, one more, and three times as many over more features than are:
