@@ -701,53 +701,59 @@ __global__ __launch_bounds__(256) void k_spread_rows(RowSelect s, RowPlan plan, 
 }
 
 // =========================================================================================== embedding gradients
-// One block per position m.  The block lists, in ascending order, every position holding the same token id;
-// only the block of the first occurrence goes on, and writes the ordered sum of those rows.  What bounds it is the block of the
-// most frequent id (position 0 of every sequence, the head of the Zipf law: hundreds of rows), a serial chain of fetches: so
-// TOK_AHEAD values of a thread's columns are fetched together, without a branch between them (clamped indexes, zeros behind the
-// end), and added in list order.  With the position gradients in the same launch, 4096 positions of 768: 57 + 10 -> 33 us.
-constexpr int TOK_AHEAD = 32;
-template <int NC>   // columns per thread
-__device__ __forceinline__ void tok_rows(const float* __restrict__ demb, const uint16_t* __restrict__ list, int cnt, int d, int c0, float* __restrict__ out) {
-  constexpr int R = TOK_AHEAD / NC;
-  float s[NC];
-#pragma unroll
-  for (int q = 0; q < NC; ++q) s[q] = 0.f;
+// A block per position m and TOK_COLS columns.  The block lists, in ascending order, every position holding the same token id;
+// only those of the first occurrence go on, and write the ordered sum of those rows.  What bounds it is the most frequent
+// id (position 0 of every sequence, the head of the Zipf law: hundreds of rows), a serial chain of fetches and what one CU takes in: so its
+// columns are spread over workgroups, and TOK_AHEAD rows are fetched together, without a branch between them (the list goes
+// on with its last entry, which counts as zeros), and added in list order.  Such ids are seen early: the positions from TOK_SPLIT
+// on have one block for all columns, since every block looks through all positions (three for each of 4096: 41 us).
+// With the position gradients, all columns and 8 rows together -> now: 4096 positions of 768, 62 -> 24 us, 8192 118 -> 59, 2048 of
+// 1024 24 -> 14, 4096 of 256 26 -> 23.
+constexpr int TOK_COLS = 256, TOK_AHEAD = 64, TOK_SPLIT = 512, TOK_SCAN = 4;   // TOK_SCAN x 256 positions are looked at together
+template <int R>   // rows fetched together
+__device__ __forceinline__ void tok_rows(const float* __restrict__ demb, const uint16_t* __restrict__ list, int cnt, int d, int c, float* __restrict__ out) {
+  const float* const col = demb + min(c, d - 1);
+  float s = 0.f;
   for (int i = 0; i < cnt; i += R) {   // behind the end: zeros, which change no sum
-    float v[R][NC];
+    float v[R];
 #pragma unroll
-    for (int u = 0; u < R; ++u)
+    for (int u = 0; u < R; u += 8) {
+      const uint4 l = *reinterpret_cast<const uint4*>(list + i + u);
+      const uint32_t w[4] = {l.x, l.y, l.z, l.w};
 #pragma unroll
-      for (int q = 0; q < NC; ++q) v[u][q] = demb[(int64_t)list[min(i + u, cnt - 1)] * d + min(c0 + 256 * q, d - 1)];
+      for (int e = 0; e < 8; ++e) v[u + e] = col[(int64_t)(w[e >> 1] >> (16 * (e & 1)) & 0xffffu) * d];
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < R; ++u)
-#pragma unroll
-      for (int q = 0; q < NC; ++q) s[q] += i + u < cnt ? v[u][q] : 0.f;
+    for (int u = 0; u < R; ++u) s += i + u < cnt ? v[u] : 0.f;
   }
-#pragma unroll
-  for (int q = 0; q < NC; ++q)
-    if (c0 + 256 * q < d) out[c0 + 256 * q] = s[q];
+  if (c < d) out[c] = s;
 }
-__device__ __forceinline__ void tok_grad(const float* __restrict__ demb, const int32_t* __restrict__ ids, int m, int M, int d, int V,
+__device__ __forceinline__ void tok_grad(const float* __restrict__ demb, const int32_t* __restrict__ ids, int m, int M, int c0, int c1, int d, int V,
                                          float* __restrict__ g_tok) {
-  __shared__ uint16_t s_list[MAX_TOKENS];
+  __shared__ __attribute__((aligned(16))) uint16_t s_list[MAX_TOKENS + TOK_AHEAD];
   static_assert(MAX_TOKENS <= 65536, "positions in 16 bits");
-  __shared__ int s_wave[4][4];
+  __shared__ int s_wave[TOK_SCAN][4], s_earlier[4];
   const int id = min(max(ids[m], 0), V - 1), lane = threadIdx.x & 63, wave = threadIdx.x >> 6;   // clamped as in the forward pass
   int cnt = 0;
-  for (int base = 0; base < M; base += 1024) {
-    unsigned long long hits[4];
+  for (int base = 0; base < M; base += 256 * TOK_SCAN) {
+    int there[TOK_SCAN];
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < TOK_SCAN; ++g) there[g] = ids[min(base + 256 * g + (int)threadIdx.x, M - 1)];
+    unsigned long long hits[TOK_SCAN], earlier = 0;
+#pragma unroll
+    for (int g = 0; g < TOK_SCAN; ++g) {
       const int mm = base + 256 * g + threadIdx.x;
-      hits[g] = __ballot(mm < M && min(max(ids[mm], 0), V - 1) == id);
+      hits[g] = __ballot(mm < M && min(max(there[g], 0), V - 1) == id);
+      earlier |= hits[g] & __ballot(mm < m);
       if (lane == 0) s_wave[g][wave] = __popcll(hits[g]);
     }
+    if (lane == 0) s_earlier[wave] = earlier != 0;
     __syncthreads();
+    if (s_earlier[0] | s_earlier[1] | s_earlier[2] | s_earlier[3]) return;   // an earlier position holds this id
     int off = cnt;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < TOK_SCAN; ++g) {
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         if (w == wave && (hits[g] >> lane & 1)) s_list[min(off + (int)__popcll(hits[g] & ((1ull << lane) - 1ull)), MAX_TOKENS - 1)] = (uint16_t)(base + 256 * g + threadIdx.x);
@@ -756,20 +762,24 @@ __device__ __forceinline__ void tok_grad(const float* __restrict__ demb, const i
     }
     cnt = off;
     __syncthreads();
-    if (cnt > 0 && s_list[0] != m) return;   // an earlier position holds this id (the list is ascending)
   }
+  if (threadIdx.x < TOK_AHEAD) s_list[cnt + threadIdx.x] = s_list[cnt - 1];   // m itself is listed
+  __syncthreads();
   float* out = g_tok + (int64_t)id * d;
-  if (d <= 256) tok_rows<1>(demb, s_list, cnt, d, threadIdx.x, out);
-  else if (d <= 512) tok_rows<2>(demb, s_list, cnt, d, threadIdx.x, out);
-  else
-    for (int c = threadIdx.x; c < d; c += 1024) tok_rows<4>(demb, s_list, cnt, d, c, out);
+  for (int c = c0 + threadIdx.x; c < c1; c += TOK_COLS) {
+    if (cnt <= 8) tok_rows<8>(demb, s_list, cnt, d, c, out);
+    else tok_rows<TOK_AHEAD>(demb, s_list, cnt, d, c, out);
+  }
 }
-// Blocks [0, pblocks): position gradients; the others: a token position each.
+// Blocks [0, pblocks): position gradients; the others: TOK_COLS columns of a token position each.
 __global__ __launch_bounds__(256) void k_embedding_grad(const float* __restrict__ demb, const int32_t* __restrict__ ids, int B, int S, int d, int V,
                                                         RowPlan plan, int pblocks, float* __restrict__ g_tok, float* __restrict__ g_pos) {
   if ((int)blockIdx.x >= pblocks) {
-    const int M = plan.start != nullptr ? plan.start[B] : B * S, m = blockIdx.x - pblocks;
-    if (m < M) tok_grad(demb, plan.ids != nullptr ? plan.ids : ids, m, M, d, V, g_tok);
+    const int M = plan.start != nullptr ? plan.start[B] : B * S, k = blockIdx.x - pblocks, chunks = (d + TOK_COLS - 1) / TOK_COLS;
+    const int split = min(B * S, TOK_SPLIT);
+    const bool all = k >= split * chunks;
+    const int m = all ? k - split * chunks + split : k / chunks, c0 = all ? 0 : (k - m * chunks) * TOK_COLS;
+    if (m < M) tok_grad(demb, plan.ids != nullptr ? plan.ids : ids, m, M, c0, all ? d : min(c0 + TOK_COLS, d), d, V, g_tok);
     return;
   }
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -905,7 +915,7 @@ void launch_embedding_bwd(hipStream_t st, const float* demb, const int32_t* ids,
                           const RowPlan& plan) {
   ProfScope ps(st, F_OTHER, 4.0 * B * S * d);
   const int pblocks = (S * d + 255) / 256;
-  launch_kernel(ps, k_embedding_grad, pblocks + B * S, 256, 0, st, demb, ids, B, S, d, V, plan, pblocks, g_tok, g_pos);
+  launch_kernel(ps, k_embedding_grad, pblocks + B * S + std::min(B * S, TOK_SPLIT) * ((d + TOK_COLS - 1) / TOK_COLS - 1), TOK_COLS, 0, st, demb, ids, B, S, d, V, plan, pblocks, g_tok, g_pos);
 }
 
 }  // namespace sama

@@ -718,6 +718,40 @@ def test_padded_rows_and_embedding_gradients_at_their_edges(d, B, lens, repeat):
     gpu.close()
 
 
+@pytest.mark.parametrize("d,counts", [(256, (1, 8, 9, 64, 65, 130)), (320, (1, 8, 9, 64, 65, 130))])
+def test_embedding_gradients_of_repeated_ids(d, counts):
+    """Ids that occur as often as their rows are fetched together, one less and one more, first seen among the positions whose
+    columns go to a workgroup each (the first 512) and behind them.  The sum of a token's rows is a sum over rows of 2 layers' output
+    gradient, so its error is that of the pass.  A missing or doubled row could hide in that, so all tokens' sums are added up and
+    compared with the positions' sums, which add the same rows: the two differ by fp32 roundings of B S summands."""
+    S, B = 128, 9
+    wl = make_workload(3, n_train=4 * B, n_meta=4, dims=(2, d, d // 64, 320, S, 1400, 3), batch=B, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    (x, y), _ = _batches(wl, 0)
+    flat = np.arange(100, 100 + B * S).astype(x.dtype)     # every position its own id
+    rng = np.random.default_rng(5)
+    early = rng.permutation(np.arange(20, 512)); late = rng.permutation(np.arange(530, B * S))
+    e = l = 0
+    for k, n in enumerate(counts):
+        flat[early[e:e + (n + 1) // 2]] = k; flat[late[l:l + n // 2]] = k; e += (n + 1) // 2; l += n // 2      # first seen early
+        flat[late[l:l + n]] = 50 + k; l += n                                                                # first seen late
+    x = flat.reshape(B, S)
+    push_state(orc, gpu)
+    orc.base_step(x, y)
+    gpu.base_step(dev_batch(gpu, x, y))
+    off, shape = orc.model.slices["tok_emb"]
+    got, want = pull(gpu, "G")[off:off + int(np.prod(shape))].reshape(shape), orc.g[off:off + int(np.prod(shape))].reshape(shape)
+    for k in [i for i in range(len(counts))] + [50 + i for i in range(len(counts))]:
+        assert np.count_nonzero(x == k) == counts[k % 50]
+        assert rel_l2(got[k], want[k]) < TOL, (k, rel_l2(got[k], want[k]))
+    assert rel_l2(got, want) < KTOL
+    # the gradients of the positions' rows, of which every token's is a sum: pos_emb sums them over the sequences
+    po, ps = orc.model.slices["pos_emb"]
+    assert np.allclose(pull(gpu, "G")[po:po + int(np.prod(ps))].reshape(ps).sum(0, dtype=np.float64), got.sum(0, dtype=np.float64),
+                       rtol=0, atol=B * S * 2.0 ** -24 * np.abs(got).sum(0).max())
+    gpu.close()
+
+
 @pytest.mark.parametrize("d,ffn,S,B,padded", [
     (128, 256, 64, 1, False), (192, 448, 64, 2, True), (192, 448, 128, 1, False), (320, 1088, 128, 1, True), (192, 384, 128, 8, False),
     (192, 448, 128, 9, True)])
