@@ -12,9 +12,11 @@
 //   one whose contraction index is the strided one (dgrad's W, both operands of wgrad) is staged as it lies in
 //   memory, [k][row], and fetched with the transposing LDS read (ds_read_b64_tr_b16)
 //   the MFMA operands of k-step t + 1 are fetched while the MFMAs of step t issue, also across the slab boundary
-//   measured on MI355X: a CU ingests at most ~25-30 B/clk from L2 (about 100-128 outstanding 128-byte requests
-//   times the loaded L2 latency), so the block tile, not the MFMA rate, bounds the kernel: 256 x 256 tiles need
-//   32 B/clk per CU at the MFMA peak, 256 x 128 need 48, 128 x 128 need 64
+//   measured on MI355X: a CU takes in 57 B/clk where L2 holds the slabs, 40 from the last-level cache and 27 where the weights
+//   come from memory (about 128 outstanding 128-byte requests over the latency of each), and at the MFMA peak 256 x 256 tiles
+//   need 32 B/clk, 256 x 128 48, 128 x 128 64: small tiles are bound by this, and the weights of a product of few rows are
+//   fetched by the launch before it (k_ln_fwd, k_ln_bwd).  The largest tiles are bound by power: without any loads a
+//   launch of 256 x 128 hi + lo tiles of 109 us takes 98, at 1.75 GHz with the matrix cores busy 65 % of the time
 //   workgroup ids are remapped so that each XCD (own L2) works on a compact patch of tiles
 //   the accumulators leave through LDS so that every global access of the epilogue is a full row segment
 //

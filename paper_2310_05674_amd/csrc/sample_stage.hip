@@ -11,7 +11,7 @@
 //
 // Everything here is small and latency-bound, a launch of its own costing as much as most of these steps.  The logits of a
 // workgroup's 32 samples come from the fp32 matrix cores, the eight waves splitting the contraction.  Sixteen lanes share a sample (classes, weight-net and corrector hidden
-// units are split between them and joined by shuffles), a workgroup holds 32 samples at a time, and a batch is spread over
+// units are split between them and joined across the lanes), a workgroup holds 32 samples at a time, and a batch is spread over
 // up to STAGE_MAX_BLOCKS workgroups.  What a mode sums over the batch (the loss, the lambda-gradient) leaves each
 // workgroup as a partial; the workgroup that finishes last adds the partials in workgroup order, so results do not depend on
 // timing.  The + and the - pass of Eq. 5 are one launch (grid.y), and the last workgroup of that launch also combines them
@@ -110,7 +110,7 @@ __device__ __forceinline__ void head_logits(const HeadView& h, int pass, int i_b
   }
 }
 
-// The same with a wave per sample: 64 strided partial sums in fp32, joined by a shuffle tree.  The losses of the two passes of
+// The same with a wave per sample: 64 strided partial sums in fp32, joined in a fixed tree.  The losses of the two passes of
 // Eq. 5 differ in their last digits only, and a deep model's gradients follow those of its logits, so what the
 // encoder's logits are rounded to is kept independent of how a workgroup's tiles split the features.
 // W, as the pass sees it, comes through LDS, CU classes and 1024 features at a time, and a wave has that many features of its
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
 
   if (seq_mode) {
     // wave w takes sequences w, w + waves, ...: its lanes stride over the positions (coalesced), keep the matching losses,
-    // and a shuffle tree adds the 64 partial sums in a fixed order
+    // and a tree over the lanes adds the 64 partial sums in a fixed order
     for (int i = tid >> 6; i < n_own; i += ST_THREADS / 64) {
       double acc = 0.0, n_i = 0.0;
       for (int j = tid & 63; j < a.n_pos; j += 64) {
