@@ -18,11 +18,16 @@ constexpr int EW_THREADS = 256;
 constexpr int EW_VEC = 4;
 constexpr int EW_U = 4;
 constexpr int EW_TRIP = EW_U * EW_THREADS;   // vectors per block per trip
+// Up to this many elements a launch is a chain, not a stream, and most CUs would have nothing to do: the updates take one vector per
+// thread.  us, four / one: Adam of 63 thousand 3.94 / 2.39, 269 thousand 4.39 / 2.99, 500 thousand 4.20 / 3.65, 2^20 4.47 / 4.47;
+// SGD 2.83 / 2.42, 3.41 / 2.72, 2.94 / 2.78, 3.15 / 3.38; the nudge 2.78 / 2.41, 2.91 / 2.49, 2.74 / 2.53, 3.11 / 2.86.
+constexpr int64_t EW_FEW = 1 << 19;
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
-inline int ew_grid(int64_t n) {
-  int64_t b = (n / EW_VEC + EW_TRIP - 1) / EW_TRIP;
+inline int ew_grid(int64_t n, int u = EW_U) {
+  const int64_t trip = u * EW_THREADS;
+  int64_t b = (n / EW_VEC + trip - 1) / trip;
   if (b < 1) b = 1;
   if (b > EW_MAX_BLOCKS) b = EW_MAX_BLOCKS;
   return (int)b;
@@ -57,21 +62,22 @@ __device__ __forceinline__ void adam_one(float g, float& m, float& v, float& th,
   th = th - a.lr_c1 * m / (fmaf(a.c2, sqrtf(v), a.eps));
 }
 
+template <int U>
 __global__ __launch_bounds__(EW_THREADS) void k_adam(float* __restrict__ g, float* __restrict__ m,
                                                      float* __restrict__ v, float* __restrict__ theta,
                                                      bf16_t* __restrict__ theta16, int64_t n, int64_t n16,
                                                      AdamArgs a) {
   if (a.dev != nullptr) { a.lr_c1 = a.dev[0]; a.c2 = a.dev[1]; }
-  const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
-  for (int64_t base = (int64_t)blockIdx.x * EW_TRIP + threadIdx.x; base < nv; base += trip) {
-    f4 G[EW_U], M[EW_U], V[EW_U], T[EW_U];
+  const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * U * EW_THREADS;
+  for (int64_t base = (int64_t)blockIdx.x * U * EW_THREADS + threadIdx.x; base < nv; base += trip) {
+    f4 G[U], M[U], V[U], T[U];
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int64_t j = base + u * EW_THREADS;
       if (j < nv) { G[u] = ld_nt(g, j); M[u] = ld_nt(m, j); V[u] = ld_nt(v, j); T[u] = ld_nt(theta, j); }
     }
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int64_t j = base + u * EW_THREADS;
       if (j < nv) {
 #pragma unroll
@@ -111,14 +117,15 @@ __global__ void k_step_scalars(StepScalars s) { step_scalars(s); }
 // mu = 0).  Also refreshes the bf16 working copy and its residual half over the first n16 elements.  In the streaming layout,
 // where an element at a time had sixteen round trips to memory one after the other: label correction with 63 thousand
 // parameters, two such steps an iteration, 206 -> 190 us.
+template <int U>
 __global__ __launch_bounds__(EW_THREADS) void k_sgd(float* __restrict__ g, float* __restrict__ buf, float* __restrict__ theta,
                                                     bf16_t* __restrict__ theta16, bf16_t* __restrict__ lo, int64_t n,
                                                     int64_t n16, float lr, float wd, float mu) {
-  const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
-  for (int64_t base = (int64_t)blockIdx.x * EW_TRIP + threadIdx.x; base < nv; base += trip) {
-    f4 G[EW_U], B[EW_U], T[EW_U];
+  const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * U * EW_THREADS;
+  for (int64_t base = (int64_t)blockIdx.x * U * EW_THREADS + threadIdx.x; base < nv; base += trip) {
+    f4 G[U], B[U], T[U];
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int64_t j = base + u * EW_THREADS;
       if (j < nv) {
         G[u] = ld_nt(g, j); T[u] = ld_nt(theta, j);
@@ -126,7 +133,7 @@ __global__ __launch_bounds__(EW_THREADS) void k_sgd(float* __restrict__ g, float
       }
     }
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int64_t j = base + u * EW_THREADS;
       if (j >= nv) continue;
       f4 b;
@@ -364,21 +371,22 @@ __global__ __launch_bounds__(EW_THREADS) void k_residual_lo(const float* __restr
 
 // theta <- theta - eps v (and the bf16 working copy with its residual half).  eps = 0 or a raised status word (a
 // skipped step) leaves everything as it is.
+template <int U>
 __global__ __launch_bounds__(EW_THREADS) void k_nudge(float* __restrict__ theta, const float* __restrict__ vdir,
                                                       const float* __restrict__ eps_ptr, const int64_t* __restrict__ status,
                                                       bf16_t* __restrict__ theta16, bf16_t* __restrict__ lo, int64_t n, int64_t n16) {
   const float eps = *eps_ptr;
   if (eps == 0.f || (status != nullptr && *status != 0)) return;
-  const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
-  for (int64_t base = (int64_t)blockIdx.x * EW_TRIP + threadIdx.x; base < nv; base += trip) {
-    f4 T[EW_U], V[EW_U];
+  const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * U * EW_THREADS;
+  for (int64_t base = (int64_t)blockIdx.x * U * EW_THREADS + threadIdx.x; base < nv; base += trip) {
+    f4 T[U], V[U];
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int64_t j = base + u * EW_THREADS;
       if (j < nv) { T[u] = ld_nt(theta, j); V[u] = ld_nt(vdir, j); }
     }
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int64_t j = base + u * EW_THREADS;
       if (j < nv) {
         f4 t;
@@ -468,13 +476,15 @@ void launch_adam(hipStream_t st, float* g, float* m, float* v, float* theta, bf1
                  int64_t n16, const AdamArgs& a) {
   if (n <= 0) return;
   ProfScope ps(st, F_ADAM, 28.0 * n + (theta16 ? 2.0 * n16 : 0.0) + (a.lo ? 2.0 * n16 : 0.0));
-  launch_kernel(ps, k_adam, ew_grid(n), EW_THREADS, 0, st, g, m, v, theta, theta16, n, n16, a);
+  if (n <= EW_FEW) launch_kernel(ps, k_adam<1>, ew_grid(n, 1), EW_THREADS, 0, st, g, m, v, theta, theta16, n, n16, a);
+  else launch_kernel(ps, k_adam<EW_U>, ew_grid(n), EW_THREADS, 0, st, g, m, v, theta, theta16, n, n16, a);
 }
 void launch_step_scalars(hipStream_t st, const StepScalars& s) { k_step_scalars<<<1, 1, 0, st>>>(s); }
 void launch_sgd(hipStream_t st, float* g, float* buf, float* theta, bf16_t* theta16, bf16_t* lo, int64_t n, int64_t n16,
                 float lr, float wd, float mu) {
   if (n <= 0) return;
-  k_sgd<<<ew_grid(n), EW_THREADS, 0, st>>>(g, buf, theta, theta16, lo, n, n16, lr, wd, mu);
+  if (n <= EW_FEW) k_sgd<1><<<ew_grid(n, 1), EW_THREADS, 0, st>>>(g, buf, theta, theta16, lo, n, n16, lr, wd, mu);
+  else k_sgd<EW_U><<<ew_grid(n), EW_THREADS, 0, st>>>(g, buf, theta, theta16, lo, n, n16, lr, wd, mu);
 }
 void launch_adapt_norm(hipStream_t st, const float* g, const float* m, const float* v, const float* gmeta, float* vdir,
                        double* partial, int64_t n, const AdaptArgs& a, float alpha, float* scalars, int64_t* status) {
@@ -521,7 +531,8 @@ void launch_nudge(hipStream_t st, float* theta, const float* vdir, const float* 
                   bf16_t* theta16, bf16_t* lo, int64_t n, int64_t n16) {
   if (n <= 0) return;
   ProfScope ps(st, F_NUDGE, 12.0 * n + (theta16 ? 2.0 * n16 : 0.0) + (lo ? 2.0 * n16 : 0.0));
-  launch_kernel(ps, k_nudge, ew_grid(n), EW_THREADS, 0, st, theta, vdir, eps_ptr, status, theta16, lo, n, n16);
+  if (n <= EW_FEW) launch_kernel(ps, k_nudge<1>, ew_grid(n, 1), EW_THREADS, 0, st, theta, vdir, eps_ptr, status, theta16, lo, n, n16);
+  else launch_kernel(ps, k_nudge<EW_U>, ew_grid(n), EW_THREADS, 0, st, theta, vdir, eps_ptr, status, theta16, lo, n, n16);
 }
 void launch_unnudge(hipStream_t st, float* theta, const float* vdir, const float* eps_ptr, const int64_t* status,
                     bf16_t* theta16, bf16_t* lo, int64_t n16) {

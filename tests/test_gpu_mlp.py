@@ -438,6 +438,27 @@ def test_sgd_update_of_every_element(d, C):
     gpu.close()
 
 
+@pytest.mark.parametrize("d,C", [(10000, 7), (65535, 8), (65536, 8), (104857, 5), (75000, 7)])
+def test_updates_on_both_sides_of_the_line_between_their_forms(d, C):
+    """524288 parameters (one vector per thread), a few more (four), and remainders of two and three elements: each element of an SGD
+    step and of the nudge theta - eps v against what the library kept, to the rounding of three and of two fp32 operations."""
+    wl, x, y, th0, lam0, r = _linear_workload(d, C, 8, 16, 0.5)
+    orc, gpu = make_pair(wl, th0, lam0, base_opt="sgd", base_lr=0.05, momentum=0.9, weight_decay=0.25)
+    m0 = r.normal(11, d * C + C).astype(np.float32)
+    gpu.set_state("M", m0)
+    b = dev_batch(gpu, x, y)
+    gpu.base_step(b)
+    g, m, th = (pull(gpu, k).astype(np.float64) for k in ("G", "M", "THETA"))
+    ulp = 2.0 ** -23
+    assert np.all(np.abs(m - (0.9 * m0.astype(np.float64) + g)) <= 2 * ulp * (np.abs(m0) + np.abs(g)))
+    assert np.all(np.abs(th - (th0 - 0.05 * m)) <= 2 * ulp * (np.abs(th0) + 0.05 * np.abs(m)))
+    gpu.meta_step(b, b)
+    eps, v = float(pull(gpu, "SCALARS")[0]), pull(gpu, "VDIR").astype(np.float64)
+    assert eps > 0
+    assert np.all(np.abs(pull(gpu, "THETA") - (th - eps * v)) <= ulp * (np.abs(th) + eps * np.abs(v)))
+    gpu.close()
+
+
 @pytest.mark.parametrize("dims", [(1, 1, 2), (16, 15, 3), (17, 33, 2), (130, 1, 4), (64, 32, 48, 10), (301, 129, 66, 5)])
 @pytest.mark.parametrize("B", [1, 31, 129, 600])
 def test_fp32_products_at_their_edges(dims, B):
