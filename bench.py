@@ -221,7 +221,7 @@ def main():
         torch.cuda.synchronize(dev)
         fam = s.profile_read()
         s.profile(False)
-        s.lib.sama_dev_side_stream(ctypes.c_int32(-1))
+        s.lib.sama_dev_side_stream(ctypes.c_int32(1))
         kernels = {}
         for name, (cnt, ms, units) in fam.items():
             avg_us = 1e3 * ms / cnt

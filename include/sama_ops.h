@@ -88,13 +88,13 @@ sama_status sama_op_nudge(float* theta, const float* vdir, const float* eps_ptr,
  *    tiles), 11..19 the hi+lo tiles (single-term problems ignore them); 0 = the heuristic (default).  Within a class
  *    every tile gives the same bits.
  *  - sama_dev_side_stream(0): the encoder's backward passes keep every launch on the context's stream (a per-kernel profile
- *    wants one stream); 1: weight gradients and optimizer slices run on the library's second stream; -1 = default: on the
- *    second stream where rows and layers are large enough.  A base step keeps its bits; a meta step adds the partial sums
- *    of ||v||^2 in another order.
+ *    wants one stream); 1 = default: weight gradients and optimizer slices run on the library's second stream where rows and
+ *    layers are large enough for it; 2: they do for every size.  Any other value means 1.  A base step keeps its bits; a
+ *    meta step adds the partial sums of ||v||^2 in another order.
  *  - sama_dev_side_sink(0): the optimizer and adaptation slices wait for the end of the backward pass instead of
  *    following each layer's gradients; 1 = default.  The same holds for its bits. */
 void sama_dev_gemm_shape(int32_t id);
-void sama_dev_side_stream(int32_t on);
+void sama_dev_side_stream(int32_t mode);
 void sama_dev_side_sink(int32_t on);
 
 #ifdef __cplusplus

@@ -6,7 +6,7 @@
 #include "model.h"
 
 namespace sama {
-static int g_side_stream = -1;   // the rule below; 0 never, 1 always
+static int g_side_stream = 1;   // 0 never, 2 always, else the rule below
 static bool g_side_sink = true;
 void encoder_side_stream(int mode) { g_side_stream = mode; }
 void encoder_side_sink(bool on) { g_side_sink = on; }
@@ -18,7 +18,10 @@ namespace {
 // 4.8e9 (1024, 12 x 192) 3003 / 2923, 4.8e9 (512, 12 x 256) 3142 / 2961, 6.4e9 (2048, 4 x 256) 1320 / 1311, 7.2e9 (4096, 4 x 192)
 // 1488 / 1557, 10e9 (512, 12 x 384) 3668 / 3619, 13e9 (4096, 4 x 256) 1634 / 1705, 15e9 (1024, 4 x 576) 1792 / 1815, 19e9 (2048,
 // 12 x 256) 3794 / 3940, 46e9 (1024, 12 x 576) 5350 / 5546.
-inline bool side_wanted(int64_t rows, int64_t params) { return g_side_stream >= 0 ? g_side_stream != 0 : rows * params >= 7000000000ll; }
+inline bool side_wanted(int64_t rows, int64_t params) {
+  if (g_side_stream == 0 || g_side_stream == 2) return g_side_stream == 2;
+  return rows * params >= 7000000000ll;
+}
 
 struct LayerOff { int64_t Wqkv, Wo, W1, W2, bqkv, bo, ln1g, ln1b, b1, b2, ln2g, ln2b; };
 

@@ -237,7 +237,7 @@ constexpr int GEMM_MAX_BATCH = 4;
 const char* check_gemm_bf16_batch(const GemmBf16Args* p, int count);
 void launch_gemm_bf16_batch(hipStream_t, const GemmBf16Args* p, int count);
 void encoder_side_sink(bool on);         // tuning hook: per-layer gradient consumers on that stream (default on)
-void encoder_side_stream(int mode);     // tuning hook: weight-gradient launches on a second stream: 0 never, 1 always, -1 (default) by size
+void encoder_side_stream(int mode);     // tuning hook: weight-gradient launches on a second stream: 0 never, 2 always, else (default) by size
 void gemm_bf16_force_shape(int shape);  // tuning hook: 0 = heuristic, else 100 * tile-order group + tile configuration id
 
 // ------------------------------------------------------------------ encoder ops (encoder_ops.hip)

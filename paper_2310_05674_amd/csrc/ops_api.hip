@@ -37,8 +37,8 @@ extern "C" {
 
 // Diagnostic switches (include/sama_ops.h): block shape of the bf16 GEMM, 0 = heuristic.
 void sama_dev_gemm_shape(int32_t shape) { gemm_bf16_force_shape(shape); }
-// 0 keeps every launch of the encoder's backward pass on the context's stream, 1 uses the second one, -1 decides by size / 0 makes the optimizer slices wait for its end.
-void sama_dev_side_stream(int32_t on) { encoder_side_stream(on); }
+// 0 keeps every launch of the encoder's backward pass on the context's stream, 2 uses the second one, 1 decides by size / 0 makes the optimizer slices wait for its end.
+void sama_dev_side_stream(int32_t mode) { encoder_side_stream(mode); }
 void sama_dev_side_sink(int32_t on) { encoder_side_sink(on != 0); }
 
 sama_status sama_op_gemm_bf16(const void* A, int64_t lda, int32_t a_trans, const void* B, const void* B2, int64_t ldb,

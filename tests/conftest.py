@@ -24,3 +24,15 @@ def pytest_collection_modifyitems(config, items):
     for it in items:
         if "gpu" in it.keywords:
             it.add_marker(skip)
+
+
+@pytest.fixture(params=[1, 2], ids=["default", "two_streams"])
+def backward_streams(request):
+    """The encoder's backward passes as a user gets them (one stream for models as small as the tests'), and with the second
+    stream that large ones take."""
+    import ctypes
+    import paper_2310_05674_amd as pkg
+    lib = pkg.load_library()
+    lib.sama_dev_side_stream(ctypes.c_int32(request.param))
+    yield request.param
+    lib.sama_dev_side_stream(ctypes.c_int32(1))

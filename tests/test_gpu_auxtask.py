@@ -32,6 +32,7 @@ def _group_errors(orc, got, want):
     return out
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_aux_base_step_parity():
     wl, orc, gpu = _setup()
     for s in range(2):
@@ -62,6 +63,7 @@ def test_aux_base_step_parity():
     gpu.close()
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_aux_meta_step_parity():
     wl, orc, gpu = _setup()
     nw = orc.model.slices["Wmlm"]

@@ -332,7 +332,7 @@ def test_second_stream_changes_no_result():
     res = {}
     for mode in (0, 1):
         orc, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
-        gpu.lib.sama_dev_side_stream(ctypes.c_int32(mode)); gpu.lib.sama_dev_side_sink(ctypes.c_int32(mode))
+        gpu.lib.sama_dev_side_stream(ctypes.c_int32(2 * mode)); gpu.lib.sama_dev_side_sink(ctypes.c_int32(mode))   # 2: also for a pass this small
         try:
             for s in range(3):
                 (x, y), (xm, ym) = _batches(wl, s)
@@ -350,6 +350,37 @@ def test_second_stream_changes_no_result():
     assert abs(res[0][1]["SCALARS"][0] - res[1][1]["SCALARS"][0]) <= 1e-6 * res[0][1]["SCALARS"][0]
     for k in ("HYPERGRAD", "THETA", "LAMBDA"):
         assert rel_l2(res[1][1][k], res[0][1][k]) < 1e-4, k
+
+
+def _update_launches(gpu, batch):
+    """Launches of the Adam kernel in one base step: one on one stream; on two streams a layer's two ranges follow its
+    gradients and the rest comes behind them."""
+    gpu.profile(True)
+    try:
+        gpu.base_step(batch)
+        return gpu.profile_read()["adam"][0]
+    finally:
+        gpu.profile(False)
+
+
+def test_second_stream_switch_returns_to_the_default():
+    """sama_dev_side_stream: 0 keeps one stream, 2 takes two for any size, and 1 is the default again, which for a pass of
+    640 rows through two small layers is one stream; so is every value that is not one of the three."""
+    import ctypes
+    wl = make_workload(3, n_train=40, n_meta=12, **SMALL)
+    _, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    (x, y), _ = _batches(wl, 0)
+    tb = dev_batch(gpu, x, y)
+    try:
+        seen = [(-2, _update_launches(gpu, tb))]       # untouched
+        for mode in (0, 1, 2, 1, 2, -1):
+            gpu.lib.sama_dev_side_stream(ctypes.c_int32(mode))
+            seen.append((mode, _update_launches(gpu, tb)))
+    finally:
+        gpu.lib.sama_dev_side_stream(ctypes.c_int32(1))
+        gpu.close()
+    print(seen)
+    assert all((n > 2 * wl.dims[0]) if mode == 2 else (n == 1) for mode, n in seen), seen
 
 
 def test_single_sequence_batches():
@@ -375,8 +406,9 @@ def test_single_sequence_batches():
     gpu.close()
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_free_running_trajectory_is_reproducible_bit_for_bit():
-    """No floating-point atomics and a fixed order in every reduction, on two streams: two runs of the same 30
+    """No floating-point atomics and a fixed order in every reduction, on one stream and on two: two runs of the same 30
     iterations (unroll 2) from the same start end in the same bits."""
     wl = make_workload(3, n_train=40, n_meta=12, **SMALL)
     outs = []
@@ -394,6 +426,7 @@ def test_free_running_trajectory_is_reproducible_bit_for_bit():
         assert np.array_equal(outs[0][k], outs[1][k]), k
 
 
+@pytest.mark.usefixtures("backward_streams")
 @pytest.mark.parametrize("variant", ["sgd", "sgd_momentum", "sama_na"])
 def test_small_encoder_sgd_and_no_adaptation(variant):
     """The bf16 encoder with an SGD base solver (D = base lr) and with the adaptation switched off (SAMA-NA, D = 1):
@@ -426,6 +459,7 @@ def test_small_encoder_sgd_and_no_adaptation(variant):
     gpu.close()
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_padded_batches_small_encoder():
     """Sequence lengths (key-padding mask): base step and meta step against the oracle on a length mix that includes a
     one-token and a full sequence; then the invariants of padding on the GPU alone: full lengths give the bits of no
@@ -565,6 +599,7 @@ def test_out_of_range_ids_and_labels_are_clamped():
         assert np.array_equal(res[0][k], res[1][k]), k
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_non_finite_hypergradient_takes_back_the_early_nudge():
     """bf16 models nudge the GEMM block of theta in the pass that writes the +- halves, before the hypergradient exists.
     When the hypergradient then turns out not to be finite (a NaN planted in the weight net's output bias, which the
@@ -619,10 +654,11 @@ def test_eval_small_encoder_with_padding():
     gpu.close()
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_checkpoint_and_resume_continue_bit_for_bit():
     """The settable state (theta, the moments, the kept gradient, lambda and its moments, the counters) is everything a
     run needs: a fresh context that is handed the state of a run after 6 iterations continues with the bits of the
-    uninterrupted run (bf16 encoder, two streams, scheduled rates)."""
+    uninterrupted run (bf16 encoder, one stream and two, scheduled rates)."""
     wl = make_workload(3, n_train=40, n_meta=12, **SMALL)
     names = ("THETA", "M", "V", "G", "LAMBDA", "META_M", "META_V")
     rate = lambda k: 1e-3 * (1.0 - 0.05 * k)
@@ -651,6 +687,7 @@ def test_checkpoint_and_resume_continue_bit_for_bit():
     b.close()
 
 
+@pytest.mark.usefixtures("backward_streams")
 @pytest.mark.parametrize("d,heads,ffn", [(1280, 20, 1344), (2048, 32, 2048)])
 def test_wide_encoder(d, heads, ffn):
     """Hidden widths above 1024 (the LayerNorm kernels then keep eight 16-byte pieces of a row per lane): one base step

@@ -69,5 +69,6 @@ def test_graph_replay_mlp():
     _run(2)
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_graph_replay_small_encoder():
     _run(3, dict(n_train=40, n_meta=12, dims=(2, 192, 3, 320, 128, 600, 3), batch=5, meta_batch=3))

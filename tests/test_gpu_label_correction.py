@@ -80,6 +80,7 @@ def test_dominant_prior_reduces_to_reweighting_on_the_gpu():
     gpu_c.close(); gpu_r.close()
 
 
+@pytest.mark.usefixtures("backward_streams")
 def test_label_correction_small_encoder_bf16():
     small = dict(dims=(2, 192, 3, 320, 128, 600, 3), batch=5, meta_batch=3)
     wl = make_workload(3, n_train=40, n_meta=12, **small)
