@@ -2,6 +2,7 @@
 // sequence (no autograd).  x0 = LN(tok[ids] + pos); per layer x <- LN1(x + Attn(x)), x <- LN2(x + FFN(x));
 // logits = x_L[:, 0] Wc^T + bc.  Residual sums and every LayerNorm input stay fp32; GEMM operands are bf16.
 #include <algorithm>
+#include <cmath>
 #include "kernels.h"
 #include "model.h"
 
@@ -11,16 +12,19 @@ static bool g_side_sink = true;
 void encoder_side_stream(int mode) { g_side_stream = mode; }
 void encoder_side_sink(bool on) { g_side_sink = on; }
 namespace {
-// Whether a backward pass over `rows` token rows puts a layer's weight gradients and what follows them on the second stream.  What the
-// chain's kernels leave of the chip is worth it once they are long and many: the events between the streams cost the host, which
-// short kernels wait for, and the pass some ten microseconds at its end.
-// us per iteration of one base step, two streams / one, by rows x parameters of the layers: 0.9e9 (512 rows, 2 x 192) 617 / 587,
-// 4.8e9 (1024, 12 x 192) 3003 / 2923, 4.8e9 (512, 12 x 256) 3142 / 2961, 6.4e9 (2048, 4 x 256) 1320 / 1311, 7.2e9 (4096, 4 x 192)
-// 1488 / 1557, 10e9 (512, 12 x 384) 3668 / 3619, 13e9 (4096, 4 x 256) 1634 / 1705, 15e9 (1024, 4 x 576) 1792 / 1815, 19e9 (2048,
-// 12 x 256) 3794 / 3940, 46e9 (1024, 12 x 576) 5350 / 5546.
-inline bool side_wanted(int64_t rows, int64_t params) {
+// Whether a backward pass over `rows` token rows (of a padded batch: all of them) puts a layer's weight gradients and what follows
+// them on the second stream.  They run beside the next layer's chain, so a single layer gains nothing and pays for the join
+// (8192 rows of 1 x 512: 1151 us an iteration of one base step on two streams, 1071 on one).  With several layers it is worth it once
+// the chain's kernels are long enough, and the layers many enough, for what it costs: with an iteration's two backward passes 100 us of
+// host time for each layer and, at their ends, 70 to 110 us of the GPU's (what a single layer loses).  The line lies where rows x parameters of the layers x sqrt(rows / 1024) do, in 1e9, us
+// on two streams / one: 1.9 (512 rows, 12 x 192) 2948 / 2806, 7.2 (1024, 4 x 384) 1468 / 1408, 7.7 (512, 12 x 384) 3750 / 3686,
+// 9.1 (2048, 4 x 256) 1318 / 1313, 10.2 (2048, 2 x 384) 960 / 926, 10.9 (256, 12 x 768) 5536 / 5560, 12.9 (4096, 2 x 256) 878 / 898,
+// 14.5 (4096, 4 x 192) 1481 / 1548, 20.5 (2048, 4 x 384) 1750 / 1764, 36 (2048, 4 x 512) 2056 / 2124, 43 (4096, 12 x 192) 4334 / 4698.
+// Of 172 shapes (1 to 24 layers of 192 to 1024, 256 to 8192 rows, 16 of them padded) four take more than 1 % longer than on the other
+// side, at most 3.2 %; by the plain product of rows and parameters 19 (6.9 %), by that of one layer 18 (6.2 %): profiles/second_stream.md.
+inline bool side_wanted(int64_t rows, int layers, int64_t layer_params) {
   if (g_side_stream == 0 || g_side_stream == 2) return g_side_stream == 2;
-  return rows * params >= 7000000000ll;
+  return layers > 1 && (double)rows * (double)(layers * layer_params) * std::sqrt((double)rows / 1024.0) >= 1.05e10;
 }
 
 struct LayerOff { int64_t Wqkv, Wo, W1, W2, bqkv, bo, ln1g, ln1b, b1, b2, ln2g, ln2b; };
@@ -303,7 +307,7 @@ class EncoderModel : public Model {
     // depends on them, and the chain's launches (small dgrad tiles, LayerNorm, attention) leave room on the CUs.
     // Their inputs alternate between two buffer sets; the chain waits for the launches of two layers ago before it
     // overwrites a set, and the pass ends with both streams joined.
-    const bool two = side_wanted(M, L_ * ((int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_)) && ensure_side();
+    const bool two = side_wanted(M, L_, (int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_) && ensure_side();
     hipStream_t ss = two ? side_ : st;
     bool sink_used = false;
     for (int l = L_ - 1; l >= 0; --l) {

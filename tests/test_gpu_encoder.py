@@ -383,6 +383,32 @@ def test_second_stream_switch_returns_to_the_default():
     assert all((n > 2 * wl.dims[0]) if mode == 2 else (n == 1) for mode, n in seen), seen
 
 
+@pytest.mark.parametrize("L,d,B,two", [
+    (1, 512, 32, False), (12, 384, 4, False), (2, 192, 8, False), (2, 192, 48, True), (4, 256, 32, True)])
+def test_second_stream_by_default(L, d, B, two):
+    """Which models take the second stream when nobody asks: a single layer never does, of several those whose rows and layers
+    are worth it (both sides of the line, sizes that were measured), and a base step's bits are those of either form."""
+    import ctypes
+    import paper_2310_05674_amd as pkg
+    wl = make_workload(3, n_train=2 * B, n_meta=4, dims=(L, d, d // 64, 4 * d, 128, 600, 3), batch=B, meta_batch=2)
+    cfg = pkg.SamaConfig.make(wl.kind, wl.dims, H=wl.H, max_batch=B, max_meta_batch=2, base_lr=1e-3)
+    th, lam = init_theta(wl, 0.02), init_lambda(wl)
+    (x, y), _ = _batches(wl, 0)
+    out, launches = {}, {}
+    try:
+        for mode in (1, 0, 2):
+            gpu = pkg.Sama(cfg, th, lam)
+            gpu.lib.sama_dev_side_stream(ctypes.c_int32(mode))
+            launches[mode] = _update_launches(gpu, dev_batch(gpu, x, y))
+            out[mode] = {k: pull(gpu, k).copy() for k in ("G", "THETA", "M", "V")}
+            gpu.close()
+    finally:
+        gpu.lib.sama_dev_side_stream(ctypes.c_int32(1))
+    assert launches[0] < launches[2] and launches[1] == launches[2 if two else 0], launches
+    for k in out[1]:
+        assert np.array_equal(out[0][k], out[1][k]) and np.array_equal(out[0][k], out[2][k]), k
+
+
 def test_single_sequence_batches():
     """One train sequence and one meta sequence (M = 128 token rows: a single partial GEMM tile row)."""
     wl = make_workload(3, n_train=40, n_meta=12, **SMALL)
