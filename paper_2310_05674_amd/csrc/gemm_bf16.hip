@@ -12,11 +12,11 @@
 //   one whose contraction index is the strided one (dgrad's W, both operands of wgrad) is staged as it lies in
 //   memory, [k][row], and fetched with the transposing LDS read (ds_read_b64_tr_b16)
 //   the MFMA operands of k-step t + 1 are fetched while the MFMAs of step t issue, also across the slab boundary
-//   measured on MI355X: a CU takes in 57 B/clk where L2 holds the slabs, 40 from the last-level cache and 27 where the weights
-//   come from memory (about 128 outstanding 128-byte requests over the latency of each), and at the MFMA peak 256 x 256 tiles
-//   need 32 B/clk, 256 x 128 48, 128 x 128 64: small tiles are bound by this, and the weights of a product of few rows are
-//   fetched by the launch before it (k_ln_fwd, k_ln_bwd).  The largest tiles are bound by power: without any loads a
-//   launch of 256 x 128 hi + lo tiles of 109 us takes 98, at 1.75 GHz with the matrix cores busy 65 % of the time
+//   measured on MI355X: a CU takes in 56 B/clk where L2 holds the slabs, 40 from the last-level cache and 26 where the weights
+//   come from memory, and at the MFMA peak 256 x 256 tiles need 32 B/clk, 256 x 128 48, 128 x 128 64: small tiles are bound by
+//   this, and the weights of a product of few rows are fetched by the launch before it (k_ln_fwd, k_ln_bwd).  The loops of the largest
+//   tiles are bound by power: without any loads a launch of 256 x 128 hi + lo tiles of 111 us takes 96 in as many clocks, at 1.73 GHz
+//   instead of 1.50, with the matrix cores busy 65 % of the time (profiles/gemm_bounds.md)
 //   workgroup ids are remapped so that each XCD (own L2) works on a compact patch of tiles
 //   the accumulators leave through LDS so that every global access of the epilogue is a full row segment
 //
@@ -64,11 +64,12 @@ struct Tile {
   static constexpr int LDS_EPI = WAVES * 32 * EPI_LD * 4;
   static constexpr int LDS_BYTES = LDS_MAIN > LDS_EPI ? LDS_MAIN : LDS_EPI;
   // Whether the GELU epilogues look their values up (gelu.h).  The table comes into a stage that the last slab does not use, while
-  // that slab is multiplied, and stays clear of the epilogue's staging.  Computed, a value is 26 quarter-rate vector instructions,
-  // 6 us of the epilogue of 256 tiles of 256 x 128 in which the matrix cores stand still; looked up it is seven and an LDS read.
-  // us computed / looked up, forward: 2048 x 4096 x 1024 (256 x 128 tiles) 39.9 / 35.9, 4096 x 3072 x 768 (256 x 192) 48.2 / 42.3;
-  // backward 41.1 / 38.7, 51.6 / 47.0; with 128 x 128 tiles, 1024 x 3072 x 768, 19.8 / 18.5.  Smaller tiles compute: the table
-  // would be more to load than a slab of them.
+  // that slab is multiplied, and stays clear of the epilogue's staging.  Computed, a value is 26 quarter-rate vector instructions
+  // in which the matrix cores stand still; looked up it is seven and an LDS read.  us computed / looked up, forward: 2048 x 4096 x
+  // 1024 (256 x 128 tiles) 37.3 / 34.5, 4096 x 3072 x 768 (256 x 192) 47.1 / 40.8; backward 40.1 / 37.7, 50.9 / 45.7; with 128 x 128
+  // tiles, 1024 x 3072 x 768, 19.6 / 18.0.  The 128 x 64 and smaller tiles compute: the table would be as much to load as a slab
+  // of them or more.  The 128 x 96 ones compute too, though looking up is 1.1 to 3.2 us faster in each of twelve products timed both
+  // ways (1024 x 3072 x 768 forward 19.2 / 17.9: profiles/gemm_bounds.md); in ten of them another tile is faster than either.
   static constexpr bool TAB = DUAL && PW > 0 && BM * BN >= 128 * 128;
   static_assert(!TAB || (NSTAGE >= 2 && STAGE_BYTES >= GELU_TAB_BYTES && LDS_MAIN - GELU_TAB_BYTES >= LDS_EPI), "room for the table");
   static_assert(A_BYTES % (1024 * LW) == 0 && B_BYTES % (1024 * LW) == 0, "slab must split into whole wave loads");
@@ -571,8 +572,9 @@ typedef Tile<32, 32, 64, 1, 1, 6, true, 2> D9;       // two workgroups per CU
 // on every CU and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.
 // The numbers are robust least-squares fits of the logarithms over 2561 timed problems (widths 192 to 2048, FFN 2 and 4 times that,
 // 64 to 8192 rows: NT, NN, pairs of NT, a layer's four TN problems in a launch; the vocabulary head's products over 8192 to
-// 50304 tokens; weights cold): profiles/gemm_tile_costs.md.  Picking by them takes 0.6% (hi + lo) and 1.0% (single-term) longer
-// in total than the fastest tile of each problem, the same on problems left out of the fit; the head's products 1.5 to 3%.
+// 50304 tokens; weights cold), taken when the GELU epilogues computed their factors and averaged over the kinds of epilogue.  On the
+// times of the kernels as they are, picking by them takes 0.9% (hi + lo) and 1.2% (single-term) longer in total than the fastest
+// tile of each problem, a fit of these 0.6% and 1.2%; GELU backward 1.7%, the head's products 0.4 to 3.3%: profiles/gemm_tile_costs.md.
 struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; };
 constexpr TileCost SINGLE[] = {
     {1, 256, 256, 1, 1.282, 1.816, 0, 0, 8.26}, {2, 256, 192, 1, 1.060, 1.218, 0, 0, 8.62},
@@ -610,8 +612,8 @@ double launch_cost(const TileCost& c, const GemmBf16Args* p, int count, int shar
 
 // How many rows of a padded batch are in use only the device knows, and how long texts are is the caller's: the tile is the one
 // that costs least in total over batches a quarter, half, three quarters and all in use.  Longer than the fastest tile of a
-// product at each of these (geometric means, the measurements of the fit): 16, 5, 5 and 8%; choosing for one share in between, two
-// thirds, 31, 11, 4 and 7%, for all rows 38, 16, 4 and 1%.
+// product at each of these (geometric means over the same timed problems): 16, 6, 7 and 9%; choosing for one share in between, two
+// thirds, 30, 11, 5 and 8%, for all rows 37, 16, 5 and 2%.
 template <int N>
 int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count) {
   bool padded = false;
