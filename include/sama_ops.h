@@ -35,9 +35,10 @@ sama_status sama_op_gemm_bf16_batch(int32_t count, const void* const* A, const v
                                     float* const* C32, const int32_t* M, const int32_t* N, const int32_t* K,
                                     int32_t a_trans, int32_t b_trans, void* hip_stream);
 
-/* The two GELU epilogues of the encoder's FFN on a dense hi + lo contraction p = A . (B + B2): with aux16 = NULL the forward
- * form, C32 = gelu(bf16(p)) and pre16 = bf16(p); with aux16 (bf16 [M x N]) the backward form, C32 = p * gelu'(aux16), b_trans as
- * above.  table: DEVICE scratch of sama_op_gelu_table_bytes() bytes, 16-byte aligned, filled by the call. */
+/* For tests (the encoder launches the kernels itself): the two GELU epilogues of the encoder's FFN on a dense hi + lo
+ * contraction p = A . (B + B2).  With aux16 = NULL the forward form, C32 = gelu(bf16(p)) and pre16 = bf16(p); with aux16
+ * (bf16 [M x N]) the backward form, C32 = p * gelu'(aux16), b_trans as above.  table: DEVICE scratch of
+ * sama_op_gelu_table_bytes() bytes, 16-byte aligned, filled by the call. */
 size_t sama_op_gelu_table_bytes(void);
 sama_status sama_op_gemm_bf16_gelu(const void* A, const void* B, const void* B2, int32_t b_trans, int32_t M, int32_t N, int32_t K,
                                    const void* aux16, void* pre16, float* C32, void* table, void* hip_stream);

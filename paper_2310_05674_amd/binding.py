@@ -336,7 +336,7 @@ def op_gemm_bf16_batch(As, Bs, outs, *, a_trans=False, b_trans=True, B2s=None):
 
 
 def op_gemm_bf16_gelu(A, B, B2, out32, *, b_trans=True, aux16=None, pre16=None):
-    """The encoder's GELU epilogues through sama_op_gemm_bf16_gelu: forward without aux16, backward with it (dense 2-D bf16
+    """For tests: the encoder's GELU epilogues through sama_op_gemm_bf16_gelu, forward without aux16, backward with it (dense 2-D bf16
     operands, fp32 output)."""
     import torch
     L = load_library()

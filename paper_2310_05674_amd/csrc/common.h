@@ -89,7 +89,7 @@ __device__ __forceinline__ T join_wave(T x, F op) { return join_group(join16(joi
 __device__ __forceinline__ float wave_sum(float x) { return join_wave(x, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ double wave_sum(double x) { return join_wave(x, [](double a, double b) { return a + b; }); }
 
-// Sum over a block of up to 1024 threads in a fixed order: wave shuffles, then the wave leaders' values
+// Sum over a block of up to 1024 threads in a fixed order: joined over the lanes of a wave, then the wave leaders' values
 // added serially from LDS.  Every thread gets the result.  `red` holds >= 16 floats.
 __device__ __forceinline__ float block_sum(float x, float* red) {
   x = wave_sum(x);

@@ -16,12 +16,13 @@ namespace {
 // them on the second stream.  They run beside the next layer's chain, so a single layer gains nothing and pays for the join
 // (8192 rows of 1 x 512: 1151 us an iteration of one base step on two streams, 1071 on one).  With several layers it is worth it once
 // the chain's kernels are long enough, and the layers many enough, for what it costs: with an iteration's two backward passes 100 us of
-// host time for each layer and, at their ends, 70 to 110 us of the GPU's (what a single layer loses).  The line lies where rows x parameters of the layers x sqrt(rows / 1024) do, in 1e9, us
-// on two streams / one: 1.9 (512 rows, 12 x 192) 2948 / 2806, 7.2 (1024, 4 x 384) 1468 / 1408, 7.7 (512, 12 x 384) 3750 / 3686,
-// 9.1 (2048, 4 x 256) 1318 / 1313, 10.2 (2048, 2 x 384) 960 / 926, 10.9 (256, 12 x 768) 5536 / 5560, 12.9 (4096, 2 x 256) 878 / 898,
-// 14.5 (4096, 4 x 192) 1481 / 1548, 20.5 (2048, 4 x 384) 1750 / 1764, 36 (2048, 4 x 512) 2056 / 2124, 43 (4096, 12 x 192) 4334 / 4698.
-// Of 172 shapes (1 to 24 layers of 192 to 1024, 256 to 8192 rows, 16 of them padded) four take more than 1 % longer than on the other
-// side, at most 3.2 %; by the plain product of rows and parameters 19 (6.9 %), by that of one layer 18 (6.2 %): profiles/second_stream.md.
+// host time for each layer and, at their ends, 65 to 120 us of the GPU's (what a single layer loses).  The line lies where rows x
+// parameters of the layers x sqrt(rows / 1024) do; in 1e9, us on two streams / one: 1.9 (512 rows, 12 x 192) 2948 / 2806, 7.2 (1024,
+// 4 x 384) 1468 / 1408, 7.7 (512, 12 x 384) 3750 / 3686, 9.1 (2048, 4 x 256) 1318 / 1313, 10.2 (2048, 2 x 384) 960 / 926, 10.9 (256,
+// 12 x 768) 5536 / 5560, 12.9 (4096, 2 x 256) 878 / 898, 14.5 (4096, 4 x 192) 1481 / 1548, 20.5 (2048, 4 x 384) 1750 / 1764, 36 (2048,
+// 4 x 512) 2056 / 2124, 43 (4096, 12 x 192) 4334 / 4698.  Of 172 shapes (1 to 24 layers of 192 to 1024, 256 to 8192 rows, 16 of them
+// padded) four take more than 1 % longer than on the other side, at most 3.2 %; by the plain product of rows and parameters 19
+// (6.9 %), by that of one layer 18 (6.2 %): profiles/second_stream.md.
 inline bool side_wanted(int64_t rows, int layers, int64_t layer_params) {
   if (g_side_stream == 0 || g_side_stream == 2) return g_side_stream == 2;
   return layers > 1 && (double)rows * (double)(layers * layer_params) * std::sqrt((double)rows / 1024.0) >= 1.05e10;
@@ -135,10 +136,12 @@ class EncoderModel : public Model {
   // that come from memory, and a LayerNorm leaves most of its bandwidth unused.  With the rows of a long product there is
   // time for both, and fetching ahead only delays the LayerNorm; and what the last-level cache (256 MB) holds from one pass to the
   // next needs no fetching: when scoring, the two halves of the weights; in training, with the optimizer's state, 20 bytes each.
-  // Without / with it, 12 x 768: scoring 128 rows 676 / 644 us, 512 825 / 735, 2048 1378 / 1251, 4096 1900 / 1897; base step of 1024
-  // rows 2964 / 2820, 2048 3869 / 3670, 4096 5519 / 5547, 4096 padded 4832 / 4728.  24 x 1024: base step of 512 rows 6754 / 6519, 2048 10697 / 10676.
-  // The stacked passes count their rows together (24 x 1024 iteration of 1024 rows with / without them 19.56 / 19.28 ms, 12 x 768 of 1024 7.15 /
-  // 7.24).  Scoring with 12 x 576 (177 MB) 699 / 708, base step of 2048 rows of 8 x 384 (260 MB with the state) 1358 / 1317.
+  // us without it / with it, where the rule has it: 12 x 768 scoring 128 rows 678 / 647, 512 828 / 738, 2048 1378 / 1237, base step of 1024 rows
+  // 3039 / 2831, of 2048 3918 / 3659; 24 x 1024 base step of 512 rows 6828 / 6422; 12 x 768 iteration of 1024 rows 7670 / 7163; base step of
+  // 2048 rows of 8 x 384 (260 MB with the state) 1436 / 1390.  Without it / with it, where the rule leaves it out: 12 x 768 scoring 4096 rows
+  // 1893 / 1864, base step of 4096 5471 / 5454, padded 4812 / 4802; 24 x 1024 base step of 2048 rows 10418 / 10350; scoring 128 rows of 12 x 576
+  // (177 MB) 542 / 551.  The stacked passes count the rows of both: left out of them, as the rule does at 24 x 1024 and 1024 rows, an
+  // iteration takes 18867 us, with it there too 18928.
   WeightsAhead weights_ahead(const PassWeights* w, int nw, bool scoring, int64_t off, int64_t n, int rows, const int32_t* in_use) const {
     WeightsAhead a{};
     a.max_rows = (2 << 20) / (nw * d_);

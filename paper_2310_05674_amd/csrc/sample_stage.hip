@@ -369,8 +369,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
 #pragma unroll
   for (int u = 0; u < PAIRS; ++u) gW2[u] = gWp[u] = gWy[u] = gb2[u] = 0.0;
 
-  static_assert(ST_MAX_RUN <= ST_SAMPLES, "one trip");
-  do {                                                    // every thread takes part (barriers with CORR)
+  static_assert(ST_MAX_RUN <= ST_SAMPLES, "a sample for each group of lanes");
+  {                                                       // every thread takes part (barriers with CORR)
     const int i = i_begin + grp;
     const bool live = i < i_end;
     const int ic = i_own;
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_sample_stage(SampleStageArgs a, 
         }
       }
     }
-  } while (false);
+  }
 
   const int total = nblk * gridDim.y;      // workgroups whose partials make the result
   if (a.mode != STAGE_GLAM) {
