@@ -86,7 +86,7 @@ sama_status sama_op_nudge(float* theta, const float* vdir, const float* eps_ptr,
  * thread-safe.
  *  - sama_dev_gemm_shape(id): every bf16 GEMM launch uses block tile `id`: 1..8 are the single-term tiles (a hi+lo
  *    problem then runs as one contraction over the concatenated operands, which rounds differently from the hi+lo
- *    tiles), 11..19 the hi+lo tiles (single-term problems ignore them); 0 = the heuristic (default).  Within a class
+ *    tiles), 11..20 the hi+lo tiles (single-term problems ignore them, 20 is for K % 128 = 0); 0 = the heuristic (default).  Within a class
  *    every tile gives the same bits.
  *  - sama_dev_side_stream(0): the encoder's backward passes keep every launch on the context's stream (a per-kernel profile
  *    wants one stream); 1 = default: weight gradients and optimizer slices run on the library's second stream where rows and

@@ -1,7 +1,11 @@
-// bf16 x bf16 -> fp32 contraction on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16) for the encoder's linear
+// bf16 x bf16 -> fp32 contraction on the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16) for the encoder's linear
 // layers: forward (X W^T), dgrad (dY W) and wgrad (dY^T X) are one kernel template over the storage of its two
 // operands.
 //
+//   16 x 16 x 32 and not 32 x 32 x 16: the large tiles are bound by power, and an issue loop fed from registers (256 workgroups of 8 waves,
+//   normal values) holds 2030 TFLOP/s at 1.98 GHz with the one and 1790 at 1.76 with the other.  Both add 16 products at a time in
+//   order and agree bit for bit.  us per launch, 32 x 32 x 16 / 16 x 16 x 32: 8192 x 1024 x 4096 hi + lo (256 x 128 tiles) 110 / 97,
+//   8192 x 4096 x 1024 123 / 115
 //   operand slabs go global -> LDS directly (global_load_lds_dwordx4, 1 KB per wave instruction) into dense,
 //   XOR-swizzled stages, NSTAGE - 1 slabs in flight, one barrier per slab; no staging registers
 //   most tiles have waves that do nothing but issue those loads: a wave that issues a slab's loads itself waits for the
@@ -11,18 +15,17 @@
 //   an operand whose contraction index is contiguous in memory is staged [row][k] and fetched with 16-byte reads;
 //   one whose contraction index is the strided one (dgrad's W, both operands of wgrad) is staged as it lies in
 //   memory, [k][row], and fetched with the transposing LDS read (ds_read_b64_tr_b16)
-//   the MFMA operands of k-step t + 1 are fetched while the MFMAs of step t issue, also across the slab boundary
+//   the MFMA operands of the next piece of a slab are fetched between the MFMAs of the current one, also across the slab boundary
 //   measured on MI355X: a CU takes in 56 B/clk where L2 holds the slabs, 40 from the last-level cache and 26 where the weights
 //   come from memory, and at the MFMA peak 256 x 256 tiles need 32 B/clk, 256 x 128 48, 128 x 128 64: small tiles are bound by
-//   this, and the weights of a product of few rows are fetched by the launch before it (k_ln_fwd, k_ln_bwd).  The loops of the largest
-//   tiles are bound by power: without any loads a launch of 256 x 128 hi + lo tiles of 111 us takes 96 in as many clocks, at 1.73 GHz
-//   instead of 1.50, with the matrix cores busy 65 % of the time (profiles/gemm_bounds.md)
+//   this, and the weights of a product of few rows are fetched by the launch before it (k_ln_fwd, k_ln_bwd).  (profiles/gemm_bounds.md)
 //   workgroup ids are remapped so that each XCD (own L2) works on a compact patch of tiles
-//   the accumulators leave through LDS so that every global access of the epilogue is a full row segment
+//   a launch starts with an empty instruction cache, so what runs before a workgroup's first load and behind its last product is short
+//   straight code
 //
 // For the theta +- eps v passes of Eq. 5 and the direct-gradient pass the weight operand is hi + lo (two bf16
-// halves).  DUAL tiles stage the A slab once together with the hi and the lo slab of B and issue two MFMAs per A
-// operand, so A is neither loaded nor fetched twice.
+// halves).  DUAL tiles stage the A slab once together with the hi and the lo slab of B, and an MFMA contracts 16 values of A with those of hi,
+// then with those of lo.
 //
 // Several independent problems of one storage class can share a launch (the + and - pass of Eq. 5, the four weight
 // gradients of a layer): more tiles per launch for the small per-layer shapes.
@@ -31,6 +34,7 @@
 // pre-activation and the activation), GELU backward (multiplies by gelu'(pre)), fp32 and/or bf16 stores.  The large hi + lo
 // tiles look the GELU factors up in a table that their loading waves bring into LDS during the last slab.
 #include <type_traits>
+#include <utility>
 #include "common.h"
 #include "gelu.h"
 #include "kernels.h"
@@ -40,38 +44,37 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void gvoid;
 constexpr int LDS_MAX = 160 * 1024;
 
-// PW: waves that only load (0: the multiplying waves load for themselves).  SB: see the kernel.
-template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NSTAGE_, bool DUAL_, int PW_ = 0, bool SB_ = false>
+// PW: waves that only load (0: the multiplying waves load for themselves).  YP: 16-column fragments of B per piece of a k-step, 0: all.
+// RD: how the fetches of a piece lie between the products of the one before: n: over the first 1 / n of them; 0: with a strided operand right
+// before its own products (fewer registers, the order left to the compiler: 2 to 8% faster with three stages and for 256 x 256), else all
+// ahead of those products.
+template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NSTAGE_, bool DUAL_, int PW_ = 0, int YP_ = 0, int RD_ = 2>
 struct Tile {
-  static constexpr int PW = PW_;
-  static constexpr bool SB = SB_;
+  static constexpr int PW = PW_, RD = RD_;
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_, NSTAGE = NSTAGE_;
   static constexpr bool DUAL = DUAL_;
   static constexpr int WAVES = WGM * WGN, LW = PW > 0 ? PW : WAVES, THREADS = (WAVES + PW) * 64;   // multiplying, loading
-  static constexpr int WM = BM / WGM, WN = BN / WGN, XT = WM / 32, YT = WN / 32;
+  static constexpr int WM = BM / WGM, WN = BN / WGN, XT = WM / 16, YT = WN / 16;
+  static constexpr int YP = YP_ > 0 ? YP_ : YT, NP = YT / YP;               // pieces of a k-step
+  static_assert(WM % 16 == 0 && WN % 32 == 0 && YT % YP == 0, "wave tiles");
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + (DUAL ? 2 : 1) * B_BYTES;
   static constexpr int NLA = A_BYTES / 1024 / LW, NLB = B_BYTES / 1024 / LW;   // 1 KB loads of a loading wave per slab
   static constexpr int NL = NLA + (DUAL ? 2 : 1) * NLB;
-  static_assert(LDS_MAX >= NSTAGE * STAGE_BYTES, "stages exceed the 160 KB of LDS");
-  static constexpr int LDS_MAIN = NSTAGE * STAGE_BYTES;
-  static constexpr int EPI_LD = WN + 8;   // 4 rows apart = 32 banks apart: the two lane halves of a staging write do not collide
-  static constexpr int LDS_EPI = WAVES * 32 * EPI_LD * 4;
-  static constexpr int LDS_BYTES = LDS_MAIN > LDS_EPI ? LDS_MAIN : LDS_EPI;
+  static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;
+  static_assert(LDS_MAX >= LDS_BYTES, "stages exceed the 160 KB of LDS");
   // Whether the GELU epilogues look their values up (gelu.h).  The table comes into a stage that the last slab does not use, while
-  // that slab is multiplied, and stays clear of the epilogue's staging.  Computed, a value is 26 quarter-rate vector instructions
-  // in which the matrix cores stand still; looked up it is seven and an LDS read.  us computed / looked up, forward: 2048 x 4096 x
-  // 1024 (256 x 128 tiles) 37.3 / 34.5, 4096 x 3072 x 768 (256 x 192) 47.1 / 40.8; backward 40.1 / 37.7, 50.9 / 45.7; with 128 x 128
-  // tiles, 1024 x 3072 x 768, 19.6 / 18.0.  The 128 x 64 and smaller tiles compute: the table would be as much to load as a slab
-  // of them or more.  The 128 x 96 ones compute too, though looking up is 1.1 to 3.2 us faster in each of twelve products timed both
-  // ways (1024 x 3072 x 768 forward 19.2 / 17.9: profiles/gemm_bounds.md); in ten of them another tile is faster than either.
-  static constexpr bool TAB = DUAL && PW > 0 && BM * BN >= 128 * 128;
-  static_assert(!TAB || (NSTAGE >= 2 && STAGE_BYTES >= GELU_TAB_BYTES && LDS_MAIN - GELU_TAB_BYTES >= LDS_EPI), "room for the table");
+  // that slab is multiplied.  Computed, a value is 26 quarter-rate vector instructions in which the matrix cores stand still; looked up it
+  // is seven and an LDS read.  us computed / looked up, forward: 2048 x 4096 x 1024 (256 x 128 tiles) 37.3 / 34.5, 4096 x 3072 x 768 (256 x
+  // 192) 47.1 / 40.8, 1024 x 3072 x 768 (128 x 128) 19.6 / 18.0, (128 x 96) 19.2 / 17.9.  The 128 x 64 and smaller tiles compute: the table
+  // would be as much to load as a slab of them or more.
+  static constexpr bool TAB = DUAL && PW > 0 && BM * BN >= 128 * 96;
+  static_assert(!TAB || (NSTAGE >= 2 && STAGE_BYTES >= GELU_TAB_BYTES), "room for the table");
   static_assert(A_BYTES % (1024 * LW) == 0 && B_BYTES % (1024 * LW) == 0, "slab must split into whole wave loads");
   static_assert(NL * (NSTAGE - 2) <= 63, "vmcnt range");
 };
@@ -80,48 +83,73 @@ struct Tile {
 // `ldsoff` of an operand's dense LDS stage.
 //   KC (contraction contiguous, storage [rows][k]): stage [R][BK]; the 16-byte chunk index within a row is XORed
 //     with (row / RP) % NCH so that 16 consecutive rows at one logical chunk fill all 64 banks.
-//   KS (contraction strided, storage [k][rows]): stage [BK][R]; the 64-byte chunk index within a k-row is XORed with
-//     chunk_swizzle(k-row) so that the four k-rows one transposing read touches fill all 64 banks.
+//   KS (contraction strided, storage [k][rows]): stage [BK][R]; the 32-byte chunk index within a k-row is XORed with
+//     chunk_swizzle(k-row) so that the eight k-rows that half a wave of a transposing read touches fill all 64 banks.
 // Rows past `nrows` are clamped (their products land in outputs the epilogue never stores).
-// A k-row of R values is R / 32 chunks; four consecutive k-rows have to put one chunk each into the four quarters of the
-// banks.  Rows a multiple of four chunks long all start at the same bank, rows of two chunks pairwise, rows of six at
-// alternating halves; rows of one or three chunks are spread already.
+// A k-row of R values is R / 16 chunks of 32 bytes.  Half a wave reads one chunk of the k-rows 0..3 and 8..11 (or these plus 4, 16 or
+// 20), and the eight have to lie in eight different eighths of the banks.  Rows a multiple of eight chunks long all start at the same
+// bank; rows of four or twelve chunks at two alternating halves, so that two bits have to tell the four k-rows of one parity apart; rows of two
+// or six chunks spread four neighbours, and one bit tells k-rows eight apart.
 template <int R>
 __device__ __forceinline__ int chunk_swizzle(int kr) {
-  constexpr int NC = R / 32;
-  static_assert(NC % 4 == 0 || NC == 1 || NC == 2 || NC == 3 || NC == 6, "tile width");
-  return NC % 4 == 0 ? (kr & 3) : (NC == 2 || NC == 6) ? ((kr >> 1) & 1) : 0;
+  constexpr int NC = R / 16;
+  static_assert(NC % 8 == 0 || NC == 4 || NC == 12 || NC == 2 || NC == 6, "tile width");
+  return NC % 8 == 0 ? (kr & 3) | ((kr >> 1) & 4) : NC % 4 == 0 ? ((kr >> 1) & 1) | ((kr >> 2) & 2) : (kr >> 3) & 1;
 }
 template <bool KC, int R, int BK>
-__device__ __forceinline__ uint32_t piece_offset(int ldsoff, int row0, int nrows, int64_t ld) {
+__device__ __forceinline__ uint32_t piece_offset(uint32_t ldsoff, uint32_t row0, uint32_t nrows, uint32_t ld) {
   if (KC) {
-    constexpr int RB = BK * 2, RP = 256 / RB, NCH = RB / 16;
-    const int r = ldsoff / RB, p = (ldsoff % RB) / 16;
-    const int c = p ^ ((r / RP) % NCH);
-    return (uint32_t)(((int64_t)min(row0 + r, nrows - 1) * ld + c * 8) * 2);
+    constexpr uint32_t RB = BK * 2, RP = 256 / RB, NCH = RB / 16;
+    const uint32_t r = ldsoff / RB, p = (ldsoff % RB) / 16;
+    const uint32_t c = p ^ ((r / RP) % NCH);
+    return min(row0 + r, nrows - 1) * ld * 2 + c * 16;
   } else {
-    constexpr int RBS = R * 2;
-    const int kr = ldsoff / RBS, q16 = (ldsoff % RBS) / 16;
-    const int ql = (((q16 >> 2) ^ chunk_swizzle<R>(kr)) << 2) | (q16 & 3);
-    return (uint32_t)(((int64_t)kr * ld + min(row0 + ql * 8, nrows - 8)) * 2);
+    constexpr uint32_t RBS = R * 2;
+    const uint32_t kr = ldsoff / RBS, q16 = (ldsoff % RBS) / 16;
+    const uint32_t ql = (((q16 >> 1) ^ (uint32_t)chunk_swizzle<R>((int)kr)) << 1) | (q16 & 1);
+    return kr * ld * 2 + min(row0 + ql * 8, nrows - 8) * 2;
+  }
+}
+// The offsets of the NLOADS loads of wave `lw` of LW, which lie LW KB apart in the stage.  Where the swizzle repeats after P loads and no row
+// is clamped, load q is load q - P a uniform distance further on: few instructions, because all of them are fetched (from L2, the instruction
+// cache is empty when a launch starts) before a workgroup's first load leaves.
+template <bool KC, int R, int BK, int LW, int NLOADS>
+__device__ __forceinline__ void load_offsets(uint32_t (&off)[NLOADS], uint32_t lw, uint32_t lane, uint32_t row0, uint32_t nrows, uint32_t ld) {
+  constexpr uint32_t ROW = KC ? BK * 2 : R * 2;     // bytes of a row of the stage
+  auto repeats = [](int p) { return p * LW * 1024 % ROW == 0 && p * LW * 1024 / ROW % 16 == 0; };
+  constexpr int P = repeats(1) ? 1 : repeats(2) ? 2 : repeats(3) ? 3 : NLOADS;
+#pragma unroll
+  for (int q = 0; q < NLOADS && q < P; ++q) off[q] = piece_offset<KC, R, BK>((q * LW + lw) * 1024 + lane * 16, row0, nrows, ld);
+  if constexpr (P < NLOADS) {
+    if (!KC || row0 + R <= nrows) {   // (of a strided operand the columns are clamped, the same in each load)
+      const uint32_t step = P * LW * 1024 / ROW * ld * 2;
+#pragma unroll
+      for (int q = P; q < NLOADS; ++q) off[q] = off[q - P] + step;
+    } else {
+#pragma unroll
+      for (int q = P; q < NLOADS; ++q) off[q] = piece_offset<KC, R, BK>((q * LW + lw) * 1024 + lane * 16, row0, nrows, ld);
+    }
   }
 }
 
-// MFMA operand (8 contraction values k = ks*16 + 8*(lane/32) + 0..7 of tile row tb + lane%32) out of a swizzled stage.
-// `lo` is the lane-dependent part precomputed by fetch_lane_offset, `tb` the first row of the 32-row tile.
-template <bool KC, int R, int BK>
-__device__ __forceinline__ int fetch_lane_offset(int lane, int ks_or_tile) {
+// MFMA operand out of a swizzled stage: the lane-dependent part of its address, for a k-step (KC) or for a 16-row fragment of the tile
+// (KS).  A lane has 8 contraction values of tile row tb + lane % 16: of a single-term product k = 32 ks + 8 (lane / 16) + 0..7; of a hi + lo
+// one 16 ks + 8 (lane / 16 % 2) + 0..7, lanes 0..31 of the hi half of B and 32..63 of the lo half, and A the same in both: the matrix core adds
+// the 32 products of an instruction 16 at a time in order, so that one instruction is 16 of hi, then 16 of lo.
+template <bool KC, int R, int BK, bool HALVES>
+__device__ __forceinline__ int fetch_lane_offset(int lane, int ks_or_frag) {
+  const int part = HALVES ? (lane >> 4) & 1 : lane >> 4;
   if (KC) {
     constexpr int RB = BK * 2, RP = 256 / RB, NCH = RB / 16;
-    const int rl = lane & 31, hi = lane >> 5;
+    static_assert(16 % RP == 0 && (16 / RP) % NCH == 0, "the swizzle repeats from fragment to fragment");
+    const int rl = lane & 15;
     const int s = (rl / RP) % NCH;
-    return rl * RB + (((2 * ks_or_tile + hi) ^ s) * 16);                  // per ks
+    return rl * RB + ((((HALVES ? 2 : 4) * ks_or_frag + part) ^ s) * 16);
   } else {
     constexpr int RBS = R * 2;
-    const int g = lane >> 4, j = lane & 15;
-    const int cc = ks_or_tile;                                            // 64-byte chunk of the tile = tile_row0 / 32
-    const int kr = 8 * (g >> 1) + (j >> 2);                               // the swizzle is the same for kr + 4 and kr + 16
-    return kr * RBS + ((cc ^ chunk_swizzle<R>(kr)) * 64) + (16 * (g & 1) + 4 * (j & 3)) * 2;   // per tile
+    const int j = lane & 15;
+    const int kr = 8 * part + (j >> 2);                                   // the swizzle is the same for kr + 4, kr + 16 and kr + 32
+    return kr * RBS + ((ks_or_frag ^ chunk_swizzle<R>(kr)) * 32) + 8 * (j & 3);
   }
 }
 
@@ -136,201 +164,155 @@ __device__ __forceinline__ void wait_loads(int younger) {
   }
 }
 
-struct GemmBatch {
-  GemmBf16Args p[GEMM_MAX_BATCH];
-  int first_tile[GEMM_MAX_BATCH + 1];   // tile ids [first_tile[k], first_tile[k + 1]) belong to problem k
-  int count, group;
-};
-
+// What the loop needs of a problem.
 struct LoopArgs {
   const bf16_t *A, *B, *B2;
-  int64_t lda, ldb;
+  uint32_t lda, ldb;
   int M, N, K, act;
-  const float* gelu_tab;
   const int32_t* rows;
-  __device__ __forceinline__ void pin() {   // keeps the reads where they are
-    asm("" : "+s"(A), "+s"(B), "+s"(B2), "+s"(lda), "+s"(ldb), "+s"(M), "+s"(N), "+s"(K), "+s"(act), "+s"(gelu_tab), "+s"(rows));
-  }
+  const float* gelu_tab;
 };
-__device__ __forceinline__ LoopArgs loop_args(const GemmBf16Args& a) { return LoopArgs{a.A, a.B, a.B2, a.lda, a.ldb, a.M, a.N, a.K, a.act, a.gelu_tab, a.rows}; }
+__host__ __device__ __forceinline__ LoopArgs loop_args(const GemmBf16Args& a) {
+  return LoopArgs{a.A, a.B, a.B2, (uint32_t)a.lda, (uint32_t)a.ldb, a.M, a.N, a.K, a.act, a.rows, a.gelu_tab};
+}
+struct GemmBatch {
+  LoopArgs first;      // of problem 0
+  int ntiles, tiles_per_xcd, count, group;
+  int first_tile[GEMM_MAX_BATCH + 1];   // tile ids [first_tile[k], first_tile[k + 1]) belong to problem k
+  int kind[GEMM_MAX_BATCH];             // of each epilogue
+  GemmBf16Args p[GEMM_MAX_BATCH];
+};
+enum { EPI_ANY, EPI_C16, EPI_C32, EPI_RES32, EPI_GELU_FWD, EPI_GELU_BWD };
 
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>   // f(0), ..., f(N - 1) with constants
+__device__ __forceinline__ void static_for(F f) { static_for_each(std::make_integer_sequence<int, N>{}, f); }
+
+// a / b for a below 2^20 and b > 0, both the same in every lane: (a + 1/2) / b is at least 1 / (2 b) from any whole number, a relative
+// distance above 2^-21, and the approximate quotient is closer to it than that.
+__device__ __forceinline__ uint32_t small_quotient(uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_readfirstlane((uint32_t)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b)));
+}
+constexpr int SMALL_TILES = 1 << 20;
+
+// What runs before a workgroup's first load is short, and so is what the loading waves alone run: with 400 instructions of index arithmetic it
+// took 1.8 to 2.7 us from a workgroup's start to its first load, three quarters of it waiting for instructions; with the 150 here 0.5
+// to 0.6 us.  us per launch before / after, hi + lo: 128 x 3072 x 768 7.4 / 6.5, 2048 x 1024 x 1024 11.1 / 10.4, 2048 x 4096 x 1024 30.9 / 29.3.
 template <typename T, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int ntiles, int tiles_per_xcd) {
+__global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) {
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, XT = T::XT, YT = T::YT, NSTAGE = T::NSTAGE, WAVES = T::WAVES;
   constexpr bool DUAL = T::DUAL;
-  // Whether the operands of a k-step are fetched right before it (fewer registers, the order left to the compiler) instead of
-  // during the step before.  With the transposing reads of a strided operand the three-stage tiles are 7-9% faster that way.
-  constexpr bool SB = T::SB || (!B_KC && T::PW > 0 && NSTAGE == 3);
+  constexpr int RD = (DUAL && !B_KC && NSTAGE == 3) || (T::RD == 0 && !(A_KC && B_KC)) ? 0 : T::RD == 0 ? 9 : T::RD;   // see Tile
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wr = (wave / T::WGN) * T::WM, wc = (wave % T::WGN) * T::WN;
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // XCD-aware order: workgroups are dealt round-robin to the 8 XCDs; each XCD gets a contiguous run of tile ids, and
   // tile ids walk down `group` tile rows before moving one tile column to the right, so that the tiles in flight on
   // one XCD form a compact patch (few distinct A and B panels in its L2).
   // Where the rows in use are known on the device only, the launch has the tiles of all rows, and the order is made here over
   // those in use (the problems of a batch then have the same rows).
-  const int32_t* const in_use = batch.p[0].rows;
-  const int rows = in_use != nullptr ? __builtin_amdgcn_readfirstlane(*in_use) : 0;
-  const bool fewer_tiles = A_KC && in_use != nullptr;
-  int pid, prob = 0;
+  // What the loop needs of problem 0 is read with the kernel's first arguments: an index into them that is computed first costs another
+  // trip to memory, 0.2 us, and most launches have one problem.
+  LoopArgs la = batch.first;
+  const uint32_t ntiles = batch.ntiles, count = batch.count, group = batch.group;
+  uint32_t per_xcd = batch.tiles_per_xcd;
+  asm("" : "+s"(la.A), "+s"(la.B), "+s"(la.B2), "+s"(la.lda), "+s"(la.ldb), "+s"(la.M), "+s"(la.N), "+s"(la.K), "+s"(la.act), "+s"(la.rows));
+  auto in_use = [](const int32_t* rows) { return (uint32_t)*(const __attribute__((address_space(4))) int32_t*)rows; };   // nobody writes it now: a scalar load
+  const bool fewer_tiles = A_KC && la.rows != nullptr;
+  uint32_t Mrows = 0;
+  if (fewer_tiles) Mrows = in_use(la.rows);
+  uint32_t pid, prob = 0;
   if (fewer_tiles) {
-    const int gy = (rows + BM - 1) / BM;
-    int n = 0;
-    for (int k = 0; k < batch.count; ++k) n += gy * ((batch.p[k].N + BN - 1) / BN);
-    const int per_xcd = (n + 7) / 8;
+    const uint32_t gy = (Mrows + BM - 1) / BM;
+    uint32_t n = gy * (((uint32_t)la.N + BN - 1) / BN);
+    for (uint32_t k = 1; k < count; ++k) n += gy * (((uint32_t)batch.p[k].N + BN - 1) / BN);
+    per_xcd = (n + 7) / 8;
     pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_xcd || pid >= n) return;
-    for (int k = 0; k + 1 < batch.count; ++k) {
-      const int t = gy * ((batch.p[k].N + BN - 1) / BN);
+    if ((blockIdx.x >> 3) >= per_xcd || pid >= n) return;
+    for (uint32_t k = 0; k + 1 < count; ++k) {
+      const uint32_t t = gy * (((uint32_t)batch.p[k].N + BN - 1) / BN);
       if (pid < t) break;
       pid -= t;
       prob = k + 1;
     }
   } else {
-    pid = (blockIdx.x & 7) * tiles_per_xcd + (blockIdx.x >> 3);
+    pid = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (pid >= ntiles) return;
-    int before = 0;
+    if (count > 1) {
+      uint32_t before = 0;
 #pragma unroll
-    for (int k = 1; k < GEMM_MAX_BATCH; ++k)
-      if (k < batch.count && pid >= batch.first_tile[k]) { prob = k; before = batch.first_tile[k]; }
-    pid -= before;
-  }
-  // What the loop needs of problem 0 is read with the kernel's first arguments: an index into them that is computed first costs another
-  // trip to memory, 0.2 us, and most launches have one problem.
-  const GemmBf16Args& a = batch.p[prob];   // for the epilogue
-  LoopArgs la = loop_args(batch.p[0]);
-  la.pin();
-  if (prob != 0) la = loop_args(a);
-  const int group = batch.group;
-  const int Mrows = fewer_tiles ? rows : la.M;
-  const int gx = (la.N + BN - 1) / BN, gy = (Mrows + BM - 1) / BM;
-  const int width = group * gx, grp = pid / width, first = grp * group;
-  const int gsz = min(gy - first, group);
-  const int ti = first + (pid % width) % gsz, tj = (pid % width) / gsz;
-  const int i0 = ti * BM, j0 = tj * BN;
-
-  f32x16 acc[XT][YT];
-#pragma unroll
-  for (int x = 0; x < XT; ++x)
-#pragma unroll
-    for (int y = 0; y < YT; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-
-  const int nk = (!A_KC && la.rows != nullptr ? __builtin_amdgcn_readfirstlane(*la.rows) : la.K) / BK;
-  // The operand pointers live in registers for the whole k loop (read through `a` they would be re-fetched from the
-  // kernel-argument segment after every inline-assembly load, a scalar-memory round trip per slab).
-  const char* const pA = reinterpret_cast<const char*>(la.A);
-  const char* const pB = reinterpret_cast<const char*>(la.B);
-  const char* const pB2 = reinterpret_cast<const char*>(la.B2);
-  const int iters = (!DUAL && pB2 != nullptr) ? 2 * nk : nk;   // non-DUAL tiles contract with hi, then with lo
-
-  // the GELU table's place: at the top, or at the bottom (and the staging of the epilogue above it) if the last slab is at the top
-  const bool look_up = T::TAB && la.act != GEMM_ACT_NONE;
-  const bool tab_low = (iters - 1) % NSTAGE == NSTAGE - 1;
-  const int tab_at = tab_low ? 0 : T::LDS_MAIN - GELU_TAB_BYTES;
-  const int lw = T::PW > 0 ? wave - WAVES : wave;            // number among the loading waves
-  const bool loader = T::PW == 0 || wave >= WAVES;
-  // per-lane global offsets of this wave's loads
-  uint32_t offA[T::NLA], offB[T::NLB];
-#pragma unroll
-  for (int q = 0; q < T::NLA; ++q) offA[q] = piece_offset<A_KC, BM, BK>((q * T::LW + lw) * 1024 + lane * 16, i0, Mrows, la.lda);
-#pragma unroll
-  for (int q = 0; q < T::NLB; ++q) offB[q] = piece_offset<B_KC, BN, BK>((q * T::LW + lw) * 1024 + lane * 16, j0, la.N, la.ldb);
-  const int64_t stepA = A_KC ? (int64_t)BK * 2 : (int64_t)BK * la.lda * 2;   // bytes per slab
-  const int64_t stepB = B_KC ? (int64_t)BK * 2 : (int64_t)BK * la.ldb * 2;
-
-  // Direct global -> LDS loads: lane l of a wave-level load lands at (m0) + 16 l.  Written as inline assembly so
-  // that the only waits on them are the explicit vmcnt waits below.
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)smem_raw;
-  // All NL loads of a slab are issued together right after the barrier that frees their stage (in waves that also
-  // multiply, spreading them over the k-steps measured 3-8% slower: it shortens the prefetch distance).
-  constexpr int KS = BK / 16;
-  auto issue = [&](int sl) {
-    if (sl >= iters || !loader) return;
-    const int stage = sl % NSTAGE;
-    const int kq = sl >= nk ? sl - nk : sl;
-    const char* ap = pA + kq * stepA;
-    const char* bp = (sl >= nk ? pB2 : pB) + kq * stepB;
-    const char* b2p = pB2 + kq * stepB;
-    const uint32_t sa = lds0 + stage * T::STAGE_BYTES + lw * 1024;
-    const uint32_t sb = sa + T::A_BYTES;
-#pragma unroll
-    for (int t = 0; t < T::NL; ++t) {
-      if (t < T::NLA) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sa + t * T::LW * 1024), "v"(offA[t]), "s"(ap) : "memory", "m0");
-      } else if (t < T::NLA + T::NLB) {
-        const int q = t - T::NLA;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sb + q * T::LW * 1024), "v"(offB[q]), "s"(bp) : "memory", "m0");
-      } else {
-        const int q = t - T::NLA - T::NLB;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(sb + T::B_BYTES + q * T::LW * 1024), "v"(offB[q]), "s"(b2p) : "memory", "m0");
-      }
+      for (uint32_t k = 1; k < GEMM_MAX_BATCH; ++k)
+        if (k < count && pid >= (uint32_t)batch.first_tile[k]) { prob = k; before = batch.first_tile[k]; }
+      pid -= before;
     }
-  };
-
-  // lane-dependent parts of the operand fetch addresses
-  int fa[A_KC ? BK / 16 : XT], fb[B_KC ? BK / 16 : YT];
-  if (A_KC) {
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) fa[ks] = fetch_lane_offset<true, BM, BK>(lane, ks) + wr * BK * 2;
-  } else {
-#pragma unroll
-    for (int x = 0; x < XT; ++x) fa[x] = fetch_lane_offset<false, BM, BK>(lane, (wr >> 5) + x);
   }
-  if (B_KC) {
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) fb[ks] = fetch_lane_offset<true, BN, BK>(lane, ks) + wc * BK * 2;
+  const GemmBf16Args& a = batch.p[prob];   // for the epilogue
+  if (prob != 0) la = loop_args(a);
+  const uint32_t rows_of = fewer_tiles ? Mrows : (uint32_t)la.M;
+  const uint32_t gx = ((uint32_t)la.N + BN - 1) / BN, gy = (rows_of + BM - 1) / BM, width = group * gx;
+  uint32_t grp, tj, ti;
+  if (ntiles < SMALL_TILES) {
+    grp = small_quotient(pid, width);
+    const uint32_t gsz = min(gy - grp * group, group), rest = pid - grp * width;
+    tj = small_quotient(rest, gsz); ti = grp * group + rest - tj * gsz;
   } else {
-#pragma unroll
-    for (int y = 0; y < YT; ++y) fb[y] = fetch_lane_offset<false, BN, BK>(lane, (wc >> 5) + y);
+    grp = pid / width;
+    const uint32_t gsz = min(gy - grp * group, group), rest = pid - grp * width;
+    tj = rest / gsz; ti = grp * group + rest - tj * gsz;
   }
+  const uint32_t i0 = ti * BM, j0 = tj * BN;
 
-  auto fetchA = [&](const unsigned char* sa, int x, int ks) -> bf16x8 {
-    if (A_KC) return *reinterpret_cast<const bf16x8*>(sa + fa[ks] + x * 32 * BK * 2);
-    const unsigned char* p = sa + fa[x] + ks * 16 * BM * 2;
-    union { bf16x8 v; s16x4 h[2]; } u;
-    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * BM * 2));
-    return u.v;
-  };
-  auto fetchB = [&](const unsigned char* sb, int y, int ks) -> bf16x8 {
-    if (B_KC) return *reinterpret_cast<const bf16x8*>(sb + fb[ks] + y * 32 * BK * 2);
-    const unsigned char* p = sb + fb[y] + ks * 16 * BN * 2;
-    union { bf16x8 v; s16x4 h[2]; } u;
-    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
-    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * BN * 2));
-    return u.v;
-  };
+  int nk = la.K / BK;
+  if (!A_KC && la.rows != nullptr) nk = (int)in_use(la.rows) / BK;   // the problems of a launch need not agree in this
+  const int iters = (!DUAL && la.B2 != nullptr) ? 2 * nk : nk;   // non-DUAL tiles contract with hi, then with lo
 
-  // ---- pipeline: NSTAGE - 1 slabs in flight; the k-steps of all slabs form one stream in which the operands of
-  // step t + 1 are fetched from LDS before the MFMAs of step t are issued (also across the slab boundary, so the
-  // LDS latency after a barrier hides behind the last MFMAs of the previous slab)
-#pragma unroll
-  for (int s = 0; s < NSTAGE - 1; ++s) issue(s);
+  // the GELU table's place: at the bottom, or at the top if the last slab is at the bottom
+  const bool look_up = T::TAB && la.act != GEMM_ACT_NONE;
+  const int tab_at = (iters - 1) % NSTAGE == 0 ? T::LDS_BYTES - GELU_TAB_BYTES : 0;
+  const uint32_t lw = T::PW > 0 ? wave - WAVES : wave;            // number among the loading waves
+  const bool loader = T::PW == 0 || wave >= WAVES;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)smem_raw;
 
-  static_assert(KS % 2 == 0, "operand double buffer parity");
-  bf16x8 av[2][XT], bv[2][YT], bw[2][DUAL ? YT : 1];
-  // make slab `sl` visible: a loading wave's own loads landed, then everyone's; afterwards the stage of slab sl - 1 is free
-  auto arrive = [&](int sl) {
-    const int younger = iters - 1 - sl;
-    if (loader) wait_loads<T::NL, NSTAGE - 2>(younger);
-    __builtin_amdgcn_s_barrier();
-    issue(sl + NSTAGE - 1);
+  // ---- loads.  Direct global -> LDS: lane l of a wave-level load lands at (m0) + 16 l.  Written as inline assembly so
+  // that the only waits on them are the explicit vmcnt waits below.  All NL loads of a slab are issued together right after the barrier that
+  // frees their stage (in waves that also multiply, spreading them over the k-steps measured 3-8% slower: it shortens the prefetch distance).
+  uint32_t offA[T::NLA], offB[T::NLB];          // of each lane, from the slab's first element
+  const char *ap = reinterpret_cast<const char*>(la.A), *bp = reinterpret_cast<const char*>(la.B), *b2p = reinterpret_cast<const char*>(la.B2);   // of the next slab
+  const uint32_t stepA = A_KC ? BK * 2 : BK * la.lda * 2, stepB = B_KC ? BK * 2 : BK * la.ldb * 2;   // bytes per slab
+  int next = 0;                                 // slab
+  uint32_t next_at = lds0 + lw * 1024;          // its stage
+  auto load = [&](uint32_t to, uint32_t off, const char* from) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(from) : "memory", "m0");
   };
-  auto fetch = [&](int sl, int ks, int buf) {
-    const unsigned char* sa = smem_raw + (sl % NSTAGE) * T::STAGE_BYTES;
-    const unsigned char* sb = sa + T::A_BYTES;
+  auto issue = [&]() {
+    if (next >= iters) return;
+    if (!DUAL && next == nk) { ap = reinterpret_cast<const char*>(la.A); bp = b2p; }
 #pragma unroll
-    for (int x = 0; x < XT; ++x) av[buf][x] = fetchA(sa, x, ks);
+    for (int q = 0; q < T::NLA; ++q) load(next_at + q * T::LW * 1024, offA[q], ap);
 #pragma unroll
-    for (int y = 0; y < YT; ++y) bv[buf][y] = fetchB(sb, y, ks);
+    for (int q = 0; q < T::NLB; ++q) load(next_at + T::A_BYTES + q * T::LW * 1024, offB[q], bp);
     if (DUAL) {
 #pragma unroll
-      for (int y = 0; y < YT; ++y) bw[buf][y] = fetchB(sb + T::B_BYTES, y, ks);
+      for (int q = 0; q < T::NLB; ++q) load(next_at + T::A_BYTES + T::B_BYTES + q * T::LW * 1024, offB[q], b2p);
+      b2p += stepB;
     }
+    ap += stepA; bp += stepB;
+    next_at = (next + 1) % NSTAGE == 0 ? lds0 + lw * 1024 : next_at + T::STAGE_BYTES;
+    ++next;
   };
+  // make slab `sl` visible: a loading wave's own loads landed, then everyone's; afterwards the stage of slab sl - 1 is free
+  auto arrive = [&](int sl) {
+    if (loader) wait_loads<T::NL, NSTAGE - 2>(iters - 1 - sl);
+    __builtin_amdgcn_s_barrier();
+    if (loader) issue();
+  };
+  if (loader) {
+    load_offsets<A_KC, BM, BK, T::LW, T::NLA>(offA, lw, lane, i0, rows_of, la.lda);
+    load_offsets<B_KC, BN, BK, T::LW, T::NLB>(offB, lw, lane, j0, la.N, la.ldb);
+#pragma unroll
+    for (int s = 0; s < NSTAGE - 1; ++s) issue();
+  }
   if (T::PW > 0 && loader) {   // the barriers of the others, and the loads
     for (int i = 0; i < iters; ++i) arrive(i);
     if constexpr (T::TAB) {
@@ -338,190 +320,309 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch, int n
         const char* const tab = reinterpret_cast<const char*>(la.gelu_tab) + (la.act == GEMM_ACT_GELU_BWD ? GELU_TAB_BYTES : 0);
 #pragma unroll
         for (int q = 0; q < (GELU_TAB_BYTES / 1024 + T::LW - 1) / T::LW; ++q) {
-          const int piece = q * T::LW + lw;
-          if (piece < GELU_TAB_BYTES / 1024)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds0 + tab_at + piece * 1024), "v"(lane * 16), "s"(tab + piece * 1024) : "memory", "m0");
+          const uint32_t piece = q * T::LW + lw;
+          if (piece < GELU_TAB_BYTES / 1024) load(lds0 + tab_at + piece * 1024, lane * 16, tab + piece * 1024);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
       }
     }
-    __syncthreads();
     return;
   }
-  arrive(0);
-  auto mfma_step = [&](int cur) {
-    if (!SB) __builtin_amdgcn_sched_barrier(0);
+
+  const int wr = (int)(wave / T::WGN) * T::WM, wc = (int)(wave % T::WGN) * T::WN;
+  // the epilogue's arguments, read while the first slab is on its way
+  const float *res32 = a.res32, *bias_at = a.bias;
+  const bf16_t* aux16 = a.aux16;
+  bf16_t *C16_pre = a.C16_pre, *C16 = a.C16;
+  float* C32 = a.C32;
+  int64_t ldc = a.ldc;
+  int kind = batch.kind[prob];
+  asm("" : "+s"(res32), "+s"(bias_at), "+s"(aux16), "+s"(C16_pre), "+s"(C16), "+s"(C32), "+s"(ldc), "+s"(kind));
+  const float bs = (bias_at != nullptr && a.bias_v != nullptr && a.beps != nullptr && a.bsign != 0.f) ? a.bsign * *(const __attribute__((address_space(4))) float*)a.beps : 0.f;
+  f32x4 acc[XT][YT];
 #pragma unroll
-    for (int x = 0; x < XT; ++x)
+  for (int x = 0; x < XT; ++x)
 #pragma unroll
-      for (int y = 0; y < YT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[cur][x], bv[cur][y], acc[x][y], 0, 0, 0);
-    if (DUAL) {
+    for (int y = 0; y < YT; ++y) acc[x][y] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  constexpr int KD = DUAL ? 16 : 32, KS = BK / KD;   // depth of a k-step, steps of a slab
+  // lane-dependent parts of the operand fetch addresses
+  const int lo_half = DUAL ? (int)(lane >> 5) * T::B_BYTES : 0;
+  int fa[A_KC ? KS : XT], fb[B_KC ? KS : YT];
+  if (A_KC) {
 #pragma unroll
-      for (int x = 0; x < XT; ++x)
+    for (int ks = 0; ks < KS; ++ks) fa[ks] = fetch_lane_offset<true, BM, BK, DUAL>(lane, ks) + wr * BK * 2;
+  } else {
 #pragma unroll
-        for (int y = 0; y < YT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[cur][x], bw[cur][y], acc[x][y], 0, 0, 0);
-    }
-    if (!SB) __builtin_amdgcn_sched_barrier(0);
+    for (int x = 0; x < XT; ++x) fa[x] = fetch_lane_offset<false, BM, BK, DUAL>(lane, (wr >> 4) + x);
+  }
+  if (B_KC) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fb[ks] = fetch_lane_offset<true, BN, BK, DUAL>(lane, ks) + wc * BK * 2 + lo_half;
+  } else {
+#pragma unroll
+    for (int y = 0; y < YT; ++y) fb[y] = fetch_lane_offset<false, BN, BK, DUAL>(lane, (wc >> 4) + y) + lo_half;
+  }
+
+  auto fetchA = [&](const unsigned char* sa, int x, int ks) -> bf16x8 {
+    if (A_KC) return *reinterpret_cast<const bf16x8*>(sa + fa[ks] + x * 16 * BK * 2);
+    const unsigned char* p = sa + fa[x] + ks * KD * BM * 2;
+    union { bf16x8 v; s16x4 h[2]; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * BM * 2));
+    return u.v;
   };
-  if (SB) {
-    for (int i = 0; i < iters; ++i) {
+  auto fetchB = [&](const unsigned char* sb, int y, int ks) -> bf16x8 {
+    if (B_KC) return *reinterpret_cast<const bf16x8*>(sb + fb[ks] + y * 16 * BK * 2);
+    const unsigned char* p = sb + fb[y] + ks * KD * BN * 2;
+    union { bf16x8 v; s16x4 h[2]; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * BN * 2));
+    return u.v;
+  };
+
+  // ---- pipeline: NSTAGE - 1 slabs in flight; a k-step is cut into pieces of YP fragments of B, and
+  // the pieces of all slabs form one stream in which the operands of piece t + 1 are fetched from LDS before the MFMAs of piece t are
+  // issued (also across the slab boundary, so the LDS latency after a barrier hides behind the last MFMAs of the previous slab)
+  constexpr int YP = T::YP, NP = T::NP, NT = KS * NP;   // NT: pieces of a slab
+  static_assert(KS % 2 == 0 && NT % 2 == 0, "operand double buffer parity");
+  bf16x8 av[2][XT], bv[2][YP];
+  // D = B-fragment x A-fragment: a lane gets four neighbouring columns of one row
+  constexpr int NM = XT * YP;
+  auto mfma = [&](auto t, auto m) {
+    constexpr int T_ = t, ks = T_ / NP, y0 = T_ % NP * YP, x = m / YP, yy = m % YP, y = (x & 1) ? YP - 1 - yy : yy;
+    acc[x][y0 + y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[T_ & 1][y], av[ks & 1][x], acc[x][y0 + y], 0, 0, 0);
+  };
+  // operand r of the piece t of the slab at `at`: first what its first products need
+  constexpr int MOST = YP + XT;
+  auto operands = [](int t) { return YP + (t % NP == 0 ? XT : 0); };
+  auto read = [&](const unsigned char* at, auto t, auto r) {
+    constexpr int T_ = t, R_ = r, ks = T_ / NP, p = T_ % NP, wa = p == 0 ? 1 : 0;
+    const unsigned char* const sb = at + T::A_BYTES;
+    if constexpr (wa == 1 && R_ == 0) av[ks & 1][0] = fetchA(at, 0, ks);
+    else if constexpr (R_ - wa < YP) bv[T_ & 1][R_ - wa] = fetchB(sb, p * YP + R_ - wa, ks);
+    else av[ks & 1][R_ - YP] = fetchA(at, R_ - YP, ks);
+  };
+  auto read_all = [&](const unsigned char* at, auto t) {
+    static_for<MOST>([&](auto r) { if constexpr (decltype(r)::value < operands(decltype(t)::value)) read(at, t, r); });
+  };
+  auto multiply = [&](auto t) {
+    if (RD != 0) __builtin_amdgcn_sched_barrier(0);
+    static_for<NM>([&](auto m) { mfma(t, m); });
+    if (RD != 0) __builtin_amdgcn_sched_barrier(0);
+  };
+  // the products of piece t with the reads of piece tn of the slab at `at` between them
+  auto multiply_reading = [&](auto t, const unsigned char* at, auto tn) {
+    constexpr int nr = operands(decltype(tn)::value);
+    constexpr auto before = [](int m) { const int b = (m * nr * RD + NM - 1) / NM; return b < nr ? b : nr; };   // reads ahead of product m - 1
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<NM>([&](auto m) {
+      static_for<MOST>([&](auto r) { if constexpr (decltype(r)::value >= before(decltype(m)::value) && decltype(r)::value < before(decltype(m)::value + 1)) read(at, tn, r); });
+      __builtin_amdgcn_sched_barrier(0);
+      mfma(t, m);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto stage_of = [&](int sl) { return smem_raw + (sl % NSTAGE) * T::STAGE_BYTES; };
+
+  arrive(0);
+  if constexpr (RD == 0) {
+    for (int i = 0; i + 1 < iters; ++i) {
       if (i > 0) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of slab i - 1 are complete
         arrive(i);
       }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) { fetch(i, ks, 0); mfma_step(0); }
+      const unsigned char* const at = stage_of(i);
+      static_for<NT>([&](auto t) { read_all(at, t); multiply(t); });
     }
   } else {
-    fetch(0, 0, 0);
+    read_all(stage_of(0), std::integral_constant<int, 0>{});
     for (int i = 0; i + 1 < iters; ++i) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int cur = ks & 1;
-        if (ks + 1 < KS) {
-          fetch(i, ks + 1, cur ^ 1);
-        } else {
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of slab i are complete
-          arrive(i + 1);
-          fetch(i + 1, 0, cur ^ 1);
-        }
-        mfma_step(cur);
-      }
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {   // last slab
-      if (ks + 1 < KS) fetch(iters - 1, ks + 1, (ks & 1) ^ 1);
-      mfma_step(ks & 1);
+      const unsigned char* const at = stage_of(i);
+      static_for<NT - 1>([&](auto t) { multiply_reading(t, at, std::integral_constant<int, decltype(t)::value + 1>{}); });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of slab i are complete
+      arrive(i + 1);
+      multiply_reading(std::integral_constant<int, NT - 1>{}, stage_of(i + 1), std::integral_constant<int, 0>{});
     }
   }
-  __syncthreads();
-
-  // ---- epilogue: accumulators -> LDS (per wave, 32 x WN fp32 at a time) -> row-contiguous global accesses
-  constexpr int EPI_LD = T::EPI_LD, LPR = T::WN / 4, RPP = 64 / LPR;   // lanes per row, rows per pass
-  float* epi = reinterpret_cast<float*>(smem_raw + (look_up && tab_low ? GELU_TAB_BYTES : 0)) + wave * 32 * EPI_LD;
-  const unsigned char* const tab = smem_raw + tab_at;
-  const int cg = lane % LPR, rq = lane / LPR;
-  const int gj = j0 + wc + 4 * cg;
-  const bool col_ok = gj < a.N && (LPR * RPP == 64 || lane < LPR * RPP);   // 96-wide wave tiles: 24 lanes a row, two rows
-  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (col_ok && a.bias != nullptr) {
-    bias = *reinterpret_cast<const float4*>(a.bias + gj);
-    if (a.bias_v != nullptr && a.beps != nullptr && a.bsign != 0.f) {
-      const float s = a.bsign * (*a.beps);
-      const float4 bv = *reinterpret_cast<const float4*>(a.bias_v + gj);
-      bias.x = fmaf(s, bv.x, bias.x); bias.y = fmaf(s, bv.y, bias.y); bias.z = fmaf(s, bv.z, bias.z); bias.w = fmaf(s, bv.w, bias.w);
-    }
-  }
-  const float* const res32 = a.res32; const bf16_t* const aux16 = a.aux16;
-  bf16_t* const C16_pre = a.C16_pre; bf16_t* const C16 = a.C16; float* const C32 = a.C32;
-  const int act = a.act;
-  const int64_t ldc = a.ldc, base = (int64_t)(i0 + wr) * ldc + j0 + wc;   // of the wave's tile
-  const uint32_t lane_off = (uint32_t)(rq * ldc) + 4u * cg;               // a step is a uniform distance plus this (rq < 8)
-  constexpr int NIT = 32 / RPP;
-  // A slice of 32 rows goes through LDS at a time and is finished four steps (of RPP rows) at a time, each operation for the
-  // four together; the side inputs (an fp32 residual or a saved pre-activation, an epilogue has one of them at most) of the next
-  // four steps are requested before the current ones are finished, across the slices.
-  constexpr int CH = 4, PER = NIT / CH, NCH = XT * PER;
-  static_assert(NIT % CH == 0, "steps of a slice");
-  const bool side = res32 != nullptr || act == GEMM_ACT_GELU_BWD;
-  auto entry = [&](uint32_t offset) { return *reinterpret_cast<const float*>(tab + offset); };   // of the GELU table
-  auto epilogue = [&](auto all_rows) {   // all_rows: every row of the tile exists
-    auto exists = [&](int row) { return decltype(all_rows)::value || i0 + wr + row < Mrows; };   // row: within the wave's tile
-    auto step = [&](int q, int u) { return base + (int64_t)((q / PER) * 32 + RPP * ((q % PER) * CH + u)) * ldc; };
-    auto row_of = [&](int q, int u) { return rq + RPP * ((q % PER) * CH + u); };   // within the slice
-    auto load_side = [&](int q, uint4 (&sv)[CH]) {
+  // ---- epilogue: a lane has four neighbouring columns of row lane % 16 of each fragment.  fp32 goes out from there, 64 bytes of a row at a
+  // time; of two neighbouring fragments in bf16, lanes 16 apart exchange halves first, so that a lane has eight neighbouring columns of
+  // one of them.  Nothing goes through LDS.
+  // A unit is a pair of fragments side by side, the units of a column of them follow each other.  Whole tiles of the usual kinds go through
+  // code of their own for each kind (few instructions, which come from L2 like those at the start); what a unit needs from memory (bias,
+  // an fp32 residual or a saved pre-activation, an epilogue has one of these at most) is requested DEPTH - 1 units before it, for the first ones while the
+  // last slab is multiplied.
+  constexpr int UNITS = YT / 2 * XT, DEPTH = XT * YT > 16 ? 2 : XT * YT == 16 ? 3 : 4;
+  const bool fast = kind != EPI_ANY && i0 + BM <= rows_of && j0 + BN <= (uint32_t)la.N;
+  const int g = (int)lane >> 4, pair_col = 16 * (g & 1) + 8 * (g >> 1);   // columns of the lane's values: 4 g, after the exchange pair_col
+  const uint32_t off32 = ((lane & 15) * (uint32_t)ldc + 4 * g) * 4, off16 = ((lane & 15) * (uint32_t)ldc + pair_col) * 2;   // (ldc < 2^24 where they are used)
+  const int64_t tile0 = ((int64_t)i0 + wr) * ldc + j0 + wc;
+  auto of_unit = [&](int unit) { return tile0 + (int64_t)(unit % XT * 16) * ldc + unit / XT * 32; };
+  uint4 sv[DEPTH][2] = {};
+  float4 bias[2][2] = {};
+  auto load_bias = [&](int h) {
+    if (bias_at == nullptr) return;
 #pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        if (!exists((q / PER) * 32 + row_of(q, u))) continue;
-        if (res32 != nullptr) {
-          sv[u] = *reinterpret_cast<const uint4*>(res32 + step(q, u) + lane_off);
-        } else {
-          const uint2 t = *reinterpret_cast<const uint2*>(aux16 + step(q, u) + lane_off);
-          sv[u].x = t.x; sv[u].y = t.y;
-        }
+    for (int u = 0; u < 2; ++u) {
+      float4 t = *reinterpret_cast<const float4*>(bias_at + j0 + wc + 32 * h + 16 * u + 4 * g);
+      if (bs != 0.f) {
+        const float4 v = *reinterpret_cast<const float4*>(a.bias_v + j0 + wc + 32 * h + 16 * u + 4 * g);
+        t.x = fmaf(bs, v.x, t.x); t.y = fmaf(bs, v.y, t.y); t.z = fmaf(bs, v.z, t.z); t.w = fmaf(bs, v.w, t.w);
       }
-    };
-    constexpr bool AHEAD = XT * YT <= 4;   // more accumulators leave no registers for two sets of side inputs
-    uint4 sv[AHEAD ? 2 : 1][CH] = {};
-    if (AHEAD && side && col_ok) load_side(0, sv[0]);
-#pragma unroll
-    for (int q = 0; q < NCH; ++q) {
-      const int x = q / PER;
-      if (!AHEAD && side && col_ok) load_side(q, sv[0]);
-      if (q % PER == 0) {
-        // the staging region is private to the wave: LDS operations of one wave complete in order, no block barrier
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-#pragma unroll
-        for (int y = 0; y < YT; ++y)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            epi[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * EPI_LD + y * 32 + (lane & 31)] = acc[x][y][r];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      }
-      if (!col_ok) continue;
-      if (AHEAD && side && q + 1 < NCH) load_side(q + 1, sv[AHEAD ? (q + 1) & 1 : 0]);
-      float c[CH][4];
-#pragma unroll
-      for (int u = 0; u < CH; ++u) {
-        const float4 v = *reinterpret_cast<const float4*>(epi + row_of(q, u) * EPI_LD + 4 * cg);
-        c[u][0] = v.x + bias.x; c[u][1] = v.y + bias.y; c[u][2] = v.z + bias.z; c[u][3] = v.w + bias.w;
-      }
-      if (res32 != nullptr) {
-#pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          const uint4 r = sv[AHEAD ? q & 1 : 0][u];
-          c[u][0] += __uint_as_float(r.x); c[u][1] += __uint_as_float(r.y); c[u][2] += __uint_as_float(r.z); c[u][3] += __uint_as_float(r.w);
-        }
-      }
-      if (act == GEMM_ACT_GELU_FWD) {
-        // the backward pass sees the rounded pre-activation, so the activation is taken from it too
-#pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          const uint2 pk = make_uint2(pack_bf16x2(c[u][0], c[u][1]), pack_bf16x2(c[u][2], c[u][3]));
-          if (C16_pre != nullptr && exists(x * 32 + row_of(q, u))) *reinterpret_cast<uint2*>(C16_pre + step(q, u) + lane_off) = pk;   // forward-only passes do not keep it
-          c[u][0] = bf16_to_f32((bf16_t)pk.x); c[u][1] = bf16_to_f32((bf16_t)(pk.x >> 16));
-          c[u][2] = bf16_to_f32((bf16_t)pk.y); c[u][3] = bf16_to_f32((bf16_t)(pk.y >> 16));
-          if constexpr (T::TAB) {
-            const uint32_t o0 = gelu_tab_offsets(pk.x), o1 = gelu_tab_offsets(pk.y);
-            c[u][0] *= entry(o0 & 0xffffu); c[u][1] *= entry(o0 >> 16); c[u][2] *= entry(o1 & 0xffffu); c[u][3] *= entry(o1 >> 16);
-          }
-        }
-        if constexpr (!T::TAB) {
-#pragma unroll
-          for (int u = 0; u < CH; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) c[u][e] = gelu_f(c[u][e]);
-        }
-      } else if (act == GEMM_ACT_GELU_BWD) {
-#pragma unroll
-        for (int u = 0; u < CH; ++u) {
-          const uint4 r = sv[AHEAD ? q & 1 : 0][u];
-          const float x[4] = {bf16_to_f32((bf16_t)r.x), bf16_to_f32((bf16_t)(r.x >> 16)), bf16_to_f32((bf16_t)r.y), bf16_to_f32((bf16_t)(r.y >> 16))};
-          if constexpr (T::TAB) {   // + 0 x: of an infinity or a NaN the derivative is NaN
-            const uint32_t o0 = gelu_tab_offsets(r.x), o1 = gelu_tab_offsets(r.y);
-            c[u][0] *= fmaf(x[0], 0.f, entry(o0 & 0xffffu)); c[u][1] *= fmaf(x[1], 0.f, entry(o0 >> 16));
-            c[u][2] *= fmaf(x[2], 0.f, entry(o1 & 0xffffu)); c[u][3] *= fmaf(x[3], 0.f, entry(o1 >> 16));
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) c[u][e] *= dgelu_f(x[e]);
-          }
-        }
-      }
-      if (C32 != nullptr) {
-#pragma unroll
-        for (int u = 0; u < CH; ++u)
-          if (exists(x * 32 + row_of(q, u))) *reinterpret_cast<float4*>(C32 + step(q, u) + lane_off) = make_float4(c[u][0], c[u][1], c[u][2], c[u][3]);
-      }
-      if (C16 != nullptr) {
-#pragma unroll
-        for (int u = 0; u < CH; ++u)
-          if (exists(x * 32 + row_of(q, u))) *reinterpret_cast<uint2*>(C16 + step(q, u) + lane_off) = make_uint2(pack_bf16x2(c[u][0], c[u][1]), pack_bf16x2(c[u][2], c[u][3]));
-      }
+      bias[h & 1][u] = t;
     }
   };
-  if (i0 + wr >= Mrows) return;
-  if (i0 + BM <= Mrows) epilogue(std::true_type{});
-  else epilogue(std::false_type{});
+  auto load_side = [&](int unit) {
+    uint4 (&v)[2] = sv[unit % DEPTH];
+    if (kind == EPI_RES32) {
+      const char* const p = reinterpret_cast<const char*>(res32 + of_unit(unit));
+      v[0] = *reinterpret_cast<const uint4*>(p + off32);
+      v[1] = *reinterpret_cast<const uint4*>(p + off32 + 64);
+    } else if (kind == EPI_GELU_BWD) {
+      v[0] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(aux16 + of_unit(unit)) + off16);
+    }
+  };
+  auto load_first = [&]() {
+    if (!fast) return;
+    load_bias(0);
+    static_for<DEPTH - 1>([&](auto u) { if constexpr (decltype(u)::value < UNITS) load_side(u); });
+  };
+  constexpr bool EARLY = XT * YT != 24;   // the 64 x 96 tiles of a wave leave no registers for it
+  if (EARLY) load_first();
+  // the last slab
+  {
+    if (RD == 0 && iters > 1) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      arrive(iters - 1);
+    }
+    const unsigned char* const at = stage_of(iters - 1);
+    if constexpr (RD == 0) {
+      static_for<NT>([&](auto t) { read_all(at, t); multiply(t); });
+    } else {
+      static_for<NT - 1>([&](auto t) { multiply_reading(t, at, std::integral_constant<int, decltype(t)::value + 1>{}); });
+      multiply(std::integral_constant<int, NT - 1>{});
+    }
+  }
+  if (!EARLY) load_first();
+  if (look_up) __syncthreads();   // the table has come
+  const unsigned char* const tab = smem_raw + tab_at;
+  auto entry = [&](uint32_t offset) { return *reinterpret_cast<const float*>(tab + offset); };
+  auto exchange = [](uint2 (&v)[2]) {   // its own inverse
+    u32x2 r = __builtin_amdgcn_permlane16_swap(v[0].x, v[1].x, false, false); v[0].x = r[0]; v[1].x = r[1];
+    r = __builtin_amdgcn_permlane16_swap(v[0].y, v[1].y, false, false); v[0].y = r[0]; v[1].y = r[1];
+  };
+  auto packed = [](const float (&c)[4]) { return make_uint2(pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3])); };
+  auto gelu = [&](float (&c)[4], uint2 pk) {   // of the rounded pre-activation, which is what the backward pass sees
+    c[0] = bf16_to_f32((bf16_t)pk.x); c[1] = bf16_to_f32((bf16_t)(pk.x >> 16)); c[2] = bf16_to_f32((bf16_t)pk.y); c[3] = bf16_to_f32((bf16_t)(pk.y >> 16));
+    if constexpr (T::TAB) {
+      const uint32_t o0 = gelu_tab_offsets(pk.x), o1 = gelu_tab_offsets(pk.y);
+      c[0] *= entry(o0 & 0xffffu); c[1] *= entry(o0 >> 16); c[2] *= entry(o1 & 0xffffu); c[3] *= entry(o1 >> 16);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c[e] = gelu_f(c[e]);
+    }
+  };
+  auto dgelu = [&](float (&c)[4], uint2 pk) {
+    const float x[4] = {bf16_to_f32((bf16_t)pk.x), bf16_to_f32((bf16_t)(pk.x >> 16)), bf16_to_f32((bf16_t)pk.y), bf16_to_f32((bf16_t)(pk.y >> 16))};
+    if constexpr (T::TAB) {   // + 0 x: of an infinity or a NaN the derivative is NaN
+      const uint32_t o0 = gelu_tab_offsets(pk.x), o1 = gelu_tab_offsets(pk.y);
+      c[0] *= fmaf(x[0], 0.f, entry(o0 & 0xffffu)); c[1] *= fmaf(x[1], 0.f, entry(o0 >> 16)); c[2] *= fmaf(x[2], 0.f, entry(o1 & 0xffffu)); c[3] *= fmaf(x[3], 0.f, entry(o1 >> 16));
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c[e] *= dgelu_f(x[e]);
+    }
+  };
+  auto add = [](float (&c)[4], uint4 r) { c[0] += __uint_as_float(r.x); c[1] += __uint_as_float(r.y); c[2] += __uint_as_float(r.z); c[3] += __uint_as_float(r.w); };
+  if (fast) {
+    auto of_kind = [&](auto k) {
+      constexpr int KIND = k;
+      static_for<UNITS>([&](auto unit_) {
+        constexpr int unit = unit_, x = unit % XT, h = unit / XT;
+        if constexpr (x == 0 && h + 1 < YT / 2) load_bias(h + 1);
+        if constexpr ((KIND == EPI_RES32 || KIND == EPI_GELU_BWD) && unit + DEPTH - 1 < UNITS) load_side(unit + DEPTH - 1);
+        const uint4 (&cur)[2] = sv[unit % DEPTH];
+        float c[2][4];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const f32x4 v = acc[x][2 * h + u];
+          const float4 b = bias[h & 1][u];
+          c[u][0] = v[0] + b.x; c[u][1] = v[1] + b.y; c[u][2] = v[2] + b.z; c[u][3] = v[3] + b.w;
+        }
+        if constexpr (KIND == EPI_RES32) { add(c[0], cur[0]); add(c[1], cur[1]); }
+        if constexpr (KIND == EPI_GELU_FWD) {
+          uint2 pk[2] = {packed(c[0]), packed(c[1])};
+          gelu(c[0], pk[0]); gelu(c[1], pk[1]);
+          if (C16_pre != nullptr) {   // forward-only passes do not keep it
+            exchange(pk);
+            *reinterpret_cast<uint4*>(reinterpret_cast<char*>(C16_pre + of_unit(unit)) + off16) = make_uint4(pk[0].x, pk[0].y, pk[1].x, pk[1].y);
+          }
+        }
+        if constexpr (KIND == EPI_GELU_BWD) {
+          uint2 pk[2] = {make_uint2(cur[0].x, cur[0].y), make_uint2(cur[0].z, cur[0].w)};
+          exchange(pk);
+          dgelu(c[0], pk[0]); dgelu(c[1], pk[1]);
+        }
+        if (KIND == EPI_C32 || KIND == EPI_RES32 || (KIND != EPI_C16 && C32 != nullptr)) {
+          char* const p = reinterpret_cast<char*>(C32 + of_unit(unit));
+          *reinterpret_cast<float4*>(p + off32) = make_float4(c[0][0], c[0][1], c[0][2], c[0][3]);
+          *reinterpret_cast<float4*>(p + off32 + 64) = make_float4(c[1][0], c[1][1], c[1][2], c[1][3]);
+        } else {
+          uint2 pk[2] = {packed(c[0]), packed(c[1])};
+          exchange(pk);
+          *reinterpret_cast<uint4*>(reinterpret_cast<char*>(C16 + of_unit(unit)) + off16) = make_uint4(pk[0].x, pk[0].y, pk[1].x, pk[1].y);
+        }
+      });
+    };
+    switch (kind) {
+      case EPI_C16: return of_kind(std::integral_constant<int, EPI_C16>{});
+      case EPI_C32: return of_kind(std::integral_constant<int, EPI_C32>{});
+      case EPI_RES32: return of_kind(std::integral_constant<int, EPI_RES32>{});
+      case EPI_GELU_FWD: return of_kind(std::integral_constant<int, EPI_GELU_FWD>{});
+      default: return of_kind(std::integral_constant<int, EPI_GELU_BWD>{});
+    }
+  }
+  // any combination, any alignment the operands may have, tiles at the edges
+  const int row0 = (int)i0 + wr + (int)(lane & 15), col0 = (int)j0 + wc + 4 * g, nrows = (int)rows_of, ncols = la.N, act = la.act;
+  static_for<UNITS>([&](auto unit_) {
+    constexpr int unit = unit_, x = unit % XT, h = unit / XT;
+    const int row = row0 + 16 * x;
+    if (row >= nrows) return;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int col = col0 + 32 * h + 16 * u;
+      if (col >= ncols) continue;
+      const int64_t at = (int64_t)row * ldc + col;
+      float c[4] = {acc[x][2 * h + u][0], acc[x][2 * h + u][1], acc[x][2 * h + u][2], acc[x][2 * h + u][3]};
+      if (bias_at != nullptr) {
+        float4 b = *reinterpret_cast<const float4*>(bias_at + col);
+        if (bs != 0.f) {
+          const float4 v = *reinterpret_cast<const float4*>(a.bias_v + col);
+          b.x = fmaf(bs, v.x, b.x); b.y = fmaf(bs, v.y, b.y); b.z = fmaf(bs, v.z, b.z); b.w = fmaf(bs, v.w, b.w);
+        }
+        c[0] += b.x; c[1] += b.y; c[2] += b.z; c[3] += b.w;
+      }
+      if (res32 != nullptr) add(c, *reinterpret_cast<const uint4*>(res32 + at));
+      if (act == GEMM_ACT_GELU_FWD) {
+        const uint2 pk = packed(c);
+        if (C16_pre != nullptr) *reinterpret_cast<uint2*>(C16_pre + at) = pk;
+        gelu(c, pk);
+      } else if (act == GEMM_ACT_GELU_BWD) {
+        dgelu(c, *reinterpret_cast<const uint2*>(aux16 + at));
+      }
+      if (C32 != nullptr) *reinterpret_cast<float4*>(C32 + at) = make_float4(c[0], c[1], c[2], c[3]);
+      if (C16 != nullptr) *reinterpret_cast<uint2*>(C16 + at) = packed(c);
+    }
+  });
+}
+
+// What a whole tile's epilogue does, where it is one of the usual things on usual alignments.
+int epilogue_kind(const GemmBf16Args& a) {
+  if (a.ldc % 8 != 0 || a.ldc >= (1 << 24) || (((uintptr_t)a.C16 | (uintptr_t)a.C16_pre | (uintptr_t)a.aux16) & 15) != 0) return EPI_ANY;
+  if ((a.C32 != nullptr) == (a.C16 != nullptr)) return EPI_ANY;
+  if (a.act != GEMM_ACT_NONE) return a.res32 != nullptr ? EPI_ANY : a.act == GEMM_ACT_GELU_FWD ? EPI_GELU_FWD : EPI_GELU_BWD;
+  if (a.res32 != nullptr) return a.C32 != nullptr ? EPI_RES32 : EPI_ANY;
+  return a.C32 != nullptr ? EPI_C32 : EPI_C16;
 }
 
 template <typename T, bool A_KC, bool B_KC>
@@ -532,40 +633,43 @@ void launch_tile(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count
     configured = true;
   }
   GemmBatch b{};
+  b.first = loop_args(p[0]);
   b.count = count; b.group = group;
   int nt = 0;
   for (int k = 0; k < count; ++k) {
     b.p[k] = p[k];
+    b.kind[k] = epilogue_kind(p[k]);
     b.first_tile[k] = nt;
     nt += ((p[k].N + T::BN - 1) / T::BN) * ((p[k].M + T::BM - 1) / T::BM);
   }
   for (int k = count; k <= GEMM_MAX_BATCH; ++k) b.first_tile[k] = nt;
-  const int per_xcd = (nt + 7) / 8;
-  launch_kernel(ps, k_gemm_bf16<T, A_KC, B_KC>, 8 * per_xcd, T::THREADS, T::LDS_BYTES, st, b, nt, per_xcd);
+  b.ntiles = nt; b.tiles_per_xcd = (nt + 7) / 8;
+  launch_kernel(ps, k_gemm_bf16<T, A_KC, B_KC>, 8 * b.tiles_per_xcd, T::THREADS, T::LDS_BYTES, st, b);
 }
 
-// Tiles <BM, BN, BK, multiplying waves in M, in N, stages, hi + lo, loading waves, operands fetched one step at a time>
+// Tiles <BM, BN, BK, multiplying waves in M, in N, stages, hi + lo, loading waves, fragments of a piece, fetches (see Tile)>
 // The 32 x 32 ones are for products of few rows (scoring one text), which a larger tile leaves to a few dozen workgroups that walk
-// the contraction slab by slab: with twice as many and five slabs in flight, 128 rows of 768 x 3072 take 14.1 us hi + lo
-// (64 x 32: 17.9) and 10.7 single-term (64 x 64: 17.2).  Splitting the contraction over the waves of a workgroup was
-// 0.8 us faster, but sums in another order, so that a text scored alone came out otherwise than in a batch.
-typedef Tile<256, 256, 64, 2, 4, 2, false> S1;
-typedef Tile<256, 192, 64, 4, 2, 2, false, 4, true> S2;
-typedef Tile<256, 128, 64, 4, 2, 3, false, 4, true> S3;
-typedef Tile<128, 128, 64, 4, 2, 4, false, 4> S4;
-typedef Tile<128, 64, 64, 4, 2, 4, false, 4> S5;
-typedef Tile<64, 64, 64, 2, 2, 4, false> S6;         // two workgroups per CU
-typedef Tile<128, 128, 64, 4, 2, 2, false> S7;       // two workgroups per CU
-typedef Tile<32, 32, 64, 1, 1, 6, false, 2> S8;      // three workgroups per CU
-typedef Tile<256, 192, 64, 4, 2, 2, true, 4, true> D1;
-typedef Tile<256, 128, 64, 4, 2, 2, true, 4> D2;
-typedef Tile<128, 128, 64, 4, 2, 3, true, 4> D3;
-typedef Tile<128, 96, 64, 4, 1, 3, true, 4> D4;
-typedef Tile<128, 64, 64, 4, 2, 4, true, 4> D5;
-typedef Tile<64, 64, 64, 2, 2, 4, true, 2> D6;
-typedef Tile<64, 64, 64, 2, 2, 3, true, 2> D7;       // two workgroups per CU
-typedef Tile<64, 32, 64, 2, 1, 4, true, 1> D8;       // two workgroups per CU
-typedef Tile<32, 32, 64, 1, 1, 6, true, 2> D9;       // two workgroups per CU
+// the contraction slab by slab: with twice as many and five slabs in flight, 128 rows of 768 x 3072 take 12.1 us hi + lo (64 x 32: 13.9;
+// one multiplying wave instead of two 13.0; slabs of 128 11.4) and 10.7 single-term (64 x 64: 17.2).  Splitting the contraction over the
+// waves of a workgroup was 0.8 us faster, but sums in another order, so that a text scored alone came out otherwise than in a batch.
+typedef Tile<256, 256, 64, 2, 4, 2, false, 0, 2, 0> S1;
+typedef Tile<256, 192, 64, 4, 2, 2, false, 4, 2, 1> S2;
+typedef Tile<256, 128, 64, 4, 2, 3, false, 4, 2, 2> S3;
+typedef Tile<128, 128, 64, 4, 2, 4, false, 4, 0, 1> S4;
+typedef Tile<128, 64, 64, 4, 2, 4, false, 4, 0, 1> S5;
+typedef Tile<64, 64, 64, 2, 2, 4, false, 0, 0, 1> S6;         // two workgroups per CU
+typedef Tile<128, 128, 64, 4, 2, 2, false, 0, 0, 1> S7;       // two workgroups per CU
+typedef Tile<32, 32, 64, 1, 1, 6, false, 2, 0, 1> S8;      // three workgroups per CU
+typedef Tile<256, 192, 64, 4, 2, 2, true, 4, 2, 1> D1;
+typedef Tile<256, 128, 64, 4, 2, 2, true, 4, 2, 2> D2;
+typedef Tile<128, 128, 64, 4, 2, 3, true, 4, 0, 2> D3;
+typedef Tile<128, 96, 64, 4, 1, 3, true, 4, 0, 2> D4;
+typedef Tile<128, 64, 64, 4, 2, 4, true, 4, 0, 1> D5;
+typedef Tile<64, 64, 64, 2, 2, 4, true, 2, 0, 1> D6;
+typedef Tile<64, 64, 64, 2, 2, 3, true, 2, 0, 1> D7;       // two workgroups per CU
+typedef Tile<64, 32, 64, 4, 1, 4, true, 2, 0, 1> D8;       // two workgroups per CU
+typedef Tile<32, 32, 64, 2, 1, 6, true, 2, 0, 0> D9;       // two workgroups per CU
+typedef Tile<32, 32, 128, 2, 1, 3, true, 2, 0, 1> D10;     // two workgroups per CU; contractions of a multiple of 128
 
 // What a launch costs with a tile, in us, beyond what it costs with any: per round, epilogue + 64-deep slabs x time of a slab.
 // A round is up to `per_cu` tiles on each of the 256 CUs; a slab takes `few` with a handful of tiles on the chip, `one` with one
@@ -575,7 +679,7 @@ typedef Tile<32, 32, 64, 1, 1, 6, true, 2> D9;       // two workgroups per CU
 // 50304 tokens; weights cold), taken when the GELU epilogues computed their factors and averaged over the kinds of epilogue.  On the
 // times of the kernels as they are, picking by them takes 0.9% (hi + lo) and 1.2% (single-term) longer in total than the fastest
 // tile of each problem, a fit of these 0.6% and 1.2%; GELU backward 1.7%, the head's products 0.4 to 3.3%: profiles/gemm_tile_costs.md.
-struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; };
+struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; int bk = 64; };
 constexpr TileCost SINGLE[] = {
     {1, 256, 256, 1, 1.282, 1.816, 0, 0, 8.26}, {2, 256, 192, 1, 1.060, 1.218, 0, 0, 8.62},
     {3, 256, 128, 1, 0.561, 0.923, 0, 0, 6.42}, {4, 128, 128, 1, 0.427, 0.600, 0, 0, 3.55},
@@ -586,7 +690,7 @@ constexpr TileCost HILO[] = {
     {13, 128, 128, 1, 0.672, 0.928, 0, 0, 4.58},  {14, 128, 96, 1, 0.671, 0.782, 0, 0, 4.52},
     {15, 128, 64, 1, 0.491, 0.603, 0, 0, 2.46},   {16, 64, 64, 1, 0.435, 0.435, 0, 0, 1.66},
     {17, 64, 64, 2, 0.449, 0.469, 0.723, 0.723, 1.59}, {18, 64, 32, 2, 0.320, 0.341, 0.528, 0.528, 1.42},
-    {19, 32, 32, 2, 0.236, 0.255, 0.381, 0.381, 1.28}};
+    {19, 32, 32, 2, 0.236, 0.255, 0.381, 0.381, 1.28}, {20, 32, 32, 2, 0.220, 0.240, 0.360, 0.360, 1.28, 128}};
 
 int g_force_shape = 0, g_group = 8;
 
@@ -616,11 +720,12 @@ double launch_cost(const TileCost& c, const GemmBf16Args* p, int count, int shar
 // thirds, 30, 11, 5 and 8%, for all rows 37, 16, 5 and 2%.
 template <int N>
 int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count) {
-  bool padded = false;
-  for (int k = 0; k < count; ++k) padded = padded || p[k].rows != nullptr;
+  bool padded = false, deep = true;   // deep: whole slabs of 128
+  for (int k = 0; k < count; ++k) { padded = padded || p[k].rows != nullptr; deep = deep && p[k].K % 128 == 0 && (!p[k].a_trans || p[k].rows == nullptr); }
   int best = 0;
   double best_cost = 0.0;
   for (const TileCost& c : costs) {
+    if (c.bk == 128 && !deep) continue;
     double cost = 0.0;
     for (int share = padded ? 1 : 4; share <= 4; ++share) cost += launch_cost(c, p, count, share);
     if (best == 0 || cost < best_cost) { best = c.id; best_cost = cost; }
@@ -633,6 +738,8 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
   const bool dual = p[0].B2 != nullptr;
   int shape = g_force_shape;
   if (shape >= 11 && !dual) shape = 0;   // hi + lo tiles read B2
+  for (int k = 0; k < count; ++k)
+    if (shape == 20 && (p[k].K % 128 != 0 || (p[k].a_trans && p[k].rows != nullptr))) shape = 0;
   if (shape == 0) shape = dual ? pick_tile(HILO, p, count) : pick_tile(SINGLE, p, count);
   switch (shape) {
     case 1: launch_tile<S1, A_KC, B_KC>(ps, st, p, count, g_group); break;
@@ -651,6 +758,7 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
     case 17: launch_tile<D7, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 18: launch_tile<D8, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 19: launch_tile<D9, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 20: launch_tile<D10, A_KC, B_KC>(ps, st, p, count, g_group); break;
     default: launch_tile<S7, A_KC, B_KC>(ps, st, p, count, g_group); break;
   }
 }

@@ -184,7 +184,7 @@ def test_gemm_bf16_tile_edges(M, N, K, a_trans, b_trans, split):
     tB2 = _dev(B2, torch.bfloat16) if split else None
     L = B.load_library()
     first = None
-    for shape in (0,) + (tuple(range(11, 20)) if split else tuple(range(1, 9))):
+    for shape in (0,) + (tuple(range(11, 21)) if split else tuple(range(1, 9))):
         L.sama_dev_gemm_shape(ctypes.c_int32(shape))
         o32 = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
         B.op_gemm_bf16(tA, tB, a_trans=a_trans, b_trans=b_trans, B2=tB2, out32=o32)
@@ -194,9 +194,38 @@ def test_gemm_bf16_tile_edges(M, N, K, a_trans, b_trans, split):
     L.sama_dev_gemm_shape(ctypes.c_int32(0))
 
 
+@pytest.mark.parametrize("M,N", [(256, 192), (264, 200), (512, 384)])
+@pytest.mark.parametrize("split", [True, False])
+def test_gemm_bf16_outputs_of_any_alignment(M, N, split):
+    """bf16 and fp32 outputs in rows of a wider matrix, at every alignment that is accepted (8 and 16 bytes, row strides of a multiple of
+    four), whole tiles and ragged ones: the bits of the dense output and nothing beside it, with every tile."""
+    import ctypes
+    from paper_2310_05674_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    K = 128
+    A, W, W2 = (torch.randn(n, K, device=DEV, generator=g).to(torch.bfloat16) for n in (M, N, N))
+    bias = torch.randn(N, device=DEV, generator=g)
+    B2 = W2 * 0.004 if split else None
+    dense = torch.empty(M, N, device=DEV)
+    B.op_gemm_bf16(A, W, B2=B2, bias=bias, out32=dense)
+    L = B.load_library()
+    try:
+        for shape in tuple(range(11, 21)) if split else tuple(range(1, 9)):
+            L.sama_dev_gemm_shape(ctypes.c_int32(shape))
+            for off, pad in ((0, 0), (4, 4), (8, 8), (8, 12)):
+                for dtype in (torch.bfloat16, torch.float32):
+                    wide = torch.full((M, N + pad + off), 7.0, device=DEV, dtype=dtype)
+                    out = wide[:, off:off + N]
+                    B.op_gemm_bf16(A, W, B2=B2, bias=bias, **{"out16" if dtype == torch.bfloat16 else "out32": out})
+                    assert torch.equal(out, dense.to(dtype)), (shape, off, pad, dtype)
+                    assert (wide[:, :off] == 7).all() and (wide[:, off + N:] == 7).all(), (shape, off, pad, dtype)
+    finally:
+        L.sama_dev_gemm_shape(ctypes.c_int32(0))
+
+
 @pytest.mark.parametrize("K", [64, 128, 192])
 def test_gelu_of_every_bf16_value(K):
-    """The tiles that look the GELU factors up (11, 12, 13) against those that compute them (14, 15, 16), bit for bit, on every bf16
+    """The tiles that look the GELU factors up (11 to 14) against those that compute them (15, 16), bit for bit, on every bf16
     value, infinities and NaNs among them, and on ragged tiles; one to three slabs put the table at each of its places.  Bar
     against float64: erf to 1.5e-7, times |x|, and a few fp32 roundings of the result."""
     import ctypes
