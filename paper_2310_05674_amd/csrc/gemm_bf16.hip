@@ -54,12 +54,14 @@ constexpr int LDS_MAX = 160 * 1024;
 // RD: how the fetches of a piece lie between the products of the one before: n: over the first 1 / n of them; 0: with a strided operand right
 // before its own products (fewer registers, the order left to the compiler: 2 to 8% faster with three stages and for 256 x 256), else all
 // ahead of those products.
-template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NSTAGE_, bool DUAL_, int PW_ = 0, int YP_ = 0, int RD_ = 2>
+template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NSTAGE_, bool DUAL_, int PW_ = 0, int YP_ = 0, int RD_ = 2, int TW_ = 0>
 struct Tile {
-  static constexpr int PW = PW_, RD = RD_;
+  static constexpr int PW = PW_, RD = RD_, TW = TW_;
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_, NSTAGE = NSTAGE_;
   static constexpr bool DUAL = DUAL_;
-  static constexpr int WAVES = WGM * WGN, LW = PW > 0 ? PW : WAVES, THREADS = (WAVES + PW) * 64;   // multiplying, loading
+  static constexpr int WAVES = WGM * WGN, LW = PW > 0 ? PW : WAVES, THREADS = (WAVES + PW + TW) * 64;   // multiplying, loading
+  // TW: 1: a wave that touches the weights ahead of the loads (see the kernel)
+  static_assert(TW == 0 || PW > 0, "a touching wave only beside loading ones");
   static constexpr int WM = BM / WGM, WN = BN / WGN, XT = WM / 16, YT = WN / 16;
   static constexpr int YP = YP_ > 0 ? YP_ : YT, NP = YT / YP;               // pieces of a k-step
   static_assert(WM % 16 == 0 && WN % 32 == 0 && YT % YP == 0, "wave tiles");
@@ -272,6 +274,43 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) {
   const int tab_at = (iters - 1) % NSTAGE == 0 ? T::LDS_BYTES - GELU_TAB_BYTES : 0;
   const uint32_t lw = T::PW > 0 ? wave - WAVES : wave;            // number among the loading waves
   const bool loader = T::PW == 0 || wave >= WAVES;
+  if constexpr (T::TW > 0) {
+    if (wave == WAVES + T::PW) {
+      // Lines of the weights' next eight slabs, a word of each: an eighth of them for each of the up to eight workgroups of an XCD that read them.
+      // Weights in memory come slowly a slab at a time, 128 bytes of a row (or a few hundred of a k-row) here and there, however many slabs are
+      // in flight; a kilobyte of a row at once comes faster, and the slabs then find it in L2.  us without / with, weights cold (1.2 GB in turn):
+      // hi + lo 2048 x 1024 x 4096 NT 36.5 / 34.4, NN 42.1 / 36.5 (128 x 64 tiles), 1024 x 1024 x 4096 NT 27.6 / 23.7, NN 36.3 / 25.0 (64 x 64);
+      // weights warm 33.1 / 33.2, 34 / 34.6, 20.8 / 22.8, 24.8 / 23.3.  With fewer than 32 slabs there is no time for it (2048 x 1024 x 1024
+      // 10.1 / 10.9); done by a multiplying wave it costs all tiles 1 to 2 us; 128 x 128 tiles gain 2 us of 49 here and lose 1.5 of 41 there.
+      constexpr int TS = 8, TN = (BN + 63) / 64;   // slabs of a chunk, loads for an eighth of its lines
+      uint32_t off[TN], got = 0;
+      const uint32_t part = ti & 7;
+#pragma unroll
+      for (int u = 0; u < TN; ++u) {
+        if (B_KC) off[u] = min(j0 + part * (BN / 8) + u * 8 + lane / 8, (uint32_t)la.N - 1) * la.ldb * 2 + lane % 8 * 128;   // a line is a row's 64 values
+        else off[u] = (part * 64 + lane) * la.ldb * 2 + min(j0 + u * 64, (uint32_t)la.N - 8) * 2;                             // or 64 columns of a k-row
+      }
+      const uint32_t step = B_KC ? TS * BK * 2 : TS * BK * la.ldb * 2;
+      auto touch = [&](int chunk) {
+        if (iters < 4 * TS || (chunk + 1) * TS > iters) return;
+        const uint64_t at = (uint64_t)chunk * step;
+#pragma unroll
+        for (int u = 0; u < TN; ++u) asm volatile("global_load_dword %0, %1, %2" : "+v"(got) : "v"(off[u]), "s"(reinterpret_cast<const char*>(la.B) + at) : "memory");
+        if (DUAL) {
+#pragma unroll
+          for (int u = 0; u < TN; ++u) asm volatile("global_load_dword %0, %1, %2" : "+v"(got) : "v"(off[u]), "s"(reinterpret_cast<const char*>(la.B2) + at) : "memory");
+        }
+      };
+      touch(0);
+      for (int i = 0; i < iters; ++i) {
+        __builtin_amdgcn_s_barrier();
+        if (i % TS == 0) touch(i / TS + 1);
+      }
+      asm volatile("s_waitcnt vmcnt(0)" : "+v"(got)::"memory");   // into a register nobody else has until then
+      if (look_up) __syncthreads();
+      return;
+    }
+  }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void*)smem_raw;
 
   // ---- loads.  Direct global -> LDS: lane l of a wave-level load lands at (m0) + 16 l.  Written as inline assembly so
@@ -664,9 +703,9 @@ typedef Tile<256, 192, 64, 4, 2, 2, true, 4, 2, 1> D1;
 typedef Tile<256, 128, 64, 4, 2, 2, true, 4, 2, 2> D2;
 typedef Tile<128, 128, 64, 4, 2, 3, true, 4, 0, 2> D3;
 typedef Tile<128, 96, 64, 4, 1, 3, true, 4, 0, 2> D4;
-typedef Tile<128, 64, 64, 4, 2, 4, true, 4, 0, 1> D5;
-typedef Tile<64, 64, 64, 2, 2, 4, true, 2, 0, 1> D6;
-typedef Tile<64, 64, 64, 2, 2, 3, true, 2, 0, 1> D7;       // two workgroups per CU
+typedef Tile<128, 64, 64, 4, 2, 4, true, 4, 0, 1, 1> D5;
+typedef Tile<64, 64, 64, 2, 2, 4, true, 2, 0, 1, 1> D6;
+typedef Tile<64, 64, 64, 2, 2, 3, true, 2, 0, 1, 1> D7;       // two workgroups per CU
 typedef Tile<64, 32, 64, 4, 1, 4, true, 2, 0, 1> D8;       // two workgroups per CU
 typedef Tile<32, 32, 64, 2, 1, 6, true, 2, 0, 0> D9;       // two workgroups per CU
 typedef Tile<32, 32, 128, 2, 1, 3, true, 2, 0, 1> D10;     // two workgroups per CU; contractions of a multiple of 128
