@@ -33,6 +33,7 @@
 // Fused epilogues: + bias (fp32, optionally perturbed), + residual (fp32), GELU forward (writes both the
 // pre-activation and the activation), GELU backward (multiplies by gelu'(pre)), fp32 and/or bf16 stores.  The large hi + lo
 // tiles look the GELU factors up in a table that their loading waves bring into LDS during the last slab.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 #include "common.h"
@@ -182,6 +183,7 @@ struct GemmBatch {
   int ntiles, tiles_per_xcd, count, group;
   int first_tile[GEMM_MAX_BATCH + 1];   // tile ids [first_tile[k], first_tile[k + 1]) belong to problem k
   int kind[GEMM_MAX_BATCH];             // of each epilogue
+  uint64_t choice;                      // k_gemm_rows: four bits for each sixteenth of the rows, the tile to take where as many are in use
   GemmBf16Args p[GEMM_MAX_BATCH];
 };
 enum { EPI_ANY, EPI_C16, EPI_C32, EPI_RES32, EPI_GELU_FWD, EPI_GELU_BWD };
@@ -202,7 +204,7 @@ constexpr int SMALL_TILES = 1 << 20;
 // took 1.8 to 2.7 us from a workgroup's start to its first load, three quarters of it waiting for instructions; with the 150 here 0.5
 // to 0.6 us.  us per launch before / after, hi + lo: 128 x 3072 x 768 7.4 / 6.5, 2048 x 1024 x 1024 11.1 / 10.4, 2048 x 4096 x 1024 30.9 / 29.3.
 template <typename T, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) {
+__device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, XT = T::XT, YT = T::YT, NSTAGE = T::NSTAGE, WAVES = T::WAVES;
   constexpr bool DUAL = T::DUAL;
   constexpr int RD = (DUAL && !B_KC && NSTAGE == 3) || (T::RD == 0 && !(A_KC && B_KC)) ? 0 : T::RD == 0 ? 9 : T::RD;   // see Tile
@@ -283,6 +285,8 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) {
       // weights warm 33.1 / 33.2, 34 / 34.6, 20.8 / 22.8, 24.8 / 23.3.  With fewer than 32 slabs there is no time for it (2048 x 1024 x 1024
       // 10.1 / 10.9); done by a multiplying wave it costs all tiles 1 to 2 us; 128 x 128 tiles gain 2 us of 49 here and lose 1.5 of 41 there.
       constexpr int TS = 8, TN = (BN + 63) / 64;   // slabs of a chunk, loads for an eighth of its lines
+      static_assert(!T::TAB, "no barrier for the table");
+      if (iters < 4 * TS) return;
       uint32_t off[TN], got = 0;
       const uint32_t part = ti & 7;
 #pragma unroll
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) {
       }
       const uint32_t step = B_KC ? TS * BK * 2 : TS * BK * la.ldb * 2;
       auto touch = [&](int chunk) {
-        if (iters < 4 * TS || (chunk + 1) * TS > iters) return;
+        if ((chunk + 1) * TS > iters) return;
         const uint64_t at = (uint64_t)chunk * step;
 #pragma unroll
         for (int u = 0; u < TN; ++u) asm volatile("global_load_dword %0, %1, %2" : "+v"(got) : "v"(off[u]), "s"(reinterpret_cast<const char*>(la.B) + at) : "memory");
@@ -307,7 +311,6 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) {
         if (i % TS == 0) touch(i / TS + 1);
       }
       asm volatile("s_waitcnt vmcnt(0)" : "+v"(got)::"memory");   // into a register nobody else has until then
-      if (look_up) __syncthreads();
       return;
     }
   }
@@ -655,6 +658,9 @@ __global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) {
   });
 }
 
+template <typename T, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) { gemm_tile<T, A_KC, B_KC>(batch); }
+
 // What a whole tile's epilogue does, where it is one of the usual things on usual alignments.
 int epilogue_kind(const GemmBf16Args& a) {
   if (a.ldc % 8 != 0 || a.ldc >= (1 << 24) || (((uintptr_t)a.C16 | (uintptr_t)a.C16_pre | (uintptr_t)a.aux16) & 15) != 0) return EPI_ANY;
@@ -664,13 +670,7 @@ int epilogue_kind(const GemmBf16Args& a) {
   return a.C32 != nullptr ? EPI_C32 : EPI_C16;
 }
 
-template <typename T, bool A_KC, bool B_KC>
-void launch_tile(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count, int group) {
-  static bool configured = false;      // per instantiation: raise the dynamic LDS limit once
-  if (!configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16<T, A_KC, B_KC>), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
-    configured = true;
-  }
+GemmBatch make_batch(const GemmBf16Args* p, int count, int group, int bm, int bn) {
   GemmBatch b{};
   b.first = loop_args(p[0]);
   b.count = count; b.group = group;
@@ -679,10 +679,21 @@ void launch_tile(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count
     b.p[k] = p[k];
     b.kind[k] = epilogue_kind(p[k]);
     b.first_tile[k] = nt;
-    nt += ((p[k].N + T::BN - 1) / T::BN) * ((p[k].M + T::BM - 1) / T::BM);
+    nt += ((p[k].N + bn - 1) / bn) * ((p[k].M + bm - 1) / bm);
   }
   for (int k = count; k <= GEMM_MAX_BATCH; ++k) b.first_tile[k] = nt;
   b.ntiles = nt; b.tiles_per_xcd = (nt + 7) / 8;
+  return b;
+}
+
+template <typename T, bool A_KC, bool B_KC>
+void launch_tile(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count, int group) {
+  static bool configured = false;      // per instantiation: raise the dynamic LDS limit once
+  if (!configured) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16<T, A_KC, B_KC>), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+    configured = true;
+  }
+  const GemmBatch b = make_batch(p, count, group, T::BM, T::BN);
   launch_kernel(ps, k_gemm_bf16<T, A_KC, B_KC>, 8 * b.tiles_per_xcd, T::THREADS, T::LDS_BYTES, st, b);
 }
 
@@ -710,14 +721,36 @@ typedef Tile<64, 32, 64, 4, 1, 4, true, 2, 0, 1> D8;       // two workgroups per
 typedef Tile<32, 32, 64, 2, 1, 6, true, 2, 0, 0> D9;       // two workgroups per CU
 typedef Tile<32, 32, 128, 2, 1, 3, true, 2, 0, 1> D10;     // two workgroups per CU; contractions of a multiple of 128
 
+// A hi + lo product of a padded batch: the tile is chosen here, by the rows in use, among four of one workgroup to a CU.  (The waves that a
+// tile does not have end at once; the bodies are those of the launches with one tile, but for the touching waves, for which 168 registers a wave
+// leave no room.)
+typedef Tile<128, 64, 64, 4, 2, 4, true, 4, 0, 1> R5;
+constexpr int ROWS_THREADS = D1::THREADS, ROWS_SHARES = 16;
+static_assert(D2::THREADS <= ROWS_THREADS && D4::THREADS <= ROWS_THREADS && R5::THREADS <= ROWS_THREADS, "waves");
+template <typename T, bool B_KC>
+__device__ __forceinline__ void gemm_rows_tile(const GemmBatch& batch) {
+  if (T::THREADS == ROWS_THREADS || (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x) < (uint32_t)T::THREADS) gemm_tile<T, true, B_KC>(batch);
+}
+template <bool B_KC>
+__global__ __launch_bounds__(ROWS_THREADS) void k_gemm_rows(GemmBatch batch) {
+  const uint32_t in_use = *(const __attribute__((address_space(4))) int32_t*)batch.first.rows;
+  const uint32_t share = small_quotient(ROWS_SHARES * in_use - 1, batch.first.M);   // 0 < in_use <= M
+  switch ((uint32_t)(batch.choice >> (4 * share)) & 15) {
+    case 1: return gemm_rows_tile<D1, B_KC>(batch);
+    case 2: return gemm_rows_tile<D2, B_KC>(batch);
+    case 4: return gemm_rows_tile<D4, B_KC>(batch);
+    default: return gemm_rows_tile<R5, B_KC>(batch);
+  }
+}
+
 // What a launch costs with a tile, in us, beyond what it costs with any: per round, epilogue + 64-deep slabs x time of a slab.
 // A round is up to `per_cu` tiles on each of the 256 CUs; a slab takes `few` with a handful of tiles on the chip, `one` with one
 // on every CU and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.
-// The numbers are robust least-squares fits of the logarithms over 2561 timed problems (widths 192 to 2048, FFN 2 and 4 times that,
+// The numbers are robust least-squares fits of the logarithms over timed problems (widths 192 to 2048, FFN 2 and 4 times that,
 // 64 to 8192 rows: NT, NN, pairs of NT, a layer's four TN problems in a launch; the vocabulary head's products over 8192 to
-// 50304 tokens; weights cold), taken when the GELU epilogues computed their factors and averaged over the kinds of epilogue.  On the
-// times of the kernels as they are, picking by them takes 0.9% (hi + lo) and 1.2% (single-term) longer in total than the fastest
-// tile of each problem, a fit of these 0.6% and 1.2%; GELU backward 1.7%, the head's products 0.4 to 3.3%: profiles/gemm_tile_costs.md.
+// 50304 tokens; weights cold).  On the times of the kernels as they are, picking by them takes 0.4% (NT), 0.3% (pairs), 0.6% (NN) and 0.5% (TN)
+// longer in total than the fastest tile of each problem, the head's products 1 to 2%; by one table for NT and NN, NN takes 2.6% and the head's
+// NN 7%: profiles/gemm_tile_costs.md.
 struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; int bk = 64; };
 constexpr TileCost SINGLE[] = {
     {1, 256, 256, 1, 1.282, 1.816, 0, 0, 8.26}, {2, 256, 192, 1, 1.060, 1.218, 0, 0, 8.62},
@@ -731,18 +764,26 @@ constexpr TileCost HILO[] = {
     {17, 64, 64, 2, 0.449, 0.469, 0.723, 0.723, 1.59}, {18, 64, 32, 2, 0.320, 0.341, 0.528, 0.528, 1.42},
     {19, 32, 32, 2, 0.236, 0.255, 0.381, 0.381, 1.28}, {20, 32, 32, 2, 0.220, 0.240, 0.360, 0.360, 1.28, 128}};
 
+constexpr TileCost HILO_NN[] = {   // the strided weights of an input gradient
+    {11, 256, 192, 1, 1.203, 1.828, 0, 0, 8.00},  {12, 256, 128, 1, 0.998, 1.366, 0, 0, 3.68},
+    {13, 128, 128, 1, 0.693, 0.886, 0, 0, 2.39},  {14, 128, 96, 1, 0.587, 0.720, 0, 0, 1.74},
+    {15, 128, 64, 1, 0.364, 0.497, 0, 0, 0.95},   {16, 64, 64, 1, 0.247, 0.339, 0, 0, 0.52},
+    {17, 64, 64, 2, 0.299, 0.373, 0.557, 0.642, 0.60}, {18, 64, 32, 2, 0.217, 0.309, 0.450, 0.498, 0.11},
+    {19, 32, 32, 2, 0.178, 0.268, 0.376, 0.422, 0.19}, {20, 32, 32, 2, 0.235, 0.335, 0.347, 0.446, 0.00, 128}};
+
 int g_force_shape = 0, g_group = 8;
 
-// Cost of a launch with `share` quarters of a padded batch's rows in use.
-double launch_cost(const TileCost& c, const GemmBf16Args* p, int count, int share) {
+// Tiles, and cost, of a launch with `share` of `of` parts of a padded batch's rows in use.
+double launch_cost(const TileCost& c, const GemmBf16Args* p, int count, int share, int of, int64_t* ntiles = nullptr) {
   int64_t tiles = 0;
   double slabs = 0.0;                                    // of all tiles
   for (int k = 0; k < count; ++k) {
-    const int64_t part = p[k].rows != nullptr ? share : 4, M = p[k].a_trans ? p[k].M : (p[k].M * part + 3) / 4, K = p[k].a_trans ? (p[k].K * part + 3) / 4 : p[k].K;
+    const int64_t part = p[k].rows != nullptr ? share : of, M = p[k].a_trans ? p[k].M : (p[k].M * part + of - 1) / of, K = p[k].a_trans ? (p[k].K * part + of - 1) / of : p[k].K;
     const int64_t t = ((M + c.bm - 1) / c.bm) * ((p[k].N + c.bn - 1) / c.bn);
     tiles += t;
     slabs += (double)t * K / 64.0;
   }
+  if (ntiles != nullptr) *ntiles = tiles;
   slabs /= (double)tiles;
   const int64_t cap = 256 * c.per_cu, rest = tiles % cap;
   double cost = (double)(tiles / cap) * (slabs * (c.per_cu > 1 ? c.all : c.one) + c.epilogue);
@@ -753,23 +794,59 @@ double launch_cost(const TileCost& c, const GemmBf16Args* p, int count, int shar
   return cost;
 }
 
-// How many rows of a padded batch are in use only the device knows, and how long texts are is the caller's: the tile is the one
-// that costs least in total over batches a quarter, half, three quarters and all in use.  Longer than the fastest tile of a
-// product at each of these (geometric means over the same timed problems): 16, 6, 7 and 9%; choosing for one share in between, two
-// thirds, 30, 11, 5 and 8%, for all rows 37, 16, 5 and 2%.
+// How many rows of a padded batch are in use only the device knows, and how long texts are is the caller's: where one tile has to do for
+// the launch, it is the one that costs least in total over batches a quarter, half, three quarters and all in use.  Longer than the fastest
+// tile of a product at each of these (geometric means): 16, 6, 7 and 9%; choosing for one share in between, two thirds, 30, 11, 5 and 8%, for
+// all rows 37, 16, 5 and 2%.
 template <int N>
-int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count) {
-  bool padded = false, deep = true;   // deep: whole slabs of 128
-  for (int k = 0; k < count; ++k) { padded = padded || p[k].rows != nullptr; deep = deep && p[k].K % 128 == 0 && (!p[k].a_trans || p[k].rows == nullptr); }
+int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count, bool padded, double* total) {
+  bool deep = true;   // whole slabs of 128
+  for (int k = 0; k < count; ++k) deep = deep && p[k].K % 128 == 0 && (!p[k].a_trans || p[k].rows == nullptr);
   int best = 0;
-  double best_cost = 0.0;
   for (const TileCost& c : costs) {
     if (c.bk == 128 && !deep) continue;
     double cost = 0.0;
-    for (int share = padded ? 1 : 4; share <= 4; ++share) cost += launch_cost(c, p, count, share);
-    if (best == 0 || cost < best_cost) { best = c.id; best_cost = cost; }
+    for (int share = padded ? 1 : 4; share <= 4; ++share) cost += launch_cost(c, p, count, share, 4);
+    if (best == 0 || cost < *total) { best = c.id; *total = cost; }
   }
   return best;
+}
+
+// The same for k_gemm_rows: the tile of least cost for each sixteenth of the rows; returns whether that is worth more over the quarters than
+// the 0.4 us a launch that the choice takes.
+template <int N>
+bool pick_by_rows(const TileCost (&costs)[N], const GemmBf16Args* p, int count, double one_tile, uint64_t* choice, int64_t* most_tiles) {
+  double total = 0.0;
+  *choice = 0; *most_tiles = 0;
+  for (int share = 1; share <= ROWS_SHARES; ++share) {
+    int best = 0;
+    double best_cost = 0.0;
+    int64_t best_tiles = 0;
+    for (const TileCost& c : costs) {
+      if (c.id != 11 && c.id != 12 && c.id != 14 && c.id != 15) continue;   // those of k_gemm_rows
+      int64_t tiles;
+      const double cost = launch_cost(c, p, count, share, ROWS_SHARES, &tiles);
+      if (best == 0 || cost < best_cost) { best = c.id - 10; best_cost = cost; best_tiles = tiles; }
+    }
+    *choice |= (uint64_t)best << (4 * (share - 1));
+    *most_tiles = std::max(*most_tiles, best_tiles);
+    if (share % (ROWS_SHARES / 4) == 0) total += best_cost + 0.4;
+  }
+  return total < one_tile;
+}
+
+template <bool B_KC>
+void launch_rows(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count, uint64_t choice, int64_t most_tiles) {
+  static bool configured = false;
+  constexpr int LDS = std::max({D1::LDS_BYTES, D2::LDS_BYTES, D4::LDS_BYTES, R5::LDS_BYTES});
+  if (!configured) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_rows<B_KC>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    configured = true;
+  }
+  GemmBatch b = make_batch(p, count, g_group, 64, 64);
+  b.choice = choice;
+  b.tiles_per_xcd = (int)((most_tiles + 7) / 8);
+  launch_kernel(ps, k_gemm_rows<B_KC>, 8 * b.tiles_per_xcd, ROWS_THREADS, LDS, st, b);
 }
 
 template <bool A_KC, bool B_KC>
@@ -779,7 +856,18 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
   if (shape >= 11 && !dual) shape = 0;   // hi + lo tiles read B2
   for (int k = 0; k < count; ++k)
     if (shape == 20 && (p[k].K % 128 != 0 || (p[k].a_trans && p[k].rows != nullptr))) shape = 0;
-  if (shape == 0) shape = dual ? pick_tile(HILO, p, count) : pick_tile(SINGLE, p, count);
+  if (shape == 0) {
+    bool padded = false;
+    for (int k = 0; k < count; ++k) padded = padded || p[k].rows != nullptr;
+    double total = 0.0;
+    shape = !dual ? pick_tile(SINGLE, p, count, padded, &total) : B_KC ? pick_tile(HILO, p, count, padded, &total) : pick_tile(HILO_NN, p, count, padded, &total);
+    if constexpr (A_KC) {
+      uint64_t choice;
+      int64_t tiles;
+      if (padded && dual && (B_KC ? pick_by_rows(HILO, p, count, total, &choice, &tiles) : pick_by_rows(HILO_NN, p, count, total, &choice, &tiles)))
+        return launch_rows<B_KC>(ps, st, p, count, choice, tiles);
+    }
+  }
   switch (shape) {
     case 1: launch_tile<S1, A_KC, B_KC>(ps, st, p, count, g_group); break;
     case 2: launch_tile<S2, A_KC, B_KC>(ps, st, p, count, g_group); break;

@@ -903,3 +903,35 @@ def test_head_of_many_classes_and_features(C, d):
         assert torch.equal(all_[:1], one)
     assert rel_l2(out[0][0].cpu().numpy(), orc.evaluate(x, y)[0]) < KTOL
     gpu.close()
+
+
+@pytest.mark.parametrize("dims", [(2, 320, 5, 896, 128, 300, 3), (2, 768, 12, 1536, 64, 300, 2)])
+def test_tile_chosen_by_the_rows_in_use(dims):
+    """Padded batches with from an eighth to all of their rows in use, at widths that are no multiple of the tiles: where the device chooses the
+    tile by the rows, every bit of a base step and of a meta step is that of one tile for all of them."""
+    import ctypes
+    from paper_2310_05674_amd import binding as B
+    L = B.load_library()
+    S, n = dims[4], 2048 // dims[4] * 2
+    wl = make_workload(3, n_train=2 * n, n_meta=8, dims=dims, batch=n, meta_batch=4)
+    _, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    (x, y), (xm, ym) = _batches(wl, 0)
+    start = {k: pull(gpu, k).copy() for k in ("THETA", "M", "V", "G", "LAMBDA", "META_M", "META_V")}
+    r = np.random.default_rng(5)
+    lens_sets = [np.full(n, k, dtype=np.int32) for k in sorted({1, 16, 17, S // 4 + 1, S // 2, S // 2 + 1, 3 * S // 4, S - 17, S - 16, S})]
+    lens_sets += [r.integers(1, S + 1, n).astype(np.int32) for _ in range(3)]
+    try:
+        for lens in lens_sets:
+            got = []
+            for shape in (0, 15):
+                L.sama_dev_gemm_shape(ctypes.c_int32(shape))
+                for k, v in start.items():
+                    gpu.set_state(k, v)
+                gpu.set_state("COUNTERS", np.array([3, 1, 0, 0], dtype=np.int64))
+                tb = dev_batch(gpu, x, y, lens=lens)
+                gpu.base_step(tb); gpu.meta_step(tb, dev_batch(gpu, xm, ym, lens=lens[:4]))
+                got.append([pull(gpu, k) for k in ("G", "THETA", "GMETA", "HYPERGRAD")])
+            assert all(np.isfinite(a).all() and np.array_equal(a, b) for a, b in zip(*got)), (int(lens.sum()), lens[:4])
+    finally:
+        L.sama_dev_gemm_shape(ctypes.c_int32(0))
+        gpu.close()
