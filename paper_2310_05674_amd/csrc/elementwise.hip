@@ -7,6 +7,7 @@
 // Each kernel streams every array exactly once with 16-byte accesses; nothing is re-read.
 #include "common.h"
 #include "kernels.h"
+#include "solver.h"
 
 namespace sama {
 
@@ -53,15 +54,6 @@ __device__ __forceinline__ void st_bf16_prefix(bf16_t* p, int64_t j, int64_t n16
 __device__ __forceinline__ float bf16_residual(float t) { return t - bf16_to_f32(f32_to_bf16(t)); }
 
 // ---------------------------------------------------------------------------------------------------------
-// Adam: m' = b1 m + (1-b1) g ; v' = b2 v + (1-b2) g^2 ; theta' = theta - lr c1 m' / (c2 sqrt(v') + eps)
-// with c1 = 1/(1-b1^t), c2 = 1/sqrt(1-b2^t) computed on the host in double.  Optionally refreshes the bf16
-// working copy of the first n16 elements (the GEMM weight matrices).
-__device__ __forceinline__ void adam_one(float g, float& m, float& v, float& th, const AdamArgs& a) {   // g includes the L2 term
-  m = fmaf(a.beta1, m, a.one_m_beta1 * g);
-  v = fmaf(a.beta2, v, a.one_m_beta2 * g * g);
-  th = th - a.lr_c1 * m / (fmaf(a.c2, sqrtf(v), a.eps));
-}
-
 template <int U>
 __global__ __launch_bounds__(EW_THREADS) void k_adam(float* __restrict__ g, float* __restrict__ m,
                                                      float* __restrict__ v, float* __restrict__ theta,
@@ -139,9 +131,11 @@ __global__ __launch_bounds__(EW_THREADS) void k_sgd(float* __restrict__ g, float
       f4 b;
 #pragma unroll
       for (int e = 0; e < EW_VEC; ++e) {
-        G[u][e] = fmaf(wd, T[u][e], G[u][e]);   // the gradient the solver was given
-        b[e] = mu != 0.f ? fmaf(mu, B[u][e], G[u][e]) : G[u][e];
-        T[u][e] = T[u][e] - lr * b[e];
+        float tt = T[u][e];
+        G[u][e] = fmaf(wd, tt, G[u][e]);   // the gradient the solver was given
+        float bb = B[u][e];
+        sgd_one(G[u][e], bb, tt, lr, mu);
+        b[e] = bb; T[u][e] = tt;
       }
       if (wd != 0.f) st_nt(g, j, G[u]);
       if (mu != 0.f) st_nt(buf, j, b);

@@ -20,8 +20,7 @@
 //   come from memory, and at the MFMA peak 256 x 256 tiles need 32 B/clk, 256 x 128 48, 128 x 128 64: small tiles are bound by
 //   this, and the weights of a product of few rows are fetched by the launch before it (k_ln_fwd, k_ln_bwd).  (profiles/gemm_bounds.md)
 //   workgroup ids are remapped so that each XCD (own L2) works on a compact patch of tiles
-//   a launch starts with an empty instruction cache, so what runs before a workgroup's first load and behind its last product is short
-//   straight code
+//   what runs before a workgroup's first load and behind its last product is short straight code
 //
 // For the theta +- eps v passes of Eq. 5 and the direct-gradient pass the weight operand is hi + lo (two bf16
 // halves).  DUAL tiles stage the A slab once together with the hi and the lo slab of B, and an MFMA contracts 16 values of A with those of hi,
@@ -114,8 +113,7 @@ __device__ __forceinline__ uint32_t piece_offset(uint32_t ldsoff, uint32_t row0,
   }
 }
 // The offsets of the NLOADS loads of wave `lw` of LW, which lie LW KB apart in the stage.  Where the swizzle repeats after P loads and no row
-// is clamped, load q is load q - P a uniform distance further on: few instructions, because all of them are fetched (from L2, the instruction
-// cache is empty when a launch starts) before a workgroup's first load leaves.
+// is clamped, load q is load q - P a uniform distance further on: few instructions, because all of them run before a workgroup's first load.
 template <bool KC, int R, int BK, int LW, int NLOADS>
 __device__ __forceinline__ void load_offsets(uint32_t (&off)[NLOADS], uint32_t lw, uint32_t lane, uint32_t row0, uint32_t nrows, uint32_t ld) {
   constexpr uint32_t ROW = KC ? BK * 2 : R * 2;     // bytes of a row of the stage
@@ -200,9 +198,10 @@ __device__ __forceinline__ uint32_t small_quotient(uint32_t a, uint32_t b) {
 }
 constexpr int SMALL_TILES = 1 << 20;
 
-// What runs before a workgroup's first load is short, and so is what the loading waves alone run: with 400 instructions of index arithmetic it
-// took 1.8 to 2.7 us from a workgroup's start to its first load, three quarters of it waiting for instructions; with the 150 here 0.5
-// to 0.6 us.  us per launch before / after, hi + lo: 128 x 3072 x 768 7.4 / 6.5, 2048 x 1024 x 1024 11.1 / 10.4, 2048 x 4096 x 1024 30.9 / 29.3.
+// What runs before a workgroup's first load is short, and the loading waves run nothing else: with 400 instructions of signed index arithmetic
+// (two integer divisions, a bounds check for each offset), scalar loads that waited for each other and a branch every dozen of them (a taken one
+// is 35 clk) it took 1.8 to 2.7 us from a workgroup's start to its first load; with the 150 here 0.5 to 0.6 us.  us per launch before / after,
+// hi + lo: 128 x 3072 x 768 7.4 / 6.5, 2048 x 1024 x 1024 11.1 / 10.4, 2048 x 4096 x 1024 30.9 / 29.3.
 template <typename T, bool A_KC, bool B_KC>
 __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, XT = T::XT, YT = T::YT, NSTAGE = T::NSTAGE, WAVES = T::WAVES;

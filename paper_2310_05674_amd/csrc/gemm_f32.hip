@@ -23,6 +23,7 @@
 #include "common.h"
 #include "kernels.h"
 #include "mfma_f32.h"
+#include "solver.h"
 
 namespace sama {
 namespace {
@@ -204,14 +205,45 @@ __device__ __forceinline__ void pick(T& a, T b, bool second) {
   a = second ? b : a;
 }
 
-// PAIR: there are two problems
-template <int XM, int XN, int FDEPTH, bool PAIR>
-__global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch) {
+// What the update of an element reads, and the update.
+struct Element { float m, v, t; };
+__device__ __forceinline__ Element state_of(const BaseUpdate& u, int64_t k) {
+  return Element{u.solver == 1 || u.mu != 0.f ? u.m[k] : 0.f, u.solver == 1 ? u.v[k] : 0.f, u.theta[k]};
+}
+__device__ __forceinline__ void update(const BaseUpdate& u, int64_t k, float g, Element s, bool store_g) {
+  const float ge = fmaf(u.wd, s.t, g);
+  if (store_g || u.wd != 0.f) u.g[k] = ge;   // the gradient the solver was given, kept for the adaptation
+  if (u.solver == 1) {
+    adam_one(ge, s.m, s.v, s.t, u.adam);
+    u.v[k] = s.v;
+  } else {
+    sgd_one(ge, s.m, s.t, u.lr, u.mu);
+  }
+  if (u.solver == 1 || u.mu != 0.f) u.m[k] = s.m;
+  u.theta[k] = s.t;
+}
+struct NoUpdate {};
+
+// PAIR: there are two problems.  UPDATE: a BaseUpdate, or NoUpdate
+template <int XM, int XN, int FDEPTH, bool PAIR, typename UPDATE>
+__global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch, UPDATE upd) {
+  constexpr bool UPD = std::is_same<UPDATE, BaseUpdate>::value;
   constexpr int TM = 16 * XM, TN = 16 * XN;
   __shared__ float red[FWAVES][TM][TN + 1];
   __shared__ float rsum[FWAVES][TM];
   const bool second = PAIR && (int)blockIdx.x >= batch.blocks[0];
   GemmF32Args a = batch.j[0];
+  if constexpr (UPD) {
+    if (upd.solver == 1 && upd.adam.dev != nullptr) { upd.adam.lr_c1 = upd.adam.dev[0]; upd.adam.c2 = upd.adam.dev[1]; }
+    if ((int)blockIdx.x >= batch.blocks[0]) {   // the parameters whose gradients earlier launches left: all but these M x N and M
+      const int64_t w0 = a.C - upd.g, b0 = a.rowsum - upd.g, nw = (int64_t)a.M * a.N;   // (dense, the vector behind the matrix)
+      int64_t k = ((int64_t)blockIdx.x - batch.blocks[0]) * (64 * FWAVES) + threadIdx.x;
+      if (k >= w0) k += nw;
+      if (k >= b0) k += a.M;
+      if (k < upd.n) update(upd, k, upd.g[k], state_of(upd, k), false);
+      return;
+    }
+  }
   if (PAIR) {
     const GemmF32Args& b = batch.j[1];
     pick(a.A, b.A, second); pick(a.sa_i, b.sa_i, second); pick(a.sa_k, b.sa_k, second);
@@ -229,6 +261,17 @@ __global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch) {
   const float bscale = (a.Bv != nullptr && a.beps != nullptr) ? a.bsign * (*a.beps) : 0.f;
   const bool rows = a.rowsum != nullptr && j0 == 0, full = (storage != F32_WGRAD || i0 + TM <= a.M) && j0 + TN <= a.N;
   float* const r0 = &red[0][0][0]; float* const r1 = &rsum[0][0];
+  // of the elements this thread will finish, and one row's
+  constexpr int NE = (TM * TN + 64 * FWAVES - 1) / (64 * FWAVES);
+  Element es[UPD ? NE : 1], er{};
+  if constexpr (UPD) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const int t = threadIdx.x + e * 64 * FWAVES, gi = min(i0 + t / TN, a.M - 1), gj = min(j0 + t % TN, a.N - 1);
+      es[e] = state_of(upd, a.C - upd.g + (int64_t)gi * a.ldc + gj);
+    }
+    er = state_of(upd, a.rowsum - upd.g + min(i0 + (int)(threadIdx.x % TM), a.M - 1));
+  }
   if (storage == F32_FORWARD) {
     if (bscale != 0.f) gemm_f32_tile<XM, XN, FDEPTH, true, true, true, true>(a, i0, j0, bscale, r0, r1);
     else gemm_f32_tile<XM, XN, FDEPTH, true, true, true, false>(a, i0, j0, 0.f, r0, r1);
@@ -240,9 +283,9 @@ __global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch) {
     else gemm_f32_tile<XM, XN, FDEPTH, false, false, false, false>(a, i0, j0, 0.f, r0, r1);
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < TM * TN; t += 64 * FWAVES) {
+  auto finish = [&](int t, const Element& el) {
     const int li = t / TN, lj = t % TN, gi = i0 + li, gj = j0 + lj;
-    if (gi >= a.M || gj >= a.N) continue;
+    if (gi >= a.M || gj >= a.N) return;
     float bias = 0.f;
     if (a.bias != nullptr) {
       bias = a.bias[gj];
@@ -252,15 +295,27 @@ __global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch) {
     float c = red[0][li][lj];
 #pragma unroll
     for (int w = 1; w < FWAVES; ++w) c += red[w][li][lj];
-    c += bias;
-    if (a.relu) c = fmaxf(c, 0.f);
-    a.C[(int64_t)gi * a.ldc + gj] = gate > 0.f ? c : 0.f;
+    if constexpr (UPD) {
+      update(upd, a.C - upd.g + (int64_t)gi * a.ldc + gj, c, el, true);
+    } else {
+      c += bias;
+      if (a.relu) c = fmaxf(c, 0.f);
+      a.C[(int64_t)gi * a.ldc + gj] = gate > 0.f ? c : 0.f;
+    }
+  };
+  if constexpr (UPD) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+      if (TM * TN % (64 * FWAVES) == 0 || (int)threadIdx.x + e * 64 * FWAVES < TM * TN) finish(threadIdx.x + e * 64 * FWAVES, es[e]);
+  } else {
+    for (int t = threadIdx.x; t < TM * TN; t += 64 * FWAVES) finish(t, er);
   }
   if (rows && (int)threadIdx.x < TM && i0 + (int)threadIdx.x < a.M) {
     float c = rsum[0][threadIdx.x];
 #pragma unroll
     for (int w = 1; w < FWAVES; ++w) c += rsum[w][threadIdx.x];
-    a.rowsum[i0 + threadIdx.x] = c;
+    if constexpr (UPD) update(upd, a.rowsum - upd.g + i0 + threadIdx.x, c, er, true);
+    else a.rowsum[i0 + threadIdx.x] = c;
   }
 }
 
@@ -270,19 +325,24 @@ int64_t tiles(const GemmF32Args* a, int count, int tm, int tn) {
   return n;
 }
 template <int XM, int XN, int FDEPTH>
-void launch_tile_f32(ProfScope& ps, hipStream_t st, const GemmF32Args* a, int count) {
+void launch_tile_f32(ProfScope& ps, hipStream_t st, const GemmF32Args* a, int count, const BaseUpdate* u) {
   GemmF32Batch b{};
   for (int k = 0; k < count; ++k) {
     b.j[k] = a[k];
     b.storage[k] = storage_of(a[k]);
     b.blocks[k] = (int)(tiles(a + k, 1, 16 * XM, 16 * XN) + 7) / 8 * 8;
   }
-  if (count == 2) launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, true>, b.blocks[0] + b.blocks[1], 64 * FWAVES, 0, st, b);
-  else launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, false>, b.blocks[0], 64 * FWAVES, 0, st, b);
+  if (u != nullptr) {
+    const int64_t rest = u->n - (int64_t)a[0].M * a[0].N - a[0].M;
+    launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, false, BaseUpdate>, b.blocks[0] + (int)((rest + 64 * FWAVES - 1) / (64 * FWAVES)), 64 * FWAVES, 0, st, b, *u);
+  } else if (count == 2) {
+    launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, true, NoUpdate>, b.blocks[0] + b.blocks[1], 64 * FWAVES, 0, st, b, NoUpdate{});
+  } else {
+    launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, false, NoUpdate>, b.blocks[0], 64 * FWAVES, 0, st, b, NoUpdate{});
+  }
 }
-}  // namespace
 
-void launch_gemm_f32_batch(hipStream_t st, const GemmF32Args* a, int count) {
+void launch(hipStream_t st, const GemmF32Args* a, int count, const BaseUpdate* u) {
   double flops = 0.0;
   for (int k = 0; k < count; ++k) {
     if (a[k].M <= 0 || a[k].N <= 0) { note_launch_error("empty fp32 GEMM"); return; }
@@ -296,9 +356,18 @@ void launch_gemm_f32_batch(hipStream_t st, const GemmF32Args* a, int count) {
   // 11.7 / 9.4, 512 (2048 x 256 x 784) 16.0 / 14.9.  Over 150 products and pairs (16 to 2048 rows, widths to 320, K to 1024) these
   // lines take 1.4% longer than the fastest tile of each, lines at 256 and 256 3.9% (geometric means).
   constexpr int CUS = 256;
-  if (tiles(a, count, 16, 16) <= 2 * CUS) launch_tile_f32<1, 1, 8>(ps, st, a, count);
-  else if (tiles(a, count, 32, 32) <= CUS) launch_tile_f32<2, 2, 4>(ps, st, a, count);
-  else launch_tile_f32<4, 2, 2>(ps, st, a, count);
+  if (tiles(a, count, 16, 16) <= 2 * CUS) launch_tile_f32<1, 1, 8>(ps, st, a, count, u);
+  else if (tiles(a, count, 32, 32) <= CUS) launch_tile_f32<2, 2, 4>(ps, st, a, count, u);
+  else launch_tile_f32<4, 2, 2>(ps, st, a, count, u);
+}
+}  // namespace
+
+void launch_gemm_f32_batch(hipStream_t st, const GemmF32Args* a, int count) { launch(st, a, count, nullptr); }
+void launch_gemm_f32_update(hipStream_t st, const GemmF32Args& a, const BaseUpdate& u) {
+  // the forms the kernel is for: a dense weight gradient with its bias gradient behind it, both in u.g
+  if (storage_of(a) != F32_WGRAD || a.ldc != a.N || a.rowsum == nullptr || a.C < u.g || a.rowsum < a.C + (int64_t)a.M * a.N || a.rowsum + a.M > u.g + u.n ||
+      a.bias != nullptr || a.gate != nullptr || a.relu) { note_launch_error("fp32 GEMM with an update: not a weight gradient"); return; }
+  launch(st, &a, 1, &u);
 }
 
 }  // namespace sama

@@ -1,6 +1,6 @@
 // ReLU MLP / multinomial logistic regression base learner in fp32: each layer is one forward GEMM with a fused
 // bias + ReLU epilogue; backward is one launch per layer: the wgrad GEMM with the bias gradient's column sums, and the
-// dgrad GEMM with the ReLU gate fused.
+// dgrad GEMM with the ReLU gate fused; in a base step the last of them also updates the parameters.
 #include "kernels.h"
 #include "model.h"
 
@@ -72,7 +72,11 @@ class MlpModel : public Model {
         g[1].M = b.n; g[1].N = dims_[l]; g[1].K = dims_[l + 1];
         g[1].gate = act_[l];
       }
-      launch_gemm_f32_batch(st, g, l > 0 ? 2 : 1);
+      // The first layer's launch, the last one, reads no weights: with it goes the update of all of them, which a launch of its own
+      // would wait for.
+      BaseUpdate u{};
+      if (l == 0 && sink_ != nullptr && sink_->take_over(&u)) launch_gemm_f32_update(st, g[0], u);
+      else launch_gemm_f32_batch(st, g, l > 0 ? 2 : 1);
       d = d_[l & 1];
     }
   }

@@ -193,6 +193,18 @@ static sama_status check_batch(sama_ctx* c, const sama_batch* b, int maxb, const
   return SAMA_OK;
 }
 
+static AdamArgs adam_args(sama_ctx* c, int64_t t) {
+  const sama_config& f = c->cfg;
+  AdamArgs a{};
+  a.beta1 = f.beta1; a.one_m_beta1 = (float)(1.0 - (double)f.beta1);
+  a.beta2 = f.beta2; a.one_m_beta2 = (float)(1.0 - (double)f.beta2);
+  a.lr_c1 = (float)((double)f.base_lr / (1.0 - pow((double)f.beta1, (double)t)));
+  a.c2 = (float)(1.0 / sqrt(1.0 - pow((double)f.beta2, (double)t)));
+  a.eps = f.adam_eps; a.weight_decay = f.weight_decay;
+  a.dev = c->step;   // the device's own step count decides (the host values above are what it holds in eager use)
+  return a;
+}
+
 // The base solver's update (App. C for Adam) of theta[off, off + count) with the gradient in c->g, for step number t.
 static void base_update_range(sama_ctx* c, hipStream_t st, int64_t t, int64_t off, int64_t count) {
   if (count <= 0) return;
@@ -201,13 +213,7 @@ static void base_update_range(sama_ctx* c, hipStream_t st, int64_t t, int64_t of
   bf16_t* t16 = (c->theta16 != nullptr && n16 > 0) ? c->theta16 + off : nullptr;
   bf16_t* lo0 = t16 != nullptr ? c->lo_0 + off : nullptr;   // every pass that writes theta keeps its residual half current
   if (f.base_opt == SAMA_OPT_ADAM) {
-    AdamArgs a{};
-    a.beta1 = f.beta1; a.one_m_beta1 = (float)(1.0 - (double)f.beta1);
-    a.beta2 = f.beta2; a.one_m_beta2 = (float)(1.0 - (double)f.beta2);
-    a.lr_c1 = (float)((double)f.base_lr / (1.0 - pow((double)f.beta1, (double)t)));
-    a.c2 = (float)(1.0 / sqrt(1.0 - pow((double)f.beta2, (double)t)));
-    a.eps = f.adam_eps; a.weight_decay = f.weight_decay;
-    a.dev = c->step;   // the device's own step count decides (the host values above are what it holds in eager use)
+    AdamArgs a = adam_args(c, t);
     a.lo = lo0;
     launch_adam(st, c->g + off, c->m + off, c->v + off, c->theta + off, t16, count, n16, a);
   } else {
@@ -224,6 +230,13 @@ struct UpdateSink : GradSink {
     if (off % 4 != 0 || count % 4 != 0 || off < 0 || off + count > c->n) return;   // left to the pass over the rest
     base_update_range(c, s, t, off, count);
     done.push_back({off, count});
+  }
+  bool take_over(BaseUpdate* u) override {
+    if (c->bf16 || !done.empty()) return false;
+    const sama_config& f = c->cfg;
+    *u = BaseUpdate{f.base_opt == SAMA_OPT_ADAM ? 1 : 2, adam_args(c, t), f.base_lr, f.weight_decay, f.momentum, c->g, c->m, c->v, c->theta, c->n};
+    done.push_back({0, c->n});
+    return true;
   }
 };
 

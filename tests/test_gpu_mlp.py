@@ -484,3 +484,47 @@ def test_fp32_products_at_their_edges(dims, B):
     assert rel_l2(pull(gpu, "GMETA"), rr["g_meta"]) < TOL
     assert rel_l2(pull(gpu, "GLAM_PLUS"), rr["glam_p"]) < 2e-5 and rel_l2(pull(gpu, "GLAM_MINUS"), rr["glam_m"]) < 2e-5
     gpu.close()
+
+
+@pytest.mark.parametrize("dims", [(7, 3), (32, 2), (301, 173, 61, 10), (33, 1, 5), (64, 16, 16, 4), (1024, 320, 320, 300, 12), (1000, 400, 250, 15)])
+@pytest.mark.parametrize("solver", ["adam", "adam_wd", "sgd", "sgd_momentum_wd"])
+def test_update_of_every_parameter(dims, solver):
+    """The update that rides on the last gradient launch, products of each tile size, one layer and four: every parameter and moment follows from the state before the step and the kept gradient.  Bars: the few fp32 roundings of each formula."""
+    import torch
+    import paper_2310_05674_amd as pkg
+    wd, mu = (0.3 if "wd" in solver else 0.0), (0.9 if "momentum" in solver else 0.0)
+    adam = solver.startswith("adam")
+    cfg = pkg.SamaConfig.make("mlp", list(dims), H=16, max_batch=50, max_meta_batch=8, base_lr=1e-2, weight_decay=wd, momentum=mu,
+                              base_opt=pkg.OPT_ADAM if adam else pkg.OPT_SGD)
+    n = sum(a * b + b for a, b in zip(dims, dims[1:]))
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    rnd = lambda k, s=1.0: torch.randn(k, device="cuda", generator=gen) * s
+    s = pkg.Sama(cfg, rnd(n, 0.1), rnd(3 * 16 + 1, 0.3))
+    s.set_state("M", rnd(n, 0.1))
+    s.set_state("V", rnd(n, 0.1) ** 2 + 1e-4)
+    s.set_state("COUNTERS", np.array([4, 1, 0, 0], dtype=np.int64))
+    th0, m0, v0 = (s.get_state(k).double() for k in ("THETA", "M", "V"))
+    x = rnd(50 * dims[0]).reshape(50, dims[0])
+    y = torch.randint(0, dims[-1], (50,), device="cuda", generator=gen, dtype=torch.int32)
+    s.base_step(s.batch(x, y))
+    g, th, m, v = (s.get_state(k).double() for k in ("G", "THETA", "M", "V"))
+    assert (g != 0).any() and torch.isfinite(th).all()
+    if wd:   # the kept gradient is the one the solver was given: zero-gradient parameters show the L2 term alone
+        assert (g - wd * th0).norm() < 10 * g.norm()
+    ulp = 2.0 ** -23
+    if adam:
+        b1, b2 = float(np.float32(0.9)), float(np.float32(0.999))
+        mw, vw = b1 * m0 + (1 - b1) * g, b2 * v0 + (1 - b2) * g * g
+        assert ((m - mw).abs() <= 4 * ulp * ((b1 * m0).abs() + ((1 - b1) * g).abs()) + 1e-30).all()
+        assert ((v - vw).abs() <= 8 * ulp * vw + 1e-30).all()
+        step = 1e-2 / (1 - b1 ** 5) * m / (v.sqrt() / (1 - b2 ** 5) ** 0.5 + 1e-8)
+    else:
+        b = mu * m0 + g if mu else g
+        if mu:
+            assert ((m - b).abs() <= 4 * ulp * ((mu * m0).abs() + g.abs()) + 1e-30).all()
+        else:
+            assert torch.equal(m, m0)
+        assert torch.equal(v, v0)
+        step = 1e-2 * (m if mu else b)
+    assert ((th - (th0 - step)).abs() <= 2e-6 * step.abs() + ulp * th0.abs() + 1e-30).all()
+    s.close()
