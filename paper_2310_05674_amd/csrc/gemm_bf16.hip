@@ -491,9 +491,9 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   // time; of two neighbouring fragments in bf16, lanes 16 apart exchange halves first, so that a lane has eight neighbouring columns of
   // one of them.  Nothing goes through LDS.
   // A unit is a pair of fragments side by side, the units of a column of them follow each other.  Whole tiles of the usual kinds go through
-  // code of their own for each kind (few instructions, which come from L2 like those at the start); what a unit needs from memory (bias,
-  // an fp32 residual or a saved pre-activation, an epilogue has one of these at most) is requested DEPTH - 1 units before it, for the first ones while the
-  // last slab is multiplied.
+  // code of their own for each kind, without a branch in it; what a unit needs from memory (bias, an fp32 residual or a saved
+  // pre-activation, an epilogue has one of these at most) is requested DEPTH - 1 units before it, for the first ones while the last slab
+  // is multiplied.
   constexpr int UNITS = YT / 2 * XT, DEPTH = XT * YT > 16 ? 2 : XT * YT == 16 ? 3 : 4;
   const bool fast = kind != EPI_ANY && i0 + BM <= rows_of && j0 + BN <= (uint32_t)la.N;
   const int g = (int)lane >> 4, pair_col = 16 * (g & 1) + 8 * (g >> 1);   // columns of the lane's values: 4 g, after the exchange pair_col
