@@ -142,9 +142,14 @@ class EncoderModel : public Model {
   // 1893 / 1864, base step of 4096 5471 / 5454, padded 4812 / 4802; 24 x 1024 base step of 2048 rows 10418 / 10350; scoring 128 rows of 12 x 576
   // (177 MB) 542 / 551.  The stacked passes count the rows of both: left out of them, as the rule does at 24 x 1024 and 1024 rows, an
   // iteration takes 18867 us, with it there too 18928.
+  // Padded batches go on to twice as many rows in use where two weights are at most 20 MB: the tiles that are chosen on the device have no wave that
+  // touches weights ahead.  Without it / with it: 12 x 768 iteration of 4096 rows, 2900 in use, 12875 / 12546, scoring 8192 padded rows 2837 / 2669 (base step
+  // of 4096, 8 x 640, 12 x 512 and 12 x 384 within 0.7 %); without lengths nothing changes at 4096 rows (5512 / 5507), and at 24 x 1024,
+  // 34 MB for two, 2048 rows lose (27180 / 27540).
   WeightsAhead weights_ahead(const PassWeights* w, int nw, bool scoring, int64_t off, int64_t n, int rows, const int32_t* in_use) const {
     WeightsAhead a{};
-    a.max_rows = (2 << 20) / (nw * d_);
+    const bool more = in_use != nullptr && std::max((int64_t)16 * d_ * d_, (int64_t)8 * ffn_ * d_) <= 20000000;   // bytes of two weights
+    a.max_rows = ((more ? 4 : 2) << 20) / (nw * d_);
     const int64_t params = L_ * ((int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_);
     if (params * (scoring ? 4 : 20) < 256000000 || (in_use == nullptr && rows >= a.max_rows)) return a;
     for (int k = 0; k < nw; ++k) { a.p[2 * k] = w[k].hi + off; a.p[2 * k + 1] = w[k].lo != nullptr ? w[k].lo + off : nullptr; }

@@ -887,6 +887,24 @@ def test_weights_fetched_ahead(B, padded):
     gpu.close()
 
 
+@pytest.mark.parametrize("kept", [52, 100, 124])
+def test_weights_fetched_ahead_of_many_padded_rows(kept):
+    """7680 rows of 640 with about 3100, 6000 and 7400 in use: the LayerNorms of a base step fetch the next weights with the first two.  Scoring
+    never does at this size; the losses of both are the same bits."""
+    import torch
+    B = 60
+    wl = make_workload(3, n_train=B, n_meta=2, dims=(4, 640, 10, 1280, 128, 300, 3), batch=B, meta_batch=2)
+    _, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    x, y = wl.x_train[:B], wl.y_train[:B]
+    lens = np.clip(np.arange(B) % 9 - 4 + kept, 1, 128).astype(np.int32)
+    out = [torch.zeros(s, device=gpu.dev) for s in ((B, 3), (B,), (B,))]
+    gpu.eval(dev_batch(gpu, x, y, lens=lens), *out)
+    gpu.base_step(dev_batch(gpu, x, y, lens=lens))
+    assert np.isfinite(pull(gpu, "G")).all()
+    assert np.array_equal(pull(gpu, "LOSSES")[:B], out[1].cpu().numpy())
+    gpu.close()
+
+
 @pytest.mark.parametrize("C,d", [(8, 192), (9, 192), (21, 1088)])
 def test_head_of_many_classes_and_features(C, d):
     """The classifier with as many classes as are taken at a time, one more, and three times as many over more features than are:
