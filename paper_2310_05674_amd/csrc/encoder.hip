@@ -22,7 +22,8 @@ namespace {
 // 12 x 768) 5536 / 5560, 12.9 (4096, 2 x 256) 878 / 898, 14.5 (4096, 4 x 192) 1481 / 1548, 20.5 (2048, 4 x 384) 1750 / 1764, 36 (2048,
 // 4 x 512) 2056 / 2124, 43 (4096, 12 x 192) 4334 / 4698.  Of 172 shapes (1 to 24 layers of 192 to 1024, 256 to 8192 rows, 16 of them
 // padded) four take more than 1 % longer than on the other side, at most 3.2 %; by the plain product of rows and parameters 19
-// (6.9 %), by that of one layer 18 (6.2 %): profiles/second_stream.md.
+// (6.9 %), by that of one layer 18 (6.2 %).  With the products faster (16x16x32 MFMAs) 16 do, at most 3.3 %; lines from 8 to 30 are no better
+// than this one: profiles/second_stream.md.
 inline bool side_wanted(int64_t rows, int layers, int64_t layer_params) {
   if (g_side_stream == 0 || g_side_stream == 2) return g_side_stream == 2;
   return layers > 1 && (double)rows * (double)(layers * layer_params) * std::sqrt((double)rows / 1024.0) >= 1.05e10;
