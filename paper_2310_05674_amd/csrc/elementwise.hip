@@ -54,6 +54,7 @@ __device__ __forceinline__ void st_bf16_prefix(bf16_t* p, int64_t j, int64_t n16
 __device__ __forceinline__ float bf16_residual(float t) { return t - bf16_to_f32(f32_to_bf16(t)); }
 
 // ---------------------------------------------------------------------------------------------------------
+// Adam over a range; optionally refreshes the bf16 working copy of its first n16 elements (the GEMM weight matrices).
 template <int U>
 __global__ __launch_bounds__(EW_THREADS) void k_adam(float* __restrict__ g, float* __restrict__ m,
                                                      float* __restrict__ v, float* __restrict__ theta,

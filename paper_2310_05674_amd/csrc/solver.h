@@ -6,8 +6,7 @@
 namespace sama {
 
 // Adam: m' = b1 m + (1-b1) g ; v' = b2 v + (1-b2) g^2 ; theta' = theta - lr c1 m' / (c2 sqrt(v') + eps)
-// with c1 = 1/(1-b1^t), c2 = 1/sqrt(1-b2^t) computed on the host in double.  Optionally refreshes the bf16
-// working copy of the first n16 elements (the GEMM weight matrices).
+// with c1 = 1/(1-b1^t), c2 = 1/sqrt(1-b2^t) computed on the host in double.
 __device__ __forceinline__ void adam_one(float g, float& m, float& v, float& th, const AdamArgs& a) {   // g includes the L2 term
   m = fmaf(a.beta1, m, a.one_m_beta1 * g);
   v = fmaf(a.beta2, v, a.one_m_beta2 * g * g);
