@@ -236,9 +236,10 @@ __global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch, UP
   if constexpr (UPD) {
     if (upd.solver == 1 && upd.adam.dev != nullptr) { upd.adam.lr_c1 = upd.adam.dev[0]; upd.adam.c2 = upd.adam.dev[1]; }
     if ((int)blockIdx.x >= batch.blocks[0]) {   // the parameters whose gradients earlier launches left: all but these M x N and M
-      const int64_t w0 = a.C - upd.g, b0 = a.rowsum - upd.g, nw = (int64_t)a.M * a.N;   // (dense, the vector behind the matrix)
+      const int64_t w0 = a.C - upd.g, b0 = a.rowsum - upd.g, nw = (int64_t)a.M * a.N;   // (dense, the vector behind the matrix), and those set apart between them
       int64_t k = ((int64_t)blockIdx.x - batch.blocks[0]) * (64 * FWAVES) + threadIdx.x;
       if (k >= w0) k += nw;
+      if (k >= upd.apart) k += upd.apart_count;
       if (k >= b0) k += a.M;
       if (k < upd.n) update(upd, k, upd.g[k], state_of(upd, k), false);
       return;
@@ -333,7 +334,7 @@ void launch_tile_f32(ProfScope& ps, hipStream_t st, const GemmF32Args* a, int co
     b.blocks[k] = (int)(tiles(a + k, 1, 16 * XM, 16 * XN) + 7) / 8 * 8;
   }
   if (u != nullptr) {
-    const int64_t rest = u->n - (int64_t)a[0].M * a[0].N - a[0].M;
+    const int64_t rest = u->n - (int64_t)a[0].M * a[0].N - a[0].M - u->apart_count;
     launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, false, BaseUpdate>, b.blocks[0] + (int)((rest + 64 * FWAVES - 1) / (64 * FWAVES)), 64 * FWAVES, 0, st, b, *u);
   } else if (count == 2) {
     launch_kernel(ps, k_gemm_f32<XM, XN, FDEPTH, true, NoUpdate>, b.blocks[0] + b.blocks[1], 64 * FWAVES, 0, st, b, NoUpdate{});
@@ -366,6 +367,7 @@ void launch_gemm_f32_batch(hipStream_t st, const GemmF32Args* a, int count) { la
 void launch_gemm_f32_update(hipStream_t st, const GemmF32Args& a, const BaseUpdate& u) {
   // the forms the kernel is for: a dense weight gradient with its bias gradient behind it, both in u.g
   if (storage_of(a) != F32_WGRAD || a.ldc != a.N || a.rowsum == nullptr || a.C < u.g || a.rowsum < a.C + (int64_t)a.M * a.N || a.rowsum + a.M > u.g + u.n ||
+      (u.apart_count != 0 && (u.apart_count < 0 || u.apart < a.C + (int64_t)a.M * a.N - u.g || u.apart + u.apart_count > a.rowsum - u.g)) ||
       a.bias != nullptr || a.gate != nullptr || a.relu) { note_launch_error("fp32 GEMM with an update: not a weight gradient"); return; }
   launch(st, &a, 1, &u);
 }

@@ -210,9 +210,10 @@ struct BaseUpdate {
   int solver;                             // 0: none, 1: Adam, 2: SGD
   AdamArgs adam; float lr, wd, mu;
   float *g, *m, *v, *theta; int64_t n;
+  int64_t apart, apart_count;             // the first, and how many, of those that the launch leaves alone: behind its product's C, before its rowsum
 };
 // A weight gradient (C and rowsum inside u.g) in one launch with the update of every parameter: the launch's own results are updated as
-// they are stored, the other gradients by workgroups beside those of the product.  us a base step with the update in a launch of its own /
+// they are stored, the other gradients (but for those set apart) by workgroups beside those of the product.  us a base step with the update in a launch of its own /
 // with the last gradient, Adam: 66 parameters 13.4 / 11.6, 63 thousand 29.9 / 27.4, 269 thousand 33.3 / 30.7, 531 thousand 58.9 / 54.7,
 // 1.6 million 80 / 70; SGD 12.9 / 11.4, 29.4 / 27.0, 32.5 / 30.1, 56.7 / 53.8, 74.7 / 69.8.
 void launch_gemm_f32_update(hipStream_t, const GemmF32Args& a, const BaseUpdate& u);

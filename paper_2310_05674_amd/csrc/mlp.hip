@@ -72,10 +72,10 @@ class MlpModel : public Model {
         g[1].M = b.n; g[1].N = dims_[l]; g[1].K = dims_[l + 1];
         g[1].gate = act_[l];
       }
-      // The first layer's launch, the last one, reads no weights: with it goes the update of all of them, which a launch of its own
-      // would wait for.
+      // The first layer's launch, the last one, reads no weights: with it goes the update of all of them, or of those it computes, which a
+      // launch of its own would wait for.
       BaseUpdate u{};
-      if (l == 0 && sink_ != nullptr && sink_->take_over(&u)) launch_gemm_f32_update(st, g[0], u);
+      if (l == 0 && sink_ != nullptr && sink_->take_over(&u, (int64_t)g[0].M * g[0].N, boff_[0])) launch_gemm_f32_update(st, g[0], u);
       else launch_gemm_f32_batch(st, g, l > 0 ? 2 : 1);
       d = d_[l & 1];
     }

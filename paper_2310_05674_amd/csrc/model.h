@@ -65,9 +65,10 @@ struct MlmBatch {
 struct GradSink {
   virtual ~GradSink() {}
   virtual void ready(hipStream_t s, int64_t off, int64_t count) = 0;
-  // The update this consumer is about to make of every parameter, handed to a model that makes it itself, along with the last of its
-  // gradients; false: the consumer has none to give away.
-  virtual bool take_over(BaseUpdate*) { return false; }
+  // The update this consumer is about to make of every parameter, handed to a model that makes it itself along with the last of its
+  // gradients, the matrix in front of `from` and a vector at `to`; of what lies between, the consumer may keep a part.  false: it has none to
+  // give away.
+  virtual bool take_over(BaseUpdate*, int64_t /*from*/, int64_t /*to*/) { return false; }
 };
 
 class Model {

@@ -231,11 +231,26 @@ struct UpdateSink : GradSink {
     base_update_range(c, s, t, off, count);
     done.push_back({off, count});
   }
-  bool take_over(BaseUpdate* u) override {
+  bool take_over(BaseUpdate* u, int64_t from, int64_t to) override {
     if (c->bf16 || !done.empty()) return false;
+    // Beside the product the other layers' weights go an element at a time, with few wavefronts to a CU (the product's registers and LDS): 2.4
+    // us a million more than in a pass of their own, 5 where they come from memory; that pass costs a launch.  The first layer's own weights save
+    // 3 to 6 us a million.  us a base step of 128 samples, Adam, every parameter in a pass of its own / all with the last gradient / the other
+    // layers' weights apart, by thousands of weights in the first layer + the others: 51 + 103 32.1 / 29.7 / 32.3, 603 + 598 69.1 / 62.7 / 67.4,
+    // 1204 + 2375 121.3 / 117.3 / 120.4, 1405 + 3229 140.0 / 138.1 / 137.9, 6291 + 4215 220.9 / 214.1 / 208.6, 3211 + 16818 383 / 471 / 377; small first
+    // layers: 49 + 597 55.7 / 54.9 / 56.2, 33 + 792 75.1 / 76.9 / 77.0, 98 + 2375 101.9 / 102.7 / 103.3, 131 + 4215 135.7 / 142.8 / 136.9.
+    const int64_t others = to - from;
+    const bool all = others <= 700000 || (others <= 2 * from && others <= 2400000);
+    if (!all && from < 500000) return false;
     const sama_config& f = c->cfg;
-    *u = BaseUpdate{f.base_opt == SAMA_OPT_ADAM ? 1 : 2, adam_args(c, t), f.base_lr, f.weight_decay, f.momentum, c->g, c->m, c->v, c->theta, c->n};
-    done.push_back({0, c->n});
+    *u = BaseUpdate{f.base_opt == SAMA_OPT_ADAM ? 1 : 2, adam_args(c, t), f.base_lr, f.weight_decay, f.momentum, c->g, c->m, c->v, c->theta, c->n, 0, 0};
+    if (all) {
+      done.push_back({0, c->n});
+    } else {
+      from = (from + 3) / 4 * 4; to = to / 4 * 4;   // what base_update_range takes starts at a vector
+      u->apart = from; u->apart_count = to - from;
+      done.push_back({0, from}); done.push_back({to, c->n - to});
+    }
     return true;
   }
 };
