@@ -88,6 +88,10 @@ sama_status sama_op_nudge(float* theta, const float* vdir, const float* eps_ptr,
  *    problem then runs as one contraction over the concatenated operands, which rounds differently from the hi+lo
  *    tiles), 11..20 the hi+lo tiles (single-term problems ignore them, 20 is for K % 128 = 0); 0 = the heuristic (default).  Within a class
  *    every tile gives the same bits.
+ *  - sama_dev_gemm_rows(choice): hi+lo products over the rows in use of a padded batch run in the launch that chooses its tile on the
+ *    device, by `choice`: four bits for each sixteenth of the rows, the lowest for up to one, each 1 (256 x 192), 2 (256 x 128), 4 (128 x 96) or
+ *    5 (128 x 64), anything else is SAMA_EINVAL; 0 = the heuristic (default).  No bit of a result depends on it.
+ *  - sama_dev_gemm_counts(counts, 2): HOST counts since the last call: launches of that kernel for forward products and for input gradients.
  *  - sama_dev_side_stream(0): the encoder's backward passes keep every launch on the context's stream (a per-kernel profile
  *    wants one stream); 1 = default: weight gradients and optimizer slices run on the library's second stream where rows and
  *    layers are large enough for it; 2: they do for every size.  Any other value means 1.  A base step keeps its bits; a
@@ -95,6 +99,8 @@ sama_status sama_op_nudge(float* theta, const float* vdir, const float* eps_ptr,
  *  - sama_dev_side_sink(0): the optimizer and adaptation slices wait for the end of the backward pass instead of
  *    following each layer's gradients; 1 = default.  The same holds for its bits. */
 void sama_dev_gemm_shape(int32_t id);
+sama_status sama_dev_gemm_rows(uint64_t choice);
+sama_status sama_dev_gemm_counts(int64_t* counts, int32_t n);
 void sama_dev_side_stream(int32_t mode);
 void sama_dev_side_sink(int32_t on);
 

@@ -33,6 +33,7 @@
 // pre-activation and the activation), GELU backward (multiplies by gelu'(pre)), fp32 and/or bf16 stores.  The large hi + lo
 // tiles look the GELU factors up in a table that their loading waves bring into LDS during the last slab.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 #include <utility>
 #include "common.h"
@@ -771,6 +772,8 @@ constexpr TileCost HILO_NN[] = {   // the strided weights of an input gradient
     {19, 32, 32, 2, 0.178, 0.268, 0.376, 0.422, 0.19}, {20, 32, 32, 2, 0.235, 0.335, 0.347, 0.446, 0.00, 128}};
 
 int g_force_shape = 0, g_group = 8;
+uint64_t g_force_rows = 0;
+std::atomic<int64_t> g_launches[GEMM_COUNTS];
 
 // Tiles, and cost, of a launch with `share` of `of` parts of a padded batch's rows in use.
 double launch_cost(const TileCost& c, const GemmBf16Args* p, int count, int share, int of, int64_t* ntiles = nullptr) {
@@ -834,6 +837,19 @@ bool pick_by_rows(const TileCost (&costs)[N], const GemmBf16Args* p, int count, 
   return total < one_tile;
 }
 
+// Tiles of the largest launch by a given choice.
+template <int N>
+int64_t most_tiles_of(const TileCost (&costs)[N], const GemmBf16Args* p, int count, uint64_t choice) {
+  int64_t most = 0;
+  for (int share = 1; share <= ROWS_SHARES; ++share)
+    for (const TileCost& c : costs) {
+      int64_t tiles = 0;
+      if (c.id == 10 + (int)((choice >> (4 * (share - 1))) & 15)) launch_cost(c, p, count, share, ROWS_SHARES, &tiles);
+      most = std::max(most, tiles);
+    }
+  return most;
+}
+
 template <bool B_KC>
 void launch_rows(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count, uint64_t choice, int64_t most_tiles) {
   static bool configured = false;
@@ -842,6 +858,7 @@ void launch_rows(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_rows<B_KC>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     configured = true;
   }
+  g_launches[B_KC ? GEMM_ROWS_NT : GEMM_ROWS_NN].fetch_add(1, std::memory_order_relaxed);
   GemmBatch b = make_batch(p, count, g_group, 64, 64);
   b.choice = choice;
   b.tiles_per_xcd = (int)((most_tiles + 7) / 8);
@@ -861,8 +878,9 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
     double total = 0.0;
     shape = !dual ? pick_tile(SINGLE, p, count, padded, &total) : B_KC ? pick_tile(HILO, p, count, padded, &total) : pick_tile(HILO_NN, p, count, padded, &total);
     if constexpr (A_KC) {
-      uint64_t choice;
+      uint64_t choice = g_force_rows;
       int64_t tiles;
+      if (choice != 0 && padded && dual) return launch_rows<B_KC>(ps, st, p, count, choice, most_tiles_of(HILO, p, count, choice));
       if (padded && dual && (B_KC ? pick_by_rows(HILO, p, count, total, &choice, &tiles) : pick_by_rows(HILO_NN, p, count, total, &choice, &tiles)))
         return launch_rows<B_KC>(ps, st, p, count, choice, tiles);
     }
@@ -919,6 +937,16 @@ const char* check_gemm_bf16(const GemmBf16Args& a) {
   return nullptr;
 }
 
+bool gemm_bf16_force_rows(uint64_t choice) {
+  for (uint64_t c = choice; c != 0; c >>= 4)
+    if ((c & 15) != 1 && (c & 15) != 2 && (c & 15) != 4 && (c & 15) != 5) return false;
+  if (choice != 0 && choice >> 60 == 0) return false;   // a tile for each sixteenth
+  g_force_rows = choice;
+  return true;
+}
+void gemm_bf16_take_counts(int64_t* counts) {
+  for (int k = 0; k < GEMM_COUNTS; ++k) counts[k] = g_launches[k].exchange(0, std::memory_order_relaxed);
+}
 void gemm_bf16_force_shape(int s) { g_force_shape = s % 100; g_group = s >= 100 ? s / 100 : 8; }
 
 const char* check_gemm_bf16_batch(const GemmBf16Args* p, int count) {

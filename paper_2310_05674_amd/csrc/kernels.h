@@ -250,6 +250,11 @@ const char* check_gemm_bf16_batch(const GemmBf16Args* p, int count);
 void launch_gemm_bf16_batch(hipStream_t, const GemmBf16Args* p, int count);
 void encoder_side_sink(bool on);         // tuning hook: per-layer gradient consumers on that stream (default on)
 void encoder_side_stream(int mode);     // tuning hook: weight-gradient launches on a second stream: 0 never, 2 always, else (default) by size
+// tuning hooks: the choice of k_gemm_rows (0: the heuristic; false: not four bits of 1, 2, 4 or 5 for each sixteenth), and how often which launch was made
+// since the last call
+bool gemm_bf16_force_rows(uint64_t choice);
+enum { GEMM_ROWS_NT, GEMM_ROWS_NN, GEMM_COUNTS };
+void gemm_bf16_take_counts(int64_t* counts);
 void gemm_bf16_force_shape(int shape);  // tuning hook: 0 = heuristic, else 100 * tile-order group + tile configuration id
 
 // ------------------------------------------------------------------ encoder ops (encoder_ops.hip)

@@ -37,6 +37,12 @@ extern "C" {
 
 // Diagnostic switches (include/sama_ops.h): block shape of the bf16 GEMM, 0 = heuristic.
 void sama_dev_gemm_shape(int32_t shape) { gemm_bf16_force_shape(shape); }
+sama_status sama_dev_gemm_rows(uint64_t choice) { return gemm_bf16_force_rows(choice) ? SAMA_OK : SAMA_EINVAL; }
+sama_status sama_dev_gemm_counts(int64_t* counts, int32_t n) {
+  if (counts == nullptr || n != GEMM_COUNTS) return SAMA_EINVAL;
+  gemm_bf16_take_counts(counts);
+  return SAMA_OK;
+}
 // 0 keeps every launch of the encoder's backward pass on the context's stream, 2 uses the second one, 1 decides by size / 0 makes the optimizer slices wait for its end.
 void sama_dev_side_stream(int32_t mode) { encoder_side_stream(mode); }
 void sama_dev_side_sink(int32_t on) { encoder_side_sink(on != 0); }

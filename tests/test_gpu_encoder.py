@@ -923,14 +923,26 @@ def test_head_of_many_classes_and_features(C, d):
     gpu.close()
 
 
-@pytest.mark.parametrize("dims", [(2, 320, 5, 896, 128, 300, 3), (2, 768, 12, 1536, 64, 300, 2)])
+def _rows_counts(L):
+    """Launches of the kernel that chooses its tile on the device since the last call: forward, input gradients."""
+    import ctypes
+    c = (ctypes.c_int64 * 2)()
+    assert L.sama_dev_gemm_counts(c, ctypes.c_int32(2)) == 0
+    return list(c)
+
+
+ROWS_CHOICES = [0] + [int(k * 16, 16) for k in "1245"] + [0x1245544221145512]   # the heuristic's, one tile for all, a mixture
+
+
+@pytest.mark.parametrize("dims", [(2, 320, 5, 896, 128, 300, 3), (2, 768, 12, 1536, 64, 300, 2), (2, 768, 12, 3072, 128, 300, 2)])
 def test_tile_chosen_by_the_rows_in_use(dims):
-    """Padded batches with from an eighth to all of their rows in use, at widths that are no multiple of the tiles: where the device chooses the
-    tile by the rows, every bit of a base step and of a meta step is that of one tile for all of them."""
+    """Padded batches with from an eighth to all of their rows in use, at widths that leave ragged tiles and whole ones: with the tile
+    chosen on the device by the rows, as the heuristic does and each of the four for each product (forward, paired and input gradients, all epilogues),
+    every bit of a base step and of a meta step is that of one tile for all of them."""
     import ctypes
     from paper_2310_05674_amd import binding as B
     L = B.load_library()
-    S, n = dims[4], 2048 // dims[4] * 2
+    S, n = dims[4], 4096 // dims[4]
     wl = make_workload(3, n_train=2 * n, n_meta=8, dims=dims, batch=n, meta_batch=4)
     _, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
     (x, y), (xm, ym) = _batches(wl, 0)
@@ -938,18 +950,32 @@ def test_tile_chosen_by_the_rows_in_use(dims):
     r = np.random.default_rng(5)
     lens_sets = [np.full(n, k, dtype=np.int32) for k in sorted({1, 16, 17, S // 4 + 1, S // 2, S // 2 + 1, 3 * S // 4, S - 17, S - 16, S})]
     lens_sets += [r.integers(1, S + 1, n).astype(np.int32) for _ in range(3)]
+    products = 4 * dims[0]                       # of a pass; the last layer's rows behind its attention are not those in use
+    taken = [0, 0]
+
+    def step(lens, shape, choice):
+        L.sama_dev_gemm_shape(ctypes.c_int32(shape))
+        assert L.sama_dev_gemm_rows(ctypes.c_uint64(choice)) == 0
+        for k, v in start.items():
+            gpu.set_state(k, v)
+        gpu.set_state("COUNTERS", np.array([3, 1, 0, 0], dtype=np.int64))
+        tb = dev_batch(gpu, x, y, lens=lens)
+        gpu.base_step(tb); gpu.meta_step(tb, dev_batch(gpu, xm, ym, lens=lens[:4]))
+        return [pull(gpu, k) for k in ("G", "THETA", "GMETA", "HYPERGRAD")]
     try:
         for lens in lens_sets:
-            got = []
-            for shape in (0, 15):
-                L.sama_dev_gemm_shape(ctypes.c_int32(shape))
-                for k, v in start.items():
-                    gpu.set_state(k, v)
-                gpu.set_state("COUNTERS", np.array([3, 1, 0, 0], dtype=np.int64))
-                tb = dev_batch(gpu, x, y, lens=lens)
-                gpu.base_step(tb); gpu.meta_step(tb, dev_batch(gpu, xm, ym, lens=lens[:4]))
-                got.append([pull(gpu, k) for k in ("G", "THETA", "GMETA", "HYPERGRAD")])
-            assert all(np.isfinite(a).all() and np.array_equal(a, b) for a, b in zip(*got)), (int(lens.sum()), lens[:4])
+            want = step(lens, 15, 0)
+            assert all(np.isfinite(a).all() for a in want)
+            _rows_counts(L)
+            for choice in ROWS_CHOICES:
+                got = step(lens, 0, choice)
+                assert all(np.array_equal(a, b) for a, b in zip(got, want)), (hex(choice), int(lens.sum()), lens[:4])
+                c = _rows_counts(L)
+                if choice == 0:
+                    taken = [a + b for a, b in zip(taken, c)]
+                else:                            # two backward passes; their forward passes and the stacked one
+                    assert c[0] == 3 * (products - 3) and c[1] == 2 * (products - 3), c
+        assert taken[0] > 0 and (taken[1] > 0 or dims[1] == 320), taken   # the heuristic does choose this launch
     finally:
-        L.sama_dev_gemm_shape(ctypes.c_int32(0))
+        L.sama_dev_gemm_shape(ctypes.c_int32(0)); L.sama_dev_gemm_rows(ctypes.c_uint64(0))
         gpu.close()
