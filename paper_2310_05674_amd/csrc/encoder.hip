@@ -140,17 +140,17 @@ class EncoderModel : public Model {
   // us without it / with it, where the rule has it: 12 x 768 scoring 128 rows 678 / 647, 512 828 / 738, 2048 1378 / 1237, base step of 1024 rows
   // 3039 / 2831, of 2048 3918 / 3659; 24 x 1024 base step of 512 rows 6828 / 6422; 12 x 768 iteration of 1024 rows 7670 / 7163; base step of
   // 2048 rows of 8 x 384 (260 MB with the state) 1436 / 1390.  Without it / with it, where the rule leaves it out: 12 x 768 scoring 4096 rows
-  // 1893 / 1864, base step of 4096 5471 / 5454, padded 4812 / 4802; 24 x 1024 base step of 2048 rows 10418 / 10350; scoring 128 rows of 12 x 576
+  // 1893 / 1864, base step of 4096 5471 / 5454; 24 x 1024 base step of 2048 rows 10418 / 10350; scoring 128 rows of 12 x 576
   // (177 MB) 542 / 551.  The stacked passes count the rows of both: left out of them, as the rule does at 24 x 1024 and 1024 rows, an
   // iteration takes 18867 us, with it there too 18928.
-  // Padded batches go on to twice as many rows in use where two weights are at most 20 MB: the tiles that are chosen on the device have no wave that
-  // touches weights ahead.  Without it / with it: 12 x 768 iteration of 4096 rows, 2900 in use, 12875 / 12546, scoring 8192 padded rows 2837 / 2669 (base step
-  // of 4096, 8 x 640, 12 x 512 and 12 x 384 within 0.7 %); without lengths nothing changes at 4096 rows (5512 / 5507), and at 24 x 1024,
-  // 34 MB for two, 2048 rows lose (27180 / 27540).
+  // Padded batches go on to twice as many rows in use: the tiles that are chosen on the device have no wave that touches weights ahead.  Without it /
+  // with it, 4096 rows, about 2900 in use: base step of 12 x 768 4515 / 4354, 12 x 960 5680 / 5621, 12 x 1024 6138 / 6088; 24 x 1024 base step of 3584 rows
+  // 12034 / 11661, scoring 3072 3736 / 3549, iteration of 3584 31847 / 30669, of 2048 23534 / 23699 (the most that any of 130 calls loses, 1.2 % on
+  // another card); 12 x 896 and narrower than 768 within 0.7 %.  Without lengths nothing changes at 4096 rows (5512 / 5507), and at 24 x 1024 2048 rows
+  // lose (27180 / 27540).
   WeightsAhead weights_ahead(const PassWeights* w, int nw, bool scoring, int64_t off, int64_t n, int rows, const int32_t* in_use) const {
     WeightsAhead a{};
-    const bool more = in_use != nullptr && std::max((int64_t)16 * d_ * d_, (int64_t)8 * ffn_ * d_) <= 20000000;   // bytes of two weights
-    a.max_rows = ((more ? 4 : 2) << 20) / (nw * d_);
+    a.max_rows = ((in_use != nullptr ? 4 : 2) << 20) / (nw * d_);
     const int64_t params = L_ * ((int64_t)4 * d_ * d_ + (int64_t)2 * ffn_ * d_);
     if (params * (scoring ? 4 : 20) < 256000000 || (in_use == nullptr && rows >= a.max_rows)) return a;
     for (int k = 0; k < nw; ++k) { a.p[2 * k] = w[k].hi + off; a.p[2 * k + 1] = w[k].lo != nullptr ? w[k].lo + off : nullptr; }

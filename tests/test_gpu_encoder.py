@@ -887,13 +887,13 @@ def test_weights_fetched_ahead(B, padded):
     gpu.close()
 
 
-@pytest.mark.parametrize("kept", [52, 100, 124])
-def test_weights_fetched_ahead_of_many_padded_rows(kept):
-    """7680 rows of 640 with about 3100, 6000 and 7400 in use: the LayerNorms of a base step fetch the next weights with the first two.  Scoring
-    never does at this size; the losses of both are the same bits."""
+@pytest.mark.parametrize("B,dims,kept", [(60, (4, 640, 10, 1280), 52), (60, (4, 640, 10, 1280), 100), (60, (4, 640, 10, 1280), 124), (36, (2, 1024, 16, 4096), 52),
+                                         (36, (2, 1024, 16, 4096), 100), (36, (2, 1024, 16, 4096), 124)])
+def test_weights_fetched_ahead_of_many_padded_rows(B, dims, kept):
+    """7680 rows of 640 with about 3100, 6000 and 7400 in use, 4608 of 1024 with 2000, 3700 and 4500: the LayerNorms of a base step fetch the next
+    weights with the first two of each.  Scoring never does at these sizes; the losses of both are the same bits."""
     import torch
-    B = 60
-    wl = make_workload(3, n_train=B, n_meta=2, dims=(4, 640, 10, 1280, 128, 300, 3), batch=B, meta_batch=2)
+    wl = make_workload(3, n_train=B, n_meta=2, dims=dims + (128, 300, 3), batch=B, meta_batch=2)
     _, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
     x, y = wl.x_train[:B], wl.y_train[:B]
     lens = np.clip(np.arange(B) % 9 - 4 + kept, 1, 128).astype(np.int32)
