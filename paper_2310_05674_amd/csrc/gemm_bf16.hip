@@ -491,18 +491,32 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   // ---- epilogue: a lane has four neighbouring columns of row lane % 16 of each fragment.  fp32 goes out from there, 64 bytes of a row at a
   // time; of two neighbouring fragments in bf16, lanes 16 apart exchange halves first, so that a lane has eight neighbouring columns of
   // one of them.  Nothing goes through LDS.
-  // A unit is a pair of fragments side by side, the units of a column of them follow each other.  Whole tiles of the usual kinds go through
+  // A unit is a pair of fragments side by side.  Whole tiles of the usual kinds go through
   // code of their own for each kind, without a branch in it; what a unit needs from memory (bias, an fp32 residual or a saved
   // pre-activation, an epilogue has one of these at most) is requested DEPTH - 1 units before it, for the first ones while the last slab
   // is multiplied.
-  constexpr int UNITS = YT / 2 * XT, DEPTH = XT * YT > 16 ? 2 : XT * YT == 16 ? 3 : 4;
+  // The units of a column of them follow each other, but for bf16 outputs of wave tiles 64 rows tall those of a row: a unit is half a 128-byte line
+  // there, and halves stored four units apart leave L2 one by one.  MiB written of 12 by 2048 x 3072 x 1024, before / along rows: 256 x 128 tiles 12.7 /
+  // 12.0, 256 x 192 14.8 / 12.0 (with the offsets of the lanes computed behind the last slab, which take 12 registers to scratch ahead of it and 4
+  // here); us 8192 x 3072 x 1024 with 256 x 192 tiles NT 76.4 / 73.7, 8192 x 2304 x 768 54.8 / 52.6.  Wave tiles 32 rows tall have two units to a column
+  // and write no more than their output; of 128 rows (256 x 256, single-term) the fp32 weight gradients would take 2 to 3 % longer.
+  constexpr int PAIRS = YT / 2, UNITS = PAIRS * XT, DEPTH = XT * YT > 16 ? 2 : XT * YT == 16 ? 3 : 4;
   const bool fast = kind != EPI_ANY && i0 + BM <= rows_of && j0 + BN <= (uint32_t)la.N;
-  const int g = (int)lane >> 4, pair_col = 16 * (g & 1) + 8 * (g >> 1);   // columns of the lane's values: 4 g, after the exchange pair_col
-  const uint32_t off32 = ((lane & 15) * (uint32_t)ldc + 4 * g) * 4, off16 = ((lane & 15) * (uint32_t)ldc + pair_col) * 2;   // (ldc < 2^24 where they are used)
+  int g;                    // columns of the lane's values: 4 g, after the exchange pair_col
+  uint32_t off32, off16;    // (ldc < 2^24 where they are used)
+  auto lane_offsets = [&](uint32_t lane_) {
+    g = (int)lane_ >> 4;
+    const int pair_col = 16 * (g & 1) + 8 * (g >> 1);
+    off32 = ((lane_ & 15) * (uint32_t)ldc + 4 * g) * 4; off16 = ((lane_ & 15) * (uint32_t)ldc + pair_col) * 2;
+  };
   const int64_t tile0 = ((int64_t)i0 + wr) * ldc + j0 + wc;
-  auto of_unit = [&](int unit) { return tile0 + (int64_t)(unit % XT * 16) * ldc + unit / XT * 32; };
+  constexpr bool ALONG = XT == 4;   // bf16 outputs
+  constexpr auto unit_x = [](bool bf16, int unit) { return ALONG && bf16 ? unit / PAIRS : unit % XT; };
+  constexpr auto unit_h = [](bool bf16, int unit) { return ALONG && bf16 ? unit % PAIRS : unit / XT; };
+  auto of_unit = [&](bool bf16, int unit) { return tile0 + (int64_t)(unit_x(bf16, unit) * 16) * ldc + unit_h(bf16, unit) * 32; };
   uint4 sv[DEPTH][2] = {};
-  float4 bias[2][2] = {};
+  constexpr int NBIAS = ALONG ? PAIRS : 2;
+  float4 bias[NBIAS][2] = {};
   auto load_bias = [&](int h) {
     if (bias_at == nullptr) return;
 #pragma unroll
@@ -512,26 +526,26 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
         const float4 v = *reinterpret_cast<const float4*>(a.bias_v + j0 + wc + 32 * h + 16 * u + 4 * g);
         t.x = fmaf(bs, v.x, t.x); t.y = fmaf(bs, v.y, t.y); t.z = fmaf(bs, v.z, t.z); t.w = fmaf(bs, v.w, t.w);
       }
-      bias[h & 1][u] = t;
+      bias[h % NBIAS][u] = t;
     }
   };
   auto load_side = [&](int unit) {
     uint4 (&v)[2] = sv[unit % DEPTH];
     if (kind == EPI_RES32) {
-      const char* const p = reinterpret_cast<const char*>(res32 + of_unit(unit));
+      const char* const p = reinterpret_cast<const char*>(res32 + of_unit(false, unit));
       v[0] = *reinterpret_cast<const uint4*>(p + off32);
       v[1] = *reinterpret_cast<const uint4*>(p + off32 + 64);
     } else if (kind == EPI_GELU_BWD) {
-      v[0] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(aux16 + of_unit(unit)) + off16);
+      v[0] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(aux16 + of_unit(true, unit)) + off16);
     }
   };
   auto load_first = [&]() {
     if (!fast) return;
-    load_bias(0);
+    static_for<ALONG ? PAIRS : 1>([&](auto h) { load_bias(h); });
     static_for<DEPTH - 1>([&](auto u) { if constexpr (decltype(u)::value < UNITS) load_side(u); });
   };
   constexpr bool EARLY = XT * YT != 24;   // the 64 x 96 tiles of a wave leave no registers for it
-  if (EARLY) load_first();
+  if (EARLY) { lane_offsets(lane); load_first(); }
   // the last slab
   {
     if (RD == 0 && iters > 1) {
@@ -546,7 +560,11 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
       multiply(std::integral_constant<int, NT - 1>{});
     }
   }
-  if (!EARLY) load_first();
+  if (!EARLY) {
+    uint32_t lane_ = lane;
+    asm volatile("" : "+v"(lane_));   // computed here and not kept over the last slab
+    lane_offsets(lane_); load_first();
+  }
   if (look_up) __syncthreads();   // the table has come
   const unsigned char* const tab = smem_raw + tab_at;
   auto entry = [&](uint32_t offset) { return *reinterpret_cast<const float*>(tab + offset); };
@@ -580,15 +598,16 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
     auto of_kind = [&](auto k) {
       constexpr int KIND = k;
       static_for<UNITS>([&](auto unit_) {
-        constexpr int unit = unit_, x = unit % XT, h = unit / XT;
-        if constexpr (x == 0 && h + 1 < YT / 2) load_bias(h + 1);
+        constexpr bool BF16 = KIND != EPI_C32 && KIND != EPI_RES32;
+        constexpr int unit = unit_, x = unit_x(BF16, unit), h = unit_h(BF16, unit);
+        if constexpr (!ALONG && x == 0 && h + 1 < PAIRS) load_bias(h + 1);
         if constexpr ((KIND == EPI_RES32 || KIND == EPI_GELU_BWD) && unit + DEPTH - 1 < UNITS) load_side(unit + DEPTH - 1);
         const uint4 (&cur)[2] = sv[unit % DEPTH];
         float c[2][4];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const f32x4 v = acc[x][2 * h + u];
-          const float4 b = bias[h & 1][u];
+          const float4 b = bias[h % NBIAS][u];
           c[u][0] = v[0] + b.x; c[u][1] = v[1] + b.y; c[u][2] = v[2] + b.z; c[u][3] = v[3] + b.w;
         }
         if constexpr (KIND == EPI_RES32) { add(c[0], cur[0]); add(c[1], cur[1]); }
@@ -597,7 +616,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
           gelu(c[0], pk[0]); gelu(c[1], pk[1]);
           if (C16_pre != nullptr) {   // forward-only passes do not keep it
             exchange(pk);
-            *reinterpret_cast<uint4*>(reinterpret_cast<char*>(C16_pre + of_unit(unit)) + off16) = make_uint4(pk[0].x, pk[0].y, pk[1].x, pk[1].y);
+            *reinterpret_cast<uint4*>(reinterpret_cast<char*>(C16_pre + of_unit(BF16, unit)) + off16) = make_uint4(pk[0].x, pk[0].y, pk[1].x, pk[1].y);
           }
         }
         if constexpr (KIND == EPI_GELU_BWD) {
@@ -606,13 +625,13 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
           dgelu(c[0], pk[0]); dgelu(c[1], pk[1]);
         }
         if (KIND == EPI_C32 || KIND == EPI_RES32 || (KIND != EPI_C16 && C32 != nullptr)) {
-          char* const p = reinterpret_cast<char*>(C32 + of_unit(unit));
+          char* const p = reinterpret_cast<char*>(C32 + of_unit(BF16, unit));
           *reinterpret_cast<float4*>(p + off32) = make_float4(c[0][0], c[0][1], c[0][2], c[0][3]);
           *reinterpret_cast<float4*>(p + off32 + 64) = make_float4(c[1][0], c[1][1], c[1][2], c[1][3]);
         } else {
           uint2 pk[2] = {packed(c[0]), packed(c[1])};
           exchange(pk);
-          *reinterpret_cast<uint4*>(reinterpret_cast<char*>(C16 + of_unit(unit)) + off16) = make_uint4(pk[0].x, pk[0].y, pk[1].x, pk[1].y);
+          *reinterpret_cast<uint4*>(reinterpret_cast<char*>(C16 + of_unit(BF16, unit)) + off16) = make_uint4(pk[0].x, pk[0].y, pk[1].x, pk[1].y);
         }
       });
     };
