@@ -74,7 +74,7 @@ struct Tile {
   // Whether the GELU epilogues look their values up (gelu.h).  The table comes into a stage that the last slab does not use, while
   // that slab is multiplied.  Computed, a value is 26 quarter-rate vector instructions in which the matrix cores stand still; looked up it
   // is seven and an LDS read.  us computed / looked up, forward: 2048 x 4096 x 1024 (256 x 128 tiles) 37.3 / 34.5, 4096 x 3072 x 768 (256 x
-  // 192) 47.1 / 40.8, 1024 x 3072 x 768 (128 x 128) 19.6 / 18.0, (128 x 96) 19.2 / 17.9.  The 128 x 64 and smaller tiles compute: the table
+  // 192) 47.1 / 40.8, 1024 x 3072 x 768 (128 x 128) 19.6 / 18.0, (128 x 96) 19.2 / 17.9 (with 32 x 32 x 16 MFMAs and the epilogue through LDS).  The 128 x 64 and smaller tiles compute: the table
   // would be as much to load as a slab of them or more.
   static constexpr bool TAB = DUAL && PW > 0 && BM * BN >= 128 * 96;
   static_assert(!TAB || (NSTAGE >= 2 && STAGE_BYTES >= GELU_TAB_BYTES), "room for the table");
@@ -284,6 +284,8 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
       // hi + lo 2048 x 1024 x 4096 NT 36.5 / 34.4, NN 42.1 / 36.5 (128 x 64 tiles), 1024 x 1024 x 4096 NT 27.6 / 23.7, NN 36.3 / 25.0 (64 x 64);
       // weights warm 33.1 / 33.2, 34 / 34.6, 20.8 / 22.8, 24.8 / 23.3.  With fewer than 32 slabs there is no time for it (2048 x 1024 x 1024
       // 10.1 / 10.9); done by a multiplying wave it costs all tiles 1 to 2 us; 128 x 128 tiles gain 2 us of 49 here and lose 1.5 of 41 there.
+      // Whole calls without it: scoring 2048 rows of 24 x 1024 +2.9%, base step of 1536 +1.2%, and where the caches hold the weights -1.9 to +0.5%; told
+      // so by the encoder and left out there, calls gained up to 1.8 and lost up to 3.4%.
       constexpr int TS = 8, TN = (BN + 63) / 64;   // slabs of a chunk, loads for an eighth of its lines
       static_assert(!T::TAB, "no barrier for the table");
       if (iters < 4 * TS) return;
@@ -767,9 +769,10 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gemm_rows(GemmBatch batch) {
 // on every CU and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.
 // The numbers are robust least-squares fits of the logarithms over timed problems (widths 192 to 2048, FFN 2 and 4 times that,
 // 64 to 8192 rows: NT, NN, pairs of NT, a layer's four TN problems in a launch; the vocabulary head's products over 8192 to
-// 50304 tokens; weights cold).  On the times of the kernels as they are, picking by them takes 0.4% (NT), 0.3% (pairs), 0.6% (NN) and 0.5% (TN)
-// longer in total than the fastest tile of each problem, the head's products 1 to 2%; by one table for NT and NN, NN takes 2.6% and the head's
-// NN 7%: profiles/gemm_tile_costs.md.
+// 50304 tokens; weights cold): HILO_NN of the kernels as they are, SINGLE and HILO of earlier ones (32 x 32 x 16 MFMAs, the epilogue through LDS), which took 1.3
+// to 1.5 times as long; HILO's last entry was set by hand beside the one before it.  On the times of the kernels as they are, picking by them takes
+// 0.4% (NT), 0.3% (pairs), 0.5% (NN) and 0.5% (TN) longer in total than the fastest tile of each problem, the head's products 1 to 2%; by
+// HILO for NN too, NN takes 2.6% and the head's NN 7%: profiles/gemm_tile_costs.md.
 struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; int bk = 64; };
 constexpr TileCost SINGLE[] = {
     {1, 256, 256, 1, 1.282, 1.816, 0, 0, 8.26}, {2, 256, 192, 1, 1.060, 1.218, 0, 0, 8.62},
@@ -834,7 +837,10 @@ int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count, bool
 }
 
 // The same for k_gemm_rows: the tile of least cost for each sixteenth of the rows; returns whether that is worth more over the quarters than
-// the 0.4 us a launch that the choice takes.
+// the 0.4 us a launch that the choice takes (0.3 in forward products, whose table is in longer microseconds; at 0.6 and 1.0 the choices are 0.01 and 0.07%
+// further from the fastest tiles).  Entry 15 stands for R5 here, which touches no weights and takes 1.07 times as long in input gradients over 2048 and more: a
+// price of its own there made padded base steps of 24 x 1024 up to 5.7% shorter and those of 6 x 1024 with FFN 2048 up to 3.4% longer, 0.2%
+// shorter in the mean of 12 models.
 template <int N>
 bool pick_by_rows(const TileCost (&costs)[N], const GemmBf16Args* p, int count, double one_tile, uint64_t* choice, int64_t* most_tiles) {
   double total = 0.0;
