@@ -23,8 +23,13 @@
 //   what runs before a workgroup's first load and behind its last product is short straight code
 //
 // For the theta +- eps v passes of Eq. 5 and the direct-gradient pass the weight operand is hi + lo (two bf16
-// halves).  DUAL tiles stage the A slab once together with the hi and the lo slab of B, and an MFMA contracts 16 values of A with those of hi,
-// then with those of lo.
+// halves).  DUAL tiles stage the A slab once together with the hi and the lo slab of B.  The same fragment of A is multiplied by 32 values of hi,
+// then by 32 of lo, so that it comes from LDS once for both: LDS reads take power and the ports that the loads write through.  With half
+// of an MFMA's lanes on hi and half on lo (A twice in every fragment, a third more LDS reads in 256 x 128 tiles, the same sums in another order) products take
+// 2.5% longer (geometric mean of 92 tile x problem), us before / now: 8192 x 1024 x 4096 97.5 / 94.4, 8192 x 4096 x 1024 103.7 / 100.5.  What is read
+// per product also decides how a tile is cut into waves: 64 x 32 of a wave in 128 x 128 and 128 x 64 tiles, where it was 32 x 64 and 32 x 32:
+// 4096 x 1024 x 4096 NT 58.9 / 53.4, NN 64.8 / 57.6, 2048 x 1024 x 4096 NT 33.8 / 32.3, NN 36.0 / 32.5; 128 x 96 with 64 x 32 for 32 x 96 NN 21.3 / 21.0, NT level.
+// (256 x 128 with four waves of 128 x 64 gains 2% at 8192 x 1024 x 4096 and loses 2% at 4096 x 768 x 3072.)
 //
 // Several independent problems of one storage class can share a launch (the + and - pass of Eq. 5, the four weight
 // gradients of a layer): more tiles per launch for the small per-layer shapes.
@@ -64,7 +69,7 @@ struct Tile {
   // TW: 1: a wave that touches the weights ahead of the loads (see the kernel)
   static_assert(TW == 0 || PW > 0, "a touching wave only beside loading ones");
   static constexpr int WM = BM / WGM, WN = BN / WGN, XT = WM / 16, YT = WN / 16;
-  static constexpr int YP = YP_ > 0 ? YP_ : YT, NP = YT / YP;               // pieces of a k-step
+  static constexpr int YP = YP_ > 0 ? YP_ : YT, NP = YT / YP * (DUAL ? 2 : 1);   // pieces of a k-step: YP fragments of B, of one half
   static_assert(WM % 16 == 0 && WN % 32 == 0 && YT % YP == 0, "wave tiles");
   static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + (DUAL ? 2 : 1) * B_BYTES;
   static constexpr int NLA = A_BYTES / 1024 / LW, NLB = B_BYTES / 1024 / LW;   // 1 KB loads of a loading wave per slab
@@ -135,18 +140,16 @@ __device__ __forceinline__ void load_offsets(uint32_t (&off)[NLOADS], uint32_t l
 }
 
 // MFMA operand out of a swizzled stage: the lane-dependent part of its address, for a k-step (KC) or for a 16-row fragment of the tile
-// (KS).  A lane has 8 contraction values of tile row tb + lane % 16: of a single-term product k = 32 ks + 8 (lane / 16) + 0..7; of a hi + lo
-// one 16 ks + 8 (lane / 16 % 2) + 0..7, lanes 0..31 of the hi half of B and 32..63 of the lo half, and A the same in both: the matrix core adds
-// the 32 products of an instruction 16 at a time in order, so that one instruction is 16 of hi, then 16 of lo.
-template <bool KC, int R, int BK, bool HALVES>
+// (KS).  A lane has 8 contraction values of tile row tb + lane % 16: k = 32 ks + 8 (lane / 16) + 0..7.
+template <bool KC, int R, int BK>
 __device__ __forceinline__ int fetch_lane_offset(int lane, int ks_or_frag) {
-  const int part = HALVES ? (lane >> 4) & 1 : lane >> 4;
+  const int part = lane >> 4;
   if (KC) {
     constexpr int RB = BK * 2, RP = 256 / RB, NCH = RB / 16;
     static_assert(16 % RP == 0 && (16 / RP) % NCH == 0, "the swizzle repeats from fragment to fragment");
     const int rl = lane & 15;
     const int s = (rl / RP) % NCH;
-    return rl * RB + ((((HALVES ? 2 : 4) * ks_or_frag + part) ^ s) * 16);
+    return rl * RB + (((4 * ks_or_frag + part) ^ s) * 16);
   } else {
     constexpr int RBS = R * 2;
     const int j = lane & 15;
@@ -390,23 +393,22 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
 #pragma unroll
     for (int y = 0; y < YT; ++y) acc[x][y] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-  constexpr int KD = DUAL ? 16 : 32, KS = BK / KD;   // depth of a k-step, steps of a slab
+  constexpr int KD = 32, KS = BK / KD;   // depth of a k-step, steps of a slab
   // lane-dependent parts of the operand fetch addresses
-  const int lo_half = DUAL ? (int)(lane >> 5) * T::B_BYTES : 0;
   int fa[A_KC ? KS : XT], fb[B_KC ? KS : YT];
   if (A_KC) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) fa[ks] = fetch_lane_offset<true, BM, BK, DUAL>(lane, ks) + wr * BK * 2;
+    for (int ks = 0; ks < KS; ++ks) fa[ks] = fetch_lane_offset<true, BM, BK>(lane, ks) + wr * BK * 2;
   } else {
 #pragma unroll
-    for (int x = 0; x < XT; ++x) fa[x] = fetch_lane_offset<false, BM, BK, DUAL>(lane, (wr >> 4) + x);
+    for (int x = 0; x < XT; ++x) fa[x] = fetch_lane_offset<false, BM, BK>(lane, (wr >> 4) + x);
   }
   if (B_KC) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) fb[ks] = fetch_lane_offset<true, BN, BK, DUAL>(lane, ks) + wc * BK * 2 + lo_half;
+    for (int ks = 0; ks < KS; ++ks) fb[ks] = fetch_lane_offset<true, BN, BK>(lane, ks) + wc * BK * 2;
   } else {
 #pragma unroll
-    for (int y = 0; y < YT; ++y) fb[y] = fetch_lane_offset<false, BN, BK, DUAL>(lane, (wc >> 4) + y) + lo_half;
+    for (int y = 0; y < YT; ++y) fb[y] = fetch_lane_offset<false, BN, BK>(lane, (wc >> 4) + y);
   }
 
   auto fetchA = [&](const unsigned char* sa, int x, int ks) -> bf16x8 {
@@ -435,7 +437,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   // D = B-fragment x A-fragment: a lane gets four neighbouring columns of one row
   constexpr int NM = XT * YP;
   auto mfma = [&](auto t, auto m) {
-    constexpr int T_ = t, ks = T_ / NP, y0 = T_ % NP * YP, x = m / YP, yy = m % YP, y = (x & 1) ? YP - 1 - yy : yy;
+    constexpr int T_ = t, ks = T_ / NP, y0 = T_ % NP / (DUAL ? 2 : 1) * YP, x = m / YP, yy = m % YP, y = (x & 1) ? YP - 1 - yy : yy;
     acc[x][y0 + y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[T_ & 1][y], av[ks & 1][x], acc[x][y0 + y], 0, 0, 0);
   };
   // operand r of the piece t of the slab at `at`: first what its first products need
@@ -443,9 +445,9 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   auto operands = [](int t) { return YP + (t % NP == 0 ? XT : 0); };
   auto read = [&](const unsigned char* at, auto t, auto r) {
     constexpr int T_ = t, R_ = r, ks = T_ / NP, p = T_ % NP, wa = p == 0 ? 1 : 0;
-    const unsigned char* const sb = at + T::A_BYTES;
+    const unsigned char* const sb = at + T::A_BYTES + (DUAL ? p % 2 * T::B_BYTES : 0);
     if constexpr (wa == 1 && R_ == 0) av[ks & 1][0] = fetchA(at, 0, ks);
-    else if constexpr (R_ - wa < YP) bv[T_ & 1][R_ - wa] = fetchB(sb, p * YP + R_ - wa, ks);
+    else if constexpr (R_ - wa < YP) bv[T_ & 1][R_ - wa] = fetchB(sb, p / (DUAL ? 2 : 1) * YP + R_ - wa, ks);
     else av[ks & 1][R_ - YP] = fetchA(at, R_ - YP, ks);
   };
   auto read_all = [&](const unsigned char* at, auto t) {
@@ -733,9 +735,9 @@ typedef Tile<128, 128, 64, 4, 2, 2, false, 0, 0, 1> S7;       // two workgroups 
 typedef Tile<32, 32, 64, 1, 1, 6, false, 2, 0, 1> S8;      // three workgroups per CU
 typedef Tile<256, 192, 64, 4, 2, 2, true, 4, 2, 1> D1;
 typedef Tile<256, 128, 64, 4, 2, 2, true, 4, 2, 2> D2;
-typedef Tile<128, 128, 64, 4, 2, 3, true, 4, 0, 2> D3;
-typedef Tile<128, 96, 64, 4, 1, 3, true, 4, 0, 2> D4;
-typedef Tile<128, 64, 64, 4, 2, 4, true, 4, 0, 1, 1> D5;
+typedef Tile<128, 128, 64, 2, 4, 3, true, 4, 0, 1> D3;
+typedef Tile<128, 96, 64, 2, 3, 3, true, 4, 0, 1> D4;
+typedef Tile<128, 64, 64, 2, 2, 4, true, 4, 0, 1, 1> D5;
 typedef Tile<64, 64, 64, 2, 2, 4, true, 2, 0, 1, 1> D6;
 typedef Tile<64, 64, 64, 2, 2, 3, true, 2, 0, 1, 1> D7;       // two workgroups per CU
 typedef Tile<64, 32, 64, 4, 1, 4, true, 2, 0, 1> D8;       // two workgroups per CU
@@ -745,7 +747,7 @@ typedef Tile<32, 32, 128, 2, 1, 3, true, 2, 0, 1> D10;     // two workgroups per
 // A hi + lo product of a padded batch: the tile is chosen here, by the rows in use, among four of one workgroup to a CU.  (The waves that a
 // tile does not have end at once; the bodies are those of the launches with one tile, but for the touching waves, for which 168 registers a wave
 // leave no room.)
-typedef Tile<128, 64, 64, 4, 2, 4, true, 4, 0, 1> R5;
+typedef Tile<128, 64, 64, 2, 2, 4, true, 4, 0, 1> R5;
 constexpr int ROWS_THREADS = D1::THREADS, ROWS_SHARES = 16;
 static_assert(D2::THREADS <= ROWS_THREADS && D4::THREADS <= ROWS_THREADS && R5::THREADS <= ROWS_THREADS, "waves");
 template <typename T, bool B_KC>
@@ -769,8 +771,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gemm_rows(GemmBatch batch) {
 // on every CU and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.
 // The numbers are robust least-squares fits of the logarithms over timed problems (widths 192 to 2048, FFN 2 and 4 times that,
 // 64 to 8192 rows: NT, NN, pairs of NT, a layer's four TN problems in a launch; the vocabulary head's products over 8192 to
-// 50304 tokens; weights cold): HILO_NN of the kernels as they are, SINGLE and HILO of earlier ones (32 x 32 x 16 MFMAs, the epilogue through LDS), which took 1.3
-// to 1.5 times as long; HILO's last entry was set by hand beside the one before it.  On the times of the kernels as they are, picking by them takes
+// 50304 tokens; weights cold): HILO_NN of the kernels before their tiles were cut for fewer LDS reads (2 to 11% longer), SINGLE and HILO of still earlier ones (32 x 32 x 16 MFMAs, the epilogue through LDS), which took 1.3
+// to 1.5 times as long; HILO's last entry was set by hand beside the one before it.  On times of the former, picking by them takes
 // 0.4% (NT), 0.3% (pairs), 0.5% (NN) and 0.5% (TN) longer in total than the fastest tile of each problem, the head's products 1 to 2%; by
 // HILO for NN too, NN takes 2.6% and the head's NN 7%: profiles/gemm_tile_costs.md.
 struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; int bk = 64; };
