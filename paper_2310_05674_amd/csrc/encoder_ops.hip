@@ -319,33 +319,48 @@ __global__ __launch_bounds__(256) void k_colsum_partial_bf16(ColsumMulti m) {
 // Sequence length S = 32 NT (NT = 2, 4 or 8 tiles of 32 positions), head width 64.
 constexpr int AD = 64;  // head width
 
-__device__ __forceinline__ s16x4 pack4(float a, float b, float c, float d) {
-  s16x4 r;
-  r[0] = (short)f32_to_bf16(a); r[1] = (short)f32_to_bf16(b); r[2] = (short)f32_to_bf16(c); r[3] = (short)f32_to_bf16(d);
-  return r;
+// eight values of an accumulator from entry r on, as an operand
+__device__ __forceinline__ bf16x8 pack8(const f32x16& a, int r) {
+  const uint4 v = make_uint4(pack_bf16x2(a[r], a[r + 1]), pack_bf16x2(a[r + 2], a[r + 3]), pack_bf16x2(a[r + 4], a[r + 5]), pack_bf16x2(a[r + 6], a[r + 7]));
+  return __builtin_bit_cast(bf16x8, v);
 }
 
 // A [ROWS x 64] bf16 matrix of a head (row stride ld in memory) is staged in LDS in dense rows of 128 bytes, the 16-byte chunk
 // index of row r XORed with chunk_swz(r).  It is read in two ways, both without bank conflicts:
 //   rows_operand: lane l takes 8 consecutive values of row base + l % 32 (sixteen rows at one chunk: sixteen 16-byte slots)
-//   ld_transposed: for the 32x32x8 MFMA, lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] through ds_read_b64_tr_b16 (the
-//     four rows one read touches lie in four different 64-byte windows)
+//   ld_transposed: lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] and the same of k0 + 8 through ds_read_b64_tr_b16 (the
+//     four rows one read touches lie in four different 64-byte windows).  These are, in this order, the rows that a lane of a 32 x 32 product tile
+//     holds in eight neighbouring entries, so that those are the other operand of a 32x32x16 MFMA as they are
 // The matrices that a tile's products walk over come from there: fetched from global memory between those dependent products,
 // each operand costs the latency of the L2 or beyond (S = 128, 384 heads: backward 37.6 us that way, 23.6 from LDS).  What a wave
 // holds for a whole tile -- the queries of the forward pass, the own rows of the backward pass -- is read by one wave only, once
 // a tile, and comes from global memory.
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 __device__ __forceinline__ int chunk_swz(int row) { return (((row >> 1) & 1) << 2) | ((row >> 2) & 3); }
-// Rows from `kept` on are zeros: what lies behind a sequence's rows may be anything.
+// Rows from `kept` on are zeros: what lies behind a sequence's rows may be anything.  They are read from the last row that is there, so that
+// all loads are under way at once: with a branch around each, every one waited for the one before it (one text of 128 positions, 12 heads
+// 9.2 -> 5.8 us).
 template <int THREADS, int ROWS>
-__device__ __forceinline__ void stage_rows(const bf16_t* __restrict__ src, int64_t ld, int kept, bf16_t* __restrict__ S) {
+struct Staged {
+  static constexpr int N = ROWS * 8 / THREADS;
+  static_assert(ROWS * 8 % THREADS == 0 && THREADS % 8 == 0, "whole pieces");
+  uint4 v[N];
+  __device__ __forceinline__ void load(const bf16_t* __restrict__ src, int ld, int kept) {
 #pragma unroll
-  for (int c0 = 0; c0 < ROWS * 8; c0 += THREADS) {
-    const int c = c0 + threadIdx.x, row = c >> 3, ec = c & 7;
-    if (ROWS * 8 % THREADS == 0 || c < ROWS * 8)
-      *reinterpret_cast<uint4*>(S + row * AD + (ec ^ chunk_swz(row)) * 8) = row < kept ? *reinterpret_cast<const uint4*>(src + (int64_t)row * ld + ec * 8) : make_uint4(0u, 0u, 0u, 0u);
+    for (int i = 0; i < N; ++i) {
+      const int row = i * (THREADS / 8) + (threadIdx.x >> 3);
+      v[i] = *reinterpret_cast<const uint4*>(src + (uint32_t)(min(row, kept - 1) * ld + (threadIdx.x & 7) * 8));
+    }
   }
-}
+  __device__ __forceinline__ void store(bf16_t* __restrict__ S, int kept) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int row = i * (THREADS / 8) + (threadIdx.x >> 3);
+      const uint32_t m = row < kept ? ~0u : 0u;
+      *reinterpret_cast<uint4*>(S + row * AD + ((threadIdx.x & 7) ^ chunk_swz(row)) * 8) = make_uint4(v[i].x & m, v[i].y & m, v[i].z & m, v[i].w & m);
+    }
+  }
+};
 struct RowsOperand { bf16x8 k[4]; };   // the four k-steps (of 16 features) of 32 rows
 __device__ __forceinline__ RowsOperand rows_operand(const bf16_t* __restrict__ S, int base, int lane) {
   RowsOperand o;
@@ -354,13 +369,21 @@ __device__ __forceinline__ RowsOperand rows_operand(const bf16_t* __restrict__ S
   for (int ks = 0; ks < 4; ++ks) o.k[ks] = *reinterpret_cast<const bf16x8*>(S + row * AD + ((2 * ks + (lane >> 5)) ^ s) * 8);
   return o;
 }
-__device__ __forceinline__ s16x4 ld_transposed(const bf16_t* __restrict__ S, int e32, int k0, int lane) {
-  const int g = lane >> 4, j = lane & 15, row = k0 + 4 * (g >> 1) + (j >> 2), e = e32 + 16 * (g & 1) + 4 * (j & 3);
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(S + row * AD + ((e >> 3) ^ chunk_swz(row)) * 8 + (e & 7)));
+__device__ __forceinline__ bf16x8 ld_transposed(const bf16_t* __restrict__ S, int e32, int k0, int lane) {
+  const int g = lane >> 4, j = lane & 15, e = e32 + 16 * (g & 1) + 4 * (j & 3);
+  union { bf16x8 v; s16x4 h[2]; } u;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = k0 + 8 * i + 4 * (g >> 1) + (j >> 2);
+    u.h[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(S + row * AD + ((e >> 3) ^ chunk_swz(row)) * 8 + (e & 7)));
+  }
+  return u.v;
 }
 
 // X^T-style product tile: acc[32 x 32] = sum_e R[row][e] * C[column][e].  Result lane layout: column = cbase + l%32,
-// rows rbase + 8(r/4) + 4(l/32) + r%4.
+// rows rbase + 8(r/4) + 4(l/32) + r%4 = rbase + tile_row(r) + own_row(l).
+__device__ __forceinline__ constexpr int tile_row(int r) { return 8 * (r >> 2) + (r & 3); }
+__device__ __forceinline__ int own_row(int lane) { return 4 * (lane >> 5); }
 __device__ __forceinline__ f32x16 rows_dot_rows(const RowsOperand& R, const RowsOperand& C) {
   f32x16 acc;
 #pragma unroll
@@ -369,6 +392,29 @@ __device__ __forceinline__ f32x16 rows_dot_rows(const RowsOperand& R, const Rows
   for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(R.k[ks], C.k[ks], acc, 0, 0, 0);
   return acc;
 }
+
+// A tile g^T[64 features][own] to row `row`: lanes 32 apart, which have neighbouring halves of eight features, exchange them first, so that
+// each stores 16 bytes of one eight.
+__device__ __forceinline__ void store_row(const f32x16 (&g)[2], float scale, bf16_t* __restrict__ row, int lane) {
+#pragma unroll
+  for (int et = 0; et < 2; ++et)
+#pragma unroll
+    for (int c = 0; c < 4; c += 2) {
+      uint32_t p[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) p[i][k] = pack_bf16x2(g[et][4 * (c + i) + 2 * k] * scale, g[et][4 * (c + i) + 2 * k + 1] * scale);
+      const u32x2 x = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false), y = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+      *reinterpret_cast<uint4*>(row + 32 * et + 8 * (c + (lane >> 5))) = make_uint4(x[0], y[0], x[1], y[1]);
+    }
+}
+
+// exp(x / 8 - m) as 2^(x c - m log2 e) with one fused multiply-add: fewer roundings than product, difference and product
+// (A score of NO_WEIGHT gives 0: key 0 of a sequence is always real.  It is put in place of scores and not 0 in place of the result, around
+// which the compiler makes a branch.)
+constexpr float LOG2E = 1.44269504088896f, SCORE_LOG2E = 0.125f * LOG2E, NO_WEIGHT = -3.0e38f;
+__device__ __forceinline__ float exp_score(float x, float m_log2e) { return __builtin_amdgcn_exp2f(fmaf(x, SCORE_LOG2E, -m_log2e)); }
 
 // The rows of sequence b, of which `kept` are there, and its real tokens (keys at positions beyond get no weight).
 struct SeqRows { int row0, kept, len; };
@@ -390,89 +436,74 @@ __device__ __forceinline__ void zero_tail(const RowPlan& plan, int B, bf16_t* __
 // probability tile is already in the B-operand layout of the 32x32x8 MFMA for O^T[e][q] = sum_key V^T[e][key] P^T[key][q].
 // With a loop over the tiles of a wave, even one that never turns, the 16 NT comparisons of keys with the length are kept as lane
 // masks across it, hundreds of scalar registers of which most spill.
-template <int NT>
-__device__ __forceinline__ void attn_scores(const RowsOperand& q, const bf16_t* __restrict__ Ks, int qt, int len, int nk,
-                                            int lane, f32x16 (&s)[NT], float& inv, float* __restrict__ lse_row) {
-#pragma unroll
-  for (int kt = 0; kt < NT; ++kt)
-    if (kt < nk) s[kt] = rows_dot_rows(rows_operand(Ks, 32 * kt, lane), q);   // nk: tiles with a real key
-  float mx = -3.0e38f;
-#pragma unroll
-  for (int kt = 0; kt < NT; ++kt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int key = 32 * kt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      s[kt][r] = (kt < nk && key < len) ? s[kt][r] * 0.125f : -3.0e38f;   // exp(-3e38 - mx) = 0: key 0 is always real
-      mx = fmaxf(mx, s[kt][r]);
-    }
-  mx = join32(mx, [](float a, float b) { return fmaxf(a, b); });
-  float sum = 0.f;
-#pragma unroll
-  for (int kt = 0; kt < NT; ++kt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { s[kt][r] = __expf(s[kt][r] - mx); sum += s[kt][r]; }
-  sum = join32(sum, [](float a, float b) { return a + b; });
-  inv = 1.f / sum;
-  if (lane < 32 && lse_row != nullptr) lse_row[32 * qt + lane] = mx + __logf(sum);
-}
-
-template <int NT> struct AttnFwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES; };
+template <int NT> struct AttnFwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES, PER_SIMD = NT < 8 ? 4 : 2; };
 template <int NT, bool PADDED>   // PADDED = false: no lengths given, the comparisons against len fold away
-__global__ __launch_bounds__(AttnFwd<NT>::THREADS) void k_attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
+__global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k_attn_fwd(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out, float* __restrict__ lse,
                                                   int heads, int d, const int32_t* __restrict__ lens, RowPlan plan, int B) {
   constexpr int S = 32 * NT, THREADS = AttnFwd<NT>::THREADS;
   static_assert(NT <= AttnFwd<NT>::WAVES, "a tile of queries per wave");
   __shared__ __attribute__((aligned(16))) bf16_t Ks[S * AD];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[S * AD];
-  const int h = blockIdx.x, b = blockIdx.y, pass = b / B, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t ld = 3 * (int64_t)d;
-  const SeqRows sr = seq_rows<PADDED>(lens, plan, pass, b - pass * B, B, S);
+  const int h = blockIdx.x, b = blockIdx.y, pass = blockIdx.z, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ld = 3 * d;
+  const SeqRows sr = seq_rows<PADDED>(lens, plan, pass, b, B, S);
   const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
   const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
-  if (PADDED && b == pass * B) zero_tail<THREADS>(plan, B, out + (int64_t)pass * B * S * d + h * AD, d);
-  float* lse_row = lse != nullptr ? lse + ((int64_t)b * heads + h) * S : nullptr;
   const int qt = wave;
   // the queries of a tile are used by one wave only: from global memory, beside the staging
   RowsOperand q;
   {
-    const bf16_t* p = Q + (int64_t)(32 * (qt < nq ? qt : 0) + (lane & 31)) * ld + 8 * (lane >> 5);
+    const bf16_t* p = Q + (uint32_t)((32 * (qt < nq ? qt : 0) + (lane & 31)) * ld + 8 * (lane >> 5));
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) q.k[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
   }
-  stage_rows<THREADS, S>(Q + d, ld, kept, Ks);
-  stage_rows<THREADS, S>(Q + 2 * d, ld, kept, Vs);
+  Staged<THREADS, S> k, v;
+  k.load(Q + d, ld, kept);
+  v.load(Q + 2 * d, ld, kept);
+  if (PADDED && b == 0) zero_tail<THREADS>(plan, B, out + (int64_t)pass * B * S * d + h * AD, d);
+  k.store(Ks, kept);
+  v.store(Vs, kept);
   __syncthreads();
   if (qt >= nq) return;
   f32x16 s[NT];
-  float inv = 0.f;
-  attn_scores<NT>(q, Ks, qt, len, nk, lane, s, inv, lse_row);
-  f32x16 o[2];
 #pragma unroll
-  for (int et = 0; et < 2; ++et) {
+  for (int kt = 0; kt < NT; ++kt)
+    if (kt < nk) s[kt] = rows_dot_rows(rows_operand(Ks, 32 * kt, lane), q);   // nk: tiles with a real key
+  float mx = NO_WEIGHT;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[et][r] = 0.f;
+  for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
-    for (int kt = 0; kt < NT; ++kt) {
-      if (kt >= nk) break;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const s16x4 pb = pack4(s[kt][4 * c] * inv, s[kt][4 * c + 1] * inv, s[kt][4 * c + 2] * inv, s[kt][4 * c + 3] * inv);
-        const s16x4 va = ld_transposed(Vs, 32 * et, 32 * kt + 8 * c, lane);
-        o[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(va, pb, o[et], 0, 0, 0);
-      }
+    for (int r = 0; r < 16; ++r) {
+      if (PADDED) s[kt][r] = kt < nk && 32 * kt + tile_row(r) < len - own_row(lane) ? s[kt][r] : NO_WEIGHT;
+      mx = fmaxf(mx, s[kt][r]);
     }
-  }
-  if (PADDED && 32 * qt + (lane & 31) >= kept) return;
-  bf16_t* orow = out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD;
+  mx = join32(mx, [](float a, float b) { return fmaxf(a, b); });
+  const float m2 = mx * SCORE_LOG2E;
+  float sum = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { s[kt][r] = exp_score(s[kt][r], m2); sum += s[kt][r]; }
+  // The probabilities enter the product before they are divided by their sum, the result after it: half as many divisions, and beside the sum.
+  f32x16 o[2];
 #pragma unroll
   for (int et = 0; et < 2; ++et)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      uint2 pk;
-      pk.x = pack_bf16x2(o[et][4 * c], o[et][4 * c + 1]);
-      pk.y = pack_bf16x2(o[et][4 * c + 2], o[et][4 * c + 3]);
-      *reinterpret_cast<uint2*>(orow + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
+    for (int r = 0; r < 16; ++r) o[et][r] = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < NT; ++kt) {
+    if (kt >= nk) break;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const bf16x8 p = pack8(s[kt], 8 * c);
+#pragma unroll
+      for (int et = 0; et < 2; ++et) o[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_transposed(Vs, 32 * et, 32 * kt + 16 * c, lane), p, o[et], 0, 0, 0);
     }
+  }
+  sum = join32(sum, [](float a, float b) { return a + b; });
+  if (lane < 32 && lse != nullptr) lse[((int64_t)b * heads + h) * S + 32 * qt + lane] = mx * 0.125f + __logf(sum);
+  if (PADDED && 32 * qt + (lane & 31) >= kept) return;
+  store_row(o, 1.f / sum, out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD, lane);
 }
 
 // Backward.  Probabilities are recomputed from q, k and the saved log-sum-exp; a wave owns 32 queries or keys at a time.
@@ -494,7 +525,7 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS) void k_attn_fwd(const bf16_t*
 // The own rows and D's are fetched behind the staged ones, whose lines they share: ahead of them, with 2 or 32 lines to an
 // instruction each, they held those up (384 heads 20.8 -> 24.4 us).
 template <int NT, bool PADDED, int PARTS>
-__global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
+__global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
                                                                       const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                                       bf16_t* __restrict__ dqkv, int heads, int d, const int32_t* __restrict__ lens,
                                                                       RowPlan plan, int B) {
@@ -502,51 +533,54 @@ __global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16
   enum { DK = 0, DQ = 1, DV = 2 };   // of two parts the first is both dK and dV
   __shared__ __attribute__((aligned(16))) bf16_t s_r[S * AD];   // dQ: K; dK and dV: Q
   __shared__ __attribute__((aligned(16))) bf16_t s_t[S * AD];   // dQ: V; dK and dV: dO
-  __shared__ float s_D[S], s_lse[S];
+  __shared__ __attribute__((aligned(16))) float s_D[S], s_lse[S];
   const int h = blockIdx.x, b = blockIdx.y, part = blockIdx.z, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t ld = 3 * (int64_t)d;
+  const int ld = 3 * d;
   const SeqRows sr = seq_rows<PADDED>(lens, plan, 0, b, B, S);
   const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
   const bf16_t* Q = qkv + (int64_t)sr.row0 * ld + h * AD;
   const bf16_t* O = out + (int64_t)sr.row0 * d + h * AD;
   const bf16_t* dO = dout + (int64_t)sr.row0 * d + h * AD;
-  if (PADDED && b == 0) {
-    zero_tail<THREADS>(plan, B, dqkv + (part == DQ ? 0 : (part == DK ? d : 2 * d)) + h * AD, ld);
-    if (PARTS == 2 && part != DQ) zero_tail<THREADS>(plan, B, dqkv + 2 * d + h * AD, ld);
-  }
   // rows 32 tile + lane % 32 of a matrix, as rows_operand() would give them
-  auto own_rows = [&](const bf16_t* X, int64_t stride, int tile) {
+  auto own_rows = [&](const bf16_t* X, int stride, int tile) {
     RowsOperand o;
-    const bf16_t* p = X + (int64_t)(32 * tile + (lane & 31)) * stride + 8 * (lane >> 5);
+    const bf16_t* p = X + (uint32_t)((32 * tile + (lane & 31)) * stride + 8 * (lane >> 5));
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) o.k[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
     return o;
   };
-  if (part == DQ) {
-    stage_rows<THREADS, S>(Q + d, ld, kept, s_r);
-    stage_rows<THREADS, S>(Q + 2 * d, ld, kept, s_t);
-  } else {
-    stage_rows<THREADS, S>(Q, ld, kept, s_r);
-    stage_rows<THREADS, S>(dO, d, kept, s_t);
+  Staged<THREADS, S> r, t;
+  r.load(part == DQ ? Q + d : Q, ld, kept);
+  t.load(part == DQ ? Q + 2 * d : dO, part == DQ ? ld : d, kept);
+  // two threads per query
+  static_assert(THREADS == 2 * S, "one turn");
+  const int dq = threadIdx.x >> 1, dhalf = threadIdx.x & 1;
+  const bool with_d = !(PARTS == 3 && part == DV);
+  uint4 o4[4], d4[4];
+  if (with_d) {
+    const uint32_t at = (uint32_t)(min(dq, kept - 1) * d + dhalf * 32);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { o4[i] = *reinterpret_cast<const uint4*>(O + at + 8 * i); d4[i] = *reinterpret_cast<const uint4*>(dO + at + 8 * i); }
   }
-  // two threads per query; 2 S is a multiple of the number of threads
-  for (int t = threadIdx.x; t < 2 * S; t += THREADS) {
-    const int q = t >> 1, half = t & 1;
-    const bool there = !PADDED || q < kept;
-    float acc = 0.f;
+  const float dlse = lse[((int64_t)b * heads + h) * S + min(dq, kept - 1)];
+  if (PADDED && b == 0) {
+    zero_tail<THREADS>(plan, B, dqkv + (part == DQ ? 0 : (part == DK ? d : 2 * d)) + h * AD, ld);
+    if (PARTS == 2 && part != DQ) zero_tail<THREADS>(plan, B, dqkv + 2 * d + h * AD, ld);
+  }
+  r.store(s_r, kept);
+  t.store(s_t, kept);
+  float D = 0.f;
+  if (with_d) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if (!there || (PARTS == 3 && part == DV)) break;
-      const uint4 o4 = *reinterpret_cast<const uint4*>(O + (int64_t)q * d + half * 32 + 8 * i);
-      const uint4 d4 = *reinterpret_cast<const uint4*>(dO + (int64_t)q * d + half * 32 + 8 * i);
-      const uint32_t ow[4] = {o4.x, o4.y, o4.z, o4.w}, dw[4] = {d4.x, d4.y, d4.z, d4.w};
+      const uint32_t ow[4] = {o4[i].x, o4[i].y, o4[i].z, o4[i].w}, dw[4] = {d4[i].x, d4[i].y, d4[i].z, d4[i].w};
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        acc = fmaf(bf16_to_f32((bf16_t)(ow[e >> 1] >> ((e & 1) * 16))), bf16_to_f32((bf16_t)(dw[e >> 1] >> ((e & 1) * 16))), acc);
+        D = fmaf(bf16_to_f32((bf16_t)(ow[e >> 1] >> ((e & 1) * 16))), bf16_to_f32((bf16_t)(dw[e >> 1] >> ((e & 1) * 16))), D);
     }
-    acc += __shfl_xor(acc, 1, 64);
-    if (half == 0) { s_D[q] = acc; s_lse[q] = there ? lse[((int64_t)b * heads + h) * S + q] : 0.f; }
+    D += __shfl_xor(D, 1, 64);
   }
+  if (dhalf == 0) { s_D[dq] = D * 0.125f; s_lse[dq] = dlse * LOG2E; }   // of rows that are not there: not used
   __syncthreads();
 
   if (wave >= nq) return;                                          // a wave owns a tile of queries (dQ) or keys
@@ -560,13 +594,23 @@ __global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16
   // g^T[e][own] += sum over the 32 rows of `tile` of T^T[e][row] w[row][own]
   auto accumulate = [&](f32x16 (&g)[2], const bf16_t* T, int tile, const f32x16& w) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const s16x4 wb = pack4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]);
+    for (int c = 0; c < 2; ++c) {
+      const bf16x8 wb = pack8(w, 8 * c);
 #pragma unroll
       for (int et = 0; et < 2; ++et)
-        g[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(T, 32 * et, 32 * tile + 8 * c, lane), wb, g[et], 0, 0, 0);
+        g[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_transposed(T, 32 * et, 32 * tile + 16 * c, lane), wb, g[et], 0, 0, 0);
     }
   };
+  auto of_queries = [&](const float* x, int qt) {   // for the rows of a lane in a tile of queries
+    f32x16 v;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float4 t = *reinterpret_cast<const float4*>(x + 32 * qt + own_row(lane) + 8 * c);
+      v[4 * c] = t.x; v[4 * c + 1] = t.y; v[4 * c + 2] = t.z; v[4 * c + 3] = t.w;
+    }
+    return v;
+  };
+  auto there = [&](int r, int qt) { return !PADDED || tile_row(r) < kept - own_row(lane) - 32 * qt; };
   if (part == DQ) {
     const float lq = s_lse[col], Dq = s_D[col];
     const RowsOperand qop = own_rows(Q, ld, own), dop = own_rows(dO, d, own);
@@ -576,8 +620,8 @@ __global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16
       const f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * kt, lane), dop);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int key = 32 * kt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        st[r] = !PADDED || key < len ? __expf(st[r] * 0.125f - lq) * (dp[r] - Dq) * 0.125f : 0.f;   // dS^T; a padded key has P = 0
+        if (PADDED) st[r] = tile_row(r) < len - own_row(lane) - 32 * kt ? st[r] : NO_WEIGHT;
+        st[r] = exp_score(st[r], lq) * fmaf(dp[r], 0.125f, -Dq);                 // dS^T
       }
       accumulate(g, s_r, kt, st);
     }
@@ -587,11 +631,9 @@ __global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16
 #pragma unroll 1
       for (int qt = 0; qt < nq; ++qt) {
         f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);
+        const f32x16 l = of_queries(s_lse, qt);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          st[r] = !PADDED || q < kept ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;
-        }
+        for (int r = 0; r < 16; ++r) st[r] = exp_score(there(r, qt) ? st[r] : NO_WEIGHT, l[r]);
         accumulate(g, s_t, qt, st);
       }
     }
@@ -601,12 +643,11 @@ __global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16
     for (int qt = 0; qt < nq; ++qt) {
       f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);          // S[q][key]
       f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * qt, lane), vop);
+      const f32x16 l = of_queries(s_lse, qt), D8 = of_queries(s_D, qt);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int q = 32 * qt + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        const bool on = !PADDED || q < kept;
-        st[r] = on ? __expf(st[r] * 0.125f - s_lse[q]) : 0.f;                    // P
-        dp[r] = on ? st[r] * (dp[r] - s_D[q]) * 0.125f : 0.f;                    // dS
+        st[r] = exp_score(there(r, qt) ? st[r] : NO_WEIGHT, l[r]);               // P
+        dp[r] = st[r] * fmaf(dp[r], 0.125f, -D8[r]);                             // dS
       }
       if constexpr (PARTS == 2) accumulate(gv, s_t, qt, st);
       accumulate(g, s_r, qt, dp);
@@ -620,16 +661,7 @@ __global__ __launch_bounds__(64 * NT, NT < 8 ? 3 : 4) void k_attn_bwd(const bf16
   }
   if (PADDED && col >= kept) return;
   auto store = [&](const f32x16 (&g)[2], int to) {   // to: where the result goes among the columns of dqkv
-    bf16_t* row = dqkv + ((int64_t)sr.row0 + col) * ld + to + h * AD;
-#pragma unroll
-    for (int et = 0; et < 2; ++et)
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        uint2 pk;
-        pk.x = pack_bf16x2(g[et][4 * c], g[et][4 * c + 1]);
-        pk.y = pack_bf16x2(g[et][4 * c + 2], g[et][4 * c + 3]);
-        *reinterpret_cast<uint2*>(row + 32 * et + 8 * c + 4 * (lane >> 5)) = pk;
-      }
+    store_row(g, 1.f, dqkv + ((int64_t)sr.row0 + col) * ld + to + h * AD, lane);
   };
   store(g, part == DQ ? 0 : (part == DK ? d : 2 * d));
   if (PARTS == 2 && part != DQ) store(gv, 2 * d);
@@ -857,7 +889,7 @@ bool attention_supports(int S) { return S == 64 || S == 128 || S == 256; }
 void launch_attention_fwd(hipStream_t st, const bf16_t* qkv, bf16_t* out, float* lse, int nw, int B, int S, int heads, int d,
                           const int32_t* lens, const RowPlan& plan) {
   ProfScope ps(st, F_ATTN_FWD, 4.0 * nw * B * heads * (double)S * S * 64.0);
-  const dim3 grid(heads, nw * B);
+  const dim3 grid(heads, B, nw);
   switch (S) {
     case 64:
       if (lens) launch_kernel(ps, k_attn_fwd<2, true>, grid, AttnFwd<2>::THREADS, 0, st, qkv, out, lse, heads, d, lens, plan, B);
