@@ -433,7 +433,11 @@ __device__ __forceinline__ void zero_tail(const RowPlan& plan, int B, bf16_t* __
 
 // Forward.  A wave owns a tile of 32 queries (S = 64: two of the four waves only stage).  S^T[key][q] tiles leave each lane
 // with one query column, so the softmax over keys is an in-lane reduction plus one exchange between the halves, and the
-// probability tile is already in the B-operand layout of the 32x32x8 MFMA for O^T[e][q] = sum_key V^T[e][key] P^T[key][q].
+// probability tile is already an operand of the MFMA for O^T[e][q] = sum_key V^T[e][key] P^T[key][q].
+// Bound by memory where the heads fill the chip (1024 heads of 128 positions, 67 MB: 21.3 -> 15.5 us, 4.3 TB/s) and by the chain of a tile where
+// they do not (12 heads 9.2 -> 5.8, 384 10.3 -> 8.0, 228 of 256 positions 14.6 -> 10.7).  What shortened it: no load waits for another, a
+// score takes seven vector instructions where it took eleven, and 32x32x16 products instead of 32x32x8 ones at half the rate; 128 registers let
+// four workgroups share a CU.
 // With a loop over the tiles of a wave, even one that never turns, the 16 NT comparisons of keys with the length are kept as lane
 // masks across it, hundreds of scalar registers of which most spill.
 template <int NT> struct AttnFwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES, PER_SIMD = NT < 8 ? 4 : 2; };
@@ -516,6 +520,8 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k
 // exponentials, product) and by the requests for the rows it stages and holds.
 //   Three parts: the scores are formed three times instead of twice, but 3 to 4 workgroups share a CU (35 KB of LDS at S = 128, at most
 //   128 registers; 2 of eight waves at S = 256, with 68 KB) where one that formed all three, with 64 KB, had it alone.
+//   (The times of these two paragraphs are of kernels with 32x32x8 products, whose masked forms branched around each exponential and each piece that
+//   was staged: beside the weight gradients, 384 heads of 128 positions 20.7 -> 16.4 us, padded 21.8 -> 14.1, 228 padded of 256 27.9 -> 20.9.)
 //   Two parts: a round of three workgroups to a CU instead of four, with a longer chain each (12 heads of S = 128: 9.8 us against
 //   6.8), so only once there are more heads than CUs: S = 128, 384 heads 18.6 us against 19.1 and, padded, 17.5 against 20.7;
 //   1024 heads 50.3 against 53.3, padded 36.7 against 39.1.  256 heads 13.7 against 12.2, 128 10.8 against 8.6.  At S = 64 the two are
