@@ -23,6 +23,9 @@ constexpr int EW_TRIP = EW_U * EW_THREADS;   // vectors per block per trip
 // thread.  us, four / one: Adam of 63 thousand 3.94 / 2.39, 269 thousand 4.39 / 2.99, 500 thousand 4.20 / 3.65, 2^20 4.47 / 4.47;
 // SGD 2.83 / 2.42, 3.41 / 2.72, 2.94 / 2.78, 3.15 / 3.38; the nudge 2.78 / 2.41, 2.91 / 2.49, 2.74 / 2.53, 3.11 / 2.86.
 constexpr int64_t EW_FEW = 1 << 19;
+// The adaptation's blocks of a quarter of the vectors would be four times as many partials and tickets (below): its blocks have four times the
+// threads instead, but for a single block, which takes no longer with four vectors a thread.  us, four / one: 269 thousand 9.0 / 6.1, 786 thousand 6.5 / 5.1.
+constexpr int64_t ADAPT_FEW = 1 << 20;
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
@@ -199,29 +202,33 @@ __device__ __forceinline__ void finish_eps(double sum_sq, float alpha, float* __
   status[0] = ok2 ? 0 : 1;
 }
 
-__global__ __launch_bounds__(EW_THREADS) void k_adapt_norm(const float* __restrict__ g, const float* __restrict__ m,
-                                                           const float* __restrict__ v, const float* __restrict__ gmeta,
-                                                           float* __restrict__ vdir, double* __restrict__ partial,
-                                                           int64_t n, AdaptArgs a, EpsFinish fin) {
+// U vectors a thread; a block has EW_TRIP of them a trip either way, so that the partials, and the tickets that the blocks of a launch take one
+// after the other, are as many.
+template <int U>
+__global__ __launch_bounds__(EW_TRIP / U) void k_adapt_norm(const float* __restrict__ g, const float* __restrict__ m,
+                                                            const float* __restrict__ v, const float* __restrict__ gmeta,
+                                                            float* __restrict__ vdir, double* __restrict__ partial,
+                                                            int64_t n, AdaptArgs a, EpsFinish fin) {
+  constexpr int THREADS = EW_TRIP / U;
   __shared__ float red[16];
-  __shared__ double dred[EW_THREADS];
+  __shared__ double dred[THREADS];
   __shared__ int s_last;
   if (a.dev != nullptr) { a.lr_c1_c2 = a.dev[2]; a.c2 = a.dev[3]; }
   const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
   float acc = 0.f;
   for (int64_t base = (int64_t)blockIdx.x * EW_TRIP + threadIdx.x; base < nv; base += trip) {
-    f4 G[EW_U], M[EW_U], V[EW_U], Q[EW_U];
+    f4 G[U], M[U], V[U], Q[U];
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
-      const int64_t j = base + u * EW_THREADS;
+    for (int u = 0; u < U; ++u) {
+      const int64_t j = base + u * THREADS;
       if (j < nv) {
         Q[u] = ld_nt(gmeta, j);
         if (a.mode == 0) { G[u] = ld_nt(g, j); M[u] = ld_nt(m, j); V[u] = ld_nt(v, j); }
       }
     }
 #pragma unroll
-    for (int u = 0; u < EW_U; ++u) {
-      const int64_t j = base + u * EW_THREADS;
+    for (int u = 0; u < U; ++u) {
+      const int64_t j = base + u * THREADS;
       if (j < nv) {
         f4 o;
         if (a.mode == 0) {
@@ -247,8 +254,8 @@ __global__ __launch_bounds__(EW_THREADS) void k_adapt_norm(const float* __restri
   if (threadIdx.x == 0) publish(partial + blockIdx.x, (double)s);
   if (fin.ticket == nullptr || !last_block(fin.ticket, gridDim.x, &s_last)) return;
   double d = 0.0;
-  for (int i = threadIdx.x; i < (int)gridDim.x; i += EW_THREADS) d += collect(partial + i);
-  finish_eps(block_tree_sum<EW_THREADS>(d, dred), fin.alpha, fin.scalars, fin.status);
+  for (int i = threadIdx.x; i < (int)gridDim.x; i += THREADS) d += collect(partial + i);
+  finish_eps(block_tree_sum<THREADS>(d, dred), fin.alpha, fin.scalars, fin.status);
 }
 
 // The second stage as a launch of its own: fixed-order sum of the per-block partials in double, then eps.
@@ -481,11 +488,16 @@ void launch_sgd(hipStream_t st, float* g, float* buf, float* theta, bf16_t* thet
   if (n <= EW_FEW) k_sgd<1><<<ew_grid(n, 1), EW_THREADS, 0, st>>>(g, buf, theta, theta16, lo, n, n16, lr, wd, mu);
   else k_sgd<EW_U><<<ew_grid(n), EW_THREADS, 0, st>>>(g, buf, theta, theta16, lo, n, n16, lr, wd, mu);
 }
+static void launch_adapt(ProfScope& ps, int grid, hipStream_t st, const float* g, const float* m, const float* v, const float* gmeta, float* vdir,
+                         double* partial, int64_t n, const AdaptArgs& a, const EpsFinish& fin) {
+  if (n > EW_TRIP * EW_VEC && n <= ADAPT_FEW) launch_kernel(ps, k_adapt_norm<1>, grid, EW_TRIP, 0, st, g, m, v, gmeta, vdir, partial, n, a, fin);
+  else launch_kernel(ps, k_adapt_norm<EW_U>, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a, fin);
+}
 void launch_adapt_norm(hipStream_t st, const float* g, const float* m, const float* v, const float* gmeta, float* vdir,
                        double* partial, int64_t n, const AdaptArgs& a, float alpha, float* scalars, int64_t* status) {
   const int grid = ew_grid(n);
   ProfScope ps(st, F_ADAPT_NORM, (a.mode == 0 ? 20.0 : 8.0) * n);
-  launch_kernel(ps, k_adapt_norm, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a, EpsFinish{});
+  launch_adapt(ps, grid, st, g, m, v, gmeta, vdir, partial, n, a, EpsFinish{});
   k_eps_from_partials<<<1, 1024, 0, st>>>(partial, grid, alpha, scalars, status);
 }
 int launch_adapt_slice(hipStream_t st, const float* g, const float* m, const float* v, const float* gmeta, float* vdir,
@@ -499,7 +511,7 @@ int launch_adapt_slice(hipStream_t st, const float* g, const float* m, const flo
   const bool here = fin.ticket != nullptr && grid <= FINISH_BLOCKS;
   if (finished != nullptr) *finished = here;
   ProfScope ps(st, F_ADAPT_NORM, (a.mode == 0 ? 20.0 : 8.0) * n);
-  launch_kernel(ps, k_adapt_norm, grid, EW_THREADS, 0, st, g, m, v, gmeta, vdir, partial, n, a, here ? fin : EpsFinish{});
+  launch_adapt(ps, grid, st, g, m, v, gmeta, vdir, partial, n, a, here ? fin : EpsFinish{});
   return grid;
 }
 void launch_eps_from_partials(hipStream_t st, const double* partial, int count, float alpha, float* scalars, int64_t* status) {

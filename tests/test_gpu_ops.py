@@ -78,6 +78,12 @@ def test_adapt_norm_kernel(n):
     assert torch.equal(scal, scal2)
 
 
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 269322, 2 ** 20 - 3, 2 ** 20])
+def test_adapt_norm_launch_forms(n):
+    """Both sides of the lines between one and four vectors a thread."""
+    test_adapt_norm_kernel(n)
+
+
 def test_adapt_norm_degenerate():
     from paper_2310_05674_amd import binding as B
     n = 1000
