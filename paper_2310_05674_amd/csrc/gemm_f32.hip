@@ -320,6 +320,142 @@ __global__ __launch_bounds__(64 * FWAVES) void k_gemm_f32(GemmF32Batch batch, UP
   }
 }
 
+// Forward products that fill the chip.  There is no chain to shorten any more, and splitting the contraction over the waves has its price: a load
+// touches 64 bytes of each of 16 rows, two chunks a wave are all that the registers hold in flight, and the partial tiles meet in LDS
+// at the end.  Here a wave owns 32 x 16 of a workgroup's 64 x 32 and walks the whole contraction.  Slabs of 64 of the operands' rows come as whole lines,
+// whatever their alignment, through registers (two slabs on their way) into three LDS stages with one barrier a slab; a wave fetches the next chunk's
+// operands ahead of a chunk's products, also across the barrier.  Chunk c adds to accumulator c % 8, and the eight are added in
+// order: the sums of the other tiles, to the bit.  Rows are 68 floats apart, so that the 16 rows of a fetch lie in 16 different places of the banks.
+// Bound by the matrix cores in the loop (2048 x 256 x 768: 12.7 thousand clk of MFMAs, 17.2 as it is; with a slab's fetches, stores and loads ahead of its
+// products instead of between them 23.9, with two workgroups of four 16 x 16 waves to a CU 18.5).  us a launch, 64 x 32 tile with the contraction
+// split / this: 2048 x 256 x 784 15.2 / 11.4, 2048 x 256 x 256 7.9 / 5.8; scoring 2048 samples with 784-256-256-10 28.5 / 24.9.
+constexpr int LDS_K = 64, LDS_ROW = LDS_K + 4, LDS_M = 64, LDS_N = 32;
+__global__ __launch_bounds__(256, 2) void k_gemm_f32_lds(GemmF32Args a, int blocks) {
+  constexpr int NP = (LDS_M + LDS_N) / 16, XM = 2;
+  __shared__ __attribute__((aligned(16))) float sm[3][LDS_M + LDS_N][LDS_ROW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), r = lane & 15, q = lane >> 4;
+  const int nbx = (a.N + LDS_N - 1) / LDS_N, local = (blockIdx.x & 7) * (blocks >> 3) + (blockIdx.x >> 3);   // as above
+  const int i0 = (local / nbx) * LDS_M, j0 = (local % nbx) * LDS_N;
+  if (i0 >= a.M) return;
+  const int nfull = a.K / LDS_K, rest = a.K % LDS_K;   // nfull > 0
+  // a thread has 16 bytes of every sixteenth row of a slab, A's, then B's; rows beyond the end are clamped
+  const int row = tid >> 4, col = 4 * (tid & 15);
+  const float* p[NP];
+#pragma unroll
+  for (int u = 0; u < NP; ++u)
+    p[u] = (u < LDS_M / 16 ? a.A + (int64_t)min(i0 + row + 16 * u, a.M - 1) * a.sa_i : a.B + (int64_t)min(j0 + row + 16 * u - LDS_M, a.N - 1) * a.sb_j) + col;
+  float4v st[2][NP], tail[NP];   // slabs on their way, by parity; what is not a whole slab, with zeros from K on
+  auto load = [&](int s, int u) {   // (of the last slab again behind it: no load in the loop is conditional, because the waits count them)
+    return *reinterpret_cast<const f4u*>(p[u] + min(s, nfull - 1) * LDS_K);
+  };
+  float (*const to)[LDS_ROW] = reinterpret_cast<float (*)[LDS_ROW]>(&sm[0][row][col]);
+  auto store = [&](int stage, int u, const float4v& v) { *reinterpret_cast<float4v*>(to[stage * (LDS_M + LDS_N) + 16 * u]) = v; };
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int u = 0; u < NP; ++u) st[i][u] = load(i, u);
+#pragma unroll
+  for (int u = 0; u < NP; ++u) tail[u] = (float4v){0.f, 0.f, 0.f, 0.f};
+  if (rest > 0) {
+    const int k = nfull * LDS_K;
+    if (col + 4 <= rest) {
+#pragma unroll
+      for (int u = 0; u < NP; ++u) tail[u] = *reinterpret_cast<const f4u*>(p[u] + k);
+    } else {
+#pragma unroll
+      for (int u = 0; u < NP; ++u)
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (col + e < rest) tail[u][e] = p[u][k + e];
+    }
+  }
+  const int wi = (wave >> 1) * 16 * XM + r, wj = LDS_M + (wave & 1) * 16 + r, gj = j0 + wj - LDS_M;
+  const float bias = a.bias != nullptr ? a.bias[min(gj, a.N - 1)] : 0.f;
+  float4v acc[XM][8], op[2][XM + 1];   // operands of a chunk: B's, A's
+#pragma unroll
+  for (int x = 0; x < XM; ++x)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[x][c] = (float4v){0.f, 0.f, 0.f, 0.f};
+  const float (*const fa)[LDS_ROW] = reinterpret_cast<const float (*)[LDS_ROW]>(&sm[0][wi][4 * q]);
+  const float (*const fb)[LDS_ROW] = reinterpret_cast<const float (*)[LDS_ROW]>(&sm[0][wj][4 * q]);
+  auto fetch = [&](int stage, int c, int i) {
+    return *reinterpret_cast<const float4v*>(&(i == 0 ? fb : fa)[stage * (LDS_M + LDS_N) + (i == 0 ? 0 : 16 * (i - 1))][16 * c]);
+  };
+  auto fetch_all = [&](int stage, int c, float4v (&v)[XM + 1]) {
+#pragma unroll
+    for (int i = 0; i <= XM; ++i) v[i] = fetch(stage, c, i);
+  };
+  // The products of a slab whose first chunk has been fetched.  Between them: the fetches for the next chunk, the slab after the next on its
+  // way to its stage, the requests for the one after those.  Each goes behind a product of its own, because with one wave to a SIMD nothing
+  // else multiplies while an LDS or address unit takes its time.
+  auto slab = [&](int s, int st0, int st1, int st2, auto odd) {
+    constexpr int P = decltype(odd)::value;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int m = 0; m < 4 * XM; ++m) {
+        const int e = m / XM, x = m % XM;
+        __builtin_amdgcn_sched_barrier(0);
+        acc[x][4 * P + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(op[c & 1][1 + x][e], op[c & 1][0][e], acc[x][4 * P + c], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (m <= XM) op[(c + 1) & 1][m] = c < 3 ? fetch(st0, c + 1, m) : fetch(st1, 0, m);
+        else if (c < 3 && m < XM + 3) store(st2, 2 * c + m - XM - 1, st[P][2 * c + m - XM - 1]);
+        else if (c < 3 && m < XM + 5) st[P][2 * c + m - XM - 3] = load(s + 4, 2 * c + m - XM - 3);
+      }
+    }
+    __syncthreads();
+  };
+  static_assert(NP == 6 && XM == 2, "places between the products");
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int u = 0; u < NP; ++u) { store(i, u, st[i][u]); st[i][u] = load(2 + i, u); }
+  __syncthreads();
+  fetch_all(0, 0, op[0]);
+  int s = 0, s0 = 0, s1 = 1, s2 = 2;   // stages of this slab and the next two
+  auto next = [&]() { const int t = s0; s0 = s1; s1 = s2; s2 = t; };
+  for (; s + 1 < nfull; s += 2) {
+    slab(s, s0, s1, s2, even); next();
+    slab(s + 1, s0, s1, s2, odd); next();
+  }
+  if (s < nfull) { slab(s, s0, s1, s2, even); next(); }
+  if (rest > 0) {
+#pragma unroll
+    for (int u = 0; u < NP; ++u) store(s1, u, tail[u]);   // (of s0 the first chunk may still be being fetched)
+    __syncthreads();
+    auto last = [&](auto odd) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (c * FCH >= rest) break;
+        fetch_all(s1, c, op[0]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int x = 0; x < XM; ++x)
+            acc[x][4 * decltype(odd)::value + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(op[0][1 + x][e], op[0][0][e], acc[x][4 * decltype(odd)::value + c], 0, 0, 0);
+      }
+    };
+    if (nfull & 1) last(odd);
+    else last(even);
+  }
+  if (gj >= a.N) return;
+#pragma unroll
+  for (int x = 0; x < XM; ++x)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int gi = i0 + (wave >> 1) * 16 * XM + 16 * x + 4 * q + e;
+      if (gi >= a.M) return;
+      float c = acc[x][0][e];
+#pragma unroll
+      for (int w = 1; w < 8; ++w) c += acc[x][w][e];
+      c += bias;
+      if (a.relu) c = fmaxf(c, 0.f);
+      a.C[(int64_t)gi * a.ldc + gj] = c;
+    }
+}
+
 int64_t tiles(const GemmF32Args* a, int count, int tm, int tn) {
   int64_t n = 0;
   for (int k = 0; k < count; ++k) n += (int64_t)((a[k].N + tn - 1) / tn) * ((a[k].M + tm - 1) / tm);
@@ -359,6 +495,11 @@ void launch(hipStream_t st, const GemmF32Args* a, int count, const BaseUpdate* u
   constexpr int CUS = 256;
   if (tiles(a, count, 16, 16) <= 2 * CUS) launch_tile_f32<1, 1, 8>(ps, st, a, count, u);
   else if (tiles(a, count, 32, 32) <= CUS) launch_tile_f32<2, 2, 4>(ps, st, a, count, u);
+  // (the first slab has to be a whole one; gates and perturbed weights belong to products that do not fill the chip)
+  else if (count == 1 && storage_of(a[0]) == F32_FORWARD && a[0].Bv == nullptr && a[0].gate == nullptr && a[0].K >= LDS_K) {
+    const int blocks = (int)(tiles(a, 1, LDS_M, LDS_N) + 7) / 8 * 8;
+    launch_kernel(ps, k_gemm_f32_lds, blocks, 256, 0, st, a[0], blocks);
+  }
   else launch_tile_f32<4, 2, 2>(ps, st, a, count, u);
 }
 }  // namespace

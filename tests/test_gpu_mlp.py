@@ -298,6 +298,28 @@ def test_every_fp32_tile(B):
     gpu.close()
 
 
+@pytest.mark.parametrize("d", [63, 64, 65, 79, 127, 128, 131, 176, 191, 192])
+def test_products_that_fill_the_chip(d):
+    """Contractions of one to three whole slabs of 64 with every kind of rest, rows and columns that are no multiple of a tile: logits, losses and weights
+    against the oracle, and the first 37 samples scored alone keep their bits."""
+    import torch
+    from datagen.workloads import Workload
+    B, dims = 1030, (d, 333, 289, 3)
+    r = CounterRNG(500 + d)
+    wl = Workload(cfg=0, kind="mlp", dims=dims, bf16=False, H=9, batch=B, meta_batch=B, base_lr=1e-2, meta_lr=1e-3, alpha=0.5,
+                  noise=0.0, n_train=B, n_meta=B, steps=1)
+    x = r.normal(1, B * d).reshape(B, d).astype(np.float32); y = r.integers(2, B, 3).astype(np.int32)
+    nt = sum(a * b + b for a, b in zip(dims, dims[1:]))
+    orc, gpu = make_pair(wl, (0.06 * r.normal(5, nt)).astype(np.float32).astype(np.float64), r.normal(6, 28).astype(np.float32).astype(np.float64))
+    out = [[torch.zeros(n, 3, device=gpu.dev), torch.zeros(n, device=gpu.dev), torch.zeros(n, device=gpu.dev)] for n in (B, 37)]
+    gpu.eval(dev_batch(gpu, x, y), *out[0])
+    gpu.eval(dev_batch(gpu, x[:37], y[:37]), *out[1])
+    for all_, few, want in zip(*out, orc.evaluate(x, y)):
+        assert torch.equal(all_[:37], few)
+        assert rel_l2(all_.cpu().numpy(), want) < TOL
+    gpu.close()
+
+
 def test_batch_size_limits():
     """One sample, the largest batch the library takes (2048), and the sizes it must refuse."""
     import torch
