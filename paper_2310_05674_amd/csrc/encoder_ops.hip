@@ -488,8 +488,10 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k
   for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { s[kt][r] = exp_score(s[kt][r], m2); sum += s[kt][r]; }
-  // The probabilities enter the product before they are divided by their sum, the result after it: half as many divisions, and beside the sum.
+  // The probabilities enter the product before they are divided by their sum, the result after it: half as many divisions, and beside the sum.  What
+  // it is divided by is the sum of the rounded ones, so that the weights of a row add up to one and what the values have in common comes through unrounded.
   f32x16 o[2];
+  float weight = 0.f;
 #pragma unroll
   for (int et = 0; et < 2; ++et)
 #pragma unroll
@@ -501,13 +503,16 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k
     for (int c = 0; c < 2; ++c) {
       const bf16x8 p = pack8(s[kt], 8 * c);
 #pragma unroll
+      for (int e = 0; e < 8; ++e) weight += (float)p[e];
+#pragma unroll
       for (int et = 0; et < 2; ++et) o[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_transposed(Vs, 32 * et, 32 * kt + 16 * c, lane), p, o[et], 0, 0, 0);
     }
   }
   sum = join32(sum, [](float a, float b) { return a + b; });
   if (lane < 32 && lse != nullptr) lse[((int64_t)b * heads + h) * S + 32 * qt + lane] = mx * 0.125f + __logf(sum);
+  weight = join32(weight, [](float a, float b) { return a + b; });
   if (PADDED && 32 * qt + (lane & 31) >= kept) return;
-  store_row(o, 1.f / sum, out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD, lane);
+  store_row(o, 1.f / weight, out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD, lane);
 }
 
 // Backward.  Probabilities are recomputed from q, k and the saved log-sum-exp; a wave owns 32 queries or keys at a time.
