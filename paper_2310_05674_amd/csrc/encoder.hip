@@ -60,14 +60,14 @@ class EncoderModel : public Model {
     for (int l = 0; l < L_; ++l) {
       const size_t R = (l == 0 ? 2 : 1) * M;
       qkv_[l] = ws.take<bf16_t>(R * 3 * d_); lse_[l] = ws.take<float>((size_t)max_b * heads_ * S_);
-      ao_[l] = ws.take<bf16_t>(R * d_); pre1_[l] = ws.take<float>(R * d_); mean1_[l] = ws.take<float>(M); rstd1_[l] = ws.take<float>(M);
+      ao_[l] = ws.take<bf16_t>(R * d_); pre1_[l] = ws.take<float>(R * d_); mean1_[l] = ws.take<float>(R); rstd1_[l] = ws.take<float>(R);
       x1_[l] = ws.take<bf16_t>(R * d_); fpre_[l] = ws.take<bf16_t>(R * ffn_); fact_[l] = ws.take<bf16_t>(R * ffn_);
-      pre2_[l] = ws.take<float>(R * d_); mean2_[l] = ws.take<float>(M); rstd2_[l] = ws.take<float>(M);
+      pre2_[l] = ws.take<float>(R * d_); mean2_[l] = ws.take<float>(R); rstd2_[l] = ws.take<float>(R);
     }
     gelu_tab_ = (float*)ws.take<char>(gelu_table_bytes());
     plan_.start = ws.take<int32_t>(MAX_SEQ + 1); plan_.rows = ws.take<int32_t>(1); plan_.ids = ws.take<int32_t>(M); plan_.src = ws.take<int32_t>(M);
     plan_.group = ws.take<int32_t>(M / ROW_GROUP);
-    pre0_ = ws.take<float>(M * d_); mean0_ = ws.take<float>(M); rstd0_ = ws.take<float>(M);
+    pre0_ = ws.take<float>(2 * M * d_); mean0_ = ws.take<float>(2 * M); rstd0_ = ws.take<float>(2 * M);
     dX_[0] = ws.take<float>(M * d_); dX_[1] = ws.take<float>(M * d_);
     res_[0] = ws.take<float>(2 * M * d_); res_[1] = ws.take<float>(2 * M * d_);
     ds32_ = ws.take<float>(M * d_); do_ = ws.take<bf16_t>(M * d_);
@@ -94,10 +94,11 @@ class EncoderModel : public Model {
 
   void prepare(hipStream_t st) override { launch_gelu_tables(st, gelu_tab_); }
 
+  struct LnOff { int64_t g, b; };   // gain and shift of a LayerNorm inside theta
   // One linear layer of `nw` stacked passes (pass k owns rows [k M, (k + 1) M) of every activation): the same
-  // epilogue `e` (its pointers are those of pass 0) for each pass, with that pass's weights.
+  // epilogue `e` (its pointers are those of pass 0) for each pass, with that pass's weights, those of the LayerNorm `ln` where the residual is its output.
   void fwd_linear(hipStream_t st, const PassWeights* w, int nw, const bf16_t* A, int K, int64_t woff, int N, int64_t boff, int M,
-                  const GemmBf16Args& e, const int32_t* rows = nullptr) const {
+                  const GemmBf16Args& e, const int32_t* rows = nullptr, LnOff ln = {}) const {
     GemmBf16Args g[2];
     for (int k = 0; k < nw; ++k) {
       g[k] = e;
@@ -108,6 +109,7 @@ class EncoderModel : public Model {
       g[k].bias = w[k].theta + boff;
       if (w[k].sign != 0.f) { g[k].bias_v = w[k].vdir + boff; g[k].beps = w[k].eps_ptr; g[k].bsign = w[k].sign; }
       if (e.res32) g[k].res32 = e.res32 + ro;
+      if (e.ln_mean) { g[k].ln_mean = e.ln_mean + (int64_t)k * M; g[k].ln_g = (int32_t)(ln.g - boff); g[k].ln_b = (int32_t)(ln.b - boff); }
       if (e.C32) g[k].C32 = e.C32 + ro;
       if (e.C16) g[k].C16 = e.C16 + ro;
       if (e.C16_pre) g[k].C16_pre = e.C16_pre + ro;
@@ -166,10 +168,19 @@ class EncoderModel : public Model {
     const RowPlan rp = b.seq_len != nullptr ? plan_ : RowPlan{};   // a padded batch: only the rows that matter
     const bool scoring = nw == 1 && !keep;
     if (b.seq_len != nullptr) launch_row_plan(st, (const int32_t*)b.x, b.seq_len, B, S_, mb ? masked(b, *mb) : RowSelect{}, rp);
+    // The residual is made by the product that adds it, from the input and the statistics of the LayerNorm, which saves the LayerNorm's
+    // fp32 output, 4 of 10 bytes an element that it reads and writes; the bits are the same.  (The last LayerNorm's, and that of the one before the rows are
+    // selected, have other readers; so have all of a pass on the bf16 weights alone, whose tiles do without.)
+    // It pays once the LayerNorm is bound by memory; a smaller product's epilogue is a chain that gets longer.  us stored / made: scoring 128 rows of 12 x 768 551 / 549 to 560,
+    // 1024 rows of 6 x 768 427 / 429, 1024 of 6 x 1024 545 / 541, 2048 759 / 753, 4096 of 6 x 768 860 / 849, 8192 of 8 x 384 836 / 822; base step of 2048 rows of
+    // 8 x 384 1316 / 1319, 4096 1740 / 1728, 2048 of 6 x 1024 2780 / 2772; padded, 3072 rows of 6 x 768 2047 / 2000.
+    constexpr int64_t MAKE_RES = 1 << 20;
+    const bool make_res = w[0].lo != nullptr && (int64_t)nw * M * d_ > MAKE_RES;
+    auto others_read = [&](int l) { return !make_res || l == L_ - 1 || (l == L_ - 2 && sel.n > 0); };   // what leaves layer l (-1: the embeddings)
     ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};   // flips behind the first pass's rows
     LnFwdArgs e{};
-    e.x = nullptr; e.ids = rp.ids ? rp.ids : (const int32_t*)b.x; e.src = rp.src; e.rows = rp.rows; e.pass_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep ? pre0_ : nullptr;
-    e.pv = pv; e.g_off = eg_; e.b_off = eb_; e.y = X_[0]; e.y32 = res_[0]; e.mean = keep ? mean0_ : nullptr; e.rstd = keep ? rstd0_ : nullptr;
+    e.x = nullptr; e.ids = rp.ids ? rp.ids : (const int32_t*)b.x; e.src = rp.src; e.rows = rp.rows; e.pass_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep || !others_read(-1) ? pre0_ : nullptr;
+    e.pv = pv; e.g_off = eg_; e.b_off = eb_; e.y = X_[0]; e.y32 = others_read(-1) ? res_[0] : nullptr; e.mean = mean0_; e.rstd = rstd0_;
     e.M = nw * M; e.d = d_; e.ahead = weights_ahead(w, nw, scoring, off_[0].Wqkv, (int64_t)4 * d_ * d_, M, rp.rows);
     launch_ln_fwd(st, e);
     for (int l = 0; l < L_; ++l) {
@@ -190,10 +201,17 @@ class EncoderModel : public Model {
       }
       g = GemmBf16Args{};
       g.res32 = last ? res_sel_ : res_[0]; g.C32 = pre1_[s];          // the residual stream stays fp32
-      fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g, in_use);
+      LnOff ln{};
+      if (!last && !others_read(l - 1)) {
+        const int before = keep ? l - 1 : 0;
+        const float* const mean = l > 0 ? mean2_[before] : mean0_;
+        g.res32 = l > 0 ? pre2_[before] : pre0_; g.ln_mean = mean; g.ln_rstd = (int32_t)((l > 0 ? rstd2_[before] : rstd0_) - mean);
+        ln = l > 0 ? LnOff{off_[l - 1].ln2g, off_[l - 1].ln2b} : LnOff{eg_, eb_};
+      }
+      fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g, in_use, ln);
       LnFwdArgs n1{};
-      n1.x = pre1_[s]; n1.pv = pv; n1.g_off = o.ln1g; n1.b_off = o.ln1b; n1.y = x1_[s]; n1.y32 = res_[1];
-      n1.mean = keep ? mean1_[s] : nullptr; n1.rstd = keep ? rstd1_[s] : nullptr; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
+      n1.x = pre1_[s]; n1.pv = pv; n1.g_off = o.ln1g; n1.b_off = o.ln1b; n1.y = x1_[s]; n1.y32 = make_res ? nullptr : res_[1];
+      n1.mean = mean1_[s]; n1.rstd = rstd1_[s]; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
       n1.ahead = weights_ahead(w, nw, scoring, o.W1, (int64_t)2 * ffn_ * d_, rows, in_use);
       launch_ln_fwd(st, n1);
       g = GemmBf16Args{};
@@ -201,10 +219,11 @@ class EncoderModel : public Model {
       fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g, in_use);
       g = GemmBf16Args{};
       g.res32 = res_[1]; g.C32 = pre2_[s];
-      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g, in_use);
+      if (make_res) { g.res32 = pre1_[s]; g.ln_mean = mean1_[s]; g.ln_rstd = (int32_t)(rstd1_[s] - mean1_[s]); }
+      fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g, in_use, {o.ln1g, o.ln1b});
       LnFwdArgs n2{};
-      n2.x = pre2_[s]; n2.pv = pv; n2.g_off = o.ln2g; n2.b_off = o.ln2b; n2.y = xout; n2.y32 = res_[0];
-      n2.mean = keep ? mean2_[s] : nullptr; n2.rstd = keep ? rstd2_[s] : nullptr; n2.M = nw * rows; n2.d = d_; n2.pass_rows = rows; n2.rows = in_use;
+      n2.x = pre2_[s]; n2.pv = pv; n2.g_off = o.ln2g; n2.b_off = o.ln2b; n2.y = xout; n2.y32 = others_read(l) ? res_[0] : nullptr;
+      n2.mean = mean2_[s]; n2.rstd = rstd2_[s]; n2.M = nw * rows; n2.d = d_; n2.pass_rows = rows; n2.rows = in_use;
       if (l + 1 < L_) n2.ahead = weights_ahead(w, nw, scoring, off_[l + 1].Wqkv, (int64_t)4 * d_ * d_, M, rp.rows);
       launch_ln_fwd(st, n2);
     }

@@ -188,7 +188,7 @@ struct GemmBatch {
   uint64_t choice;                      // k_gemm_rows: four bits for each sixteenth of the rows, the tile to take where as many are in use
   GemmBf16Args p[GEMM_MAX_BATCH];
 };
-enum { EPI_ANY, EPI_C16, EPI_C32, EPI_RES32, EPI_GELU_FWD, EPI_GELU_BWD };
+enum { EPI_ANY, EPI_C16, EPI_C32, EPI_RES32, EPI_GELU_FWD, EPI_GELU_BWD, EPI_LN32 };
 
 template <typename F, int... I>
 __device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
@@ -206,10 +206,13 @@ constexpr int SMALL_TILES = 1 << 20;
 // (two integer divisions, a bounds check for each offset), scalar loads that waited for each other and a branch every dozen of them (a taken one
 // is 35 clk) it took 1.8 to 2.7 us from a workgroup's start to its first load; with the 150 here 0.5 to 0.6 us.  us per launch before / after,
 // hi + lo: 128 x 3072 x 768 7.4 / 6.5, 2048 x 1024 x 1024 11.1 / 10.4, 2048 x 4096 x 1024 30.9 / 29.3.
-template <typename T, bool A_KC, bool B_KC>
+// LN: the residual is a LayerNorm's output and made here of its input; a kernel of its own, because with one more kind of epilogue the others of the 256 x 128 tile kept 52 bytes
+// a lane in scratch, small products took 1% longer, and the compiler gave up on k_gemm_rows.
+template <typename T, bool A_KC, bool B_KC, bool LN = false>
 __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   constexpr int BM = T::BM, BN = T::BN, BK = T::BK, XT = T::XT, YT = T::YT, NSTAGE = T::NSTAGE, WAVES = T::WAVES;
   constexpr bool DUAL = T::DUAL;
+  static_assert(!LN || (DUAL && A_KC && B_KC), "forward hi + lo products");
   constexpr int RD = (DUAL && !B_KC && NSTAGE == 3) || (T::RD == 0 && !(A_KC && B_KC)) ? 0 : T::RD == 0 ? 9 : T::RD;   // see Tile
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   const uint32_t lane = threadIdx.x & 63;
@@ -505,7 +508,8 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   // here); us 8192 x 3072 x 1024 with 256 x 192 tiles NT 76.4 / 73.7, 8192 x 2304 x 768 54.8 / 52.6.  Wave tiles 32 rows tall have two units to a column
   // and write no more than their output; of 128 rows (256 x 256, single-term) the fp32 weight gradients would take 2 to 3 % longer.
   constexpr int PAIRS = YT / 2, UNITS = PAIRS * XT, DEPTH = XT * YT > 16 ? 2 : XT * YT == 16 ? 3 : 4;
-  const bool fast = kind != EPI_ANY && i0 + BM <= rows_of && j0 + BN <= (uint32_t)la.N;
+  const uint32_t wave_row = i0 + wr, wave_col = j0 + wc;
+  const bool fast = kind != EPI_ANY && wave_row + T::WM <= rows_of && wave_col + T::WN <= (uint32_t)la.N;   // this wave's part of the tile is whole
   int g;                    // columns of the lane's values: 4 g, after the exchange pair_col
   uint32_t off32, off16;    // (ldc < 2^24 where they are used)
   auto lane_offsets = [&](uint32_t lane_) {
@@ -521,21 +525,49 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   uint4 sv[DEPTH][2] = {};
   constexpr int NBIAS = ALONG ? PAIRS : 2;
   float4 bias[NBIAS][2] = {};
+  auto at_columns = [&](const float* base, const float* v, int col) {   // four of the bias, or of a gain or shift, perturbed
+    float4 t = *reinterpret_cast<const float4*>(base + col);
+    if (bs != 0.f) {
+      const float4 d = *reinterpret_cast<const float4*>(v + col);
+      t.x = fmaf(bs, d.x, t.x); t.y = fmaf(bs, d.y, t.y); t.z = fmaf(bs, d.z, t.z); t.w = fmaf(bs, d.w, t.w);
+    }
+    return t;
+  };
   auto load_bias = [&](int h) {
     if (bias_at == nullptr) return;
 #pragma unroll
+    for (int u = 0; u < 2; ++u) bias[h % NBIAS][u] = at_columns(bias_at, a.bias_v, wave_col + 32 * h + 16 * u + 4 * g);
+  };
+  // The LayerNorm's output is not stored and read again, but made here of its input: of each row the mean and the reciprocal deviation, of each
+  // column gain and shift; the same operations, so the same bits.
+  const float* ln_mean = nullptr;
+  int ln_rstd = 0, ln_g = 0, ln_b = 0;
+  if constexpr (LN) {
+    ln_mean = a.ln_mean; ln_rstd = a.ln_rstd; ln_g = a.ln_g; ln_b = a.ln_b;
+    asm("" : "+s"(ln_mean), "+s"(ln_rstd), "+s"(ln_g), "+s"(ln_b));
+  }
+  constexpr int LN_XT = LN ? XT : 1, LN_BUF = PAIRS < 2 ? 1 : 2;
+  float row_mean[LN_XT], row_rstd[LN_XT];
+  float4 gain[LN_BUF][2], shift[LN_BUF][2];
+  auto load_ln_columns = [&](int h) {
+#pragma unroll
     for (int u = 0; u < 2; ++u) {
-      float4 t = *reinterpret_cast<const float4*>(bias_at + j0 + wc + 32 * h + 16 * u + 4 * g);
-      if (bs != 0.f) {
-        const float4 v = *reinterpret_cast<const float4*>(a.bias_v + j0 + wc + 32 * h + 16 * u + 4 * g);
-        t.x = fmaf(bs, v.x, t.x); t.y = fmaf(bs, v.y, t.y); t.z = fmaf(bs, v.z, t.z); t.w = fmaf(bs, v.w, t.w);
-      }
-      bias[h % NBIAS][u] = t;
+      const int col = wave_col + 32 * h + 16 * u + 4 * g;
+      gain[h % LN_BUF][u] = at_columns(bias_at + ln_g, a.bias_v + ln_g, col);
+      shift[h % LN_BUF][u] = at_columns(bias_at + ln_b, a.bias_v + ln_b, col);
+      bias[h % LN_BUF][u] = at_columns(bias_at, a.bias_v, col);
     }
+  };
+  auto load_ln = [&]() {
+    if (!fast) return;
+    const uint32_t row = wave_row + (lane & 15);
+#pragma unroll
+    for (int x = 0; x < LN_XT; ++x) { row_mean[x] = ln_mean[row + 16 * x]; row_rstd[x] = ln_mean[ln_rstd + row + 16 * x]; }
+    load_ln_columns(0);
   };
   auto load_side = [&](int unit) {
     uint4 (&v)[2] = sv[unit % DEPTH];
-    if (kind == EPI_RES32) {
+    if (LN || kind == EPI_RES32) {
       const char* const p = reinterpret_cast<const char*>(res32 + of_unit(false, unit));
       v[0] = *reinterpret_cast<const uint4*>(p + off32);
       v[1] = *reinterpret_cast<const uint4*>(p + off32 + 64);
@@ -545,11 +577,13 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   };
   auto load_first = [&]() {
     if (!fast) return;
-    static_for<ALONG ? PAIRS : 1>([&](auto h) { load_bias(h); });
+    if constexpr (!LN) static_for<ALONG ? PAIRS : 1>([&](auto h) { load_bias(h); });
     static_for<DEPTH - 1>([&](auto u) { if constexpr (decltype(u)::value < UNITS) load_side(u); });
   };
   constexpr bool EARLY = XT * YT != 24;   // the 64 x 96 tiles of a wave leave no registers for it
+  constexpr bool LN_EARLY = XT * YT <= 12;   // the larger ones have none for the statistics and gains either
   if (EARLY) { lane_offsets(lane); load_first(); }
+  if constexpr (LN && LN_EARLY) load_ln();
   // the last slab
   {
     if (RD == 0 && iters > 1) {
@@ -570,6 +604,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
     lane_offsets(lane_); load_first();
   }
   if (look_up) __syncthreads();   // the table has come
+  if (wave_row >= rows_of || wave_col >= (uint32_t)la.N) return;
   const unsigned char* const tab = smem_raw + tab_at;
   auto entry = [&](uint32_t offset) { return *reinterpret_cast<const float*>(tab + offset); };
   auto exchange = [](uint2 (&v)[2]) {   // its own inverse
@@ -598,23 +633,33 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
     }
   };
   auto add = [](float (&c)[4], uint4 r) { c[0] += __uint_as_float(r.x); c[1] += __uint_as_float(r.y); c[2] += __uint_as_float(r.z); c[3] += __uint_as_float(r.w); };
+  auto add_ln = [](float (&c)[4], uint4 r, float mu, float rs, float4 gn, float4 sh) {
+    c[0] += fmaf((__uint_as_float(r.x) - mu) * rs, gn.x, sh.x); c[1] += fmaf((__uint_as_float(r.y) - mu) * rs, gn.y, sh.y);
+    c[2] += fmaf((__uint_as_float(r.z) - mu) * rs, gn.z, sh.z); c[3] += fmaf((__uint_as_float(r.w) - mu) * rs, gn.w, sh.w);
+  };
   if (fast) {
     auto of_kind = [&](auto k) {
       constexpr int KIND = k;
+      if constexpr (KIND == EPI_LN32 && !LN_EARLY) load_ln();
       static_for<UNITS>([&](auto unit_) {
-        constexpr bool BF16 = KIND != EPI_C32 && KIND != EPI_RES32;
+        constexpr bool BF16 = KIND != EPI_C32 && KIND != EPI_RES32 && KIND != EPI_LN32;
         constexpr int unit = unit_, x = unit_x(BF16, unit), h = unit_h(BF16, unit);
-        if constexpr (!ALONG && x == 0 && h + 1 < PAIRS) load_bias(h + 1);
-        if constexpr ((KIND == EPI_RES32 || KIND == EPI_GELU_BWD) && unit + DEPTH - 1 < UNITS) load_side(unit + DEPTH - 1);
+        if constexpr (!LN && !ALONG && x == 0 && h + 1 < PAIRS) load_bias(h + 1);
+        if constexpr (KIND == EPI_LN32 && x == 0 && h + 1 < PAIRS) load_ln_columns(h + 1);
+        if constexpr ((KIND == EPI_RES32 || KIND == EPI_LN32 || KIND == EPI_GELU_BWD) && unit + DEPTH - 1 < UNITS) load_side(unit + DEPTH - 1);
         const uint4 (&cur)[2] = sv[unit % DEPTH];
         float c[2][4];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const f32x4 v = acc[x][2 * h + u];
-          const float4 b = bias[h % NBIAS][u];
+          const float4 b = bias[KIND == EPI_LN32 ? h % LN_BUF : h % NBIAS][u];
           c[u][0] = v[0] + b.x; c[u][1] = v[1] + b.y; c[u][2] = v[2] + b.z; c[u][3] = v[3] + b.w;
         }
         if constexpr (KIND == EPI_RES32) { add(c[0], cur[0]); add(c[1], cur[1]); }
+        if constexpr (KIND == EPI_LN32) {
+#pragma unroll
+          for (int u = 0; u < 2; ++u) add_ln(c[u], cur[u], row_mean[x], row_rstd[x], gain[h % LN_BUF][u], shift[h % LN_BUF][u]);
+        }
         if constexpr (KIND == EPI_GELU_FWD) {
           uint2 pk[2] = {packed(c[0]), packed(c[1])};
           gelu(c[0], pk[0]); gelu(c[1], pk[1]);
@@ -628,7 +673,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
           exchange(pk);
           dgelu(c[0], pk[0]); dgelu(c[1], pk[1]);
         }
-        if (KIND == EPI_C32 || KIND == EPI_RES32 || (KIND != EPI_C16 && C32 != nullptr)) {
+        if (KIND == EPI_C32 || KIND == EPI_RES32 || KIND == EPI_LN32 || (KIND != EPI_C16 && C32 != nullptr)) {
           char* const p = reinterpret_cast<char*>(C32 + of_unit(BF16, unit));
           *reinterpret_cast<float4*>(p + off32) = make_float4(c[0][0], c[0][1], c[0][2], c[0][3]);
           *reinterpret_cast<float4*>(p + off32 + 64) = make_float4(c[1][0], c[1][1], c[1][2], c[1][3]);
@@ -639,12 +684,16 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
         }
       });
     };
-    switch (kind) {
-      case EPI_C16: return of_kind(std::integral_constant<int, EPI_C16>{});
-      case EPI_C32: return of_kind(std::integral_constant<int, EPI_C32>{});
-      case EPI_RES32: return of_kind(std::integral_constant<int, EPI_RES32>{});
-      case EPI_GELU_FWD: return of_kind(std::integral_constant<int, EPI_GELU_FWD>{});
-      default: return of_kind(std::integral_constant<int, EPI_GELU_BWD>{});
+    if constexpr (LN) {
+      return of_kind(std::integral_constant<int, EPI_LN32>{});
+    } else {
+      switch (kind) {
+        case EPI_C16: return of_kind(std::integral_constant<int, EPI_C16>{});
+        case EPI_C32: return of_kind(std::integral_constant<int, EPI_C32>{});
+        case EPI_RES32: return of_kind(std::integral_constant<int, EPI_RES32>{});
+        case EPI_GELU_FWD: return of_kind(std::integral_constant<int, EPI_GELU_FWD>{});
+        default: return of_kind(std::integral_constant<int, EPI_GELU_BWD>{});
+      }
     }
   }
   // any combination, any alignment the operands may have, tiles at the edges
@@ -660,14 +709,11 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
       const int64_t at = (int64_t)row * ldc + col;
       float c[4] = {acc[x][2 * h + u][0], acc[x][2 * h + u][1], acc[x][2 * h + u][2], acc[x][2 * h + u][3]};
       if (bias_at != nullptr) {
-        float4 b = *reinterpret_cast<const float4*>(bias_at + col);
-        if (bs != 0.f) {
-          const float4 v = *reinterpret_cast<const float4*>(a.bias_v + col);
-          b.x = fmaf(bs, v.x, b.x); b.y = fmaf(bs, v.y, b.y); b.z = fmaf(bs, v.z, b.z); b.w = fmaf(bs, v.w, b.w);
-        }
+        const float4 b = at_columns(bias_at, a.bias_v, col);
         c[0] += b.x; c[1] += b.y; c[2] += b.z; c[3] += b.w;
       }
-      if (res32 != nullptr) add(c, *reinterpret_cast<const uint4*>(res32 + at));
+      if constexpr (LN) add_ln(c, *reinterpret_cast<const uint4*>(res32 + at), ln_mean[row], ln_mean[ln_rstd + row], at_columns(bias_at + ln_g, a.bias_v + ln_g, col), at_columns(bias_at + ln_b, a.bias_v + ln_b, col));
+      else if (res32 != nullptr) add(c, *reinterpret_cast<const uint4*>(res32 + at));
       if (act == GEMM_ACT_GELU_FWD) {
         const uint2 pk = packed(c);
         if (C16_pre != nullptr) *reinterpret_cast<uint2*>(C16_pre + at) = pk;
@@ -681,15 +727,15 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& batch) {
   });
 }
 
-template <typename T, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) { gemm_tile<T, A_KC, B_KC>(batch); }
+template <typename T, bool A_KC, bool B_KC, bool LN>
+__global__ __launch_bounds__(T::THREADS) void k_gemm_bf16(GemmBatch batch) { gemm_tile<T, A_KC, B_KC, LN>(batch); }
 
 // What a whole tile's epilogue does, where it is one of the usual things on usual alignments.
 int epilogue_kind(const GemmBf16Args& a) {
   if (a.ldc % 8 != 0 || a.ldc >= (1 << 24) || (((uintptr_t)a.C16 | (uintptr_t)a.C16_pre | (uintptr_t)a.aux16) & 15) != 0) return EPI_ANY;
   if ((a.C32 != nullptr) == (a.C16 != nullptr)) return EPI_ANY;
   if (a.act != GEMM_ACT_NONE) return a.res32 != nullptr ? EPI_ANY : a.act == GEMM_ACT_GELU_FWD ? EPI_GELU_FWD : EPI_GELU_BWD;
-  if (a.res32 != nullptr) return a.C32 != nullptr ? EPI_RES32 : EPI_ANY;
+  if (a.res32 != nullptr) return a.C32 == nullptr ? EPI_ANY : a.ln_mean != nullptr ? EPI_LN32 : EPI_RES32;
   return a.C32 != nullptr ? EPI_C32 : EPI_C16;
 }
 
@@ -709,15 +755,15 @@ GemmBatch make_batch(const GemmBf16Args* p, int count, int group, int bm, int bn
   return b;
 }
 
-template <typename T, bool A_KC, bool B_KC>
+template <typename T, bool A_KC, bool B_KC, bool LN = false>
 void launch_tile(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count, int group) {
   static bool configured = false;      // per instantiation: raise the dynamic LDS limit once
   if (!configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16<T, A_KC, B_KC>), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16<T, A_KC, B_KC, LN>), hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
     configured = true;
   }
   const GemmBatch b = make_batch(p, count, group, T::BM, T::BN);
-  launch_kernel(ps, k_gemm_bf16<T, A_KC, B_KC>, 8 * b.tiles_per_xcd, T::THREADS, T::LDS_BYTES, st, b);
+  launch_kernel(ps, k_gemm_bf16<T, A_KC, B_KC, LN>, 8 * b.tiles_per_xcd, T::THREADS, T::LDS_BYTES, st, b);
 }
 
 // Tiles <BM, BN, BK, multiplying waves in M, in N, stages, hi + lo, loading waves, fragments of a piece, fetches (see Tile)>
@@ -750,19 +796,21 @@ typedef Tile<32, 32, 128, 2, 1, 3, true, 2, 0, 1> D10;     // two workgroups per
 typedef Tile<128, 64, 64, 2, 2, 4, true, 4, 0, 1> R5;
 constexpr int ROWS_THREADS = D1::THREADS, ROWS_SHARES = 16;
 static_assert(D2::THREADS <= ROWS_THREADS && D4::THREADS <= ROWS_THREADS && R5::THREADS <= ROWS_THREADS, "waves");
-template <typename T, bool B_KC>
+template <typename T, bool B_KC, bool LN>
 __device__ __forceinline__ void gemm_rows_tile(const GemmBatch& batch) {
-  if (T::THREADS == ROWS_THREADS || (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x) < (uint32_t)T::THREADS) gemm_tile<T, true, B_KC>(batch);
+  if (T::THREADS == ROWS_THREADS || (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x) < (uint32_t)T::THREADS) gemm_tile<T, true, B_KC, LN>(batch);
 }
-template <bool B_KC>
+template <bool B_KC, bool LN>
 __global__ __launch_bounds__(ROWS_THREADS) void k_gemm_rows(GemmBatch batch) {
   const uint32_t in_use = *(const __attribute__((address_space(4))) int32_t*)batch.first.rows;
   const uint32_t share = small_quotient(ROWS_SHARES * in_use - 1, batch.first.M);   // 0 < in_use <= M
   switch ((uint32_t)(batch.choice >> (4 * share)) & 15) {
-    case 1: return gemm_rows_tile<D1, B_KC>(batch);
-    case 2: return gemm_rows_tile<D2, B_KC>(batch);
-    case 4: return gemm_rows_tile<D4, B_KC>(batch);
-    default: return gemm_rows_tile<R5, B_KC>(batch);
+    case 1:
+      if constexpr (!LN) gemm_rows_tile<D1, B_KC, LN>(batch);   // (never chosen with LN)
+      return;
+    case 2: return gemm_rows_tile<D2, B_KC, LN>(batch);
+    case 4: return gemm_rows_tile<D4, B_KC, LN>(batch);
+    default: return gemm_rows_tile<R5, B_KC, LN>(batch);
   }
 }
 
@@ -830,7 +878,7 @@ int pick_tile(const TileCost (&costs)[N], const GemmBf16Args* p, int count, bool
   for (int k = 0; k < count; ++k) deep = deep && p[k].K % 128 == 0 && (!p[k].a_trans || p[k].rows == nullptr);
   int best = 0;
   for (const TileCost& c : costs) {
-    if (c.bk == 128 && !deep) continue;
+    if ((c.bk == 128 && !deep) || (c.id == 11 && p[0].ln_mean != nullptr)) continue;
     double cost = 0.0;
     for (int share = padded ? 1 : 4; share <= 4; ++share) cost += launch_cost(c, p, count, share, 4);
     if (best == 0 || cost < *total) { best = c.id; *total = cost; }
@@ -853,6 +901,7 @@ bool pick_by_rows(const TileCost (&costs)[N], const GemmBf16Args* p, int count, 
     int64_t best_tiles = 0;
     for (const TileCost& c : costs) {
       if (c.id != 11 && c.id != 12 && c.id != 14 && c.id != 15) continue;   // those of k_gemm_rows
+      if (c.id == 11 && p[0].ln_mean != nullptr) continue;   // has no registers for it: 284 bytes a lane in scratch
       int64_t tiles;
       const double cost = launch_cost(c, p, count, share, ROWS_SHARES, &tiles);
       if (best == 0 || cost < best_cost) { best = c.id - 10; best_cost = cost; best_tiles = tiles; }
@@ -877,26 +926,27 @@ int64_t most_tiles_of(const TileCost (&costs)[N], const GemmBf16Args* p, int cou
   return most;
 }
 
-template <bool B_KC>
+template <bool B_KC, bool LN>
 void launch_rows(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count, uint64_t choice, int64_t most_tiles) {
   static bool configured = false;
   constexpr int LDS = std::max({D1::LDS_BYTES, D2::LDS_BYTES, D4::LDS_BYTES, R5::LDS_BYTES});
   if (!configured) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_rows<B_KC>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_rows<B_KC, LN>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     configured = true;
   }
   g_launches[B_KC ? GEMM_ROWS_NT : GEMM_ROWS_NN].fetch_add(1, std::memory_order_relaxed);
   GemmBatch b = make_batch(p, count, g_group, 64, 64);
   b.choice = choice;
   b.tiles_per_xcd = (int)((most_tiles + 7) / 8);
-  launch_kernel(ps, k_gemm_rows<B_KC>, 8 * b.tiles_per_xcd, ROWS_THREADS, LDS, st, b);
+  launch_kernel(ps, k_gemm_rows<B_KC, LN>, 8 * b.tiles_per_xcd, ROWS_THREADS, LDS, st, b);
 }
 
-template <bool A_KC, bool B_KC>
+// LN (here and in the kernels): every problem has a LayerNorm's residual
+template <bool A_KC, bool B_KC, bool LN = false>
 void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int count) {
   const bool dual = p[0].B2 != nullptr;
   int shape = g_force_shape;
-  if (shape >= 11 && !dual) shape = 0;   // hi + lo tiles read B2
+  if ((shape >= 11 && !dual) || (LN && shape <= 11)) shape = 0;   // hi + lo tiles read B2
   for (int k = 0; k < count; ++k)
     if (shape == 20 && (p[k].K % 128 != 0 || (p[k].a_trans && p[k].rows != nullptr))) shape = 0;
   if (shape == 0) {
@@ -907,30 +957,39 @@ void launch_class(ProfScope& ps, hipStream_t st, const GemmBf16Args* p, int coun
     if constexpr (A_KC) {
       uint64_t choice = g_force_rows;
       int64_t tiles;
-      if (choice != 0 && padded && dual) return launch_rows<B_KC>(ps, st, p, count, choice, most_tiles_of(HILO, p, count, choice));
+      for (int share = 0; LN && share < ROWS_SHARES; ++share)
+        if ((choice >> (4 * share) & 15) == 1) choice ^= (uint64_t)(1 ^ 2) << (4 * share);
+      if (choice != 0 && padded && dual) return launch_rows<B_KC, LN>(ps, st, p, count, choice, most_tiles_of(HILO, p, count, choice));
       if (padded && dual && (B_KC ? pick_by_rows(HILO, p, count, total, &choice, &tiles) : pick_by_rows(HILO_NN, p, count, total, &choice, &tiles)))
-        return launch_rows<B_KC>(ps, st, p, count, choice, tiles);
+        return launch_rows<B_KC, LN>(ps, st, p, count, choice, tiles);
     }
   }
   switch (shape) {
-    case 1: launch_tile<S1, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 2: launch_tile<S2, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 3: launch_tile<S3, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 4: launch_tile<S4, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 5: launch_tile<S5, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 6: launch_tile<S6, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 8: launch_tile<S8, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 11: launch_tile<D1, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 12: launch_tile<D2, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 13: launch_tile<D3, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 14: launch_tile<D4, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 15: launch_tile<D5, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 16: launch_tile<D6, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 17: launch_tile<D7, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 18: launch_tile<D8, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 19: launch_tile<D9, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    case 20: launch_tile<D10, A_KC, B_KC>(ps, st, p, count, g_group); break;
-    default: launch_tile<S7, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    case 12: return launch_tile<D2, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 13: return launch_tile<D3, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 14: return launch_tile<D4, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 15: return launch_tile<D5, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 16: return launch_tile<D6, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 17: return launch_tile<D7, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 18: return launch_tile<D8, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 19: return launch_tile<D9, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    case 20: return launch_tile<D10, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+    default: break;
+  }
+  if constexpr (LN) {
+    launch_tile<D2, A_KC, B_KC, LN>(ps, st, p, count, g_group);
+  } else {
+    switch (shape) {
+      case 1: launch_tile<S1, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      case 2: launch_tile<S2, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      case 3: launch_tile<S3, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      case 4: launch_tile<S4, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      case 5: launch_tile<S5, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      case 6: launch_tile<S6, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      case 8: launch_tile<S8, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      case 11: launch_tile<D1, A_KC, B_KC>(ps, st, p, count, g_group); break;
+      default: launch_tile<S7, A_KC, B_KC>(ps, st, p, count, g_group); break;
+    }
   }
 }
 }  // namespace
@@ -958,6 +1017,8 @@ const char* check_gemm_bf16(const GemmBf16Args& a) {
   if (((uintptr_t)a.C16 | (uintptr_t)a.C16_pre | (uintptr_t)a.aux16) & 7) return "bf16 epilogue tensors must be 8-byte aligned";
   if (a.act != GEMM_ACT_NONE && (a.gelu_tab == nullptr || ((uintptr_t)a.gelu_tab & 15) != 0)) return "the GELU epilogues need their 16-byte aligned table";
   if (a.res32 != nullptr && a.act == GEMM_ACT_GELU_BWD) return "a residual and the GELU backward exclude each other";
+  if (a.ln_mean != nullptr && (a.res32 == nullptr || a.bias == nullptr || a.B2 == nullptr || a.a_trans || !a.b_trans)) return "a LayerNorm's residual belongs to a forward hi + lo product with a bias";
+  if (a.ln_mean != nullptr && ((a.ln_g | a.ln_b) & 3) != 0) return "gains and shifts must be 16-byte aligned";
   if (a.lda < (a.a_trans ? a.M : a.K) || a.ldb < (a.b_trans ? a.K : a.N) || a.ldc < a.N) return "leading dimension too small";
   const int64_t abytes = (int64_t)(a.a_trans ? a.K : a.M) * a.lda * 2, bbytes = (int64_t)(a.b_trans ? a.N : a.K) * a.ldb * 2;
   if (abytes >= ((int64_t)1 << 31) || bbytes >= ((int64_t)1 << 31)) return "operands must be smaller than 2 GiB";
@@ -980,8 +1041,8 @@ const char* check_gemm_bf16_batch(const GemmBf16Args* p, int count) {
   if (count < 1 || count > GEMM_MAX_BATCH) return "batch of 1 to 4 problems";
   for (int k = 0; k < count; ++k) {
     if (const char* e = check_gemm_bf16(p[k])) return e;
-    if (p[k].a_trans != p[0].a_trans || p[k].b_trans != p[0].b_trans || (p[k].B2 != nullptr) != (p[0].B2 != nullptr))
-      return "the problems of a batch must share operand storage and the hi + lo form";
+    if (p[k].a_trans != p[0].a_trans || p[k].b_trans != p[0].b_trans || (p[k].B2 != nullptr) != (p[0].B2 != nullptr) || (p[k].ln_mean != nullptr) != (p[0].ln_mean != nullptr))
+      return "the problems of a batch must share operand storage, the hi + lo form and whether a LayerNorm's output is added";
   }
   return nullptr;
 }
@@ -997,7 +1058,8 @@ void launch_gemm_bf16_batch(hipStream_t st, const GemmBf16Args* p, int count) {
   const bool hilo = p[0].B2 != nullptr;
   ProfScope ps(st, p[0].a_trans ? F_GEMM_TN : (p[0].b_trans ? (hilo ? F_GEMM_NT_HILO : F_GEMM_NT) : (hilo ? F_GEMM_NN_HILO : F_GEMM_NN)), flops);
   // a_trans = 0: A is [M][K], contraction contiguous.  b_trans = 1: B is [N][K], contraction contiguous.
-  if (!p[0].a_trans && p[0].b_trans) launch_class<true, true>(ps, st, p, count);
+  if (p[0].ln_mean != nullptr) launch_class<true, true, true>(ps, st, p, count);
+  else if (!p[0].a_trans && p[0].b_trans) launch_class<true, true>(ps, st, p, count);
   else if (!p[0].a_trans && !p[0].b_trans) launch_class<true, false>(ps, st, p, count);
   else if (p[0].a_trans && !p[0].b_trans) launch_class<false, false>(ps, st, p, count);
   else launch_class<false, true>(ps, st, p, count);

@@ -233,6 +233,9 @@ struct GemmBf16Args {
   int64_t ldc;
   const float* bias; const float* bias_v; const float* beps; float bsign;
   const float* res32;
+  // null, or res32 is the input of a LayerNorm whose output is the residual (forward hi + lo products): the mean of each row, 1 / deviation ln_rstd behind it,
+  // and gain and shift of each column ln_g and ln_b from the bias (from bias_v what perturbs them)
+  const float* ln_mean; int32_t ln_rstd, ln_g, ln_b;
   int act; const bf16_t* aux16; bf16_t* C16_pre;
   const float* gelu_tab;   // the GELU epilogues: what launch_gelu_tables() wrote
   float* C32; bf16_t* C16;

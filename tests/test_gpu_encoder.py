@@ -905,6 +905,48 @@ def test_weights_fetched_ahead_of_many_padded_rows(B, dims, kept):
     gpu.close()
 
 
+@pytest.mark.parametrize("B,dims,S,padded", [(88, (3, 192, 3, 320), 64, False), (90, (3, 192, 3, 320), 64, True), (30, (3, 320, 5, 640), 128, False), (29, (4, 320, 5, 640), 128, True),
+                                             (13, (3, 704, 11, 1408), 128, True), (9, (3, 1024, 16, 1024), 128, False), (32, (3, 1024, 16, 2048), 256, False), (33, (2, 640, 10, 1280), 64, True)])
+def test_residual_made_from_the_layernorms_input(B, dims, S, padded):
+    """Beyond 2^20 elements of rows x width the products make the residual themselves, below it the LayerNorm stores it: texts scored alone and in such a batch have the same bits.
+    (33 sequences of 640 and 88 of 192: one pass is on the near or just the far side, the two of a meta step on the far one.)  Widths with tiles cut short, any number of rows in use.
+    The stacked passes, whose gains and shifts are perturbed, against the oracle."""
+    import torch
+    C, d = 3, dims[1]
+    wl = make_workload(3, n_train=B, n_meta=2, dims=dims + (S, 300, C), batch=B, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    x, y = wl.x_train[:B], wl.y_train[:B]
+    lens = np.clip((np.arange(B) * 37) % (2 * S), 1, S).astype(np.int32) if padded else None
+
+    def score(sel):
+        out = [torch.zeros(s, device=gpu.dev) for s in ((len(sel), C), (len(sel),), (len(sel),))]
+        gpu.eval(dev_batch(gpu, x[sel], y[sel], lens=None if lens is None else lens[sel]), *out)
+        return [o.cpu().numpy() for o in out]
+    push_state(orc, gpu)
+    every = score(np.arange(B))
+    for i in (0, 1, B // 2, B - 1):
+        for name, one, all_ in zip(("logits", "losses", "weights"), score(np.array([i])), every):
+            assert np.array_equal(one[0], all_[i]), (name, i)
+    gpu.base_step(dev_batch(gpu, x, y, lens=lens))
+    assert np.array_equal(pull(gpu, "LOSSES")[:B], every[1])
+    if B * S * d < 1500000:   # the oracle's time
+        xo = with_lengths(x, lens) if padded else x
+        for _ in range(3):
+            orc.base_step(xo, y)
+        push_state(orc, gpu)
+        orc.base_step(xo, y)
+        gpu.base_step(dev_batch(gpu, x, y, lens=lens))
+        errs = _group_errors(orc, pull(gpu, "G"), orc.g)
+        assert rel_l2(pull(gpu, "G"), orc.g) < KTOL and all(e < TOL for e in errs.values()), errs
+        push_state(orc, gpu)
+        r = orc.meta_step(xo, y, wl.x_meta[:2], wl.y_meta[:2])
+        gpu.meta_step(dev_batch(gpu, x, y, lens=lens), dev_batch(gpu, wl.x_meta[:2], wl.y_meta[:2]))
+        e = dict(gmeta=rel_l2(pull(gpu, "GMETA"), r["g_meta"]), glam_p=rel_l2(pull(gpu, "GLAM_PLUS"), r["glam_p"]), glam_m=rel_l2(pull(gpu, "GLAM_MINUS"), r["glam_m"]))
+        print(" ".join(f"{k}={v:.2e}" for k, v in e.items()))
+        assert all(v < KTOL for v in e.values()), e
+    gpu.close()
+
+
 @pytest.mark.parametrize("C,d", [(8, 192), (9, 192), (21, 1088)])
 def test_head_of_many_classes_and_features(C, d):
     """The classifier with as many classes as are taken at a time, one more, and three times as many over more features than are:
