@@ -176,7 +176,8 @@ class EncoderModel : public Model {
     // 8 x 384 1316 / 1319, 4096 1740 / 1728, 2048 of 6 x 1024 2780 / 2772; padded, 3072 rows of 6 x 768 2047 / 2000.
     constexpr int64_t MAKE_RES = 1 << 20;
     const bool make_res = w[0].lo != nullptr && (int64_t)nw * M * d_ > MAKE_RES;
-    auto others_read = [&](int l) { return !make_res || l == L_ - 1 || (l == L_ - 2 && sel.n > 0); };   // what leaves layer l (-1: the embeddings)
+    const bool far = eb_ - off_[0].bo > INT32_MAX;   // beyond a product's offsets: two billion embedding weights lie between
+    auto others_read = [&](int l) { return !make_res || l == L_ - 1 || (l == L_ - 2 && sel.n > 0) || (l < 0 && far); };   // what leaves layer l (-1: the embeddings)
     ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};   // flips behind the first pass's rows
     LnFwdArgs e{};
     e.x = nullptr; e.ids = rp.ids ? rp.ids : (const int32_t*)b.x; e.src = rp.src; e.rows = rp.rows; e.pass_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep || !others_read(-1) ? pre0_ : nullptr;
