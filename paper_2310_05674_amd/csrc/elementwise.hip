@@ -203,20 +203,25 @@ __device__ __forceinline__ void finish_eps(double sum_sq, float alpha, float* __
 }
 
 // U vectors a thread; a block has EW_TRIP of them a trip either way, so that the partials, and the tickets that the blocks of a launch take one
-// after the other, are as many.
+// after the other, are as many.  The squares are added in one order either way too: with a vector a thread the first EW_THREADS threads add up
+// those of the others, out of LDS.
 template <int U>
 __global__ __launch_bounds__(EW_TRIP / U) void k_adapt_norm(const float* __restrict__ g, const float* __restrict__ m,
                                                             const float* __restrict__ v, const float* __restrict__ gmeta,
                                                             float* __restrict__ vdir, double* __restrict__ partial,
                                                             int64_t n, AdaptArgs a, EpsFinish fin) {
   constexpr int THREADS = EW_TRIP / U;
+  constexpr bool SHARED = U < EW_U;
   __shared__ float red[16];
   __shared__ double dred[THREADS];
   __shared__ int s_last;
+  __shared__ f4 s_o[SHARED ? EW_TRIP : 1];
   if (a.dev != nullptr) { a.lr_c1_c2 = a.dev[2]; a.c2 = a.dev[3]; }
   const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
   float acc = 0.f;
-  for (int64_t base = (int64_t)blockIdx.x * EW_TRIP + threadIdx.x; base < nv; base += trip) {
+  auto add_squares = [&](f4 o) { acc = fmaf(o.x, o.x, acc); acc = fmaf(o.y, o.y, acc); acc = fmaf(o.z, o.z, acc); acc = fmaf(o.w, o.w, acc); };
+  for (int64_t first = (int64_t)blockIdx.x * EW_TRIP; first < nv; first += trip) {
+    const int64_t base = first + threadIdx.x;
     f4 G[U], M[U], V[U], Q[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -240,8 +245,18 @@ __global__ __launch_bounds__(EW_TRIP / U) void k_adapt_norm(const float* __restr
           o = a.scalar * Q[u];
         }
         st_nt(vdir, j, o);
-        acc = fmaf(o.x, o.x, acc); acc = fmaf(o.y, o.y, acc); acc = fmaf(o.z, o.z, acc); acc = fmaf(o.w, o.w, acc);
+        if (SHARED) s_o[u * THREADS + threadIdx.x] = o;
+        else add_squares(o);
       }
+    }
+    if (SHARED) {
+      __syncthreads();
+      if (threadIdx.x < EW_THREADS) {
+#pragma unroll
+        for (int u = 0; u < EW_U; ++u)
+          if (base + u * EW_THREADS < nv) add_squares(s_o[u * EW_THREADS + threadIdx.x]);
+      }
+      __syncthreads();
     }
   }
   const int64_t k = nv * EW_VEC + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -10,6 +10,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float LN_EPS = 1e-5f;
 
@@ -319,18 +320,16 @@ __global__ __launch_bounds__(256) void k_colsum_partial_bf16(ColsumMulti m) {
 // Sequence length S = 32 NT (NT = 2, 4 or 8 tiles of 32 positions), head width 64.
 constexpr int AD = 64;  // head width
 
-// eight values of an accumulator from entry r on, as an operand
-__device__ __forceinline__ bf16x8 pack8(const f32x16& a, int r) {
-  const uint4 v = make_uint4(pack_bf16x2(a[r], a[r + 1]), pack_bf16x2(a[r + 2], a[r + 3]), pack_bf16x2(a[r + 4], a[r + 5]), pack_bf16x2(a[r + 6], a[r + 7]));
-  return __builtin_bit_cast(bf16x8, v);
+// four values as an operand
+__device__ __forceinline__ s16x4 pack4(float a, float b, float c, float d) {
+  return __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d)));
 }
 
 // A [ROWS x 64] bf16 matrix of a head (row stride ld in memory) is staged in LDS in dense rows of 128 bytes, the 16-byte chunk
 // index of row r XORed with chunk_swz(r).  It is read in two ways, both without bank conflicts:
 //   rows_operand: lane l takes 8 consecutive values of row base + l % 32 (sixteen rows at one chunk: sixteen 16-byte slots)
-//   ld_transposed: lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] and the same of k0 + 8 through ds_read_b64_tr_b16 (the
-//     four rows one read touches lie in four different 64-byte windows).  These are, in this order, the rows that a lane of a 32 x 32 product tile
-//     holds in eight neighbouring entries, so that those are the other operand of a 32x32x16 MFMA as they are
+//   ld_transposed: for the 32x32x8 MFMA, lane l gets S[k0 + 4 (l / 32) + 0..3][e32 + l % 32] through ds_read_b64_tr_b16 (the
+//     four rows one read touches lie in four different 64-byte windows)
 // The matrices that a tile's products walk over come from there: fetched from global memory between those dependent products,
 // each operand costs the latency of the L2 or beyond (S = 128, 384 heads: backward 37.6 us that way, 23.6 from LDS).  What a wave
 // holds for a whole tile -- the queries of the forward pass, the own rows of the backward pass -- is read by one wave only, once
@@ -369,15 +368,9 @@ __device__ __forceinline__ RowsOperand rows_operand(const bf16_t* __restrict__ S
   for (int ks = 0; ks < 4; ++ks) o.k[ks] = *reinterpret_cast<const bf16x8*>(S + row * AD + ((2 * ks + (lane >> 5)) ^ s) * 8);
   return o;
 }
-__device__ __forceinline__ bf16x8 ld_transposed(const bf16_t* __restrict__ S, int e32, int k0, int lane) {
-  const int g = lane >> 4, j = lane & 15, e = e32 + 16 * (g & 1) + 4 * (j & 3);
-  union { bf16x8 v; s16x4 h[2]; } u;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = k0 + 8 * i + 4 * (g >> 1) + (j >> 2);
-    u.h[i] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(S + row * AD + ((e >> 3) ^ chunk_swz(row)) * 8 + (e & 7)));
-  }
-  return u.v;
+__device__ __forceinline__ s16x4 ld_transposed(const bf16_t* __restrict__ S, int e32, int k0, int lane) {
+  const int g = lane >> 4, j = lane & 15, row = k0 + 4 * (g >> 1) + (j >> 2), e = e32 + 16 * (g & 1) + 4 * (j & 3);
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(S + row * AD + ((e >> 3) ^ chunk_swz(row)) * 8 + (e & 7)));
 }
 
 // X^T-style product tile: acc[32 x 32] = sum_e R[row][e] * C[column][e].  Result lane layout: column = cbase + l%32,
@@ -395,7 +388,7 @@ __device__ __forceinline__ f32x16 rows_dot_rows(const RowsOperand& R, const Rows
 
 // A tile g^T[64 features][own] to row `row`: lanes 32 apart, which have neighbouring halves of eight features, exchange them first, so that
 // each stores 16 bytes of one eight.
-__device__ __forceinline__ void store_row(const f32x16 (&g)[2], float scale, bf16_t* __restrict__ row, int lane) {
+__device__ __forceinline__ void store_row(const f32x16 (&g)[2], bf16_t* __restrict__ row, int lane) {
 #pragma unroll
   for (int et = 0; et < 2; ++et)
 #pragma unroll
@@ -404,17 +397,18 @@ __device__ __forceinline__ void store_row(const f32x16 (&g)[2], float scale, bf1
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) p[i][k] = pack_bf16x2(g[et][4 * (c + i) + 2 * k] * scale, g[et][4 * (c + i) + 2 * k + 1] * scale);
+        for (int k = 0; k < 2; ++k) p[i][k] = pack_bf16x2(g[et][4 * (c + i) + 2 * k], g[et][4 * (c + i) + 2 * k + 1]);
       const u32x2 x = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false), y = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
       *reinterpret_cast<uint4*>(row + 32 * et + 8 * (c + (lane >> 5))) = make_uint4(x[0], y[0], x[1], y[1]);
     }
 }
 
-// exp(x / 8 - m) as 2^(x c - m log2 e) with one fused multiply-add: fewer roundings than product, difference and product
+// exp(x / 8 - m).  The difference comes before the factor of 2^x: with that folded into one multiply-add the rounding of m log2 e, which
+// grows with the scores, stays in the result, and from 10^10 on the largest score's own weight is 0 or infinite.
 // (A score of NO_WEIGHT gives 0: key 0 of a sequence is always real.  It is put in place of scores and not 0 in place of the result, around
 // which the compiler makes a branch.)
-constexpr float LOG2E = 1.44269504088896f, SCORE_LOG2E = 0.125f * LOG2E, NO_WEIGHT = -3.0e38f;
-__device__ __forceinline__ float exp_score(float x, float m_log2e) { return __builtin_amdgcn_exp2f(fmaf(x, SCORE_LOG2E, -m_log2e)); }
+constexpr float NO_WEIGHT = -__builtin_inff();
+__device__ __forceinline__ float exp_score(float x, float m) { return __expf(fmaf(x, 0.125f, -m)); }
 
 // The rows of sequence b, of which `kept` are there, and its real tokens (keys at positions beyond get no weight).
 struct SeqRows { int row0, kept, len; };
@@ -434,10 +428,12 @@ __device__ __forceinline__ void zero_tail(const RowPlan& plan, int B, bf16_t* __
 // Forward.  A wave owns a tile of 32 queries (S = 64: two of the four waves only stage).  S^T[key][q] tiles leave each lane
 // with one query column, so the softmax over keys is an in-lane reduction plus one exchange between the halves, and the
 // probability tile is already an operand of the MFMA for O^T[e][q] = sum_key V^T[e][key] P^T[key][q].
-// Bound by memory where the heads fill the chip (1024 heads of 128 positions, 67 MB: 21.3 -> 15.5 us, 4.3 TB/s) and by the chain of a tile where
-// they do not (12 heads 9.2 -> 5.8, 384 10.3 -> 8.0, 228 of 256 positions 14.6 -> 10.7).  What shortened it: no load waits for another, a
-// score takes seven vector instructions where it took eleven, and 32x32x16 products instead of 32x32x8 ones at half the rate; 128 registers let
-// four workgroups share a CU.
+// Bound by memory where the heads fill the chip (1024 heads of 128 positions, 67 MB: 22.9 -> 16.2 us, 4.1 TB/s of the 5.9 of a plain copy) and by the
+// chain of a tile where they do not (12 padded heads 9.1 -> 6.2, 384 10.7 -> 8.4, 228 padded of 256 positions 14.9 -> 11.9).  What shortened it: no load
+// waits for another, masks without branches, stores of 16 bytes, and 128 registers, which let four workgroups share a CU.
+// A probability is divided by the row's sum and then rounded to bf16, and a tile's products are added eight keys at a time.  (Divided after the product, by
+// the sum of the rounded ones, with 32x32x16 products and one multiply-add for a score, the kernels are 3% faster and the hypergradients of
+// deep encoders others: 2% to 7% in the worst of a dozen, most 0.1%.)
 // With a loop over the tiles of a wave, even one that never turns, the 16 NT comparisons of keys with the length are kept as lane
 // masks across it, hundreds of scalar registers of which most spill.
 template <int NT> struct AttnFwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES, PER_SIMD = NT < 8 ? 4 : 2; };
@@ -482,16 +478,16 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k
       mx = fmaxf(mx, s[kt][r]);
     }
   mx = join32(mx, [](float a, float b) { return fmaxf(a, b); });
-  const float m2 = mx * SCORE_LOG2E;
+  mx *= 0.125f;
   float sum = 0.f;
 #pragma unroll
   for (int kt = 0; kt < NT; ++kt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { s[kt][r] = exp_score(s[kt][r], m2); sum += s[kt][r]; }
-  // The probabilities enter the product before they are divided by their sum, the result after it: half as many divisions, and beside the sum.  What
-  // it is divided by is the sum of the rounded ones, so that the weights of a row add up to one and what the values have in common comes through unrounded.
+    for (int r = 0; r < 16; ++r) { s[kt][r] = exp_score(s[kt][r], mx); sum += s[kt][r]; }
+  sum = join32(sum, [](float a, float b) { return a + b; });
+  const float inv = 1.f / sum;
+  if (lane < 32 && lse != nullptr) lse[((int64_t)b * heads + h) * S + 32 * qt + lane] = mx + __logf(sum);
   f32x16 o[2];
-  float weight = 0.f;
 #pragma unroll
   for (int et = 0; et < 2; ++et)
 #pragma unroll
@@ -500,19 +496,14 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k
   for (int kt = 0; kt < NT; ++kt) {
     if (kt >= nk) break;
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const bf16x8 p = pack8(s[kt], 8 * c);
+    for (int c = 0; c < 4; ++c) {
+      const s16x4 p = pack4(s[kt][4 * c] * inv, s[kt][4 * c + 1] * inv, s[kt][4 * c + 2] * inv, s[kt][4 * c + 3] * inv);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) weight += (float)p[e];
-#pragma unroll
-      for (int et = 0; et < 2; ++et) o[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_transposed(Vs, 32 * et, 32 * kt + 16 * c, lane), p, o[et], 0, 0, 0);
+      for (int et = 0; et < 2; ++et) o[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(Vs, 32 * et, 32 * kt + 8 * c, lane), p, o[et], 0, 0, 0);
     }
   }
-  sum = join32(sum, [](float a, float b) { return a + b; });
-  if (lane < 32 && lse != nullptr) lse[((int64_t)b * heads + h) * S + 32 * qt + lane] = mx * 0.125f + __logf(sum);
-  weight = join32(weight, [](float a, float b) { return a + b; });
   if (PADDED && 32 * qt + (lane & 31) >= kept) return;
-  store_row(o, 1.f / weight, out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD, lane);
+  store_row(o, out + ((int64_t)sr.row0 + 32 * qt + (lane & 31)) * d + h * AD, lane);
 }
 
 // Backward.  Probabilities are recomputed from q, k and the saved log-sum-exp; a wave owns 32 queries or keys at a time.
@@ -525,8 +516,8 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k
 // exponentials, product) and by the requests for the rows it stages and holds.
 //   Three parts: the scores are formed three times instead of twice, but 3 to 4 workgroups share a CU (35 KB of LDS at S = 128, at most
 //   128 registers; 2 of eight waves at S = 256, with 68 KB) where one that formed all three, with 64 KB, had it alone.
-//   (The times of these two paragraphs are of kernels with 32x32x8 products, whose masked forms branched around each exponential and each piece that
-//   was staged: beside the weight gradients, 384 heads of 128 positions 20.7 -> 16.4 us, padded 21.8 -> 14.1, 228 padded of 256 27.9 -> 20.9.)
+//   (The times of these two paragraphs are of kernels whose masked forms branched around each exponential and each piece that was staged, and
+//   requested the pieces one by one: 384 heads of 128 positions 21.7 -> 18.0 us, padded 21.9 -> 14.6, 256 heads 16.6 -> 13.5, 228 padded of 256 28.8 -> 21.7.)
 //   Two parts: a round of three workgroups to a CU instead of four, with a longer chain each (12 heads of S = 128: 9.8 us against
 //   6.8), so only once there are more heads than CUs: S = 128, 384 heads 18.6 us against 19.1 and, padded, 17.5 against 20.7;
 //   1024 heads 50.3 against 53.3, padded 36.7 against 39.1.  256 heads 13.7 against 12.2, 128 10.8 against 8.6.  At S = 64 the two are
@@ -545,7 +536,7 @@ __global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const 
   __shared__ __attribute__((aligned(16))) bf16_t s_r[S * AD];   // dQ: K; dK and dV: Q
   __shared__ __attribute__((aligned(16))) bf16_t s_t[S * AD];   // dQ: V; dK and dV: dO
   __shared__ __attribute__((aligned(16))) float s_D[S], s_lse[S];
-  const int h = blockIdx.x, b = blockIdx.y, part = blockIdx.z, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int h = blockIdx.x, b = blockIdx.y, part = blockIdx.z, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ld = 3 * d;
   const SeqRows sr = seq_rows<PADDED>(lens, plan, 0, b, B, S);
   const int len = sr.len, kept = sr.kept, nk = PADDED ? (len + 31) / 32 : NT, nq = PADDED ? (kept + 31) / 32 : NT;
@@ -591,7 +582,7 @@ __global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const 
     }
     D += __shfl_xor(D, 1, 64);
   }
-  if (dhalf == 0) { s_D[dq] = D * 0.125f; s_lse[dq] = dlse * LOG2E; }   // of rows that are not there: not used
+  if (dhalf == 0) { s_D[dq] = D * 0.125f; s_lse[dq] = dlse; }   // of rows that are not there: not used
   __syncthreads();
 
   if (wave >= nq) return;                                          // a wave owns a tile of queries (dQ) or keys
@@ -605,22 +596,15 @@ __global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const 
   // g^T[e][own] += sum over the 32 rows of `tile` of T^T[e][row] w[row][own]
   auto accumulate = [&](f32x16 (&g)[2], const bf16_t* T, int tile, const f32x16& w) {
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const bf16x8 wb = pack8(w, 8 * c);
+    for (int c = 0; c < 4; ++c) {
+      const s16x4 wb = pack4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]);
 #pragma unroll
       for (int et = 0; et < 2; ++et)
-        g[et] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ld_transposed(T, 32 * et, 32 * tile + 16 * c, lane), wb, g[et], 0, 0, 0);
+        g[et] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ld_transposed(T, 32 * et, 32 * tile + 8 * c, lane), wb, g[et], 0, 0, 0);
     }
   };
-  auto of_queries = [&](const float* x, int qt) {   // for the rows of a lane in a tile of queries
-    f32x16 v;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float4 t = *reinterpret_cast<const float4*>(x + 32 * qt + own_row(lane) + 8 * c);
-      v[4 * c] = t.x; v[4 * c + 1] = t.y; v[4 * c + 2] = t.z; v[4 * c + 3] = t.w;
-    }
-    return v;
-  };
+  // of a lane's rows 8 c .. 8 c + 3 in a tile of queries (four at a time: all sixteen of both values took registers that there were not)
+  auto of_queries = [&](const float* x, int qt, int c) { return *reinterpret_cast<const f32x4*>(x + 32 * qt + own_row(lane) + 8 * c); };
   auto there = [&](int r, int qt) { return !PADDED || tile_row(r) < kept - own_row(lane) - 32 * qt; };
   if (part == DQ) {
     const float lq = s_lse[col], Dq = s_D[col];
@@ -642,9 +626,12 @@ __global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const 
 #pragma unroll 1
       for (int qt = 0; qt < nq; ++qt) {
         f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);
-        const f32x16 l = of_queries(s_lse, qt);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) st[r] = exp_score(there(r, qt) ? st[r] : NO_WEIGHT, l[r]);
+        for (int c = 0; c < 4; ++c) {
+          const f32x4 l = of_queries(s_lse, qt, c);
+#pragma unroll
+          for (int r = 4 * c; r < 4 * c + 4; ++r) st[r] = exp_score(there(r, qt) ? st[r] : NO_WEIGHT, l[r & 3]);
+        }
         accumulate(g, s_t, qt, st);
       }
     }
@@ -654,11 +641,14 @@ __global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const 
     for (int qt = 0; qt < nq; ++qt) {
       f32x16 st = rows_dot_rows(rows_operand(s_r, 32 * qt, lane), kop);          // S[q][key]
       f32x16 dp = rows_dot_rows(rows_operand(s_t, 32 * qt, lane), vop);
-      const f32x16 l = of_queries(s_lse, qt), D8 = of_queries(s_D, qt);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        st[r] = exp_score(there(r, qt) ? st[r] : NO_WEIGHT, l[r]);               // P
-        dp[r] = st[r] * fmaf(dp[r], 0.125f, -D8[r]);                             // dS
+      for (int c = 0; c < 4; ++c) {
+        const f32x4 l = of_queries(s_lse, qt, c), D8 = of_queries(s_D, qt, c);
+#pragma unroll
+        for (int r = 4 * c; r < 4 * c + 4; ++r) {
+          st[r] = exp_score(there(r, qt) ? st[r] : NO_WEIGHT, l[r & 3]);         // P
+          dp[r] = st[r] * fmaf(dp[r], 0.125f, -D8[r & 3]);                       // dS
+        }
       }
       if constexpr (PARTS == 2) accumulate(gv, s_t, qt, st);
       accumulate(g, s_r, qt, dp);
@@ -672,7 +662,7 @@ __global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const 
   }
   if (PADDED && col >= kept) return;
   auto store = [&](const f32x16 (&g)[2], int to) {   // to: where the result goes among the columns of dqkv
-    store_row(g, 1.f, dqkv + ((int64_t)sr.row0 + col) * ld + to + h * AD, lane);
+    store_row(g, dqkv + ((int64_t)sr.row0 + col) * ld + to + h * AD, lane);
   };
   store(g, part == DQ ? 0 : (part == DK ? d : 2 * d));
   if (PARTS == 2 && part != DQ) store(gv, 2 * d);

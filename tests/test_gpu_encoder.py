@@ -603,6 +603,54 @@ def test_attention_backward_on_both_sides_of_its_parts(B, padded):
     gpu.close()
 
 
+def _golden_encoders():
+    import importlib.util
+    import json
+    import os
+    spec = importlib.util.spec_from_file_location("make_encoder_bits", os.path.join(os.path.dirname(__file__), "golden", "make_encoder_bits.py"))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod, json.load(open(mod.FILE)) if os.path.exists(mod.FILE) else {}
+
+
+GOLDEN, GOLDEN_BITS = _golden_encoders()
+
+
+@pytest.mark.parametrize("case", GOLDEN.CASES, ids=GOLDEN.name_of)
+def test_small_encoders_keep_their_bits(case):
+    """Every output of a scored batch, a base and a meta step has the recorded bits: roundings and the order of sums have not changed anywhere on the way."""
+    want, got = GOLDEN_BITS[GOLDEN.name_of(case)], GOLDEN.encoder_bits(case)
+    assert got == want, {k: (got[k], want[k]) for k in want if got[k] != want[k]}
+
+
+@pytest.mark.parametrize("S,padded", [(64, False), (64, True), (128, False), (128, True), (256, False), (256, True)])
+def test_attention_with_scores_of_ten_to_the_twelfth(S, padded):
+    """Wq = Wk = 2^17 I: every query takes its own key's value alone.  The largest score's weight is one however large it is, so logits and
+    the gradients behind the scores are those of the oracle, and nothing is infinite.  (The scores' own gradients are differences that vanish.)"""
+    dims = (1, 192, 3, 320, S, 300, 3)
+    wl = make_workload(3, n_train=6, n_meta=2, dims=dims, batch=6, meta_batch=2)
+    orc, gpu = make_pair(wl, init_theta(wl, 0.02), init_lambda(wl), base_lr=1e-3)
+    off, shape = orc.model.slices["l0.Wqkv"]
+    W = orc.theta[off:off + int(np.prod(shape))].reshape(shape)
+    W[:192], W[192:384] = 2.0 ** 17 * np.eye(192), 2.0 ** 17 * np.eye(192)
+    push_state(orc, gpu)
+    x, y = wl.x_train[:6], wl.y_train[:6]
+    lens = np.array([1, S, S // 2 + 3, 17, S - 1, 33], dtype=np.int32) if padded else None
+    xo = with_lengths(x, lens) if padded else x
+    import torch
+    out = [torch.zeros(s, device=gpu.dev) for s in ((6, 3), (6,), (6,))]
+    gpu.eval(dev_batch(gpu, x, y, lens=lens), *out)
+    for got, want in zip(out, orc.evaluate(xo, y)):
+        assert rel_l2(got.cpu().numpy(), want) < KTOL
+    orc.base_step(xo, y)
+    gpu.base_step(dev_batch(gpu, x, y, lens=lens))
+    g = pull(gpu, "G")
+    assert np.all(np.isfinite(g))
+    errs = _group_errors(orc, g, orc.g)
+    assert all(errs[k] < TOL for k in ("l0.Wo", "l0.W1", "l0.W2", "Wc")), errs
+    gpu.close()
+
+
 def test_out_of_range_ids_and_labels_are_clamped():
     """Token ids outside [0, V) and labels outside [0, C) are clamped on the device by every kernel that indexes with
     them (embedding gather, token-gradient scatter, per-sample stage): a batch carrying such values gives the bits of

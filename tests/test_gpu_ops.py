@@ -84,6 +84,26 @@ def test_adapt_norm_launch_forms(n):
     test_adapt_norm_kernel(n)
 
 
+@pytest.mark.parametrize("n", [4100, 8192, 269324, 2 ** 20 - 4, 2 ** 20])
+def test_adapt_norm_adds_in_one_order(n):
+    """The norm of n elements, a multiple of a vector's four, has the bits of the norm of the same elements and zeros behind them, which another launch form takes."""
+    from paper_2310_05674_amd import binding as B
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    many = 2 ** 20 + 8192
+    for seed in range(4):
+        x = [torch.zeros(many, device=DEV) for _ in range(4)]
+        for k, scale in enumerate((1.0, 0.3, 1.0, 1.0)):
+            x[k][:n] = torch.randn(n, device=DEV, generator=gen) * scale
+        x[2].abs_().add_(0.1)   # (an element with gmeta = 0 adds 0 whatever the moments are)
+        scal = []
+        for m in (n, many):
+            out, partial = torch.empty(m, device=DEV), torch.zeros(65536, dtype=torch.float64, device=DEV)
+            s, status = torch.zeros(4, device=DEV), torch.zeros(1, dtype=torch.int64, device=DEV)
+            B.op_adapt_norm(*(t[:m] for t in x), out, partial, 7, 1e-3, 0.9, 0.999, 1e-8, 1.0, s, status)
+            scal.append((s.cpu(), partial[:(n + 4095) // 4096].cpu()))
+        assert torch.equal(scal[0][1], scal[1][1]) and torch.equal(scal[0][0], scal[1][0])
+
+
 def test_adapt_norm_degenerate():
     from paper_2310_05674_amd import binding as B
     n = 1000
@@ -198,6 +218,30 @@ def test_gemm_bf16_tile_edges(M, N, K, a_trans, b_trans, split):
         first = got if first is None else first
         assert rel_l2(got, want) < 1e-5 and np.array_equal(got, first), shape
     L.sama_dev_gemm_shape(ctypes.c_int32(0))
+
+
+@pytest.mark.parametrize("b_trans", [True, False])
+@pytest.mark.parametrize("M,N,K", [(264, 200, 128), (136, 392, 384)])
+def test_hi_lo_products_add_sixteen_at_a_time(M, N, K, b_trans):
+    """The order of a hi + lo product's sums, with every tile: 16 products of hi, those of lo with the same 16 values of A, the next 16 of hi.  That is the
+    single-term product of the operands written out in this order, to the bit.  (hi and lo of one size, so that the order shows.)"""
+    import ctypes
+    from paper_2310_05674_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    A, hi, lo = (torch.randn(n, K, device=DEV, generator=g).to(torch.bfloat16) for n in (M, N, N))
+    stored = lambda x: x if b_trans else x.t().contiguous()
+    sixteens = lambda x, y: torch.stack([x.view(-1, K // 16, 16), y.view(-1, K // 16, 16)], 2).reshape(-1, 2 * K).contiguous()
+    want = torch.empty(M, N, device=DEV)
+    B.op_gemm_bf16(sixteens(A, A), stored(sixteens(hi, lo)), b_trans=b_trans, out32=want)
+    L = B.load_library()
+    try:
+        for shape in (0,) + tuple(range(11, 21)):
+            L.sama_dev_gemm_shape(ctypes.c_int32(shape))
+            got = torch.full((M, N), float("nan"), device=DEV)
+            B.op_gemm_bf16(A, stored(hi), b_trans=b_trans, B2=stored(lo), out32=got)
+            assert torch.equal(got, want), shape
+    finally:
+        L.sama_dev_gemm_shape(ctypes.c_int32(0))
 
 
 @pytest.mark.parametrize("M,N", [(256, 192), (264, 200), (512, 384)])
