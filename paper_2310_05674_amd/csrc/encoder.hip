@@ -60,14 +60,14 @@ class EncoderModel : public Model {
     for (int l = 0; l < L_; ++l) {
       const size_t R = (l == 0 ? 2 : 1) * M;
       qkv_[l] = ws.take<bf16_t>(R * 3 * d_); lse_[l] = ws.take<float>((size_t)max_b * heads_ * S_);
-      ao_[l] = ws.take<bf16_t>(R * d_); pre1_[l] = ws.take<float>(R * d_); mean1_[l] = ws.take<float>(R); rstd1_[l] = ws.take<float>(R);
+      ao_[l] = ws.take<bf16_t>(R * d_); pre1_[l] = ws.take<float>(R * d_); mean1_[l] = ws.take<float>(M); rstd1_[l] = ws.take<float>(M);
       x1_[l] = ws.take<bf16_t>(R * d_); fpre_[l] = ws.take<bf16_t>(R * ffn_); fact_[l] = ws.take<bf16_t>(R * ffn_);
-      pre2_[l] = ws.take<float>(R * d_); mean2_[l] = ws.take<float>(R); rstd2_[l] = ws.take<float>(R);
+      pre2_[l] = ws.take<float>(R * d_); mean2_[l] = ws.take<float>(M); rstd2_[l] = ws.take<float>(M);
     }
     gelu_tab_ = (float*)ws.take<char>(gelu_table_bytes());
     plan_.start = ws.take<int32_t>(MAX_SEQ + 1); plan_.rows = ws.take<int32_t>(1); plan_.ids = ws.take<int32_t>(M); plan_.src = ws.take<int32_t>(M);
     plan_.group = ws.take<int32_t>(M / ROW_GROUP);
-    pre0_ = ws.take<float>(2 * M * d_); mean0_ = ws.take<float>(2 * M); rstd0_ = ws.take<float>(2 * M);
+    pre0_ = ws.take<float>(M * d_); mean0_ = ws.take<float>(M); rstd0_ = ws.take<float>(M);
     dX_[0] = ws.take<float>(M * d_); dX_[1] = ws.take<float>(M * d_);
     res_[0] = ws.take<float>(2 * M * d_); res_[1] = ws.take<float>(2 * M * d_);
     ds32_ = ws.take<float>(M * d_); do_ = ws.take<bf16_t>(M * d_);
@@ -95,6 +95,8 @@ class EncoderModel : public Model {
   void prepare(hipStream_t st) override { launch_gelu_tables(st, gelu_tab_); }
 
   struct LnOff { int64_t g, b; };   // gain and shift of a LayerNorm inside theta
+  struct RowStats { float *mean, *rstd; };
+  struct LnInput { const float* x; RowStats st; LnOff off; };   // what a LayerNorm's output is made of
   // One linear layer of `nw` stacked passes (pass k owns rows [k M, (k + 1) M) of every activation): the same
   // epilogue `e` (its pointers are those of pass 0) for each pass, with that pass's weights, those of the LayerNorm `ln` where the residual is its output.
   void fwd_linear(hipStream_t st, const PassWeights* w, int nw, const bf16_t* A, int K, int64_t woff, int N, int64_t boff, int M,
@@ -178,10 +180,15 @@ class EncoderModel : public Model {
     const bool make_res = w[0].lo != nullptr && (int64_t)nw * M * d_ > MAKE_RES;
     const bool far = eb_ - off_[0].bo > INT32_MAX;   // beyond a product's offsets: two billion embedding weights lie between
     auto others_read = [&](int l) { return !make_res || l == L_ - 1 || (l == L_ - 2 && sel.n > 0) || (l < 0 && far); };   // what leaves layer l (-1: the embeddings)
+    // A pass that is not kept needs the input and the statistics of a LayerNorm until that product only: they pass through memory that
+    // nobody reads then, the embeddings through that of the residual, statistics (the embeddings' and a layer's last ones in turn) through that of the backward pass.
+    auto passing = [&](int k) { return make_res ? RowStats{dX_[0] + (int64_t)4 * k * M, dX_[0] + (int64_t)(4 * k + 2) * M} : RowStats{nullptr, nullptr}; };
+    float* const emb = keep ? pre0_ : res_[0];
+    LnInput before{emb, keep ? RowStats{mean0_, rstd0_} : passing(0), {eg_, eb_}};   // of what comes into the layer
     ParamView pv{w[0].theta, w[0].vdir, w[0].eps_ptr, w[0].sign, nw == 2 ? M : 0};   // flips behind the first pass's rows
     LnFwdArgs e{};
-    e.x = nullptr; e.ids = rp.ids ? rp.ids : (const int32_t*)b.x; e.src = rp.src; e.rows = rp.rows; e.pass_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep || !others_read(-1) ? pre0_ : nullptr;
-    e.pv = pv; e.g_off = eg_; e.b_off = eb_; e.y = X_[0]; e.y32 = others_read(-1) ? res_[0] : nullptr; e.mean = mean0_; e.rstd = rstd0_;
+    e.x = nullptr; e.ids = rp.ids ? rp.ids : (const int32_t*)b.x; e.src = rp.src; e.rows = rp.rows; e.pass_rows = M; e.S = S_; e.V = V_; e.tok_off = tok_; e.pos_off = pos_; e.x_out = keep || !others_read(-1) ? emb : nullptr;
+    e.pv = pv; e.g_off = eg_; e.b_off = eb_; e.y = X_[0]; e.y32 = others_read(-1) ? res_[0] : nullptr; e.mean = before.st.mean; e.rstd = before.st.rstd;
     e.M = nw * M; e.d = d_; e.ahead = weights_ahead(w, nw, scoring, off_[0].Wqkv, (int64_t)4 * d_ * d_, M, rp.rows);
     launch_ln_fwd(st, e);
     for (int l = 0; l < L_; ++l) {
@@ -204,15 +211,14 @@ class EncoderModel : public Model {
       g.res32 = last ? res_sel_ : res_[0]; g.C32 = pre1_[s];          // the residual stream stays fp32
       LnOff ln{};
       if (!last && !others_read(l - 1)) {
-        const int before = keep ? l - 1 : 0;
-        const float* const mean = l > 0 ? mean2_[before] : mean0_;
-        g.res32 = l > 0 ? pre2_[before] : pre0_; g.ln_mean = mean; g.ln_rstd = (int32_t)((l > 0 ? rstd2_[before] : rstd0_) - mean);
-        ln = l > 0 ? LnOff{off_[l - 1].ln2g, off_[l - 1].ln2b} : LnOff{eg_, eb_};
+        g.res32 = before.x; g.ln_mean = before.st.mean; g.ln_rstd = (int32_t)(before.st.rstd - before.st.mean);
+        ln = before.off;
       }
       fwd_linear(st, w, nw, last ? ao_sel_ : ao_[s], d_, o.Wo, d_, o.bo, rows, g, in_use, ln);
+      const RowStats s1 = keep ? RowStats{mean1_[s], rstd1_[s]} : passing(1), s2 = keep ? RowStats{mean2_[s], rstd2_[s]} : passing(0);
       LnFwdArgs n1{};
       n1.x = pre1_[s]; n1.pv = pv; n1.g_off = o.ln1g; n1.b_off = o.ln1b; n1.y = x1_[s]; n1.y32 = make_res ? nullptr : res_[1];
-      n1.mean = mean1_[s]; n1.rstd = rstd1_[s]; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
+      n1.mean = s1.mean; n1.rstd = s1.rstd; n1.M = nw * rows; n1.d = d_; n1.pass_rows = rows; n1.rows = in_use;
       n1.ahead = weights_ahead(w, nw, scoring, o.W1, (int64_t)2 * ffn_ * d_, rows, in_use);
       launch_ln_fwd(st, n1);
       g = GemmBf16Args{};
@@ -220,13 +226,14 @@ class EncoderModel : public Model {
       fwd_linear(st, w, nw, x1_[s], d_, o.W1, ffn_, o.b1, rows, g, in_use);
       g = GemmBf16Args{};
       g.res32 = res_[1]; g.C32 = pre2_[s];
-      if (make_res) { g.res32 = pre1_[s]; g.ln_mean = mean1_[s]; g.ln_rstd = (int32_t)(rstd1_[s] - mean1_[s]); }
+      if (make_res) { g.res32 = pre1_[s]; g.ln_mean = s1.mean; g.ln_rstd = (int32_t)(s1.rstd - s1.mean); }
       fwd_linear(st, w, nw, fact_[s], ffn_, o.W2, d_, o.b2, rows, g, in_use, {o.ln1g, o.ln1b});
       LnFwdArgs n2{};
       n2.x = pre2_[s]; n2.pv = pv; n2.g_off = o.ln2g; n2.b_off = o.ln2b; n2.y = xout; n2.y32 = others_read(l) ? res_[0] : nullptr;
-      n2.mean = mean2_[s]; n2.rstd = rstd2_[s]; n2.M = nw * rows; n2.d = d_; n2.pass_rows = rows; n2.rows = in_use;
+      n2.mean = s2.mean; n2.rstd = s2.rstd; n2.M = nw * rows; n2.d = d_; n2.pass_rows = rows; n2.rows = in_use;
       if (l + 1 < L_) n2.ahead = weights_ahead(w, nw, scoring, off_[l + 1].Wqkv, (int64_t)4 * d_ * d_, M, rp.rows);
       launch_ln_fwd(st, n2);
+      before = LnInput{pre2_[s], s2, {o.ln2g, o.ln2b}};
     }
     HeadView h{};                                   // position 0 of the fp32 output of the last LayerNorm
     h.x = res_[0]; h.stride = (int64_t)(sel.n > 0 ? SELECT_SEQ_ROWS : S_) * d_; h.pass_stride = (int64_t)(sel.n > 0 ? sel.n : M) * d_; h.k = d_;

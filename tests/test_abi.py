@@ -49,6 +49,19 @@ def test_layout_matches_datagen(lib, cfg):
     assert ng == sum(r * cc for n, o, r, cc in want if n.split(".")[-1] in ("Wqkv", "Wo", "W1", "W2") or (w["kind"] == "mlp" and n.startswith("W")))
 
 
+@pytest.mark.parametrize("kind,dims,batch,meta,aux,given", [
+    ("encoder", (1, 64, 1, 64, 64, 100, 2), 1, 1, {}, 2201344), ("encoder", (2, 192, 3, 320, 128, 600, 3), 5, 3, {}, 40659968),
+    ("encoder", (4, 256, 4, 1024, 128, 8192, 4), 32, 32, {}, 431997440), ("encoder", (12, 768, 12, 3072, 128, 30522, 6), 32, 32, {}, 5031641856),
+    ("encoder", (24, 1024, 16, 4096, 128, 50265, 2), 16, 16, {}, 12981743360),
+    ("encoder", (12, 768, 12, 3072, 256, 50304, 6), 16, 16, dict(aux_mlm=1, max_aux_batch=16, max_aux_masked=832), 8823574272),
+    ("mlp", (784, 256, 256, 10), 128, 128, {}, 7814656)])
+def test_a_workspace_that_was_large_enough_still_is(lib, kind, dims, batch, meta, aux, given):
+    """Callers allocate the workspace themselves and may have its size written down."""
+    import paper_2310_05674_amd as pkg
+    c = pkg.SamaConfig.make(kind, dims, H=4 if dims[1] == 64 else 100, max_batch=batch, max_meta_batch=meta, **aux)
+    assert lib.sama_workspace_bytes(C.byref(c)) <= given
+
+
 def test_masked_token_head_layout_and_limits(lib):
     import paper_2310_05674_amd as pkg
     from paper_2310_05674_amd.binding import param_tensors
