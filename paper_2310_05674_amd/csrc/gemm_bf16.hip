@@ -811,8 +811,8 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gemm_rows(GemmBatch batch) {
   const uint32_t share = small_quotient(ROWS_SHARES * in_use - 1, batch.first.M);   // 0 < in_use <= M
   switch ((uint32_t)(batch.choice >> (4 * share)) & 15) {
     case 1:
-      if constexpr (!LN) gemm_rows_tile<D1, B_KC, LN>(batch);   // (never chosen with LN)
-      return;
+      if constexpr (!LN) return gemm_rows_tile<D1, B_KC, LN>(batch);
+      [[fallthrough]];   // (with LN the host chooses the next one instead)
     case 2: return gemm_rows_tile<D2, B_KC, LN>(batch);
     case 4: return gemm_rows_tile<D4<B_KC>, B_KC, LN>(batch);
     default: return gemm_rows_tile<R5, B_KC, LN>(batch);
