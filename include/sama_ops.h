@@ -43,6 +43,15 @@ size_t sama_op_gelu_table_bytes(void);
 sama_status sama_op_gemm_bf16_gelu(const void* A, const void* B, const void* B2, int32_t b_trans, int32_t M, int32_t N, int32_t K,
                                    const void* aux16, void* pre16, float* C32, void* table, void* hip_stream);
 
+/* For tests: the residual epilogue of the encoder's hi + lo products, C32 = A . (B + B2)^T + bias + r, `count` (1 or 2) stacked passes of M rows
+ * (A, x and C32 [count * M] rows; B [N x K] shared, B2 [count][N x K]).  params: [3][N] bias, gain and shift; with v ([3][N]) and eps (DEVICE
+ * scalar), which go together, params + eps v in the first pass and params - eps v in the second.  stats NULL: r = x.  Else r is the LayerNorm's
+ * output gain (x - mean) rstd + shift, stats: [2][count * M] means, then reciprocal deviations.  rows: DEVICE count, or NULL: only the first *rows
+ * (at least 1, at most M) rows of each pass are computed, as in a padded batch. */
+sama_status sama_op_gemm_bf16_residual(int32_t count, const void* A, const void* B, const void* B2, int32_t M, int32_t N, int32_t K,
+                                       const float* params, const float* v, const float* eps, const float* x, const float* stats,
+                                       float* C32, const int32_t* rows, void* hip_stream);
+
 /* Base solver update, Adam form (Sec. 2; Kingma & Ba Alg. 1 with bias correction at step t >= 1), over n fp32
  * elements in place; theta16 (bf16 [n16], n16 <= n) receives the rounded leading part of theta, or NULL.  With
  * weight_decay != 0 the L2 term is added in front of the solver and g is overwritten with g + weight_decay * theta

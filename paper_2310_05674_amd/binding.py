@@ -106,6 +106,7 @@ def load_library():
     L.sama_op_gemm_bf16_batch.argtypes = [i32, vp, vp, vp, vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32), i32, i32, vp]
     L.sama_op_gelu_table_bytes.restype = C.c_size_t; L.sama_op_gelu_table_bytes.argtypes = []
     L.sama_op_gemm_bf16_gelu.restype = C.c_int; L.sama_op_gemm_bf16_gelu.argtypes = [vp, vp, vp, i32, i32, i32, i32, vp, vp, vp, vp, vp]
+    L.sama_op_gemm_bf16_residual.restype = C.c_int; L.sama_op_gemm_bf16_residual.argtypes = [i32, vp, vp, vp, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp]
     L.sama_set_lr.restype = C.c_int; L.sama_set_lr.argtypes = [vp, f32, f32]
     L.sama_eval.restype = C.c_int; L.sama_eval.argtypes = [vp, vp, vp, vp, vp]
     L.sama_aux_eval.restype = C.c_int; L.sama_aux_eval.argtypes = [vp, vp, vp, vp]
@@ -345,6 +346,16 @@ def op_gemm_bf16_gelu(A, B, B2, out32, *, b_trans=True, aux16=None, pre16=None):
     rc = L.sama_op_gemm_bf16_gelu(_p(A), _p(B), _p(B2), int(b_trans), M, out32.shape[1], K, _p(aux16), _p(pre16), _p(out32), _p(table), _stream())
     if rc != 0:
         raise SamaError(rc, "sama_op_gemm_bf16_gelu rejected the arguments")
+
+
+def op_gemm_bf16_residual(A, B, B2, params, x, out32, *, v=None, eps=None, stats=None, rows=None):
+    """For tests: a hi + lo product plus bias and residual through sama_op_gemm_bf16_residual.  A [passes, M, K], B [N, K], B2 [passes, N, K] bf16,
+    params and v [3, N], x and out32 [passes, M, N], stats [2, passes, M] or None, rows an int32 device tensor or None."""
+    n, M, K = A.shape
+    rc = load_library().sama_op_gemm_bf16_residual(n, _p(A), _p(B), _p(B2), M, B.shape[0], K, _p(params), _p(v), _p(eps), _p(x), _p(stats), _p(out32),
+                                                   _p(rows), _stream())
+    if rc != 0:
+        raise SamaError(rc, "sama_op_gemm_bf16_residual rejected the arguments")
 
 
 def op_adam(g, m, v, theta, theta16, n16, t, lr, beta1, beta2, eps, wd=0.0):

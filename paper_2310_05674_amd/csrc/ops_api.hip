@@ -97,6 +97,27 @@ sama_status sama_op_gemm_bf16_gelu(const void* A, const void* B, const void* B2,
   return hipGetLastError() == hipSuccess ? SAMA_OK : SAMA_EHIP;
 }
 
+sama_status sama_op_gemm_bf16_residual(int32_t count, const void* A, const void* B, const void* B2, int32_t M, int32_t N, int32_t K,
+                                       const float* params, const float* v, const float* eps, const float* x, const float* stats,
+                                       float* C32, const int32_t* rows, void* hip_stream) {
+  if (count < 1 || count > 2 || !A || !B || !B2 || !params || !x || !C32 || (v != nullptr) != (eps != nullptr)) return SAMA_EINVAL;
+  GemmBf16Args g[2];
+  for (int k = 0; k < count; ++k) {
+    const int64_t row0 = (int64_t)k * M;
+    g[k] = GemmBf16Args{};
+    g[k].A = (const bf16_t*)A + row0 * K; g[k].lda = K;
+    g[k].B = (const bf16_t*)B; g[k].B2 = (const bf16_t*)B2 + (int64_t)k * N * K; g[k].b_trans = 1; g[k].ldb = K;
+    g[k].M = M; g[k].N = N; g[k].K = K; g[k].ldc = N; g[k].rows = rows;
+    g[k].bias = params; g[k].bias_v = v; g[k].beps = eps; g[k].bsign = v ? (k == 0 ? 1.f : -1.f) : 0.f;
+    g[k].res32 = x + row0 * N; g[k].C32 = C32 + row0 * N;
+    if (stats) { g[k].ln_mean = stats + row0; g[k].ln_rstd = count * M; g[k].ln_g = N; g[k].ln_b = 2 * N; }
+  }
+  if (check_gemm_bf16_batch(g, count) != nullptr) return SAMA_EINVAL;
+  (void)hipGetLastError();
+  launch_gemm_bf16_batch((hipStream_t)hip_stream, g, count);
+  return hipGetLastError() == hipSuccess ? SAMA_OK : SAMA_EHIP;
+}
+
 sama_status sama_op_adam(float* g, float* m, float* v, float* theta, void* theta16, int64_t n, int64_t n16, int64_t t,
                          float lr, float beta1, float beta2, float eps, float weight_decay, void* hip_stream) {
   if (!g || !m || !v || !theta || n < 0 || n16 < 0 || n16 > n || t < 1) return SAMA_EINVAL;

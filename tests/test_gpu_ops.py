@@ -327,6 +327,49 @@ def test_gelu_of_every_bf16_value(K):
     assert torch.equal(got[16, "ragged", True].nan_to_num(7.0), got[16, "f", True][:200, :136].nan_to_num(7.0))
 
 
+@pytest.mark.parametrize("M,N", [(256, 384), (264, 200), (520, 328), (128, 96)])
+@pytest.mark.parametrize("passes,perturbed", [(1, False), (1, True), (2, True)])
+def test_residual_made_of_a_layernorms_input(M, N, passes, perturbed):
+    """The product that makes a LayerNorm's output and adds it against the one that is given that output, bit for bit: every hi + lo tile, whole and ragged
+    ones, one pass and two, perturbed parameters; and with part of the rows in use, the launches that choose their tile on the device."""
+    import ctypes
+    from paper_2310_05674_amd import binding as B
+    g = torch.Generator(device=DEV).manual_seed(M + 3 * N + passes)
+    randn = lambda *s: torch.randn(*s, device=DEV, generator=g)
+    K = 256
+    A, W, W2 = randn(passes, M, K).to(torch.bfloat16), randn(N, K).to(torch.bfloat16), (0.01 * randn(passes, N, K)).to(torch.bfloat16)
+    params, v, eps = randn(3, N), randn(3, N), torch.tensor([0.03], device=DEV)
+    x, stats = 3 * randn(passes, M, N), torch.stack([randn(passes, M), 0.5 + randn(passes, M).abs()]).contiguous()
+    fma = lambda a, b, c: (a.double() * b.double() + c.double()).float()   # (the product is exact)
+    kw = dict(v=v, eps=eps) if perturbed else {}
+    made = torch.empty_like(x)
+    for k in range(passes):
+        _, gain, shift = fma(eps if k == 0 else -eps, v, params) if perturbed else params
+        made[k] = fma((x[k] - stats[0, k][:, None]) * stats[1, k][:, None], gain[None], shift[None])
+    want = torch.empty_like(x)
+    B.op_gemm_bf16_residual(A, W, W2, params, made, want, **kw)
+    L = B.load_library()
+
+    def check(rows, what):
+        got = torch.full_like(x, 7.0)
+        used = None if rows is None else torch.tensor([rows], dtype=torch.int32, device=DEV)
+        B.op_gemm_bf16_residual(A, W, W2, params, x, got, stats=stats, rows=used, **kw)
+        assert torch.equal(got[:, :rows], want[:, :rows]), what
+        assert rows is None or (got[:, rows:] == 7).all(), what
+    try:
+        for shape in (0,) + tuple(range(11, 21)):
+            L.sama_dev_gemm_shape(ctypes.c_int32(shape))
+            check(None, shape)
+            check(M // 32 * 16, shape)
+        L.sama_dev_gemm_shape(ctypes.c_int32(0))
+        for choice in ("1", "2", "4", "5"):
+            assert L.sama_dev_gemm_rows(ctypes.c_uint64(int(choice * 16, 16))) == 0
+            for rows in sorted({16, 112, M // 32 * 16, M // 16 * 16} - {r for r in (16, 112) if r > M}):
+                check(rows, (choice, rows))
+    finally:
+        L.sama_dev_gemm_shape(ctypes.c_int32(0)); L.sama_dev_gemm_rows(ctypes.c_uint64(0))
+
+
 def test_gemm_rejects_unsupported_shapes():
     from paper_2310_05674_amd import binding as B
     A = torch.zeros((64, 96), dtype=torch.bfloat16, device=DEV); Bm = torch.zeros((64, 96), dtype=torch.bfloat16, device=DEV)
