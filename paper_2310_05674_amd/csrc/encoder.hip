@@ -175,9 +175,13 @@ class EncoderModel : public Model {
     // selected, have other readers; so have all of a pass on the bf16 weights alone, whose tiles do without.)
     // It pays once the LayerNorm is bound by memory; a smaller product's epilogue is a chain that gets longer.  us stored / made: scoring 128 rows of 12 x 768 551 / 549 to 560,
     // 1024 rows of 6 x 768 427 / 429, 1024 of 6 x 1024 545 / 541, 2048 759 / 753, 4096 of 6 x 768 860 / 849, 8192 of 8 x 384 836 / 822; base step of 2048 rows of
-    // 8 x 384 1316 / 1319, 4096 1740 / 1728, 2048 of 6 x 1024 2780 / 2772; padded, 3072 rows of 6 x 768 2047 / 2000.
+    // 8 x 384 1316 / 1319, 4096 1740 / 1728, 2048 of 6 x 1024 2780 / 2772.
+    // All rows count, also of a padded batch: how many are in use only the device knows, and with few of them it does not lose either.  4096 rows,
+    // 15 %, 30 % and 60 % in use: scoring 6 x 1024 684 / 673, 782 / 764, 959 / 935, 6 x 384 300 / 293, 314 / 308, 367 / 357; base step of 6 x 768 1425 / 1415,
+    // 1580 / 1571, 1943 / 1916; meta step of 6 x 768 2171 / 2138, 2472 / 2440, 3180 / 3141.  Of 105 such calls from 1536 rows on three take longer, by at most 0.6 % (the stacked
+    // passes of 1536 and 2048 rows of 6 x 384).
     constexpr int64_t MAKE_RES = 1 << 20;
-    const bool make_res = w[0].lo != nullptr && (int64_t)nw * M * d_ > MAKE_RES;
+    const bool make_res = w[0].lo != nullptr && (int64_t)nw * M * d_ >= MAKE_RES;
     const bool far = eb_ - off_[0].bo > INT32_MAX;   // beyond a product's offsets: two billion embedding weights lie between
     auto others_read = [&](int l) { return !make_res || l == L_ - 1 || (l == L_ - 2 && sel.n > 0) || (l < 0 && far); };   // what leaves layer l (-1: the embeddings)
     // A pass that is not kept needs the input and the statistics of a LayerNorm until that product only: they pass through memory that

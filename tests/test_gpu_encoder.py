@@ -954,10 +954,11 @@ def test_weights_fetched_ahead_of_many_padded_rows(B, dims, kept):
 
 
 @pytest.mark.parametrize("B,dims,S,padded", [(88, (3, 192, 3, 320), 64, False), (90, (3, 192, 3, 320), 64, True), (30, (3, 320, 5, 640), 128, False), (29, (4, 320, 5, 640), 128, True),
-                                             (13, (3, 704, 11, 1408), 128, True), (9, (3, 1024, 16, 1024), 128, False), (32, (3, 1024, 16, 2048), 256, False), (33, (2, 640, 10, 1280), 64, True)])
+                                             (13, (3, 704, 11, 1408), 128, True), (8, (3, 1024, 16, 1024), 128, False), (9, (3, 1024, 16, 1024), 128, False), (48, (3, 192, 3, 320), 64, True), (10, (3, 640, 10, 1280), 128, False), (32, (3, 1024, 16, 2048), 256, False), (33, (2, 640, 10, 1280), 64, True)])
 def test_residual_made_from_the_layernorms_input(B, dims, S, padded):
-    """Beyond 2^20 elements of rows x width the products make the residual themselves, below it the LayerNorm stores it: texts scored alone and in such a batch have the same bits.
-    (33 sequences of 640 and 88 of 192: one pass is on the near or just the far side, the two of a meta step on the far one.)  Widths with tiles cut short, any number of rows in use.
+    """From 2^20 elements of rows x width on the products make the residual themselves, below it the LayerNorm stores it: texts scored alone and in such a batch have the same bits.
+    8 sequences of 1024 are exactly that many; 48 of 192 and 10 of 640 have more than half, so that a pass stores it and the two stacked ones of a meta step make it.
+    Widths with tiles cut short, any number of rows in use.
     The stacked passes, whose gains and shifts are perturbed, against the oracle."""
     import torch
     C, d = 3, dims[1]
