@@ -514,20 +514,21 @@ __global__ __launch_bounds__(AttnFwd<NT>::THREADS, AttnFwd<NT>::PER_SIMD) void k
 // A workgroup (blockIdx.z) forms one of the three, or (PARTS 2) dQ or the other two: it stages the two matrices it walks over, and
 // its waves hold the rows of their own tile and 32 or 64 accumulators.  Bound by the latency of a tile's chain (LDS, product,
 // exponentials, product) and by the requests for the rows it stages and holds.
-//   Three parts: the scores are formed three times instead of twice, but 3 to 4 workgroups share a CU (35 KB of LDS at S = 128, at most
-//   128 registers; 2 of eight waves at S = 256, with 68 KB) where one that formed all three, with 64 KB, had it alone.
-//   (The times of these two paragraphs are of kernels whose masked forms branched around each exponential and each piece that was staged, and
-//   requested the pieces one by one: 384 heads of 128 positions 21.7 -> 18.0 us, padded 21.9 -> 14.6, 256 heads 16.6 -> 13.5, 228 padded of 256 28.8 -> 21.7.)
-//   Two parts: a round of three workgroups to a CU instead of four, with a longer chain each (12 heads of S = 128: 9.8 us against
-//   6.8), so only once there are more heads than CUs: S = 128, 384 heads 18.6 us against 19.1 and, padded, 17.5 against 20.7;
-//   1024 heads 50.3 against 53.3, padded 36.7 against 39.1.  256 heads 13.7 against 12.2, 128 10.8 against 8.6.  At S = 64 the two are
-//   equal; at S = 256 the registers leave one workgroup to a CU (padded 52 against 47 us).
+//   Three parts: the scores are formed three times instead of twice, but 4 workgroups share a CU (35 KB of LDS at S = 128, 128
+//   registers; 2 of eight waves at S = 256, with 68 KB) where one that formed all three, with 64 KB, had it alone.
+//   Two parts: a round of three workgroups to a CU instead of four, with a longer chain each, so only once there are more heads than CUs.  us two / three,
+//   heads of 128 positions: 60 9.8 / 7.4, 192 12.8 / 11.8, 252 14.7 / 14.5, 324 17.2 / 17.3, 512 24.0 / 25.7, 1024 49.1 / 54.5; padded 60 8.7 / 8.0, 132 9.6 / 9.2, 252 11.9 /
+//   12.8, 384 14.3 / 14.7, 1024 34.1 / 37.0.  At S = 64 the two were equal; at S = 256 the registers left one workgroup to a CU (padded 52 against 47 us).
+// No form keeps anything in scratch: of the rows' values four are read at a time, the lane is found anew behind the loops, and S = 64 has three waves to a
+// SIMD and 130 registers (padded, with 128 and 20 bytes of scratch, 768 heads 13.7 / 12.1 us, 1536 25.3 / 23.5).
+// All staged rows are requested at once and masks take no branch around exponentials and pieces: 384 heads of 128 positions 21.7 -> 18.0 us, padded 21.9 -> 14.6,
+// 256 heads 16.6 -> 13.5, 228 padded of 256 28.8 -> 21.7.  (The times below are of kernels before that.)
 // A wave has one tile and no loop around it: with one, the padded forms kept lane masks and eight-wave forms values across it in
 // scratch (384 heads, S = 128 padded 22.0 -> 20.7 us; S = 256 52 -> 48 us, padded 52 -> 47 us).
 // The own rows and D's are fetched behind the staged ones, whose lines they share: ahead of them, with 2 or 32 lines to an
 // instruction each, they held those up (384 heads 20.8 -> 24.4 us).
 template <int NT, bool PADDED, int PARTS>
-__global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
+__global__ __launch_bounds__(64 * NT, PARTS == 2 || NT == 2 ? 3 : 4) void k_attn_bwd(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out,
                                                                       const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                                       bf16_t* __restrict__ dqkv, int heads, int d, const int32_t* __restrict__ lens,
                                                                       RowPlan plan, int B) {
@@ -654,15 +655,16 @@ __global__ __launch_bounds__(64 * NT, PARTS == 2 ? 3 : 4) void k_attn_bwd(const 
       accumulate(g, s_r, qt, dp);
     }
   }
-  if (PADDED && part != DQ && col >= len) {                      // a key without weight
+  const int lane_now = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), col_now = 32 * own + (lane_now & 31);   // not kept over the loops
+  if (PADDED && part != DQ && col_now >= len) {                  // a key without weight
 #pragma unroll
     for (int et = 0; et < 2; ++et)
 #pragma unroll
       for (int r = 0; r < 16; ++r) g[et][r] = gv[et][r] = 0.f;
   }
-  if (PADDED && col >= kept) return;
+  if (PADDED && col_now >= kept) return;
   auto store = [&](const f32x16 (&g)[2], int to) {   // to: where the result goes among the columns of dqkv
-    store_row(g, dqkv + ((int64_t)sr.row0 + col) * ld + to + h * AD, lane);
+    store_row(g, dqkv + ((int64_t)sr.row0 + col_now) * ld + to + h * AD, lane_now);
   };
   store(g, part == DQ ? 0 : (part == DK ? d : 2 * d));
   if (PARTS == 2 && part != DQ) store(gv, 2 * d);
