@@ -24,7 +24,8 @@ constexpr int EW_TRIP = EW_U * EW_THREADS;   // vectors per block per trip
 // SGD 2.83 / 2.42, 3.41 / 2.72, 2.94 / 2.78, 3.15 / 3.38; the nudge 2.78 / 2.41, 2.91 / 2.49, 2.74 / 2.53, 3.11 / 2.86.
 constexpr int64_t EW_FEW = 1 << 19;
 // The adaptation's blocks of a quarter of the vectors would be four times as many partials and tickets (below): its blocks have four times the
-// threads instead, but for a single block, which takes no longer with four vectors a thread.  us, four / one: 269 thousand 9.0 / 6.1, 786 thousand 6.5 / 5.1.
+// threads instead, but for a single block, which takes no longer with four vectors a thread.  us, four / one: 8 thousand 4.8 / 3.9, 269 thousand 5.6 / 4.7,
+// 524 thousand 6.0 / 5.0, 2^20 6.7 / 5.7.
 constexpr int64_t ADAPT_FEW = 1 << 20;
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
@@ -220,8 +221,7 @@ __global__ __launch_bounds__(EW_TRIP / U) void k_adapt_norm(const float* __restr
   const int64_t nv = n / EW_VEC, trip = (int64_t)gridDim.x * EW_TRIP;
   float acc = 0.f;
   auto add_squares = [&](f4 o) { acc = fmaf(o.x, o.x, acc); acc = fmaf(o.y, o.y, acc); acc = fmaf(o.z, o.z, acc); acc = fmaf(o.w, o.w, acc); };
-  for (int64_t first = (int64_t)blockIdx.x * EW_TRIP; first < nv; first += trip) {
-    const int64_t base = first + threadIdx.x;
+  for (int64_t base = (int64_t)blockIdx.x * EW_TRIP + threadIdx.x; (SHARED ? base - threadIdx.x : base) < nv; base += trip) {   // a block that shares turns as one
     f4 G[U], M[U], V[U], Q[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
