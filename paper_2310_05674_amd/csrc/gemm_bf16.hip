@@ -824,10 +824,10 @@ __global__ __launch_bounds__(ROWS_THREADS) void k_gemm_rows(GemmBatch batch) {
 // on every CU and, where two fit, `two` as soon as some CU holds two and `all` when every one does; in between in proportion.
 // The numbers are robust least-squares fits of the logarithms over timed problems (widths 192 to 2048, FFN 2 and 4 times that,
 // 64 to 8192 rows: NT, NN, pairs of NT, a layer's four TN problems in a launch; the vocabulary head's products over 8192 to
-// 50304 tokens; weights cold): HILO_NN of the kernels before their tiles were cut for fewer LDS reads (2 to 11% longer), SINGLE and HILO of still earlier ones (32 x 32 x 16 MFMAs, the epilogue through LDS), which took 1.3
+// 50304 tokens; weights cold): HILO_NN of the kernels before 128 x 128 and 128 x 64 tiles were cut into 64 x 32 waves (up to 2% longer), SINGLE and HILO of still earlier ones (32 x 32 x 16 MFMAs, the epilogue through LDS), which took 1.3
 // to 1.5 times as long; HILO's last entry was set by hand beside the one before it.  On times of the former, picking by them takes
 // 0.4% (NT), 0.3% (pairs), 0.5% (NN) and 0.5% (TN) longer in total than the fastest tile of each problem, the head's products 1 to 2%; by
-// HILO for NN too, NN takes 2.6% and the head's NN 7%: profiles/gemm_tile_costs.md.
+// HILO for NN too, NN takes 2.6% and the head's NN 7%.  On times of the present kernels it is 0.8% (NT), 0.7% (pairs) and 1.3% (NN): profiles/gemm_tile_costs.md.
 struct TileCost { int id, bm, bn, per_cu; double few, one, two, all, epilogue; int bk = 64; };
 constexpr TileCost SINGLE[] = {
     {1, 256, 256, 1, 1.282, 1.816, 0, 0, 8.26}, {2, 256, 192, 1, 1.060, 1.218, 0, 0, 8.62},

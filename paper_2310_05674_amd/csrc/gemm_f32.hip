@@ -8,7 +8,8 @@
 // contraction between them in interleaved chunks of 16 and fetch their operands from global memory straight into the
 // MFMA operand layout (lane (r, q) holds row r and the four contraction indices 4q .. 4q+3 of a chunk) -- no LDS staging, no
 // barrier inside the loop, FDEPTH chunks of loads in flight ahead of the MFMAs.  The eight partial tiles are added in wave order
-// through LDS, so the result does not depend on timing.
+// through LDS, so the result does not depend on timing.  Forward products that fill the chip have no chain to shorten; they go through
+// LDS, a wave with the whole contraction (k_gemm_f32_lds), and add in the same order.
 // Loads are as wide as the storage allows, whatever the alignment (gfx950 takes a 16-byte load at any float): along the
 // contraction index 16 bytes, across the rows the two or four that a lane's tiles need of one index; and the loop has
 // no branches that depend on the operands' edges: rows are clamped, and the chunk that is not whole is apart.  us for rows x
@@ -490,12 +491,16 @@ void launch(hipStream_t st, const GemmF32Args* a, int count, const BaseUpdate* u
   // The smallest tile gives the shortest chain and the most workgroups, but reads every operand row once per 16 columns.  us, 16 x 16 /
   // 32 x 32: 256 tiles of 16 x 16 (512 x 128 x 784) 5.4 / 8.7, 512 (512 x 256 x 784) 8.1 / 8.8, 640 (512 x 320 x 1024) 14.5 / 11.0;
   // 32 x 32 / 64 x 32: 256 tiles of 32 x 32 (1024 x 256 x 784) 9.0 / 14.3, 320 (a weight gradient over 512 rows, 320 x 1024)
-  // 11.7 / 9.4, 512 (2048 x 256 x 784) 16.0 / 14.9.  Over 150 products and pairs (16 to 2048 rows, widths to 320, K to 1024) these
+  // 11.7 / 9.4.  Over 150 products and pairs (16 to 2048 rows, widths to 320, K to 1024) these
   // lines take 1.4% longer than the fastest tile of each, lines at 256 and 256 3.9% (geometric means).
+  // The line at 256 holds for k_gemm_f32_lds too.  Up to it (56 forward products of 160 to 256 tiles of 32 x 32, K from 64 to 1024) that takes 5 to 30% longer than
+  // 32 x 32: 1024 x 256 x 64 4.3 / 4.5, x 256 5.8 / 6.6, x 784 10.0 / 12.6.  Beyond (72 products) it takes 3 to 30% less than 64 x 32 with the contraction
+  // split: 1536 x 192 x 64 5.1 / 4.6, x 191 8.0 / 6.7, x 784 14.9 / 13.4, 2048 x 130 x 64 5.1 / 4.3, 2048 x 320 x 1024 31.1 / 23.2.
   constexpr int CUS = 256;
   if (tiles(a, count, 16, 16) <= 2 * CUS) launch_tile_f32<1, 1, 8>(ps, st, a, count, u);
   else if (tiles(a, count, 32, 32) <= CUS) launch_tile_f32<2, 2, 4>(ps, st, a, count, u);
-  // (the first slab has to be a whole one; gates and perturbed weights belong to products that do not fill the chip)
+  // (the first slab has to be a whole one; the pair of a perturbed forward pass, which large batches have, stays with the tile whose waves
+  // form theta +- eps v as they load, and a gate belongs to a gradient)
   else if (count == 1 && storage_of(a[0]) == F32_FORWARD && a[0].Bv == nullptr && a[0].gate == nullptr && a[0].K >= LDS_K) {
     const int blocks = (int)(tiles(a, 1, LDS_M, LDS_N) + 7) / 8 * 8;
     launch_kernel(ps, k_gemm_f32_lds, blocks, 256, 0, st, a[0], blocks);
