@@ -433,7 +433,7 @@ __device__ __forceinline__ void zero_tail(const RowPlan& plan, int B, bf16_t* __
 // waits for another, masks without branches, stores of 16 bytes, and 128 registers, which let four workgroups share a CU.
 // A probability is divided by the row's sum and then rounded to bf16, and a tile's products are added eight keys at a time.  (Divided after the product, by
 // the sum of the rounded ones, with 32x32x16 products and one multiply-add for a score, the kernels are 3% faster and the hypergradients of
-// deep encoders others: 2% to 7% in the worst of a dozen, most 0.1%.)
+// deep encoders others: 2% to 10% in the worst of two dozen, most below 0.2%.)
 // With a loop over the tiles of a wave, even one that never turns, the 16 NT comparisons of keys with the length are kept as lane
 // masks across it, hundreds of scalar registers of which most spill.
 template <int NT> struct AttnFwd { static constexpr int WAVES = NT < 8 ? 4 : 8, THREADS = 64 * WAVES, PER_SIMD = NT < 8 ? 4 : 2; };

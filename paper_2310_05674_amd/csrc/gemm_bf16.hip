@@ -24,7 +24,7 @@
 //
 // For the theta +- eps v passes of Eq. 5 and the direct-gradient pass the weight operand is hi + lo (two bf16
 // halves).  DUAL tiles stage the A slab once together with the hi and the lo slab of B, and an MFMA contracts 16 values of A with those of hi,
-// then with those of lo.  That order of the sums is kept: a hypergradient, a difference of two nearly equal gradients, has moved by up to 7% of its
+// then with those of lo.  That order of the sums is kept: a hypergradient, a difference of two nearly equal gradients, has moved by up to 10% of its
 // size where it was given up.  It costs a second read of every fragment of A from LDS: with 32 values of hi and then 32 of lo, which needs none,
 // products take 0.5% (256 x 192 tiles) to 5% (input gradients, 128 x 64) less.  Read once and doubled in registers (v_permlane32_swap) they
 // take longer: scoring 8192 rows of 24 x 1024 9.41 ms, this way 8.88.
